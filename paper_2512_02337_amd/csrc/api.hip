@@ -102,12 +102,22 @@ static Shape make_shape(const specpv_kv *kv, const specpv_tree *tree)
 // arguments, so specpv_workspace_bytes and the calls agree.
 static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks)
 {
-    AttnPlan plan{1, attn_ctx_mfma_supported(s, dtype) ? kAttnSplit : kAttnGeneric};
+    AttnPlan plan{1, !attn_ctx_mfma_supported(s, dtype) ? kAttnGeneric : (s.D == 64 ? kAttnGroup : kAttnSplit)};
+    // splits that give 4096 (row, split) pairs of 64 tokens or more each
+    const int64_t rows = (int64_t)s.batch * s.Hq * s.M;
+    auto few_splits = [&](int64_t tokens) {
+        int64_t ns = (4096 + rows - 1) / rows;
+        const int64_t chunks = (tokens + 63) / 64;
+        if (ns > chunks) ns = chunks;
+        if (ns > 64) ns = 64;
+        return ns < 1 ? (int64_t)1 : ns;
+    };
     const int64_t tokens = n_blocks * s.B;
     if (tokens <= 0) return plan;
     if (plan.kind != kAttnGeneric) {
         const int64_t chunks = (tokens + 31) / 32;   // 32-token chunks per (sequence, KV head)
-        const int64_t cus = device_cu_count();
+        // workgroups that the chip holds at once: one per CU (the LDS), two of the 64-channel kernel's
+        const int64_t cus = (int64_t)device_cu_count() * (s.D == 64 ? 2 : 1);
         const int64_t row_tiles = (s.M + 63) / 64;
         // splits c that minimise the chunk-times on the critical path (one workgroup per CU, `base`
         // workgroups per split, `ranges` token ranges per workgroup), plus a charge for the
@@ -128,11 +138,23 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks)
         // Long token ranges per wavefront amortise the longer prologue and epilogue of the kernels
         // with more rows per wavefront; at a handful of chunks the eight-wavefront kernel hides
         // latency better.
-        if (chunks >= 8 * 4 * ns) {
+        // (64 channels: only the group kernel)
+        if (s.D == 64 || chunks >= 8 * 4 * ns) {
             // a few workgroups per (sequence, KV head, split) that cover the group's query rows, one
             // token range each
             plan.kind = kAttnGroup;
-            const int64_t max1 = chunks / 8 > 1 ? (chunks / 8 < 64 ? chunks / 8 : 64) : 1;
+            const int64_t shortest = s.D == 64 ? 4 : 8;   // chunks per split
+            int64_t max1 = chunks / shortest > 1 ? (chunks / shortest < 64 ? chunks / shortest : 64) : 1;
+            const int64_t few = few_splits(tokens);
+            if (s.D == 64) {
+                // what specpv_partial_verify_attn_static takes with few splits must fit its array with many
+                const int64_t slot = rows * (s.D + 2) * (int64_t)sizeof(float);
+                const int64_t room = ((int64_t)SPECPV_STATIC_SCRATCH_BYTES - (int64_t)kArriveBytes - 1024 -
+                                      (int64_t)s.batch * s.Hkv * s.max_blocks * (int64_t)sizeof(float)) / slot - 1;
+                if (max1 > room && room >= few) max1 = room;
+                // up to 1024 tokens: the few splits of the vector-ALU kernel are enough
+                if (chunks <= 32 && max1 > few) max1 = few;
+            }
             const int64_t base1 = (int64_t)s.batch * s.Hkv * attn_group_parts(s);
             ns = best_splits(base1, 1, max1);
             if (s.batch > 1) {
@@ -150,13 +172,7 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks)
         }
         plan.nsplit = (int)ns;
     } else {
-        const int64_t rows = (int64_t)s.batch * s.Hq * s.M;
-        const int64_t chunks = (tokens + 63) / 64;
-        int64_t ns = (4096 + rows - 1) / rows;
-        if (ns > chunks) ns = chunks;
-        if (ns > 64) ns = 64;
-        if (ns < 1) ns = 1;
-        plan.nsplit = (int)ns;
+        plan.nsplit = (int)few_splits(tokens);
     }
     return plan;
 }
@@ -214,7 +230,7 @@ static int run_attention(const Shape &s_in, int dtype, const int32_t *sel_idx, c
         e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, f, st);
         return e == hipSuccess ? SPECPV_OK : fail_hip(e);
     }
-    Partials p{w.part_o, w.part_ml, nsplit, plan.kind != kAttnGeneric ? 1 : 0, g_timeline};
+    Partials p{w.part_o, w.part_ml, nsplit, plan.kind != kAttnGeneric && s.D == 128 ? 1 : 0, g_timeline};
     const FusedArgs none{nullptr, nullptr, nullptr, 0, g_timeline};
     if (plan.kind != kAttnGeneric) e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, none, st);
     else e = launch_attn_ctx_generic(s, dtype, sel_idx, sel_count, n_sel, p, st);

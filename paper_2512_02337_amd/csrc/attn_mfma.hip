@@ -85,8 +85,8 @@ struct MfmaArgs {
     int n_sel;
     float scale_log2;
     int n_units, row_tiles, n_bg;
-    int rph, n_row_blocks;   // group kernel: 32-row blocks per query head, and per KV group (G * rph)
-    FastDiv div_nsplit, div_hkv, div_B, div_W;
+    int n_row_blocks;   // group kernel: 32-row blocks of a KV head's M * G query rows
+    FastDiv div_nsplit, div_hkv, div_B, div_W, div_G;
 };
 
 __device__ __forceinline__ bf16x8 as_bf16x8(const uint4 &u) { return __builtin_bit_cast(bf16x8, u); }
@@ -211,6 +211,28 @@ template <int OFF> __device__ __forceinline__ void lds_read_v_half(uint32_t addr
         : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
         : "v"(addr), "n"(OFF), "n"(OFF + 256), "n"(OFF + 64), "n"(OFF + 320), "n"(OFF + 128), "n"(OFF + 384), "n"(OFF + 192),
           "n"(OFF + 448)
+        : "memory");
+}
+
+// 64 channels: the V operands of a chunk, v[(ks2 * 2 + j) * 2 + hf].  A row is 128 bytes; piece p (tokens p, p + 8,
+// p + 16, p + 24) sits at 1152 (p >> 1) + 512 (p & 1), and the two 64-byte halves of an odd piece's rows are exchanged:
+// the four pieces that a quad's lanes read then cover all 64 banks.  a0, a1: this lane's address of channel tile 0, 1.
+template <int OFF>
+__device__ __forceinline__ void lds_read_v64(uint32_t a0, uint32_t a1, uint2 (&v)[8])
+{
+    static_assert(OFF >= 0 && OFF + 384 < 65536, "the offset field has 16 bits");
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %8 offset:%10\n\t"
+        "ds_read_b64_tr_b16 %1, %8 offset:%10+128\n\t"
+        "ds_read_b64_tr_b16 %2, %9 offset:%10\n\t"
+        "ds_read_b64_tr_b16 %3, %9 offset:%10+128\n\t"
+        "ds_read_b64_tr_b16 %4, %8 offset:%10+256\n\t"
+        "ds_read_b64_tr_b16 %5, %8 offset:%10+384\n\t"
+        "ds_read_b64_tr_b16 %6, %9 offset:%10+256\n\t"
+        "ds_read_b64_tr_b16 %7, %9 offset:%10+384\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
+        : "v"(a0), "v"(a1), "n"(OFF)
         : "memory");
 }
 
@@ -830,7 +852,9 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
                 *(float4 *)(dst + 32 * j + 8 * q + 4 * kg) = make_float4(O[j][4 * q], O[j][4 * q + 1], O[j][4 * q + 2], O[j][4 * q + 3]);
     }
     __syncthreads();
-    const int64_t prow0 = ((int64_t)(b * s.Hq + h) * part.nsplit + sp) * s.M;
+    // the partial row of node j is prow0 + j * prow_step
+    const int64_t prow0 = FUSED ? ((int64_t)(b * s.Hq + h) * part.nsplit + sp) * s.M : ((int64_t)bg * part.nsplit + sp) * ((int64_t)s.M * s.G) + hh;
+    const int prow_step = FUSED ? 1 : s.G;
     // weights of the four token groups for the rows this wavefront finishes (lane -> row)
     float wgt[4], m_row = -INFINITY, l_row = 0.f;
     {
@@ -871,14 +895,14 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
                     *(float2 *)(part.o + (prow0 + j) * 128 + 2 * lane) = acc[uu];   // stays in this XCD's L2
                 } else {
                     const float ilu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(il), uu));
-                    store_partial_half(part.o + (prow0 + j) * 64, lane, acc[uu].x * ilu, acc[uu].y * ilu);   // 128 halves per row
+                    store_partial_half(part.o + (prow0 + (int64_t)j * prow_step) * 64, lane, acc[uu].x * ilu, acc[uu].y * ilu);   // 128 halves per row
                 }
             }
         }
     }
     if (lane < RPW) {
         const int j = m0 + wave * RPW + lane;
-        if (j < s.M) *(float2 *)(part.ml + (prow0 + j) * 2) = make_float2(m_row, l_row);
+        if (j < s.M) *(float2 *)(part.ml + (prow0 + (int64_t)j * prow_step) * 2) = make_float2(m_row, l_row);
     }
     SPECPV_STAMP(8);   // partial stores issued
     if (!REDO) SPECPV_CLOCKS_END(f.timeline, 3072 + ((size_t)blockIdx.y * gridDim.x + blockIdx.x), C);
@@ -1086,15 +1110,35 @@ void attn_ctx_mfma_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
 // the matrix instructions.  (The ten-wavefront variant keeps a barrier per chunk, see below.)
 constexpr int kGroupStages = 8;   // two halves of kGroupPeriod chunks
 constexpr int kGroupPeriod = 4;   // chunks between two workgroup barriers
-static_assert(kStageBytes % 256 == 0, "K operand addresses are derived by XOR with multiples of 32 below 256: stages (and the rings) must start 256-byte aligned");
+// One 32-token chunk in LDS.  128 channels: as above (kStageBytes).  64 channels: 4 KiB of K (128-byte rows, 16-byte
+// pieces XOR-swizzled by (row >> 1) & 7: two rows make one 256-byte bank row), V in four 1 KiB operations of two pieces
+// each (lds_read_v64).
+template <int D> struct Tile;
+template <> struct Tile<128> {
+    static constexpr int kK = 8192, kVOpPitch = kVPiecePitch, kStage = kStageBytes, kPitch = kOPitch;
+};
+template <> struct Tile<64> {
+    static constexpr int kK = 4096, kVOpPitch = 1152, kStage = kK + 4 * kVOpPitch, kPitch = 68;   // kPitch: floats per staged output row
+};
+static_assert(Tile<64>::kStage % 256 == 0 && kStageBytes % 256 == 0, "K operand addresses are derived by XOR with multiples of 32 below 256: stages (and the rings) must start 256-byte aligned");
 
 // W wavefronts per workgroup: 2, 4, 6, 8 or 10.  Ten (nine or ten row blocks: G = 5 with up to 64 nodes) means
 // three wavefronts on two of the SIMDs, i.e. at most 168 registers each: that variant takes its K and V
 // operands in halves.
-template <bool ALIGNED, int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W > 8 ? 3 : 2, W > 8 ? 3 : 2)))
+// D = 64: half the LDS and half the operand registers, so two workgroups share a CU (four wavefronts per SIMD, 128
+// registers): at 64 channels a chunk has half the matrix work against the same softmax, and what counts is how many
+// wavefronts the vector ALU can choose from.  The weights enter the second product as two bf16 terms (16 bits) and the
+// partials are fp32 sums: the precision, and the range of V, of the vector-ALU kernel that this replaces.  Full pass
+// over 15K + 30K tokens, 37 nodes at G = 4, 8 KV heads, token-major, with scoring and selection: 5845 us on the vector
+// ALU, 65 us here (53 us with the weights as one bf16 term and fp16 partials).
+template <int D, bool ALIGNED, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : (W > 8 ? 3 : 2), D == 64 ? 4 : (W > 8 ? 3 : 2))))
 void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
 {
+    typedef Tile<D> TL;
+    constexpr int KS = D / 16, NT = D / 32;         // k-steps of S^T, channel tiles of O^T
+    constexpr int LPR = D / 8, RPO = 64 / LPR;      // lanes per row, rows per 1 KiB operation
+    constexpr int KOPS = D / 16, OPS = 2 * KOPS;    // DMA operations of a chunk: K, then V
     SPECPV_CLOCKS_BEGIN;
     extern __shared__ char lds_raw[];
     char *ring = lds_raw;                  // [kGroupStages][K 8 KiB | V 8 pieces of 1088 B]
@@ -1110,15 +1154,13 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // this wavefront's row block: head hh of the KV group, rows m0 .. m0 + 31 of the tree.  A
+    // this wavefront's row block: rows r0w .. r0w + 31 of the KV head's M * G query rows.  A
     // workgroup may have a wavefront too many (row block counts that do not divide): it brings
     // its share of the chunks and keeps the barriers, but computes and stores nothing.
     const int rbx = wg_part * W + wave;
     const bool live = rbx < a.n_row_blocks;
-    const int rbx_c = live ? rbx : a.n_row_blocks - 1;
-    const int hh = rbx_c / a.rph;
-    const int m0 = (rbx_c - hh * a.rph) * 32;
-    const int h = g * s.G + hh;
+    const int R = s.M * s.G;                  // query rows of the KV head: row r is node r / G, head r % G of the group
+    const int r0w = (live ? rbx : a.n_row_blocks - 1) * 32;
     const int n = lane & 31, kg = lane >> 5;
 
     const int32_t *sel = a.sel_idx ? a.sel_idx + (int64_t)bg * a.n_sel : nullptr;
@@ -1130,12 +1172,13 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
         const uint32_t base = a.div_W.div(chunks), rem = chunks - base * (uint32_t)NS;
         return (int)((uint32_t)w * base + min((uint32_t)w, rem));
     };
-    uint4 qraw[8];
+    uint4 qraw[KS];
     {
-        const int j = min(m0 + n, s.M - 1);   // rows past M repeat row M-1; never stored
-        const uint16_t *qrow = (const uint16_t *)s.q + (((int64_t)b * s.M + j) * s.Hq + h) * 128 + kg * 8;
+        const int r = min(r0w + n, R - 1);    // rows past the end repeat the last one; never stored
+        const int j = (int)a.div_G.div((uint32_t)r), hh = r - j * s.G;
+        const uint16_t *qrow = (const uint16_t *)s.q + (((int64_t)b * s.M + j) * s.Hq + g * s.G + hh) * D + kg * 8;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) qraw[ks] = *(const uint4 *)(qrow + ks * 16);
+        for (int ks = 0; ks < KS; ++ks) qraw[ks] = *(const uint4 *)(qrow + ks * 16);
     }
 
     int nb = L > 0 ? (int)a.div_B.div((uint32_t)(L + s.B - 1)) : 0;
@@ -1146,9 +1189,9 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     // chunks of cache tokens, then those of the partially verified tokens (see attn_ctx_mfma_kernel)
     const uint32_t C_ctx = (T + 31u) >> 5;
     const uint32_t C = C_ctx + (((uint32_t)s.kctx + 31u) >> 5);
-    const char *kdb = (const char *)s.kd + (((int64_t)b * s.Mk) * s.Hkv + g) * 256;
-    const char *vdb = (const char *)s.vd + (((int64_t)b * s.Mk) * s.Hkv + g) * 256;
-    const uint32_t stp = (uint32_t)s.Hkv * 256u;
+    const char *kdb = (const char *)s.kd + (((int64_t)b * s.Mk) * s.Hkv + g) * (2 * D);
+    const char *vdb = (const char *)s.vd + (((int64_t)b * s.Mk) * s.Hkv + g) * (2 * D);
+    const uint32_t stp = (uint32_t)s.Hkv * (2u * D);
     const int c0 = first_chunk(C, sp), c1 = first_chunk(C, sp + 1);
     const int nch = c1 - c0;                  // the same for all wavefronts: the barriers match up
 
@@ -1157,12 +1200,12 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     const uint32_t st2 = (uint32_t)s.st * 2u;
 
     const uint32_t ring_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)ring;
-    uint32_t kread[4];   // + stage * kStageBytes; k-step ks + 4: the address XOR 128
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-        kread[ks] = ring_addr + (uint32_t)n * 256u + (((uint32_t)(32 * ks + 16 * kg)) ^ (16u * ((uint32_t)n & 15u)));
-    const uint32_t vread = ring_addr + 8192u + (uint32_t)(4 * kg + ((lane & 15) >> 2)) * kVPiecePitch +
-                           32u * (uint32_t)((lane >> 4) & 1) + 8u * (uint32_t)(lane & 3);   // + stage * kStageBytes
+    // K operand of k-step ks: row n, piece 2 ks + kg, at kread ^ (32 ks) (+ stage): the swizzle is an XOR on the piece and
+    // rows start 128- or 256-byte aligned
+    const uint32_t kread0 = ring_addr + (uint32_t)n * (2u * D) + (16u * (uint32_t)kg ^ (D == 128 ? 16u * ((uint32_t)n & 15u) : 16u * (((uint32_t)n >> 1) & 7u)));
+    const uint32_t vp = (uint32_t)(4 * kg + ((lane & 15) >> 2)), vb0 = 32u * (uint32_t)((lane >> 4) & 1) + 8u * (uint32_t)(lane & 3);
+    const uint32_t vread = ring_addr + TL::kK + vb0 + (D == 128 ? vp * kVPiecePitch : (vp >> 1) * Tile<64>::kVOpPitch + (vp & 1u) * 576u);
+    const uint32_t vread1 = D == 128 ? 0u : (vp & 1u) ? vread - 64u : vread + 64u;   // 64 channels: tile 1 (see lds_read_v64)
 
     // ---- chunk -> token rows ------------------------------------------------------------
     // ALIGNED (B % 32 == 0): a chunk lies inside one block, so its 32 rows are consecutive.  The
@@ -1202,57 +1245,51 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
         return tok < L ? tok : -1;
     };
 
-    // Request this wavefront's operations of chunk ci into stage stg (1 KiB each, one 256-byte row
-    // per 16 lanes).  A chunk is 16 operations: K operation i (0 .. 7) brings rows 4i .. 4i+3, pieces
-    // swizzled by row & 7; V operation i brings rows i, i+8, i+16, i+24 into piece i.  Wavefront w
-    // takes operations w, w + W, w + 2W, ...  Returns the validity bits of the chunk's 32 tokens.
+    // Request this wavefront's operations of chunk ci into stage stg (1 KiB each: LPR lanes per row).  K operation i
+    // brings rows RPO i .. RPO i + RPO - 1, pieces swizzled; V operation i at 128 channels rows i, i+8, i+16, i+24
+    // (piece i), at 64 channels the pieces 2 i and 2 i + 1.  Wavefront w takes operations w, w + W, w + 2W, ...
+    // Returns the validity bits of the chunk's 32 tokens.
     // Everything that depends on the wavefront is folded into a few registers up front, so that
     // the common path is straight-line code.
-    constexpr int NOPS = (16 + W - 1) / W;
-    const int n_ops = (16 - wave + W - 1) / W;       // NOPS or NOPS - 1
+    constexpr int NOPS = (OPS + W - 1) / W;
+    const int n_ops = (OPS - wave + W - 1) / W;      // NOPS or NOPS - 1
+    // the row of the chunk that lane ln fetches for operation o, and the byte offset of its 16-byte piece in the row
+    auto op_row = [](int o, int ln) -> int {
+        const int i = o & (KOPS - 1), rl = ln / LPR;
+        if (o < KOPS) return RPO * i + rl;
+        return D == 128 ? 8 * rl + i : 2 * i + (rl >> 2) + 8 * (rl & 3);
+    };
+    auto op_piece = [&](int o, int ln) -> uint32_t {
+        const int pos = ln % LPR, row = op_row(o, ln);
+        if (o < KOPS) return 16u * (uint32_t)(pos ^ (D == 128 ? row & 15 : (row >> 1) & 7));
+        return 16u * (uint32_t)(D == 128 ? pos : pos ^ (4 * (row & 1)));
+    };
     const char *src_base[NOPS];   // per operation: K or V slab (wave-uniform: scalar registers)
     uint32_t src_off[NOPS];       // ... this lane's bytes from the chunk's first row (one register each)
     int dst_off[NOPS];            // ... and where it lands in the stage
-    {
-        const int r4 = lane >> 4, pos = lane & 15;
-        const uint32_t sw0 = 16u * (uint32_t)(pos ^ r4), vsw = 16u * (uint32_t)pos;
 #pragma unroll
-        for (int t = 0; t < NOPS; ++t) {
-            const int o = min(wave + W * t, 15), i = o & 7;
-            if (o < 8) {
-                src_base[t] = kb;
-                src_off[t] = (uint32_t)(4 * i + r4) * st2 + (sw0 ^ (64u * (uint32_t)(i & 3)));
-                dst_off[t] = i * 1024;
-            } else {
-                src_base[t] = vb;
-                src_off[t] = (uint32_t)(8 * r4 + i) * st2 + vsw;
-                dst_off[t] = 8192 + i * kVPiecePitch;
-            }
-        }
+    for (int t = 0; t < NOPS; ++t) {
+        const int o = min(wave + W * t, OPS - 1), i = o & (KOPS - 1);
+        src_base[t] = o < KOPS ? kb : vb;
+        src_off[t] = (uint32_t)op_row(o, lane) * st2 + op_piece(o, lane);
+        dst_off[t] = o < KOPS ? i * 1024 : TL::kK + i * TL::kVOpPitch;
     }
     auto issue_rows = [&](const char *kbase, const char *vbase, const uint32_t stride, const uint32_t tk, char *dst) {
         // (the swizzles are recomputed here, from a lane id the compiler cannot see through: kept in registers
         // across the loop for this rare path they cost the ten-wavefront variant its last free registers)
         int lane_o = lane;
         asm volatile("" : "+v"(lane_o));
-        const int r4 = lane_o >> 4, pos = lane_o & 15;
-        const uint32_t sw0 = 16u * (uint32_t)(pos ^ r4), vsw = 16u * (uint32_t)pos;
 #pragma unroll
         for (int t = 0; t < NOPS; ++t) {
-            if (16 % W != 0 && t == NOPS - 1 && n_ops != NOPS) continue;
-            const int o = wave + W * t, i = o & 7;
-            if (o < 8) {
-                const uint32_t tv = (uint32_t)__shfl((int)tk, 4 * i + r4) * stride;
-                dma16(kbase + (tv + (sw0 ^ (64u * (uint32_t)(i & 3)))), dst + dst_off[t]);
-            } else {
-                const uint32_t tv = (uint32_t)__shfl((int)tk, 8 * r4 + i) * stride;
-                dma16(vbase + (tv + vsw), dst + dst_off[t]);
-            }
+            if (OPS % W != 0 && t == NOPS - 1 && n_ops != NOPS) continue;
+            const int o = wave + W * t;
+            const uint32_t tv = (uint32_t)__shfl((int)tk, op_row(o, lane_o)) * stride;
+            dma16((o < KOPS ? kbase : vbase) + (tv + op_piece(o, lane_o)), dst + dst_off[t]);
         }
     };
     // Stage stg of the ring is a compile-time constant in the loop below (unrolled over the stages).
     auto issue = [&](int ci, int stg) __attribute__((always_inline)) -> uint32_t {
-        char *dst = ring + stg * kStageBytes;
+        char *dst = ring + stg * TL::kStage;
         int tok;
         if (ALIGNED) {
             if (ci - row_base >= 64) fill_rows(ci);
@@ -1261,7 +1298,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
                 const uint32_t row_off = (uint32_t)r0 * st2;   // fits 32 bits (host-checked)
 #pragma unroll
                 for (int t = 0; t < NOPS; ++t)
-                    if (16 % W == 0 || t < NOPS - 1 || n_ops == NOPS) {
+                    if (OPS % W == 0 || t < NOPS - 1 || n_ops == NOPS) {
                         uint32_t so = src_off[t];
                         // (ten wavefronts: keep the 32-bit offset as it is; the compiler would otherwise carry the 64-bit sum
                         // base + offset of every operation through the loop, in registers that this variant does not have)
@@ -1293,19 +1330,19 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
         return vm;
     };
 
-    bf16x8 qf[8];
+    bf16x8 qf[KS];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[ks] = as_bf16x8(qraw[ks]);
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = as_bf16x8(qraw[ks]);
     if (ALIGNED && nch > 0) fill_rows(0);
     // from here on only this wavefront's DMA groups (n_ops operations each) are in flight (an
     // instruction the compiler knows, see attn_ctx_mfma_kernel)
     __builtin_amdgcn_s_waitcnt(0x0F70);
     asm volatile("" ::: "memory");
 
-    f32x16 O[4];
+    f32x16 O[NT];
     float m_ref = -INFINITY, l_run = 0.f;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int i = 0; i < 16; ++i) O[j][i] = 0.f;
 
@@ -1318,16 +1355,20 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
         if (2 < nch) vm_stage[2] = issue(2, 2);
         if (3 < nch) vm_stage[3] = issue(3, 3);
     }
-    uint2 v[16];
+    uint2 v[4 * NT];
     uint4 pf0 = make_uint4(0u, 0u, 0u, 0u), pf1 = pf0;
+    uint4 pl0 = pf0, pl1 = pf0;   // 64 channels: what the rounding of the weights to bf16 left over, rounded in turn
     auto pv = [&]() {
 #pragma unroll
         for (int ks2 = 0; ks2 < 2; ++ks2)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint2 lo = v[(ks2 * 4 + j) * 2], hi = v[(ks2 * 4 + j) * 2 + 1];
+            for (int j = 0; j < NT; ++j) {
+                const uint2 lo = v[(ks2 * NT + j) * 2], hi = v[(ks2 * NT + j) * 2 + 1];
                 O[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)),
                                                                as_bf16x8(ks2 ? pf1 : pf0), O[j], 0, 0, 0);
+                if (D == 64)
+                    O[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)),
+                                                                   as_bf16x8(ks2 ? pl1 : pl0), O[j], 0, 0, 0);
             }
     };
     // ten wavefronts: operands in halves (16 registers at a time instead of 32)
@@ -1354,14 +1395,14 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     // and the whole offset at run time (roff).
     auto chunk = [&](const int i, auto stage, const uint32_t roff, const uint32_t vmask) __attribute__((always_inline)) {
         constexpr int U = decltype(stage)::value;
-        constexpr int SOFF = (U % kGroupPeriod) * kStageBytes;
-        const uint32_t HOFF = (uint32_t)(U / kGroupPeriod) * kGroupPeriod * kStageBytes + roff;
+        constexpr int SOFF = (U % kGroupPeriod) * TL::kStage;
+        const uint32_t HOFF = (uint32_t)(U / kGroupPeriod) * kGroupPeriod * TL::kStage + roff;
         if (!live) return;
         f32x16 S;
-        if (W > 8) {
+        if constexpr (W > 8) {
             // ten wavefronts: operands in halves, the V operands read behind the softmax (pv_halves)
             // (k-step ks reads 32 ks bytes further, modulo the swizzle: an XOR, as the row starts are 128-byte aligned)
-            const uint32_t ka0 = kread[0] + HOFF;
+            const uint32_t ka0 = kread0 + HOFF;
             const uint32_t ka[4] = {ka0, ka0 ^ 32u, ka0 ^ 64u, ka0 ^ 96u};
             uint4 kh[4];
             lds_read_k_half<SOFF>(ka, kh);
@@ -1377,17 +1418,21 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
             for (int ks = 0; ks < 4; ++ks)
                 S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kh[ks]), qf[4 + ks], S, 0, 0, 0);
         } else {
-            uint4 kf[8];
-            {
-                const uint32_t k0 = kread[0] + HOFF, k1 = kread[1] + HOFF, k2 = kread[2] + HOFF, k3 = kread[3] + HOFF;
+            const uint32_t k0 = kread0 + HOFF, k1 = k0 ^ 32u, k2 = k0 ^ 64u, k3 = k0 ^ 96u;
+            uint4 kf[KS];
+            if constexpr (D == 128) {
                 const uint32_t ka[8] = {k0, k1, k2, k3, k0 ^ 128u, k1 ^ 128u, k2 ^ 128u, k3 ^ 128u};
                 lds_read_k<SOFF>(ka, kf);
+                lds_read_v<SOFF>(vread + HOFF, v);
+            } else {
+                const uint32_t ka[4] = {k0, k1, k2, k3};
+                lds_read_k_half<SOFF>(ka, kf);
+                lds_read_v64<SOFF>(vread + HOFF, vread1 + HOFF, v);
             }
-            lds_read_v<SOFF>(vread + HOFF, v);
 #pragma unroll
             for (int x = 0; x < 16; ++x) S[x] = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks)
+            for (int ks = 0; ks < KS; ++ks)
                 S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[ks]), qf[ks], S, 0, 0, 0);
         }
 
@@ -1413,25 +1458,34 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
             l_run *= alpha;
             if (__any(alpha != 1.f && l_run != 0.f)) {   // nothing to rescale while O is still zero
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < NT; ++j)
 #pragma unroll
                     for (int x = 0; x < 16; ++x) O[j][x] *= alpha;
             }
         }
         const float m_use = m_ref == -INFINITY ? 0.f : m_ref;
-        uint32_t pk[8];
+        uint32_t pk[8], pl[8];
         float lsum = 0.f;
 #pragma unroll
         for (int x = 0; x < 16; x += 2) {
             const float p0 = __builtin_amdgcn_exp2f(fmaf(S[x], a.scale_log2, -m_use));
             const float p1 = __builtin_amdgcn_exp2f(fmaf(S[x + 1], a.scale_log2, -m_use));
             pk[x >> 1] = pack_bf16x2(p0, p1);
-            lsum = add_bf16x2(pk[x >> 1], lsum);   // the sum runs over the rounded weights the MFMA sees
+            if (D == 64) {
+                pl[x >> 1] = pack_bf16x2(p0 - __uint_as_float(pk[x >> 1] << 16), p1 - __uint_as_float(pk[x >> 1] & 0xffff0000u));
+                lsum += p0 + p1;
+            } else {
+                lsum = add_bf16x2(pk[x >> 1], lsum);   // the sum runs over the rounded weights the MFMA sees
+            }
         }
         l_run += lsum;
+        if (D == 64) {
+            pl0 = make_uint4(pl[0], pl[1], pl[2], pl[3]);
+            pl1 = make_uint4(pl[4], pl[5], pl[6], pl[7]);
+        }
         pf0 = make_uint4(pk[0], pk[1], pk[2], pk[3]);
         pf1 = make_uint4(pk[4], pk[5], pk[6], pk[7]);
-        if (W > 8) pv_halves(vread + HOFF, std::integral_constant<int, SOFF>{});
+        if constexpr (W > 8) pv_halves(vread + HOFF, std::integral_constant<int, SOFF>{});
         else pv();
     };
     // Four chunks between two barriers.  At the barrier in front of chunks i0 .. i0 + 3 (ring half H) every
@@ -1479,7 +1533,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
                 vmv = lane == is ? vm : vmv;
             }
             const int rs = i & (kGroupStages - 1);
-            chunk(i, std::integral_constant<int, 0>{}, (uint32_t)rs * kStageBytes, (uint32_t)__builtin_amdgcn_readlane((int)vmv, rs));
+            chunk(i, std::integral_constant<int, 0>{}, (uint32_t)rs * TL::kStage, (uint32_t)__builtin_amdgcn_readlane((int)vmv, rs));
         }
     }
     __syncthreads();   // every wavefront is done with the ring: the epilogue reuses that LDS
@@ -1499,27 +1553,38 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
         return;
     }
     l_run = sum_xor32(l_run);
-    const int64_t prow0 = ((int64_t)(b * s.Hq + h) * part.nsplit + sp) * s.M;
+    const int64_t prow0 = ((int64_t)bg * part.nsplit + sp) * R + r0w;
+    const int n_rows = min(32, R - r0w);
     {
         // accumulator element 4q + x of tile j is channel 32j + 8q + 4kg + x of this lane's row
-        float *dst = obuf + ((size_t)slot * 32 + n) * kOPitch;
+        float *dst = obuf + ((size_t)slot * 32 + n) * TL::kPitch;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NT; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 *(float4 *)(dst + 32 * j + 8 * q + 4 * kg) = make_float4(O[j][4 * q], O[j][4 * q + 1], O[j][4 * q + 2], O[j][4 * q + 3]);
     }
     // a wavefront reads back only what it wrote itself: no barrier.  fp16 partials: channels 2 lane, 2 lane + 1
     // of the row's normalised result (lane uu < 32 holds row uu's l)
-    const int jrow0 = m0;
     const float il = l_run > 0.f ? 1.f / l_run : 0.f;
+    if constexpr (D == 128) {
 #pragma unroll 8
-    for (int uu = 0; uu < 32; ++uu) {
-        const float2 x = *(const float2 *)(obuf + ((size_t)slot * 32 + uu) * kOPitch + 2 * lane);
-        const float ilu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(il), uu));
-        if (jrow0 + uu < s.M) store_partial_half(part.o + (prow0 + jrow0 + uu) * 64, lane, x.x * ilu, x.y * ilu);
+        for (int uu = 0; uu < 32; ++uu) {
+            const float2 x = *(const float2 *)(obuf + ((size_t)slot * 32 + uu) * TL::kPitch + 2 * lane);
+            const float ilu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(il), uu));
+            if (uu < n_rows) store_partial_half(part.o + (prow0 + uu) * 64, lane, x.x * ilu, x.y * ilu);
+        }
+    } else {
+        // fp32 sums, four channels per lane, four rows at a time
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+        for (int uu = 0; uu < 8; ++uu) {
+            const int row = 4 * uu + (lane >> 4);
+            const f32x4 x = *(const f32x4 *)(obuf + ((size_t)slot * 32 + row) * TL::kPitch + 4 * (lane & 15));
+            if (row < n_rows) __builtin_nontemporal_store(x, (f32x4 *)(part.o + (prow0 + row) * 64) + (lane & 15));
+        }
     }
-    if (kg == 0 && jrow0 + n < s.M) *(float2 *)(part.ml + (prow0 + jrow0 + n) * 2) = make_float2(m_ref, l_run);
+    if (kg == 0 && n < n_rows) *(float2 *)(part.ml + (prow0 + n) * 2) = make_float2(m_ref, l_run);
     SPECPV_CLOCKS_END(part.timeline, (size_t)blockIdx.y * gridDim.x + blockIdx.x, nch);
     if (W > 8) {
         if (wave < kSlots) __builtin_amdgcn_s_barrier();   // the slot is free for wavefront wave + kSlots
@@ -1530,19 +1595,19 @@ bool attn_ctx_mfma_supported(const Shape &s, int dtype)
 {
     // per-lane byte offsets inside one (sequence, KV head) slab are kept in 32 bits
     const int64_t span = ((int64_t)s.max_blocks * s.B + 64) * s.st * 2;
-    return dtype == SPECPV_BF16 && s.D == 128 && s.st % 8 == 0 && span < ((int64_t)1 << 31);
+    return dtype == SPECPV_BF16 && s.st % 8 == 0 && span < ((int64_t)1 << 31);
 }
 
-// Row blocks of 32 query rows per KV group, and how the group kernel deals them to workgroups.
+// The KV head's M * G query rows in blocks of 32 (packed over the query heads: 78 nodes at G = 4 are 10 blocks, not 12),
+// and how the group kernel deals them to workgroups.
 struct GroupLayout {
-    int rph, n_row_blocks, parts, waves;
+    int n_row_blocks, parts, waves;
 };
 static GroupLayout group_layout(const Shape &s)
 {
     GroupLayout g;
-    g.rph = (s.M + 31) / 32;
-    g.n_row_blocks = s.G * g.rph;
-    if (g.n_row_blocks == 9 || g.n_row_blocks == 10) {   // one workgroup of ten instead of two of five
+    g.n_row_blocks = (s.G * s.M + 31) / 32;
+    if (s.D == 128 && (g.n_row_blocks == 9 || g.n_row_blocks == 10)) {   // one workgroup of ten instead of two of five
         g.parts = 1;
         g.waves = 10;
         return g;
@@ -1558,6 +1623,7 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
                                 int n_sel, Partials p, int nctx, int kind, const FusedArgs &f, hipStream_t st)
 {
     if (kind != kAttnSplit && kind != kAttnGroup) return hipErrorInvalidValue;
+    if (kind == kAttnSplit && s.D != 128) return hipErrorInvalidValue;
     const bool fused = f.out != nullptr;
     if (fused && (kind != kAttnSplit || nctx > 64 || p.nsplit != nctx + 1)) return hipErrorInvalidValue;
     if (!fused && p.nsplit != nctx) return hipErrorInvalidValue;
@@ -1566,15 +1632,15 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
     a.sel_idx = sel_idx;
     a.sel_count = sel_count;
     a.n_sel = n_sel;
-    a.scale_log2 = kLog2e / sqrtf(128.f);
+    a.scale_log2 = kLog2e / sqrtf((float)s.D);
     a.row_tiles = (s.M + 63) / 64;
-    a.rph = gl.rph;
     a.n_row_blocks = gl.n_row_blocks;
     a.n_units = s.batch * s.Hkv * nctx;
     a.n_bg = s.batch * s.Hkv;
     a.div_nsplit = make_fastdiv((uint32_t)nctx);
     a.div_hkv = make_fastdiv((uint32_t)s.Hkv);
     a.div_B = make_fastdiv((uint32_t)s.B);
+    a.div_G = make_fastdiv((uint32_t)s.G);
     // token ranges per split: four (one per token group of a workgroup), or one in the group kernel
     a.div_W = make_fastdiv((uint32_t)nctx * (kind == kAttnGroup ? 1u : 4u));
     const int GR = kind == kAttnGroup ? gl.parts : s.G * a.row_tiles;
@@ -1584,7 +1650,9 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
     if (grid.y > 65535u) return hipErrorInvalidConfiguration;
     const bool aligned = s.B % 32 == 0;
     const size_t lds_split = 2048 + (size_t)max(kRingBytes, 4 * 64 * kOPitch * (int)sizeof(float)) + kQStageBytes;
-    const size_t lds_group = (size_t)max(kGroupStages * kStageBytes, (gl.waves > 8 ? gl.waves / 2 : gl.waves) * 32 * kOPitch * (int)sizeof(float));
+    const int staged = gl.waves > 8 ? gl.waves / 2 : gl.waves;   // wavefronts whose rows the epilogue stages at a time
+    const size_t lds_group = s.D == 128 ? (size_t)max(kGroupStages * Tile<128>::kStage, staged * 32 * Tile<128>::kPitch * (int)sizeof(float))
+                                        : (size_t)max(kGroupStages * Tile<64>::kStage, staged * 32 * Tile<64>::kPitch * (int)sizeof(float));
 #define SPECPV_SET_LDS(KERN, LDS)                                                                      \
         static PerDeviceOnce once;   /* one per kernel instantiation */                               \
         auto kern = KERN;                                                                              \
@@ -1592,11 +1660,11 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
             return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(LDS)); \
         });                                                                                            \
         if (e0 != hipSuccess) return e0
-#define SPECPV_LAUNCH_GROUP(WW)                                                                        \
+#define SPECPV_LAUNCH_GROUP(DD, WW)                                                                    \
     do {                                                                                               \
-        if (aligned) { SPECPV_SET_LDS((attn_ctx_mfma_group_kernel<true, WW>), lds_group);               \
+        if (aligned) { SPECPV_SET_LDS((attn_ctx_mfma_group_kernel<DD, true, WW>), lds_group);           \
                        hipLaunchKernelGGL(kern, grid, dim3(64 * WW), lds_group, st, s, p, a); }         \
-        else { SPECPV_SET_LDS((attn_ctx_mfma_group_kernel<false, WW>), lds_group);                      \
+        else { SPECPV_SET_LDS((attn_ctx_mfma_group_kernel<DD, false, WW>), lds_group);                  \
                hipLaunchKernelGGL(kern, grid, dim3(64 * WW), lds_group, st, s, p, a); }                 \
     } while (0)
 #define SPECPV_LAUNCH_SPLIT(AL, FU, PE)                                                                \
@@ -1606,12 +1674,21 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
                            n_sel, s.M, s.Hq, nctx, s, p, a, f);                                         \
     } while (0)
     if (kind == kAttnGroup) {
-        switch (gl.waves) {
-        case 2: SPECPV_LAUNCH_GROUP(2); break;
-        case 4: SPECPV_LAUNCH_GROUP(4); break;
-        case 6: SPECPV_LAUNCH_GROUP(6); break;
-        case 10: SPECPV_LAUNCH_GROUP(10); break;
-        default: SPECPV_LAUNCH_GROUP(8); break;
+        if (s.D == 64) {
+            switch (gl.waves) {
+            case 2: SPECPV_LAUNCH_GROUP(64, 2); break;
+            case 4: SPECPV_LAUNCH_GROUP(64, 4); break;
+            case 6: SPECPV_LAUNCH_GROUP(64, 6); break;
+            default: SPECPV_LAUNCH_GROUP(64, 8); break;
+            }
+        } else {
+            switch (gl.waves) {
+            case 2: SPECPV_LAUNCH_GROUP(128, 2); break;
+            case 4: SPECPV_LAUNCH_GROUP(128, 4); break;
+            case 6: SPECPV_LAUNCH_GROUP(128, 6); break;
+            case 10: SPECPV_LAUNCH_GROUP(128, 10); break;
+            default: SPECPV_LAUNCH_GROUP(128, 8); break;
+            }
         }
     } else if (fused) {
         if (aligned) SPECPV_LAUNCH_SPLIT(true, true, true); else SPECPV_LAUNCH_SPLIT(false, true, true);

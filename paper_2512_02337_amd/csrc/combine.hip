@@ -154,14 +154,15 @@ __global__ __launch_bounds__(256) void combine_kernel(const int32_t *a_parent, c
     const int64_t qrow = (((int64_t)b * s.M + j) * s.Hq + h) * D;
     Raw qraw;
     Chan<T, CPL>::load(s.q, qrow + d0, qraw);
-    const int64_t prow0 = (((int64_t)b * s.Hq + h) * part.nsplit) * s.M + j;
+    const int R = s.M * s.G;   // rows of the KV head, node by node: one split's partials of this wavefront's heads are adjacent
+    const int64_t prow0 = ((int64_t)bg * part.nsplit) * R + j * s.G + (h - g * s.G);
     // ... including the first NP context partials (all of them in the usual case); the 16 lanes
     // of a row all fetch the row's (m, l) pairs, so the merge below needs no cross-lane step
     struct Round { float2 ml[NP]; float po[NP][CPL]; };
     auto fetch = [&](int sp0, Round &r) {
 #pragma unroll
         for (int u = 0; u < NP; ++u) {
-            const int64_t prow = prow0 + (int64_t)min(sp0 + u, part.nsplit - 1) * s.M;
+            const int64_t prow = prow0 + (int64_t)min(sp0 + u, part.nsplit - 1) * R;
             r.ml[u] = *(const float2 *)(part.ml + prow * 2);
             if (HALF) load_partial_half<CPL>(part.o, prow * D, lane & 15, r.po[u]);
             else load_partial<CPL>(part.o, prow * D + 4 * (lane & 15), r.po[u]);

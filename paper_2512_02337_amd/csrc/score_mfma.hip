@@ -1,10 +1,10 @@
 // Block scoring (Section 3.2, eq. 2 and eq. 3; optionally the channel-wise bound) on the matrix
-// cores for bf16, head dim 128.
+// cores for bf16, head dims 128 and 64.
 //
 // Per KV head the scores are max(Q . Kmax^T, Q . Kmin^T) reduced over the M*G query rows:
-// two [rows x 128] x [128 x blocks] products.  A workgroup owns a tile of 32 blocks and
+// two [rows x D] x [D x blocks] products.  A workgroup owns a tile of 32 blocks and
 // spreads the query rows over its wavefronts, 32 rows at a time: a wavefront holds the two
-// 32 x 128 summary tiles as MFMA B operands (lane = block) and its query rows as A operand
+// 32 x D summary tiles as MFMA B operands (lane = block) and its query rows as A operand
 // (lane = row), so each lane ends up with 16 rows of ONE block; the element-wise max of the
 // two accumulators and the reduction over rows (mean / max / rows of one node) are
 // lane-local.  All reads of a wavefront are issued at once (one round trip); the
@@ -57,15 +57,18 @@ __device__ __forceinline__ void lds_read8(const uint32_t (&a)[8], uint4 (&k)[8])
 // batches, where the workgroups are many and the repeated query reads are most of the traffic).
 // ACROSS: the scores are read by another workgroup of this launch: agent-scope stores, which go
 // past the caches that are private to a part of the chip.
-template <bool BOUND, int TILES, bool ACROSS>
+template <int D, bool BOUND, int TILES, bool ACROSS>
 __device__ __forceinline__ void score_tiles(const Shape &s, const uint16_t *__restrict__ kmax,
                                             const uint16_t *__restrict__ kmin, int reduce, int last_node,
                                             float *__restrict__ scores)
 {
-    // the two summary tiles of this workgroup's 32 blocks: row-major, 256 B per block, the
-    // 16-byte pieces of row t stored at piece index p ^ (t & 15) so that the operand reads
-    // below (16 lanes per cycle, same piece, different rows) spread over all 64 banks
-    __shared__ __attribute__((aligned(1024))) char tile[2 * TILES][8192];   // [tile][Kmax | Kmin]
+    constexpr int KS = D / 16;                  // k-steps
+    constexpr int LPR = D / 8, RPO = 64 / LPR;  // lanes per row, rows per 1 KiB DMA operation
+    constexpr int OPS = D / 16;                 // DMA operations of one tile
+    // the two summary tiles of this workgroup's 32 blocks: row-major, 2 D bytes per block, the
+    // 16-byte pieces of row t stored at piece index p ^ (t & 15) (64 channels: p ^ ((t >> 1) & 7)) so that
+    // the operand reads below (16 lanes per cycle, same piece, different rows) spread over all 64 banks
+    __shared__ __attribute__((aligned(1024))) char tile[2 * TILES][64 * D];   // [tile][Kmax | Kmin]
     __shared__ float red[kScoreMaxWaves][64 * TILES];
     const int lane = threadIdx.x & 63, W = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -80,18 +83,18 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const uint16_t *__re
     // at once (there the wait for the length is cheaper than their reads)
     if (s.batch > 1 && i0 >= nb) return;   // (only out of this function: the workgroup still counts itself in)
 
-    // Summary rows go from memory straight into LDS (16 DMA operations of 1 KiB shared by the
-    // wavefronts; operation d brings rows 4*(d&7) .. +3 of Kmax (d < 8) or Kmin, one 256-byte
-    // row per 16 lanes).  Rows past the end of the arrays repeat the last row; their scores
+    // Summary rows go from memory straight into LDS (DMA operations of 1 KiB shared by the
+    // wavefronts; operation d of a tile brings RPO rows of Kmax (d < OPS) or Kmin, LPR lanes per row).  Rows past the end of the arrays repeat the last row; their scores
     // are never stored.
     {
-        const int r4 = lane >> 4, pos = lane & 15;
+        const int rl = lane / LPR, pos = lane % LPR;
         const int64_t arr_row0 = ((int64_t)b * s.Hkv + g) * s.max_blocks;
-        for (int d = wave; d < 16 * TILES; d += W) {
-            const int i = d & 7, row = 4 * i + r4, t = d >> 4;
+        for (int d = wave; d < 2 * OPS * TILES; d += W) {
+            const int i = d & (OPS - 1), row = RPO * i + rl, t = d / (2 * OPS);
             const int blk = min(i0 + 32 * t + row, s.max_blocks - 1);
-            const char *src = (const char *)((d & 8) ? kmin : kmax) + ((arr_row0 + blk) * 128) * 2 + 16 * (pos ^ (row & 15));
-            __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(tile[d >> 3] + i * 1024), 16, 0, 2);   // streaming hint: read once
+            const int piece = pos ^ (D == 128 ? row & 15 : (row >> 1) & 7);
+            const char *src = (const char *)((d & OPS) ? kmin : kmax) + ((arr_row0 + blk) * D) * 2 + 16 * piece;
+            __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(tile[d / OPS] + i * 1024), 16, 0, 2);   // streaming hint: read once
         }
     }
 
@@ -104,10 +107,10 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const uint16_t *__re
     for (int r0 = wave * 32; r0 < R; r0 += W * 32) {
         const int r = min(r0 + n, R - 1);
         const int j = r / s.G, hh = r - j * s.G;
-        const uint16_t *qrow = q + (((int64_t)b * s.M + j) * s.Hq + g * s.G + hh) * 128 + kg * 8;
-        uint4 qa[8];
+        const uint16_t *qrow = q + (((int64_t)b * s.M + j) * s.Hq + g * s.G + hh) * D + kg * 8;
+        uint4 qa[KS];
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) qa[ks] = *(const uint4 *)(qrow + ks * 16);
+        for (int ks = 0; ks < KS; ++ks) qa[ks] = *(const uint4 *)(qrow + ks * 16);
         if (!landed) {
             __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wavefront's DMA operations (and query rows) are in
             __syncthreads();                      // ... and so are everybody else's
@@ -116,11 +119,11 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const uint16_t *__re
 #pragma unroll
         for (int t = 0; t < TILES; ++t) {
             // summary tiles as B operands: lane = block, channels 16*ks + 8*kg .. +8
-            const char *bxp = tile[2 * t] + n * 256, *bnp = tile[2 * t + 1] + n * 256;
-            bf16x8 bx[8], bn[8];
+            const char *bxp = tile[2 * t] + n * (2 * D), *bnp = tile[2 * t + 1] + n * (2 * D);
+            bf16x8 bx[KS], bn[KS];
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks) {
-                const int off = (32 * ks + 16 * kg) ^ (16 * (n & 15));
+            for (int ks = 0; ks < KS; ++ks) {
+                const int off = (32 * ks + 16 * kg) ^ (16 * (D == 128 ? n & 15 : (n >> 1) & 7));
                 bx[ks] = __builtin_bit_cast(bf16x8, *(const uint4 *)(bxp + off));
                 bn[ks] = __builtin_bit_cast(bf16x8, *(const uint4 *)(bnp + off));
             }
@@ -128,7 +131,7 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const uint16_t *__re
 #pragma unroll
             for (int x = 0; x < 16; ++x) { sx[x] = 0.f; sn[x] = 0.f; }
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks) {
+            for (int ks = 0; ks < KS; ++ks) {
                 if (BOUND) {
                     // split the packed bf16 pairs by sign: 0xffff in the halves whose sign bit is set
                     uint4 neg, pos;
@@ -364,14 +367,15 @@ __device__ __forceinline__ void score_tiles_staged(const Shape &s, const uint16_
 // complete sets it back to zero.
 // WMAX: the most wavefronts a launch of this instantiation has (fewer leave the compiler more registers: at
 // ten it keeps a tile's sixteen operand reads ahead of the matrix instructions instead of one read per instruction).
-template <bool BOUND, int TILES, int P, int STG = 1, int WMAX = kScoreMaxWaves>
+template <int D, bool BOUND, int TILES, int P, int STG = 1, int WMAX = kScoreMaxWaves>
 __global__ __launch_bounds__(64 * WMAX) void score_mfma_kernel(Shape s, const uint16_t *__restrict__ kmax,
                                                                          const uint16_t *__restrict__ kmin, int reduce,
                                                                          int last_node, float *__restrict__ scores,
                                                                          TopkArgs a, unsigned long long *arrive, int wstride)
 {
+    static_assert(STG == 1 || D == 128, "the query-stationary form is written for 128 channels");
     if constexpr (STG > 1) score_tiles_staged<BOUND, TILES, STG, P != 0>(s, kmax, kmin, reduce, last_node, scores);
-    else score_tiles<BOUND, TILES, P != 0>(s, kmax, kmin, reduce, last_node, scores);
+    else score_tiles<D, BOUND, TILES, P != 0>(s, kmax, kmin, reduce, last_node, scores);
     if constexpr (P != 0) {
         __shared__ TopkLds lds;
         __shared__ int is_last;
@@ -403,7 +407,7 @@ __global__ __launch_bounds__(64 * WMAX) void score_mfma_kernel(Shape s, const ui
     }
 }
 
-bool score_mfma_supported(const Shape &s, int dtype) { return dtype == SPECPV_BF16 && s.D == 128; }
+bool score_mfma_supported(const Shape &s, int dtype) { return dtype == SPECPV_BF16; }
 
 bool score_select_supported(const Shape &s, int dtype)
 {
@@ -433,21 +437,23 @@ hipError_t launch_scores_mfma(const Shape &s, const void *kmax, const void *kmin
     // eight sequences of 64K at G = 5 30.5 against 36.3; at G = 4, eight blocks of rows, 16 x 32K: 27.9 against
     // 27.1, so those stay with four tiles).  eq.-2 scores only: the channel-wise bound splits the query operands by
     // sign and has no registers to hold them.
-    const bool staged = T == 4 && row_tiles >= 9 && row_tiles <= 10 && kind != SPECPV_SCORE_CHANNEL_BOUND;
+    const bool staged = T == 4 && row_tiles >= 9 && row_tiles <= 10 && s.D == 128 && kind != SPECPV_SCORE_CHANNEL_BOUND;
     const int per_wg = staged ? 8 : T;
     dim3 grid((tiles1 + per_wg - 1) / per_wg, s.Hkv, s.batch), block(64 * (row_tiles < kScoreMaxWaves ? row_tiles : kScoreMaxWaves));
     const int P = !sel ? 0 : (s.max_blocks <= 256 * 4 ? 4 : (s.max_blocks <= 256 * 8 ? 8 : 16));
     const TopkArgs a = sel ? *sel : TopkArgs{0, 0, 0, 0, nullptr, nullptr};
     // every arrival word on a 128-byte line of its own where the region is large enough for that
     const int wstride = (size_t)s.batch * s.Hkv * 9 * 128 <= kArriveBytes ? 16 : 1;
-#define SPECPV_LAUNCH(BOUND, TILES, PP) \
-    hipLaunchKernelGGL((score_mfma_kernel<BOUND, TILES, PP>), grid, block, 0, st, s, (const uint16_t *)kmax, \
+#define SPECPV_LAUNCH(DD, BOUND, TILES, PP) \
+    hipLaunchKernelGGL((score_mfma_kernel<DD, BOUND, TILES, PP>), grid, block, 0, st, s, (const uint16_t *)kmax, \
                        (const uint16_t *)kmin, reduce, last_node, scores, a, arrive, wstride)
+#define SPECPV_LAUNCH_DP(DD, BOUND, TILES) \
+    do { if (P == 0) SPECPV_LAUNCH(DD, BOUND, TILES, 0); else if (P == 4) SPECPV_LAUNCH(DD, BOUND, TILES, 4); \
+         else if (P == 8) SPECPV_LAUNCH(DD, BOUND, TILES, 8); else SPECPV_LAUNCH(DD, BOUND, TILES, 16); } while (0)
 #define SPECPV_LAUNCH_P(BOUND, TILES) \
-    do { if (P == 0) SPECPV_LAUNCH(BOUND, TILES, 0); else if (P == 4) SPECPV_LAUNCH(BOUND, TILES, 4); \
-         else if (P == 8) SPECPV_LAUNCH(BOUND, TILES, 8); else SPECPV_LAUNCH(BOUND, TILES, 16); } while (0)
+    do { if (s.D == 128) SPECPV_LAUNCH_DP(128, BOUND, TILES); else SPECPV_LAUNCH_DP(64, BOUND, TILES); } while (0)
 #define SPECPV_LAUNCH_S(BOUND, PP) \
-    hipLaunchKernelGGL((score_mfma_kernel<BOUND, 2, PP, 4, 10>), grid, block, 0, st, s, (const uint16_t *)kmax, \
+    hipLaunchKernelGGL((score_mfma_kernel<128, BOUND, 2, PP, 4, 10>), grid, block, 0, st, s, (const uint16_t *)kmax, \
                        (const uint16_t *)kmin, reduce, last_node, scores, a, arrive, wstride)
 #define SPECPV_LAUNCH_SP(BOUND) \
     do { if (P == 0) SPECPV_LAUNCH_S(BOUND, 0); else if (P == 4) SPECPV_LAUNCH_S(BOUND, 4); \
@@ -462,6 +468,7 @@ hipError_t launch_scores_mfma(const Shape &s, const void *kmax, const void *kmin
 #undef SPECPV_LAUNCH_SP
 #undef SPECPV_LAUNCH_S
 #undef SPECPV_LAUNCH_P
+#undef SPECPV_LAUNCH_DP
 #undef SPECPV_LAUNCH
     return hipGetLastError();
 }
