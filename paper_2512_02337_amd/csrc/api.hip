@@ -114,6 +114,14 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks)
     };
     const int64_t tokens = n_blocks * s.B;
     if (tokens <= 0) return plan;
+    // what specpv_partial_verify_attn_static took with the few splits of fp32 partials must fit its array with more:
+    // no more splits than have room, where the few have
+    auto static_room = [&](int64_t few, int64_t ns) {
+        const int64_t slot = rows * (s.D + 2) * (int64_t)sizeof(float);
+        const int64_t room = ((int64_t)SPECPV_STATIC_SCRATCH_BYTES - (int64_t)kArriveBytes - 1024 -
+                              (int64_t)s.batch * s.Hkv * s.max_blocks * (int64_t)sizeof(float)) / slot - 1;
+        return ns > room && room >= few ? room : ns;
+    };
     if (plan.kind != kAttnGeneric) {
         const int64_t chunks = (tokens + 31) / 32;   // 32-token chunks per (sequence, KV head)
         // workgroups that the chip holds at once: one per CU (the LDS), two of the 64-channel kernel's
@@ -147,11 +155,7 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks)
             int64_t max1 = chunks / shortest > 1 ? (chunks / shortest < 64 ? chunks / shortest : 64) : 1;
             const int64_t few = few_splits(tokens);
             if (s.D == 64) {
-                // what specpv_partial_verify_attn_static takes with few splits must fit its array with many
-                const int64_t slot = rows * (s.D + 2) * (int64_t)sizeof(float);
-                const int64_t room = ((int64_t)SPECPV_STATIC_SCRATCH_BYTES - (int64_t)kArriveBytes - 1024 -
-                                      (int64_t)s.batch * s.Hkv * s.max_blocks * (int64_t)sizeof(float)) / slot - 1;
-                if (max1 > room && room >= few) max1 = room;
+                max1 = static_room(few, max1);
                 // up to 1024 tokens: the few splits of the vector-ALU kernel are enough
                 if (chunks <= 32 && max1 > few) max1 = few;
             }
@@ -172,7 +176,23 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks)
         }
         plan.nsplit = (int)ns;
     } else {
-        plan.nsplit = (int)few_splits(tokens);
+        // two wavefronts of 32 rows per SIMD, 64 tokens or more each (the few splits up to 1024 tokens, and half that many
+        // tokens each for the shortest ranges, whose time is one wavefront's chain)
+        const int64_t few = few_splits(tokens);
+        int64_t ns = few;
+        if (tokens > 1024) {
+            const int64_t waves = (int64_t)((s.G * s.M + 31) / 32) * s.batch * s.Hkv;
+            ns = (8 * (int64_t)device_cu_count() + waves - 1) / waves;
+            if (ns > tokens / 64) ns = tokens / 64;
+            if (ns > 64) ns = 64;
+            if (ns < few) ns = few;
+        } else if (tokens <= 512) {
+            const int64_t most = (tokens + 31) / 32 < 8 ? (tokens + 31) / 32 : 8;
+            const int64_t want = (4096 + rows - 1) / rows;
+            ns = want < most ? want : most;
+            if (ns < few) ns = few;
+        }
+        plan.nsplit = (int)static_room(few, ns);
     }
     return plan;
 }
