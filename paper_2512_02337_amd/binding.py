@@ -3,6 +3,10 @@
 The wrappers take torch tensors where the C call takes device pointers, check
 dtype / device / contiguity (the C side cannot see those), and pass the current
 torch stream.  They allocate nothing: outputs and workspace come from the caller.
+
+A call goes through the extension module _native (csrc/binding_native.cpp), which makes the same checks and enters
+the library in half a microsecond; where it finds an argument that the call does not take, it leaves the call to the
+checks here, which say what is wrong.
 """
 import ctypes
 import os
@@ -62,6 +66,10 @@ class _Cfg(ctypes.Structure):
 
 
 _lib = None
+_native = None
+# the library's functions in the order of the extension's table
+_TABLE = ["specpv_block_summarize", "specpv_select_blocks", "specpv_partial_verify_attn", "specpv_partial_verify_attn_static",
+          "specpv_full_verify_refresh", "specpv_gather_blocks", "specpv_commit_accepted", "specpv_commit_accepted_layers"]
 
 
 def lib_path():
@@ -70,7 +78,7 @@ def lib_path():
 
 def load():
     """dlopen libspecpv.so.  Raises if it has not been built: there is no fallback."""
-    global _lib, _LIB_PATH
+    global _lib, _LIB_PATH, _native
     if _lib is not None:
         return _lib
     # SPECPV_LIB names another build of the same library (the instrumented one that timeline.py measures with)
@@ -78,6 +86,11 @@ def load():
     if not os.path.exists(_LIB_PATH):
         raise RuntimeError("libspecpv.so is not built (%s missing): run "
                            "`python -m paper_2512_02337_amd.build` first" % _LIB_PATH)
+    try:
+        from . import _native as native
+    except ImportError as e:
+        raise RuntimeError("the extension module _native is not built (%s): run "
+                           "`python -m paper_2512_02337_amd.build` first" % e) from e
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i32, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
     P = ctypes.POINTER
@@ -113,8 +126,15 @@ def load():
     lib.specpv_strerror.argtypes = [ctypes.c_int]
     lib.specpv_last_hip_error.restype = ctypes.c_char_p
     lib.specpv_version.restype = ctypes.c_int
+    native.set_table(*[ctypes.cast(getattr(lib, name), vp).value for name in _TABLE])
+    _native = native
     _lib = lib
     return lib
+
+
+def _loaded():
+    load()
+    return _native
 
 
 def _check(rc):
@@ -228,6 +248,9 @@ def specpv_workspace_bytes(kv, tree=None, cfg=None):
 
 
 def specpv_block_summarize(kv, blk_begin, blk_end, kmax, kmin):
+    rc = (_native or _loaded()).summarize(kv, blk_begin, blk_end, kmax, kmin)
+    if rc is not None:
+        return _check(rc)
     for name, t in (("kmax", kmax), ("kmin", kmin)):
         if tuple(t.shape) != kv.summary_shape():
             raise ValueError("%s: [batch, Hkv, max_blocks, D]" % name)
@@ -249,6 +272,9 @@ def _check_sel(kv, sel_idx, sel_count, n_sel):
 
 
 def specpv_select_blocks(kv, tree, kmax, kmin, cfg, sel_idx, sel_count, scores=None, workspace=None):
+    rc = (_native or _loaded()).select(kv, tree, kmax, kmin, cfg, sel_idx, sel_count, scores, workspace)
+    if rc is not None:
+        return _check(rc)
     _match(kv, tree)
     _check_sel(kv, sel_idx, sel_count, cfg.n_sel)
     if scores is not None and tuple(scores.shape) != (kv.batch, kv.Hkv, kv.max_blocks):
@@ -264,6 +290,9 @@ def specpv_select_blocks(kv, tree, kmax, kmin, cfg, sel_idx, sel_count, scores=N
 
 
 def specpv_partial_verify_attn(kv, tree, sel_idx, sel_count, out, lse=None, workspace=None):
+    rc = (_native or _loaded()).partial(kv, tree, sel_idx, sel_count, out, lse, workspace)
+    if rc is not None:
+        return _check(rc)
     _match(kv, tree)
     n_sel = 0
     if sel_idx is not None:
@@ -284,6 +313,9 @@ def specpv_partial_verify_attn(kv, tree, sel_idx, sel_count, out, lse=None, work
 def specpv_partial_verify_attn_static(kv, tree, sel_idx, sel_count, out, lse=None):
     """specpv_partial_verify_attn without a workspace: the partial results live in the library's own
     static device array (at most STATIC_SCRATCH_BYTES; larger shapes raise SpecPVError -3)."""
+    rc = (_native or _loaded()).partial_static(kv, tree, sel_idx, sel_count, out, lse)
+    if rc is not None and rc != -3:   # (-3: the text below)
+        return _check(rc)
     _match(kv, tree)
     n_sel = 0
     if sel_idx is not None:
@@ -307,6 +339,9 @@ STATIC_SCRATCH_BYTES = 16 << 20
 
 def specpv_full_verify_refresh(kv, tree, kmax, kmin, stale_blk_begin, cfg, out, lse, sel_idx, sel_count,
                                scores=None, workspace=None):
+    rc = (_native or _loaded()).refresh(kv, tree, kmax, kmin, stale_blk_begin, cfg, out, lse, sel_idx, sel_count, scores, workspace)
+    if rc is not None:
+        return _check(rc)
     _match(kv, tree)
     _check_sel(kv, sel_idx, sel_count, cfg.n_sel)
     if out.shape != tree.q.shape:
@@ -329,6 +364,9 @@ def specpv_full_verify_refresh(kv, tree, kmax, kmin, stale_blk_begin, cfg, out, 
 
 def specpv_gather_blocks(kv, sel_idx, sel_count, out_k, out_v, out_len=None):
     """out_k / out_v [batch, Hkv, n_sel * B, D]; out_len int32 [batch] (optional)."""
+    rc = (_native or _loaded()).gather(kv, sel_idx, sel_count, out_k, out_v, out_len)
+    if rc is not None:
+        return _check(rc)
     n_sel = sel_idx.shape[-1]
     _check_sel(kv, sel_idx, sel_count, n_sel)
     for name, t in (("out_k", out_k), ("out_v", out_v)):
@@ -373,6 +411,10 @@ def specpv_commit_accepted(kv, buf_k, buf_v, pending_cap, M_tree, n_pending, acc
     """buf_k / buf_v [batch, pending_cap + M_tree, Hkv, D]; n_pending, n_accepted int32 [batch];
     accepted int32 [batch, max_accept]; optional sel_idx / sel_count (the layer's kept-block lists, extended
     by a commit to the cache) and dropped int32 [batch, 2] -- all on the GPU."""
+    rc = (_native or _loaded()).commit(kv, buf_k, buf_v, pending_cap, M_tree, n_pending, accepted, n_accepted, mode, kmax, kmin,
+                                       workspace, sel_idx, sel_count, dropped)
+    if rc is not None:
+        return _check(rc)
     for name, t in (("buf_k", buf_k), ("buf_v", buf_v)):
         if tuple(t.shape) != (kv.batch, pending_cap + M_tree, kv.Hkv, kv.D):
             raise ValueError("%s: [batch, pending_cap + M_tree, Hkv, D]" % name)
@@ -396,6 +438,10 @@ def specpv_commit_accepted_layers(kvs, buf_ks, buf_vs, pending_cap, M_tree, n_pe
     """specpv_commit_accepted for all layers of a model at once: kvs, buf_ks, buf_vs (and kmaxs, kmins,
     sel_idxs, sel_counts) are lists with one entry per layer; the layers share shape, strides, dtype and
     ONE ctx_len tensor."""
+    rc = (_native or _loaded()).commit_layers(kvs, buf_ks, buf_vs, pending_cap, M_tree, n_pending, accepted, n_accepted, mode,
+                                              kmaxs, kmins, workspace, sel_idxs, sel_counts, dropped)
+    if rc is not None:
+        return _check(rc)
     n = len(kvs)
     if n < 1 or len(buf_ks) != n or len(buf_vs) != n:
         raise ValueError("one kv, buf_k and buf_v per layer")

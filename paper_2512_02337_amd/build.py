@@ -1,11 +1,14 @@
-"""Builds libspecpv.so (HIP, gfx950) in-tree with hipcc."""
+"""Builds libspecpv.so (HIP, gfx950) in-tree with hipcc, and the extension module of the binding with g++."""
 import os
 import subprocess
+import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspecpv.so")
+NATIVE = os.path.join(HERE, "_native.so")
 # the same library with time stamps inside the partial-verify attention kernel (timeline.py uses it)
 LIB_TIMELINE = os.path.join(HERE, "libspecpv_timeline.so")
 SOURCES = ["api.hip", "summarize.hip", "select.hip", "score_mfma.hip", "attn_generic.hip",
@@ -50,11 +53,32 @@ def build(verbose=False, jobs=8, lib=LIB, defines=()):
     return lib
 
 
+def build_native():
+    """The extension module: host code against the C ABI's header, Python and torch."""
+    import torch
+    from torch.utils import cpp_extension
+    root = os.path.dirname(torch.__file__)
+    tmp = NATIVE + ".tmp%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I" + os.path.join(ROOT, "include"),
+           "-I" + sysconfig.get_paths()["include"]]
+    cmd += ["-isystem" + p for p in cpp_extension.include_paths("cuda")]
+    cmd += [os.path.join(CSRC, "binding_native.cpp"), "-o", tmp, "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    p = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if p.returncode != 0:
+        raise RuntimeError("g++ failed on binding_native.cpp:\n" + p.stdout)
+    os.replace(tmp, NATIVE)
+    return NATIVE
+
+
 def build_timeline(verbose=False):
     """The instrumented variant: same sources, -DSPECPV_TIMELINE, its own file name."""
     return build(verbose=verbose, lib=LIB_TIMELINE, defines=("SPECPV_TIMELINE",))
 
 
 if __name__ == "__main__":
-    import sys
-    print(build_timeline(verbose=True) if "--timeline" in sys.argv[1:] else build(verbose=True))
+    if "--timeline" in sys.argv[1:]:
+        print(build_timeline(verbose=True))
+    else:
+        print(build(verbose=True))
+        print(build_native())
