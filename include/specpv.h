@@ -121,7 +121,8 @@ typedef struct specpv_select_cfg {
  * A workspace must be ZERO-FILLED ONCE before its first use (hipMemset, torch.zeros): its first
  * 64 KiB hold the arrival words through which the workgroups of the single-kernel route of
  * specpv_partial_verify_attn (specpv_debug_set_route) find out which of them finishes a row tile, and
- * those of the one-launch route of the selection (specpv_debug_set_select_route) which of them selects.
+ * those of the one-launch route of the selection (specpv_debug_set_select_route) which of them selects; a commit
+ * with lists keeps its count of missing list entries there between its two launches.
  * Every call leaves them zero again, so one fill at
  * allocation is enough, whatever shapes use the workspace afterwards.  A call that is given
  * words that are not zero computes garbage (it cannot notice). */

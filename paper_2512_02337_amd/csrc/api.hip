@@ -480,12 +480,11 @@ int specpv_commit_accepted(const specpv_kv *kv, void *buf_k, void *buf_v, int32_
     if ((kmax || kmin) && (!kmax || !kmin || (((uintptr_t)kmax | (uintptr_t)kmin) & 15))) return SPECPV_EINVAL;
     if ((int64_t)pending_cap + max_accept > 128 || (int64_t)pending_cap + M_tree > SPECPV_MAX_M) return SPECPV_ELIMIT;
     if (!workspace || workspace_bytes < kArriveBytes + (size_t)kv->batch * sizeof(int32_t)) return SPECPV_EWORKSPACE;
-    workspace = (char *)workspace + kArriveBytes;   // the arrival words stay zero
     const Shape s = make_shape(kv, nullptr);
     void *k1 = const_cast<void *>(kv->k), *v1 = const_cast<void *>(kv->v);
     const hipError_t e = launch_commit(s, kv->dtype, 1, &k1, &v1, &buf_k, &buf_v, pending_cap, M_tree, n_pending, accepted,
                                        n_accepted, max_accept, mode != SPECPV_MODE_PARTIAL, &kmax, &kmin,
-                                       lists, dropped, (int32_t *)workspace, (hipStream_t)stream);
+                                       lists, dropped, (uint32_t *)workspace, (hipStream_t)stream);
     return e == hipSuccess ? SPECPV_OK : fail_hip(e);
 }
 
@@ -527,11 +526,10 @@ int specpv_commit_accepted_layers(const specpv_kv *const *kv, void *const *buf_k
         vp[l] = const_cast<void *>(x->v);
     }
     if (!workspace || workspace_bytes < kArriveBytes + (size_t)kv[0]->batch * sizeof(int32_t)) return SPECPV_EWORKSPACE;
-    workspace = (char *)workspace + kArriveBytes;   // the arrival words stay zero
     const Shape s = make_shape(kv[0], nullptr);
     const hipError_t e = launch_commit(s, kv[0]->dtype, n_layers, kp, vp, buf_k, buf_v, pending_cap, M_tree, n_pending,
                                        accepted, n_accepted, max_accept, mode != SPECPV_MODE_PARTIAL, kmax, kmin,
-                                       lists, dropped, (int32_t *)workspace, (hipStream_t)stream);
+                                       lists, dropped, (uint32_t *)workspace, (hipStream_t)stream);
     return e == hipSuccess ? SPECPV_OK : fail_hip(e);
 }
 

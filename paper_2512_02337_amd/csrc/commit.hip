@@ -9,33 +9,50 @@ namespace specpv {
 
 constexpr int kCommitMaxRows = 128;   // pending + accepted rows one call moves per sequence (host-checked)
 
-// One workgroup per (KV head, sequence); a row of D elements is D * sizeof(T) / 16 lanes.
-// Every source row is read into registers before anything is written (the compaction of
-// the buffer moves rows within one array).
 // Several layers in one launch: blockIdx.z picks the layer's pointers from a table that travels
 // with the kernel arguments.  All layers share one shape, one set of strides and the counters.
 constexpr int kCommitLayers = 32;   // layers per launch
 struct CommitLayers {
     void *k[kCommitLayers], *v[kCommitLayers], *buf_k[kCommitLayers], *buf_v[kCommitLayers];
     void *kmax[kCommitLayers], *kmin[kCommitLayers];
+    int32_t *idx[kCommitLayers], *cnt[kCommitLayers];
 };
+// Sequences per launch: one word each, at the head of the workspace, tells the update which of them had a list without
+// room for a block (0 otherwise; zero before and after the call).
+constexpr int kCommitSeqs = (int)(kArriveBytes / sizeof(uint32_t));
 
+// Everything that a commit does for one (KV head, sequence, layer), by one workgroup; a row of D elements is
+// D * sizeof(T) / 16 lanes.  What bounds it is the chain of cold reads -- counters, then rows, then the touched
+// blocks' older rows -- of a few KiB each, so the whole of it is one launch (copy, lists and summaries as launches of
+// their own took 4.9 + 3.3 + 8.4 us for 32 layers, of which this takes 7.5: the whole call 24 -> 15 us) and only the counters, which every
+// workgroup reads, are moved by a launch behind it.
+//  * Every source row is read into registers before anything is written (the compaction of the buffer moves rows
+//    within one array).
+//  * Lists (Section 3.3: the committed tokens stay part of the partial cache): every block that received a token joins
+//    the kept-block list behind the entries it has, unless it is listed already (the ragged last block of the local
+//    window).
+//  * Summaries (eq. 1) of the blocks that received tokens: a wavefront per block, lanes over 16-byte pieces of a row.
 template <typename T, int D>
-__global__ __launch_bounds__(256) void commit_copy_kernel(Shape s, CommitLayers lay, int P, int Mt,
-                                                          const int32_t *n_pending, const int32_t *accepted,
-                                                          const int32_t *n_accepted, int max_accept, int to_cache)
+__global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, int b0, int P, int Mt, const int32_t *n_pending,
+                                                     const int32_t *accepted, const int32_t *n_accepted, int max_accept, int to_cache,
+                                                     int with_sums, int n_sel, uint32_t *missed_words)
 {
     T *const buf_k = (T *)lay.buf_k[blockIdx.z], *const buf_v = (T *)lay.buf_v[blockIdx.z];
-    s.k = lay.k[blockIdx.z];
-    s.v = lay.v[blockIdx.z];
-    constexpr int LPR = D * (int)sizeof(T) / 16;   // lanes per row
+    T *const cache_k = (T *)lay.k[blockIdx.z], *const cache_v = (T *)lay.v[blockIdx.z];
+    constexpr int E = Elem<T>::kPerVec;
+    constexpr int LPR = D / E;                     // lanes per row
     constexpr int RPP = 256 / LPR;                 // rows per pass
     constexpr int PASSES = (kCommitMaxRows + RPP - 1) / RPP;
-    const int g = blockIdx.x, b = blockIdx.y;
-    const int c = threadIdx.x % LPR, r0 = threadIdx.x / LPR;
+    const int g = blockIdx.x, bl = blockIdx.y, b = b0 + bl;
+    const int c = threadIdx.x % LPR, r0 = threadIdx.x / LPR, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int L = s.ctx_len[b];
-    const int n = min(max(n_pending[b], 0), P);
-    int a = min(max(n_accepted[b], 0), max_accept);
+    const int n_raw = n_pending[b], a_raw = n_accepted[b];
+    // the accepted path, requested with the counters: lane t holds entries t and t + 64 (max_accept <= 128)
+    const int32_t *acc = accepted + (int64_t)b * max_accept;
+    const int acc0 = lane < max_accept ? acc[lane] : 0, acc1 = lane + 64 < max_accept ? acc[lane + 64] : 0;
+    const int n = min(max(n_raw, 0), P);
+    const int a = min(max(a_raw, 0), max_accept);
     int total = n + a;
     if (to_cache) total = min(total, max(0, s.max_blocks * s.B - L));   // the cache is full: the rest is dropped
     else total = min(total, P);
@@ -47,10 +64,13 @@ __global__ __launch_bounds__(256) void commit_copy_kernel(Shape s, CommitLayers 
 #pragma unroll
     for (int p = 0; p < PASSES; ++p) {
         const int i = p * RPP + r0;
+        const int x = i - n;
+        const int e0 = __shfl(acc0, x & 63), e1 = __shfl(acc1, x & 63);
+        kr[p] = vr[p] = make_uint4(0u, 0u, 0u, 0u);
         if (i < total) {
             int src;
-            if (i < n) src = P - n + i;                             // pending token i (oldest first)
-            else src = P + min(max(accepted[(int64_t)b * max_accept + (i - n)], 0), Mt - 1);   // accepted candidate
+            if (i < n) src = P - n + i;                                   // pending token i (oldest first)
+            else src = P + min(max(x < 64 ? e0 : e1, 0), Mt - 1);         // accepted candidate
             kr[p] = *buf_row(buf_k, src);
             vr[p] = *buf_row(buf_v, src);
         }
@@ -62,28 +82,83 @@ __global__ __launch_bounds__(256) void commit_copy_kernel(Shape s, CommitLayers 
         if (i < total) {
             if (to_cache) {
                 const int64_t off = (int64_t)b * s.sb + (int64_t)g * s.sh + (int64_t)(L + i) * s.st;
-                *((uint4 *)((T *)s.k + off) + c) = kr[p];
-                *((uint4 *)((T *)s.v + off) + c) = vr[p];
+                *((uint4 *)(cache_k + off) + c) = kr[p];
+                *((uint4 *)(cache_v + off) + c) = vr[p];
             } else {
                 *buf_row(buf_k, P - total + i) = kr[p];
                 *buf_row(buf_v, P - total + i) = vr[p];
             }
         }
     }
+    if (!to_cache || total == 0 || !(with_sums || n_sel)) return;   // uniform
+    const int first = L / s.B, last = (L + total - 1) / s.B;        // blocks that received tokens (all below max_blocks)
+    if (n_sel && wave == 3) {
+        int32_t *row = lay.idx[blockIdx.z] + ((int64_t)b * s.Hkv + g) * n_sel;
+        int32_t *cntp = lay.cnt[blockIdx.z] + (int64_t)b * s.Hkv + g;
+        const int cnt0 = min(max(*cntp, 0), n_sel);
+        int cnt = cnt0, missed = 0;
+        for (int blk = first; blk <= last; ++blk) {
+            bool here = false;
+            for (int i = lane; i < cnt0; i += 64) here |= row[i] == blk;
+            if (__any(here)) continue;
+            if (cnt < n_sel) { if (lane == 0) row[cnt] = blk; ++cnt; }
+            else ++missed;
+        }
+        if (lane == 0) {
+            *cntp = cnt;
+            if (missed) atomicMax(&missed_words[bl], (uint32_t)missed);
+        }
+    }
+    if (!with_sums) return;
+    __syncthreads();   // the new rows are in the cache (stores of this workgroup, read back by it)
+    constexpr int WRP = 64 / LPR;   // rows per wavefront pass
+    const int wr = lane / LPR;
+    const T *base = cache_k + (int64_t)b * s.sb + (int64_t)g * s.sh + c * E;   // (64 is a multiple of LPR: c is lane % LPR)
+    T *const kmax = (T *)lay.kmax[blockIdx.z], *const kmin = (T *)lay.kmin[blockIdx.z];
+    for (int i = first + wave; i <= last; i += 4) {
+        const int t0 = i * s.B, t1 = min(t0 + s.B, L + total);
+        float mx[E], mn[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) { mx[e] = -INFINITY; mn[e] = INFINITY; }
+        auto fold = [&](const uint4 &u) {
+            float f[E];
+            Elem<T>::unpack(u, f);
+#pragma unroll
+            for (int e = 0; e < E; ++e) { mx[e] = fmaxf(mx[e], f[e]); mn[e] = fminf(mn[e], f[e]); }
+        };
+        for (int t = t0 + wr; t < t1; t += 8 * WRP) {
+            uint4 u[8];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) u[x] = *(const uint4 *)(base + (int64_t)min(t + x * WRP, t1 - 1) * s.st);   // (the last row again: no effect)
+#pragma unroll
+            for (int x = 0; x < 8; ++x) fold(u[x]);
+        }
+#pragma unroll
+        for (int off = LPR; off < 64; off <<= 1) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                mx[e] = fmaxf(mx[e], __shfl_xor(mx[e], off));
+                mn[e] = fminf(mn[e], __shfl_xor(mn[e], off));
+            }
+        }
+        if (wr == 0) {
+            const int64_t o = (((int64_t)b * s.Hkv + g) * s.max_blocks + i) * D + c * E;
+            *(uint4 *)(kmax + o) = Elem<T>::pack(mx);
+            *(uint4 *)(kmin + o) = Elem<T>::pack(mn);
+        }
+    }
 }
 
-// One thread per sequence, after the copies: the new lengths (the old committed length goes to
-// old_len for the summary update).
-__global__ void commit_update_kernel(Shape s, int P, int32_t *ctx_len, int32_t *n_pending,
-                                     const int32_t *n_accepted, int max_accept, int to_cache, int32_t *old_len,
-                                     int32_t *dropped)
+// One thread per sequence, behind everything that reads the counters: the new lengths, and what found no room.
+__global__ void commit_update_kernel(Shape s, int b0, int n_seq, int P, int32_t *ctx_len, int32_t *n_pending,
+                                     const int32_t *n_accepted, int max_accept, int to_cache, uint32_t *missed_words, int32_t *dropped)
 {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= s.batch) return;
+    const int bl = blockIdx.x * blockDim.x + threadIdx.x, b = b0 + bl;
+    if (bl >= n_seq) return;
     const int L = ctx_len[b];
     const int n = min(max(n_pending[b], 0), P);
     const int a = min(max(n_accepted[b], 0), max_accept);
-    old_len[b] = L;
+    const uint32_t missed = missed_words ? missed_words[bl] : 0u;   // nullptr: a commit without lists
     int stored;
     if (to_cache) {
         stored = min(n + a, max(0, s.max_blocks * s.B - L));
@@ -93,84 +168,10 @@ __global__ void commit_update_kernel(Shape s, int P, int32_t *ctx_len, int32_t *
         stored = min(n + a, P);
         n_pending[b] = stored;
     }
+    if (missed) missed_words[bl] = 0u;
     if (dropped) {
-        dropped[2 * b] = n + a - stored;   // tokens that found no room
-        dropped[2 * b + 1] = 0;            // list entries that found no room: commit_extend_lists_kernel
-    }
-}
-
-// After a commit to the cache (Section 3.3: the committed tokens stay part of the partial cache):
-// every block that holds one of the tokens old_len .. new length - 1 joins the kept-block list of
-// each KV head, behind the entries it has, unless the block is listed already (the ragged last
-// block of the local window).  One wavefront per (KV head, sequence, layer).
-struct CommitLists {
-    int32_t *idx[kCommitLayers], *cnt[kCommitLayers];
-};
-__global__ __launch_bounds__(64) void commit_extend_lists_kernel(Shape s, CommitLists ls, int n_sel,
-                                                                 const int32_t *old_len, int32_t *dropped)
-{
-    const int g = blockIdx.x, b = blockIdx.y, lane = threadIdx.x;
-    const int L = s.ctx_len[b], L0 = old_len[b];
-    if (L <= L0) return;
-    int32_t *row = ls.idx[blockIdx.z] + ((int64_t)b * s.Hkv + g) * n_sel;
-    int32_t *cntp = ls.cnt[blockIdx.z] + (int64_t)b * s.Hkv + g;
-    const int cnt0 = min(max(*cntp, 0), n_sel);
-    const int first = L0 / s.B, last = (L - 1) / s.B;
-    int cnt = cnt0, missed = 0;
-    for (int blk = first; blk <= last; ++blk) {
-        bool here = false;
-        for (int i = lane; i < cnt0; i += 64) here |= row[i] == blk;
-        if (__any(here)) continue;
-        if (cnt < n_sel) { if (lane == 0) row[cnt] = blk; ++cnt; }
-        else ++missed;
-    }
-    if (lane == 0) {
-        *cntp = cnt;
-        if (missed && dropped) atomicMax(&dropped[2 * b + 1], missed);
-    }
-}
-
-// eq. 1 for the blocks old_len / B .. (new length - 1) / B of every sequence: one wavefront per
-// (block, KV head), lanes over 16-byte pieces of a row, rows strided over the lane groups.
-template <typename T, int D>
-__global__ __launch_bounds__(64) void summarize_tail_kernel(Shape s, CommitLayers lay, const int32_t *old_len)
-{
-    constexpr int E = Elem<T>::kPerVec;
-    constexpr int LPR = D / E;
-    constexpr int RPP = 64 / LPR;
-    const int layer = blockIdx.z / s.batch;
-    const int lane = threadIdx.x, g = blockIdx.y, b = blockIdx.z - layer * s.batch;
-    void *const kmax = lay.kmax[layer], *const kmin = lay.kmin[layer];
-    s.k = lay.k[layer];
-    const int L = s.ctx_len[b], L0 = old_len[b];
-    if (L <= L0) return;
-    const int i = L0 / s.B + blockIdx.x;
-    if (i >= s.max_blocks || (int64_t)i * s.B >= L) return;
-    const int t0 = i * s.B, t1 = min(t0 + s.B, L);
-    const int c = lane % LPR, rsub = lane / LPR;
-    const T *base = (const T *)s.k + (int64_t)b * s.sb + (int64_t)g * s.sh + c * E;
-    float mx[E], mn[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) { mx[e] = -INFINITY; mn[e] = INFINITY; }
-    for (int t = t0 + rsub; t < t1; t += RPP) {
-        const uint4 u = *(const uint4 *)(base + (int64_t)t * s.st);
-        float f[E];
-        Elem<T>::unpack(u, f);
-#pragma unroll
-        for (int e = 0; e < E; ++e) { mx[e] = fmaxf(mx[e], f[e]); mn[e] = fminf(mn[e], f[e]); }
-    }
-#pragma unroll
-    for (int off = LPR; off < 64; off <<= 1) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            mx[e] = fmaxf(mx[e], __shfl_xor(mx[e], off));
-            mn[e] = fminf(mn[e], __shfl_xor(mn[e], off));
-        }
-    }
-    if (rsub == 0) {
-        const int64_t o = (((int64_t)b * s.Hkv + g) * s.max_blocks + i) * D + c * E;
-        *(uint4 *)((T *)kmax + o) = Elem<T>::pack(mx);
-        *(uint4 *)((T *)kmin + o) = Elem<T>::pack(mn);
+        dropped[2 * b] = n + a - stored;        // tokens that found no room
+        dropped[2 * b + 1] = (int32_t)missed;   // list entries that found no room
     }
 }
 
@@ -180,62 +181,39 @@ hipError_t launch_commit(const Shape &s, int dtype, int n_layers, void *const *k
                          void *const *buf_k, void *const *buf_v, int P, int Mt,
                          int32_t *n_pending, const int32_t *accepted, const int32_t *n_accepted,
                          int max_accept, int to_cache, void *const *kmax, void *const *kmin,
-                         const specpv_lists *lists, int32_t *dropped, int32_t *old_len, hipStream_t st)
+                         const specpv_lists *lists, int32_t *dropped, uint32_t *missed_words, hipStream_t st)
 {
     if (P + max_accept > kCommitMaxRows) return hipErrorInvalidValue;
     const bool summaries = to_cache && kmax && kmin && kmax[0] && kmin[0];
-    // the copies of every layer read the counters, so all of them go before the update
-    for (int l0 = 0; l0 < n_layers; l0 += kCommitLayers) {
-        const int nl = n_layers - l0 < kCommitLayers ? n_layers - l0 : kCommitLayers;
-        CommitLayers lay = {};
-        for (int l = 0; l < nl; ++l) {
-            lay.k[l] = k[l0 + l]; lay.v[l] = v[l0 + l];
-            lay.buf_k[l] = buf_k[l0 + l]; lay.buf_v[l] = buf_v[l0 + l];
-        }
-        const dim3 grid(s.Hkv, s.batch, nl);
-#define SPECPV_COPY(T, DD)                                                                             \
-    hipLaunchKernelGGL((commit_copy_kernel<T, DD>), grid, dim3(256), 0, st, s, lay, P, Mt,              \
-                       n_pending, accepted, n_accepted, max_accept, to_cache)
-        if (dtype == SPECPV_BF16) {
-            if (s.D == 128) SPECPV_COPY(bf16_t, 128); else SPECPV_COPY(bf16_t, 64);
-        } else {
-            if (s.D == 128) SPECPV_COPY(float, 128); else SPECPV_COPY(float, 64);
-        }
-#undef SPECPV_COPY
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(commit_update_kernel, dim3((s.batch + 63) / 64), dim3(64), 0, st, s, P,
-                       (int32_t *)s.ctx_len, n_pending, n_accepted, max_accept, to_cache, old_len, dropped);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (to_cache && lists) {
+    const bool with_lists = to_cache && lists;
+    for (int b0 = 0; b0 < s.batch; b0 += kCommitSeqs) {
+        const int n_seq = s.batch - b0 < kCommitSeqs ? s.batch - b0 : kCommitSeqs;
+        // the workgroups of every layer read the counters, so all of them go before the update
         for (int l0 = 0; l0 < n_layers; l0 += kCommitLayers) {
             const int nl = n_layers - l0 < kCommitLayers ? n_layers - l0 : kCommitLayers;
-            CommitLists ls = {};
-            for (int l = 0; l < nl; ++l) { ls.idx[l] = lists[l0 + l].sel_idx; ls.cnt[l] = lists[l0 + l].sel_count; }
-            hipLaunchKernelGGL(commit_extend_lists_kernel, dim3(s.Hkv, s.batch, nl), dim3(64), 0, st, s, ls,
-                               lists[0].n_sel, old_len, dropped);
-            e = hipGetLastError();
+            CommitLayers lay = {};
+            for (int l = 0; l < nl; ++l) {
+                lay.k[l] = k[l0 + l]; lay.v[l] = v[l0 + l];
+                lay.buf_k[l] = buf_k[l0 + l]; lay.buf_v[l] = buf_v[l0 + l];
+                if (summaries) { lay.kmax[l] = kmax[l0 + l]; lay.kmin[l] = kmin[l0 + l]; }
+                if (with_lists) { lay.idx[l] = lists[l0 + l].sel_idx; lay.cnt[l] = lists[l0 + l].sel_count; }
+            }
+            const dim3 grid(s.Hkv, n_seq, nl);
+#define SPECPV_COMMIT(T, DD)                                                                                                      \
+    hipLaunchKernelGGL((commit_kernel<T, DD>), grid, dim3(256), 0, st, s, lay, b0, P, Mt, n_pending, accepted, n_accepted, max_accept, \
+                       to_cache, summaries ? 1 : 0, with_lists ? lists[0].n_sel : 0, missed_words)
+            if (dtype == SPECPV_BF16) {
+                if (s.D == 128) SPECPV_COMMIT(bf16_t, 128); else SPECPV_COMMIT(bf16_t, 64);
+            } else {
+                if (s.D == 128) SPECPV_COMMIT(float, 128); else SPECPV_COMMIT(float, 64);
+            }
+#undef SPECPV_COMMIT
+            const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
-    }
-    if (!summaries) return hipSuccess;
-    // blocks that can have received one of at most P + max_accept tokens
-    const int touched = (P + max_accept + s.B - 1) / s.B + 1;
-    for (int l0 = 0; l0 < n_layers; l0 += kCommitLayers) {
-        const int nl = n_layers - l0 < kCommitLayers ? n_layers - l0 : kCommitLayers;
-        CommitLayers lay = {};
-        for (int l = 0; l < nl; ++l) { lay.k[l] = k[l0 + l]; lay.kmax[l] = kmax[l0 + l]; lay.kmin[l] = kmin[l0 + l]; }
-        const dim3 g2(touched, s.Hkv, s.batch * nl);
-#define SPECPV_SUM(T, DD) hipLaunchKernelGGL((summarize_tail_kernel<T, DD>), g2, dim3(64), 0, st, s, lay, old_len)
-        if (dtype == SPECPV_BF16) {
-            if (s.D == 128) SPECPV_SUM(bf16_t, 128); else SPECPV_SUM(bf16_t, 64);
-        } else {
-            if (s.D == 128) SPECPV_SUM(float, 128); else SPECPV_SUM(float, 64);
-        }
-#undef SPECPV_SUM
-        e = hipGetLastError();
+        hipLaunchKernelGGL(commit_update_kernel, dim3((n_seq + 63) / 64), dim3(64), 0, st, s, b0, n_seq, P,
+                           (int32_t *)s.ctx_len, n_pending, n_accepted, max_accept, to_cache, with_lists ? missed_words : nullptr, dropped);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

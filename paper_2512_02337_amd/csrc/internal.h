@@ -181,7 +181,8 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
 int attn_group_parts(const Shape &s);
 hipError_t launch_combine(const Shape &s, int dtype, Partials p, void *out, float *lse, hipStream_t st);
 // to_cache != 0: pending + accepted rows go to the cache tail (lengths, summaries updated);
-// otherwise the accepted rows join the pending rows of the buffer.  old_len: [batch] scratch.
+// otherwise the accepted rows join the pending rows of the buffer.  missed_words: the zeroed words at the
+// head of a workspace (kArriveBytes; zero again when the launches have finished).
 // n_layers layers that share shape, strides and counters are committed together.
 // lists (n_layers entries, or nullptr): kept-block lists that take in the blocks a commit to the
 // cache touches.  dropped ([batch, 2], or nullptr): tokens not stored, list entries not found.
@@ -189,7 +190,7 @@ hipError_t launch_commit(const Shape &s, int dtype, int n_layers, void *const *k
                          void *const *buf_k, void *const *buf_v, int P, int Mt,
                          int32_t *n_pending, const int32_t *accepted, const int32_t *n_accepted,
                          int max_accept, int to_cache, void *const *kmax, void *const *kmin,
-                         const specpv_lists *lists, int32_t *dropped, int32_t *old_len,
+                         const specpv_lists *lists, int32_t *dropped, uint32_t *missed_words,
                          hipStream_t st);
 
 hipError_t launch_gather(const Shape &s, int dtype, const int32_t *sel_idx, const int32_t *sel_count, int n_sel,
