@@ -97,12 +97,66 @@ static Shape make_shape(const specpv_kv *kv, const specpv_tree *tree)
     return s;
 }
 
+// What a call with bf16 at 128 channels would take, in microseconds, with one of the matrix-core kernels and `ns` splits,
+// less what does not depend on that choice: fitted to about 25000 timings of whole calls (HIP graph replays; 1 to 78 nodes,
+// G = 2, 4, 5 and 8, 2 to 128 (sequence, KV head) pairs, 512 to 131072 attended tokens; residual 6 %, and choosing by it
+// loses 0.5 % against the best measured choice of each shape).  A workgroup per CU at a time takes its token range, p
+// chunks one after the other, in `rounds`; besides that the K / V bytes have to come out of the L2s (once per tile) and
+// of HBM; partials are written and read back.
+struct AttnCost {
+    const Shape &s;
+    int64_t chunks;
+    double kv;   // MB of K and V
+    AttnCost(const Shape &sh, int64_t ch) : s(sh), chunks(ch), kv((double)sh.batch * sh.Hkv * (double)ch * 16384e-6) {}
+    double us(int64_t rounds, int64_t p, double start, double per_chunk, int64_t tiles, int64_t ns) const
+    {
+        const double chain = (double)rounds * (start + (double)p * per_chunk);
+        const double memory = kv * (0.021 * (double)tiles + 0.116);
+        const double partials = (double)s.batch * s.Hkv * (double)ns * s.M * s.G * 512e-6;   // MB
+        return sqrt(chain * chain + memory * memory) + (ns > 16 ? 0.77 : 0.0) + 0.192 * partials;
+    }
+    // the tile kernel with tg token groups (attn_tile.hip)
+    double tile(int tg, int64_t ns, int64_t cus) const
+    {
+        const int64_t rows = 256 / tg, tiles = ((int64_t)s.M * s.G + rows - 1) / rows, bg = (int64_t)s.batch * s.Hkv;
+        // (pairs that are a multiple of 8 stay on their XCD)
+        const int64_t rounds = bg % 8 ? (bg * tiles * ns + cus - 1) / cus : (bg / 8 * tiles * ns + cus / 8 - 1) / (cus / 8);
+        const int64_t p = (chunks + ns * tg - 1) / (ns * tg);
+        return us(rounds, p, tg == 2 ? 2.10 : (tg == 4 ? 1.64 : 1.71), tg == 2 ? 0.97 : (tg == 4 ? 1.49 : 2.11), tiles, ns);
+    }
+    // the group kernel (attn_mfma.hip)
+    double group(int parts, int waves, int64_t ns, int64_t cus) const
+    {
+        const int64_t rounds = ((int64_t)s.batch * s.Hkv * parts * ns + cus - 1) / cus, p = (chunks + ns - 1) / ns;
+        const double c = waves <= 2 ? 0.61 : (waves <= 4 ? 0.65 : (waves <= 6 ? 0.84 : (waves <= 8 ? 0.89 : 1.32)));
+        return us(rounds, p, 2.11, c, parts, ns);
+    }
+};
+
+// The fewest splits that specpv_partial_verify_attn_static has to have room for: the count by which a shape was first
+// judged to fit its array (as fp32 partials).  Calls that fitted then still do (plan_attention).
+static int64_t first_splits(const Shape &s, int64_t chunks, int64_t cus)
+{
+    auto best_of = [&](int64_t base, int64_t ranges, int64_t most) {
+        int64_t ns = 1, best = -1;
+        for (int64_t c = 1; c <= most; ++c) {
+            const int64_t cost = (base * c + cus - 1) / cus * ((chunks + ranges * c - 1) / (ranges * c) * 8 + 10) + c;
+            if (best < 0 || cost < best) { best = cost; ns = c; }
+        }
+        return ns;
+    };
+    auto at_most = [](int64_t c) { return c < 1 ? (int64_t)1 : (c < 64 ? c : (int64_t)64); };
+    const int64_t ns = best_of((int64_t)s.batch * s.Hq * ((s.M + 63) / 64), 4, at_most(chunks / 4));
+    return chunks >= 32 * ns ? best_of((int64_t)s.batch * s.Hkv * attn_group_parts(s), 1, at_most(chunks / 8)) : ns;
+}
+
 // Which kernel the context part of the attention runs on and how many KV splits it uses when
 // it covers n_blocks blocks per (sequence, KV head).  Host-only and deterministic in its
-// arguments, so specpv_workspace_bytes and the calls agree.
-static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks)
+// arguments, so specpv_workspace_bytes and the calls agree.  full: every block of sequences whose
+// lengths only the device knows (n_blocks is the most that any of them has).
+static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool full)
 {
-    AttnPlan plan{1, !attn_ctx_mfma_supported(s, dtype) ? kAttnGeneric : (s.D == 64 ? kAttnGroup : kAttnSplit)};
+    AttnPlan plan{1, !attn_ctx_mfma_supported(s, dtype) ? kAttnGeneric : (s.D == 64 ? kAttnGroup : kAttnSplit), 4};
     // splits that give 4096 (row, split) pairs of 64 tokens or more each
     const int64_t rows = (int64_t)s.batch * s.Hq * s.M;
     auto few_splits = [&](int64_t tokens) {
@@ -112,77 +166,29 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks)
         if (ns > 64) ns = 64;
         return ns < 1 ? (int64_t)1 : ns;
     };
-    const int64_t tokens = n_blocks * s.B;
+    // (a list may have room for more blocks than there are)
+    const int64_t tokens = (n_blocks < s.max_blocks ? n_blocks : (int64_t)s.max_blocks) * s.B;
     if (tokens <= 0) return plan;
-    // what specpv_partial_verify_attn_static took with the few splits of fp32 partials must fit its array with more:
-    // no more splits than have room, where the few have
-    auto static_room = [&](int64_t few, int64_t ns) {
-        const int64_t slot = rows * (s.D + 2) * (int64_t)sizeof(float);
-        const int64_t room = ((int64_t)SPECPV_STATIC_SCRATCH_BYTES - (int64_t)kArriveBytes - 1024 -
-                              (int64_t)s.batch * s.Hkv * s.max_blocks * (int64_t)sizeof(float)) / slot - 1;
-        return ns > room && room >= few ? room : ns;
+    // what specpv_partial_verify_attn_static took with the splits of fp32 partials that a call had at first must fit its
+    // array with more of them: no more splits than have room, where those few have
+    auto static_room = [&](auto few_of, int64_t ns) {
+        const bool half = plan.kind != kAttnGeneric && s.D == 128;
+        const int64_t slot = rows * (s.D + 2) * (int64_t)sizeof(float), bytes = half ? rows * (2 * s.D + 8) : slot;
+        const int64_t fixed = (int64_t)kArriveBytes + 1024;
+        const int64_t room = ((int64_t)SPECPV_STATIC_SCRATCH_BYTES - fixed) / bytes - (half ? 0 : 1);
+        if (ns <= room || room < 1) return ns;
+        const bool few_fit = fixed + slot * (few_of() + 1) + (int64_t)s.batch * s.Hkv * s.max_blocks * (int64_t)sizeof(float) <= (int64_t)SPECPV_STATIC_SCRATCH_BYTES;
+        return few_fit ? room : ns;
     };
-    if (plan.kind != kAttnGeneric) {
-        const int64_t chunks = (tokens + 31) / 32;   // 32-token chunks per (sequence, KV head)
-        // workgroups that the chip holds at once: one per CU (the LDS), two of the 64-channel kernel's
-        const int64_t cus = (int64_t)device_cu_count() * (s.D == 64 ? 2 : 1);
-        const int64_t row_tiles = (s.M + 63) / 64;
-        // splits c that minimise the chunk-times on the critical path (one workgroup per CU, `base`
-        // workgroups per split, `ranges` token ranges per workgroup), plus a charge for the
-        // epilogue and the partials
-        auto best_splits = [&](int64_t base, int64_t ranges, int64_t max_ns) {
-            int64_t best = 1, best_cost = -1;
-            for (int64_t c = 1; c <= max_ns; ++c) {
-                const int64_t rounds = (base * c + cus - 1) / cus;
-                const int64_t per_wave = (chunks + ranges * c - 1) / (ranges * c);
-                const int64_t cost = rounds * (per_wave * 8 + 10) + c;
-                if (best_cost < 0 || cost < best_cost) { best = c; best_cost = cost; }
-            }
-            return best;
-        };
-        // a workgroup per (sequence, query head, 64-node row tile, split), four token ranges each
-        const int64_t max4 = chunks / 4 > 1 ? (chunks / 4 < 64 ? chunks / 4 : 64) : 1;
-        int64_t ns = best_splits((int64_t)s.batch * s.Hq * row_tiles, 4, max4);
-        // Long token ranges per wavefront amortise the longer prologue and epilogue of the kernels
-        // with more rows per wavefront; at a handful of chunks the eight-wavefront kernel hides
-        // latency better.
-        // (64 channels: only the group kernel)
-        if (s.D == 64 || chunks >= 8 * 4 * ns) {
-            // a few workgroups per (sequence, KV head, split) that cover the group's query rows, one
-            // token range each
-            plan.kind = kAttnGroup;
-            const int64_t shortest = s.D == 64 ? 4 : 8;   // chunks per split
-            int64_t max1 = chunks / shortest > 1 ? (chunks / shortest < 64 ? chunks / shortest : 64) : 1;
-            const int64_t few = few_splits(tokens);
-            if (s.D == 64) {
-                max1 = static_room(few, max1);
-                // up to 1024 tokens: the few splits of the vector-ALU kernel are enough
-                if (chunks <= 32 && max1 > few) max1 = few;
-            }
-            const int64_t base1 = (int64_t)s.batch * s.Hkv * attn_group_parts(s);
-            ns = best_splits(base1, 1, max1);
-            if (s.batch > 1) {
-                // The sequences of a batch may differ in length, and the lengths live on the device:
-                // many small workgroups (about four per CU, 64 chunks or more each: shorter ones are
-                // mostly prologue and epilogue) let the hardware scheduler even that out (measured on
-                // 32K + 64K + 96K + 128K at G = 5: 1089 -> 841 us with eight workgroups of six wavefronts per
-                // CU; with workgroups of ten, 752 us at eight per CU, 687 at four, 704 at two: every split
-                // is another partial for the combine, 85 us at 64 splits against 37 at 32).
-                int64_t c = (4 * cus + base1 - 1) / base1;
-                if (c > max1) c = max1;
-                while (c > ns && (chunks + c - 1) / c < 64) --c;
-                if (c > ns) ns = c;
-            }
-        }
-        plan.nsplit = (int)ns;
-    } else {
+    const int64_t cus = device_cu_count();
+    if (plan.kind == kAttnGeneric) {
         // two wavefronts of 32 rows per SIMD, 64 tokens or more each (the few splits up to 1024 tokens, and half that many
         // tokens each for the shortest ranges, whose time is one wavefront's chain)
         const int64_t few = few_splits(tokens);
         int64_t ns = few;
         if (tokens > 1024) {
             const int64_t waves = (int64_t)((s.G * s.M + 31) / 32) * s.batch * s.Hkv;
-            ns = (8 * (int64_t)device_cu_count() + waves - 1) / waves;
+            ns = (8 * cus + waves - 1) / waves;
             if (ns > tokens / 64) ns = tokens / 64;
             if (ns > 64) ns = 64;
             if (ns < few) ns = few;
@@ -192,17 +198,71 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks)
             ns = want < most ? want : most;
             if (ns < few) ns = few;
         }
-        plan.nsplit = (int)static_room(few, ns);
+        plan.nsplit = (int)static_room([&] { return few; }, ns);
+    } else {
+        const int64_t chunks = (tokens + 31) / 32;   // 32-token chunks per (sequence, KV head)
+        const int parts = attn_group_parts(s);
+        const int64_t base = (int64_t)s.batch * s.Hkv * parts;   // group kernel: workgroups per split
+        int64_t ns = 1;
+        if (s.D == 64) {
+            // the group kernel; two workgroups share a CU, four chunks or more per split
+            const int64_t slots = 2 * cus;
+            int64_t most = chunks / 4 > 1 ? (chunks / 4 < 64 ? chunks / 4 : 64) : 1, best = -1;
+            const int64_t few = few_splits(tokens);
+            most = static_room([&] { return few; }, most);
+            // up to 1024 tokens: the few splits of the vector-ALU kernel are enough
+            if (chunks <= 32 && most > few) most = few;
+            for (int64_t c = 1; c <= most; ++c) {
+                const int64_t cost = (base * c + slots - 1) / slots * ((chunks + c - 1) / c * 8 + 10) + c;
+                if (best < 0 || cost < best) { best = cost; ns = c; }
+            }
+            if (s.batch > 1) {
+                int64_t c = (4 * slots + base - 1) / base;
+                if (c > most) c = most;
+                while (c > ns && (chunks + c - 1) / c < 64) --c;
+                if (c > ns) ns = c;
+            }
+        } else {
+            const AttnCost cost(s, chunks);
+            const int waves = attn_group_waves(s);
+            double best = -1.0;
+            auto take = [&](double us, int kind, int tg, int64_t c) {
+                if (best < 0.0 || us < best) { best = us; plan.kind = kind; plan.tg = tg; ns = c; }
+            };
+            // split counts that divide evenly, those that the combine kernel takes in one go, and those that fill the chip
+            int64_t cand[16] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
+            for (int k = 1; k <= 4; ++k) cand[11 + k] = k * cus / base;
+            for (int64_t c : cand) {
+                if (c < 1 || c > 64) continue;
+                for (int tg = 2; tg <= 8; tg *= 2)
+                    if (c * tg <= 2 * chunks) take(cost.tile(tg, c, cus), kAttnSplit, tg, c);
+                if (chunks >= 2 * c) take(cost.group(parts, waves, c, cus), kAttnGroup, 4, c);
+            }
+            if (full && s.batch > 1 && plan.kind == kAttnGroup) {
+                // The sequences of a batch may differ in length, and the lengths live on the device:
+                // many small workgroups (about four per CU, 64 chunks or more each: shorter ones are
+                // mostly prologue and epilogue) let the hardware scheduler even that out (measured on
+                // 32K + 64K + 96K + 128K at G = 5: 752 us at eight per CU, 687 at four, 704 at two: every split
+                // is another partial for the combine, 85 us at 64 splits against 37 at 32).
+                int64_t c = (4 * cus + base - 1) / base;
+                if (c > 64) c = 64;
+                while (c > ns && (chunks + c - 1) / c < 64) --c;
+                if (c > ns) ns = c;
+            }
+            ns = static_room([&] { return first_splits(s, chunks, cus); }, ns);
+        }
+        plan.nsplit = (int)ns;
     }
     return plan;
 }
 
 // Workspace layout: [arrival words, kArriveBytes, zero between calls][partial O][(m, l) pairs][scores],
-// the partial arrays sized for nsplit + 1 slots (the context splits and the draft-tree segment).
+// the partial arrays sized for nsplit + 1 slots of fp32 (the context splits and the draft-tree segment).  fp16 partials
+// take less: `half_total` bytes with the pairs right behind them and no scores.
 struct Workspace {
     unsigned long long *arrive;
-    float *part_o, *part_ml, *scores;
-    size_t total;
+    float *part_o, *part_ml, *scores, *half_ml;
+    size_t total, half_total;
 };
 
 static Workspace layout_workspace(const Shape &s, int nsplit, void *base)
@@ -218,6 +278,9 @@ static Workspace layout_workspace(const Shape &s, int nsplit, void *base)
     w.part_ml = (float *)(p + kArriveBytes + po);
     w.scores = (float *)(p + kArriveBytes + po + pm);
     w.total = kArriveBytes + po + pm + sc;
+    const size_t ho = align_up((size_t)s.batch * s.Hq * nsplit * s.M * s.D * sizeof(uint16_t));
+    w.half_ml = (float *)(p + kArriveBytes + ho);
+    w.half_total = kArriveBytes + ho + align_up((size_t)s.batch * s.Hq * nsplit * s.M * 2 * sizeof(float));
     return w;
 }
 
@@ -228,20 +291,21 @@ static unsigned long long *g_timeline = nullptr;   // where instrumented builds 
 
 static int run_attention(const Shape &s_in, int dtype, const int32_t *sel_idx, const int32_t *sel_count,
                          int n_sel, void *out, float *lse, void *workspace, size_t workspace_bytes,
-                         hipStream_t st)
+                         bool own_scratch, hipStream_t st)
 {
-    const AttnPlan plan = plan_attention(s_in, dtype, sel_idx ? n_sel : s_in.max_blocks);
+    const AttnPlan plan = plan_attention(s_in, dtype, sel_idx ? n_sel : s_in.max_blocks, !sel_idx);
     Shape s = s_in;
     // the matrix-core kernels take the partially verified tokens in front of the tree along with the cache
     // tokens (dense: every query row attends all of them); the vector-ALU kernel leaves them to the combine
     s.kctx = plan.kind != kAttnGeneric ? s.koff : 0;
     const int nsplit = plan.nsplit;
     const Workspace w = layout_workspace(s, nsplit, workspace);
-    if (!workspace || workspace_bytes < w.total) return SPECPV_EWORKSPACE;
+    const bool half = plan.kind != kAttnGeneric && s.D == 128;   // fp16 partials
+    if (!workspace || workspace_bytes < (own_scratch && half ? w.half_total : w.total)) return SPECPV_EWORKSPACE;
     const int route = __atomic_load_n(&g_route, __ATOMIC_RELAXED);
     // The single-kernel route is correct but measured slower than two launches (the last workgroup of a
     // tile reads all of the tile's partials through one CU): it runs only on request.
-    const bool fused = plan.kind == kAttnSplit && route >= 2 && nsplit <= 64 &&
+    const bool fused = plan.kind == kAttnSplit && route >= 2 && nsplit <= 64 && workspace_bytes >= w.total &&
                        (size_t)s.batch * s.Hq * 2 * sizeof(unsigned long long) <= kArriveBytes;
     hipError_t e;
     if (fused) {
@@ -250,9 +314,10 @@ static int run_attention(const Shape &s_in, int dtype, const int32_t *sel_idx, c
         e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, f, st);
         return e == hipSuccess ? SPECPV_OK : fail_hip(e);
     }
-    Partials p{w.part_o, w.part_ml, nsplit, plan.kind != kAttnGeneric && s.D == 128 ? 1 : 0, g_timeline};
+    Partials p{w.part_o, half ? w.half_ml : w.part_ml, nsplit, half ? 1 : 0, g_timeline};
     const FusedArgs none{nullptr, nullptr, nullptr, 0, g_timeline};
-    if (plan.kind != kAttnGeneric) e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, none, st);
+    if (plan.kind == kAttnSplit) e = launch_attn_ctx_tile(s, sel_idx, sel_count, n_sel, p, plan.tg, g_timeline, st);
+    else if (plan.kind != kAttnGeneric) e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, none, st);
     else e = launch_attn_ctx_generic(s, dtype, sel_idx, sel_count, n_sel, p, st);
     if (e != hipSuccess) return fail_hip(e);
     e = launch_combine(s, dtype, p, out, lse, st);
@@ -321,10 +386,10 @@ size_t specpv_workspace_bytes(const specpv_kv *kv, const specpv_tree *tree, cons
     if (!tree) return kArriveBytes + align_up((size_t)kv->batch * sizeof(int32_t));
     if (check_tree(kv, tree, false) != SPECPV_OK) return 0;
     const Shape s = make_shape(kv, tree);
-    int nsplit = plan_attention(s, kv->dtype, s.max_blocks).nsplit;
+    int nsplit = plan_attention(s, kv->dtype, s.max_blocks, true).nsplit;
     if (cfg) {
         const int64_t n_sel = (int64_t)cfg->n_sink_blocks + cfg->k_blocks + cfg->n_recent_blocks + cfg->n_extra_slots;
-        const int n2 = plan_attention(s, kv->dtype, n_sel).nsplit;
+        const int n2 = plan_attention(s, kv->dtype, n_sel, false).nsplit;
         if (n2 > nsplit) nsplit = n2;
     }
     return layout_workspace(s, nsplit, nullptr).total;
@@ -374,7 +439,7 @@ int specpv_partial_verify_attn(const specpv_kv *kv, const specpv_tree *tree, con
     if (sel_idx && (!sel_count || n_sel < 0)) return SPECPV_EINVAL;
     if (sel_idx && n_sel > (1 << 24)) return SPECPV_ELIMIT;
     const Shape s = make_shape(kv, tree);
-    return run_attention(s, kv->dtype, sel_idx, sel_count, n_sel, out, lse, workspace, workspace_bytes,
+    return run_attention(s, kv->dtype, sel_idx, sel_count, n_sel, out, lse, workspace, workspace_bytes, false,
                          (hipStream_t)stream);
 }
 
@@ -389,16 +454,18 @@ int specpv_partial_verify_attn_static(const specpv_kv *kv, const specpv_tree *tr
     if (sel_idx && n_sel > (1 << 24)) return SPECPV_ELIMIT;
     const Shape s = make_shape(kv, tree);
     // the same plan as specpv_partial_verify_attn; its partial results must fit the static array
-    const AttnPlan plan = plan_attention(s, kv->dtype, sel_idx ? n_sel : s.max_blocks);
-    if (layout_workspace(s, plan.nsplit, nullptr).total > (size_t)SPECPV_STATIC_SCRATCH_BYTES) {
+    const AttnPlan plan = plan_attention(s, kv->dtype, sel_idx ? n_sel : s.max_blocks, !sel_idx);
+    const Workspace w = layout_workspace(s, plan.nsplit, nullptr);
+    const size_t need = plan.kind != kAttnGeneric && s.D == 128 ? w.half_total : w.total;
+    if (need > (size_t)SPECPV_STATIC_SCRATCH_BYTES) {
         snprintf(g_hip_err, sizeof(g_hip_err), "static scratch: the call needs %zu bytes, the array holds %zu",
-                 layout_workspace(s, plan.nsplit, nullptr).total, (size_t)SPECPV_STATIC_SCRATCH_BYTES);
+                 need, (size_t)SPECPV_STATIC_SCRATCH_BYTES);
         return SPECPV_ELIMIT;
     }
     void *ws = nullptr;
     const hipError_t e = static_scratch(&ws);
     if (e != hipSuccess) return fail_hip(e);
-    return run_attention(s, kv->dtype, sel_idx, sel_count, n_sel, out, lse, ws, (size_t)SPECPV_STATIC_SCRATCH_BYTES,
+    return run_attention(s, kv->dtype, sel_idx, sel_count, n_sel, out, lse, ws, (size_t)SPECPV_STATIC_SCRATCH_BYTES, true,
                          (hipStream_t)stream);
 }
 
@@ -414,7 +481,7 @@ int specpv_full_verify_refresh(const specpv_kv *kv, const specpv_tree *tree, voi
     if (!kmax || !kmin || !out || !sel_idx || !sel_count) return SPECPV_EINVAL;
     if (((uintptr_t)kmax | (uintptr_t)kmin | (uintptr_t)out) & 15) return SPECPV_EINVAL;
     const Shape s = make_shape(kv, tree);
-    const int nsplit = plan_attention(s, kv->dtype, s.max_blocks).nsplit;
+    const int nsplit = plan_attention(s, kv->dtype, s.max_blocks, true).nsplit;
     const Workspace w = layout_workspace(s, nsplit, workspace);
     if (!workspace || workspace_bytes < w.total) return SPECPV_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
@@ -422,7 +489,7 @@ int specpv_full_verify_refresh(const specpv_kv *kv, const specpv_tree *tree, voi
         const hipError_t e = launch_summarize(s, kv->dtype, stale_blk_begin, -1, kmax, kmin, st);
         if (e != hipSuccess) return fail_hip(e);
     }
-    rc = run_attention(s, kv->dtype, nullptr, nullptr, 0, out, lse, workspace, workspace_bytes, st);
+    rc = run_attention(s, kv->dtype, nullptr, nullptr, 0, out, lse, workspace, workspace_bytes, false, st);
     if (rc != SPECPV_OK) return rc;
     return run_select(s, kv->dtype, tree, kmax, kmin, cfg, sel_idx, sel_count, scores ? scores : w.scores, w.arrive, st);
 }

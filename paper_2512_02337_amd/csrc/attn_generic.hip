@@ -2,7 +2,7 @@
 // instructions (fp32 inputs, and bf16 caches too large for the 32-bit offsets of the bf16 kernels).  Products and
 // sums are fp32, as on the vector ALU, at twice its rate.
 //
-// A wavefront owns NR tiles of 16 query rows of a KV head (row r = node r / G, head r % G of the group) and one KV
+// A wavefront owns NR tiles of 16 query rows of a KV head (row r = head r / M of the group, node r % M) and one KV
 // split, and walks the split's tokens 16 at a time (v_mfma_f32_16x16x4_f32):
 //   S^T = K . Q^T     lane & 15 = token of the A operand, query row of the B operand; lane / 16 picks the channels
 //                     16 i + 4 (lane / 16) .. + 3, so both come from memory as 16-byte pieces, no LDS in between;
@@ -57,7 +57,7 @@ void attn_ctx_generic_kernel(Shape s, const int32_t *sel_idx, const int32_t *sel
 #pragma unroll
     for (int t = 0; t < NR; ++t) {
         const int r = min(r0 + 16 * t + n, R - 1);   // rows past the end repeat the last one; never stored
-        const int j = r / s.G, hh = r - j * s.G;
+        const int hh = r / s.M, j = r - hh * s.M;
         const T *qrow = (const T *)s.q + (((int64_t)b * s.M + j) * s.Hq + g * s.G + hh) * D + 4 * kg;
 #pragma unroll
         for (int i = 0; i < KQ; ++i) q[t][i] = Quad<T>::load(qrow + 16 * i);

@@ -1,0 +1,248 @@
+// What the matrix-core attention kernels share: operand types, the layout of a 32-token chunk in LDS, LDS-DMA and the
+// hand-written LDS reads, and the form in which partial results are stored.
+#pragma once
+#include "internal.h"
+#include <type_traits>
+
+namespace specpv {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((address_space(3))) void *lds_void_ptr;
+typedef const __attribute__((address_space(1))) void *glb_void_ptr;
+
+constexpr int kOPitch = 132;         // floats per staged output row (128 + 4: conflict-free 16-byte writes)
+// One 32-token chunk in LDS: 8 KiB of K (row-major, 16-byte pieces XOR-swizzled by row & 15: the LDS has 64
+// banks, so the 16 lanes that a 16-byte read serves per cycle must cover all 16 pieces of a 256-byte bank row;
+// with row & 7 the operand reads ran at half the rate) and
+// the V rows in 8 pieces of 4 rows (tokens i, i+8, i+16, i+24 in piece i), 1088 bytes apart, for
+// the transposing LDS reads (see lds_read_v).
+constexpr int kVPiecePitch = 1088;
+constexpr int kStageBytes = 8192 + 8 * kVPiecePitch;
+// Cache policy of the K / V requests: 2 = the streaming hint (nt).  K / V rows are used once per
+// workgroup; with the hint the requests are served faster, and the sharing of a KV head's rows
+// between its query heads' workgroups through L2 is unaffected (same fetch counters).
+constexpr int kKvAux = 2;
+constexpr float kRescaleSlack = 8.f; // the reference max may lag the true max by 2^8
+
+// Exact n / d for 0 <= n < 2^31 with a host-prepared multiplier (no integer divide
+// on the GPU: one takes about forty vector instructions).
+struct FastDiv {
+    uint32_t mul, shift, d;
+    __device__ __forceinline__ uint32_t div(uint32_t n) const { return d == 1 ? n : (__umulhi(n, mul) >> shift); }
+};
+static FastDiv make_fastdiv(uint32_t d)
+{
+    FastDiv f;
+    f.d = d;
+    uint32_t l = 0;
+    while ((1ull << l) < d) ++l;                       // l = ceil(log2 d)
+    if (d <= 1) { f.mul = 0; f.shift = 0; return f; }
+    f.mul = (uint32_t)(((1ull << (31 + l)) + d - 1) / d);   // ceil(2^(31+l) / d) <= 2^32 - 1 for d >= 2
+    f.shift = l - 1;
+    return f;
+}
+
+struct MfmaArgs {
+    const int32_t *sel_idx, *sel_count;
+    int n_sel;
+    float scale_log2;
+    int n_units, row_tiles, n_bg;
+    int n_row_blocks;   // group kernel: 32-row blocks of a KV head's M * G query rows
+    FastDiv div_nsplit, div_hkv, div_B, div_W, div_M;
+};
+
+__device__ __forceinline__ bf16x8 as_bf16x8(const uint4 &u) { return __builtin_bit_cast(bf16x8, u); }
+
+__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
+{
+    bf16x2 v = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(uint32_t, v);
+}
+// acc + lo(p) + hi(p) for a packed bf16 pair
+__device__ __forceinline__ float add_bf16x2(uint32_t p, float acc)
+{
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p), ones, acc, false);
+}
+
+// 16 bytes per lane from global memory straight into LDS (no registers involved):
+// lane l of the wavefront lands at lds_dst + 16*l.
+__device__ __forceinline__ void dma16(const char *gsrc, char *lds_dst)
+{
+    __builtin_amdgcn_global_load_lds((glb_void_ptr)gsrc, (lds_void_ptr)lds_dst, 16, 0, kKvAux);
+}
+
+// Four such operations 1 KiB apart on both sides (K rows 4 i .. 4 i + 3 for i = 0 .. 3, or 4 .. 7): gbase is
+// wavefront-uniform, row_off the lane's row (lane / 16) in bytes, sw0 its piece 16 * ((lane & 15) ^ (lane / 16));
+// operation i fetches the piece that the swizzle by row & 15 puts at the lane's place, sw0 ^ 64 i.  The
+// immediate offset of the instruction is added to the global and to the LDS address.
+__device__ __forceinline__ void dma16x4(const char *gbase, uint32_t row_off, uint32_t sw0, char *lds_dst)
+{
+    __builtin_amdgcn_global_load_lds((glb_void_ptr)(gbase + (row_off + sw0)), (lds_void_ptr)lds_dst, 16, 0, kKvAux);
+    __builtin_amdgcn_global_load_lds((glb_void_ptr)(gbase + (row_off + (sw0 ^ 64u))), (lds_void_ptr)lds_dst, 16, 1024, kKvAux);
+    __builtin_amdgcn_global_load_lds((glb_void_ptr)(gbase + (row_off + (sw0 ^ 128u))), (lds_void_ptr)lds_dst, 16, 2048, kKvAux);
+    __builtin_amdgcn_global_load_lds((glb_void_ptr)(gbase + (row_off + (sw0 ^ 192u))), (lds_void_ptr)lds_dst, 16, 3072, kKvAux);
+}
+
+// The LDS reads of staged K / V are written in assembly so that the compiler does not
+// put a full vector-memory wait in front of them (it cannot tell which in-flight
+// LDS-DMA a read depends on); the waits are placed by hand instead.
+template <int OFF>
+__device__ __forceinline__ void lds_read_k(const uint32_t (&a)[8], uint4 (&k)[8])
+{
+    asm volatile(
+        "ds_read_b128 %0, %8 offset:%16\n\t"
+        "ds_read_b128 %1, %9 offset:%16\n\t"
+        "ds_read_b128 %2, %10 offset:%16\n\t"
+        "ds_read_b128 %3, %11 offset:%16\n\t"
+        "ds_read_b128 %4, %12 offset:%16\n\t"
+        "ds_read_b128 %5, %13 offset:%16\n\t"
+        "ds_read_b128 %6, %14 offset:%16\n\t"
+        "ds_read_b128 %7, %15 offset:%16\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(k[0]), "=&v"(k[1]), "=&v"(k[2]), "=&v"(k[3]), "=&v"(k[4]), "=&v"(k[5]), "=&v"(k[6]), "=&v"(k[7])
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]), "n"(OFF)
+        : "memory");
+}
+
+// Four k-steps (half of a chunk's K operands).
+template <int OFF> __device__ __forceinline__ void lds_read_k_half(const uint32_t (&a)[4], uint4 (&k)[4])
+{
+    asm volatile(
+        "ds_read_b128 %0, %4 offset:%8\n\t"
+        "ds_read_b128 %1, %5 offset:%8\n\t"
+        "ds_read_b128 %2, %6 offset:%8\n\t"
+        "ds_read_b128 %3, %7 offset:%8\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(k[0]), "=&v"(k[1]), "=&v"(k[2]), "=&v"(k[3])
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "n"(OFF)
+        : "memory");
+}
+
+// V operands (A operand of O^T += V^T . P^T: per lane 8 tokens of ONE channel) through the
+// transposing LDS read ds_read_b64_tr_b16.  Inside a group of 16 lanes, lane s reads 8 bytes
+// (4 channels) and receives, as lane 4a + c, element c of what lanes a, a+4, a+8, a+12 read.
+// With lane s reading token (s >> 2) of a token quad and channels 4 * (s & 3) .. +3 of a
+// 16-channel group, every lane ends up with the four tokens of the quad for channel
+// (lane & 15) of the group: lane m = lane & 31 holds channel 32j + m of tile j, its k-group the
+// tokens 16*ks2 + 8*hf + 4*kg + 0..3.  The four rows of a quad sit in four different V pieces,
+// 1088 bytes apart, i.e. 64 bytes apart modulo the bank cycle: no bank conflicts.
+// v[(ks2 * 4 + j) * 2 + hf]; addr = piece (4*kg + (s >> 2)), byte 32 * (group & 1) + 8 * (s & 3).
+// OFF: a constant byte offset (a ring stage), added by the instructions themselves.
+template <int OFF = 0>
+__device__ __forceinline__ void lds_read_v(uint32_t addr, uint2 (&v)[16])
+{
+    static_assert(OFF >= 0 && OFF + 960 < 65536, "the offset field has 16 bits");
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %16 offset:%17\n\t"
+        "ds_read_b64_tr_b16 %1, %16 offset:%17+256\n\t"
+        "ds_read_b64_tr_b16 %2, %16 offset:%17+64\n\t"
+        "ds_read_b64_tr_b16 %3, %16 offset:%17+320\n\t"
+        "ds_read_b64_tr_b16 %4, %16 offset:%17+128\n\t"
+        "ds_read_b64_tr_b16 %5, %16 offset:%17+384\n\t"
+        "ds_read_b64_tr_b16 %6, %16 offset:%17+192\n\t"
+        "ds_read_b64_tr_b16 %7, %16 offset:%17+448\n\t"
+        "ds_read_b64_tr_b16 %8, %16 offset:%17+512\n\t"
+        "ds_read_b64_tr_b16 %9, %16 offset:%17+768\n\t"
+        "ds_read_b64_tr_b16 %10, %16 offset:%17+576\n\t"
+        "ds_read_b64_tr_b16 %11, %16 offset:%17+832\n\t"
+        "ds_read_b64_tr_b16 %12, %16 offset:%17+640\n\t"
+        "ds_read_b64_tr_b16 %13, %16 offset:%17+896\n\t"
+        "ds_read_b64_tr_b16 %14, %16 offset:%17+704\n\t"
+        "ds_read_b64_tr_b16 %15, %16 offset:%17+960\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7]),
+          "=&v"(v[8]), "=&v"(v[9]), "=&v"(v[10]), "=&v"(v[11]), "=&v"(v[12]), "=&v"(v[13]), "=&v"(v[14]), "=&v"(v[15])
+        : "v"(addr), "n"(OFF)
+        : "memory");
+}
+
+// Half of that: the operands of token half ks2 (OFF = 512 ks2), v[j * 2 + hf].
+template <int OFF> __device__ __forceinline__ void lds_read_v_half(uint32_t addr, uint2 (&v)[8])
+{
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %8 offset:%9\n\t"
+        "ds_read_b64_tr_b16 %1, %8 offset:%10\n\t"
+        "ds_read_b64_tr_b16 %2, %8 offset:%11\n\t"
+        "ds_read_b64_tr_b16 %3, %8 offset:%12\n\t"
+        "ds_read_b64_tr_b16 %4, %8 offset:%13\n\t"
+        "ds_read_b64_tr_b16 %5, %8 offset:%14\n\t"
+        "ds_read_b64_tr_b16 %6, %8 offset:%15\n\t"
+        "ds_read_b64_tr_b16 %7, %8 offset:%16\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
+        : "v"(addr), "n"(OFF), "n"(OFF + 256), "n"(OFF + 64), "n"(OFF + 320), "n"(OFF + 128), "n"(OFF + 384), "n"(OFF + 192),
+          "n"(OFF + 448)
+        : "memory");
+}
+
+// 64 channels: the V operands of a chunk, v[(ks2 * 2 + j) * 2 + hf].  A row is 128 bytes; piece p (tokens p, p + 8,
+// p + 16, p + 24) sits at 1152 (p >> 1) + 512 (p & 1), and the two 64-byte halves of an odd piece's rows are exchanged:
+// the four pieces that a quad's lanes read then cover all 64 banks.  a0, a1: this lane's address of channel tile 0, 1.
+template <int OFF>
+__device__ __forceinline__ void lds_read_v64(uint32_t a0, uint32_t a1, uint2 (&v)[8])
+{
+    static_assert(OFF >= 0 && OFF + 384 < 65536, "the offset field has 16 bits");
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %8 offset:%10\n\t"
+        "ds_read_b64_tr_b16 %1, %8 offset:%10+128\n\t"
+        "ds_read_b64_tr_b16 %2, %9 offset:%10\n\t"
+        "ds_read_b64_tr_b16 %3, %9 offset:%10+128\n\t"
+        "ds_read_b64_tr_b16 %4, %8 offset:%10+256\n\t"
+        "ds_read_b64_tr_b16 %5, %8 offset:%10+384\n\t"
+        "ds_read_b64_tr_b16 %6, %9 offset:%10+256\n\t"
+        "ds_read_b64_tr_b16 %7, %9 offset:%10+384\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
+        : "v"(a0), "v"(a1), "n"(OFF)
+        : "memory");
+}
+
+// The split-KV partials are written once here and read once by the combine kernel, which runs on
+// other CUs (and mostly other XCDs): stored with the streaming hint they do not linger in this
+// XCD's L2 as dirty lines that the end of the kernel has to write back (measured: 3.6 % of the
+// partial-verify step).
+// Two values of a split's normalised result as fp16 (clamped to fp16's range), one streaming 4-byte store.
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void store_partial_half(float *row, int lane, float a, float b)
+{
+    const f16x2 hv = {(_Float16)__builtin_amdgcn_fmed3f(a, -65504.f, 65504.f), (_Float16)__builtin_amdgcn_fmed3f(b, -65504.f, 65504.f)};
+    __builtin_nontemporal_store(__builtin_bit_cast(uint32_t, hv), (uint32_t *)row + lane);
+}
+
+// max / sum over the two half-wavefronts (lane and lane ^ 32)
+__device__ __forceinline__ float max_xor32(float x)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_xor32(float x)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Instrumented builds (-DSPECPV_TIMELINE): core clock against real time over a workgroup's life.  Cycles, 10 ns ticks and
+// the number of chunks go to words 0 .. 2 of row ROW of the stamp buffer (the real-time counter runs at 100 MHz
+// whatever the chip does, s_memtime counts core cycles).
+#ifdef SPECPV_TIMELINE
+#define SPECPV_CLOCKS_BEGIN const unsigned long long clk0_ = clock64(), rt0_ = __builtin_amdgcn_s_memrealtime()
+#define SPECPV_CLOCKS_END(TL, ROW, NCH)                                                                       \
+    do {                                                                                                      \
+        if ((TL) && threadIdx.x == 0 && (size_t)(ROW) < 4096) {                                               \
+            unsigned long long *t_ = (TL) + (size_t)(ROW) * 16;                                               \
+            t_[0] = clock64() - clk0_;                                                                        \
+            t_[1] = __builtin_amdgcn_s_memrealtime() - rt0_;                                                  \
+            t_[2] = (unsigned long long)(NCH);                                                                \
+        }                                                                                                     \
+    } while (0)
+#else
+#define SPECPV_CLOCKS_BEGIN do {} while (0)
+#define SPECPV_CLOCKS_END(TL, ROW, NCH) do {} while (0)
+#endif
+
+}  // namespace specpv

@@ -26,250 +26,19 @@
 // 2^8 ahead of it, so rescaling the accumulators is rare.
 //
 // Epilogue: the four token groups merge their (O, m, l) through LDS and write one
-// split-KV partial per (head, split, node); combine.hip finishes.
+// split-KV partial per (head, split, node).
 //
-// attn_ctx_mfma_kernel (above description) is used when a wavefront has only a few chunks to go
-// through (the partial verification over a 4K-token cache); attn_ctx_mfma_group_kernel, further
-// down, when it has many (full verification of a long context): there a workgroup serves all
-// query heads of a KV head.
-#include "internal.h"
-#include <type_traits>
+// attn_ctx_mfma_kernel (above description, with the rest of the call in the same kernel) is the single-kernel route
+// of specpv_debug_set_route; attn_ctx_mfma_group_kernel, further down, is used when a wavefront has many chunks to go
+// through (full verification of a long context, batches): there a workgroup serves all query heads of a KV head.  Short
+// ranges (the partial verification over a 4K-token cache) run attn_tile.hip.
+#include "attn_mfma.h"
 
 namespace specpv {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-typedef __attribute__((address_space(3))) void *lds_void_ptr;
-typedef const __attribute__((address_space(1))) void *glb_void_ptr;
-
-constexpr int kOPitch = 132;         // floats per staged output row (128 + 4: conflict-free 16-byte writes)
-// One 32-token chunk in LDS: 8 KiB of K (row-major, 16-byte pieces XOR-swizzled by row & 15: the LDS has 64
-// banks, so the 16 lanes that a 16-byte read serves per cycle must cover all 16 pieces of a 256-byte bank row;
-// with row & 7 the operand reads ran at half the rate) and
-// the V rows in 8 pieces of 4 rows (tokens i, i+8, i+16, i+24 in piece i), 1088 bytes apart, for
-// the transposing LDS reads (see lds_read_v).
-constexpr int kVPiecePitch = 1088;
-constexpr int kStageBytes = 8192 + 8 * kVPiecePitch;
 constexpr int kStages = 2;           // ring depth per wavefront pair (eight-wavefront kernel)
 constexpr int kRingBytes = 4 * kStages * kStageBytes;
 constexpr int kQStageBytes = 2 * 8 * 1024;   // the query rows of a workgroup's two row blocks as MFMA operands (eight-wavefront kernel)
-// Cache policy of the K / V requests: 2 = the streaming hint (nt).  K / V rows are used once per
-// workgroup; with the hint the requests are served faster, and the sharing of a KV head's rows
-// between its query heads' workgroups through L2 is unaffected (same fetch counters).
-constexpr int kKvAux = 2;
-constexpr float kRescaleSlack = 8.f; // the reference max may lag the true max by 2^8
-
-// Exact n / d for 0 <= n < 2^31 with a host-prepared multiplier (no integer divide
-// on the GPU: one takes about forty vector instructions).
-struct FastDiv {
-    uint32_t mul, shift, d;
-    __device__ __forceinline__ uint32_t div(uint32_t n) const { return d == 1 ? n : (__umulhi(n, mul) >> shift); }
-};
-static FastDiv make_fastdiv(uint32_t d)
-{
-    FastDiv f;
-    f.d = d;
-    uint32_t l = 0;
-    while ((1ull << l) < d) ++l;                       // l = ceil(log2 d)
-    if (d <= 1) { f.mul = 0; f.shift = 0; return f; }
-    f.mul = (uint32_t)(((1ull << (31 + l)) + d - 1) / d);   // ceil(2^(31+l) / d) <= 2^32 - 1 for d >= 2
-    f.shift = l - 1;
-    return f;
-}
-
-struct MfmaArgs {
-    const int32_t *sel_idx, *sel_count;
-    int n_sel;
-    float scale_log2;
-    int n_units, row_tiles, n_bg;
-    int n_row_blocks;   // group kernel: 32-row blocks of a KV head's M * G query rows
-    FastDiv div_nsplit, div_hkv, div_B, div_W, div_G;
-};
-
-__device__ __forceinline__ bf16x8 as_bf16x8(const uint4 &u) { return __builtin_bit_cast(bf16x8, u); }
-
-__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
-{
-    bf16x2 v = {(__bf16)a, (__bf16)b};
-    return __builtin_bit_cast(uint32_t, v);
-}
-// acc + lo(p) + hi(p) for a packed bf16 pair
-__device__ __forceinline__ float add_bf16x2(uint32_t p, float acc)
-{
-    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p), ones, acc, false);
-}
-
-// 16 bytes per lane from global memory straight into LDS (no registers involved):
-// lane l of the wavefront lands at lds_dst + 16*l.
-__device__ __forceinline__ void dma16(const char *gsrc, char *lds_dst)
-{
-    __builtin_amdgcn_global_load_lds((glb_void_ptr)gsrc, (lds_void_ptr)lds_dst, 16, 0, kKvAux);
-}
-
-// Four such operations 1 KiB apart on both sides (K rows 4 i .. 4 i + 3 for i = 0 .. 3, or 4 .. 7): gbase is
-// wavefront-uniform, row_off the lane's row (lane / 16) in bytes, sw0 its piece 16 * ((lane & 15) ^ (lane / 16));
-// operation i fetches the piece that the swizzle by row & 15 puts at the lane's place, sw0 ^ 64 i.  The
-// immediate offset of the instruction is added to the global and to the LDS address.
-__device__ __forceinline__ void dma16x4(const char *gbase, uint32_t row_off, uint32_t sw0, char *lds_dst)
-{
-    __builtin_amdgcn_global_load_lds((glb_void_ptr)(gbase + (row_off + sw0)), (lds_void_ptr)lds_dst, 16, 0, kKvAux);
-    __builtin_amdgcn_global_load_lds((glb_void_ptr)(gbase + (row_off + (sw0 ^ 64u))), (lds_void_ptr)lds_dst, 16, 1024, kKvAux);
-    __builtin_amdgcn_global_load_lds((glb_void_ptr)(gbase + (row_off + (sw0 ^ 128u))), (lds_void_ptr)lds_dst, 16, 2048, kKvAux);
-    __builtin_amdgcn_global_load_lds((glb_void_ptr)(gbase + (row_off + (sw0 ^ 192u))), (lds_void_ptr)lds_dst, 16, 3072, kKvAux);
-}
-
-// The LDS reads of staged K / V are written in assembly so that the compiler does not
-// put a full vector-memory wait in front of them (it cannot tell which in-flight
-// LDS-DMA a read depends on); the waits are placed by hand instead.
-template <int OFF>
-__device__ __forceinline__ void lds_read_k(const uint32_t (&a)[8], uint4 (&k)[8])
-{
-    asm volatile(
-        "ds_read_b128 %0, %8 offset:%16\n\t"
-        "ds_read_b128 %1, %9 offset:%16\n\t"
-        "ds_read_b128 %2, %10 offset:%16\n\t"
-        "ds_read_b128 %3, %11 offset:%16\n\t"
-        "ds_read_b128 %4, %12 offset:%16\n\t"
-        "ds_read_b128 %5, %13 offset:%16\n\t"
-        "ds_read_b128 %6, %14 offset:%16\n\t"
-        "ds_read_b128 %7, %15 offset:%16\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(k[0]), "=&v"(k[1]), "=&v"(k[2]), "=&v"(k[3]), "=&v"(k[4]), "=&v"(k[5]), "=&v"(k[6]), "=&v"(k[7])
-        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]), "n"(OFF)
-        : "memory");
-}
-
-// Four k-steps (half of a chunk's K operands).
-template <int OFF> __device__ __forceinline__ void lds_read_k_half(const uint32_t (&a)[4], uint4 (&k)[4])
-{
-    asm volatile(
-        "ds_read_b128 %0, %4 offset:%8\n\t"
-        "ds_read_b128 %1, %5 offset:%8\n\t"
-        "ds_read_b128 %2, %6 offset:%8\n\t"
-        "ds_read_b128 %3, %7 offset:%8\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(k[0]), "=&v"(k[1]), "=&v"(k[2]), "=&v"(k[3])
-        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "n"(OFF)
-        : "memory");
-}
-
-// V operands (A operand of O^T += V^T . P^T: per lane 8 tokens of ONE channel) through the
-// transposing LDS read ds_read_b64_tr_b16.  Inside a group of 16 lanes, lane s reads 8 bytes
-// (4 channels) and receives, as lane 4a + c, element c of what lanes a, a+4, a+8, a+12 read.
-// With lane s reading token (s >> 2) of a token quad and channels 4 * (s & 3) .. +3 of a
-// 16-channel group, every lane ends up with the four tokens of the quad for channel
-// (lane & 15) of the group: lane m = lane & 31 holds channel 32j + m of tile j, its k-group the
-// tokens 16*ks2 + 8*hf + 4*kg + 0..3.  The four rows of a quad sit in four different V pieces,
-// 1088 bytes apart, i.e. 64 bytes apart modulo the bank cycle: no bank conflicts.
-// v[(ks2 * 4 + j) * 2 + hf]; addr = piece (4*kg + (s >> 2)), byte 32 * (group & 1) + 8 * (s & 3).
-// OFF: a constant byte offset (a ring stage), added by the instructions themselves.
-template <int OFF = 0>
-__device__ __forceinline__ void lds_read_v(uint32_t addr, uint2 (&v)[16])
-{
-    static_assert(OFF >= 0 && OFF + 960 < 65536, "the offset field has 16 bits");
-    asm volatile(
-        "ds_read_b64_tr_b16 %0, %16 offset:%17\n\t"
-        "ds_read_b64_tr_b16 %1, %16 offset:%17+256\n\t"
-        "ds_read_b64_tr_b16 %2, %16 offset:%17+64\n\t"
-        "ds_read_b64_tr_b16 %3, %16 offset:%17+320\n\t"
-        "ds_read_b64_tr_b16 %4, %16 offset:%17+128\n\t"
-        "ds_read_b64_tr_b16 %5, %16 offset:%17+384\n\t"
-        "ds_read_b64_tr_b16 %6, %16 offset:%17+192\n\t"
-        "ds_read_b64_tr_b16 %7, %16 offset:%17+448\n\t"
-        "ds_read_b64_tr_b16 %8, %16 offset:%17+512\n\t"
-        "ds_read_b64_tr_b16 %9, %16 offset:%17+768\n\t"
-        "ds_read_b64_tr_b16 %10, %16 offset:%17+576\n\t"
-        "ds_read_b64_tr_b16 %11, %16 offset:%17+832\n\t"
-        "ds_read_b64_tr_b16 %12, %16 offset:%17+640\n\t"
-        "ds_read_b64_tr_b16 %13, %16 offset:%17+896\n\t"
-        "ds_read_b64_tr_b16 %14, %16 offset:%17+704\n\t"
-        "ds_read_b64_tr_b16 %15, %16 offset:%17+960\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7]),
-          "=&v"(v[8]), "=&v"(v[9]), "=&v"(v[10]), "=&v"(v[11]), "=&v"(v[12]), "=&v"(v[13]), "=&v"(v[14]), "=&v"(v[15])
-        : "v"(addr), "n"(OFF)
-        : "memory");
-}
-
-// Half of that: the operands of token half ks2 (OFF = 512 ks2), v[j * 2 + hf].
-template <int OFF> __device__ __forceinline__ void lds_read_v_half(uint32_t addr, uint2 (&v)[8])
-{
-    asm volatile(
-        "ds_read_b64_tr_b16 %0, %8 offset:%9\n\t"
-        "ds_read_b64_tr_b16 %1, %8 offset:%10\n\t"
-        "ds_read_b64_tr_b16 %2, %8 offset:%11\n\t"
-        "ds_read_b64_tr_b16 %3, %8 offset:%12\n\t"
-        "ds_read_b64_tr_b16 %4, %8 offset:%13\n\t"
-        "ds_read_b64_tr_b16 %5, %8 offset:%14\n\t"
-        "ds_read_b64_tr_b16 %6, %8 offset:%15\n\t"
-        "ds_read_b64_tr_b16 %7, %8 offset:%16\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
-        : "v"(addr), "n"(OFF), "n"(OFF + 256), "n"(OFF + 64), "n"(OFF + 320), "n"(OFF + 128), "n"(OFF + 384), "n"(OFF + 192),
-          "n"(OFF + 448)
-        : "memory");
-}
-
-// 64 channels: the V operands of a chunk, v[(ks2 * 2 + j) * 2 + hf].  A row is 128 bytes; piece p (tokens p, p + 8,
-// p + 16, p + 24) sits at 1152 (p >> 1) + 512 (p & 1), and the two 64-byte halves of an odd piece's rows are exchanged:
-// the four pieces that a quad's lanes read then cover all 64 banks.  a0, a1: this lane's address of channel tile 0, 1.
-template <int OFF>
-__device__ __forceinline__ void lds_read_v64(uint32_t a0, uint32_t a1, uint2 (&v)[8])
-{
-    static_assert(OFF >= 0 && OFF + 384 < 65536, "the offset field has 16 bits");
-    asm volatile(
-        "ds_read_b64_tr_b16 %0, %8 offset:%10\n\t"
-        "ds_read_b64_tr_b16 %1, %8 offset:%10+128\n\t"
-        "ds_read_b64_tr_b16 %2, %9 offset:%10\n\t"
-        "ds_read_b64_tr_b16 %3, %9 offset:%10+128\n\t"
-        "ds_read_b64_tr_b16 %4, %8 offset:%10+256\n\t"
-        "ds_read_b64_tr_b16 %5, %8 offset:%10+384\n\t"
-        "ds_read_b64_tr_b16 %6, %9 offset:%10+256\n\t"
-        "ds_read_b64_tr_b16 %7, %9 offset:%10+384\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
-        : "v"(a0), "v"(a1), "n"(OFF)
-        : "memory");
-}
-
-// The split-KV partials are written once here and read once by the combine kernel, which runs on
-// other CUs (and mostly other XCDs): stored with the streaming hint they do not linger in this
-// XCD's L2 as dirty lines that the end of the kernel has to write back (measured: 3.6 % of the
-// partial-verify step).
-// Two values of a split's normalised result as fp16 (clamped to fp16's range), one streaming 4-byte store.
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void store_partial_half(float *row, int lane, float a, float b)
-{
-    const f16x2 hv = {(_Float16)__builtin_amdgcn_fmed3f(a, -65504.f, 65504.f), (_Float16)__builtin_amdgcn_fmed3f(b, -65504.f, 65504.f)};
-    __builtin_nontemporal_store(__builtin_bit_cast(uint32_t, hv), (uint32_t *)row + lane);
-}
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void store_partial(float *p, float2 v)
-{
-    f32x2 x = {v.x, v.y};
-#ifndef SPECPV_PARTIAL_PLAIN
-    __builtin_nontemporal_store(x, (f32x2 *)p);
-#else
-    *(f32x2 *)p = x;
-#endif
-}
-
-// max / sum over the two half-wavefronts (lane and lane ^ 32)
-__device__ __forceinline__ float max_xor32(float x)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float sum_xor32(float x)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
 
 __device__ __forceinline__ float max_xor16(float x)
 {
@@ -347,7 +116,7 @@ __device__ __forceinline__ int pop_node(unsigned long long &lo, unsigned long lo
 // read -> stage may be refilled".  Every wavefront runs the same number of iterations
 // (the largest chunk count in the workgroup), so the barriers always match up.
 //
-// FUSED: the whole call in this one kernel.
+// The whole call in this one kernel (attn_tile.hip is the context part alone, the first of two kernels):
 //  * The draft-tree segment (a node attends itself and its ancestors, tree decode of Algorithm 1)
 //    is one more partial per row, in slot `nctx` behind the context splits: the workgroup of
 //    split sp computes it for the rows r = sp (mod nctx) of its tile on the vector ALU, one row
@@ -369,23 +138,8 @@ constexpr int kXccBits = 7;
         if (f.timeline && threadIdx.x == 0 && !REDO)                                                          \
             f.timeline[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 16 + (i)] = __builtin_amdgcn_s_memrealtime(); \
     } while (0)
-// core clock against real time over a workgroup's life: cycles, 10 ns ticks and the number of chunks go to
-// words 0 .. 2 of row ROW of the stamp buffer (the real-time counter runs at 100 MHz whatever the chip does,
-// s_memtime counts core cycles)
-#define SPECPV_CLOCKS_BEGIN const unsigned long long clk0_ = clock64(), rt0_ = __builtin_amdgcn_s_memrealtime()
-#define SPECPV_CLOCKS_END(TL, ROW, NCH)                                                                       \
-    do {                                                                                                      \
-        if ((TL) && threadIdx.x == 0 && (size_t)(ROW) < 4096) {                                               \
-            unsigned long long *t_ = (TL) + (size_t)(ROW) * 16;                                               \
-            t_[0] = clock64() - clk0_;                                                                        \
-            t_[1] = __builtin_amdgcn_s_memrealtime() - rt0_;                                                  \
-            t_[2] = (unsigned long long)(NCH);                                                                \
-        }                                                                                                     \
-    } while (0)
 #else
 #define SPECPV_STAMP(i) do {} while (0)
-#define SPECPV_CLOCKS_BEGIN do {} while (0)
-#define SPECPV_CLOCKS_END(TL, ROW, NCH) do {} while (0)
 #endif        // per-XCC arrival count (splits <= 64)
 
 // One pass over the token ranges of split `sp0` of `ns_eff` splits.  REDO = false: the ordinary pass of
@@ -393,9 +147,7 @@ constexpr int kXccBits = 7;
 // recompute route.  REDO = true: that route -- the pass runs as the only split of one (sp0 = 0, ns_eff = 1).
 // Everything, the argument-dependent reads included, is done again in the second pass, so that it keeps
 // no register of the first one alive.
-// PEND: partially verified tokens may stand in front of the tree (s.kctx > 0); without it the kernel is the one
-// that the headline shape runs, free of that path's registers and tests.
-template <bool ALIGNED, bool FUSED, bool REDO, bool PEND>
+template <bool ALIGNED, bool REDO>
 __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a, FusedArgs f, const int nctx,
                                               const int sp0, const int ns_eff, char *lds_raw)
 {
@@ -456,7 +208,7 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
     const int rows_tile = min(64, s.M - m0);            // >= 1
     int par0 = -1, par1 = -1;
     uint4 qd_first = make_uint4(0u, 0u, 0u, 0u);
-    if (FUSED) {
+    {
         const int32_t *par = s.parent + (int64_t)b * s.Mk;
         if (lane < s.Mk) par0 = par[lane];
         if (lane + 64 < s.Mk) par1 = par[lane + 64];
@@ -472,7 +224,7 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
     // chunks of cache tokens, then the chunks of the partially verified tokens (the first kctx draft nodes: a
     // chain that every query node descends from, so all rows attend all of them, like cache tokens)
     const uint32_t C_ctx = (T + 31u) >> 5;
-    const int kctx = PEND ? s.kctx : 0;
+    const int kctx = s.kctx;
     const uint32_t C = C_ctx + (((uint32_t)kctx + 31u) >> 5);
     const char *kdb = (const char *)s.kd + (((int64_t)b * s.Mk) * s.Hkv + g) * 256;
     const char *vdb = (const char *)s.vd + (((int64_t)b * s.Mk) * s.Hkv + g) * 256;
@@ -511,7 +263,6 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
     const int c0 = first_chunk(C, wsid), c1 = first_chunk(C, wsid + 1);
     const int nch = c1 - c0;
     const int nch_max = first_chunk(C, sp * 4 + 1) - first_chunk(C, sp * 4);   // token group 0 has the most
-    if (!FUSED) SPECPV_STAMP(9);   // the scalar reads (lengths, list length) are in: the chunk counts are known
 
     // ---- chunk -> token rows ------------------------------------------------------------
     // ALIGNED (B % 32 == 0): a chunk lies inside one block, so its 32 rows are consecutive.  The
@@ -587,7 +338,7 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
         char *dst = my_ring + stg * kStageBytes;
         char *dstv = dst + 8192;
         int tok;
-        if (PEND && kctx > 0 && (uint32_t)(c0 + ci) >= C_ctx) {
+        if (kctx > 0 && (uint32_t)(c0 + ci) >= C_ctx) {
             // a chunk of partially verified tokens: rows of the draft K / V arrays
             const int pr = (int)((uint32_t)(c0 + ci) - C_ctx) * 32 + n;
             const int ptok = pr < kctx ? pr : -1;
@@ -648,7 +399,7 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
     asm volatile("" ::: "memory");
     SPECPV_STAMP(1);   // arguments, lengths, list, query rows, parents are in
 
-    // ---- draft-tree segment of this workgroup's rows (FUSED) --------------------------------
+    // ---- draft-tree segment of this workgroup's rows --------------------------------
     // Row r of the tile (node koff + m0 + r) is handled by the workgroup with sp = r mod ns_eff, there
     // by wavefront (r / ns_eff) mod 8.  Sixteen lanes per draft node (a lane owns 8 adjacent
     // channels), four nodes of the root path at a time; the result goes to slot nctx of the
@@ -746,12 +497,7 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) qf[ks] = as_bf16x8(qraw[ks]);
     };
-    if (FUSED) {
-        draft_rows();
-    } else {
-        if (nch > 0) issue(0);
-        if (nch > 1) issue(1);
-    }
+    draft_rows();
     SPECPV_STAMP(2);   // first chunks requested, draft rows done
     for (int i = 0; i < nch_max; ++i) {
         const bool active = i < nch;
@@ -852,9 +598,7 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
                 *(float4 *)(dst + 32 * j + 8 * q + 4 * kg) = make_float4(O[j][4 * q], O[j][4 * q + 1], O[j][4 * q + 2], O[j][4 * q + 3]);
     }
     __syncthreads();
-    // the partial row of node j is prow0 + j * prow_step
-    const int64_t prow0 = FUSED ? ((int64_t)(b * s.Hq + h) * part.nsplit + sp) * s.M : ((int64_t)bg * part.nsplit + sp) * ((int64_t)s.M * s.G) + hh;
-    const int prow_step = FUSED ? 1 : s.G;
+    const int64_t prow0 = ((int64_t)(b * s.Hq + h) * part.nsplit + sp) * s.M;
     // weights of the four token groups for the rows this wavefront finishes (lane -> row)
     float wgt[4], m_row = -INFINITY, l_row = 0.f;
     {
@@ -870,10 +614,8 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
         }
     }
     {
-        // fp32 partials (single-kernel route): positions 2 lane, 2 lane + 1 of the stored order; fp16 partials:
-        // channels 2 lane, 2 lane + 1, normalised by the row's l
-        const int chan0 = FUSED ? partial_chan(2 * lane, 128) : 2 * lane;
-        const float il = l_row > 0.f ? 1.f / l_row : 0.f;
+        // positions 2 lane, 2 lane + 1 of the stored order
+        const int chan0 = partial_chan(2 * lane, 128);
         float2 acc[RPW];
 #pragma unroll
         for (int uu = 0; uu < RPW; ++uu) {
@@ -890,44 +632,17 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
 #pragma unroll
         for (int uu = 0; uu < RPW; ++uu) {
             const int j = m0 + wave * RPW + uu;
-            if (j < s.M) {
-                if (FUSED) {
-                    *(float2 *)(part.o + (prow0 + j) * 128 + 2 * lane) = acc[uu];   // stays in this XCD's L2
-                } else {
-                    const float ilu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(il), uu));
-                    store_partial_half(part.o + (prow0 + (int64_t)j * prow_step) * 64, lane, acc[uu].x * ilu, acc[uu].y * ilu);   // 128 halves per row
-                }
-            }
+            if (j < s.M) *(float2 *)(part.o + (prow0 + j) * 128 + 2 * lane) = acc[uu];   // stays in this XCD's L2
         }
     }
     if (lane < RPW) {
         const int j = m0 + wave * RPW + lane;
-        if (j < s.M) *(float2 *)(part.ml + (prow0 + (int64_t)j * prow_step) * 2) = make_float2(m_row, l_row);
+        if (j < s.M) *(float2 *)(part.ml + (prow0 + j) * 2) = make_float2(m_row, l_row);
     }
     SPECPV_STAMP(8);   // partial stores issued
     if (!REDO) SPECPV_CLOCKS_END(f.timeline, 3072 + ((size_t)blockIdx.y * gridDim.x + blockIdx.x), C);
-    if (!FUSED) {
-        // The combine kernel that follows reads the tree's parents and, one trip later, its K / V rows: nobody
-        // has touched those in this call yet.  Ask for them here, on the way out (nothing waits for the data):
-        // they are then in this XCD's L2, where that kernel's workgroups of the same KV head run.
-        if (wave == 0 && s.kd && s.vd && s.parent) {
-            const int nw = s.G * nctx, w = hh * nctx + sp;
-            const char *base = (lane & 16) ? (const char *)s.vd : (const char *)s.kd;
-            for (int node = w; node < s.Mk; node += nw) {
-                uint32_t tmp;
-                const char *p = base + (((int64_t)b * s.Mk + node) * s.Hkv + g) * 256 + (lane & 15) * 16;
-                if (lane < 32) asm volatile("global_load_dword %0, %1, off" : "=v"(tmp) : "v"(p) : "memory");
-            }
-            if (w == 0 && lane < 2) {
-                uint32_t tmp;
-                const char *p = (const char *)(s.parent + (int64_t)b * s.Mk) + lane * 256;
-                if (lane * 64 < s.Mk) asm volatile("global_load_dword %0, %1, off" : "=v"(tmp) : "v"(p) : "memory");
-            }
-        }
-        return false;
-    }
 
-    // ---- arrival; the last workgroup of the tile finishes it (FUSED) ------------------------
+    // ---- arrival; the last workgroup of the tile finishes it ------------------------
     unsigned long long *word = f.arrive + ((int64_t)(b * s.Hq + h) * 2 + rt);
     unsigned long long *sh_word = (unsigned long long *)lds_raw;   // ms / ls are dead
     int nslots, slot_step;
@@ -1068,7 +783,7 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
     return false;
 }
 
-template <bool ALIGNED, bool FUSED, bool PEND>
+template <bool ALIGNED>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_ctx_mfma_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, const int32_t *a_ctx_len,
                           const void *a_q, int a_n_sel, int a_M, int a_Hq, int a_nctx,
@@ -1079,9 +794,8 @@ void attn_ctx_mfma_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     a.sel_idx = a_sel_idx; a.sel_count = a_sel_count; a.n_sel = a_n_sel;
     extern __shared__ char lds_raw[];
     const int sp0 = (int)blockIdx.y - (int)a.div_nsplit.div(blockIdx.y) * a_nctx;
-    if (attn_ctx_pass<ALIGNED, FUSED, false, PEND>(s, part, a, f, a_nctx, sp0, a_nctx, lds_raw)) {
-        if (FUSED) attn_ctx_pass<ALIGNED, true, true, PEND>(s, part, a, f, a_nctx, 0, 1, lds_raw);
-    }
+    if (attn_ctx_pass<ALIGNED, false>(s, part, a, f, a_nctx, sp0, a_nctx, lds_raw))
+        attn_ctx_pass<ALIGNED, true>(s, part, a, f, a_nctx, 0, 1, lds_raw);
 }
 
 // ---- group variant: the query heads of a KV head in one workgroup --------------------------
@@ -1159,7 +873,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     // its share of the chunks and keeps the barriers, but computes and stores nothing.
     const int rbx = wg_part * W + wave;
     const bool live = rbx < a.n_row_blocks;
-    const int R = s.M * s.G;                  // query rows of the KV head: row r is node r / G, head r % G of the group
+    const int R = s.M * s.G;                  // query rows of the KV head: row r is head r / M of the group, node r % M
     const int r0w = (live ? rbx : a.n_row_blocks - 1) * 32;
     const int n = lane & 31, kg = lane >> 5;
 
@@ -1175,7 +889,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     uint4 qraw[KS];
     {
         const int r = min(r0w + n, R - 1);    // rows past the end repeat the last one; never stored
-        const int j = (int)a.div_G.div((uint32_t)r), hh = r - j * s.G;
+        const int hh = (int)a.div_M.div((uint32_t)r), j = r - hh * s.M;
         const uint16_t *qrow = (const uint16_t *)s.q + (((int64_t)b * s.M + j) * s.Hq + g * s.G + hh) * D + kg * 8;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qraw[ks] = *(const uint4 *)(qrow + ks * 16);
@@ -1618,6 +1332,7 @@ static GroupLayout group_layout(const Shape &s)
     return g;
 }
 int attn_group_parts(const Shape &s) { return group_layout(s).parts; }
+int attn_group_waves(const Shape &s) { return group_layout(s).waves; }
 
 hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const int32_t *sel_count,
                                 int n_sel, Partials p, int nctx, int kind, const FusedArgs &f, hipStream_t st)
@@ -1625,8 +1340,7 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
     if (kind != kAttnSplit && kind != kAttnGroup) return hipErrorInvalidValue;
     if (kind == kAttnSplit && s.D != 128) return hipErrorInvalidValue;
     const bool fused = f.out != nullptr;
-    if (fused && (kind != kAttnSplit || nctx > 64 || p.nsplit != nctx + 1)) return hipErrorInvalidValue;
-    if (!fused && p.nsplit != nctx) return hipErrorInvalidValue;
+    if (fused != (kind == kAttnSplit) || (fused && nctx > 64) || p.nsplit != nctx + (fused ? 1 : 0)) return hipErrorInvalidValue;
     const GroupLayout gl = group_layout(s);
     MfmaArgs a;
     a.sel_idx = sel_idx;
@@ -1640,7 +1354,7 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
     a.div_nsplit = make_fastdiv((uint32_t)nctx);
     a.div_hkv = make_fastdiv((uint32_t)s.Hkv);
     a.div_B = make_fastdiv((uint32_t)s.B);
-    a.div_G = make_fastdiv((uint32_t)s.G);
+    a.div_M = make_fastdiv((uint32_t)s.M);
     // token ranges per split: four (one per token group of a workgroup), or one in the group kernel
     a.div_W = make_fastdiv((uint32_t)nctx * (kind == kAttnGroup ? 1u : 4u));
     const int GR = kind == kAttnGroup ? gl.parts : s.G * a.row_tiles;
@@ -1667,9 +1381,9 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
         else { SPECPV_SET_LDS((attn_ctx_mfma_group_kernel<DD, false, WW>), lds_group);                  \
                hipLaunchKernelGGL(kern, grid, dim3(64 * WW), lds_group, st, s, p, a); }                 \
     } while (0)
-#define SPECPV_LAUNCH_SPLIT(AL, FU, PE)                                                                \
+#define SPECPV_LAUNCH_SPLIT(AL)                                                                        \
     do {                                                                                               \
-        SPECPV_SET_LDS((attn_ctx_mfma_kernel<AL, FU, PE>), lds_split);                                  \
+        SPECPV_SET_LDS((attn_ctx_mfma_kernel<AL>), lds_split);                                          \
         hipLaunchKernelGGL(kern, grid, dim3(512), lds_split, st, sel_idx, sel_count, s.ctx_len, s.q,    \
                            n_sel, s.M, s.Hq, nctx, s, p, a, f);                                         \
     } while (0)
@@ -1690,11 +1404,8 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
             default: SPECPV_LAUNCH_GROUP(128, 8); break;
             }
         }
-    } else if (fused) {
-        if (aligned) SPECPV_LAUNCH_SPLIT(true, true, true); else SPECPV_LAUNCH_SPLIT(false, true, true);
     } else {
-        if (s.kctx > 0) { if (aligned) SPECPV_LAUNCH_SPLIT(true, false, true); else SPECPV_LAUNCH_SPLIT(false, false, true); }
-        else { if (aligned) SPECPV_LAUNCH_SPLIT(true, false, false); else SPECPV_LAUNCH_SPLIT(false, false, false); }
+        if (aligned) SPECPV_LAUNCH_SPLIT(true); else SPECPV_LAUNCH_SPLIT(false);
     }
 #undef SPECPV_LAUNCH_SPLIT
 #undef SPECPV_LAUNCH_GROUP

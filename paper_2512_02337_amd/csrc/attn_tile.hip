@@ -1,0 +1,554 @@
+// Context part of the verification attention for short token ranges (the partial verification over a few thousand
+// kept tokens): bf16, head dim 128, matrix cores.
+//
+// Work decomposition.  The M * G query rows of a KV head are packed over its heads (row r = head r / M, node r % M) and
+// cut into tiles of 32 * RB rows.  A workgroup of eight wavefronts owns one tile and one KV split; its wavefronts are
+// TG token groups x RB row blocks of 32 rows (TG * RB = 8).  A token group owns a contiguous range of 32-token chunks and
+// an LDS ring of RB stages; the RB wavefronts of a group bring a chunk's rows together and all read it.  Nothing is
+// gathered: K and V rows go from their place in the cache straight into the ring by LDS-DMA (global_load_lds), and
+// from there into MFMA operand registers.
+//   TG = 8: tiles of 32 rows, one stage per wavefront.  One chunk per wavefront and the call is over in one round trip.
+//   TG = 4: tiles of 64 rows, two stages.
+//   TG = 2: tiles of 128 rows, four stages, three chunks requested up front.  Each K / V byte is pulled by half as many
+//           workgroups as with TG = 4.
+// What bounds it at one sequence is latency, not a rate: arguments and list 1.5 us, the first chunk 2 us later, then a
+// chain of chunks that a wavefront takes 0.86 us each for when they are there; a ring of two stages refilled at 3 us
+// of loaded latency made that 1.8 us.  The planner (plan_attention) chooses TG and the splits.  Calls of one sequence, 8 KV
+// heads at G = 4, 4096 kept tokens, against tiles of one head's 64 nodes (TG = 4, 8 splits, whatever the node count):
+// 60 nodes 17.4 -> 16.5 us (TG = 2, 16 splits), 1 node 15.4 -> 11.7 us (TG = 8, 16 splits); 8192 tokens, 60 nodes
+// 32.3 -> 21.2 us.
+//
+// Per chunk (v_mfma_f32_32x32x16_bf16, fp32 accumulate):
+//   S^T = K . Q^T     tokens are the M index, query rows the N index, so each
+//                     lane holds 16 tokens of ONE query row: max, sum and rescale
+//                     are lane-local (one exchange with lane ^ 32);
+//   O^T += V^T . P^T  the S^T accumulator, converted to bf16, already has the
+//                     B-operand layout; V comes out of LDS transposed (8 tokens
+//                     of one channel per lane) through ds_read_b64_tr_b16.
+// The reference maximum of a row is only moved when the true maximum runs more than 2^8 ahead of it.
+//
+// Epilogue: the TG token groups merge their (O, m, l) through LDS and write one split-KV partial per (split, row);
+// combine.hip finishes.
+//
+// grid: x = tile * 8 + xcd, y = (bg / 8) * nsplit + split   with bg = b * Hkv + g and xcd = bg % 8.  Workgroups are
+// handed to the 8 XCDs round-robin in linear order and gridDim.x is a multiple of 8, so a (sequence, KV head) stays on
+// XCD bg % 8 with all its splits and tiles: the K/V bytes of a split come from HBM once and from that XCD's L2 for the
+// other tiles, and the partials of a head are merged on the XCD that wrote them.  Where
+// the pairs are no multiple of 8 (two KV heads: two XCDs would do all the work), the (pair, split) units are dealt to the
+// XCDs instead, y = unit / 8: the tiles of a unit still share an L2.
+#include "attn_mfma.h"
+
+namespace specpv {
+
+#ifdef SPECPV_TIMELINE
+#define SPECPV_STAMP(i)                                                                                                      \
+    do {                                                                                                                     \
+        if (timeline && threadIdx.x == 0)                                                                                    \
+            timeline[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 16 + (i)] = __builtin_amdgcn_s_memrealtime();           \
+    } while (0)
+#else
+#define SPECPV_STAMP(i) do {} while (0)
+#endif
+
+constexpr int kTileRing = 8 * kStageBytes;
+static_assert(kTileRing == 8 * 32 * kOPitch * (int)sizeof(float), "the merge of the token groups reuses the ring exactly");
+
+// PEND: partially verified tokens may stand in front of the tree (s.kctx > 0).
+template <bool ALIGNED, int TG, bool PEND>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, const int32_t *a_ctx_len,
+                          const void *a_q, int a_n_sel, int a_M, int a_Hq, int a_nctx,
+                          Shape s, Partials part, MfmaArgs a, unsigned long long *timeline)
+{
+    constexpr int RB = 8 / TG, STG = RB;               // row blocks per workgroup; ring stages per token group
+    constexpr int AHEAD = TG == 2 ? 3 : STG;           // chunks requested in front of the one in use
+    constexpr int KOPS = RB == 4 ? 4 : 8;              // K (or V) operations of a chunk that one wavefront issues
+    constexpr int OPS = RB == 1 ? 16 : KOPS;           // all operations of a chunk that one wavefront issues
+    // the leading scalar arguments repeat what the first round of reads needs: they arrive in registers
+    s.ctx_len = a_ctx_len; s.q = a_q; s.M = a_M; s.Hq = a_Hq;
+    a.sel_idx = a_sel_idx; a.sel_count = a_sel_count; a.n_sel = a_n_sel;
+    const int nctx = a_nctx;
+    extern __shared__ char lds_raw[];
+    float *ms = (float *)lds_raw;            // [TG][32 RB]
+    float *ls = ms + 256;                    // [TG][32 RB]
+    char *ring = lds_raw + 2048;             // [TG][STG][K 8 KiB | V]
+    float *obuf = (float *)(lds_raw + 2048); // [TG][32 RB][kOPitch], reuses the ring after the main loop
+    SPECPV_CLOCKS_BEGIN;
+    SPECPV_STAMP(0);   // entry
+
+    // ---- which piece of work is this workgroup -------------------------------------
+    const int xcd = blockIdx.x & 7, tile = blockIdx.x >> 3;
+    int bg, sp;
+    if ((a.n_bg & 7) == 0) {
+        const int bgh = (int)a.div_nsplit.div(blockIdx.y);
+        sp = (int)blockIdx.y - bgh * nctx;
+        bg = bgh * 8 + xcd;
+    } else {
+        const int u = (int)blockIdx.y * 8 + xcd;
+        bg = (int)a.div_nsplit.div((uint32_t)u);
+        sp = u - bg * nctx;
+        if (bg >= a.n_bg) return;
+    }
+    const int b = (int)a.div_hkv.div((uint32_t)bg);
+    const int g = bg - b * s.Hkv;
+    const int R = s.M * s.G, row0 = tile * (32 * RB);
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tg = wave & (TG - 1), rb = wave / TG;
+    const int n = lane & 31, kg = lane >> 5;
+
+    // Everything whose address only depends on the kernel arguments is requested up
+    // front, so that the cold-miss latencies of these small reads overlap: context
+    // length, list length, the kept-block list (up to 256 entries, lane t: entries t, t + 64, ..)
+    // and the query rows.
+    const int32_t *sel = a.sel_idx ? a.sel_idx + (int64_t)bg * a.n_sel : nullptr;
+    const uint32_t Bu = (uint32_t)s.B;
+    const int L = s.ctx_len[b];
+    const int cnt_raw = sel ? a.sel_count[bg] : 0;
+    const bool list_in_regs = ALIGNED && sel && a.n_sel <= 256;
+    int idv[4] = {-1, -1, -1, -1};
+    if (list_in_regs) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+            if (lane + 64 * x < a.n_sel) idv[x] = sel[lane + 64 * x];
+    }
+    // The query rows of a row block are the same for its TG wavefronts: each brings its share of the eight k-steps
+    // straight into LDS, laid out as the operands are read (k-step ks: 1 KiB, lane l's 16 bytes at 16 l), and all read
+    // the whole from there once the requests have landed -- fewer bytes through the CU's memory path in the phase where
+    // the first K / V chunks are requested.  TG = 2: four row blocks are more than the ring leaves free, so they stand
+    // in the groups' last stages, whose first chunk is requested behind them.
+    auto q_stage = [&](int rbq) -> char * {
+        return TG == 2 ? ring + ((rbq >> 1) * STG + (STG - 1)) * kStageBytes + (rbq & 1) * 8192 : ring + kTileRing + rbq * 8192;
+    };
+    {
+        const int r = min(row0 + rb * 32 + n, R - 1);   // rows past the end repeat the last one; never stored
+        const int hh = (int)a.div_M.div((uint32_t)r), j = r - hh * s.M;
+        const char *qrow = (const char *)((const uint16_t *)s.q + (((int64_t)b * s.M + j) * s.Hq + g * s.G + hh) * 128 + kg * 8);
+        char *dst = q_stage(rb);
+#pragma unroll
+        for (int x = 0; x < 8 / TG; ++x) {
+            const int ks = tg * (8 / TG) + x;   // a k-step is 16 channels: 32 bytes
+            __builtin_amdgcn_global_load_lds((glb_void_ptr)(qrow + 32 * ks), (lds_void_ptr)(dst + 1024 * ks), 16, 0, 0);
+        }
+    }
+
+    int nb = L > 0 ? (int)a.div_B.div((uint32_t)(L + s.B - 1)) : 0;
+    if (nb > s.max_blocks) nb = s.max_blocks;
+    int cnt = nb;
+    if (sel) cnt = max(0, min(cnt_raw, a.n_sel));
+    const uint32_t T = nb > 0 ? (uint32_t)cnt * Bu : 0u;   // host guarantees max_blocks * B <= 2^30
+    // chunks of cache tokens, then the chunks of the partially verified tokens (the first kctx draft nodes: a
+    // chain that every query node descends from, so all rows attend all of them, like cache tokens)
+    const uint32_t C_ctx = (T + 31u) >> 5;
+    const int kctx = PEND ? s.kctx : 0;
+    const uint32_t C = C_ctx + (((uint32_t)kctx + 31u) >> 5);
+    const char *kdb = (const char *)s.kd + (((int64_t)b * s.Mk) * s.Hkv + g) * 256;
+    const char *vdb = (const char *)s.vd + (((int64_t)b * s.Mk) * s.Hkv + g) * 256;
+    const uint32_t stp = (uint32_t)s.Hkv * 256u;   // bytes from one draft node's row to the next
+
+    // uniform slab bases; per-lane byte offsets inside a slab fit 32 bits (host-checked)
+    const char *kb = (const char *)s.k + ((int64_t)b * s.sb + (int64_t)g * s.sh) * 2;
+    const char *vb = (const char *)s.v + ((int64_t)b * s.sb + (int64_t)g * s.sh) * 2;
+    const uint32_t st2 = (uint32_t)s.st * 2u;   // bytes per token row step
+
+    char *my_ring = ring + tg * (STG * kStageBytes);
+    const uint32_t ring_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)my_ring;
+    // K tile in LDS: row-major, 256 B per token, the 16-byte pieces of row t stored at
+    // piece index (p ^ (t & 15)) so that the operand reads below (16 lanes per cycle, same piece,
+    // different rows) spread over all 64 banks.  Operand piece of k-step ks: 2*ks + kg, i.e. kread ^ 32 ks
+    // (rows and stages start 256-byte aligned).
+    const uint32_t kread = ring_addr + (uint32_t)n * 256u + ((16u * (uint32_t)kg) ^ (16u * ((uint32_t)n & 15u)));   // + stage * kStageBytes
+    const uint32_t vread = ring_addr + 8192u + (uint32_t)(4 * kg + ((lane & 15) >> 2)) * kVPiecePitch +
+                           32u * (uint32_t)((lane >> 4) & 1) + 8u * (uint32_t)(lane & 3);   // + stage * kStageBytes
+
+    const int r4 = lane >> 4, pos = lane & 15;
+    const uint32_t sw0 = 16u * (uint32_t)(pos ^ r4), vsw = 16u * (uint32_t)pos;   // K row 4 i + r4: piece pos ^ ((4 i + r4) & 15) = sw0 ^ 64 (i & 3)
+    const uint32_t lane_row_off = (uint32_t)r4 * st2;
+    const bool do_k = RB == 1 || rb < RB / 2, do_v = RB == 1 || rb >= RB / 2;   // which half of a chunk this wavefront brings
+    const int op0 = RB == 4 ? 4 * (rb & 1) : 0;                                // ... from which operation on
+
+    const int W = nctx * TG, wsid = sp * TG + tg;
+    // chunks of a list that precede the share of token group w; shares differ by at most one
+    auto first_chunk = [&](uint32_t chunks, int w) -> int {
+        const uint32_t base = a.div_W.div(chunks), rem = chunks - base * (uint32_t)W;
+        return (int)((uint32_t)w * base + min((uint32_t)w, rem));
+    };
+    const int c0 = first_chunk(C, wsid), c1 = first_chunk(C, wsid + 1);
+    const int nch = c1 - c0;
+    const int nch_max = first_chunk(C, sp * TG + 1) - first_chunk(C, sp * TG);   // token group 0 has the most
+    SPECPV_STAMP(9);   // the scalar reads (lengths, list length) are in: the chunk counts are known
+
+    // ---- chunk -> token rows ------------------------------------------------------------
+    // ALIGNED (B % 32 == 0): a chunk lies inside one block, so its 32 rows are consecutive.  The
+    // first rows of the next 64 chunks of this wavefront sit in a register (lane t: chunk
+    // row_base + t) and are picked with readlane.  Encoding: r >= 0: all 32 rows r .. r+31 are
+    // valid tokens (the common case, handled without any further test); -1: no valid token;
+    // -2 - r: rows from r on, cut off by the context length.
+    int row_base = 0, row0vec = -1;
+    auto encode_row = [&](int blk, uint32_t p0, uint32_t slot) -> int {
+        if (blk < 0 || blk >= nb) return -1;
+        const int r = blk * s.B + (int)(p0 - slot * Bu);
+        return r >= L ? -1 : (r + 32 > L ? -2 - r : r);
+    };
+    auto fill_rows = [&](int cb) {
+        row_base = cb;
+        int r = -1;
+        if (cb + lane < nch && (uint32_t)(c0 + cb + lane) < C_ctx) {
+            const uint32_t p0 = (uint32_t)(c0 + cb + lane) * 32u;   // < T: the slot below is < cnt
+            const uint32_t slot = a.div_B.div(p0);
+            r = encode_row(sel ? sel[slot] : (int)slot, p0, slot);
+        }
+        row0vec = r;
+        // wait for the list entries here, inside the rare branch, so that the common path that
+        // joins behind it carries no pending load (and no wait on the DMA prefetch)
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    };
+    // the first 64 chunks: the list sits in registers (lane t: entries t, t + 64, ...), so this is a
+    // cross-lane read and no second trip to memory
+    auto fill_rows_first = [&]() {
+        if (!list_in_regs) { fill_rows(0); return; }
+        const uint32_t p0 = (uint32_t)(c0 + lane) * 32u;
+        const uint32_t slot = a.div_B.div(p0);
+        const int src = (int)(slot & 63u);
+        const int e0 = __shfl(idv[0], src), e1 = __shfl(idv[1], src), e2 = __shfl(idv[2], src), e3 = __shfl(idv[3], src);
+        const int q4 = (int)(slot >> 6);
+        const int blk = q4 == 0 ? e0 : (q4 == 1 ? e1 : (q4 == 2 ? e2 : e3));
+        row0vec = (lane < nch && (uint32_t)(c0 + lane) < C_ctx) ? encode_row(blk, p0, slot) : -1;   // p0 < T there: the slot is < cnt
+    };
+    // general case: this lane's token (t = lane & 31) of chunk ci, or -1
+    auto lane_row = [&](int ci) -> int {
+        const uint32_t p = (uint32_t)(c0 + ci) * 32u + (uint32_t)n;
+        if (p >= T) return -1;
+        const uint32_t slot = a.div_B.div(p);
+        const int blk = sel ? sel[slot] : (int)slot;
+        if (blk < 0 || blk >= nb) return -1;
+        const int tok = blk * s.B + (int)(p - slot * Bu);
+        return tok < L ? tok : -1;
+    };
+
+    uint32_t vmv = 0u;   // validity words of the chunks in the ring: lane t holds those of stage t
+
+    // Request this wavefront's share of chunk ci, 1 KiB per operation (one 256-byte row per 16 lanes): K operation i
+    // brings rows 4i .. 4i+3, pieces swizzled by row & 15; V operation i brings rows i, i+8, i+16, i+24 into piece i.
+    // rows given per lane (t = lane & 31: token tk of the chunk)
+    auto issue_rows = [&](const char *kbase, const char *vbase, const uint32_t stride, const uint32_t tk, char *dst) {
+        if (do_k) {
+#pragma unroll
+            for (int x = 0; x < KOPS; ++x) {
+                const int i = op0 + x;
+                const uint32_t tv = (uint32_t)__shfl((int)tk, 4 * i + r4) * stride;
+                dma16(kbase + (tv + (sw0 ^ (64u * (uint32_t)(i & 3)))), dst + i * 1024);
+            }
+        }
+        if (do_v) {
+#pragma unroll
+            for (int x = 0; x < KOPS; ++x) {
+                const int i = op0 + x;
+                const uint32_t tv = (uint32_t)__shfl((int)tk, 8 * r4 + i) * stride;
+                dma16(vbase + (tv + vsw), dst + 8192 + i * kVPiecePitch);
+            }
+        }
+    };
+    auto issue = [&](int ci) {
+        const int stg = ci & (STG - 1);
+        char *dst = my_ring + stg * kStageBytes;
+        int tok;
+        if (PEND && kctx > 0 && (uint32_t)(c0 + ci) >= C_ctx) {
+            // a chunk of partially verified tokens: rows of the draft K / V arrays
+            const int pr = (int)((uint32_t)(c0 + ci) - C_ctx) * 32 + n;
+            const int ptok = pr < kctx ? pr : -1;
+            const uint32_t vm = (uint32_t)__ballot(ptok >= 0);
+            vmv = lane == stg ? vm : vmv;
+            issue_rows(kdb, vdb, stp, (uint32_t)max(ptok, 0), dst);
+            return;
+        }
+        if (ALIGNED) {
+            if (ci - row_base >= 64) fill_rows(ci);
+            const int r0 = __builtin_amdgcn_readlane(row0vec, ci - row_base);
+            if (r0 >= 0) {
+                vmv = lane == stg ? 0xffffffffu : vmv;
+                const size_t first = (size_t)((uint32_t)r0 * st2);   // fits 32 bits (host-checked)
+                if (st2 == 256u) {
+                    // rows are 256 bytes apart (the usual head-major cache): the instruction's
+                    // immediate offset, added to the global and to the LDS address, covers the step
+                    // between consecutive operations (K: 1 KiB on both sides; V: 256 bytes, with the
+                    // LDS base adjusted for the rest of the piece pitch)
+                    if (do_k) {
+                        dma16x4(kb + first + op0 * 1024, lane_row_off, sw0, dst + op0 * 1024);
+                        if (KOPS == 8) dma16x4(kb + first + 4096, lane_row_off, sw0, dst + 4096);
+                    }
+                    if (do_v) {
+                        const char *vsrc = vb + first + op0 * 256 + ((uint32_t)r4 * 2048u + vsw);
+                        char *dstv = dst + 8192 + op0 * kVPiecePitch;
+#define SPECPV_VOP(i) __builtin_amdgcn_global_load_lds((glb_void_ptr)vsrc, (lds_void_ptr)(dstv + (i) * (kVPiecePitch - 256)), 16, (i) * 256, kKvAux)
+                        SPECPV_VOP(0); SPECPV_VOP(1); SPECPV_VOP(2); SPECPV_VOP(3);
+                        if (KOPS == 8) { SPECPV_VOP(4); SPECPV_VOP(5); SPECPV_VOP(6); SPECPV_VOP(7); }
+#undef SPECPV_VOP
+                    }
+                } else {
+                    if (do_k) {
+#pragma unroll
+                        for (int x = 0; x < KOPS; ++x)
+                            dma16(kb + first + (size_t)(4 * (op0 + x)) * st2 + (lane_row_off + (sw0 ^ (64u * (uint32_t)(x & 3)))), dst + (op0 + x) * 1024);
+                    }
+                    if (do_v) {
+#pragma unroll
+                        for (int x = 0; x < KOPS; ++x)
+                            dma16(vb + first + (size_t)(8 * r4 + op0 + x) * st2 + vsw, dst + 8192 + (op0 + x) * kVPiecePitch);
+                    }
+                }
+                return;
+            }
+            const int rr = -2 - r0;   // r0 == -1 gives -1
+            tok = (rr >= 0 && rr + n < L) ? rr + n : -1;
+        } else {
+            tok = lane_row(ci);
+        }
+        const uint32_t vm = (uint32_t)__ballot(tok >= 0);
+        vmv = lane == stg ? vm : vmv;
+        issue_rows(kb, vb, st2, tok >= 0 ? (uint32_t)tok : 0u, dst);   // row 0 exists (L > 0); masked later
+    };
+
+    if (ALIGNED && nch > 0) fill_rows_first();
+    // every load above has been consumed here: from now on the only vector-memory
+    // operations of this wavefront in flight are its own DMA groups (OPS operations each)
+    // (as an instruction the compiler knows, not inline assembly: otherwise it assumes that the
+    // loads of the prologue may still be in flight at the loop header and waits for vmcnt(0),
+    // i.e. for the prefetch just issued, at the first use of Q in every iteration)
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), expcnt and lgkmcnt untouched
+    asm volatile("" ::: "memory");
+    SPECPV_STAMP(1);   // arguments, lengths, list, query rows are in
+
+    f32x16 O[4];
+    float m_ref = -INFINITY, l_run = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) O[j][i] = 0.f;
+
+    // ---- main loop ---------------------------------------------------------------------
+    bf16x8 qf[8];   // Q fragments (B operand of S^T = K . Q^T): row = lane & 31
+    // This wavefront's share of the query rows has landed (the wait above); the barrier in front of the first chunk
+    // covers the others' shares.
+    auto read_q = [&]() {
+        const uint32_t q0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)q_stage(rb) + (uint32_t)(lane * 16);
+        const uint32_t qa[8] = {q0, q0 + 1024u, q0 + 2048u, q0 + 3072u, q0 + 4096u, q0 + 5120u, q0 + 6144u, q0 + 7168u};
+        uint4 qraw[8];
+        lds_read_k<0>(qa, qraw);
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) qf[ks] = as_bf16x8(qraw[ks]);
+    };
+#pragma unroll
+    for (int c = 0; c < AHEAD; ++c)
+        if (c < nch) issue(c);
+    SPECPV_STAMP(2);   // first chunks requested
+    for (int i = 0; i < nch_max; ++i) {
+        const bool active = i < nch;
+        const int stg = i & (STG - 1);
+        if (i < 4) SPECPV_STAMP(12 + i);   // done with chunk i - 1, about to wait for chunk i
+        // own share of chunk i has landed: the younger groups (at most AHEAD - 1) may stay in flight
+        if (AHEAD >= 3 && i + 2 < nch) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * OPS) : "memory");
+        else if (AHEAD >= 2 && i + 1 < nch) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(OPS) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (RB > 1 || i == 0) __builtin_amdgcn_s_barrier();   // ... and so have the other wavefronts' shares
+        if (i < 4) SPECPV_STAMP(3 + i);   // chunk i has landed
+        if (i == 0) {
+            read_q();
+            if (TG == 2) __builtin_amdgcn_s_barrier();   // the last stages no longer hold query rows
+        }
+        // four stages: the one that chunk i - 1 was read from is free (every wavefront has passed this iteration's barrier)
+        if (TG == 2 && i + AHEAD < nch) issue(i + AHEAD);
+        uint4 kf[8];
+        uint2 v[16];
+        const uint32_t vmask = (uint32_t)__builtin_amdgcn_readlane((int)vmv, stg);
+        if (active) {
+            const uint32_t k0 = kread + (uint32_t)stg * kStageBytes;
+            const uint32_t ka[8] = {k0, k0 ^ 32u, k0 ^ 64u, k0 ^ 96u, k0 ^ 128u, k0 ^ 160u, k0 ^ 192u, k0 ^ 224u};
+            lds_read_k<0>(ka, kf);
+            lds_read_v<0>(vread + (uint32_t)stg * kStageBytes, v);
+        }
+        if (TG == 4) __builtin_amdgcn_s_barrier();       // both wavefronts of the pair hold chunk i in registers
+        if (TG != 2 && i + AHEAD < nch) issue(i + AHEAD);
+        if (!active) continue;
+
+        f32x16 S;
+#pragma unroll
+        for (int x = 0; x < 16; ++x) S[x] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks)
+            S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[ks]), qf[ks], S, 0, 0, 0);
+
+        if (vmask != 0xffffffffu) {
+#pragma unroll
+            for (int x = 0; x < 16; ++x) {
+                const int tt = (x >> 2) * 8 + kg * 4 + (x & 3);
+                if (!((vmask >> tt) & 1u)) S[x] = -INFINITY;
+            }
+        }
+        float mx = fmaxf(S[0], S[1]);
+#pragma unroll
+        for (int x = 2; x < 16; x += 2) mx = fmaxf(fmaxf(mx, S[x]), S[x + 1]);
+        mx *= a.scale_log2;
+        // the reference max only moves when the true max gets more than 2^slack ahead (tested on each lane's half of
+        // the chunk's tokens; the row's maximum is formed behind the branch -- in the group kernel the same change
+        // measured 3 % slower, so it keeps the exchange in front)
+        if (__any(mx > m_ref + kRescaleSlack)) {
+            mx = max_xor32(mx);
+            const float m_new = mx > m_ref + kRescaleSlack ? mx : m_ref;
+            const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_ref - m_new);
+            m_ref = m_new;
+            l_run *= alpha;
+            if (__any(alpha != 1.f && l_run != 0.f)) {   // nothing to rescale while O is still zero
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int x = 0; x < 16; ++x) O[j][x] *= alpha;
+            }
+        }
+        const float m_use = m_ref == -INFINITY ? 0.f : m_ref;
+        uint32_t pk[8];
+        float lsum = 0.f;
+#pragma unroll
+        for (int x = 0; x < 16; x += 2) {
+            const float p0 = __builtin_amdgcn_exp2f(fmaf(S[x], a.scale_log2, -m_use));
+            const float p1 = __builtin_amdgcn_exp2f(fmaf(S[x + 1], a.scale_log2, -m_use));
+            pk[x >> 1] = pack_bf16x2(p0, p1);
+            lsum = add_bf16x2(pk[x >> 1], lsum);   // the sum runs over the rounded weights the MFMA sees
+        }
+        l_run += lsum;
+        const uint4 pf0 = make_uint4(pk[0], pk[1], pk[2], pk[3]), pf1 = make_uint4(pk[4], pk[5], pk[6], pk[7]);
+#pragma unroll
+        for (int ks2 = 0; ks2 < 2; ++ks2)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint2 lo = v[(ks2 * 4 + j) * 2], hi = v[(ks2 * 4 + j) * 2 + 1];
+                O[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)),
+                                                               as_bf16x8(ks2 ? pf1 : pf0), O[j], 0, 0, 0);
+            }
+    }
+    __syncthreads();   // every wavefront is done with the rings: the epilogue reuses that LDS
+    SPECPV_STAMP(7);   // main loop done
+
+    // ---- merge the token groups --------------------------------------------------------
+    {
+        l_run = sum_xor32(l_run);
+        const int row = rb * 32 + n;
+        if (kg == 0) {
+            ms[tg * (32 * RB) + row] = m_ref;
+            ls[tg * (32 * RB) + row] = l_run;
+        }
+        // accumulator element 4q + x of tile j is channel 32j + 8q + 4kg + x of this lane's row
+        float *dst = obuf + ((size_t)tg * (32 * RB) + row) * kOPitch;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *(float4 *)(dst + 32 * j + 8 * q + 4 * kg) = make_float4(O[j][4 * q], O[j][4 * q + 1], O[j][4 * q + 2], O[j][4 * q + 3]);
+    }
+    __syncthreads();
+    constexpr int RPW = 4 * RB;   // rows each wavefront finishes
+    const int64_t prow0 = ((int64_t)bg * part.nsplit + sp) * R + row0 + wave * RPW;
+    const int n_rows = min(RPW, R - row0 - wave * RPW);   // may be negative
+    // weights of the token groups for the rows this wavefront finishes (lane -> row)
+    float wgt[TG], m_row = -INFINITY, l_row = 0.f;
+    {
+        const int row = wave * RPW + (lane & (RPW - 1));
+        float mw[TG];
+#pragma unroll
+        for (int w = 0; w < TG; ++w) { mw[w] = ms[w * (32 * RB) + row]; m_row = fmaxf(m_row, mw[w]); }
+        const float m_use = m_row == -INFINITY ? 0.f : m_row;
+#pragma unroll
+        for (int w = 0; w < TG; ++w) {
+            wgt[w] = __builtin_amdgcn_exp2f(mw[w] - m_use);   // 0 for a token group without valid tokens
+            l_row = fmaf(ls[w * (32 * RB) + row], wgt[w], l_row);
+        }
+    }
+    {
+        // channels 2 lane, 2 lane + 1 of each row, normalised by the row's l
+        const float il = l_row > 0.f ? 1.f / l_row : 0.f;
+        float2 acc[RPW];
+#pragma unroll
+        for (int uu = 0; uu < RPW; ++uu) {
+            acc[uu] = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int w = 0; w < TG; ++w) {
+                const float ww = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wgt[w]), uu));   // uniform: no LDS shuffle
+                const float2 x = *(const float2 *)(obuf + ((size_t)w * (32 * RB) + wave * RPW + uu) * kOPitch + 2 * lane);
+                acc[uu].x = fmaf(ww, x.x, acc[uu].x);
+                acc[uu].y = fmaf(ww, x.y, acc[uu].y);
+            }
+        }
+#pragma unroll
+        for (int uu = 0; uu < RPW; ++uu) {
+            const float ilu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(il), uu));
+            if (uu < n_rows) store_partial_half(part.o + (prow0 + uu) * 64, lane, acc[uu].x * ilu, acc[uu].y * ilu);   // 128 halves per row
+        }
+    }
+    if (lane < n_rows && lane < RPW) *(float2 *)(part.ml + (prow0 + lane) * 2) = make_float2(m_row, l_row);
+    SPECPV_STAMP(8);   // partial stores issued
+    SPECPV_CLOCKS_END(timeline, 3072 + ((size_t)blockIdx.y * gridDim.x + blockIdx.x), first_chunk(C, sp * TG + TG) - first_chunk(C, sp * TG));
+    // The combine kernel that follows reads the tree's parents and, one trip later, its K / V rows: nobody
+    // has touched those in this call yet.  Ask for them here, on the way out (nothing waits for the data):
+    // they are then in this XCD's L2, where that kernel's workgroups of the same KV head run.
+    if (wave == 0 && s.kd && s.vd && s.parent) {
+        const int nw = (int)(gridDim.x >> 3) * nctx, w = tile * nctx + sp;
+        const char *base = (lane & 16) ? (const char *)s.vd : (const char *)s.kd;
+        for (int node = w; node < s.Mk; node += nw) {
+            uint32_t tmp;
+            const char *p = base + (((int64_t)b * s.Mk + node) * s.Hkv + g) * 256 + (lane & 15) * 16;
+            if (lane < 32) asm volatile("global_load_dword %0, %1, off" : "=v"(tmp) : "v"(p) : "memory");
+        }
+        if (w == 0 && lane < 2) {
+            uint32_t tmp;
+            const char *p = (const char *)(s.parent + (int64_t)b * s.Mk) + lane * 256;
+            if (lane * 64 < s.Mk) asm volatile("global_load_dword %0, %1, off" : "=v"(tmp) : "v"(p) : "memory");
+        }
+    }
+}
+
+hipError_t launch_attn_ctx_tile(const Shape &s, const int32_t *sel_idx, const int32_t *sel_count, int n_sel, Partials p,
+                                int tg, unsigned long long *timeline, hipStream_t st)
+{
+    if (s.D != 128 || (tg != 2 && tg != 4 && tg != 8)) return hipErrorInvalidValue;
+    const int rows = 256 / tg, tiles = (s.M * s.G + rows - 1) / rows, nctx = p.nsplit;
+    MfmaArgs a = {};
+    a.sel_idx = sel_idx;
+    a.sel_count = sel_count;
+    a.n_sel = n_sel;
+    a.scale_log2 = kLog2e / sqrtf(128.f);
+    a.n_bg = s.batch * s.Hkv;
+    a.div_nsplit = make_fastdiv((uint32_t)nctx);
+    a.div_hkv = make_fastdiv((uint32_t)s.Hkv);
+    a.div_B = make_fastdiv((uint32_t)s.B);
+    a.div_M = make_fastdiv((uint32_t)s.M);
+    a.div_W = make_fastdiv((uint32_t)(nctx * tg));   // token ranges: one per token group of every split
+    const dim3 grid(8 * tiles, (a.n_bg * nctx + 7) / 8);
+    if (grid.y > 65535u) return hipErrorInvalidConfiguration;
+    const bool aligned = s.B % 32 == 0, pend = s.kctx > 0;
+    const size_t lds = 2048 + kTileRing + (tg == 2 ? 0 : (8 / tg) * 8192);
+#define SPECPV_LAUNCH(AL, TGV, PE)                                                                                   \
+    do {                                                                                                             \
+        static PerDeviceOnce once;   /* one per kernel instantiation */                                             \
+        auto kern = attn_ctx_tile_kernel<AL, TGV, PE>;                                                               \
+        const hipError_t e0 = once.run([&] {                                                                         \
+            return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);    \
+        });                                                                                                          \
+        if (e0 != hipSuccess) return e0;                                                                             \
+        hipLaunchKernelGGL(kern, grid, dim3(512), lds, st, sel_idx, sel_count, s.ctx_len, s.q, n_sel, s.M, s.Hq,     \
+                           nctx, s, p, a, timeline);                                                                 \
+    } while (0)
+#define SPECPV_LAUNCH_TG(TGV)                                                                                        \
+    do {                                                                                                             \
+        if (aligned) { if (pend) SPECPV_LAUNCH(true, TGV, true); else SPECPV_LAUNCH(true, TGV, false); }              \
+        else { if (pend) SPECPV_LAUNCH(false, TGV, true); else SPECPV_LAUNCH(false, TGV, false); }                    \
+    } while (0)
+    if (tg == 2) SPECPV_LAUNCH_TG(2);
+    else if (tg == 4) SPECPV_LAUNCH_TG(4);
+    else SPECPV_LAUNCH_TG(8);
+#undef SPECPV_LAUNCH_TG
+#undef SPECPV_LAUNCH
+    return hipGetLastError();
+}
+
+}  // namespace specpv

@@ -4,7 +4,15 @@
 // partials of the context part by their log-sum-exp weights, normalise and store.
 // Sixteen lanes per output row (a lane owns D / 16 adjacent channels), four query heads of
 // one KV group per wavefront: they share the node, its root path and the draft K / V rows.
+// TWO: two wavefronts per four rows, one for the tree segment and one for the partials: each is a chain of a round trip or
+// two and a few hundred dependent instructions (a wavefront by itself issues one per eight cycles), and the two chains
+// have nothing in common until the last step.  Up to 16 partials are requested at once, 16 bytes per lane each, and a
+// lane works out the weights of its own partials only.  Calls of one sequence, against one wavefront that fetched eight
+// partials a round in 8-byte pieces and kept every (m, l) pair in every lane: with 8 splits 17.4 -> 17.3 us, with 16 20.7
+// -> 16.5, with 32 24.7 -> 19.8.
+// (A tree segment on the matrix cores, dense over 32 nodes with a bit mask, was slower: 18.6 us with 8 splits.)
 #include "internal.h"
+#include <type_traits>
 
 namespace specpv {
 
@@ -36,6 +44,12 @@ template <int CPL> struct Chan<float, CPL> {
 #pragma unroll
         for (int x = 0; x < CPL / 4; ++x) { f[4 * x] = r[x].x; f[4 * x + 1] = r[x].y; f[4 * x + 2] = r[x].z; f[4 * x + 3] = r[x].w; }
     }
+    static __device__ __forceinline__ float dot(const Raw &a, const Raw &b) {
+        float d = 0.f;
+#pragma unroll
+        for (int x = 0; x < CPL / 4; ++x) d = fmaf(a[x].w, b[x].w, fmaf(a[x].z, b[x].z, fmaf(a[x].y, b[x].y, fmaf(a[x].x, b[x].x, d))));
+        return d;
+    }
     static __device__ __forceinline__ void store_stream(void *p, int64_t i, const float *f) {
         typedef float f32x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
@@ -45,8 +59,17 @@ template <int CPL> struct Chan<float, CPL> {
         }
     }
 };
+// acc + a.lo * b.lo + a.hi * b.hi for packed bf16 pairs
+__device__ __forceinline__ float dot_bf16x2(uint32_t a, uint32_t b, float acc)
+{
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, b), acc, false);
+}
 template <> struct Chan<bf16_t, 8> {
     typedef uint4 Raw;
+    static __device__ __forceinline__ float dot(const Raw &a, const Raw &b) {
+        return dot_bf16x2(a.w, b.w, dot_bf16x2(a.z, b.z, dot_bf16x2(a.y, b.y, dot_bf16x2(a.x, b.x, 0.f))));
+    }
     static __device__ __forceinline__ void load(const void *p, int64_t i, Raw &r) { r = *(const uint4 *)((const uint16_t *)p + i); }
     static __device__ __forceinline__ void unpack(const Raw &r, float *f) { Elem<bf16_t>::unpack(r, f); }
     static __device__ __forceinline__ void store_stream(void *p, int64_t i, const float *f) {
@@ -59,6 +82,7 @@ template <> struct Chan<bf16_t, 8> {
 };
 template <> struct Chan<bf16_t, 4> {
     typedef uint2 Raw;
+    static __device__ __forceinline__ float dot(const Raw &a, const Raw &b) { return dot_bf16x2(a.y, b.y, dot_bf16x2(a.x, b.x, 0.f)); }
     static __device__ __forceinline__ void load(const void *p, int64_t i, Raw &r) { r = *(const uint2 *)((const uint16_t *)p + i); }
     static __device__ __forceinline__ void unpack(const Raw &r, float *f) {
         f[0] = __uint_as_float(r.x << 16); f[1] = __uint_as_float(r.x & 0xffff0000u);
@@ -89,49 +113,99 @@ template <int CPL> __device__ __forceinline__ void load_partial(const float *p, 
     }
 }
 
-// The same for the fp16 form of the partials: the lane's CPL channels (adjacent, in order) of a row of D
-// halves whose first element has index i.
-template <int CPL> __device__ __forceinline__ void load_partial_half(const float *p, int64_t i, int lane16, float *f)
-{
-    typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-    const f16x4 *src = (const f16x4 *)((const _Float16 *)p + i + lane16 * CPL);
+// The lane's channels of one partial as they come from memory, and as fp32 once they are used.
+template <int CPL, bool HALF> struct Part {   // fp32 form
+    float f[CPL];
+    __device__ __forceinline__ void load(const float *p, int64_t row, int D, int lane16) { load_partial<CPL>(p, row * D + 4 * lane16, f); }
+    __device__ __forceinline__ void value(float *v) const
+    {
 #pragma unroll
-    for (int x = 0; x < CPL / 4; ++x) {
-        const f16x4 v = __builtin_nontemporal_load(src + x);
-        f[4 * x] = (float)v[0]; f[4 * x + 1] = (float)v[1]; f[4 * x + 2] = (float)v[2]; f[4 * x + 3] = (float)v[3];
+        for (int x = 0; x < CPL; ++x) v[x] = f[x];
     }
+};
+template <> struct Part<8, true> {   // fp16 form: the lane's eight adjacent channels are one 16-byte piece
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 raw;
+    __device__ __forceinline__ void load(const float *p, int64_t row, int D, int lane16)
+    {
+        raw = __builtin_nontemporal_load((const u32x4 *)((const _Float16 *)p + row * D + lane16 * 8));
+    }
+    __device__ __forceinline__ void value(float *v) const
+    {
+        typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+        const f16x8 h = __builtin_bit_cast(f16x8, raw);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) v[x] = (float)h[x];
+    }
+};
+
+// The value of lane U of a row of 16 lanes, in all of them.
+template <int U> __device__ __forceinline__ float row_bcast(float v) { return dpp_row<0x150 + U>(v); }   // row_newbcast
+__device__ __forceinline__ float row16_max(float x)
+{
+    x = fmaxf(x, dpp_row<0xB1>(x));
+    x = fmaxf(x, dpp_row<0x4E>(x));
+    x = fmaxf(x, dpp_row<0x141>(x));
+    return fmaxf(x, dpp_row<0x140>(x));
 }
 
-// NP: context partials fetched per round (the smallest of 2, 4, 8 that covers the split count keeps
-// the registers, and with them the resident wavefronts of a batch, in proportion).
-// MULTI: more splits than NP (the many splits of a full verification): rounds of NP, each round's
-// reads requested before the previous round is merged.  Without it the split count is at most NP.
-// NB: path nodes whose draft K / V rows are requested in the first go: 8 (a tree of candidates alone), or 24
-// when partially verified tokens stand in front of the tree as keys (every candidate's path then starts with
-// that whole chain; more registers, so only then).
-// HALF: the partials' O rows are fp16 and normalised (see Partials); else fp32 sums.
+// The root path of tree node j as a bit set; par0 / par1 hold parent[lane] / parent[lane + 64].  Everything is
+// wave-uniform (scalar registers).  Nodes below `stop` (partially verified tokens that the context kernels have attended
+// already) end the walk.
+__device__ __forceinline__ void root_path(int j, int n_nodes, int stop, int par0, int par1, unsigned long long &lo, unsigned long long &hi)
+{
+    int at = j;
+    for (int guard = 0; at >= stop && guard < n_nodes; ++guard) {
+        // (values, not a choice between two variables: the compiler would put those into memory)
+        const unsigned long long bit = 1ull << (at & 63);
+        lo |= at < 64 ? bit : 0ull;
+        hi |= at < 64 ? 0ull : bit;
+        const int pa = __builtin_amdgcn_readlane(at < 64 ? par0 : par1, at & 63);
+        at = pa < at ? pa : -1;   // a malformed parent[] (not strictly decreasing) ends the walk
+    }
+}
+// lowest node of the set (removed from it), or -1
+__device__ __forceinline__ int pop_node(unsigned long long &lo, unsigned long long &hi)
+{
+    const bool low = lo != 0ull;
+    const unsigned long long word = low ? lo : hi;
+    const int at = word ? __builtin_ctzll(word) + (low ? 0 : 64) : -1;
+    lo &= lo - (low ? 1ull : 0ull);
+    hi &= hi - (low || hi == 0ull ? 0ull : 1ull);
+    return at;
+}
+
 #ifdef SPECPV_TIMELINE
-#define SPECPV_CSTAMP(i)                                                                                     \
+#define SPECPV_CSTAMP(i, W)                                                                                  \
     do {                                                                                                     \
-        if (part.timeline && threadIdx.x == 0)                                                               \
+        if (part.timeline && threadIdx.x == 64 * (W))                                                        \
             part.timeline[(2048 + ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 16 + (i)] = \
                 __builtin_amdgcn_s_memrealtime();                                                            \
     } while (0)
 #else
-#define SPECPV_CSTAMP(i) do {} while (0)
+#define SPECPV_CSTAMP(i, W) do {} while (0)
 #endif
 
-template <typename T, int D, int NP, bool MULTI, int NB, bool HALF>
-__global__ __launch_bounds__(256) void combine_kernel(const int32_t *a_parent, const void *a_q, const float *a_po,
+// NP: context partials fetched at once (the smallest of 2, 4, 8, 16 that covers the split count keeps
+// the registers, and with them the resident wavefronts of a batch, in proportion).
+// MULTI: more splits than 16 (a full verification): rounds of NP = 8, each round's
+// reads requested before the previous round is merged.
+// NB: path nodes whose draft K / V rows are requested in the first go: 8 (a tree of candidates alone), or 24
+// when partially verified tokens stand in front of the tree as keys (every candidate's path then starts with
+// that whole chain; more registers, so only then).
+// HALF: the partials' O rows are fp16 and normalised (see Partials); else fp32 sums.
+template <typename T, int D, int NP, bool MULTI, int NB, bool HALF, bool TWO>
+__global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, const void *a_q, const float *a_po,
                                                     const float *a_pml, int a_M, int a_Hq, int a_G, int a_nsplit,
                                                     Shape s, Partials part, void *out, float *lse, float scale_log2)
 {
     // the leading scalar arguments repeat what the first round of reads needs; they can be preloaded into registers
     s.parent = a_parent; s.q = a_q; s.M = a_M; s.Hq = a_Hq; s.G = a_G;
     part.o = const_cast<float *>(a_po); part.ml = const_cast<float *>(a_pml); part.nsplit = a_nsplit;
-    SPECPV_CSTAMP(0);   // entry
     constexpr int CPL = D / 16;   // channels per lane: d = (lane & 15) * CPL + x
     typedef typename Chan<T, CPL>::Raw Raw;
+    __shared__ float tree_od[TWO ? 4 : 1][CPL / 4][64][4];   // [four heads][channels, four at a time][lane]
+    __shared__ float2 tree_ml[TWO ? 4 : 1][64];
     const int lane = threadIdx.x & 63;
     const int d0 = (lane & 15) * CPL;
     // x = XCD (workgroups go to the XCDs round-robin in linear order), y = node, z = bg / 8: the rows
@@ -140,165 +214,184 @@ __global__ __launch_bounds__(256) void combine_kernel(const int32_t *a_parent, c
     if (bg >= s.batch * s.Hkv) return;
     const int j = (int)blockIdx.y;
     const int b = bg / s.Hkv;
-    // four query heads of the KV group per wavefront; a group size that is no multiple of four
-    // leaves lanes that repeat the last head and store nothing
-    const int g = bg - b * s.Hkv, hh = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 4 + (lane >> 4);
+    // wavefronts 0 .. n - 1: the tree segments of four query heads each; n .. 2n - 1: their partials.  A group size that is
+    // no multiple of four leaves lanes that repeat the last head and store nothing
+    const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nq = TWO ? (int)(blockDim.x >> 7) : 0;
+    const bool tree_role = wave < nq;
+    const int quad = TWO && !tree_role ? wave - nq : wave;
+    const int g = bg - b * s.Hkv, hh = quad * 4 + (lane >> 4);
     const bool live = hh < s.G;
-    const int h = g * s.G + (live ? hh : s.G - 1);
-
-    // ---- every read whose address is known from the arguments goes out first ----------
-    // the tree has s.Mk nodes; query row j is node j + s.koff (the nodes in front are keys only)
-    const int32_t *par = s.parent + (int64_t)b * s.Mk;
-    const int par0 = lane < s.Mk ? par[lane] : -1;
-    const int par1 = lane + 64 < s.Mk ? par[lane + 64] : -1;
+    const int hc = live ? hh : s.G - 1, h = g * s.G + hc;
     const int64_t qrow = (((int64_t)b * s.M + j) * s.Hq + h) * D;
-    Raw qraw;
-    Chan<T, CPL>::load(s.q, qrow + d0, qraw);
-    const int R = s.M * s.G;   // rows of the KV head, node by node: one split's partials of this wavefront's heads are adjacent
-    const int64_t prow0 = ((int64_t)bg * part.nsplit) * R + j * s.G + (h - g * s.G);
-    // ... including the first NP context partials (all of them in the usual case); the 16 lanes
-    // of a row all fetch the row's (m, l) pairs, so the merge below needs no cross-lane step
-    struct Round { float2 ml[NP]; float po[NP][CPL]; };
-    auto fetch = [&](int sp0, Round &r) {
-#pragma unroll
-        for (int u = 0; u < NP; ++u) {
-            const int64_t prow = prow0 + (int64_t)min(sp0 + u, part.nsplit - 1) * R;
-            r.ml[u] = *(const float2 *)(part.ml + prow * 2);
-            if (HALF) load_partial_half<CPL>(part.o, prow * D, lane & 15, r.po[u]);
-            else load_partial<CPL>(part.o, prow * D + 4 * (lane & 15), r.po[u]);
-        }
-    };
-    Round ra;
-    fetch(0, ra);
+    if (wave == 0) SPECPV_CSTAMP(0, 0);   // entry
 
-    // ---- root path of node j as a bit set (wave-uniform walk over the parent registers) --
-    unsigned long long anc_lo = 0ull, anc_hi = 0ull;
-    {
-        int a = j + s.koff;
-        // (nodes below kctx are partially verified tokens that the context kernels have attended already)
-        for (int guard = 0; a >= s.kctx && guard < s.Mk; ++guard) {
-            if (a < 64) anc_lo |= 1ull << a; else anc_hi |= 1ull << (a - 64);
-            const int pa = a < 64 ? __builtin_amdgcn_readlane(par0, a) : __builtin_amdgcn_readlane(par1, a - 64);
-            a = pa < a ? pa : -1;   // a malformed parent[] (not strictly decreasing) ends the walk
-        }
-    }
-    SPECPV_CSTAMP(1);   // parents in, root path walked
-    // ---- second (and last) round of reads: draft K / V of the first 8 nodes of the path ----
-    auto pop = [&]() -> int {
-        int a = -1;
-        if (anc_lo) { a = __builtin_ctzll(anc_lo); anc_lo &= anc_lo - 1; }
-        else if (anc_hi) { a = 64 + __builtin_ctzll(anc_hi); anc_hi &= anc_hi - 1; }
-        return a;
+    // ---- draft-tree segment: first the reads that only need the arguments, then the root path and its rows, then the sums ----
+    int par0 = -1, par1 = -1;
+    Raw qraw;
+    auto tree_first = [&]() __attribute__((always_inline)) {
+        // the tree has s.Mk nodes; query row j is node j + s.koff (the nodes in front are keys only)
+        const int32_t *par = s.parent + (int64_t)b * s.Mk;
+        if (lane < s.Mk) par0 = par[lane];
+        if (lane + 64 < s.Mk) par1 = par[lane + 64];
+        Chan<T, CPL>::load(s.q, qrow + d0, qraw);
     };
+    unsigned long long anc_lo = 0ull, anc_hi = 0ull;
+    const int64_t drow0 = (((int64_t)b * s.Mk) * s.Hkv + g) * D + d0;
+    const int drow_step = s.Hkv * D;   // (Mk <= 128 rows: 32-bit offsets)
     int a8[NB];
     Raw kd8[NB], vd8[NB];
+    auto tree_rows = [&]() __attribute__((always_inline)) {
+        root_path(j + s.koff, s.Mk, s.kctx, par0, par1, anc_lo, anc_hi);
+        if (wave == 0) SPECPV_CSTAMP(1, 0);   // parents in, root path walked
 #pragma unroll
-    for (int u = 0; u < NB; ++u) {
-        a8[u] = pop();
-        const int64_t drow = (((int64_t)b * s.Mk + max(a8[u], 0)) * s.Hkv + g) * D;
-        Chan<T, CPL>::load(s.kd, drow + d0, kd8[u]);
-        Chan<T, CPL>::load(s.vd, drow + d0, vd8[u]);
-    }
-
-    // ---- context partials, merged relative to their running maximum (first-round data) ----
-    float m_ctx = -INFINITY, l_ctx = 0.f, o[CPL];
-#pragma unroll
-    for (int x = 0; x < CPL; ++x) o[x] = 0.f;
-    auto merge = [&](int sp0, const Round &r) {
-        float m_new = m_ctx;
-#pragma unroll
-        for (int u = 0; u < NP; ++u)
-            if (sp0 + u < part.nsplit) m_new = fmaxf(m_new, r.ml[u].x);
-        const float m_use = m_new == -INFINITY ? 0.f : m_new;
-        const float alpha = exp2f(m_ctx - m_use);   // 0 while nothing has been merged
-        l_ctx *= alpha;
-#pragma unroll
-        for (int x = 0; x < CPL; ++x) o[x] *= alpha;
-#pragma unroll
-        for (int u = 0; u < NP; ++u) {
-            const float w = (sp0 + u < part.nsplit && r.ml[u].y > 0.f) ? exp2f(r.ml[u].x - m_use) : 0.f;
-            l_ctx = fmaf(r.ml[u].y, w, l_ctx);
-            const float wo = HALF ? w * r.ml[u].y : w;   // a normalised partial weighs in with its l
-#pragma unroll
-            for (int x = 0; x < CPL; ++x) o[x] = fmaf(wo, r.po[u][x], o[x]);
+        for (int u = 0; u < NB; ++u) {
+            a8[u] = pop_node(anc_lo, anc_hi);
+            const int64_t drow = drow0 + max(a8[u], 0) * drow_step;
+            Chan<T, CPL>::load(s.kd, drow, kd8[u]);
+            Chan<T, CPL>::load(s.vd, drow, vd8[u]);
         }
-        m_ctx = m_new;
     };
-    if (!MULTI) {
-        merge(0, ra);
-    } else {
-        // two register sets in turn; a fetch and the merge in front of which it goes out stay in one
-        // basic block, so that the merge waits for its own round only
-        Round rb;
-        for (int sp0 = 0;;) {
-            if (sp0 + NP >= part.nsplit) { merge(sp0, ra); break; }
-            fetch(sp0 + NP, rb);
-            merge(sp0, ra);
-            sp0 += NP;
-            if (sp0 + NP >= part.nsplit) { merge(sp0, rb); break; }
-            fetch(sp0 + NP, ra);
-            merge(sp0, rb);
-            sp0 += NP;
-        }
-    }
-
-    SPECPV_CSTAMP(2);   // context partials in and merged
-    // ---- draft-tree segment: the node itself and its ancestors --------------------------
-    float qv[CPL];
-    Chan<T, CPL>::unpack(qraw, qv);
-    float m = -INFINITY, l = 0.f, od[CPL];
+    float m = -INFINITY, l = 0.f, od[CPL];   // the node itself and its ancestors
 #pragma unroll
     for (int x = 0; x < CPL; ++x) od[x] = 0.f;
-    // online softmax over four nodes (slots without a node have a[u] < 0 and weigh nothing)
-    auto four = [&](const int *a, const Raw *kdv, const Raw *vdv) {
-        float z[4];
+    auto tree_sums = [&]() __attribute__((always_inline)) {
+        // online softmax over four nodes (slots without a node have a[u] < 0 and weigh nothing)
+        auto four = [&](const int *a, const Raw *kdv, const Raw *vdv) __attribute__((always_inline)) {
+            float z[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            float kf[CPL];
-            Chan<T, CPL>::unpack(kdv[u], kf);
-            float dot = 0.f;
+            for (int u = 0; u < 4; ++u) z[u] = a[u] >= 0 ? row16_sum(Chan<T, CPL>::dot(qraw, kdv[u])) * scale_log2 : -INFINITY;
+            const float m_new = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), m);
+            const float m_use = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = __builtin_amdgcn_exp2f(m - m_use);
+            l *= alpha;
 #pragma unroll
-            for (int x = 0; x < CPL; ++x) dot = fmaf(qv[x], kf[x], dot);
-            z[u] = a[u] >= 0 ? row16_sum(dot) * scale_log2 : -INFINITY;
-        }
-        const float m_new = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), m);
-        const float m_use = m_new == -INFINITY ? 0.f : m_new;
-        const float alpha = exp2f(m - m_use);
-        l *= alpha;
+            for (int x = 0; x < CPL; ++x) od[x] *= alpha;
 #pragma unroll
-        for (int x = 0; x < CPL; ++x) od[x] *= alpha;
+            for (int u = 0; u < 4; ++u) {
+                const float pe = __builtin_amdgcn_exp2f(z[u] - m_use);   // 0 for the unused slots
+                l += pe;
+                float vf[CPL];
+                Chan<T, CPL>::unpack(vdv[u], vf);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float pe = exp2f(z[u] - m_use);   // 0 for the unused slots
-            l += pe;
-            float vf[CPL];
-            Chan<T, CPL>::unpack(vdv[u], vf);
-#pragma unroll
-            for (int x = 0; x < CPL; ++x) od[x] = fmaf(pe, vf[x], od[x]);
-        }
-        m = m_new;
-    };
-    four(a8, kd8, vd8);
-#pragma unroll
-    for (int u = 4; u < NB; u += 4)
-        if (a8[u] >= 0) four(a8 + u, kd8 + u, vd8 + u);
-    while (anc_lo | anc_hi) {   // paths longer than 8 nodes (partially verified tokens in front of the tree): 8 per trip
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            a8[u] = pop();
-            const int64_t drow = (((int64_t)b * s.Mk + max(a8[u], 0)) * s.Hkv + g) * D;
-            Chan<T, CPL>::load(s.kd, drow + d0, kd8[u]);
-            Chan<T, CPL>::load(s.vd, drow + d0, vd8[u]);
-        }
+                for (int x = 0; x < CPL; ++x) od[x] = fmaf(pe, vf[x], od[x]);
+            }
+            m = m_new;
+        };
         four(a8, kd8, vd8);
-        if (a8[4] >= 0) four(a8 + 4, kd8 + 4, vd8 + 4);
+#pragma unroll
+        for (int u = 4; u < NB; u += 4)
+            if (a8[u] >= 0) four(a8 + u, kd8 + u, vd8 + u);
+        while (anc_lo | anc_hi) {   // longer paths (partially verified tokens in front of the tree): 8 per trip
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                a8[u] = pop_node(anc_lo, anc_hi);
+                const int64_t drow = drow0 + max(a8[u], 0) * drow_step;
+                Chan<T, CPL>::load(s.kd, drow, kd8[u]);
+                Chan<T, CPL>::load(s.vd, drow, vd8[u]);
+            }
+            four(a8, kd8, vd8);
+            if (a8[4] >= 0) four(a8 + 4, kd8 + 4, vd8 + 4);
+        }
+    };
+    if (TWO && tree_role) {
+        tree_first();
+        tree_rows();
+        tree_sums();
+#pragma unroll
+        for (int x = 0; x < CPL / 4; ++x) *(float4 *)tree_od[quad][x][lane] = make_float4(od[4 * x], od[4 * x + 1], od[4 * x + 2], od[4 * x + 3]);
+        tree_ml[quad][lane] = make_float2(m, l);
+        if (wave == 0) SPECPV_CSTAMP(3, 0);   // draft K / V rows in, tree segment done
+        __syncthreads();
+        return;
     }
 
-    SPECPV_CSTAMP(3);   // draft K / V rows in, tree segment done
+    // ---- context partials -----------------------------------------------------------------
+    const int R = s.M * s.G;   // rows of the KV head, head by head
+    const int64_t prow0 = ((int64_t)bg * part.nsplit) * R + hc * s.M + j;
+    const int ns = part.nsplit;
+    // (m, l) of partials u, u + 16, ... in lane u of the row's sixteen: each lane works out the weights of its own
+    constexpr int KM = MULTI ? 4 : 1;
+    const int u16 = lane & 15;
+    float2 ml[KM];
+#pragma unroll
+    for (int k = 0; k < KM; ++k) {
+        const int sp = u16 + 16 * k;
+        ml[k] = sp < ns ? *(const float2 *)(part.ml + (prow0 + (int64_t)sp * R) * 2) : make_float2(-INFINITY, 0.f);
+    }
+    typedef Part<CPL, HALF> P;
+    auto fetch = [&](int sp0, P (&r)[NP]) {
+#pragma unroll
+        for (int u = 0; u < NP; ++u) r[u].load(part.o, prow0 + (int64_t)min(sp0 + u, ns - 1) * R, D, u16);
+    };
+    P ra[NP];
+    fetch(0, ra);
+    if (!TWO) {
+        tree_first();
+        tree_rows();
+    }
+    float m_ctx = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < KM; ++k) m_ctx = fmaxf(m_ctx, ml[k].y > 0.f ? ml[k].x : -INFINITY);
+    m_ctx = row16_max(m_ctx);
+    float w[KM], l_ctx = 0.f, o[CPL];
+#pragma unroll
+    for (int k = 0; k < KM; ++k) {
+        const float e = ml[k].y > 0.f ? __builtin_amdgcn_exp2f(ml[k].x - m_ctx) : 0.f;
+        l_ctx = fmaf(ml[k].y, e, l_ctx);
+        w[k] = HALF ? e * ml[k].y : e;   // a normalised partial weighs in with its l
+    }
+    l_ctx = row16_sum(l_ctx);
+#pragma unroll
+    for (int x = 0; x < CPL; ++x) o[x] = 0.f;
+    auto add = [&](const P &r, float wt) {
+        float v[CPL];
+        r.value(v);
+#pragma unroll
+        for (int x = 0; x < CPL; ++x) o[x] = fmaf(wt, v[x], o[x]);
+    };
+    // partials OFF .. of the sixteen whose weights wk holds (weights past the split count are 0)
+    auto add_n = [&](const P *r, float wk, auto off, auto count) __attribute__((always_inline)) {
+        constexpr int O = decltype(off)::value, N = decltype(count)::value;
+        add(r[0], row_bcast<O>(wk)); add(r[1], row_bcast<O + 1>(wk));
+        if constexpr (N >= 4) { add(r[2], row_bcast<O + 2>(wk)); add(r[3], row_bcast<O + 3>(wk)); }
+        if constexpr (N >= 8) { add(r[4], row_bcast<O + 4>(wk)); add(r[5], row_bcast<O + 5>(wk)); add(r[6], row_bcast<O + 6>(wk)); add(r[7], row_bcast<O + 7>(wk)); }
+    };
+    typedef std::integral_constant<int, 0> I0;
+    typedef std::integral_constant<int, 8> I8;
+    if constexpr (!MULTI) {
+        add_n(ra, w[0], I0{}, std::integral_constant<int, NP < 8 ? NP : 8>{});
+        if constexpr (NP == 16) add_n(ra + 8, w[0], I8{}, I8{});
+    } else {
+        static_assert(!MULTI || NP == 8, "eight partials per round");
+        P rb[NP];
+#pragma unroll
+        for (int k = 0; k < KM; ++k) {   // two register sets in turn
+            if (16 * k >= ns) break;
+            if (16 * k + 8 < ns) fetch(16 * k + 8, rb);
+            add_n(ra, w[k], I0{}, I8{});
+            if (16 * k + 8 >= ns) break;
+            if (16 * k + 16 < ns) fetch(16 * k + 16, ra);
+            add_n(rb, w[k], I8{}, I8{});
+        }
+    }
+    if (wave == nq) SPECPV_CSTAMP(2, nq);   // context partials in and merged
+    if (TWO) {
+        __syncthreads();
+        const float2 tml = tree_ml[quad][lane];
+        m = tml.x;
+        l = tml.y;
+#pragma unroll
+        for (int x = 0; x < CPL / 4; ++x) {
+            const float4 v = *(const float4 *)tree_od[quad][x][lane];
+            od[4 * x] = v.x; od[4 * x + 1] = v.y; od[4 * x + 2] = v.z; od[4 * x + 3] = v.w;
+        }
+    } else {
+        tree_sums();
+    }
     // ---- merge the two and store ---------------------------------------------------------
-    const float m_all = fmaxf(m, m_ctx);
-    const float wd = exp2f(m - m_all);
-    const float wc = m_ctx == -INFINITY ? 0.f : exp2f(m_ctx - m_all);
+    const float m_all = fmaxf(m, m_ctx);   // finite: the node itself is on its path
+    const float wd = __builtin_amdgcn_exp2f(m - m_all);
+    const float wc = m_ctx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ctx - m_all);
     const float den = l * wd + l_ctx * wc;
     const float inv = 1.f / den;
     if (!live) return;
@@ -306,28 +399,48 @@ __global__ __launch_bounds__(256) void combine_kernel(const int32_t *a_parent, c
 #pragma unroll
     for (int x = 0; x < CPL; ++x) res[x] = (od[x] * wd + o[x] * wc) * inv;
     Chan<T, CPL>::store_stream(out, qrow + d0, res);
-    if (lse && (lane & 15) == 0) lse[((int64_t)b * s.M + j) * s.Hq + h] = (m_all + log2f(den)) * kLn2;
-    SPECPV_CSTAMP(4);   // stored (issued)
+    if (lse && u16 == 0) lse[((int64_t)b * s.M + j) * s.Hq + h] = (m_all + log2f(den)) * kLn2;
+    if (wave == nq) SPECPV_CSTAMP(4, nq);   // stored (issued)
+}
+
+// Two wavefronts per four rows shorten the chain; where the rows fill the chip several times over, one wavefront that does
+// both has fewer instructions in all and less to start.  Partial step, 60 nodes at G = 4, 8 KV heads: one sequence 17.9
+// against 18.4 us, two 23.5 against 23.3, eight 59.1 against 57.6, sixteen 99.4 against 97.5.
+static bool combine_two_waves(const Shape &s)
+{
+    return (int64_t)s.batch * s.Hkv * s.M * ((s.G + 3) / 4) <= 2 * (int64_t)device_cu_count();
 }
 
 template <typename T, int D>
 static void launch_combine_t(const Shape &s, Partials p, void *out, float *lse, hipStream_t st)
 {
-    dim3 grid(8, s.M, (s.batch * s.Hkv + 7) / 8), block(64 * ((s.G + 3) / 4));
+    const bool two = combine_two_waves(s);
+    dim3 grid(8, s.M, (s.batch * s.Hkv + 7) / 8), block((two ? 128 : 64) * ((s.G + 3) / 4));
     const float scale_log2 = kLog2e / sqrtf((float)s.D);
+    // fp16 partials: bf16 at 128 channels; the other element types and head dims have fp32 ones
+    constexpr bool kHalf = std::is_same<T, bf16_t>::value && D == 128;
 #define SPECPV_LAUNCH_K(NP, MULTI, NB, HALF)                                                                              \
-    hipLaunchKernelGGL((combine_kernel<T, D, NP, MULTI, NB, HALF>), grid, block, 0, st, s.parent, s.q, (const float *)p.o, \
-                       (const float *)p.ml, s.M, s.Hq, s.G, p.nsplit, s, p, out, lse, scale_log2)
+    do {                                                                                                                \
+        if (two) hipLaunchKernelGGL((combine_kernel<T, D, NP, MULTI, NB, HALF, true>), grid, block, 0, st, s.parent, s.q, (const float *)p.o, \
+                                    (const float *)p.ml, s.M, s.Hq, s.G, p.nsplit, s, p, out, lse, scale_log2);           \
+        else hipLaunchKernelGGL((combine_kernel<T, D, NP, MULTI, NB, HALF, false>), grid, block, 0, st, s.parent, s.q, (const float *)p.o, \
+                                (const float *)p.ml, s.M, s.Hq, s.G, p.nsplit, s, p, out, lse, scale_log2);               \
+    } while (0)
+#define SPECPV_LAUNCH_H(NP, MULTI, NB)                                                                                   \
+    do {                                                                                                                \
+        if (kHalf && p.o_half) SPECPV_LAUNCH_K(NP, MULTI, NB, kHalf); else SPECPV_LAUNCH_K(NP, MULTI, NB, false);        \
+    } while (0)
 #define SPECPV_LAUNCH_NP(NP, MULTI)                                                                                      \
     do {                                                                                                                \
-        if (s.koff > s.kctx) { if (p.o_half) SPECPV_LAUNCH_K(NP, MULTI, 24, true); else SPECPV_LAUNCH_K(NP, MULTI, 24, false); } \
-        else { if (p.o_half) SPECPV_LAUNCH_K(NP, MULTI, 8, true); else SPECPV_LAUNCH_K(NP, MULTI, 8, false); }           \
+        if (s.koff > s.kctx) SPECPV_LAUNCH_H(NP, MULTI, 24); else SPECPV_LAUNCH_H(NP, MULTI, 8);                         \
     } while (0)
     if (p.nsplit <= 2) SPECPV_LAUNCH_NP(2, false);
     else if (p.nsplit <= 4) SPECPV_LAUNCH_NP(4, false);
     else if (p.nsplit <= 8) SPECPV_LAUNCH_NP(8, false);
+    else if (p.nsplit <= 16) SPECPV_LAUNCH_NP(16, false);
     else SPECPV_LAUNCH_NP(8, true);
 #undef SPECPV_LAUNCH_NP
+#undef SPECPV_LAUNCH_H
 #undef SPECPV_LAUNCH_K
 }
 

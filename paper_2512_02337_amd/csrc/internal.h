@@ -31,7 +31,7 @@ struct Shape {
     int kctx;
 };
 
-// Split-KV partial results of the context part, one per (b, g, split, row), row j * G + hh of KV head g being node j of
+// Split-KV partial results of the context part, one per (b, g, split, row), row hh * M + j of KV head g being node j of
 // its query head hh (the single-kernel route keeps its own order, [batch, Hq, nsplit, M]: it reads them back itself):
 //   part_ml [batch, Hkv, nsplit, M * G, 2] fp32   (m, l): m = max_t z_t, l = sum_t 2^(z_t - m),
 // with z = q.k * log2(e)/sqrt(D).  A split without any valid token stores m = -inf, l = 0.
@@ -162,6 +162,7 @@ enum AttnKind { kAttnGeneric = 0, kAttnSplit = 1, kAttnGroup = 3 };
 struct AttnPlan {
     int nsplit;
     int kind;
+    int tg;   // kAttnSplit: token groups per workgroup
 };
 // The whole call in the eight-wavefront kernel (kAttnSplit only): the draft-tree segment as one more
 // partial (slot nctx of nctx + 1), arrival words, the last workgroup of a tile merges and stores.
@@ -177,8 +178,12 @@ constexpr size_t kArriveBytes = 64 << 10;   // head of every workspace: 8192 arr
 // p.nsplit: slots per (sequence, head) in the partial arrays = nctx, or nctx + 1 when fused
 hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const int32_t *sel_count,
                                 int n_sel, Partials p, int nctx, int kind, const FusedArgs &f, hipStream_t st);
+// the kAttnSplit kernel (two-kernel route): tg = 2, 4 or 8 token groups and 256 / tg query rows per workgroup
+hipError_t launch_attn_ctx_tile(const Shape &s, const int32_t *sel_idx, const int32_t *sel_count, int n_sel, Partials p,
+                                int tg, unsigned long long *timeline, hipStream_t st);
 // workgroups per (sequence, KV head, split) of the kAttnGroup kernel
 int attn_group_parts(const Shape &s);
+int attn_group_waves(const Shape &s);   // wavefronts of each
 hipError_t launch_combine(const Shape &s, int dtype, Partials p, void *out, float *lse, hipStream_t st);
 // to_cache != 0: pending + accepted rows go to the cache tail (lengths, summaries updated);
 // otherwise the accepted rows join the pending rows of the buffer.  missed_words: the zeroed words at the
