@@ -156,7 +156,7 @@ static int64_t first_splits(const Shape &s, int64_t chunks, int64_t cus)
 // lengths only the device knows (n_blocks is the most that any of them has).
 static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool full)
 {
-    AttnPlan plan{1, !attn_ctx_mfma_supported(s, dtype) ? kAttnGeneric : (s.D == 64 ? kAttnGroup : kAttnSplit), 4};
+    AttnPlan plan{1, !attn_ctx_mfma_supported(s, dtype) ? kAttnGeneric : (s.D == 64 ? kAttnGroup : kAttnSplit), 4, 0};
     // splits that give 4096 (row, split) pairs of 64 tokens or more each
     const int64_t rows = (int64_t)s.batch * s.Hq * s.M;
     auto few_splits = [&](int64_t tokens) {
@@ -216,12 +216,6 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
                 const int64_t cost = (base * c + slots - 1) / slots * ((chunks + c - 1) / c * 8 + 10) + c;
                 if (best < 0 || cost < best) { best = cost; ns = c; }
             }
-            if (s.batch > 1) {
-                int64_t c = (4 * slots + base - 1) / base;
-                if (c > most) c = most;
-                while (c > ns && (chunks + c - 1) / c < 64) --c;
-                if (c > ns) ns = c;
-            }
         } else {
             const AttnCost cost(s, chunks);
             const int waves = attn_group_waves(s);
@@ -238,34 +232,43 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
                     if (c * tg <= 2 * chunks) take(cost.tile(tg, c, cus), kAttnSplit, tg, c);
                 if (chunks >= 2 * c) take(cost.group(parts, waves, c, cus), kAttnGroup, 4, c);
             }
-            if (full && s.batch > 1 && plan.kind == kAttnGroup) {
-                // The sequences of a batch may differ in length, and the lengths live on the device:
-                // many small workgroups (about four per CU, 64 chunks or more each: shorter ones are
-                // mostly prologue and epilogue) let the hardware scheduler even that out (measured on
-                // 32K + 64K + 96K + 128K at G = 5: 752 us at eight per CU, 687 at four, 704 at two: every split
-                // is another partial for the combine, 85 us at 64 splits against 37 at 32).
-                int64_t c = (4 * cus + base - 1) / base;
-                if (c > 64) c = 64;
-                while (c > ns && (chunks + c - 1) / c < 64) --c;
-                if (c > ns) ns = c;
-            }
             ns = static_room([&] { return first_splits(s, chunks, cus); }, ns);
         }
         plan.nsplit = (int)ns;
+        // The sequences of a batch may differ in length, and the lengths live on the device: for a full pass the group
+        // kernel's workgroups take equal shares of all chunks.  (Before, four times as many splits as fill the chip evened
+        // that out, at the price of as many partials: full pass over 32K + 64K + 96K + 128K tokens at G = 5, 64 nodes:
+        // attention 510 us and combine 51 us with the splits, 525 and 15 us with the shares.)  Up to 1024 tokens there is
+        // nothing to even out.
+        if (full && s.batch > 1 && s.batch <= 64 && plan.kind == kAttnGroup && chunks > 32 && (int64_t)s.batch * s.Hkv * chunks < ((int64_t)1 << 30)) {
+            const int64_t pairs = (int64_t)s.batch * s.Hkv, R = (int64_t)s.M * s.G;
+            int64_t wgs = cus * (s.D == 64 ? 2 : 1) / parts;
+            if (wgs > pairs * chunks / 8) wgs = pairs * chunks / 8;   // eight chunks or more each
+            if (wgs < 1) wgs = 1;
+            // the workspace of as many splits as hold that many slots
+            const int64_t bytes = (wgs + pairs) * R * (s.D == 128 ? 2 * s.D + 8 : 4 * s.D + 8) + 512, slot = pairs * R * (4 * s.D + 8);
+            const int64_t splits = (bytes + slot - 1) / slot > 1 ? (bytes + slot - 1) / slot - 1 : 1;
+            const bool fits = (int64_t)kArriveBytes + bytes <= (int64_t)SPECPV_STATIC_SCRATCH_BYTES;
+            if (splits <= 64 && (fits || static_room([&] { return s.D == 64 ? few_splits(tokens) : first_splits(s, chunks, cus); }, 64) == 64)) {
+                plan.stream = (int)wgs;
+                plan.nsplit = (int)splits;
+            }
+        }
     }
     return plan;
 }
 
 // Workspace layout: [arrival words, kArriveBytes, zero between calls][partial O][(m, l) pairs][scores],
 // the partial arrays sized for nsplit + 1 slots of fp32 (the context splits and the draft-tree segment).  fp16 partials
-// take less: `half_total` bytes with the pairs right behind them and no scores.
+// (bf16 at 128 channels) and the slots of Partials::stream take less: `tight_total` bytes, with the pairs right behind the
+// rows in use and no scores.
 struct Workspace {
     unsigned long long *arrive;
-    float *part_o, *part_ml, *scores, *half_ml;
-    size_t total, half_total;
+    float *part_o, *part_ml, *scores, *tight_ml;
+    size_t total, tight_total;
 };
 
-static Workspace layout_workspace(const Shape &s, int nsplit, void *base)
+static Workspace layout_workspace(const Shape &s, int nsplit, int stream, void *base)
 {
     Workspace w;
     const size_t slots = (size_t)nsplit + 1;
@@ -278,9 +281,11 @@ static Workspace layout_workspace(const Shape &s, int nsplit, void *base)
     w.part_ml = (float *)(p + kArriveBytes + po);
     w.scores = (float *)(p + kArriveBytes + po + pm);
     w.total = kArriveBytes + po + pm + sc;
-    const size_t ho = align_up((size_t)s.batch * s.Hq * nsplit * s.M * s.D * sizeof(uint16_t));
-    w.half_ml = (float *)(p + kArriveBytes + ho);
-    w.half_total = kArriveBytes + ho + align_up((size_t)s.batch * s.Hq * nsplit * s.M * 2 * sizeof(float));
+    const size_t R = (size_t)s.M * s.G, held = (size_t)s.batch * s.Hkv * R * nsplit;
+    const size_t rows = stream ? ((size_t)stream + (size_t)s.batch * s.Hkv) * R : held;   // partial rows in use
+    const size_t ho = align_up(rows * s.D * (s.D == 128 ? sizeof(uint16_t) : sizeof(float)));
+    w.tight_ml = (float *)(p + kArriveBytes + ho);
+    w.tight_total = kArriveBytes + ho + align_up(rows * 2 * sizeof(float));
     return w;
 }
 
@@ -299,9 +304,10 @@ static int run_attention(const Shape &s_in, int dtype, const int32_t *sel_idx, c
     // tokens (dense: every query row attends all of them); the vector-ALU kernel leaves them to the combine
     s.kctx = plan.kind != kAttnGeneric ? s.koff : 0;
     const int nsplit = plan.nsplit;
-    const Workspace w = layout_workspace(s, nsplit, workspace);
+    const Workspace w = layout_workspace(s, nsplit, plan.stream, workspace);
     const bool half = plan.kind != kAttnGeneric && s.D == 128;   // fp16 partials
-    if (!workspace || workspace_bytes < (own_scratch && half ? w.half_total : w.total)) return SPECPV_EWORKSPACE;
+    const bool tight = half || plan.stream;
+    if (!workspace || workspace_bytes < (own_scratch && tight ? w.tight_total : w.total)) return SPECPV_EWORKSPACE;
     const int route = __atomic_load_n(&g_route, __ATOMIC_RELAXED);
     // The single-kernel route is correct but measured slower than two launches (the last workgroup of a
     // tile reads all of the tile's partials through one CU): it runs only on request.
@@ -309,12 +315,12 @@ static int run_attention(const Shape &s_in, int dtype, const int32_t *sel_idx, c
                        (size_t)s.batch * s.Hq * 2 * sizeof(unsigned long long) <= kArriveBytes;
     hipError_t e;
     if (fused) {
-        Partials p{w.part_o, w.part_ml, nsplit + 1, 0, nullptr};
+        Partials p{w.part_o, w.part_ml, nsplit + 1, 0, 0, nullptr};
         const FusedArgs f{out, lse, w.arrive, route == 3 ? 1 : 0, g_timeline};
         e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, f, st);
         return e == hipSuccess ? SPECPV_OK : fail_hip(e);
     }
-    Partials p{w.part_o, half ? w.half_ml : w.part_ml, nsplit, half ? 1 : 0, g_timeline};
+    Partials p{w.part_o, tight ? w.tight_ml : w.part_ml, nsplit, half ? 1 : 0, plan.stream, g_timeline};
     const FusedArgs none{nullptr, nullptr, nullptr, 0, g_timeline};
     if (plan.kind == kAttnSplit) e = launch_attn_ctx_tile(s, sel_idx, sel_count, n_sel, p, plan.tg, g_timeline, st);
     else if (plan.kind != kAttnGeneric) e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, none, st);
@@ -392,7 +398,7 @@ size_t specpv_workspace_bytes(const specpv_kv *kv, const specpv_tree *tree, cons
         const int n2 = plan_attention(s, kv->dtype, n_sel, false).nsplit;
         if (n2 > nsplit) nsplit = n2;
     }
-    return layout_workspace(s, nsplit, nullptr).total;
+    return layout_workspace(s, nsplit, 0, nullptr).total;
 }
 
 int specpv_block_summarize(const specpv_kv *kv, int32_t blk_begin, int32_t blk_end,
@@ -455,8 +461,8 @@ int specpv_partial_verify_attn_static(const specpv_kv *kv, const specpv_tree *tr
     const Shape s = make_shape(kv, tree);
     // the same plan as specpv_partial_verify_attn; its partial results must fit the static array
     const AttnPlan plan = plan_attention(s, kv->dtype, sel_idx ? n_sel : s.max_blocks, !sel_idx);
-    const Workspace w = layout_workspace(s, plan.nsplit, nullptr);
-    const size_t need = plan.kind != kAttnGeneric && s.D == 128 ? w.half_total : w.total;
+    const Workspace w = layout_workspace(s, plan.nsplit, plan.stream, nullptr);
+    const size_t need = plan.stream || (plan.kind != kAttnGeneric && s.D == 128) ? w.tight_total : w.total;
     if (need > (size_t)SPECPV_STATIC_SCRATCH_BYTES) {
         snprintf(g_hip_err, sizeof(g_hip_err), "static scratch: the call needs %zu bytes, the array holds %zu",
                  need, (size_t)SPECPV_STATIC_SCRATCH_BYTES);
@@ -482,7 +488,7 @@ int specpv_full_verify_refresh(const specpv_kv *kv, const specpv_tree *tree, voi
     if (((uintptr_t)kmax | (uintptr_t)kmin | (uintptr_t)out) & 15) return SPECPV_EINVAL;
     const Shape s = make_shape(kv, tree);
     const int nsplit = plan_attention(s, kv->dtype, s.max_blocks, true).nsplit;
-    const Workspace w = layout_workspace(s, nsplit, workspace);
+    const Workspace w = layout_workspace(s, nsplit, 0, workspace);
     if (!workspace || workspace_bytes < w.total) return SPECPV_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     if (stale_blk_begin >= 0) {

@@ -845,7 +845,9 @@ static_assert(Tile<64>::kStage % 256 == 0 && kStageBytes % 256 == 0, "K operand 
 // partials are fp32 sums: the precision, and the range of V, of the vector-ALU kernel that this replaces.  Full pass
 // over 15K + 30K tokens, 37 nodes at G = 4, 8 KV heads, token-major, with scoring and selection: 5845 us on the vector
 // ALU, 65 us here (53 us with the weights as one bf16 term and fp16 partials).
-template <int D, bool ALIGNED, int W>
+// SK: shares of the chunks of all (sequence, KV head) pairs instead of splits (Partials::stream): a workgroup goes through
+// the one to three pairs that its share touches, one after the other.
+template <int D, bool ALIGNED, int W, bool SK>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : (W > 8 ? 3 : 2), D == 64 ? 4 : (W > 8 ? 3 : 2))))
 void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
 {
@@ -861,12 +863,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     const int xcd = blockIdx.x & 7, wg_part = blockIdx.x >> 3;
     const int u = blockIdx.y * 8 + xcd;
     if (u >= a.n_units) return;
-    const int bg = (int)a.div_nsplit.div((uint32_t)u);
-    const int sp = u - bg * part.nsplit;
-    const int b = (int)a.div_hkv.div((uint32_t)bg);
-    const int g = bg - b * s.Hkv;
-
-    const int lane = threadIdx.x & 63;
+    int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // this wavefront's row block: rows r0w .. r0w + 31 of the KV head's M * G query rows.  A
     // workgroup may have a wavefront too many (row block counts that do not divide): it brings
@@ -875,7 +872,34 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     const bool live = rbx < a.n_row_blocks;
     const int R = s.M * s.G;                  // query rows of the KV head: row r is head r / M of the group, node r % M
     const int r0w = (live ? rbx : a.n_row_blocks - 1) * 32;
+    int share_at = 0, share_end = 1;   // SK: this workgroup's chunks in the row of all pairs' chunks
+    int seq_chunks = 0, seq_upto = 0;
+    if (SK) {
+        const StreamShare sh(s, lane, part.stream);
+        if (u >= sh.wgs) return;
+        share_at = sh.begin(u);
+        share_end = sh.begin(u + 1);
+        seq_chunks = sh.chunks;
+        seq_upto = sh.upto;
+    }
+    do {
+    if (SK) asm volatile("" : "+v"(lane));   // what follows from it is worked out per pair, not held in registers
     const int n = lane & 31, kg = lane >> 5;
+    int bg, b, g, c0, nch, sp = 0;
+    if (SK) {
+        b = __popcll(__ballot(seq_upto * s.Hkv <= share_at));
+        const int C_b = __builtin_amdgcn_readlane(seq_chunks, b), before = (__builtin_amdgcn_readlane(seq_upto, b) - C_b) * s.Hkv;
+        g = (int)((uint32_t)(share_at - before) / (uint32_t)C_b);
+        bg = b * s.Hkv + g;
+        c0 = share_at - before - g * C_b;
+        nch = min(C_b - c0, share_end - share_at);
+        share_at += nch;
+    } else {
+        bg = (int)a.div_nsplit.div((uint32_t)u);
+        sp = u - bg * part.nsplit;
+        b = (int)a.div_hkv.div((uint32_t)bg);
+        g = bg - b * s.Hkv;
+    }
 
     const int32_t *sel = a.sel_idx ? a.sel_idx + (int64_t)bg * a.n_sel : nullptr;
     const int NS = part.nsplit;               // div_W divides by the number of splits here
@@ -906,8 +930,11 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     const char *kdb = (const char *)s.kd + (((int64_t)b * s.Mk) * s.Hkv + g) * (2 * D);
     const char *vdb = (const char *)s.vd + (((int64_t)b * s.Mk) * s.Hkv + g) * (2 * D);
     const uint32_t stp = (uint32_t)s.Hkv * (2u * D);
-    const int c0 = first_chunk(C, sp), c1 = first_chunk(C, sp + 1);
-    const int nch = c1 - c0;                  // the same for all wavefronts: the barriers match up
+    // the number of chunks is the same for all wavefronts: the barriers match up
+    if (!SK) {
+        c0 = first_chunk(C, sp);
+        nch = first_chunk(C, sp + 1) - c0;
+    }
 
     const char *kb = (const char *)s.k + ((int64_t)b * s.sb + (int64_t)g * s.sh) * 2;
     const char *vb = (const char *)s.v + ((int64_t)b * s.sb + (int64_t)g * s.sh) * 2;
@@ -1257,17 +1284,10 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     // every wavefront, live or not, passes that one barrier)
     constexpr int kSlots = W > 8 ? W / 2 : W;
     const int slot = wave < kSlots ? wave : wave - kSlots;
-    if (W > 8) {
-        if (wave >= kSlots) __builtin_amdgcn_s_barrier();
-        if (!live) {
-            if (wave < kSlots) __builtin_amdgcn_s_barrier();
-            return;
-        }
-    } else if (!live) {
-        return;
-    }
+    if (W > 8 && wave >= kSlots) __builtin_amdgcn_s_barrier();
+    if (live) {
     l_run = sum_xor32(l_run);
-    const int64_t prow0 = ((int64_t)bg * part.nsplit + sp) * R + r0w;
+    const int64_t prow0 = (SK ? (int64_t)(u + bg) : (int64_t)bg * part.nsplit + sp) * R + r0w;
     const int n_rows = min(32, R - r0w);
     {
         // accumulator element 4q + x of tile j is channel 32j + 8q + 4kg + x of this lane's row
@@ -1299,10 +1319,11 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
         }
     }
     if (kg == 0 && n < n_rows) *(float2 *)(part.ml + (prow0 + n) * 2) = make_float2(m_ref, l_run);
-    SPECPV_CLOCKS_END(part.timeline, (size_t)blockIdx.y * gridDim.x + blockIdx.x, nch);
-    if (W > 8) {
-        if (wave < kSlots) __builtin_amdgcn_s_barrier();   // the slot is free for wavefront wave + kSlots
+    if (!SK || share_at >= share_end) SPECPV_CLOCKS_END(part.timeline, (size_t)blockIdx.y * gridDim.x + blockIdx.x, nch);
     }
+    if (W > 8 && wave < kSlots) __builtin_amdgcn_s_barrier();   // the slot is free for wavefront wave + kSlots
+    if (SK) __syncthreads();   // the next pair's chunks go where the rows were staged
+    } while (SK && share_at < share_end);
 }
 
 bool attn_ctx_mfma_supported(const Shape &s, int dtype)
@@ -1341,6 +1362,7 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
     if (kind == kAttnSplit && s.D != 128) return hipErrorInvalidValue;
     const bool fused = f.out != nullptr;
     if (fused != (kind == kAttnSplit) || (fused && nctx > 64) || p.nsplit != nctx + (fused ? 1 : 0)) return hipErrorInvalidValue;
+    if (p.stream && (kind != kAttnGroup || s.batch > 64 || sel_idx)) return hipErrorInvalidValue;
     const GroupLayout gl = group_layout(s);
     MfmaArgs a;
     a.sel_idx = sel_idx;
@@ -1349,7 +1371,7 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
     a.scale_log2 = kLog2e / sqrtf((float)s.D);
     a.row_tiles = (s.M + 63) / 64;
     a.n_row_blocks = gl.n_row_blocks;
-    a.n_units = s.batch * s.Hkv * nctx;
+    a.n_units = p.stream ? p.stream : s.batch * s.Hkv * nctx;
     a.n_bg = s.batch * s.Hkv;
     a.div_nsplit = make_fastdiv((uint32_t)nctx);
     a.div_hkv = make_fastdiv((uint32_t)s.Hkv);
@@ -1374,12 +1396,15 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
             return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(LDS)); \
         });                                                                                            \
         if (e0 != hipSuccess) return e0
+#define SPECPV_LAUNCH_GROUP_K(DD, AL, WW, SS)                                                          \
+    do {                                                                                               \
+        SPECPV_SET_LDS((attn_ctx_mfma_group_kernel<DD, AL, WW, SS>), lds_group);                        \
+        hipLaunchKernelGGL(kern, grid, dim3(64 * WW), lds_group, st, s, p, a);                          \
+    } while (0)
 #define SPECPV_LAUNCH_GROUP(DD, WW)                                                                    \
     do {                                                                                               \
-        if (aligned) { SPECPV_SET_LDS((attn_ctx_mfma_group_kernel<DD, true, WW>), lds_group);           \
-                       hipLaunchKernelGGL(kern, grid, dim3(64 * WW), lds_group, st, s, p, a); }         \
-        else { SPECPV_SET_LDS((attn_ctx_mfma_group_kernel<DD, false, WW>), lds_group);                  \
-               hipLaunchKernelGGL(kern, grid, dim3(64 * WW), lds_group, st, s, p, a); }                 \
+        if (aligned) { if (p.stream) SPECPV_LAUNCH_GROUP_K(DD, true, WW, true); else SPECPV_LAUNCH_GROUP_K(DD, true, WW, false); } \
+        else { if (p.stream) SPECPV_LAUNCH_GROUP_K(DD, false, WW, true); else SPECPV_LAUNCH_GROUP_K(DD, false, WW, false); }       \
     } while (0)
 #define SPECPV_LAUNCH_SPLIT(AL)                                                                        \
     do {                                                                                               \
@@ -1409,6 +1434,7 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
     }
 #undef SPECPV_LAUNCH_SPLIT
 #undef SPECPV_LAUNCH_GROUP
+#undef SPECPV_LAUNCH_GROUP_K
 #undef SPECPV_SET_LDS
     return hipGetLastError();
 }

@@ -194,6 +194,8 @@ __device__ __forceinline__ int pop_node(unsigned long long &lo, unsigned long lo
 // when partially verified tokens stand in front of the tree as keys (every candidate's path then starts with
 // that whole chain; more registers, so only then).
 // HALF: the partials' O rows are fp16 and normalised (see Partials); else fp32 sums.
+// part.stream > 0 (MULTI only): the number and the place of a pair's partials follow from the sequence lengths, which the
+// partials' wavefront reads first.
 template <typename T, int D, int NP, bool MULTI, int NB, bool HALF, bool TWO>
 __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, const void *a_q, const float *a_po,
                                                     const float *a_pml, int a_M, int a_Hq, int a_G, int a_nsplit,
@@ -307,42 +309,28 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
 
     // ---- context partials -----------------------------------------------------------------
     const int R = s.M * s.G;   // rows of the KV head, head by head
-    const int64_t prow0 = ((int64_t)bg * part.nsplit) * R + hc * s.M + j;
-    const int ns = part.nsplit;
+    int ns = part.nsplit;
+    int64_t slot0 = (int64_t)bg * ns;
+    if (MULTI && part.stream) {
+        const StreamShare sh(s, lane, part.stream);
+        const int C_b = __builtin_amdgcn_readlane(sh.chunks, b);
+        const int at = (__builtin_amdgcn_readlane(sh.upto, b) - C_b) * s.Hkv + g * C_b;
+        const int w0 = C_b > 0 ? sh.owner(at) : 0;
+        ns = C_b > 0 ? sh.owner(at + C_b - 1) - w0 + 1 : 0;
+        slot0 = w0 + bg;
+    }
+    const int64_t prow0 = slot0 * R + hc * s.M + j;
     // (m, l) of partials u, u + 16, ... in lane u of the row's sixteen: each lane works out the weights of its own
-    constexpr int KM = MULTI ? 4 : 1;
+    constexpr int KM = MULTI ? 4 : 1;   // (64 partials at a time; a pair that holds most of a batch may have more)
     const int u16 = lane & 15;
-    float2 ml[KM];
-#pragma unroll
-    for (int k = 0; k < KM; ++k) {
-        const int sp = u16 + 16 * k;
-        ml[k] = sp < ns ? *(const float2 *)(part.ml + (prow0 + (int64_t)sp * R) * 2) : make_float2(-INFINITY, 0.f);
-    }
     typedef Part<CPL, HALF> P;
-    auto fetch = [&](int sp0, P (&r)[NP]) {
-#pragma unroll
-        for (int u = 0; u < NP; ++u) r[u].load(part.o, prow0 + (int64_t)min(sp0 + u, ns - 1) * R, D, u16);
-    };
-    P ra[NP];
-    fetch(0, ra);
-    if (!TWO) {
-        tree_first();
-        tree_rows();
-    }
-    float m_ctx = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < KM; ++k) m_ctx = fmaxf(m_ctx, ml[k].y > 0.f ? ml[k].x : -INFINITY);
-    m_ctx = row16_max(m_ctx);
-    float w[KM], l_ctx = 0.f, o[CPL];
-#pragma unroll
-    for (int k = 0; k < KM; ++k) {
-        const float e = ml[k].y > 0.f ? __builtin_amdgcn_exp2f(ml[k].x - m_ctx) : 0.f;
-        l_ctx = fmaf(ml[k].y, e, l_ctx);
-        w[k] = HALF ? e * ml[k].y : e;   // a normalised partial weighs in with its l
-    }
-    l_ctx = row16_sum(l_ctx);
+    float m_ctx = -INFINITY, l_ctx = 0.f, o[CPL];
 #pragma unroll
     for (int x = 0; x < CPL; ++x) o[x] = 0.f;
+    auto fetch = [&](int sp0, P (&r)[NP]) {
+#pragma unroll
+        for (int u = 0; u < NP; ++u) r[u].load(part.o, prow0 + (int64_t)max(min(sp0 + u, ns - 1), 0) * R, D, u16);
+    };
     auto add = [&](const P &r, float wt) {
         float v[CPL];
         r.value(v);
@@ -358,20 +346,56 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
     };
     typedef std::integral_constant<int, 0> I0;
     typedef std::integral_constant<int, 8> I8;
-    if constexpr (!MULTI) {
-        add_n(ra, w[0], I0{}, std::integral_constant<int, NP < 8 ? NP : 8>{});
-        if constexpr (NP == 16) add_n(ra + 8, w[0], I8{}, I8{});
-    } else {
-        static_assert(!MULTI || NP == 8, "eight partials per round");
-        P rb[NP];
+    for (int s0 = 0;; s0 += 16 * KM) {   // 16 KM partials at a time (one trip, but for a pair with more than 64)
+        float2 ml[KM];
 #pragma unroll
-        for (int k = 0; k < KM; ++k) {   // two register sets in turn
-            if (16 * k >= ns) break;
-            if (16 * k + 8 < ns) fetch(16 * k + 8, rb);
-            add_n(ra, w[k], I0{}, I8{});
-            if (16 * k + 8 >= ns) break;
-            if (16 * k + 16 < ns) fetch(16 * k + 16, ra);
-            add_n(rb, w[k], I8{}, I8{});
+        for (int k = 0; k < KM; ++k) {
+            const int sp = s0 + u16 + 16 * k;
+            ml[k] = sp < ns ? *(const float2 *)(part.ml + (prow0 + (int64_t)sp * R) * 2) : make_float2(-INFINITY, 0.f);
+        }
+        P ra[NP];
+        fetch(s0, ra);
+        if (!TWO && s0 == 0) {
+            tree_first();
+            tree_rows();
+        }
+        float m_new = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < KM; ++k) m_new = fmaxf(m_new, ml[k].y > 0.f ? ml[k].x : -INFINITY);
+        m_new = fmaxf(row16_max(m_new), m_ctx);
+        if (MULTI && s0 > 0) {
+            const float alpha = m_ctx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ctx - m_new);
+            l_ctx *= alpha;
+#pragma unroll
+            for (int x = 0; x < CPL; ++x) o[x] *= alpha;
+        }
+        m_ctx = m_new;
+        float w[KM], l_new = 0.f;
+#pragma unroll
+        for (int k = 0; k < KM; ++k) {
+            const float e = ml[k].y > 0.f ? __builtin_amdgcn_exp2f(ml[k].x - m_ctx) : 0.f;
+            l_new = fmaf(ml[k].y, e, l_new);
+            w[k] = HALF ? e * ml[k].y : e;   // a normalised partial weighs in with its l
+        }
+        l_ctx += row16_sum(l_new);
+        if constexpr (!MULTI) {
+            add_n(ra, w[0], I0{}, std::integral_constant<int, NP < 8 ? NP : 8>{});
+            if constexpr (NP == 16) add_n(ra + 8, w[0], I8{}, I8{});
+            break;
+        } else {
+            static_assert(!MULTI || NP == 8, "eight partials per round");
+            P rb[NP];
+#pragma unroll
+            for (int k = 0; k < KM; ++k) {   // two register sets in turn
+                const int at = s0 + 16 * k;
+                if (at >= ns) break;
+                if (at + 8 < ns) fetch(at + 8, rb);
+                add_n(ra, w[k], I0{}, I8{});
+                if (at + 8 >= ns) break;
+                if (at + 16 < ns && k + 1 < KM) fetch(at + 16, ra);
+                add_n(rb, w[k], I8{}, I8{});
+            }
+            if (s0 + 16 * KM >= ns) break;
         }
     }
     if (wave == nq) SPECPV_CSTAMP(2, nq);   // context partials in and merged
@@ -434,7 +458,8 @@ static void launch_combine_t(const Shape &s, Partials p, void *out, float *lse, 
     do {                                                                                                                \
         if (s.koff > s.kctx) SPECPV_LAUNCH_H(NP, MULTI, 24); else SPECPV_LAUNCH_H(NP, MULTI, 8);                         \
     } while (0)
-    if (p.nsplit <= 2) SPECPV_LAUNCH_NP(2, false);
+    if (p.stream) SPECPV_LAUNCH_NP(8, true);
+    else if (p.nsplit <= 2) SPECPV_LAUNCH_NP(2, false);
     else if (p.nsplit <= 4) SPECPV_LAUNCH_NP(4, false);
     else if (p.nsplit <= 8) SPECPV_LAUNCH_NP(8, false);
     else if (p.nsplit <= 16) SPECPV_LAUNCH_NP(16, false);

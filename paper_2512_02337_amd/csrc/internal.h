@@ -45,11 +45,16 @@ struct Shape {
 //     (0 if l = 0), channels in order.  A convex combination of V rows, so within fp16's range as long as
 //     |v| <= 65504 (larger magnitudes are clamped); its 11 significant bits are 8 times finer than the
 //     bf16 output.  Half the bytes of the fp32 form: the partials are the call's second-largest traffic.
+// stream > 0: no fixed number of splits.  The chunks of all (sequence, KV head) pairs in a row are dealt to `stream`
+// workgroups in equal, contiguous shares (StreamShare), and the partial of workgroup w for pair u stands in slot w + u --
+// pairs and workgroups both advance along the row, so no two (w, u) that meet share a slot, and a pair's slots are
+// adjacent.
 struct Partials {
     float *o;
     float *ml;
     int nsplit;
     int o_half;
+    int stream;
     unsigned long long *timeline;   // instrumented builds (-DSPECPV_TIMELINE): the combine kernel's time stamps go to rows 2048.. of this buffer
 };
 __host__ __device__ constexpr int partial_pos(int c, int D)
@@ -73,6 +78,39 @@ constexpr bool partial_order_is_a_permutation()
     return true;
 }
 static_assert(partial_order_is_a_permutation(), "partial_pos / partial_chan must be inverse permutations of a row");
+
+// The shares of the workgroups where Partials::stream > 0: every wavefront works them out from the sequence lengths (at
+// most 64 sequences, one per lane).  A sequence counts its chunks of 32 cache tokens (whole blocks) and of partially
+// verified tokens.
+struct StreamShare {
+    int chunks, upto;     // of sequence `lane`: its chunks, and those of the sequences 0 .. lane (one KV head)
+    int total, wgs;       // chunks of all pairs; workgroups with a share
+    int share, longer;    // the first `longer` shares have share + 1 chunks, the others share
+    __device__ __forceinline__ StreamShare(const Shape &s, int lane, int stream)
+    {
+        const int L = lane < s.batch ? s.ctx_len[lane] : 0;
+        int nb = L > 0 ? (int)(((uint32_t)L + (uint32_t)s.B - 1u) / (uint32_t)s.B) : 0;
+        if (nb > s.max_blocks) nb = s.max_blocks;
+        chunks = lane < s.batch ? (int)(((uint32_t)nb * (uint32_t)s.B + 31u) >> 5) + ((s.kctx + 31) >> 5) : 0;
+        upto = chunks;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int below = __shfl_up(upto, o);
+            upto += lane >= o ? below : 0;
+        }
+        total = __builtin_amdgcn_readlane(upto, 63) * s.Hkv;
+        wgs = min(stream, total);
+        share = wgs > 0 ? (int)((uint32_t)total / (uint32_t)wgs) : 0;
+        longer = total - share * wgs;
+    }
+    // where the share of workgroup w begins, and the workgroup whose share chunk x lies in
+    __device__ __forceinline__ int begin(int w) const { return w * share + min(w, longer); }
+    __device__ __forceinline__ int owner(int x) const
+    {
+        const int head = longer * (share + 1);
+        return x < head ? (int)((uint32_t)x / (uint32_t)(share + 1)) : longer + (int)((uint32_t)(x - head) / (uint32_t)share);
+    }
+};
 
 template <typename T> struct Elem;
 template <> struct Elem<float> {
@@ -162,7 +200,8 @@ enum AttnKind { kAttnGeneric = 0, kAttnSplit = 1, kAttnGroup = 3 };
 struct AttnPlan {
     int nsplit;
     int kind;
-    int tg;   // kAttnSplit: token groups per workgroup
+    int tg;       // kAttnSplit: token groups per workgroup
+    int stream;   // kAttnGroup: workgroups that share the chunks of all pairs (see Partials), or 0
 };
 // The whole call in the eight-wavefront kernel (kAttnSplit only): the draft-tree segment as one more
 // partial (slot nctx of nctx + 1), arrival words, the last workgroup of a tile merges and stores.
