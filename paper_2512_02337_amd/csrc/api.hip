@@ -111,9 +111,9 @@ struct AttnCost {
     double us(int64_t rounds, int64_t p, double start, double per_chunk, int64_t tiles, int64_t ns) const
     {
         const double chain = (double)rounds * (start + (double)p * per_chunk);
-        const double memory = kv * (0.021 * (double)tiles + 0.116);
+        const double memory = kv * (0.02 * (double)tiles + 0.115);
         const double partials = (double)s.batch * s.Hkv * (double)ns * s.M * s.G * 512e-6;   // MB
-        return sqrt(chain * chain + memory * memory) + (ns > 16 ? 0.77 : 0.0) + 0.192 * partials;
+        return sqrt(chain * chain + memory * memory) + (ns > 16 ? 0.82 : 0.0) + 0.199 * partials;
     }
     // the tile kernel with tg token groups (attn_tile.hip)
     double tile(int tg, int64_t ns, int64_t cus) const
@@ -122,14 +122,13 @@ struct AttnCost {
         // (pairs that are a multiple of 8 stay on their XCD)
         const int64_t rounds = bg % 8 ? (bg * tiles * ns + cus - 1) / cus : (bg / 8 * tiles * ns + cus / 8 - 1) / (cus / 8);
         const int64_t p = (chunks + ns * tg - 1) / (ns * tg);
-        return us(rounds, p, tg == 2 ? 2.10 : (tg == 4 ? 1.64 : 1.71), tg == 2 ? 0.97 : (tg == 4 ? 1.49 : 2.11), tiles, ns);
+        return us(rounds, p, tg == 2 ? 2.03 : (tg == 4 ? 1.59 : 1.67), tg == 2 ? 0.97 : (tg == 4 ? 1.50 : 2.13), tiles, ns);
     }
     // the group kernel (attn_mfma.hip)
-    double group(int parts, int waves, int64_t ns, int64_t cus) const
+    double group(int parts, int blocks, int64_t ns, int64_t cus) const
     {
         const int64_t rounds = ((int64_t)s.batch * s.Hkv * parts * ns + cus - 1) / cus, p = (chunks + ns - 1) / ns;
-        const double c = waves <= 2 ? 0.61 : (waves <= 4 ? 0.65 : (waves <= 6 ? 0.84 : (waves <= 8 ? 0.89 : 1.32)));
-        return us(rounds, p, 2.11, c, parts, ns);
+        return us(rounds, p, 3.11, attn_group_chunk_us(blocks), parts, ns);
     }
 };
 
@@ -147,7 +146,8 @@ static int64_t first_splits(const Shape &s, int64_t chunks, int64_t cus)
     };
     auto at_most = [](int64_t c) { return c < 1 ? (int64_t)1 : (c < 64 ? c : (int64_t)64); };
     const int64_t ns = best_of((int64_t)s.batch * s.Hq * ((s.M + 63) / 64), 4, at_most(chunks / 4));
-    return chunks >= 32 * ns ? best_of((int64_t)s.batch * s.Hkv * attn_group_parts(s), 1, at_most(chunks / 8)) : ns;
+    const int64_t row_blocks = (s.G * s.M + 31) / 32, parts = row_blocks == 9 || row_blocks == 10 ? 1 : (row_blocks + 7) / 8;
+    return chunks >= 32 * ns ? best_of((int64_t)s.batch * s.Hkv * parts, 1, at_most(chunks / 8)) : ns;
 }
 
 // Which kernel the context part of the attention runs on and how many KV splits it uses when
@@ -218,7 +218,7 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             }
         } else {
             const AttnCost cost(s, chunks);
-            const int waves = attn_group_waves(s);
+            const int blocks = attn_group_blocks(s);
             double best = -1.0;
             auto take = [&](double us, int kind, int tg, int64_t c) {
                 if (best < 0.0 || us < best) { best = us; plan.kind = kind; plan.tg = tg; ns = c; }
@@ -230,7 +230,7 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
                 if (c < 1 || c > 64) continue;
                 for (int tg = 2; tg <= 8; tg *= 2)
                     if (c * tg <= 2 * chunks) take(cost.tile(tg, c, cus), kAttnSplit, tg, c);
-                if (chunks >= 2 * c) take(cost.group(parts, waves, c, cus), kAttnGroup, 4, c);
+                if (chunks >= 2 * c) take(cost.group(parts, blocks, c, cus), kAttnGroup, 4, c);
             }
             ns = static_room([&] { return first_splits(s, chunks, cus); }, ns);
         }

@@ -206,12 +206,16 @@ __device__ __forceinline__ void lds_read_v64(uint32_t a0, uint32_t a1, uint2 (&v
 // other CUs (and mostly other XCDs): stored with the streaming hint they do not linger in this
 // XCD's L2 as dirty lines that the end of the kernel has to write back (measured: 3.6 % of the
 // partial-verify step).
-// Two values of a split's normalised result as fp16 (clamped to fp16's range), one streaming 4-byte store.
+// Two values of a split's normalised result as fp16, clamped to fp16's range.
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void store_partial_half(float *row, int lane, float a, float b)
+__device__ __forceinline__ uint32_t half_pair(float a, float b)
 {
     const f16x2 hv = {(_Float16)__builtin_amdgcn_fmed3f(a, -65504.f, 65504.f), (_Float16)__builtin_amdgcn_fmed3f(b, -65504.f, 65504.f)};
-    __builtin_nontemporal_store(__builtin_bit_cast(uint32_t, hv), (uint32_t *)row + lane);
+    return __builtin_bit_cast(uint32_t, hv);
+}
+__device__ __forceinline__ void store_partial_half(float *row, int lane, float a, float b)
+{
+    __builtin_nontemporal_store(half_pair(a, b), (uint32_t *)row + lane);
 }
 
 // max / sum over the two half-wavefronts (lane and lane ^ 32)

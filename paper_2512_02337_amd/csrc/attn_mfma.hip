@@ -800,45 +800,62 @@ void attn_ctx_mfma_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
 
 // ---- group variant: the query heads of a KV head in one workgroup --------------------------
 // For long token ranges.  The G x ceil(M / 32) blocks of 32 query rows that share a KV head are
-// dealt to workgroups of up to 10 wavefronts, one row block per wavefront (G = 4, M <= 64: one
-// workgroup of 8; G = 5: one workgroup of 10; more row blocks: two or more workgroups).  A workgroup
-// owns (sequence, KV head, its row blocks, KV split) and walks the split's chunks once for all of
-// them: its W wavefronts share ONE ring of eight stages and each brings its share of a chunk's 16 DMA
+// dealt to workgroups of up to 12 wavefronts (G = 4, M <= 64: one workgroup of 8; more row blocks than 10: two or more
+// workgroups).  A workgroup owns (sequence, KV head, its row blocks, KV split) and walks the split's chunks once for
+// all of them: its W wavefronts share ONE ring of four stages and each brings its share of a chunk's 16 DMA
 // operations, so every K / V byte is requested from memory exactly once per workgroup, whatever
 // the caches do.
-// The ring has two halves of four chunks.  One workgroup barrier per FOUR chunks: at the barrier in
-// front of chunks i .. i + 3 all of them have landed (requested one period earlier), every wavefront
-// is done with the other half, and chunks i + 4 .. i + 7 are requested into it at once.  (A barrier
-// per chunk, with the requests three chunks ahead in a ring of four, cost 430 of 2300 core cycles
-// per chunk: it puts the wavefronts of a SIMD back in step every chunk, so that they queue for
-// the LDS, the matrix cores and the vector ALU together instead of filling each other's gaps.)
+// The ring has two halves of two chunks.  One workgroup barrier per TWO chunks: at the barrier in
+// front of chunks i, i + 1 both have landed (requested one period earlier), every wavefront
+// is done with the other half, and chunks i + 2, i + 3 are requested into it at once.  Measured, us per pass with
+// [chunks per barrier, chunks in flight]: partial step of four sequences at G = 5 (two layers, 16 chunks a workgroup)
+// [4, 4] 86.2, [2, 6] 84.9, [2, 4] 84.7, [2, 3] 81.8, [2, 2] 80.8, [1, 4] 92.5, [1, 1] 82.3; full pass over 64K tokens and 78 nodes
+// [4, 4] 117.0, [2, 6] 114.0, [2, 2] 112.3, [1, 3] 117.4, [1, 1] 115.3; over the ragged batch at G = 5 474, 480, 465, 505, 496.
+// A barrier per chunk puts the wavefronts of a SIMD back in step every chunk, so that they queue for the LDS, the
+// matrix cores and the vector ALU together instead of filling each other's gaps; requests further ahead gain nothing
+// once a period covers the latency of memory, and the first chunks wait behind them.
 // A wavefront keeps its rows to itself over the whole split, so the epilogue has nothing to
 // merge: it only turns the accumulators into row-major partials.
-// The chunk loop is unrolled over the eight ring stages: with the stage a compile-time constant,
+// The chunk loop is unrolled over the ring stages: with the stage a compile-time constant,
 // stage offsets are immediate fields of the LDS reads and of the requests' LDS addresses, the
 // validity words of the stages are scalar registers, and the request of a chunk tests the common
 // case (32 valid consecutive rows) first.  What a wavefront executes per chunk besides its
 // arithmetic is what this loop pays for: measured in core cycles per chunk and workgroup (128K
 // context, 32 splits), 2590 with a run-time stage and a barrier per chunk, 2295 unrolled, 2085
 // with the four-chunk period; 1400 for the requests and barriers alone (timing probe), 1024 for
-// the matrix instructions.  (The ten-wavefront variant keeps a barrier per chunk, see below.)
-constexpr int kGroupStages = 8;   // two halves of kGroupPeriod chunks
-constexpr int kGroupPeriod = 4;   // chunks between two workgroup barriers
+// the matrix instructions.
+constexpr int kGroupPeriod = 2;                  // chunks between two workgroup barriers
+constexpr int kGroupStages = 2 * kGroupPeriod;   // two halves
 // One 32-token chunk in LDS.  128 channels: as above (kStageBytes).  64 channels: 4 KiB of K (128-byte rows, 16-byte
 // pieces XOR-swizzled by (row >> 1) & 7: two rows make one 256-byte bank row), V in four 1 KiB operations of two pieces
 // each (lds_read_v64).
 template <int D> struct Tile;
 template <> struct Tile<128> {
-    static constexpr int kK = 8192, kVOpPitch = kVPiecePitch, kStage = kStageBytes, kPitch = kOPitch;
+    static constexpr int kK = 8192, kVOpPitch = kVPiecePitch, kStage = kStageBytes;
+    static constexpr int kRowPitch = 272, kRows = 32 * kRowPitch, kHandOver = 64 * 64 * 4 + 512;   // staged rows of a row block; accumulators, m and l of another wavefront
 };
 template <> struct Tile<64> {
-    static constexpr int kK = 4096, kVOpPitch = 1152, kStage = kK + 4 * kVOpPitch, kPitch = 68;   // kPitch: floats per staged output row
+    static constexpr int kK = 4096, kVOpPitch = 1152, kStage = kK + 4 * kVOpPitch;
+    static constexpr int kRowPitch = 272, kRows = 32 * kRowPitch, kHandOver = 64 * 32 * 4 + 512;
 };
 static_assert(Tile<64>::kStage % 256 == 0 && kStageBytes % 256 == 0, "K operand addresses are derived by XOR with multiples of 32 below 256: stages (and the rings) must start 256-byte aligned");
 
-// W wavefronts per workgroup: 2, 4, 6, 8 or 10.  Ten (nine or ten row blocks: G = 5 with up to 64 nodes) means
-// three wavefronts on two of the SIMDs, i.e. at most 168 registers each: that variant takes its K and V
-// operands in halves.
+// RB row blocks per workgroup: 2, 4, 6, 8 or 10.  The CU has four SIMDs: up to four, or eight, row blocks have a wavefront
+// each; the two that 2, 6 and 10 leave over are shared by two wavefronts each, one of which takes the even chunks and one
+// the odd ones, so that every SIMD has the same work (before, a wavefront per row block: full pass over a ragged batch of 320K tokens at
+// G = 5, 64 nodes, 525 us, 460 with twelve wavefronts; 64 channels, 37 nodes at G = 4 over 45K tokens, 51 us, 43 with
+// eight for its five row blocks; one and two row blocks over 8K to 128K tokens, 20 % less).
+// Ten row blocks (nine or ten: G = 5 with up to 64 nodes) are twelve wavefronts, three per SIMD, i.e. at most 168
+// registers each: that variant takes its K and V operands in halves.
+constexpr int group_waves(int rb) { return rb % 4 ? (rb & ~3) + 4 : rb; }
+// LDS: the ring, and in its place at the end the staged rows of all row blocks, and the sums that the odd chunks' wavefronts
+// hand over.
+template <int D> constexpr int group_lds(int rb)
+{
+    const int ring = kGroupStages * Tile<D>::kStage, rows = rb * Tile<D>::kRows + (rb % 4 ? 2 * Tile<D>::kHandOver : 0);
+    return ring > rows ? ring : rows;
+}
+static_assert(group_lds<128>(10) <= 160 * 1024 && group_lds<128>(4) <= 80 * 1024 && group_lds<64>(8) <= 80 * 1024, "");
 // D = 64: half the LDS and half the operand registers, so two workgroups share a CU (four wavefronts per SIMD, 128
 // registers): at 64 channels a chunk has half the matrix work against the same softmax, and what counts is how many
 // wavefronts the vector ALU can choose from.  The weights enter the second product as two bf16 terms (16 bits) and the
@@ -847,18 +864,19 @@ static_assert(Tile<64>::kStage % 256 == 0 && kStageBytes % 256 == 0, "K operand 
 // ALU, 65 us here (53 us with the weights as one bf16 term and fp16 partials).
 // SK: shares of the chunks of all (sequence, KV head) pairs instead of splits (Partials::stream): a workgroup goes through
 // the one to three pairs that its share touches, one after the other.
-template <int D, bool ALIGNED, int W, bool SK>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : (W > 8 ? 3 : 2), D == 64 ? 4 : (W > 8 ? 3 : 2))))
+template <int D, bool ALIGNED, int RB, bool SK>
+__global__ __launch_bounds__(64 * group_waves(RB)) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : (RB > 8 ? 3 : 2), D == 64 ? 4 : (RB > 8 ? 3 : 2))))
 void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
 {
     typedef Tile<D> TL;
+    constexpr int W = group_waves(RB), F = RB & ~3;   // wavefronts; those with a row block to themselves
+    constexpr bool PAIRED = W != RB;                // the others share one between two
     constexpr int KS = D / 16, NT = D / 32;         // k-steps of S^T, channel tiles of O^T
     constexpr int LPR = D / 8, RPO = 64 / LPR;      // lanes per row, rows per 1 KiB operation
     constexpr int KOPS = D / 16, OPS = 2 * KOPS;    // DMA operations of a chunk: K, then V
     SPECPV_CLOCKS_BEGIN;
     extern __shared__ char lds_raw[];
     char *ring = lds_raw;                  // [kGroupStages][K 8 KiB | V 8 pieces of 1088 B]
-    float *obuf = (float *)lds_raw;        // [W wavefronts][32 rows][kOPitch], reuses the ring after the main loop
 
     const int xcd = blockIdx.x & 7, wg_part = blockIdx.x >> 3;
     const int u = blockIdx.y * 8 + xcd;
@@ -868,7 +886,8 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     // this wavefront's row block: rows r0w .. r0w + 31 of the KV head's M * G query rows.  A
     // workgroup may have a wavefront too many (row block counts that do not divide): it brings
     // its share of the chunks and keeps the barriers, but computes and stores nothing.
-    const int rbx = wg_part * W + wave;
+    const int rb = wave < F ? wave : F + ((wave - F) >> 1), odd = wave < F ? 0 : (wave - F) & 1;
+    const int rbx = wg_part * RB + rb;
     const bool live = rbx < a.n_row_blocks;
     const int R = s.M * s.G;                  // query rows of the KV head: row r is head r / M of the group, node r % M
     const int r0w = (live ? rbx : a.n_row_blocks - 1) * 32;
@@ -988,12 +1007,13 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
 
     // Request this wavefront's operations of chunk ci into stage stg (1 KiB each: LPR lanes per row).  K operation i
     // brings rows RPO i .. RPO i + RPO - 1, pieces swizzled; V operation i at 128 channels rows i, i+8, i+16, i+24
-    // (piece i), at 64 channels the pieces 2 i and 2 i + 1.  Wavefront w takes operations w, w + W, w + 2W, ...
+    // (piece i), at 64 channels the pieces 2 i and 2 i + 1.  A wavefront takes operations op0, op0 + W, op0 + 2W, ...
     // Returns the validity bits of the chunk's 32 tokens.
     // Everything that depends on the wavefront is folded into a few registers up front, so that
     // the common path is straight-line code.
     constexpr int NOPS = (OPS + W - 1) / W;
-    const int n_ops = (OPS - wave + W - 1) / W;      // NOPS or NOPS - 1
+    const int op0 = PAIRED ? (wave < F ? wave + W - F : wave - F) : wave;   // (those with half the arithmetic request more)
+    const int n_ops = (OPS - op0 + W - 1) / W;       // NOPS or NOPS - 1
     // the row of the chunk that lane ln fetches for operation o, and the byte offset of its 16-byte piece in the row
     auto op_row = [](int o, int ln) -> int {
         const int i = o & (KOPS - 1), rl = ln / LPR;
@@ -1010,20 +1030,20 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     int dst_off[NOPS];            // ... and where it lands in the stage
 #pragma unroll
     for (int t = 0; t < NOPS; ++t) {
-        const int o = min(wave + W * t, OPS - 1), i = o & (KOPS - 1);
+        const int o = min(op0 + W * t, OPS - 1), i = o & (KOPS - 1);
         src_base[t] = o < KOPS ? kb : vb;
         src_off[t] = (uint32_t)op_row(o, lane) * st2 + op_piece(o, lane);
         dst_off[t] = o < KOPS ? i * 1024 : TL::kK + i * TL::kVOpPitch;
     }
     auto issue_rows = [&](const char *kbase, const char *vbase, const uint32_t stride, const uint32_t tk, char *dst) {
         // (the swizzles are recomputed here, from a lane id the compiler cannot see through: kept in registers
-        // across the loop for this rare path they cost the ten-wavefront variant its last free registers)
+        // across the loop for this rare path they cost the twelve-wavefront variant its last free registers)
         int lane_o = lane;
         asm volatile("" : "+v"(lane_o));
 #pragma unroll
         for (int t = 0; t < NOPS; ++t) {
             if (OPS % W != 0 && t == NOPS - 1 && n_ops != NOPS) continue;
-            const int o = wave + W * t;
+            const int o = op0 + W * t;
             const uint32_t tv = (uint32_t)__shfl((int)tk, op_row(o, lane_o)) * stride;
             dma16((o < KOPS ? kbase : vbase) + (tv + op_piece(o, lane_o)), dst + dst_off[t]);
         }
@@ -1041,9 +1061,9 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
                 for (int t = 0; t < NOPS; ++t)
                     if (OPS % W == 0 || t < NOPS - 1 || n_ops == NOPS) {
                         uint32_t so = src_off[t];
-                        // (ten wavefronts: keep the 32-bit offset as it is; the compiler would otherwise carry the 64-bit sum
+                        // (168 registers: keep the 32-bit offset as it is; the compiler would otherwise carry the 64-bit sum
                         // base + offset of every operation through the loop, in registers that this variant does not have)
-                        if (W > 8) asm volatile("" : "+v"(so));
+                        if (RB > 8) asm volatile("" : "+v"(so));
                         __builtin_amdgcn_global_load_lds((glb_void_ptr)((src_base[t] + row_off) + so), (lds_void_ptr)(dst + dst_off[t]), 16, 0, kKvAux);
                     }
                 return 0xffffffffu;
@@ -1088,14 +1108,10 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
         for (int i = 0; i < 16; ++i) O[j][i] = 0.f;
 
     // validity bits of the chunks in the ring, one word per stage (the same in every lane)
-    uint32_t vm_stage[kGroupStages] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-    static_assert(kGroupStages == 8 && kGroupPeriod == 4, "the first requests and the loops below are written for two halves of four stages");
-    if (W <= 8) {
-        if (0 < nch) vm_stage[0] = issue(0, 0);
-        if (1 < nch) vm_stage[1] = issue(1, 1);
-        if (2 < nch) vm_stage[2] = issue(2, 2);
-        if (3 < nch) vm_stage[3] = issue(3, 3);
-    }
+    uint32_t vm_stage[kGroupStages] = {0u, 0u, 0u, 0u};
+    static_assert(kGroupPeriod == 2, "the first requests and the loop below are written for two halves of two stages");
+    if (0 < nch) vm_stage[0] = issue(0, 0);
+    if (1 < nch) vm_stage[1] = issue(1, 1);
     uint2 v[4 * NT];
     uint4 pf0 = make_uint4(0u, 0u, 0u, 0u), pf1 = pf0;
     uint4 pl0 = pf0, pl1 = pf0;   // 64 channels: what the rounding of the weights to bf16 left over, rounded in turn
@@ -1112,7 +1128,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
                                                                    as_bf16x8(ks2 ? pl1 : pl0), O[j], 0, 0, 0);
             }
     };
-    // ten wavefronts: operands in halves (16 registers at a time instead of 32)
+    // three wavefronts per SIMD: operands in halves (16 registers at a time instead of 32)
     auto pv_halves = [&](const uint32_t vaddr, auto off) __attribute__((always_inline)) {
         constexpr int OFF = decltype(off)::value;
         uint2 vh[8];
@@ -1131,17 +1147,17 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     // One chunk; its ring stage U = i % 4 is a compile-time constant (the loop below is unrolled over the
     // stages), so that stage offsets are immediate fields of the LDS reads and of the requests' LDS
     // addresses, and the validity words live in scalar registers.
-    // Stage U compile-time (the unrolled loop): the stage inside its ring half is an immediate field of the LDS
-    // reads (16 bits), the half is reached through the address register.  The ten-wavefront loop passes stage 0
-    // and the whole offset at run time (roff).
-    auto chunk = [&](const int i, auto stage, const uint32_t roff, const uint32_t vmask) __attribute__((always_inline)) {
+    // The stage inside its ring half is an immediate field of the LDS reads (16 bits), the half is reached through the
+    // address register.  A row block's two wavefronts take the even and the odd chunks.
+    const bool live0 = live && (!PAIRED || wave < F || odd == 0), live1 = live && (!PAIRED || wave < F || odd == 1);
+    auto chunk = [&](auto stage, const uint32_t vmask) __attribute__((always_inline)) {
         constexpr int U = decltype(stage)::value;
         constexpr int SOFF = (U % kGroupPeriod) * TL::kStage;
-        const uint32_t HOFF = (uint32_t)(U / kGroupPeriod) * kGroupPeriod * TL::kStage + roff;
-        if (!live) return;
+        constexpr uint32_t HOFF = (uint32_t)(U / kGroupPeriod) * kGroupPeriod * TL::kStage;
+        if (!((U & 1) ? live1 : live0)) return;
         f32x16 S;
-        if constexpr (W > 8) {
-            // ten wavefronts: operands in halves, the V operands read behind the softmax (pv_halves)
+        if constexpr (RB > 8) {
+            // three wavefronts per SIMD: operands in halves, the V operands read behind the softmax (pv_halves)
             // (k-step ks reads 32 ks bytes further, modulo the swizzle: an XOR, as the row starts are 128-byte aligned)
             const uint32_t ka0 = kread0 + HOFF;
             const uint32_t ka[4] = {ka0, ka0 ^ 32u, ka0 ^ 64u, ka0 ^ 96u};
@@ -1226,102 +1242,93 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
         }
         pf0 = make_uint4(pk[0], pk[1], pk[2], pk[3]);
         pf1 = make_uint4(pk[4], pk[5], pk[6], pk[7]);
-        if constexpr (W > 8) pv_halves(vread + HOFF, std::integral_constant<int, SOFF>{});
+        if constexpr (RB > 8) pv_halves(vread + HOFF, std::integral_constant<int, SOFF>{});
         else pv();
     };
-    // Four chunks between two barriers.  At the barrier in front of chunks i0 .. i0 + 3 (ring half H) every
+    // Two chunks between two barriers.  At the barrier in front of chunks i0, i0 + 1 (ring half H) every
     // wavefront's requests have landed -- they were made a whole period ago, so the wait is for all of
-    // them -- and every wavefront is done with the other half, into which the next four chunks are
-    // requested at once; then come four chunks of arithmetic without a request or a wait in between.
+    // them -- and every wavefront is done with the other half, into which the next two chunks are
+    // requested at once; then come two chunks of arithmetic without a request or a wait in between.
     auto period = [&](const int i0, auto half) __attribute__((always_inline)) {
         constexpr int H = decltype(half)::value, S0 = kGroupPeriod * H, N0 = kGroupPeriod * (1 - H);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
-        if (i0 + 4 < nch) vm_stage[N0] = issue(i0 + 4, N0);
-        if (i0 + 5 < nch) vm_stage[N0 + 1] = issue(i0 + 5, N0 + 1);
-        if (i0 + 6 < nch) vm_stage[N0 + 2] = issue(i0 + 6, N0 + 2);
-        if (i0 + 7 < nch) vm_stage[N0 + 3] = issue(i0 + 7, N0 + 3);
-        chunk(i0, std::integral_constant<int, S0>{}, 0u, vm_stage[S0]);
-        if (i0 + 1 < nch) chunk(i0 + 1, std::integral_constant<int, S0 + 1>{}, 0u, vm_stage[S0 + 1]);
-        if (i0 + 2 < nch) chunk(i0 + 2, std::integral_constant<int, S0 + 2>{}, 0u, vm_stage[S0 + 2]);
-        if (i0 + 3 < nch) chunk(i0 + 3, std::integral_constant<int, S0 + 3>{}, 0u, vm_stage[S0 + 3]);
+        if (i0 + 2 < nch) vm_stage[N0] = issue(i0 + 2, N0);
+        if (i0 + 3 < nch) vm_stage[N0 + 1] = issue(i0 + 3, N0 + 1);
+        chunk(std::integral_constant<int, S0>{}, vm_stage[S0]);
+        if (i0 + 1 < nch) chunk(std::integral_constant<int, S0 + 1>{}, vm_stage[S0 + 1]);
     };
-    if (W <= 8) {
-        for (int i0 = 0; i0 < nch; i0 += kGroupStages) {
-            period(i0, std::integral_constant<int, 0>{});
-            if (i0 + kGroupPeriod < nch) period(i0 + kGroupPeriod, std::integral_constant<int, 1>{});
-        }
-    } else {
-        // Ten wavefronts (three on two of the SIMDs, 168 registers): a barrier per chunk, requests three chunks
-        // ahead, the stage a run-time value -- measured against the period loop above on the ragged batch of four
-        // at G = 5: partial step (16 chunks per workgroup) 32.1 against 37.1 us, full pass 532 against 525 us.
-        constexpr int kAhead = 3;
-        uint32_t vmv = 0u;   // validity words of the chunks in the ring: lane t holds those of stage t
-        for (int c = 0; c < kAhead && c < nch; ++c) {
-            const uint32_t vm = issue(c, c);
-            vmv = lane == c ? vm : vmv;
-        }
-        for (int i = 0; i < nch; ++i) {
-            // own part of chunk i has landed: kAhead - 1 younger groups of n_ops operations may stay in flight
-            // (towards the end of the range there are fewer: wait for all, they are due anyway)
-            if (i + kAhead - 1 >= nch) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            else if (n_ops == NOPS) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NOPS * (kAhead - 1)) : "memory");
-            else asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NOPS - 1) * (kAhead - 1)) : "memory");
-            __builtin_amdgcn_s_barrier();   // ... and so have the others'; chunk i-1 has been read by all
-            if (i + kAhead < nch) {
-                const int is = (i + kAhead) & (kGroupStages - 1);
-                const uint32_t vm = issue(i + kAhead, is);
-                vmv = lane == is ? vm : vmv;
-            }
-            const int rs = i & (kGroupStages - 1);
-            chunk(i, std::integral_constant<int, 0>{}, (uint32_t)rs * TL::kStage, (uint32_t)__builtin_amdgcn_readlane((int)vmv, rs));
-        }
+    for (int i0 = 0; i0 < nch; i0 += kGroupStages) {
+        period(i0, std::integral_constant<int, 0>{});
+        if (i0 + kGroupPeriod < nch) period(i0 + kGroupPeriod, std::integral_constant<int, 1>{});
     }
     __syncthreads();   // every wavefront is done with the ring: the epilogue reuses that LDS
 
     // ---- one partial per (head, split, node): accumulators -> row-major through LDS ------
-    // (ten wavefronts: the staging area holds five at a time, so the second five wait for the first;
-    // every wavefront, live or not, passes that one barrier)
-    constexpr int kSlots = W > 8 ? W / 2 : W;
-    const int slot = wave < kSlots ? wave : wave - kSlots;
-    if (W > 8 && wave >= kSlots) __builtin_amdgcn_s_barrier();
-    if (live) {
+    if (PAIRED) {
+        // the odd chunks' wavefront hands its sums over as they lie in its registers, behind the staged rows
+        float *raw = (float *)(ring + RB * TL::kRows + (rb - F) * TL::kHandOver);
+        if (wave >= F && odd) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *(float4 *)(raw + ((j * 4 + q) * 64 + lane) * 4) = make_float4(O[j][4 * q], O[j][4 * q + 1], O[j][4 * q + 2], O[j][4 * q + 3]);
+            *(float2 *)(raw + NT * 1024 + 2 * lane) = make_float2(m_ref, l_run);
+        }
+        __syncthreads();
+        if (wave >= F && !odd) {
+            const float2 ml = *(const float2 *)(raw + NT * 1024 + 2 * lane);
+            const float m_new = fmaxf(m_ref, ml.x), m_use = m_new == -INFINITY ? 0.f : m_new;
+            const float a0 = __builtin_amdgcn_exp2f(m_ref - m_use), a1 = __builtin_amdgcn_exp2f(ml.x - m_use);
+            m_ref = m_new;
+            l_run = l_run * a0 + ml.y * a1;
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4 x = *(const float4 *)(raw + ((j * 4 + q) * 64 + lane) * 4);
+                    O[j][4 * q] = fmaf(x.x, a1, O[j][4 * q] * a0);
+                    O[j][4 * q + 1] = fmaf(x.y, a1, O[j][4 * q + 1] * a0);
+                    O[j][4 * q + 2] = fmaf(x.z, a1, O[j][4 * q + 2] * a0);
+                    O[j][4 * q + 3] = fmaf(x.w, a1, O[j][4 * q + 3] * a0);
+                }
+        }
+    }
+    if (live && !odd) {
     l_run = sum_xor32(l_run);
     const int64_t prow0 = (SK ? (int64_t)(u + bg) : (int64_t)bg * part.nsplit + sp) * R + r0w;
     const int n_rows = min(32, R - r0w);
-    {
-        // accumulator element 4q + x of tile j is channel 32j + 8q + 4kg + x of this lane's row
-        float *dst = obuf + ((size_t)slot * 32 + n) * TL::kPitch;
+    // accumulator element 4q + x of tile j is channel 32j + 8q + 4kg + x of this lane's row.  A wavefront reads back
+    // only what it wrote itself: no barrier.  Sixteen bytes per lane, four rows per store; at 128 channels normalised and
+    // rounded to fp16 on the way into LDS, so that all row blocks have room there at once (as fp32, ten row blocks took
+    // turns and stores were a row each: partial step of four sequences at G = 5, two layers, 92.8 us, 88.1 so).
+    char *rows = ring + rb * TL::kRows;
+    if constexpr (D == 128) {   // the normalised result as fp16
+        const float il = l_run > 0.f ? 1.f / l_run : 0.f;
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                *(float4 *)(dst + 32 * j + 8 * q + 4 * kg) = make_float4(O[j][4 * q], O[j][4 * q + 1], O[j][4 * q + 2], O[j][4 * q + 3]);
-    }
-    // a wavefront reads back only what it wrote itself: no barrier.  fp16 partials: channels 2 lane, 2 lane + 1
-    // of the row's normalised result (lane uu < 32 holds row uu's l)
-    const float il = l_run > 0.f ? 1.f / l_run : 0.f;
-    if constexpr (D == 128) {
-#pragma unroll 8
-        for (int uu = 0; uu < 32; ++uu) {
-            const float2 x = *(const float2 *)(obuf + ((size_t)slot * 32 + uu) * TL::kPitch + 2 * lane);
-            const float ilu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(il), uu));
-            if (uu < n_rows) store_partial_half(part.o + (prow0 + uu) * 64, lane, x.x * ilu, x.y * ilu);
-        }
-    } else {
-        // fp32 sums, four channels per lane, four rows at a time
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
+                *(uint2 *)(rows + n * TL::kRowPitch + 64 * j + 16 * q + 8 * kg) =
+                    make_uint2(half_pair(O[j][4 * q] * il, O[j][4 * q + 1] * il), half_pair(O[j][4 * q + 2] * il, O[j][4 * q + 3] * il));
+    } else {                    // the sums as fp32
 #pragma unroll
-        for (int uu = 0; uu < 8; ++uu) {
-            const int row = 4 * uu + (lane >> 4);
-            const f32x4 x = *(const f32x4 *)(obuf + ((size_t)slot * 32 + row) * TL::kPitch + 4 * (lane & 15));
-            if (row < n_rows) __builtin_nontemporal_store(x, (f32x4 *)(part.o + (prow0 + row) * 64) + (lane & 15));
-        }
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *(float4 *)(rows + n * TL::kRowPitch + 128 * j + 32 * q + 16 * kg) = make_float4(O[j][4 * q], O[j][4 * q + 1], O[j][4 * q + 2], O[j][4 * q + 3]);
+    }
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int uu = 0; uu < 8; ++uu) {
+        const int row = 4 * uu + (lane >> 4);
+        const u32x4 x = *(const u32x4 *)(rows + row * TL::kRowPitch + 16 * (lane & 15));
+        if (row < n_rows) __builtin_nontemporal_store(x, (u32x4 *)(part.o + (prow0 + row) * 64) + (lane & 15));
     }
     if (kg == 0 && n < n_rows) *(float2 *)(part.ml + (prow0 + n) * 2) = make_float2(m_ref, l_run);
     if (!SK || share_at >= share_end) SPECPV_CLOCKS_END(part.timeline, (size_t)blockIdx.y * gridDim.x + blockIdx.x, nch);
     }
-    if (W > 8 && wave < kSlots) __builtin_amdgcn_s_barrier();   // the slot is free for wavefront wave + kSlots
     if (SK) __syncthreads();   // the next pair's chunks go where the rows were staged
     } while (SK && share_at < share_end);
 }
@@ -1334,26 +1341,31 @@ bool attn_ctx_mfma_supported(const Shape &s, int dtype)
 }
 
 // The KV head's M * G query rows in blocks of 32 (packed over the query heads: 78 nodes at G = 4 are 10 blocks, not 12),
-// and how the group kernel deals them to workgroups.
+// and how the group kernel deals them to workgroups: 2, 4, 6, 8 or 10 each.
 struct GroupLayout {
-    int n_row_blocks, parts, waves;
+    int n_row_blocks, parts, blocks;
 };
 static GroupLayout group_layout(const Shape &s)
 {
-    GroupLayout g;
-    g.n_row_blocks = (s.G * s.M + 31) / 32;
-    if (s.D == 128 && (g.n_row_blocks == 9 || g.n_row_blocks == 10)) {   // one workgroup of ten instead of two of five
-        g.parts = 1;
-        g.waves = 10;
-        return g;
+    GroupLayout g{(s.G * s.M + 31) / 32, 0, 0};
+    // the fewest microseconds per chunk for all row blocks (attn_group_chunk_us; a part also pulls the chunk
+    // through its L2; full pass over 128K tokens at eight row blocks: 212 us with one workgroup of eight, 224 with two of four)
+    double best = -1.0;
+    for (int blocks = 2; blocks <= (s.D == 128 ? 10 : 8); blocks += 2) {
+        const int parts = (g.n_row_blocks + blocks - 1) / blocks;
+        const double us = parts * (attn_group_chunk_us(blocks) + 0.05);
+        if (best < 0.0 || us < best) { best = us; g.parts = parts; g.blocks = blocks; }
     }
-    g.parts = (g.n_row_blocks + 7) / 8;
-    const int w = (g.n_row_blocks + g.parts - 1) / g.parts;   // 1 .. 8
-    g.waves = w <= 2 ? 2 : (w <= 4 ? 4 : (w <= 6 ? 6 : 8));
     return g;
 }
+// What a workgroup takes per 32-token chunk with that many row blocks, 128 channels, every CU busy (fitted to measured
+// times, see AttnCost in api.hip).
+double attn_group_chunk_us(int blocks)
+{
+    return blocks <= 2 ? 0.395 : (blocks <= 4 ? 0.616 : (blocks <= 6 ? 0.72 : (blocks <= 8 ? 0.87 : 1.133)));
+}
 int attn_group_parts(const Shape &s) { return group_layout(s).parts; }
-int attn_group_waves(const Shape &s) { return group_layout(s).waves; }
+int attn_group_blocks(const Shape &s) { return group_layout(s).blocks; }
 
 hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const int32_t *sel_count,
                                 int n_sel, Partials p, int nctx, int kind, const FusedArgs &f, hipStream_t st)
@@ -1386,9 +1398,6 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
     if (grid.y > 65535u) return hipErrorInvalidConfiguration;
     const bool aligned = s.B % 32 == 0;
     const size_t lds_split = 2048 + (size_t)max(kRingBytes, 4 * 64 * kOPitch * (int)sizeof(float)) + kQStageBytes;
-    const int staged = gl.waves > 8 ? gl.waves / 2 : gl.waves;   // wavefronts whose rows the epilogue stages at a time
-    const size_t lds_group = s.D == 128 ? (size_t)max(kGroupStages * Tile<128>::kStage, staged * 32 * Tile<128>::kPitch * (int)sizeof(float))
-                                        : (size_t)max(kGroupStages * Tile<64>::kStage, staged * 32 * Tile<64>::kPitch * (int)sizeof(float));
 #define SPECPV_SET_LDS(KERN, LDS)                                                                      \
         static PerDeviceOnce once;   /* one per kernel instantiation */                               \
         auto kern = KERN;                                                                              \
@@ -1396,10 +1405,10 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
             return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(LDS)); \
         });                                                                                            \
         if (e0 != hipSuccess) return e0
-#define SPECPV_LAUNCH_GROUP_K(DD, AL, WW, SS)                                                          \
+#define SPECPV_LAUNCH_GROUP_K(DD, AL, RR, SS)                                                          \
     do {                                                                                               \
-        SPECPV_SET_LDS((attn_ctx_mfma_group_kernel<DD, AL, WW, SS>), lds_group);                        \
-        hipLaunchKernelGGL(kern, grid, dim3(64 * WW), lds_group, st, s, p, a);                          \
+        SPECPV_SET_LDS((attn_ctx_mfma_group_kernel<DD, AL, RR, SS>), group_lds<DD>(RR));                \
+        hipLaunchKernelGGL(kern, grid, dim3(64 * group_waves(RR)), group_lds<DD>(RR), st, s, p, a);     \
     } while (0)
 #define SPECPV_LAUNCH_GROUP(DD, WW)                                                                    \
     do {                                                                                               \
@@ -1414,14 +1423,14 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
     } while (0)
     if (kind == kAttnGroup) {
         if (s.D == 64) {
-            switch (gl.waves) {
+            switch (gl.blocks) {
             case 2: SPECPV_LAUNCH_GROUP(64, 2); break;
             case 4: SPECPV_LAUNCH_GROUP(64, 4); break;
             case 6: SPECPV_LAUNCH_GROUP(64, 6); break;
             default: SPECPV_LAUNCH_GROUP(64, 8); break;
             }
         } else {
-            switch (gl.waves) {
+            switch (gl.blocks) {
             case 2: SPECPV_LAUNCH_GROUP(128, 2); break;
             case 4: SPECPV_LAUNCH_GROUP(128, 4); break;
             case 6: SPECPV_LAUNCH_GROUP(128, 6); break;

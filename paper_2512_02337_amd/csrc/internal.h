@@ -222,7 +222,8 @@ hipError_t launch_attn_ctx_tile(const Shape &s, const int32_t *sel_idx, const in
                                 int tg, unsigned long long *timeline, hipStream_t st);
 // workgroups per (sequence, KV head, split) of the kAttnGroup kernel
 int attn_group_parts(const Shape &s);
-int attn_group_waves(const Shape &s);   // wavefronts of each
+int attn_group_blocks(const Shape &s);   // row blocks of each
+double attn_group_chunk_us(int blocks);
 hipError_t launch_combine(const Shape &s, int dtype, Partials p, void *out, float *lse, hipStream_t st);
 // to_cache != 0: pending + accepted rows go to the cache tail (lengths, summaries updated);
 // otherwise the accepted rows join the pending rows of the buffer.  missed_words: the zeroed words at the
