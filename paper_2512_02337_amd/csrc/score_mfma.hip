@@ -403,7 +403,7 @@ __global__ __launch_bounds__(64 * WMAX) void score_mfma_kernel(Shape s, const ui
         }
         __syncthreads();
         if (!is_last) return;
-        topk_fast_body<P, true>(lds, scores, s.ctx_len, s.B, s.max_blocks, s.Hkv, g, b, a);
+        topk_fast_body<P, 256, true>(lds, scores, s.ctx_len, s.B, s.max_blocks, s.Hkv, g, b, a);
     }
 }
 

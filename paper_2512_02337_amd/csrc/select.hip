@@ -193,13 +193,13 @@ __global__ __launch_bounds__(256) void topk_kernel(const float *scores, const in
     if (tid == 0) sel_count[(int64_t)b * Hkv + g] = base;
 }
 
-// Faster selection for lists of up to 256 * P blocks (P <= 16): see topk.h.
-template <int P>
-__global__ __launch_bounds__(256) void topk_fast_kernel(const float *scores, const int32_t *ctx_len, int B,
+// Faster selection for lists of up to NT * P blocks: see topk.h.
+template <int P, int NT>
+__global__ __launch_bounds__(NT) void topk_fast_kernel(const float *scores, const int32_t *ctx_len, int B,
                                                         int max_blocks, int Hkv, TopkArgs a)
 {
     __shared__ TopkLds lds;
-    topk_fast_body<P, false>(lds, scores, ctx_len, B, max_blocks, Hkv, blockIdx.x, blockIdx.y, a);
+    topk_fast_body<P, NT, false>(lds, scores, ctx_len, B, max_blocks, Hkv, blockIdx.x, blockIdx.y, a);
 }
 
 bool score_mfma_supported(const Shape &s, int dtype);
@@ -220,15 +220,21 @@ hipError_t launch_scores(const Shape &s, int dtype, const void *kmax, const void
 hipError_t launch_topk(const Shape &s, const float *scores, int ns, int nr, int k, int n_row,
                        int32_t *sel_idx, int32_t *sel_count, hipStream_t st)
 {
-    dim3 grid(s.Hkv, s.batch), block(256);
+    // Four blocks a thread as long as the workgroup can grow: the time is the length of a thread's chain.  Scoring and
+    // selection of one sequence, eight KV heads, 60 nodes at G = 4, before (256 threads, radix passes only; above 4096
+    // blocks the kernel that re-reads the scores) and now: 1024 blocks 11.3 -> 10.7 us, 2048 15.8 -> 13.5,
+    // 3840 25.9 -> 21.0, 8192 85.8 -> 29.3.
+    const dim3 grid(s.Hkv, s.batch);
     const TopkArgs a{ns, nr, k, n_row, sel_idx, sel_count};
-#define SPECPV_TOPK(KERN) \
-    hipLaunchKernelGGL(KERN, grid, block, 0, st, scores, s.ctx_len, s.B, s.max_blocks, s.Hkv, a)
-    if (s.max_blocks <= 256 * 4) SPECPV_TOPK(topk_fast_kernel<4>);
-    else if (s.max_blocks <= 256 * 8) SPECPV_TOPK(topk_fast_kernel<8>);
-    else if (s.max_blocks <= 256 * 16) SPECPV_TOPK(topk_fast_kernel<16>);
+#define SPECPV_TOPK(P, NT) \
+    hipLaunchKernelGGL((topk_fast_kernel<P, NT>), grid, dim3(NT), 0, st, scores, s.ctx_len, s.B, s.max_blocks, s.Hkv, a)
+    if (s.max_blocks <= 1024) SPECPV_TOPK(4, 256);
+    else if (s.max_blocks <= 2048) SPECPV_TOPK(4, 512);
+    else if (s.max_blocks <= 4096) SPECPV_TOPK(4, 1024);
+    else if (s.max_blocks <= 8192) SPECPV_TOPK(8, 1024);
+    else if (s.max_blocks <= 16384) SPECPV_TOPK(16, 1024);
     else
-        hipLaunchKernelGGL(topk_kernel, grid, block, 0, st, scores, s.ctx_len, s.B, s.max_blocks, s.Hkv, ns, nr, k, n_row,
+        hipLaunchKernelGGL(topk_kernel, grid, dim3(256), 0, st, scores, s.ctx_len, s.B, s.max_blocks, s.Hkv, ns, nr, k, n_row,
                            sel_idx, sel_count);
 #undef SPECPV_TOPK
     return hipGetLastError();

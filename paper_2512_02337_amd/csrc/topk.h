@@ -1,11 +1,16 @@
-// Selection of sink + retrieval + local blocks (Section 3.2) for lists of up to 256 * P blocks
+// Selection of sink + retrieval + local blocks (Section 3.2) for lists of up to NT * P blocks
 // (P <= 16), as a device function: the selection kernel calls it, and so does the last workgroup
 // of a (sequence, KV head) in the scoring kernel when the two run as one launch.
 //
-// The first 256 threads of the workgroup work: thread t owns the P consecutive blocks
+// The first NT threads of the workgroup work: thread t owns the P consecutive blocks
 // t*P .. t*P+P-1 and keeps their scores in registers, so that
-//   - the radix select reads memory once and only runs over the score bits in which the
-//     candidates differ (at most 4 passes of 8 bits, one barrier each);
+//   - memory is read once;
+//   - a first pass counts the candidates in 256 equal steps between the smallest and the largest
+//     score.  That spreads them over the bins (the leading float bits put most of them into a few
+//     exponents, and LDS atomics on one address go one after the other) and usually leaves a
+//     handful that share the threshold's step: up to 64 of those are ranked directly;
+//   - otherwise a radix select runs over the score bits in which the candidates differ (at most 4
+//     passes of 8 bits, one barrier each);
 //   - ties at the threshold score are broken towards the lower index by ranking the tied
 //     blocks in index order instead of four more radix passes over the index bits;
 //   - tie ranks and the ascending output positions come from one workgroup-wide prefix sum.
@@ -65,10 +70,45 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
 // per lane, for the keys that are no longer in the race (never read).
 struct TopkLds {
     __attribute__((aligned(16))) uint32_t hist[3][320];
-    __attribute__((aligned(16))) uint32_t wave_min[4];
-    __attribute__((aligned(16))) uint32_t wave_max[4];
-    __attribute__((aligned(16))) uint32_t wave_tot[4];
+    __attribute__((aligned(16))) uint32_t wave_min[16];
+    __attribute__((aligned(16))) uint32_t wave_max[16];
+    __attribute__((aligned(16))) uint32_t wave_tot[16];
+    uint32_t list[64];
+    uint32_t n_list;
 };
+
+// the score with these bits (the inverse of score_bits)
+__device__ __forceinline__ float bits_score(uint32_t k)
+{
+    return __uint_as_float((k & 0x80000000u) ? k ^ 0x80000000u : ~k);
+}
+
+// Every wavefront for itself: the threshold's digit in a histogram of 256 (lane l owns digits 4l .. 4l+3), the number of
+// keys above that digit and in it.  suf[x] = number of keys with digit >= 4l + x: exactly one (lane, x) has
+// suf[x] >= krem > suf[x + 1].
+struct Digit {
+    uint32_t digit;
+    int above, count;
+};
+__device__ __forceinline__ Digit threshold_digit(const uint32_t *hist, int krem, int lane)
+{
+    const uint4 h = *(const uint4 *)&hist[4 * lane];
+    const uint32_t mine = h.x + h.y + h.z + h.w;
+    const uint32_t pre = (uint32_t)wave_inclusive_scan((int)mine);
+    const uint32_t higher = (uint32_t)__builtin_amdgcn_readlane((int)pre, 63) - pre;   // keys with digit >= 4l + 4
+    const uint32_t s3 = higher + h.w, s2 = s3 + h.z, s1 = s2 + h.y, s0 = s1 + h.x;
+    const uint32_t kr = (uint32_t)krem;
+    const bool mine_has = s0 >= kr && higher < kr;
+    const int x = s3 >= kr ? 3 : (s2 >= kr ? 2 : (s1 >= kr ? 1 : 0));      // the largest x with suf[x] >= krem
+    const uint32_t above = x == 3 ? higher : (x == 2 ? s3 : (x == 1 ? s2 : s1));
+    const uint32_t count = x == 3 ? h.w : (x == 2 ? h.z : (x == 1 ? h.y : h.x));
+    const int owner = __builtin_ctzll(__ballot(mine_has));
+    Digit d;
+    d.digit = (uint32_t)(4 * owner + __builtin_amdgcn_readlane(x, owner));
+    d.above = __builtin_amdgcn_readlane((int)above, owner);
+    d.count = __builtin_amdgcn_readlane((int)count, owner);
+    return d;
+}
 
 // Every thread of the workgroup calls this (it holds workgroup barriers).  ACROSS: the scores
 // were stored by other workgroups of the same launch with agent-scope stores and are read the
@@ -78,17 +118,18 @@ struct TopkLds {
 // number of barriers, not the arithmetic: a pass of the radix select is one round of LDS atomics,
 // ONE barrier, and a suffix scan of the histogram that every wavefront does for itself; ties and
 // output positions come from ONE more workgroup-wide prefix sum.
-template <int P, bool ACROSS>
+template <int P, int NT, bool ACROSS>
 __device__ __forceinline__ void topk_fast_body(TopkLds &lds, const float *scores, const int32_t *ctx_len, int B,
                                                int max_blocks, int Hkv, int g, int b, const TopkArgs &a)
 {
+    constexpr int NW = NT / 64;   // 4, 8 or 16
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ns = a.ns, nr = a.nr, k = a.k, n_row = a.n_row;
     const int n_sel = ns + k + nr;
     const float *sc = scores + ((int64_t)b * Hkv + g) * max_blocks;
     int32_t *out = a.sel_idx + ((int64_t)b * Hkv + g) * n_row;
 
-    const int i0 = tid * P;   // threads past 256 start behind the last block: they keep nothing
+    const int i0 = tid * P;   // threads past NT start behind the last block: they keep nothing
     // the scores are requested before the context length is known (any block below max_blocks
     // is readable), so the two cold reads overlap
     float raw[P];
@@ -101,6 +142,7 @@ __device__ __forceinline__ void topk_fast_body(TopkLds &lds, const float *scores
             raw[j] = *p;
     }
     if (tid < 256) { lds.hist[0][tid] = 0; lds.hist[1][tid] = 0; }   // ahead of the first barrier below
+    if (tid == 0) lds.n_list = 0;
     const int L = ctx_len[b];
     int nb = L > 0 ? (L + B - 1) / B : 0;
     if (nb > max_blocks) nb = max_blocks;
@@ -127,17 +169,62 @@ __device__ __forceinline__ void topk_fast_body(TopkLds &lds, const float *scores
         // they differ are common to all keys and need no pass.
         kmin = wave_min_u32(kmin);
         kmax = wave_max_u32(kmax);
-        if (lane == 0 && wave < 4) { lds.wave_min[wave] = kmin; lds.wave_max[wave] = kmax; }
+        if (lane == 0 && wave < NW) { lds.wave_min[wave] = kmin; lds.wave_max[wave] = kmax; }
         __syncthreads();
         {
-            const uint4 mn = *(const uint4 *)lds.wave_min, mx = *(const uint4 *)lds.wave_max;
-            kmin = min(min(mn.x, mn.y), min(mn.z, mn.w));
-            kmax = max(max(mx.x, mx.y), max(mx.z, mx.w));
+#pragma unroll
+            for (int v = 0; v < NW; v += 4) {
+                const uint4 mn = *(const uint4 *)(lds.wave_min + v), mx = *(const uint4 *)(lds.wave_max + v);
+                kmin = min(min(kmin, min(mn.x, mn.y)), min(mn.z, mn.w));
+                kmax = max(max(kmax, max(mx.x, mx.y)), max(mx.z, mx.w));
+            }
         }
         const uint32_t diff = kmin ^ kmax;
         int top = diff ? 32 - __builtin_clz(diff) : 0;   // number of low bits that are not common to all keys
         prefix = top < 32 ? (kmax >> top) << top : 0u;
         int cur = 0;
+        // First pass in equal steps of the score: the step number never falls as the score grows, so it is a leading
+        // digit like any other.  (Left out where the range is no finite number, zero, or too small to divide by.)
+        const float fmin = bits_score(kmin), range = bits_score(kmax) - fmin, scale = 255.9f / range;
+        if (isfinite(fmin) && isfinite(range) && isfinite(scale) && range > 0.f) {
+            uint32_t dig[P];
+#pragma unroll
+            for (int j = 0; j < P; ++j) dig[j] = ((cand >> j) & 1u) ? min((uint32_t)((bits_score(key[j]) - fmin) * scale), 255u) : 256u + (uint32_t)lane;
+            if (wave < NW) {
+#pragma unroll
+                for (int j = 0; j < P; ++j) atomicAdd(&lds.hist[0][dig[j]], 1u);
+            }
+            __syncthreads();
+            const Digit d = threshold_digit(lds.hist[0], krem, lane);
+            krem -= d.above;
+#pragma unroll
+            for (int j = 0; j < P; ++j)
+                if (dig[j] != d.digit) live &= ~(1u << j);
+            cur = 1;
+            if (d.count <= 64) {
+                if (wave < NW) {
+#pragma unroll
+                    for (int j = 0; j < P; ++j)
+                        if ((live >> j) & 1u) lds.list[atomicAdd(&lds.n_list, 1u)] = key[j];
+                }
+                __syncthreads();
+                // every wavefront for itself: how many of the listed keys are greater, how many equal
+                const uint32_t own = lane < d.count ? lds.list[lane] : 0u;
+                int greater = 0, equal = 0;
+                for (int i = 0; i < d.count; ++i) {
+                    const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)own, i);
+                    greater += o > own ? 1 : 0;
+                    equal += o == own ? 1 : 0;
+                }
+                const int owner = __builtin_ctzll(__ballot(lane < d.count && greater < krem && greater + equal >= krem));
+                prefix = (uint32_t)__builtin_amdgcn_readlane((int)own, owner);
+                krem -= __builtin_amdgcn_readlane(greater, owner);
+#pragma unroll
+                for (int j = 0; j < P; ++j)
+                    if (key[j] != prefix) live &= ~(1u << j);
+                top = 0;   // all bits decided
+            }
+        }
         while (top > 0) {
             const int width = top < 8 ? top : 8, shift = top - width;
             const uint32_t mask = (1u << width) - 1u;
@@ -146,28 +233,16 @@ __device__ __forceinline__ void topk_fast_body(TopkLds &lds, const float *scores
             uint32_t dig[P];
 #pragma unroll
             for (int j = 0; j < P; ++j) dig[j] = (key[j] >> shift) & mask;
-            if (wave < 4) {
+            if (wave < NW) {
                 // no branch per key: a key that is out of the race counts in its lane's own spare entry
 #pragma unroll
                 for (int j = 0; j < P; ++j)
                     atomicAdd(&lds.hist[cur][((live >> j) & 1u) ? dig[j] : 256u + (uint32_t)lane], 1u);
             }
             __syncthreads();
-            // Every wavefront for itself: lane l owns digits 4l .. 4l+3; suf[x] = number of live keys with
-            // digit >= 4l + x.  Exactly one (lane, x) has suf[x] >= krem > suf[x + 1]: that digit is the
-            // threshold's, and suf[x + 1] keys lie above it.
-            const uint4 h = *(const uint4 *)&lds.hist[cur][4 * lane];
-            const uint32_t mine = h.x + h.y + h.z + h.w;
-            const uint32_t pre = (uint32_t)wave_inclusive_scan((int)mine);
-            const uint32_t higher = (uint32_t)__builtin_amdgcn_readlane((int)pre, 63) - pre;   // keys with digit >= 4l + 4
-            const uint32_t s3 = higher + h.w, s2 = s3 + h.z, s1 = s2 + h.y, s0 = s1 + h.x;
-            const uint32_t kr = (uint32_t)krem;
-            const bool mine_has = s0 >= kr && higher < kr;
-            const int x = s3 >= kr ? 3 : (s2 >= kr ? 2 : (s1 >= kr ? 1 : 0));      // the largest x with suf[x] >= krem
-            const uint32_t above = x == 3 ? higher : (x == 2 ? s3 : (x == 1 ? s2 : s1));
-            const int owner = __builtin_ctzll(__ballot(mine_has));
-            const uint32_t digit = (uint32_t)(4 * owner + __builtin_amdgcn_readlane(x, owner));
-            krem -= __builtin_amdgcn_readlane((int)above, owner);
+            const Digit d = threshold_digit(lds.hist[cur], krem, lane);
+            const uint32_t digit = d.digit;
+            krem -= d.above;
             prefix |= digit << shift;
 #pragma unroll
             for (int j = 0; j < P; ++j)
@@ -178,7 +253,7 @@ __device__ __forceinline__ void topk_fast_body(TopkLds &lds, const float *scores
     }
     // prefix is the k-th largest score key; the keys still live are the ones that tie with it, and krem
     // (>= 1) of those are kept, lowest indices first.  One prefix sum carries two counts: blocks that are
-    // kept whatever the ties (low half) and tied blocks (high half), both at most 4096.
+    // kept whatever the ties (low half) and tied blocks (high half), both at most 16384.
     uint32_t sure = 0;
 #pragma unroll
     for (int j = 0; j < P; ++j) {
@@ -190,16 +265,19 @@ __device__ __forceinline__ void topk_fast_body(TopkLds &lds, const float *scores
     const uint32_t tie = any_topk ? live : 0u;
     const uint32_t packed = (uint32_t)__popc(sure) | ((uint32_t)__popc(tie) << 16);
     const uint32_t inc = (uint32_t)wave_inclusive_scan((int)packed);
-    if (lane == 63 && wave < 4) lds.wave_tot[wave] = inc;
+    if (lane == 63 && wave < NW) lds.wave_tot[wave] = inc;
     __syncthreads();
     uint32_t before = inc - packed, total = 0;
     {
-        const uint4 wt = *(const uint4 *)lds.wave_tot;
-        const uint32_t w[4] = {wt.x, wt.y, wt.z, wt.w};
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            if (v < wave) before += w[v];
-            total += w[v];
+        for (int v0 = 0; v0 < NW; v0 += 4) {
+            const uint4 wt = *(const uint4 *)(lds.wave_tot + v0);
+            const uint32_t w[4] = {wt.x, wt.y, wt.z, wt.w};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                if (v0 + v < wave) before += w[v];
+                total += w[v];
+            }
         }
     }
     const int kr = krem;
