@@ -9,6 +9,7 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <exception>
 #include <initializer_list>
 #include <memory>
 #include <vector>
@@ -124,7 +125,7 @@ int64_t row_entries(const specpv_select_cfg *c) { return (int64_t)c->n_sink_bloc
 
 void *stream() { return (void *)c10::hip::getCurrentHIPStream().stream(); }
 
-// Enters the library without the interpreter's lock (as ctypes does).
+// Enters the library without the interpreter's lock (as ctypes does).  The C ABI throws nothing.
 template <typename F> PyObject *enter(F f)
 {
     int rc;
@@ -132,6 +133,20 @@ template <typename F> PyObject *enter(F f)
     rc = f();
     Py_END_ALLOW_THREADS
     return PyLong_FromLong(rc);
+}
+
+// What stands in the method table.  torch reports by C++ exceptions what a tensor cannot give (no storage under vmap or
+// while tracing, no GPU for a stream), and none may leave through the interpreter's frames: the call then goes to
+// binding.py like any other that is not taken here, and asking for the same thing there raises the Python error.
+typedef PyObject *(*Method)(PyObject *, PyObject *const *, Py_ssize_t);
+template <Method M> PyObject *guarded(PyObject *self, PyObject *const *a, Py_ssize_t n)
+{
+    try {
+        return M(self, a, n);
+    } catch (const std::exception &) {   // (not the unwinding of a thread that ends while the interpreter does)
+        PyErr_Clear();
+        Py_RETURN_NONE;
+    }
 }
 
 #define SPECPV_ARGS(N) \
@@ -350,7 +365,7 @@ PyObject *set_table(PyObject *, PyObject *const *a, Py_ssize_t n)   // the addre
     Py_RETURN_NONE;
 }
 
-#define SPECPV_METHOD(NAME) {#NAME, (PyCFunction)(void (*)(void))NAME, METH_FASTCALL, nullptr}
+#define SPECPV_METHOD(NAME) {#NAME, (PyCFunction)(void (*)(void))guarded<NAME>, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {SPECPV_METHOD(set_table), SPECPV_METHOD(summarize), SPECPV_METHOD(select),        SPECPV_METHOD(partial), SPECPV_METHOD(partial_static),
                          SPECPV_METHOD(refresh),   SPECPV_METHOD(gather),    SPECPV_METHOD(commit_layers), SPECPV_METHOD(commit),  {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", "The calls of binding.py without the Python work per call.", -1, methods, nullptr, nullptr, nullptr, nullptr};
