@@ -68,6 +68,15 @@ __device__ __forceinline__ float add_bf16x2(uint32_t p, float acc)
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p), ones, acc, false);
 }
+// x less the low / the high half of a packed bf16 pair that holds x rounded (the difference is exact): one instruction,
+// where widening the half and subtracting it are two.  The constants go through registers: as an immediate, (-1, 0) is
+// written as the inline constant -1.0, of which the instruction takes the other half.
+struct Bf16Halves {
+    uint32_t lo = 0x0000bf80u, hi = 0xbf800000u;   // (-1, 0), (0, -1)
+    __device__ __forceinline__ Bf16Halves() { asm("" : "+s"(lo), "+s"(hi)); }
+    __device__ __forceinline__ float sub_lo(float x, uint32_t p) const { return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p), __builtin_bit_cast(bf16x2, lo), x, false); }
+    __device__ __forceinline__ float sub_hi(float x, uint32_t p) const { return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p), __builtin_bit_cast(bf16x2, hi), x, false); }
+};
 
 // 16 bytes per lane from global memory straight into LDS (no registers involved):
 // lane l of the wavefront lands at lds_dst + 16*l.

@@ -858,10 +858,12 @@ template <int D> constexpr int group_lds(int rb)
 static_assert(group_lds<128>(10) <= 160 * 1024 && group_lds<128>(4) <= 80 * 1024 && group_lds<64>(8) <= 80 * 1024, "");
 // D = 64: half the LDS and half the operand registers, so two workgroups share a CU (four wavefronts per SIMD, 128
 // registers): at 64 channels a chunk has half the matrix work against the same softmax, and what counts is how many
-// wavefronts the vector ALU can choose from.  The weights enter the second product as two bf16 terms (16 bits) and the
-// partials are fp32 sums: the precision, and the range of V, of the vector-ALU kernel that this replaces.  Full pass
+// wavefronts the vector ALU can choose from.  The weights enter the second product as three bf16 terms, all 24 bits of
+// fp32, and the partials are fp32 sums: the precision, and the range of V, of the vector-ALU kernel that this replaces.
+// Rows whose exact result cancels to 0, error relative to sum |w v|, rms over 300 / 2048 / 16384 tokens: vector ALU
+// 2.3e-8 / 1.3e-8 / 6.5e-9, here 1.9e-8 / 1.1e-8 / 4.9e-9, with two terms (16 bits) 3.6e-7 / 1.4e-7 / 5.6e-8.  Full pass
 // over 15K + 30K tokens, 37 nodes at G = 4, 8 KV heads, token-major, with scoring and selection: 5845 us on the vector
-// ALU, 65 us here (53 us with the weights as one bf16 term and fp16 partials).
+// ALU, 62.4 us here (55.1 us with two terms; 67.4 us with three whose differences take a widening and a subtraction each).
 // SK: shares of the chunks of all (sequence, KV head) pairs instead of splits (Partials::stream): a workgroup goes through
 // the one to three pairs that its share touches, one after the other.
 template <int D, bool ALIGNED, int RB, bool SK>
@@ -1114,8 +1116,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     if (1 < nch) vm_stage[1] = issue(1, 1);
     uint2 v[4 * NT];
     uint4 pf0 = make_uint4(0u, 0u, 0u, 0u), pf1 = pf0;
-    uint4 pl0 = pf0, pl1 = pf0;   // 64 channels: what the rounding of the weights to bf16 left over, rounded in turn
-    auto pv = [&]() {
+    auto pv = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int ks2 = 0; ks2 < 2; ++ks2)
 #pragma unroll
@@ -1123,9 +1124,6 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
                 const uint2 lo = v[(ks2 * NT + j) * 2], hi = v[(ks2 * NT + j) * 2 + 1];
                 O[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)),
                                                                as_bf16x8(ks2 ? pf1 : pf0), O[j], 0, 0, 0);
-                if (D == 64)
-                    O[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)),
-                                                                   as_bf16x8(ks2 ? pl1 : pl0), O[j], 0, 0, 0);
             }
     };
     // three wavefronts per SIMD: operands in halves (16 registers at a time instead of 32)
@@ -1221,7 +1219,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
             }
         }
         const float m_use = m_ref == -INFINITY ? 0.f : m_ref;
-        uint32_t pk[8], pl[8];
+        uint32_t pk[8];
         float lsum = 0.f;
 #pragma unroll
         for (int x = 0; x < 16; x += 2) {
@@ -1229,21 +1227,34 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
             const float p1 = __builtin_amdgcn_exp2f(fmaf(S[x + 1], a.scale_log2, -m_use));
             pk[x >> 1] = pack_bf16x2(p0, p1);
             if (D == 64) {
-                pl[x >> 1] = pack_bf16x2(p0 - __uint_as_float(pk[x >> 1] << 16), p1 - __uint_as_float(pk[x >> 1] & 0xffff0000u));
+                S[x] = p0;
+                S[x + 1] = p1;
                 lsum += p0 + p1;
             } else {
                 lsum = add_bf16x2(pk[x >> 1], lsum);   // the sum runs over the rounded weights the MFMA sees
             }
         }
         l_run += lsum;
-        if (D == 64) {
-            pl0 = make_uint4(pl[0], pl[1], pl[2], pl[3]);
-            pl1 = make_uint4(pl[4], pl[5], pl[6], pl[7]);
-        }
         pf0 = make_uint4(pk[0], pk[1], pk[2], pk[3]);
         pf1 = make_uint4(pk[4], pk[5], pk[6], pk[7]);
         if constexpr (RB > 8) pv_halves(vread + HOFF, std::integral_constant<int, SOFF>{});
         else pv();
+        if constexpr (D == 64) {
+            // what the rounding of the weights left over, twice: each term takes eight bits more (the differences are exact)
+            const Bf16Halves halves;
+#pragma unroll
+            for (int term = 1; term < 3; ++term) {
+#pragma unroll
+                for (int x = 0; x < 16; x += 2) {
+                    S[x] = halves.sub_lo(S[x], pk[x >> 1]);
+                    S[x + 1] = halves.sub_hi(S[x + 1], pk[x >> 1]);
+                    pk[x >> 1] = pack_bf16x2(S[x], S[x + 1]);
+                }
+                pf0 = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+                pf1 = make_uint4(pk[4], pk[5], pk[6], pk[7]);
+                pv();
+            }
+        }
     };
     // Two chunks between two barriers.  At the barrier in front of chunks i0, i0 + 1 (ring half H) every
     // wavefront's requests have landed -- they were made a whole period ago, so the wait is for all of
