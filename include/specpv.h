@@ -124,7 +124,11 @@ typedef struct specpv_select_cfg {
  * those of the one-launch route of the selection (specpv_debug_set_select_route) which of them selects; a commit
  * with lists keeps its count of missing list entries there between its two launches.
  * Every call leaves them zero again, so one fill at
- * allocation is enough, whatever shapes use the workspace afterwards.  A call that is given
+ * allocation is enough, whatever shapes use the workspace afterwards.
+ * The size is what these descriptors' calls make best use of.  A smaller tree, fewer sequences or a shorter
+ * cache may ask for more than a larger one (their work is split further); their calls take a workspace that
+ * was sized for the larger one all the same, and split as far as it has room.  A call is refused
+ * (SPECPV_EWORKSPACE) only where the results of one split, or the scores it has to keep, do not fit.  A call that is given
  * words that are not zero computes garbage (it cannot notice). */
 size_t specpv_workspace_bytes(const specpv_kv *kv, const specpv_tree *tree, const specpv_select_cfg *cfg);
 

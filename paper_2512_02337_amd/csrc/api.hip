@@ -1,6 +1,7 @@
 // C ABI of libspecpv: argument validation, workspace layout, split planning and
 // the launch sequences of the four calls.  No kernels live here.
 #include <math.h>
+#include <stdint.h>
 #include <stdio.h>
 #include <string.h>
 
@@ -150,13 +151,28 @@ static int64_t first_splits(const Shape &s, int64_t chunks, int64_t cus)
     return chunks >= 32 * ns ? best_of((int64_t)s.batch * s.Hkv * parts, 1, at_most(chunks / 8)) : ns;
 }
 
+// Bytes of a partial row: O as fp16 (bf16 at 128 channels) or fp32, and the (m, l) pair.
+static bool half_partials(const Shape &s, int kind) { return kind != kAttnGeneric && s.D == 128; }
+static size_t part_row_bytes(const Shape &s, int kind)
+{
+    return (size_t)s.D * (half_partials(s, kind) ? sizeof(uint16_t) : sizeof(float)) + 2 * sizeof(float);
+}
+
 // Which kernel the context part of the attention runs on and how many KV splits it uses when
 // it covers n_blocks blocks per (sequence, KV head).  Host-only and deterministic in its
 // arguments, so specpv_workspace_bytes and the calls agree.  full: every block of sequences whose
 // lengths only the device knows (n_blocks is the most that any of them has).
-static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool full)
+// bytes: what the caller's workspace has.  A smaller tree may be worth more splits than a larger one, so a workspace that
+// was sized for the largest tree of a decode loop need not hold the plan of every smaller one: then the call takes the
+// splits that fit (one always does where the larger tree's plan did).
+static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool full, size_t bytes)
 {
     AttnPlan plan{1, !attn_ctx_mfma_supported(s, dtype) ? kAttnGeneric : (s.D == 64 ? kAttnGroup : kAttnSplit), 4, 0};
+    // partial rows that have room (Workspace), and splits
+    const size_t row_bytes = part_row_bytes(s, plan.kind), pair_rows = (size_t)s.M * s.G, fixed_bytes = kArriveBytes + 512;
+    const int64_t room_rows = bytes > fixed_bytes ? (int64_t)((bytes - fixed_bytes) / row_bytes) : 0;   // (< 2^63: a row has more than one byte)
+    const int64_t room_splits = room_rows / ((int64_t)s.batch * s.Hkv * (int64_t)pair_rows);
+    auto at_hand = [&](int64_t ns) { return ns <= room_splits ? ns : (room_splits > 1 ? room_splits : (int64_t)1); };
     // splits that give 4096 (row, split) pairs of 64 tokens or more each
     const int64_t rows = (int64_t)s.batch * s.Hq * s.M;
     auto few_splits = [&](int64_t tokens) {
@@ -198,7 +214,7 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             ns = want < most ? want : most;
             if (ns < few) ns = few;
         }
-        plan.nsplit = (int)static_room([&] { return few; }, ns);
+        plan.nsplit = (int)at_hand(static_room([&] { return few; }, ns));
     } else {
         const int64_t chunks = (tokens + 31) / 32;   // 32-token chunks per (sequence, KV head)
         const int parts = attn_group_parts(s);
@@ -209,7 +225,7 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             const int64_t slots = 2 * cus;
             int64_t most = chunks / 4 > 1 ? (chunks / 4 < 64 ? chunks / 4 : 64) : 1, best = -1;
             const int64_t few = few_splits(tokens);
-            most = static_room([&] { return few; }, most);
+            most = at_hand(static_room([&] { return few; }, most));
             // up to 1024 tokens: the few splits of the vector-ALU kernel are enough
             if (chunks <= 32 && most > few) most = few;
             for (int64_t c = 1; c <= most; ++c) {
@@ -227,7 +243,7 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             int64_t cand[16] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
             for (int k = 1; k <= 4; ++k) cand[11 + k] = k * cus / base;
             for (int64_t c : cand) {
-                if (c < 1 || c > 64) continue;
+                if (c < 1 || c > 64 || c > at_hand(c)) continue;
                 for (int tg = 2; tg <= 8; tg *= 2)
                     if (c * tg <= 2 * chunks) take(cost.tile(tg, c, cus), kAttnSplit, tg, c);
                 if (chunks >= 2 * c) take(cost.group(parts, blocks, c, cus), kAttnGroup, 4, c);
@@ -244,12 +260,12 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             const int64_t pairs = (int64_t)s.batch * s.Hkv, R = (int64_t)s.M * s.G;
             int64_t wgs = cus * (s.D == 64 ? 2 : 1) / parts;
             if (wgs > pairs * chunks / 8) wgs = pairs * chunks / 8;   // eight chunks or more each
-            if (wgs < 1) wgs = 1;
+            if (wgs > room_rows / R - pairs) wgs = room_rows / R - pairs;
             // the workspace of as many splits as hold that many slots
             const int64_t bytes = (wgs + pairs) * R * (s.D == 128 ? 2 * s.D + 8 : 4 * s.D + 8) + 512, slot = pairs * R * (4 * s.D + 8);
             const int64_t splits = (bytes + slot - 1) / slot > 1 ? (bytes + slot - 1) / slot - 1 : 1;
             const bool fits = (int64_t)kArriveBytes + bytes <= (int64_t)SPECPV_STATIC_SCRATCH_BYTES;
-            if (splits <= 64 && (fits || static_room([&] { return s.D == 64 ? few_splits(tokens) : first_splits(s, chunks, cus); }, 64) == 64)) {
+            if (wgs >= 1 && splits <= 64 && (fits || static_room([&] { return s.D == 64 ? few_splits(tokens) : first_splits(s, chunks, cus); }, 64) == 64)) {
                 plan.stream = (int)wgs;
                 plan.nsplit = (int)splits;
             }
@@ -258,34 +274,36 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
     return plan;
 }
 
-// Workspace layout: [arrival words, kArriveBytes, zero between calls][partial O][(m, l) pairs][scores],
-// the partial arrays sized for nsplit + 1 slots of fp32 (the context splits and the draft-tree segment).  fp16 partials
-// (bf16 at 128 channels) and the slots of Partials::stream take less: `tight_total` bytes, with the pairs right behind the
-// rows in use and no scores.
+// Workspace: [arrival words, kArriveBytes, zero between calls][partial O][(m, l) pairs], `need` bytes for the rows of a
+// plan.  `total` is what specpv_workspace_bytes promises: room for nsplit + 1 slots of fp32 (the context splits and the
+// draft-tree segment, as the single-kernel route lays them out: O, pairs at fused_ml) and, behind them, the scores.
+// Scores that a call keeps in the workspace stand behind the arrival words: they are written when the partials have been
+// read.
 struct Workspace {
     unsigned long long *arrive;
-    float *part_o, *part_ml, *scores, *tight_ml;
-    size_t total, tight_total;
+    float *part_o, *part_ml, *fused_ml, *scores;
+    size_t need, total, scores_need;
 };
 
-static Workspace layout_workspace(const Shape &s, int nsplit, int stream, void *base)
+static Workspace layout_workspace(const Shape &s, const AttnPlan &plan, void *base)
 {
     Workspace w;
-    const size_t slots = (size_t)nsplit + 1;
+    const size_t slots = (size_t)plan.nsplit + 1;
     const size_t po = align_up((size_t)s.batch * s.Hq * slots * s.M * s.D * sizeof(float));
     const size_t pm = align_up((size_t)s.batch * s.Hq * slots * s.M * 2 * sizeof(float));
     const size_t sc = align_up((size_t)s.batch * s.Hkv * s.max_blocks * sizeof(float));
     char *p = (char *)base;
     w.arrive = (unsigned long long *)p;
     w.part_o = (float *)(p + kArriveBytes);
-    w.part_ml = (float *)(p + kArriveBytes + po);
-    w.scores = (float *)(p + kArriveBytes + po + pm);
+    w.fused_ml = (float *)(p + kArriveBytes + po);
+    w.scores = (float *)(p + kArriveBytes);
     w.total = kArriveBytes + po + pm + sc;
-    const size_t R = (size_t)s.M * s.G, held = (size_t)s.batch * s.Hkv * R * nsplit;
-    const size_t rows = stream ? ((size_t)stream + (size_t)s.batch * s.Hkv) * R : held;   // partial rows in use
-    const size_t ho = align_up(rows * s.D * (s.D == 128 ? sizeof(uint16_t) : sizeof(float)));
-    w.tight_ml = (float *)(p + kArriveBytes + ho);
-    w.tight_total = kArriveBytes + ho + align_up(rows * 2 * sizeof(float));
+    w.scores_need = kArriveBytes + sc;
+    const size_t R = (size_t)s.M * s.G, pairs = (size_t)s.batch * s.Hkv;
+    const size_t rows = (plan.stream ? (size_t)plan.stream + pairs : pairs * plan.nsplit) * R;   // partial rows in use
+    const size_t ho = align_up(rows * (part_row_bytes(s, plan.kind) - 2 * sizeof(float)));
+    w.part_ml = (float *)(p + kArriveBytes + ho);
+    w.need = kArriveBytes + ho + align_up(rows * 2 * sizeof(float));
     return w;
 }
 
@@ -294,20 +312,16 @@ static Workspace layout_workspace(const Shape &s, int nsplit, int stream, void *
 static int g_route = 0;
 static unsigned long long *g_timeline = nullptr;   // where instrumented builds (-DSPECPV_TIMELINE) put their time stamps
 
-static int run_attention(const Shape &s_in, int dtype, const int32_t *sel_idx, const int32_t *sel_count,
-                         int n_sel, void *out, float *lse, void *workspace, size_t workspace_bytes,
-                         bool own_scratch, hipStream_t st)
+static int run_attention(const Shape &s_in, const AttnPlan &plan, int dtype, const int32_t *sel_idx, const int32_t *sel_count,
+                         int n_sel, void *out, float *lse, void *workspace, size_t workspace_bytes, hipStream_t st)
 {
-    const AttnPlan plan = plan_attention(s_in, dtype, sel_idx ? n_sel : s_in.max_blocks, !sel_idx);
     Shape s = s_in;
     // the matrix-core kernels take the partially verified tokens in front of the tree along with the cache
     // tokens (dense: every query row attends all of them); the vector-ALU kernel leaves them to the combine
     s.kctx = plan.kind != kAttnGeneric ? s.koff : 0;
     const int nsplit = plan.nsplit;
-    const Workspace w = layout_workspace(s, nsplit, plan.stream, workspace);
-    const bool half = plan.kind != kAttnGeneric && s.D == 128;   // fp16 partials
-    const bool tight = half || plan.stream;
-    if (!workspace || workspace_bytes < (own_scratch && tight ? w.tight_total : w.total)) return SPECPV_EWORKSPACE;
+    const Workspace w = layout_workspace(s, plan, workspace);
+    if (!workspace || workspace_bytes < w.need) return SPECPV_EWORKSPACE;
     const int route = __atomic_load_n(&g_route, __ATOMIC_RELAXED);
     // The single-kernel route is correct but measured slower than two launches (the last workgroup of a
     // tile reads all of the tile's partials through one CU): it runs only on request.
@@ -315,12 +329,12 @@ static int run_attention(const Shape &s_in, int dtype, const int32_t *sel_idx, c
                        (size_t)s.batch * s.Hq * 2 * sizeof(unsigned long long) <= kArriveBytes;
     hipError_t e;
     if (fused) {
-        Partials p{w.part_o, w.part_ml, nsplit + 1, 0, 0, nullptr};
+        Partials p{w.part_o, w.fused_ml, nsplit + 1, 0, 0, nullptr};
         const FusedArgs f{out, lse, w.arrive, route == 3 ? 1 : 0, g_timeline};
         e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, f, st);
         return e == hipSuccess ? SPECPV_OK : fail_hip(e);
     }
-    Partials p{w.part_o, tight ? w.tight_ml : w.part_ml, nsplit, half ? 1 : 0, plan.stream, g_timeline};
+    Partials p{w.part_o, w.part_ml, nsplit, half_partials(s, plan.kind) ? 1 : 0, plan.stream, g_timeline};
     const FusedArgs none{nullptr, nullptr, nullptr, 0, g_timeline};
     if (plan.kind == kAttnSplit) e = launch_attn_ctx_tile(s, sel_idx, sel_count, n_sel, p, plan.tg, g_timeline, st);
     else if (plan.kind != kAttnGeneric) e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, none, st);
@@ -392,13 +406,13 @@ size_t specpv_workspace_bytes(const specpv_kv *kv, const specpv_tree *tree, cons
     if (!tree) return kArriveBytes + align_up((size_t)kv->batch * sizeof(int32_t));
     if (check_tree(kv, tree, false) != SPECPV_OK) return 0;
     const Shape s = make_shape(kv, tree);
-    int nsplit = plan_attention(s, kv->dtype, s.max_blocks, true).nsplit;
+    AttnPlan plan = plan_attention(s, kv->dtype, s.max_blocks, true, SIZE_MAX);
     if (cfg) {
         const int64_t n_sel = (int64_t)cfg->n_sink_blocks + cfg->k_blocks + cfg->n_recent_blocks + cfg->n_extra_slots;
-        const int n2 = plan_attention(s, kv->dtype, n_sel, false).nsplit;
-        if (n2 > nsplit) nsplit = n2;
+        const AttnPlan partial = plan_attention(s, kv->dtype, n_sel, false, SIZE_MAX);
+        if (partial.nsplit > plan.nsplit) plan = partial;
     }
-    return layout_workspace(s, nsplit, 0, nullptr).total;
+    return layout_workspace(s, plan, nullptr).total;
 }
 
 int specpv_block_summarize(const specpv_kv *kv, int32_t blk_begin, int32_t blk_end,
@@ -445,8 +459,8 @@ int specpv_partial_verify_attn(const specpv_kv *kv, const specpv_tree *tree, con
     if (sel_idx && (!sel_count || n_sel < 0)) return SPECPV_EINVAL;
     if (sel_idx && n_sel > (1 << 24)) return SPECPV_ELIMIT;
     const Shape s = make_shape(kv, tree);
-    return run_attention(s, kv->dtype, sel_idx, sel_count, n_sel, out, lse, workspace, workspace_bytes, false,
-                         (hipStream_t)stream);
+    const AttnPlan plan = plan_attention(s, kv->dtype, sel_idx ? n_sel : s.max_blocks, !sel_idx, workspace_bytes);
+    return run_attention(s, plan, kv->dtype, sel_idx, sel_count, n_sel, out, lse, workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 int specpv_partial_verify_attn_static(const specpv_kv *kv, const specpv_tree *tree, const int32_t *sel_idx,
@@ -460,9 +474,9 @@ int specpv_partial_verify_attn_static(const specpv_kv *kv, const specpv_tree *tr
     if (sel_idx && n_sel > (1 << 24)) return SPECPV_ELIMIT;
     const Shape s = make_shape(kv, tree);
     // the same plan as specpv_partial_verify_attn; its partial results must fit the static array
-    const AttnPlan plan = plan_attention(s, kv->dtype, sel_idx ? n_sel : s.max_blocks, !sel_idx);
-    const Workspace w = layout_workspace(s, plan.nsplit, plan.stream, nullptr);
-    const size_t need = plan.stream || (plan.kind != kAttnGeneric && s.D == 128) ? w.tight_total : w.total;
+    const AttnPlan plan = plan_attention(s, kv->dtype, sel_idx ? n_sel : s.max_blocks, !sel_idx, SIZE_MAX);
+    const Workspace w = layout_workspace(s, plan, nullptr);
+    const size_t need = plan.stream || half_partials(s, plan.kind) ? w.need : w.total;
     if (need > (size_t)SPECPV_STATIC_SCRATCH_BYTES) {
         snprintf(g_hip_err, sizeof(g_hip_err), "static scratch: the call needs %zu bytes, the array holds %zu",
                  need, (size_t)SPECPV_STATIC_SCRATCH_BYTES);
@@ -471,8 +485,7 @@ int specpv_partial_verify_attn_static(const specpv_kv *kv, const specpv_tree *tr
     void *ws = nullptr;
     const hipError_t e = static_scratch(&ws);
     if (e != hipSuccess) return fail_hip(e);
-    return run_attention(s, kv->dtype, sel_idx, sel_count, n_sel, out, lse, ws, (size_t)SPECPV_STATIC_SCRATCH_BYTES, true,
-                         (hipStream_t)stream);
+    return run_attention(s, plan, kv->dtype, sel_idx, sel_count, n_sel, out, lse, ws, (size_t)SPECPV_STATIC_SCRATCH_BYTES, (hipStream_t)stream);
 }
 
 int specpv_full_verify_refresh(const specpv_kv *kv, const specpv_tree *tree, void *kmax, void *kmin,
@@ -487,15 +500,15 @@ int specpv_full_verify_refresh(const specpv_kv *kv, const specpv_tree *tree, voi
     if (!kmax || !kmin || !out || !sel_idx || !sel_count) return SPECPV_EINVAL;
     if (((uintptr_t)kmax | (uintptr_t)kmin | (uintptr_t)out) & 15) return SPECPV_EINVAL;
     const Shape s = make_shape(kv, tree);
-    const int nsplit = plan_attention(s, kv->dtype, s.max_blocks, true).nsplit;
-    const Workspace w = layout_workspace(s, nsplit, 0, workspace);
-    if (!workspace || workspace_bytes < w.total) return SPECPV_EWORKSPACE;
+    const AttnPlan plan = plan_attention(s, kv->dtype, s.max_blocks, true, workspace_bytes);
+    const Workspace w = layout_workspace(s, plan, workspace);
+    if (!workspace || workspace_bytes < w.need || (!scores && workspace_bytes < w.scores_need)) return SPECPV_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     if (stale_blk_begin >= 0) {
         const hipError_t e = launch_summarize(s, kv->dtype, stale_blk_begin, -1, kmax, kmin, st);
         if (e != hipSuccess) return fail_hip(e);
     }
-    rc = run_attention(s, kv->dtype, nullptr, nullptr, 0, out, lse, workspace, workspace_bytes, false, st);
+    rc = run_attention(s, plan, kv->dtype, nullptr, nullptr, 0, out, lse, workspace, workspace_bytes, st);
     if (rc != SPECPV_OK) return rc;
     return run_select(s, kv->dtype, tree, kmax, kmin, cfg, sel_idx, sel_count, scores ? scores : w.scores, w.arrive, st);
 }
