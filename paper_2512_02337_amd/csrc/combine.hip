@@ -59,7 +59,10 @@ template <int CPL> struct Chan<float, CPL> {
         }
     }
 };
-// acc + a.lo * b.lo + a.hi * b.hi for packed bf16 pairs
+// acc + a.lo * b.lo + a.hi * b.hi for packed bf16 pairs: half the instructions of widening both and two fp32 FMAs, and the
+// same error (products of bf16 are exact in fp32).  Log-sum-exp of the draft segment alone against 64 bits, 37 and 60
+// nodes, queries of 1 and 4 times unit variance: rms 2.2e-7 and 2.3e-7, at most 2.0e-6, at 64 channels, 2.3e-7 and
+// 2.4e-7, at most 2.6e-6, at 128, with either.
 __device__ __forceinline__ float dot_bf16x2(uint32_t a, uint32_t b, float acc)
 {
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;

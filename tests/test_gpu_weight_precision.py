@@ -1,4 +1,8 @@
-"""bf16 at 64 channels: the softmax weights reach the second product with all of fp32's bits.
+"""Precision of the sums against 64 bits.
+
+Draft segment: its log-sum-exp alone (no context), which is not rounded to 16 bits.
+
+bf16 at 64 channels: the softmax weights reach the second product with all of fp32's bits.
 
 The output's own rounding (2^-9) hides what the sums lose, so the values are chosen to cancel: the last tokens of every KV
 head share a key, and their values take away what all others sum up to, until the exact result is nearly 0 and the output
@@ -69,3 +73,34 @@ def test_weights_keep_their_bits(gpu_lib, lens, M, G, B, kept):
         rms = torch.stack(err).pow(2).mean().sqrt().item()
         say("   %d tokens, %d nodes, G = %d, B = %d: rms error / sum |w v| = 2^%.1f / sqrt(n)" % (T, M, G, B, math.log2(rms * math.sqrt(T))))
         assert rms <= 2.0 ** -19 / math.sqrt(T), (lens, M, G, B, kept, T, rms)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_draft_scores_are_fp32(gpu_lib, D, dtype):
+    """Products of 16-bit inputs are exact in fp32; what a sum of D of them loses is bounded here by eight roundings of the
+    sum of their magnitudes (the vector ALU's chain of eight per lane and four more across lanes: 1.2e-6 to 2.6e-6 at
+    most on these inputs, with either of its instructions for the products), and the log-sum-exp adds two of its own."""
+    sp, dev, Hkv, G, M = gpu_lib, "cuda", 2, 4, 60
+    g = torch.Generator(device=dev).manual_seed(D)
+    rn = lambda *s: torch.randn(s, generator=g, device=dev).to(dtype)
+    k, kd, vd, q = rn(1, Hkv, 64, D), rn(1, M, Hkv, D), rn(1, M, Hkv, D), 4 * rn(1, M, Hkv * G, D)
+    parent = [-1] + [(j - 1) // 2 for j in range(1, M)]
+    kv = sp.KV(k, k, torch.zeros((1,), dtype=torch.int32, device=dev), 64)
+    tree = sp.Tree(q, kd, vd, torch.tensor([parent], dtype=torch.int32, device=dev))
+    out, lse = torch.zeros_like(q), torch.zeros((1, M, Hkv * G), device=dev)
+    sp.specpv_partial_verify_attn(kv, tree, None, None, out, lse, torch.zeros((sp.specpv_workspace_bytes(kv, tree),), dtype=torch.uint8, device=dev))
+    torch.cuda.synchronize()
+    worst = 0.0
+    for j in range(M):
+        path, a = [], j
+        while a >= 0:
+            path.append(a)
+            a = parent[a]
+        for h in range(Hkv * G):
+            p = kd[0, path, h // G].double() * q[0, j, h].double() / math.sqrt(D)
+            want, mag = torch.logsumexp(p.sum(1), 0).item(), p.abs().sum(1).max().item()
+            err = abs(lse[0, j, h].item() - want)
+            worst = max(worst, err)
+            assert err <= 2.0 ** -24 * (8 * mag + 2 * (abs(want) + 1)), (D, dtype, j, h, err, mag, want)
+    say("   D = %d, %s: max error %.3g" % (D, dtype, worst))
