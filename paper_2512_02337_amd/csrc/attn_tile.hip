@@ -489,21 +489,18 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     SPECPV_STAMP(8);   // partial stores issued
     SPECPV_CLOCKS_END(timeline, 3072 + ((size_t)blockIdx.y * gridDim.x + blockIdx.x), first_chunk(C, sp * TG + TG) - first_chunk(C, sp * TG));
     // The combine kernel that follows reads the tree's parents and, one trip later, its K / V rows: nobody
-    // has touched those in this call yet.  Ask for them here, on the way out (nothing waits for the data):
-    // they are then in this XCD's L2, where that kernel's workgroups of the same KV head run.
+    // has touched those in this call yet.  Ask for them here, on the way out: they are then in this XCD's L2, where that
+    // kernel's workgroups of the same KV head run.  Eight lanes per node (four 64-byte pieces of its K row, four of its V
+    // row), so that one instruction of the wavefront covers eight nodes.  The loads are ones that the compiler knows and
+    // waits for: a load in flight whose register it takes to be free may land in whatever it puts there next, the address
+    // of another load for instance.
     if (wave == 0 && s.kd && s.vd && s.parent) {
         const int nw = (int)(gridDim.x >> 3) * nctx, w = tile * nctx + sp;
-        const char *base = (lane & 16) ? (const char *)s.vd : (const char *)s.kd;
-        for (int node = w; node < s.Mk; node += nw) {
-            uint32_t tmp;
-            const char *p = base + (((int64_t)b * s.Mk + node) * s.Hkv + g) * 256 + (lane & 15) * 16;
-            if (lane < 32) asm volatile("global_load_dword %0, %1, off" : "=v"(tmp) : "v"(p) : "memory");
-        }
-        if (w == 0 && lane < 2) {
-            uint32_t tmp;
-            const char *p = (const char *)(s.parent + (int64_t)b * s.Mk) + lane * 256;
-            if (lane * 64 < s.Mk) asm volatile("global_load_dword %0, %1, off" : "=v"(tmp) : "v"(p) : "memory");
-        }
+        const char *base = ((lane & 4) ? (const char *)s.vd : (const char *)s.kd) + ((int64_t)b * s.Mk * s.Hkv + g) * 256 + (lane & 3) * 64;
+        uint32_t seen = 0u;
+        if (w == 0 && lane < 8 && lane * 16 < s.Mk) seen = (uint32_t)s.parent[(int64_t)b * s.Mk + lane * 16];
+        for (int node = w + nw * (lane >> 3); node < s.Mk; node += 8 * nw) seen |= *(const uint32_t *)(base + (int64_t)node * s.Hkv * 256);
+        asm volatile("" ::"v"(seen));
     }
 }
 
