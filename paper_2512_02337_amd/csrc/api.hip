@@ -158,139 +158,6 @@ static size_t part_row_bytes(const Shape &s, int kind)
     return (size_t)s.D * (half_partials(s, kind) ? sizeof(uint16_t) : sizeof(float)) + 2 * sizeof(float);
 }
 
-// Which kernel the context part of the attention runs on and how many KV splits it uses when
-// it covers n_blocks blocks per (sequence, KV head).  Host-only and deterministic in its
-// arguments, so specpv_workspace_bytes and the calls agree.  full: every block of sequences whose
-// lengths only the device knows (n_blocks is the most that any of them has).
-// bytes: what the caller's workspace has.  A smaller tree may be worth more splits than a larger one, so a workspace that
-// was sized for the largest tree of a decode loop need not hold the plan of every smaller one: then the call takes the
-// splits that fit (one always does where the larger tree's plan did).
-static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool full, size_t bytes)
-{
-    AttnPlan plan{1, !attn_ctx_mfma_supported(s, dtype) ? kAttnGeneric : (s.D == 64 ? kAttnGroup : kAttnSplit), 4, 0};
-    // partial rows that have room (Workspace), and splits
-    const size_t row_bytes = part_row_bytes(s, plan.kind), pair_rows = (size_t)s.M * s.G, fixed_bytes = kArriveBytes + 512;
-    const int64_t room_rows = bytes > fixed_bytes ? (int64_t)((bytes - fixed_bytes) / row_bytes) : 0;   // (< 2^63: a row has more than one byte)
-    const int64_t room_splits = room_rows / ((int64_t)s.batch * s.Hkv * (int64_t)pair_rows);
-    auto at_hand = [&](int64_t ns) { return ns <= room_splits ? ns : (room_splits > 1 ? room_splits : (int64_t)1); };
-    // splits that give 4096 (row, split) pairs of 64 tokens or more each
-    const int64_t rows = (int64_t)s.batch * s.Hq * s.M;
-    auto few_splits = [&](int64_t tokens) {
-        int64_t ns = (4096 + rows - 1) / rows;
-        const int64_t chunks = (tokens + 63) / 64;
-        if (ns > chunks) ns = chunks;
-        if (ns > 64) ns = 64;
-        return ns < 1 ? (int64_t)1 : ns;
-    };
-    // (a list may have room for more blocks than there are)
-    const int64_t tokens = (n_blocks < s.max_blocks ? n_blocks : (int64_t)s.max_blocks) * s.B;
-    if (tokens <= 0) return plan;
-    // what specpv_partial_verify_attn_static took with the splits of fp32 partials that a call had at first must fit its
-    // array with more of them: no more splits than have room, where those few have
-    auto static_room = [&](auto few_of, int64_t ns) {
-        const bool half = plan.kind != kAttnGeneric && s.D == 128;
-        const int64_t slot = rows * (s.D + 2) * (int64_t)sizeof(float), bytes = half ? rows * (2 * s.D + 8) : slot;
-        const int64_t fixed = (int64_t)kArriveBytes + 1024;
-        const int64_t room = ((int64_t)SPECPV_STATIC_SCRATCH_BYTES - fixed) / bytes - (half ? 0 : 1);
-        if (ns <= room || room < 1) return ns;
-        const bool few_fit = fixed + slot * (few_of() + 1) + (int64_t)s.batch * s.Hkv * s.max_blocks * (int64_t)sizeof(float) <= (int64_t)SPECPV_STATIC_SCRATCH_BYTES;
-        return few_fit ? room : ns;
-    };
-    const int64_t cus = device_cu_count();
-    if (plan.kind == kAttnGeneric) {
-        // two wavefronts of 32 rows per SIMD, 64 tokens or more each (the few splits up to 1024 tokens, and half that many
-        // tokens each for the shortest ranges, whose time is one wavefront's chain)
-        const int64_t few = few_splits(tokens);
-        int64_t ns = few;
-        if (tokens > 1024) {
-            const int64_t waves = (int64_t)((s.G * s.M + 31) / 32) * s.batch * s.Hkv;
-            ns = (8 * cus + waves - 1) / waves;
-            if (ns > tokens / 64) ns = tokens / 64;
-            if (ns > 64) ns = 64;
-            if (ns < few) ns = few;
-        } else if (tokens <= 512) {
-            const int64_t most = (tokens + 31) / 32 < 8 ? (tokens + 31) / 32 : 8;
-            const int64_t want = (4096 + rows - 1) / rows;
-            ns = want < most ? want : most;
-            if (ns < few) ns = few;
-        }
-        plan.nsplit = (int)at_hand(static_room([&] { return few; }, ns));
-    } else {
-        const int64_t chunks = (tokens + 31) / 32;   // 32-token chunks per (sequence, KV head)
-        const int parts = attn_group_parts(s);
-        const int64_t base = (int64_t)s.batch * s.Hkv * parts;   // group kernel: workgroups per split
-        int64_t ns = 1;
-        if (s.D == 64) {
-            // the group kernel; two workgroups share a CU, four chunks or more per split
-            const int64_t slots = 2 * cus;
-            int64_t most = chunks / 4 > 1 ? (chunks / 4 < 64 ? chunks / 4 : 64) : 1, best = -1;
-            const int64_t few = few_splits(tokens);
-            most = at_hand(static_room([&] { return few; }, most));
-            // up to 1024 tokens: the few splits of the vector-ALU kernel are enough
-            if (chunks <= 32 && most > few) most = few;
-            for (int64_t c = 1; c <= most; ++c) {
-                const int64_t cost = (base * c + slots - 1) / slots * ((chunks + c - 1) / c * 8 + 10) + c;
-                if (best < 0 || cost < best) { best = cost; ns = c; }
-            }
-        } else {
-            const AttnCost cost(s, chunks);
-            const int blocks = attn_group_blocks(s);
-            // AttnCost takes every sequence to be as long as the longest.  The group kernel, below, evens out the lengths of
-            // a full pass; the tile kernel, which a few nodes may be faster with, does not.  24 nodes at G = 4, 16 sequences
-            // of 16K (512 chunks), 8 KV heads, tile kernel against shares: equal lengths 190 / 210 us, 1/16 to 16/16 of it
-            // 152 / 127, one long and fifteen short ones 141 / 50; four sequences of 8K (256 chunks): 35 / 39, 32 / 35, 30 / 28.
-            const bool uneven = full && s.batch > 1 && chunks > 256;
-            double best = -1.0;
-            auto take = [&](double us, int kind, int tg, int64_t c) {
-                if (best < 0.0 || us < best) { best = us; plan.kind = kind; plan.tg = tg; ns = c; }
-            };
-            // split counts that divide evenly, those that the combine kernel takes in one go, and those that fill the chip
-            int64_t cand[16] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
-            for (int k = 1; k <= 4; ++k) cand[11 + k] = k * cus / base;
-            for (int64_t c : cand) {
-                if (c < 1 || c > 64 || c > at_hand(c)) continue;
-                for (int tg = 2; tg <= 8; tg *= 2)
-                    if (c * tg <= 2 * chunks && !uneven) take(cost.tile(tg, c, cus), kAttnSplit, tg, c);
-                if (chunks >= 2 * c) take(cost.group(parts, blocks, c, cus), kAttnGroup, 4, c);
-            }
-            ns = static_room([&] { return first_splits(s, chunks, cus); }, ns);
-        }
-        plan.nsplit = (int)ns;
-        // The sequences of a batch may differ in length, and the lengths live on the device: for a full pass the group
-        // kernel's workgroups take equal shares of all chunks.  (Before, four times as many splits as fill the chip evened
-        // that out, at the price of as many partials: full pass over 32K + 64K + 96K + 128K tokens at G = 5, 64 nodes:
-        // attention 510 us and combine 51 us with the splits, 525 and 15 us with the shares.)  Up to 1024 tokens there is
-        // nothing to even out.
-        if (full && s.batch > 1 && s.batch <= 64 && plan.kind == kAttnGroup && chunks > 32 && (int64_t)s.batch * s.Hkv * chunks < ((int64_t)1 << 30)) {
-            const int64_t pairs = (int64_t)s.batch * s.Hkv, R = (int64_t)s.M * s.G;
-            int64_t wgs = cus * (s.D == 64 ? 2 : 1) / parts;
-            if (wgs > pairs * chunks / 8) wgs = pairs * chunks / 8;   // eight chunks or more each
-            if (wgs > room_rows / R - pairs) wgs = room_rows / R - pairs;
-            // the workspace of as many splits as hold that many slots
-            const int64_t bytes = (wgs + pairs) * R * (s.D == 128 ? 2 * s.D + 8 : 4 * s.D + 8) + 512, slot = pairs * R * (4 * s.D + 8);
-            const int64_t splits = (bytes + slot - 1) / slot > 1 ? (bytes + slot - 1) / slot - 1 : 1;
-            const bool fits = (int64_t)kArriveBytes + bytes <= (int64_t)SPECPV_STATIC_SCRATCH_BYTES;
-            if (wgs >= 1 && splits <= 64 && (fits || static_room([&] { return s.D == 64 ? few_splits(tokens) : first_splits(s, chunks, cus); }, 64) == 64)) {
-                plan.stream = (int)wgs;
-                plan.nsplit = (int)splits;
-            }
-        }
-        // ... and where there are no shares (more than 64 sequences, a workspace without room for the slots), about eight
-        // workgroups per CU, 64 chunks or more each, for the hardware to deal out.  100 sequences of 16K, 4 KV heads, 60
-        // nodes at G = 4, with the model's three splits / with six: equal lengths 1090 / 1050 us, 1/100 to 100/100 of it
-        // 580 / 580, one long to fifteen short ones 310 / 255; 128 of 16K, 2 KV heads, 24 nodes, one split / eight:
-        // 459 / 380, 354 / 233, 345 / 115.
-        if (full && s.batch > 1 && plan.kind == kAttnGroup && !plan.stream) {
-            int64_t c = (8 * cus + base - 1) / base;
-            if (c > 64) c = 64;
-            while (c > ns && (chunks + c - 1) / c < 64) --c;
-            c = at_hand(static_room([&] { return s.D == 64 ? few_splits(tokens) : first_splits(s, chunks, cus); }, c));
-            if (c > ns) plan.nsplit = (int)c;
-        }
-    }
-    return plan;
-}
-
 // Workspace: [arrival words, kArriveBytes, zero between calls][partial O][(m, l) pairs], `need` bytes for the rows of a
 // plan.  `total` is what specpv_workspace_bytes promises: room for nsplit + 1 slots of fp32 (the context splits and the
 // draft-tree segment, as the single-kernel route lays them out: O, pairs at fused_ml) and, behind them, the scores.
@@ -322,6 +189,163 @@ static Workspace layout_workspace(const Shape &s, const AttnPlan &plan, void *ba
     w.part_ml = (float *)(p + kArriveBytes + ho);
     w.need = kArriveBytes + ho + align_up(rows * 2 * sizeof(float));
     return w;
+}
+
+// What specpv_partial_verify_attn_static asks of its array.
+static size_t static_need(const Shape &s, const AttnPlan &plan)
+{
+    const Workspace w = layout_workspace(s, plan, nullptr);
+    return plan.stream || half_partials(s, plan.kind) ? w.need : w.total;
+}
+
+// Which kernel the context part of the attention runs on and how many KV splits it uses when
+// it covers n_blocks blocks per (sequence, KV head).  Host-only and deterministic in its
+// arguments, so specpv_workspace_bytes and the calls agree.  full: every block of sequences whose
+// lengths only the device knows (n_blocks is the most that any of them has).
+// bytes: what the caller's workspace has.  A smaller tree may be worth more splits than a larger one, so a workspace that
+// was sized for the largest tree of a decode loop need not hold the plan of every smaller one: then the call takes the
+// splits that fit (one always does where the larger tree's plan did).
+static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool full, size_t bytes)
+{
+    AttnPlan plan{1, !attn_ctx_mfma_supported(s, dtype) ? kAttnGeneric : (s.D == 64 ? kAttnGroup : kAttnSplit), 4, 0};
+    // partial rows that have room (Workspace), and splits
+    const size_t row_bytes = part_row_bytes(s, plan.kind), pair_rows = (size_t)s.M * s.G, fixed_bytes = kArriveBytes + 512;
+    const int64_t room_rows = bytes > fixed_bytes ? (int64_t)((bytes - fixed_bytes) / row_bytes) : 0;   // (< 2^63: a row has more than one byte)
+    const int64_t room_splits = room_rows / ((int64_t)s.batch * s.Hkv * (int64_t)pair_rows);
+    auto at_hand = [&](int64_t ns) { return ns <= room_splits ? ns : (room_splits > 1 ? room_splits : (int64_t)1); };
+    // splits that give 4096 (row, split) pairs of 64 tokens or more each
+    const int64_t rows = (int64_t)s.batch * s.Hq * s.M;
+    auto few_splits = [&](int64_t tokens) {
+        int64_t ns = (4096 + rows - 1) / rows;
+        const int64_t chunks = (tokens + 63) / 64;
+        if (ns > chunks) ns = chunks;
+        if (ns > 64) ns = 64;
+        return ns < 1 ? (int64_t)1 : ns;
+    };
+    // (a list may have room for more blocks than there are)
+    const int64_t tokens = (n_blocks < s.max_blocks ? n_blocks : (int64_t)s.max_blocks) * s.B;
+    if (tokens <= 0) return plan;
+    // what specpv_partial_verify_attn_static took with the splits of fp32 partials that a call had at first must fit its
+    // array with more of them: no more splits than have room, where those few have
+    const int64_t static_slot = rows * (s.D + 2) * (int64_t)sizeof(float), static_fixed = (int64_t)kArriveBytes + 1024;
+    auto static_splits = [&]() {
+        const bool half = half_partials(s, plan.kind);
+        return ((int64_t)SPECPV_STATIC_SCRATCH_BYTES - static_fixed) / (half ? rows * (2 * s.D + 8) : static_slot) - (half ? 0 : 1);
+    };
+    auto static_room = [&](auto few_of, int64_t ns) {
+        const int64_t room = static_splits();
+        if (ns <= room || room < 1) return ns;
+        const bool few_fit = static_fixed + static_slot * (few_of() + 1) + (int64_t)s.batch * s.Hkv * s.max_blocks * (int64_t)sizeof(float) <= (int64_t)SPECPV_STATIC_SCRATCH_BYTES;
+        return few_fit ? room : ns;
+    };
+    const int64_t cus = device_cu_count();
+    if (plan.kind == kAttnGeneric) {
+        // two wavefronts of 32 rows per SIMD, 64 tokens or more each (the few splits up to 1024 tokens, and half that many
+        // tokens each for the shortest ranges, whose time is one wavefront's chain)
+        const int64_t few = few_splits(tokens);
+        int64_t ns = few;
+        if (tokens > 1024) {
+            const int64_t waves = (int64_t)((s.G * s.M + 31) / 32) * s.batch * s.Hkv;
+            ns = (8 * cus + waves - 1) / waves;
+            if (ns > tokens / 64) ns = tokens / 64;
+            if (ns > 64) ns = 64;
+            if (ns < few) ns = few;
+        } else if (tokens <= 512) {
+            const int64_t most = (tokens + 31) / 32 < 8 ? (tokens + 31) / 32 : 8;
+            const int64_t want = (4096 + rows - 1) / rows;
+            ns = want < most ? want : most;
+            if (ns < few) ns = few;
+        }
+        plan.nsplit = (int)at_hand(static_room([&] { return few; }, ns));
+    } else {
+        const int64_t chunks = (tokens + 31) / 32;   // 32-token chunks per (sequence, KV head)
+        const int parts = attn_group_parts(s);
+        const int64_t base = (int64_t)s.batch * s.Hkv * parts;   // group kernel: workgroups per split
+        int64_t ns = 1;
+        bool keep_static = false;
+        if (s.D == 64) {
+            // the group kernel; two workgroups share a CU, four chunks or more per split
+            const int64_t slots = 2 * cus;
+            int64_t most = chunks / 4 > 1 ? (chunks / 4 < 64 ? chunks / 4 : 64) : 1, best = -1;
+            const int64_t few = few_splits(tokens);
+            most = at_hand(static_room([&] { return few; }, most));
+            // up to 1024 tokens: the few splits of the vector-ALU kernel are enough
+            if (chunks <= 32 && most > few) most = few;
+            for (int64_t c = 1; c <= most; ++c) {
+                const int64_t cost = (base * c + slots - 1) / slots * ((chunks + c - 1) / c * 8 + 10) + c;
+                if (best < 0 || cost < best) { best = cost; ns = c; }
+            }
+        } else {
+            const AttnCost cost(s, chunks);
+            const int blocks = attn_group_blocks(s);
+            // AttnCost takes every sequence to be as long as the longest.  The group kernel, below, evens out the lengths of
+            // a full pass; the tile kernel, which a few nodes may be faster with, does not.  24 nodes at G = 4, 16 sequences
+            // of 16K (512 chunks), 8 KV heads, tile kernel against shares: equal lengths 190 / 210 us, 1/16 to 16/16 of it
+            // 152 / 127, one long and fifteen short ones 141 / 50; four sequences of 8K (256 chunks): 35 / 39, 32 / 35, 30 / 28.
+            const bool uneven = full && s.batch > 1 && chunks > 256;
+            double best = -1.0, best_tile = -1.0;
+            int64_t ns_tile = 1;
+            auto take = [&](double us, int kind, int tg, int64_t c) {
+                if (uneven && kind == kAttnSplit) {
+                    if (best_tile < 0.0 || us < best_tile) { best_tile = us; ns_tile = c; }
+                } else if (best < 0.0 || us < best) {
+                    best = us; plan.kind = kind; plan.tg = tg; ns = c;
+                }
+            };
+            // split counts that divide evenly, those that the combine kernel takes in one go, and those that fill the chip
+            int64_t cand[16] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
+            for (int k = 1; k <= 4; ++k) cand[11 + k] = k * cus / base;
+            for (int64_t c : cand) {
+                if (c < 1 || c > 64 || c > at_hand(c)) continue;
+                for (int tg = 2; tg <= 8; tg *= 2)
+                    if (c * tg <= 2 * chunks) take(cost.tile(tg, c, cus), kAttnSplit, tg, c);
+                if (chunks >= 2 * c) take(cost.group(parts, blocks, c, cus), kAttnGroup, 4, c);
+            }
+            ns = static_room([&] { return first_splits(s, chunks, cus); }, ns);
+            // (where the tile kernel would have been taken and its partials fit the static array, the group kernel's do too)
+            keep_static = best_tile >= 0.0 && best_tile < best && static_room([&] { return first_splits(s, chunks, cus); }, ns_tile) <= static_splits();
+            if (keep_static && ns > static_splits()) ns = static_splits();
+        }
+        plan.nsplit = (int)ns;
+        // The sequences of a batch may differ in length, and the lengths live on the device: for a full pass the group
+        // kernel's workgroups take equal shares of all chunks.  (Before, four times as many splits as fill the chip evened
+        // that out, at the price of as many partials: full pass over 32K + 64K + 96K + 128K tokens at G = 5, 64 nodes:
+        // attention 510 us and combine 51 us with the splits, 525 and 15 us with the shares.)  Up to 1024 tokens there is
+        // nothing to even out.
+        if (full && s.batch > 1 && s.batch <= 64 && plan.kind == kAttnGroup && chunks > 32 && (int64_t)s.batch * s.Hkv * chunks < ((int64_t)1 << 30)) {
+            const int64_t pairs = (int64_t)s.batch * s.Hkv, R = (int64_t)s.M * s.G;
+            int64_t wgs = cus * (s.D == 64 ? 2 : 1) / parts;
+            if (wgs > pairs * chunks / 8) wgs = pairs * chunks / 8;   // eight chunks or more each
+            if (wgs < 1) wgs = 1;
+            const int64_t static_slots = ((int64_t)SPECPV_STATIC_SCRATCH_BYTES - static_fixed) / (R * (int64_t)row_bytes) - pairs;
+            if (keep_static && wgs > static_slots && static_slots >= wgs / 2) wgs = static_slots;
+            // the workspace of as many splits as hold that many slots
+            const int64_t bytes = (wgs + pairs) * R * (int64_t)row_bytes + 512, slot = pairs * R * (4 * s.D + 8);
+            const int64_t splits = (bytes + slot - 1) / slot > 1 ? (bytes + slot - 1) / slot - 1 : 1;
+            const bool fits = (int64_t)kArriveBytes + bytes <= (int64_t)SPECPV_STATIC_SCRATCH_BYTES;
+            const int64_t at_most = room_rows / R - pairs;   // ... that the caller's has room for
+            if (at_most >= 1 && splits <= 64 && (fits || (!keep_static && static_room([&] { return s.D == 64 ? few_splits(tokens) : first_splits(s, chunks, cus); }, 64) == 64))) {
+                plan.stream = (int)(wgs < at_most ? wgs : at_most);
+                plan.nsplit = (int)splits;
+            }
+        }
+        // ... and for more sequences than the shares are worked out for, about eight workgroups per CU, 64 chunks or more
+        // each, for the hardware to deal out.  100 sequences of 16K, 4 KV heads, 60 nodes at G = 4, with the model's three
+        // splits / with six: equal lengths 1090 / 1050 us, 1/100 to 100/100 of it 580 / 580, one long to fifteen short ones
+        // 310 / 255; 128 of 16K, 2 KV heads, 24 nodes, one split / eight: 459 / 380, 354 / 233, 345 / 115.
+        if (full && s.batch > 64 && plan.kind == kAttnGroup) {
+            int64_t c = (8 * cus + base - 1) / base;
+            if (c > 64) c = 64;
+            while (c > ns && (chunks + c - 1) / c < 64) --c;
+            // (what fits the static array still does)
+            auto in_static = [&](int64_t n) { return static_need(s, AttnPlan{(int)n, plan.kind, plan.tg, 0}) <= (size_t)SPECPV_STATIC_SCRATCH_BYTES; };
+            if (in_static(ns))
+                while (c > ns && !in_static(c)) --c;
+            c = at_hand(c);
+            if (c > ns) plan.nsplit = (int)c;
+        }
+    }
+    return plan;
 }
 
 // Process-wide choice of how specpv_partial_verify_attn runs shapes that the eight-wavefront kernel
@@ -492,8 +516,7 @@ int specpv_partial_verify_attn_static(const specpv_kv *kv, const specpv_tree *tr
     const Shape s = make_shape(kv, tree);
     // the same plan as specpv_partial_verify_attn; its partial results must fit the static array
     const AttnPlan plan = plan_attention(s, kv->dtype, sel_idx ? n_sel : s.max_blocks, !sel_idx, SIZE_MAX);
-    const Workspace w = layout_workspace(s, plan, nullptr);
-    const size_t need = plan.stream || half_partials(s, plan.kind) ? w.need : w.total;
+    const size_t need = static_need(s, plan);
     if (need > (size_t)SPECPV_STATIC_SCRATCH_BYTES) {
         snprintf(g_hip_err, sizeof(g_hip_err), "static scratch: the call needs %zu bytes, the array holds %zu",
                  need, (size_t)SPECPV_STATIC_SCRATCH_BYTES);

@@ -67,6 +67,18 @@ def test_any_smaller_shape_fits():
     assert _calls(kv, tree, _cfg(), one - 256, 0) == (EWORKSPACE,) * 3
 
 
+@no_gpu
+@pytest.mark.parametrize("Hkv,G,D,B,nb,batch,M", [(1, 4, 128, 64, 261, 9, 60), (8, 1, 128, 64, 775, 65, 18), (4, 4, 128, 7, 1735, 2, 60),
+                                                  (1, 4, 128, 64, 236, 9, 60), (1, 1, 64, 7, 7228, 100, 60), (2, 1, 64, 32, 6242, 100, 60)])
+def test_full_passes_that_fit_the_static_array(Hkv, G, D, B, nb, batch, M):
+    """Long full passes over batches whose partials fit the library's own array with the splits of equally long
+    sequences: what is done about uneven lengths does not take them beyond it."""
+    lib, vp = specpv.load(), ctypes.c_void_p
+    rc = lib.specpv_partial_verify_attn_static(ctypes.byref(_shape(Hkv, G, nb, B, D, 1, batch)), ctypes.byref(_tree(M=M, n_q_heads=Hkv * G)),
+                                               None, None, 0, vp(0x300), None, None)
+    assert rc == -4, rc   # as far as the first launch; -3: the array is too small
+
+
 SHAPE = dict(Hq=16, Hkv=2, D=128, dtype="bf16", B=64, M=40, tree="bounded", ns=1, nr=4, k=27, beta=1.5, layers=1, name="reuse")
 
 
