@@ -55,6 +55,41 @@ struct MfmaArgs {
     FastDiv div_nsplit, div_hkv, div_B, div_W, div_M;
 };
 
+// Which cache rows the 32-token chunks of one (sequence, KV head) cover: chunk c holds tokens 32 c .. 32 c + 31 of the kept
+// blocks, in the order of the list (sel == nullptr: of all blocks).
+struct ChunkRows {
+    const int32_t *sel;
+    FastDiv div_B;
+    int B, nb, L;    // block size, blocks and tokens of the sequence
+    uint32_t T;      // 32 * chunks, or less: tokens of the kept blocks
+    // B % 32 == 0: a chunk lies inside one block, so its 32 rows are consecutive.  r >= 0: all 32 rows r .. r + 31 are valid
+    // tokens (the common case, handled without any further test); -1: no valid token; -2 - r: rows from r on, cut off by
+    // the context length.  blk: the list entry of slot, the block that token p0 of the list lies in.
+    __device__ __forceinline__ int encode(int blk, uint32_t p0, uint32_t slot) const
+    {
+        if (blk < 0 || blk >= nb) return -1;
+        const int r = blk * B + (int)(p0 - slot * (uint32_t)B);
+        return r >= L ? -1 : (r + 32 > L ? -2 - r : r);
+    }
+    __device__ __forceinline__ int first_row(uint32_t c) const   // c: a chunk of the list
+    {
+        const uint32_t p0 = c * 32u;   // < T: the slot below is < count
+        const uint32_t slot = div_B.div(p0);
+        return encode(sel ? sel[slot] : (int)slot, p0, slot);
+    }
+    // any block size: the row of token n of chunk c, or -1
+    __device__ __forceinline__ int row(uint32_t c, int n) const
+    {
+        const uint32_t p = c * 32u + (uint32_t)n;
+        if (p >= T) return -1;
+        const uint32_t slot = div_B.div(p);
+        const int blk = sel ? sel[slot] : (int)slot;
+        if (blk < 0 || blk >= nb) return -1;
+        const int tok = blk * B + (int)(p - slot * (uint32_t)B);
+        return tok < L ? tok : -1;
+    }
+};
+
 __device__ __forceinline__ bf16x8 as_bf16x8(const uint4 &u) { return __builtin_bit_cast(bf16x8, u); }
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
@@ -237,6 +272,70 @@ __device__ __forceinline__ float sum_xor32(float x)
 {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// One 32-token chunk against a row block of 32 query rows, operands in registers: S^T = K . Q^T, the running maximum and
+// sum of each row, O^T += V^T . P^T.  kf: K operands of the eight k-steps; v: V operands (lds_read_v); qf: the query rows;
+// vmask: which of the 32 tokens count; m_ref, l_run: reference maximum and sum of row lane & 31 (l_run over this lane's
+// half of the tokens).
+__device__ __forceinline__ void attend_chunk(const uint4 (&kf)[8], const uint2 (&v)[16], const bf16x8 (&qf)[8], uint32_t vmask, int kg,
+                                             float scale_log2, f32x16 (&O)[4], float &m_ref, float &l_run)
+{
+    f32x16 S;
+#pragma unroll
+    for (int x = 0; x < 16; ++x) S[x] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks)
+        S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[ks]), qf[ks], S, 0, 0, 0);
+
+    if (vmask != 0xffffffffu) {
+        int kg_o = kg;   // (rare: nothing of it is kept in registers across the caller's loop)
+        asm volatile("" : "+v"(kg_o));
+        const uint32_t mine = vmask >> (kg_o * 4);
+#pragma unroll
+        for (int x = 0; x < 16; ++x)
+            if (!((mine >> ((x >> 2) * 8 + (x & 3))) & 1u)) S[x] = -INFINITY;
+    }
+    float mx = fmaxf(S[0], S[1]);
+#pragma unroll
+    for (int x = 2; x < 16; x += 2) mx = fmaxf(fmaxf(mx, S[x]), S[x + 1]);
+    mx *= scale_log2;
+    // the reference max only moves when the true max gets more than 2^slack ahead (tested on each lane's half of
+    // the chunk's tokens; the row's maximum is formed behind the branch -- in the group kernel the same change
+    // measured 3 % slower, so it keeps the exchange in front)
+    if (__any(mx > m_ref + kRescaleSlack)) {
+        mx = max_xor32(mx);
+        const float m_new = mx > m_ref + kRescaleSlack ? mx : m_ref;
+        const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_ref - m_new);
+        m_ref = m_new;
+        l_run *= alpha;
+        if (__any(alpha != 1.f && l_run != 0.f)) {   // nothing to rescale while O is still zero
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int x = 0; x < 16; ++x) O[j][x] *= alpha;
+        }
+    }
+    const float m_use = m_ref == -INFINITY ? 0.f : m_ref;
+    uint32_t pk[8];
+    float lsum = 0.f;
+#pragma unroll
+    for (int x = 0; x < 16; x += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(S[x], scale_log2, -m_use));
+        const float p1 = __builtin_amdgcn_exp2f(fmaf(S[x + 1], scale_log2, -m_use));
+        pk[x >> 1] = pack_bf16x2(p0, p1);
+        lsum = add_bf16x2(pk[x >> 1], lsum);   // the sum runs over the rounded weights the MFMA sees
+    }
+    l_run += lsum;
+    const uint4 pf0 = make_uint4(pk[0], pk[1], pk[2], pk[3]), pf1 = make_uint4(pk[4], pk[5], pk[6], pk[7]);
+#pragma unroll
+    for (int ks2 = 0; ks2 < 2; ++ks2)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint2 lo = v[(ks2 * 4 + j) * 2], hi = v[(ks2 * 4 + j) * 2 + 1];
+            O[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)),
+                                                           as_bf16x8(ks2 ? pf1 : pf0), O[j], 0, 0, 0);
+        }
 }
 
 // Instrumented builds (-DSPECPV_TIMELINE): core clock against real time over a workgroup's life.  Cycles, 10 ns ticks and

@@ -50,57 +50,21 @@ __device__ __forceinline__ float sum_xor16(float x)
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-// Sum over the 16 lanes of a DPP row, result in every lane of the row: lane ^ 1, lane ^ 2, then the
-// mirrors inside 8 and 16 lanes.
-template <int CTRL> __device__ __forceinline__ float dpp_row_f32(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float row16_sum(float x)
-{
-    x += dpp_row_f32<0xB1>(x);
-    x += dpp_row_f32<0x4E>(x);
-    x += dpp_row_f32<0x141>(x);
-    x += dpp_row_f32<0x140>(x);
-    return x;
-}
 // max / sum over the 8 lanes 8 u .. 8 u + 7 (lane ^ 1, lane ^ 2, mirror inside 8)
 __device__ __forceinline__ float oct_max(float x)
 {
-    x = fmaxf(x, dpp_row_f32<0xB1>(x));
-    x = fmaxf(x, dpp_row_f32<0x4E>(x));
-    x = fmaxf(x, dpp_row_f32<0x141>(x));
+    x = fmaxf(x, dpp_row<0xB1>(x));
+    x = fmaxf(x, dpp_row<0x4E>(x));
+    x = fmaxf(x, dpp_row<0x141>(x));
     return x;
 }
 __device__ __forceinline__ float oct_sum(float x)
 {
-    x += dpp_row_f32<0xB1>(x);
-    x += dpp_row_f32<0x4E>(x);
-    x += dpp_row_f32<0x141>(x);
+    x += dpp_row<0xB1>(x);
+    x += dpp_row<0x4E>(x);
+    x += dpp_row<0x141>(x);
     return x;
 }
-// The root path of tree node j as a bit set; par0 / par1 hold parent[lane] / parent[lane + 64].
-// Everything is wave-uniform (scalar registers).
-// Nodes below `stop` (partially verified tokens that the context kernels attend) end the walk.
-__device__ __forceinline__ void root_path(int j, int n_nodes, int stop, int par0, int par1, unsigned long long &lo,
-                                          unsigned long long &hi)
-{
-    int aa = j;
-    for (int guard = 0; aa >= stop && guard < n_nodes; ++guard) {
-        if (aa < 64) lo |= 1ull << aa; else hi |= 1ull << (aa - 64);
-        const int pa = aa < 64 ? __builtin_amdgcn_readlane(par0, aa) : __builtin_amdgcn_readlane(par1, aa - 64);
-        aa = pa < aa ? pa : -1;   // a malformed parent[] (not strictly decreasing) ends the walk
-    }
-}
-// lowest node of the set (removed from it), or -1
-__device__ __forceinline__ int pop_node(unsigned long long &lo, unsigned long long &hi)
-{
-    int aa = -1;
-    if (lo) { aa = __builtin_ctzll(lo); lo &= lo - 1; }
-    else if (hi) { aa = 64 + __builtin_ctzll(hi); hi &= hi - 1; }
-    return aa;
-}
-
 // ---- eight-wavefront kernel: one query head, one tile of up to 64 nodes, one KV split ----------
 // grid: x = r * 8 + xcd   (r = query head within the group + G * row tile),
 //       y = (bg / 8) * nsplit + split   with bg = b * Hkv + g and xcd = bg % 8.
@@ -264,26 +228,15 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
     const int nch = c1 - c0;
     const int nch_max = first_chunk(C, sp * 4 + 1) - first_chunk(C, sp * 4);   // token group 0 has the most
 
-    // ---- chunk -> token rows ------------------------------------------------------------
-    // ALIGNED (B % 32 == 0): a chunk lies inside one block, so its 32 rows are consecutive.  The
-    // first rows of the next 64 chunks of this wavefront sit in a register (lane t: chunk
-    // row_base + t) and are picked with readlane.  Encoding: r >= 0: all 32 rows r .. r+31 are
-    // valid tokens (the common case, handled without any further test); -1: no valid token;
-    // -2 - r: rows from r on, cut off by the context length.
+    // ---- chunk -> token rows (see ChunkRows) ---------------------------------------------
+    // ALIGNED (B % 32 == 0): the first rows of the next 64 chunks of this wavefront sit in a register (lane t: chunk
+    // row_base + t) and are picked with readlane.
+    const ChunkRows rows_of{sel, a.div_B, s.B, nb, L, T};
     int row_base = 0, row0vec = -1;
-    auto encode_row = [&](int blk, uint32_t p0, uint32_t slot) -> int {
-        if (blk < 0 || blk >= nb) return -1;
-        const int r = blk * s.B + (int)(p0 - slot * Bu);
-        return r >= L ? -1 : (r + 32 > L ? -2 - r : r);
-    };
     auto fill_rows = [&](int cb) {
         row_base = cb;
         int r = -1;
-        if (cb + lane < nch && (uint32_t)(c0 + cb + lane) < C_ctx) {
-            const uint32_t p0 = (uint32_t)(c0 + cb + lane) * 32u;   // < T: the slot below is < cnt
-            const uint32_t slot = a.div_B.div(p0);
-            r = encode_row(sel ? sel[slot] : (int)slot, p0, slot);
-        }
+        if (cb + lane < nch && (uint32_t)(c0 + cb + lane) < C_ctx) r = rows_of.first_row((uint32_t)(c0 + cb + lane));
         row0vec = r;
         // wait for the list entries here, inside the rare branch, so that the common path that
         // joins behind it carries no pending load (and no wait on the DMA prefetch)
@@ -299,17 +252,7 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
         const int e0 = __shfl(idv[0], src), e1 = __shfl(idv[1], src), e2 = __shfl(idv[2], src), e3 = __shfl(idv[3], src);
         const int q4 = (int)(slot >> 6);
         const int blk = q4 == 0 ? e0 : (q4 == 1 ? e1 : (q4 == 2 ? e2 : e3));
-        row0vec = (lane < nch && (uint32_t)(c0 + lane) < C_ctx) ? encode_row(blk, p0, slot) : -1;   // p0 < T there: the slot is < cnt
-    };
-    // general case: this lane's token (t = lane & 31) of chunk ci, or -1
-    auto lane_row = [&](int ci) -> int {
-        const uint32_t p = (uint32_t)(c0 + ci) * 32u + (uint32_t)n;
-        if (p >= T) return -1;
-        const uint32_t slot = a.div_B.div(p);
-        const int blk = sel ? sel[slot] : (int)slot;
-        if (blk < 0 || blk >= nb) return -1;
-        const int tok = blk * s.B + (int)(p - slot * Bu);
-        return tok < L ? tok : -1;
+        row0vec = (lane < nch && (uint32_t)(c0 + lane) < C_ctx) ? rows_of.encode(blk, p0, slot) : -1;   // p0 < T there: the slot is < cnt
     };
 
     uint32_t vmask_st[kStages];   // validity bits of the chunk this wavefront last requested rows for, per stage
@@ -381,7 +324,7 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
             const int rr = -2 - r0;   // r0 == -1 gives -1
             tok = (rr >= 0 && rr + n < L) ? rr + n : -1;
         } else {
-            tok = lane_row(ci);
+            tok = rows_of.row((uint32_t)(c0 + ci), n);
         }
         const uint32_t vm = (uint32_t)__ballot(tok >= 0);
         const uint32_t tk = tok >= 0 ? (uint32_t)tok : 0u;   // row 0 exists (L > 0); masked later
@@ -523,60 +466,7 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
         if (i + 2 < nch) issue(i + 2);
         if (!active) continue;
 
-        f32x16 S;
-#pragma unroll
-        for (int x = 0; x < 16; ++x) S[x] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks)
-            S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[ks]), qf[ks], S, 0, 0, 0);
-
-        if (vmask != 0xffffffffu) {
-#pragma unroll
-            for (int x = 0; x < 16; ++x) {
-                const int tt = (x >> 2) * 8 + kg * 4 + (x & 3);
-                if (!((vmask >> tt) & 1u)) S[x] = -INFINITY;
-            }
-        }
-        float mx = fmaxf(S[0], S[1]);
-#pragma unroll
-        for (int x = 2; x < 16; x += 2) mx = fmaxf(fmaxf(mx, S[x]), S[x + 1]);
-        mx *= a.scale_log2;
-        // the reference max only moves when the true max gets more than 2^slack ahead (tested on each lane's half of
-        // the chunk's tokens; the row's maximum is formed behind the branch -- in the group kernel the same change
-        // measured 3 % slower, so it keeps the exchange in front)
-        if (__any(mx > m_ref + kRescaleSlack)) {
-            mx = max_xor32(mx);
-            const float m_new = mx > m_ref + kRescaleSlack ? mx : m_ref;
-            const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_ref - m_new);
-            m_ref = m_new;
-            l_run *= alpha;
-            if (__any(alpha != 1.f && l_run != 0.f)) {   // nothing to rescale while O is still zero
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int x = 0; x < 16; ++x) O[j][x] *= alpha;
-            }
-        }
-        const float m_use = m_ref == -INFINITY ? 0.f : m_ref;
-        uint32_t pk[8];
-        float lsum = 0.f;
-#pragma unroll
-        for (int x = 0; x < 16; x += 2) {
-            const float p0 = __builtin_amdgcn_exp2f(fmaf(S[x], a.scale_log2, -m_use));
-            const float p1 = __builtin_amdgcn_exp2f(fmaf(S[x + 1], a.scale_log2, -m_use));
-            pk[x >> 1] = pack_bf16x2(p0, p1);
-            lsum = add_bf16x2(pk[x >> 1], lsum);   // the sum runs over the rounded weights the MFMA sees
-        }
-        l_run += lsum;
-        const uint4 pf0 = make_uint4(pk[0], pk[1], pk[2], pk[3]), pf1 = make_uint4(pk[4], pk[5], pk[6], pk[7]);
-#pragma unroll
-        for (int ks2 = 0; ks2 < 2; ++ks2)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint2 lo = v[(ks2 * 4 + j) * 2], hi = v[(ks2 * 4 + j) * 2 + 1];
-                O[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)),
-                                                               as_bf16x8(ks2 ? pf1 : pf0), O[j], 0, 0, 0);
-            }
+        attend_chunk(kf, v, qf, vmask, kg, a.scale_log2, O, m_ref, l_run);
     }
     __syncthreads();   // every wavefront is done with the rings: the epilogue reuses that LDS
     SPECPV_STAMP(7);   // main loop done
@@ -969,42 +859,21 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     const uint32_t vread = ring_addr + TL::kK + vb0 + (D == 128 ? vp * kVPiecePitch : (vp >> 1) * Tile<64>::kVOpPitch + (vp & 1u) * 576u);
     const uint32_t vread1 = D == 128 ? 0u : (vp & 1u) ? vread - 64u : vread + 64u;   // 64 channels: tile 1 (see lds_read_v64)
 
-    // ---- chunk -> token rows ------------------------------------------------------------
-    // ALIGNED (B % 32 == 0): a chunk lies inside one block, so its 32 rows are consecutive.  The
-    // first rows of the next 64 chunks sit in a register (lane t: chunk row_base + t) and are
-    // picked with readlane.  Encoding: r >= 0: all 32 rows r .. r+31 are valid tokens (the common
-    // case, handled without any further test); -1: no valid token; -2 - r: rows from r on, cut
-    // off by the context length; kPendingChunk: a chunk of partially verified tokens.
+    // ---- chunk -> token rows (see ChunkRows) ---------------------------------------------
+    // ALIGNED (B % 32 == 0): the first rows of the next 64 chunks sit in a register (lane t: chunk row_base + t) and are
+    // picked with readlane; kPendingChunk: a chunk of partially verified tokens.
     constexpr int kPendingChunk = (int)0x80000000;
+    const ChunkRows rows_of{sel, a.div_B, s.B, nb, L, T};
     int row_base = 0, row0vec = -1;
     auto fill_rows = [&](int cb) {
         row_base = cb;
         int r = -1;
         if (cb + lane < nch && (uint32_t)(c0 + cb + lane) >= C_ctx) r = kPendingChunk;
-        if (cb + lane < nch && (uint32_t)(c0 + cb + lane) < C_ctx) {
-            const uint32_t p0 = (uint32_t)(c0 + cb + lane) * 32u;   // < T: the slot below is < cnt
-            const uint32_t slot = a.div_B.div(p0);
-            const int blk = sel ? sel[slot] : (int)slot;
-            if (blk >= 0 && blk < nb) {
-                r = blk * s.B + (int)(p0 - slot * Bu);
-                if (r >= L) r = -1;
-                else if (r + 32 > L) r = -2 - r;
-            }
-        }
+        if (cb + lane < nch && (uint32_t)(c0 + cb + lane) < C_ctx) r = rows_of.first_row((uint32_t)(c0 + cb + lane));
         row0vec = r;
         // wait for the list entries here, inside the rare branch, so that the common path that
         // joins behind it carries no pending load (and no wait on the DMA prefetch)
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-    };
-    // general case: this lane's token (t = lane & 31) of chunk ci, or -1
-    auto lane_row = [&](int ci) -> int {
-        const uint32_t p = (uint32_t)(c0 + ci) * 32u + (uint32_t)n;
-        if (p >= T) return -1;
-        const uint32_t slot = a.div_B.div(p);
-        const int blk = sel ? sel[slot] : (int)slot;
-        if (blk < 0 || blk >= nb) return -1;
-        const int tok = blk * s.B + (int)(p - slot * Bu);
-        return tok < L ? tok : -1;
     };
 
     // Request this wavefront's operations of chunk ci into stage stg (1 KiB each: LPR lanes per row).  K operation i
@@ -1085,7 +954,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
                 issue_rows(kdb, vdb, stp, (uint32_t)max(ptok, 0), dst);
                 return (uint32_t)__ballot(ptok >= 0);
             }
-            tok = lane_row(ci);
+            tok = rows_of.row((uint32_t)(c0 + ci), n);
         }
         const uint32_t vm = (uint32_t)__ballot(tok >= 0);
         const uint32_t tk = tok >= 0 ? (uint32_t)tok : 0u;   // row 0 exists (L > 0); masked later

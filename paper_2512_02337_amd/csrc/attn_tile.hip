@@ -179,26 +179,15 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     const int nch_max = first_chunk(C, sp * TG + 1) - first_chunk(C, sp * TG);   // token group 0 has the most
     SPECPV_STAMP(9);   // the scalar reads (lengths, list length) are in: the chunk counts are known
 
-    // ---- chunk -> token rows ------------------------------------------------------------
-    // ALIGNED (B % 32 == 0): a chunk lies inside one block, so its 32 rows are consecutive.  The
-    // first rows of the next 64 chunks of this wavefront sit in a register (lane t: chunk
-    // row_base + t) and are picked with readlane.  Encoding: r >= 0: all 32 rows r .. r+31 are
-    // valid tokens (the common case, handled without any further test); -1: no valid token;
-    // -2 - r: rows from r on, cut off by the context length.
+    // ---- chunk -> token rows (see ChunkRows) ---------------------------------------------
+    // ALIGNED (B % 32 == 0): the first rows of the next 64 chunks of this wavefront sit in a register (lane t: chunk
+    // row_base + t) and are picked with readlane.
+    const ChunkRows rows_of{sel, a.div_B, s.B, nb, L, T};
     int row_base = 0, row0vec = -1;
-    auto encode_row = [&](int blk, uint32_t p0, uint32_t slot) -> int {
-        if (blk < 0 || blk >= nb) return -1;
-        const int r = blk * s.B + (int)(p0 - slot * Bu);
-        return r >= L ? -1 : (r + 32 > L ? -2 - r : r);
-    };
     auto fill_rows = [&](int cb) {
         row_base = cb;
         int r = -1;
-        if (cb + lane < nch && (uint32_t)(c0 + cb + lane) < C_ctx) {
-            const uint32_t p0 = (uint32_t)(c0 + cb + lane) * 32u;   // < T: the slot below is < cnt
-            const uint32_t slot = a.div_B.div(p0);
-            r = encode_row(sel ? sel[slot] : (int)slot, p0, slot);
-        }
+        if (cb + lane < nch && (uint32_t)(c0 + cb + lane) < C_ctx) r = rows_of.first_row((uint32_t)(c0 + cb + lane));
         row0vec = r;
         // wait for the list entries here, inside the rare branch, so that the common path that
         // joins behind it carries no pending load (and no wait on the DMA prefetch)
@@ -214,17 +203,8 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
         const int e0 = __shfl(idv[0], src), e1 = __shfl(idv[1], src), e2 = __shfl(idv[2], src), e3 = __shfl(idv[3], src);
         const int q4 = (int)(slot >> 6);
         const int blk = q4 == 0 ? e0 : (q4 == 1 ? e1 : (q4 == 2 ? e2 : e3));
-        row0vec = (lane < nch && (uint32_t)(c0 + lane) < C_ctx) ? encode_row(blk, p0, slot) : -1;   // p0 < T there: the slot is < cnt
-    };
-    // general case: this lane's token (t = lane & 31) of chunk ci, or -1
-    auto lane_row = [&](int ci) -> int {
-        const uint32_t p = (uint32_t)(c0 + ci) * 32u + (uint32_t)n;
-        if (p >= T) return -1;
-        const uint32_t slot = a.div_B.div(p);
-        const int blk = sel ? sel[slot] : (int)slot;
-        if (blk < 0 || blk >= nb) return -1;
-        const int tok = blk * s.B + (int)(p - slot * Bu);
-        return tok < L ? tok : -1;
+        const int r = rows_of.encode(blk, p0, slot);   // (without a branch around it)
+        row0vec = (lane < nch && (uint32_t)(c0 + lane) < C_ctx) ? r : -1;   // p0 < T there: the slot is < cnt
     };
 
     uint32_t vmv = 0u;   // validity words of the chunks in the ring: lane t holds those of stage t
@@ -303,7 +283,7 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
             const int rr = -2 - r0;   // r0 == -1 gives -1
             tok = (rr >= 0 && rr + n < L) ? rr + n : -1;
         } else {
-            tok = lane_row(ci);
+            tok = rows_of.row((uint32_t)(c0 + ci), n);
         }
         const uint32_t vm = (uint32_t)__ballot(tok >= 0);
         vmv = lane == stg ? vm : vmv;
@@ -372,60 +352,7 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
         if (TG != 2 && i + AHEAD < nch) issue(i + AHEAD);
         if (!active) continue;
 
-        f32x16 S;
-#pragma unroll
-        for (int x = 0; x < 16; ++x) S[x] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks)
-            S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[ks]), qf[ks], S, 0, 0, 0);
-
-        if (vmask != 0xffffffffu) {
-#pragma unroll
-            for (int x = 0; x < 16; ++x) {
-                const int tt = (x >> 2) * 8 + kg * 4 + (x & 3);
-                if (!((vmask >> tt) & 1u)) S[x] = -INFINITY;
-            }
-        }
-        float mx = fmaxf(S[0], S[1]);
-#pragma unroll
-        for (int x = 2; x < 16; x += 2) mx = fmaxf(fmaxf(mx, S[x]), S[x + 1]);
-        mx *= a.scale_log2;
-        // the reference max only moves when the true max gets more than 2^slack ahead (tested on each lane's half of
-        // the chunk's tokens; the row's maximum is formed behind the branch -- in the group kernel the same change
-        // measured 3 % slower, so it keeps the exchange in front)
-        if (__any(mx > m_ref + kRescaleSlack)) {
-            mx = max_xor32(mx);
-            const float m_new = mx > m_ref + kRescaleSlack ? mx : m_ref;
-            const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_ref - m_new);
-            m_ref = m_new;
-            l_run *= alpha;
-            if (__any(alpha != 1.f && l_run != 0.f)) {   // nothing to rescale while O is still zero
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int x = 0; x < 16; ++x) O[j][x] *= alpha;
-            }
-        }
-        const float m_use = m_ref == -INFINITY ? 0.f : m_ref;
-        uint32_t pk[8];
-        float lsum = 0.f;
-#pragma unroll
-        for (int x = 0; x < 16; x += 2) {
-            const float p0 = __builtin_amdgcn_exp2f(fmaf(S[x], a.scale_log2, -m_use));
-            const float p1 = __builtin_amdgcn_exp2f(fmaf(S[x + 1], a.scale_log2, -m_use));
-            pk[x >> 1] = pack_bf16x2(p0, p1);
-            lsum = add_bf16x2(pk[x >> 1], lsum);   // the sum runs over the rounded weights the MFMA sees
-        }
-        l_run += lsum;
-        const uint4 pf0 = make_uint4(pk[0], pk[1], pk[2], pk[3]), pf1 = make_uint4(pk[4], pk[5], pk[6], pk[7]);
-#pragma unroll
-        for (int ks2 = 0; ks2 < 2; ++ks2)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint2 lo = v[(ks2 * 4 + j) * 2], hi = v[(ks2 * 4 + j) * 2 + 1];
-                O[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)),
-                                                               as_bf16x8(ks2 ? pf1 : pf0), O[j], 0, 0, 0);
-            }
+        attend_chunk(kf, v, qf, vmask, kg, a.scale_log2, O, m_ref, l_run);
     }
     __syncthreads();   // every wavefront is done with the rings: the epilogue reuses that LDS
     SPECPV_STAMP(7);   // main loop done

@@ -16,22 +16,6 @@
 
 namespace specpv {
 
-// Sum over the 16 lanes of a DPP row, result in every lane of the row: lane ^ 1, lane ^ 2,
-// then the mirrors inside 8 and 16 lanes.
-template <int CTRL>
-__device__ __forceinline__ float dpp_row(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float row16_sum(float x)
-{
-    x += dpp_row<0xB1>(x);
-    x += dpp_row<0x4E>(x);
-    x += dpp_row<0x141>(x);
-    x += dpp_row<0x140>(x);
-    return x;
-}
-
 // CPL adjacent channels of one row, 16 bytes per memory instruction (rows are 16-byte aligned).
 template <typename T, int CPL> struct Chan;
 template <int CPL> struct Chan<float, CPL> {
@@ -150,32 +134,6 @@ __device__ __forceinline__ float row16_max(float x)
     x = fmaxf(x, dpp_row<0x4E>(x));
     x = fmaxf(x, dpp_row<0x141>(x));
     return fmaxf(x, dpp_row<0x140>(x));
-}
-
-// The root path of tree node j as a bit set; par0 / par1 hold parent[lane] / parent[lane + 64].  Everything is
-// wave-uniform (scalar registers).  Nodes below `stop` (partially verified tokens that the context kernels have attended
-// already) end the walk.
-__device__ __forceinline__ void root_path(int j, int n_nodes, int stop, int par0, int par1, unsigned long long &lo, unsigned long long &hi)
-{
-    int at = j;
-    for (int guard = 0; at >= stop && guard < n_nodes; ++guard) {
-        // (values, not a choice between two variables: the compiler would put those into memory)
-        const unsigned long long bit = 1ull << (at & 63);
-        lo |= at < 64 ? bit : 0ull;
-        hi |= at < 64 ? 0ull : bit;
-        const int pa = __builtin_amdgcn_readlane(at < 64 ? par0 : par1, at & 63);
-        at = pa < at ? pa : -1;   // a malformed parent[] (not strictly decreasing) ends the walk
-    }
-}
-// lowest node of the set (removed from it), or -1
-__device__ __forceinline__ int pop_node(unsigned long long &lo, unsigned long long &hi)
-{
-    const bool low = lo != 0ull;
-    const unsigned long long word = low ? lo : hi;
-    const int at = word ? __builtin_ctzll(word) + (low ? 0 : 64) : -1;
-    lo &= lo - (low ? 1ull : 0ull);
-    hi &= hi - (low || hi == 0ull ? 0ull : 1ull);
-    return at;
 }
 
 #ifdef SPECPV_TIMELINE
@@ -457,9 +415,10 @@ static void launch_combine_t(const Shape &s, Partials p, void *out, float *lse, 
     do {                                                                                                                \
         if (kHalf && p.o_half) SPECPV_LAUNCH_K(NP, MULTI, NB, kHalf); else SPECPV_LAUNCH_K(NP, MULTI, NB, false);        \
     } while (0)
+// (the kernels that write fp16 partials have attended the partially verified tokens: kctx == koff)
 #define SPECPV_LAUNCH_NP(NP, MULTI)                                                                                      \
     do {                                                                                                                \
-        if (s.koff > s.kctx) SPECPV_LAUNCH_H(NP, MULTI, 24); else SPECPV_LAUNCH_H(NP, MULTI, 8);                         \
+        if (s.koff > s.kctx) SPECPV_LAUNCH_K(NP, MULTI, 24, false); else SPECPV_LAUNCH_H(NP, MULTI, 8);                  \
     } while (0)
     if (p.stream) SPECPV_LAUNCH_NP(8, true);
     else if (p.nsplit <= 2) SPECPV_LAUNCH_NP(2, false);
