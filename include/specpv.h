@@ -320,7 +320,7 @@ int specpv_debug_set_route(int route);
  *   1  one launch where that is possible, two elsewhere: every scoring workgroup counts itself in on
  *      arrival words of its (sequence, KV head) at the head of the workspace, and the last one to
  *      arrive selects (no workgroup waits for another; the words are zero again afterwards).
- *      Possible where the matrix-core scoring kernel applies (bf16, head dim 128), the tree has more
+ *      Possible where the matrix-core scoring kernel applies (bf16), the tree has more
  *      than 96 query rows per KV head, max_blocks <= 4096, batch * n_kv_heads <= 910 and the call
  *      has a workspace of 64 KiB or more
  *   2  two launches: scoring, then selection
@@ -334,6 +334,7 @@ int specpv_debug_set_select_route(int route);
  * the combine kernel writes rows 2048 + workgroup, and rows 3072 + workgroup receive three words per attention
  * workgroup: core cycles (s_memtime), 10 ns ticks and chunks of its life, from which the core clock follows.
  * The kernel for long token ranges (full verification) writes only those three words, to row workgroup.
+ * Workgroups beyond those rows (2048, 1024, 1024) write nothing.
  * paper_2512_02337_amd/timeline.py names the points and prints their medians.  A regular build takes no
  * stamps and answers a non-NULL buf with SPECPV_EINVAL. */
 int specpv_debug_set_timeline(void *buf);

@@ -14,9 +14,10 @@
 // What bounds it at one sequence is latency, not a rate: arguments and list 1.5 us, the first chunk 2 us later, then a
 // chain of chunks that a wavefront takes 0.86 us each for when they are there; a ring of two stages refilled at 3 us
 // of loaded latency made that 1.8 us.  The planner (plan_attention) chooses TG and the splits.  Calls of one sequence, 8 KV
-// heads at G = 4, 4096 kept tokens, against tiles of one head's 64 nodes (TG = 4, 8 splits, whatever the node count):
-// 60 nodes 17.4 -> 16.5 us (TG = 2, 16 splits), 1 node 15.4 -> 11.7 us (TG = 8, 16 splits); 8192 tokens, 60 nodes
-// 32.3 -> 21.2 us.
+// heads at G = 4, in graphs of 16 layers, against tiles of one head's 64 nodes (TG = 4, 8 splits, whatever the node count),
+// side by side on one card: 4096 kept tokens, 60 nodes 17.7 -> 17.2 us (TG = 2, 16 splits; on other cards 17.8 -> 17.6 and
+// 17.8 -> 18.1), 1 node 14.9 -> 11.6 us (TG = 8, 16 splits); 8192 tokens, 60 nodes 31.8 -> 22.5 us; 2048 tokens, 60 nodes
+// 13.8 -> 14.4 us (called one by one 13.8 -> 13.9).
 //
 // Per chunk (v_mfma_f32_32x32x16_bf16, fp32 accumulate):
 //   S^T = K . Q^T     tokens are the M index, query rows the N index, so each
@@ -43,7 +44,7 @@ namespace specpv {
 #ifdef SPECPV_TIMELINE
 #define SPECPV_STAMP(i)                                                                                                      \
     do {                                                                                                                     \
-        if (timeline && threadIdx.x == 0)                                                                                    \
+        if (timeline && threadIdx.x == 0 && blockIdx.y * gridDim.x + blockIdx.x < 2048u)                                     \
             timeline[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 16 + (i)] = __builtin_amdgcn_s_memrealtime();           \
     } while (0)
 #else
