@@ -28,10 +28,10 @@ HBM_PEAK_GBS = 8000.0
 # rocprofv3 --kernel-trace --stats run, as committed under profiles/.  They describe the launch plan named here
 # (kernels and split count); the line carries them only while the library still plans the call that way.
 RECORDED = {"llama8b_128k": {
-    "plan": {"kernels": ["attn_ctx_mfma_kernel", "combine_kernel"], "splits": 8},
-    "traffic_bytes": (8663 + 2419) * 2 * 1024 + (3960 + 480) * 1024,
+    "plan": {"kernels": ["attn_ctx_tile_kernel", "combine_kernel"], "splits": 16},
+    "traffic_bytes": (8682 + 4397) * 2 * 1024 + (7920 + 480) * 1024,
     "traffic_source": "profiles/pmc_traffic_llama8b_128k.md",
-    "kernels": [{"name": "attn_ctx_mfma_kernel", "us": 12.5}, {"name": "combine_kernel", "us": 4.8}],
+    "kernels": [{"name": "attn_ctx_tile_kernel", "us": 11.8}, {"name": "combine_kernel", "us": 5.2}],
     "kernels_source": "profiles/kernel_durations_llama8b_128k.md"}}
 
 
@@ -382,7 +382,7 @@ def main():
     if not args.no_cpu_baseline:
         cpu = cpu_baseline(layers)
 
-    # the recorded counter / trace figures only describe the launch plan they were taken with: 8 context splits
+    # the recorded counter / trace figures only describe the launch plan they were taken with, by its context splits
     # (read off the workspace size: 64 KiB of arrival words + (splits + 1) x (partial O + (m, l) pairs) + scores)
     rec = RECORDED.get(args.workload) if n_layers == cfg["layers"] else None
     if rec is not None:
@@ -417,7 +417,7 @@ def main():
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": rec["traffic_bytes"] if rec else None,
                      "traffic_is": "recorded (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, %s), not measured by this run" % rec["traffic_source"] if rec else None,
-                     "kernel": "context attention (attn_ctx_mfma_kernel at the default workload; the planner picks by shape) + combine_kernel = one specpv_partial_verify_attn call (one layer)",
+                     "kernel": "context attention (attn_ctx_tile_kernel at the default workload; the planner picks by shape) + combine_kernel = one specpv_partial_verify_attn call (one layer)",
                      "kernels": [dict(k, frac=round(bytes_layer / (k["us"] * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
                                       source="recorded: " + rec["kernels_source"]) for k in rec["kernels"]] if rec else None,
                      "algorithmic_bytes_per_launch": bytes_layer, "us_per_launch": round(us_layer, 3),

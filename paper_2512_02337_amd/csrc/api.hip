@@ -99,9 +99,11 @@ static Shape make_shape(const specpv_kv *kv, const specpv_tree *tree)
 }
 
 // What a call with bf16 at 128 channels would take, in microseconds, with one of the matrix-core kernels and `ns` splits,
-// less what does not depend on that choice: fitted to about 25000 timings of whole calls (HIP graph replays; 1 to 78 nodes,
-// G = 2, 4, 5 and 8, 2 to 128 (sequence, KV head) pairs, 512 to 131072 attended tokens; residual 6 %, and choosing by it
-// loses 0.5 % against the best measured choice of each shape).  A workgroup per CU at a time takes its token range, p
+// less what does not depend on that choice.  The constants were fitted to whole calls in graph replays; against 1578 other
+// timings (130 shapes: 1 to 78 nodes, G = 2, 4, 5 and 8, 2 to 128 (sequence, KV head) pairs, 512 to 131072 attended tokens;
+// profiles/plan_timings) the model is 8 % off, root mean square, and the plan it chooses 1.2 % slower than the fastest
+// measured one in the mean, 14 % at most.  Taking the fewest partials among plans that the model holds within 1, 2, 4 or
+// 6 % of the best: 1.1, 1.3, 1.4, 1.9 %, so the best it is.  A workgroup per CU at a time takes its token range, p
 // chunks one after the other, in `rounds`; besides that the K / V bytes have to come out of the L2s (once per tile) and
 // of HBM; partials are written and read back.
 struct AttnCost {

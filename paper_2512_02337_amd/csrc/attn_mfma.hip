@@ -99,7 +99,7 @@ constexpr int kXccBits = 7;
 #ifdef SPECPV_TIMELINE
 #define SPECPV_STAMP(i)                                                                                       \
     do {                                                                                                      \
-        if (f.timeline && threadIdx.x == 0 && !REDO)                                                          \
+        if (f.timeline && threadIdx.x == 0 && !REDO && blockIdx.y * gridDim.x + blockIdx.x < 2048u)           \
             f.timeline[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 16 + (i)] = __builtin_amdgcn_s_memrealtime(); \
     } while (0)
 #else
@@ -711,8 +711,8 @@ void attn_ctx_mfma_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
 // validity words of the stages are scalar registers, and the request of a chunk tests the common
 // case (32 valid consecutive rows) first.  What a wavefront executes per chunk besides its
 // arithmetic is what this loop pays for: measured in core cycles per chunk and workgroup (128K
-// context, 32 splits), 2590 with a run-time stage and a barrier per chunk, 2295 unrolled, 2085
-// with the four-chunk period; 1400 for the requests and barriers alone (timing probe), 1024 for
+// context, 32 splits, eight row blocks), 2590 with a run-time stage and a barrier per chunk, 2295 unrolled, 2085
+// with a period of four chunks, 2033 with two; 1400 for the requests and barriers alone (timing probe), 1024 for
 // the matrix instructions.
 constexpr int kGroupPeriod = 2;                  // chunks between two workgroup barriers
 constexpr int kGroupStages = 2 * kGroupPeriod;   // two halves
@@ -1238,8 +1238,8 @@ static GroupLayout group_layout(const Shape &s)
     }
     return g;
 }
-// What a workgroup takes per 32-token chunk with that many row blocks, 128 channels, every CU busy (fitted to measured
-// times, see AttnCost in api.hip).
+// What a workgroup takes per 32-token chunk with that many row blocks, 128 channels, every CU busy (fitted, see AttnCost in
+// api.hip).
 double attn_group_chunk_us(int blocks)
 {
     return blocks <= 2 ? 0.395 : (blocks <= 4 ? 0.616 : (blocks <= 6 ? 0.72 : (blocks <= 8 ? 0.87 : 1.133)));

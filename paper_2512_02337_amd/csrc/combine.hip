@@ -7,10 +7,10 @@
 // TWO: two wavefronts per four rows, one for the tree segment and one for the partials: each is a chain of a round trip or
 // two and a few hundred dependent instructions (a wavefront by itself issues one per eight cycles), and the two chains
 // have nothing in common until the last step.  Up to 16 partials are requested at once, 16 bytes per lane each, and a
-// lane works out the weights of its own partials only.  Calls of one sequence, against one wavefront that fetched eight
-// partials a round in 8-byte pieces and kept every (m, l) pair in every lane: with 8 splits 17.4 -> 17.3 us, with 16 20.7
-// -> 16.5, with 32 24.7 -> 19.8.
-// (A tree segment on the matrix cores, dense over 32 nodes with a bit mask, was slower: 18.6 us with 8 splits.)
+// lane works out the weights of its own partials only.  One sequence, 60 nodes, 8 KV heads at G = 4 (kernel trace,
+// medians): 4.9 us with 8 splits, 4.8 with 16, 7 with 32 (full pass); one wavefront that fetched eight partials a round
+// in 8-byte pieces and kept every (m, l) pair in every lane took 4.8 us with 8 splits and 14.4 with 32.
+// (A tree segment on the matrix cores, dense over 32 nodes with a bit mask, was slower: a call 18.6 us with 8 splits.)
 #include "internal.h"
 #include <type_traits>
 
@@ -139,7 +139,7 @@ __device__ __forceinline__ float row16_max(float x)
 #ifdef SPECPV_TIMELINE
 #define SPECPV_CSTAMP(i, W)                                                                                  \
     do {                                                                                                     \
-        if (part.timeline && threadIdx.x == 64 * (W))                                                        \
+        if (part.timeline && threadIdx.x == 64 * (W) && (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x < 1024u) \
             part.timeline[(2048 + ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 16 + (i)] = \
                 __builtin_amdgcn_s_memrealtime();                                                            \
     } while (0)
