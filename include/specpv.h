@@ -178,7 +178,8 @@ int specpv_partial_verify_attn(const specpv_kv *kv, const specpv_tree *tree,
 
 /* For callers that can neither allocate nor pass a workspace: code under HIP graph capture with
  * fixed arguments, tight serving loops, harnesses that forbid hipMalloc.  The same computation
- * as specpv_partial_verify_attn (same kernels, bit-identical results) with the split-KV partial
+ * as specpv_partial_verify_attn (same kernels, results bit-identical to those with a workspace of the
+ * size that specpv_workspace_bytes states) with the split-KV partial
  * results kept in a file-scope device array of SPECPV_STATIC_SCRATCH_BYTES inside the library
  * (one copy per GPU, held until the process ends).  The call allocates nothing and calls no
  * allocating routine.  A call whose partial results would not fit (specpv_workspace_bytes with
