@@ -99,16 +99,22 @@ bool integer(PyObject *o, int32_t *v)
     return true;
 }
 
+// A reference that is given back, also where what follows throws.
+struct Ref {
+    PyObject *o;
+    explicit Ref(PyObject *p) : o(p) {}
+    ~Ref() { Py_XDECREF(o); }
+    Ref(const Ref &) = delete;
+    Ref &operator=(const Ref &) = delete;
+};
 // kv and tree belong together (binding.py: _match)
 bool match(const Desc<specpv_kv> &kv, PyObject *tree_obj, const Desc<specpv_tree> &tree)
 {
     if (!kv || !tree) return false;
-    PyObject *q = PyObject_GetAttr(tree_obj, s_q), *kd = PyObject_GetAttr(tree_obj, s_kd);
+    const Ref q(PyObject_GetAttr(tree_obj, s_q)), kd(PyObject_GetAttr(tree_obj, s_kd));
     void *p = nullptr;
-    bool ok = q && kd && tensor(q, scalar(kv.get()), {kv->batch, tree->M - tree->n_key_only, tree->n_q_heads, kv->head_dim}, &p) && p == tree->q;
-    if (ok && kd != Py_None) ok = tensor(kd, scalar(kv.get()), {kv->batch, tree->M, kv->n_kv_heads, kv->head_dim}, &p) && p == tree->kd;
-    Py_XDECREF(q);
-    Py_XDECREF(kd);
+    bool ok = q.o && kd.o && tensor(q.o, scalar(kv.get()), {kv->batch, tree->M - tree->n_key_only, tree->n_q_heads, kv->head_dim}, &p) && p == tree->q;
+    if (ok && kd.o != Py_None) ok = tensor(kd.o, scalar(kv.get()), {kv->batch, tree->M, kv->n_kv_heads, kv->head_dim}, &p) && p == tree->kd;
     if (PyErr_Occurred()) PyErr_Clear();
     return ok;
 }
