@@ -205,6 +205,116 @@ __device__ __forceinline__ void lds_read_v(uint32_t addr, uint2 (&v)[16])
         : "memory");
 }
 
+// Two chunks' worth of operands and both score tiles in one statement (128 channels): K operands of chunks 0 and 1 (byte
+// offsets K0, K1 from a[]), S^T = K . Q^T of each, and behind the products the V operands of both (offsets V0, V1 from va;
+// the layout of lds_read_v) in the registers that held K.  A wavefront's LDS reads then run under its own matrix
+// instructions, and 64 tokens cost one round trip to LDS instead of four.  At most 15 reads are in flight (the counter has
+// four bits); a register is read into again only behind the matrix instruction that was its last reader; "s_nop 11": the
+// twelve wait states between a 32x32x16 product and the vector ALU's read of it, which the compiler does not count in here.
+// With the single test of the maximum for both (attend_pair), core cycles per chunk of the full pass over 128K tokens, eight
+// row blocks: 2033 -> 1780.  The chip runs that loop at the clock its power allows (1.4 to 1.9 GHz), so a workgroup's 128
+// chunks went from 138 - 150 us to 126 - 139, not in proportion.  Tried as well: the two wavefronts of a SIMD passing the
+// barrier at different points of this (2110), one of them requesting behind its scores (1890), wave priorities (no change).
+template <int K0, int K1, int V0, int V1>
+__device__ __forceinline__ void score_pair(const uint32_t (&a)[8], uint32_t va, const bf16x8 (&q)[8], f32x16 &S0, f32x16 &S1,
+                                           uint4 (&v0)[8], uint4 (&v1)[8])
+{
+    static_assert(K0 >= 0 && K1 >= 0 && V0 >= 0 && V1 >= 0 && K0 < 65536 && K1 < 65536 && V0 + 960 < 65536 && V1 + 960 < 65536, "the offset field has 16 bits");
+    asm volatile(
+        "ds_read_b128 v[192:195], %[a0] offset:%[k0]\n\t"
+        "ds_read_b128 v[196:199], %[a1] offset:%[k0]\n\t"
+        "ds_read_b128 v[200:203], %[a2] offset:%[k0]\n\t"
+        "ds_read_b128 v[204:207], %[a3] offset:%[k0]\n\t"
+        "ds_read_b128 v[208:211], %[a4] offset:%[k0]\n\t"
+        "ds_read_b128 v[212:215], %[a5] offset:%[k0]\n\t"
+        "ds_read_b128 v[216:219], %[a6] offset:%[k0]\n\t"
+        "ds_read_b128 v[220:223], %[a7] offset:%[k0]\n\t"
+        "s_waitcnt lgkmcnt(7)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s0], v[192:195], %[q0], 0\n\t"
+        "ds_read_b128 v[224:227], %[a0] offset:%[k1]\n\t"
+        "ds_read_b128 v[228:231], %[a1] offset:%[k1]\n\t"
+        "s_waitcnt lgkmcnt(8)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s0], v[196:199], %[q1], %[s0]\n\t"
+        "ds_read_b128 v[232:235], %[a2] offset:%[k1]\n\t"
+        "ds_read_b128 v[236:239], %[a3] offset:%[k1]\n\t"
+        "s_waitcnt lgkmcnt(9)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s0], v[200:203], %[q2], %[s0]\n\t"
+        "ds_read_b128 v[240:243], %[a4] offset:%[k1]\n\t"
+        "ds_read_b128 v[244:247], %[a5] offset:%[k1]\n\t"
+        "s_waitcnt lgkmcnt(10)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s0], v[204:207], %[q3], %[s0]\n\t"
+        "ds_read_b128 v[248:251], %[a6] offset:%[k1]\n\t"
+        "ds_read_b128 v[252:255], %[a7] offset:%[k1]\n\t"
+        "s_waitcnt lgkmcnt(11)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s0], v[208:211], %[q4], %[s0]\n\t"
+        "ds_read_b64_tr_b16 v[192:193], %[va] offset:%[v0]+0\n\t"
+        "ds_read_b64_tr_b16 v[194:195], %[va] offset:%[v0]+256\n\t"
+        "s_waitcnt lgkmcnt(12)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s0], v[212:215], %[q5], %[s0]\n\t"
+        "ds_read_b64_tr_b16 v[196:197], %[va] offset:%[v0]+64\n\t"
+        "ds_read_b64_tr_b16 v[198:199], %[va] offset:%[v0]+320\n\t"
+        "s_waitcnt lgkmcnt(13)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s0], v[216:219], %[q6], %[s0]\n\t"
+        "ds_read_b64_tr_b16 v[200:201], %[va] offset:%[v0]+128\n\t"
+        "ds_read_b64_tr_b16 v[202:203], %[va] offset:%[v0]+384\n\t"
+        "s_waitcnt lgkmcnt(14)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s0], v[220:223], %[q7], %[s0]\n\t"
+        "s_waitcnt lgkmcnt(13)\n\t"
+        "ds_read_b64_tr_b16 v[204:205], %[va] offset:%[v0]+192\n\t"
+        "ds_read_b64_tr_b16 v[206:207], %[va] offset:%[v0]+448\n\t"
+        "s_waitcnt lgkmcnt(8)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s1], v[224:227], %[q0], 0\n\t"
+        "ds_read_b64_tr_b16 v[208:209], %[va] offset:%[v0]+512\n\t"
+        "ds_read_b64_tr_b16 v[210:211], %[va] offset:%[v0]+768\n\t"
+        "ds_read_b64_tr_b16 v[224:225], %[va] offset:%[v1]+0\n\t"
+        "ds_read_b64_tr_b16 v[226:227], %[va] offset:%[v1]+256\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s1], v[228:231], %[q1], %[s1]\n\t"
+        "s_waitcnt lgkmcnt(11)\n\t"
+        "ds_read_b64_tr_b16 v[212:213], %[va] offset:%[v0]+576\n\t"
+        "ds_read_b64_tr_b16 v[214:215], %[va] offset:%[v0]+832\n\t"
+        "ds_read_b64_tr_b16 v[228:229], %[va] offset:%[v1]+64\n\t"
+        "ds_read_b64_tr_b16 v[230:231], %[va] offset:%[v1]+320\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s1], v[232:235], %[q2], %[s1]\n\t"
+        "s_waitcnt lgkmcnt(11)\n\t"
+        "ds_read_b64_tr_b16 v[216:217], %[va] offset:%[v0]+640\n\t"
+        "ds_read_b64_tr_b16 v[218:219], %[va] offset:%[v0]+896\n\t"
+        "ds_read_b64_tr_b16 v[232:233], %[va] offset:%[v1]+128\n\t"
+        "ds_read_b64_tr_b16 v[234:235], %[va] offset:%[v1]+384\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s1], v[236:239], %[q3], %[s1]\n\t"
+        "s_waitcnt lgkmcnt(11)\n\t"
+        "ds_read_b64_tr_b16 v[220:221], %[va] offset:%[v0]+704\n\t"
+        "ds_read_b64_tr_b16 v[222:223], %[va] offset:%[v0]+960\n\t"
+        "ds_read_b64_tr_b16 v[236:237], %[va] offset:%[v1]+192\n\t"
+        "ds_read_b64_tr_b16 v[238:239], %[va] offset:%[v1]+448\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s1], v[240:243], %[q4], %[s1]\n\t"
+        "s_waitcnt lgkmcnt(13)\n\t"
+        "ds_read_b64_tr_b16 v[240:241], %[va] offset:%[v1]+512\n\t"
+        "ds_read_b64_tr_b16 v[242:243], %[va] offset:%[v1]+768\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s1], v[244:247], %[q5], %[s1]\n\t"
+        "s_waitcnt lgkmcnt(13)\n\t"
+        "ds_read_b64_tr_b16 v[244:245], %[va] offset:%[v1]+576\n\t"
+        "ds_read_b64_tr_b16 v[246:247], %[va] offset:%[v1]+832\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s1], v[248:251], %[q6], %[s1]\n\t"
+        "s_waitcnt lgkmcnt(13)\n\t"
+        "ds_read_b64_tr_b16 v[248:249], %[va] offset:%[v1]+640\n\t"
+        "ds_read_b64_tr_b16 v[250:251], %[va] offset:%[v1]+896\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[s1], v[252:255], %[q7], %[s1]\n\t"
+        "s_waitcnt lgkmcnt(13)\n\t"
+        "ds_read_b64_tr_b16 v[252:253], %[va] offset:%[v1]+704\n\t"
+        "ds_read_b64_tr_b16 v[254:255], %[va] offset:%[v1]+960\n\t"
+        "s_nop 11\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : [s0] "=&v"(S0), [s1] "=&v"(S1),
+          "=&{v[192:195]}"(v0[0]), "=&{v[196:199]}"(v0[1]), "=&{v[200:203]}"(v0[2]), "=&{v[204:207]}"(v0[3]),
+          "=&{v[208:211]}"(v0[4]), "=&{v[212:215]}"(v0[5]), "=&{v[216:219]}"(v0[6]), "=&{v[220:223]}"(v0[7]),
+          "=&{v[224:227]}"(v1[0]), "=&{v[228:231]}"(v1[1]), "=&{v[232:235]}"(v1[2]), "=&{v[236:239]}"(v1[3]),
+          "=&{v[240:243]}"(v1[4]), "=&{v[244:247]}"(v1[5]), "=&{v[248:251]}"(v1[6]), "=&{v[252:255]}"(v1[7])
+        : [a0] "v"(a[0]), [a1] "v"(a[1]), [a2] "v"(a[2]), [a3] "v"(a[3]), [a4] "v"(a[4]), [a5] "v"(a[5]), [a6] "v"(a[6]), [a7] "v"(a[7]), [va] "v"(va),
+          [q0] "v"(q[0]), [q1] "v"(q[1]), [q2] "v"(q[2]), [q3] "v"(q[3]), [q4] "v"(q[4]), [q5] "v"(q[5]), [q6] "v"(q[6]), [q7] "v"(q[7]),
+          [k0] "n"(K0), [k1] "n"(K1), [v0] "n"(V0), [v1] "n"(V1)
+        : "memory");
+}
+
 // Half of that: the operands of token half ks2 (OFF = 512 ks2), v[j * 2 + hf].
 template <int OFF> __device__ __forceinline__ void lds_read_v_half(uint32_t addr, uint2 (&v)[8])
 {
@@ -274,12 +384,100 @@ __device__ __forceinline__ float sum_xor32(float x)
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Running state of a query row (lane & 31; each lane's sum runs over its half of the tokens).  The reference maximum only
+// moves when the true maximum runs more than 2^8 ahead of it: the common chunk tests that and does nothing else.  Before the first valid token the reference stands at -3e38, where exp2(fma(S, scale, 3e38)) is 0 for a
+// masked score (-inf) as anywhere else, so that no test for "nothing seen yet" is needed.
+struct RowState {
+    float neg_ref = 3e38f;     // minus the reference maximum, in log2 units
+    float l = 0.f;
+    // reference maximum of a row with sum l_row; -inf for a row without valid tokens
+    __device__ __forceinline__ float ref(float l_row) const { return l_row > 0.f ? -neg_ref : -INFINITY; }
+};
+
+__device__ __forceinline__ float tile_max(const f32x16 &S)
+{
+    float mx = fmaxf(fmaxf(S[0], S[1]), S[2]);
+#pragma unroll
+    for (int x = 3; x < 15; x += 2) mx = fmaxf(fmaxf(mx, S[x]), S[x + 1]);
+    return fmaxf(mx, S[15]);
+}
+
+// mx: largest raw score of this lane's tokens in the chunk.
+template <int NT> __device__ __forceinline__ void follow_max(float mx, float scale_log2, RowState &st, f32x16 (&O)[NT])
+{
+    if (!__any(fmaf(mx, scale_log2, st.neg_ref) > kRescaleSlack)) return;
+    const float top = max_xor32(mx) * scale_log2;   // the row's tokens in both lane halves
+    const float ref = -st.neg_ref, ref_new = top > ref + kRescaleSlack ? top : ref;
+    const float alpha = __builtin_amdgcn_exp2f(ref - ref_new);
+    const bool rescale = __any(alpha != 1.f && st.l != 0.f);   // nothing to rescale while O is still zero
+    st.neg_ref = -ref_new;
+    st.l *= alpha;
+    if (rescale) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int x = 0; x < 16; ++x) O[j][x] *= alpha;
+    }
+}
+
+// vmask: which of the chunk's 32 tokens count
+__device__ __forceinline__ void mask_scores(uint32_t vmask, int kg, f32x16 &S)
+{
+    if (vmask == 0xffffffffu) return;
+    int kg_o = kg;   // (rare: nothing of it is kept in registers across the caller's loop)
+    asm volatile("" : "+v"(kg_o));
+    const uint32_t mine = vmask >> (kg_o * 4);
+#pragma unroll
+    for (int x = 0; x < 16; ++x)
+        if (!((mine >> ((x >> 2) * 8 + (x & 3))) & 1u)) S[x] = -INFINITY;
+}
+
+// Weights of a chunk as bf16 pairs (the B operands of the second product); the sum runs over the rounded weights that the
+// matrix instructions see.
+__device__ __forceinline__ void softmax_weights(const f32x16 &S, float scale_log2, RowState &st, uint32_t (&pk)[8])
+{
+    float lsum = 0.f;
+#pragma unroll
+    for (int x = 0; x < 16; x += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(S[x], scale_log2, st.neg_ref));
+        const float p1 = __builtin_amdgcn_exp2f(fmaf(S[x + 1], scale_log2, st.neg_ref));
+        pk[x >> 1] = pack_bf16x2(p0, p1);
+        lsum = add_bf16x2(pk[x >> 1], lsum);
+    }
+    st.l += lsum;
+}
+
+// O^T += V^T . P^T of one chunk; v: one 16-byte operand per (token half, channel tile)
+__device__ __forceinline__ void add_values(const uint4 (&v)[8], const uint32_t (&pk)[8], f32x16 (&O)[4])
+{
+    const uint4 pf[2] = {make_uint4(pk[0], pk[1], pk[2], pk[3]), make_uint4(pk[4], pk[5], pk[6], pk[7])};
+#pragma unroll
+    for (int ks2 = 0; ks2 < 2; ++ks2)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            O[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(v[ks2 * 4 + j]), as_bf16x8(pf[ks2]), O[j], 0, 0, 0);
+}
+
+// Two chunks whose scores and V operands score_pair has left in registers: one maximum and one test of it for 64 tokens.
+__device__ __forceinline__ void attend_pair(f32x16 &S0, f32x16 &S1, const uint4 (&v0)[8], const uint4 (&v1)[8], uint32_t vm0, uint32_t vm1,
+                                            int kg, float scale_log2, f32x16 (&O)[4], RowState &st)
+{
+    if ((vm0 & vm1) != 0xffffffffu) {
+        mask_scores(vm0, kg, S0);
+        mask_scores(vm1, kg, S1);
+    }
+    follow_max(fmaxf(tile_max(S0), tile_max(S1)), scale_log2, st, O);
+    uint32_t pk[8];
+    softmax_weights(S0, scale_log2, st, pk);
+    add_values(v0, pk, O);
+    softmax_weights(S1, scale_log2, st, pk);
+    add_values(v1, pk, O);
+}
+
 // One 32-token chunk against a row block of 32 query rows, operands in registers: S^T = K . Q^T, the running maximum and
-// sum of each row, O^T += V^T . P^T.  kf: K operands of the eight k-steps; v: V operands (lds_read_v); qf: the query rows;
-// vmask: which of the 32 tokens count; m_ref, l_run: reference maximum and sum of row lane & 31 (l_run over this lane's
-// half of the tokens).
+// sum of each row, O^T += V^T . P^T.  kf: K operands of the eight k-steps; v: V operands (lds_read_v); qf: the query rows.
 __device__ __forceinline__ void attend_chunk(const uint4 (&kf)[8], const uint2 (&v)[16], const bf16x8 (&qf)[8], uint32_t vmask, int kg,
-                                             float scale_log2, f32x16 (&O)[4], float &m_ref, float &l_run)
+                                             float scale_log2, f32x16 (&O)[4], RowState &st)
 {
     f32x16 S;
 #pragma unroll
@@ -287,55 +485,14 @@ __device__ __forceinline__ void attend_chunk(const uint4 (&kf)[8], const uint2 (
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks)
         S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[ks]), qf[ks], S, 0, 0, 0);
-
-    if (vmask != 0xffffffffu) {
-        int kg_o = kg;   // (rare: nothing of it is kept in registers across the caller's loop)
-        asm volatile("" : "+v"(kg_o));
-        const uint32_t mine = vmask >> (kg_o * 4);
-#pragma unroll
-        for (int x = 0; x < 16; ++x)
-            if (!((mine >> ((x >> 2) * 8 + (x & 3))) & 1u)) S[x] = -INFINITY;
-    }
-    float mx = fmaxf(S[0], S[1]);
-#pragma unroll
-    for (int x = 2; x < 16; x += 2) mx = fmaxf(fmaxf(mx, S[x]), S[x + 1]);
-    mx *= scale_log2;
-    // the reference max only moves when the true max gets more than 2^slack ahead (tested on each lane's half of
-    // the chunk's tokens; the row's maximum is formed behind the branch -- in the group kernel the same change
-    // measured 3 % slower, so it keeps the exchange in front)
-    if (__any(mx > m_ref + kRescaleSlack)) {
-        mx = max_xor32(mx);
-        const float m_new = mx > m_ref + kRescaleSlack ? mx : m_ref;
-        const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_ref - m_new);
-        m_ref = m_new;
-        l_run *= alpha;
-        if (__any(alpha != 1.f && l_run != 0.f)) {   // nothing to rescale while O is still zero
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int x = 0; x < 16; ++x) O[j][x] *= alpha;
-        }
-    }
-    const float m_use = m_ref == -INFINITY ? 0.f : m_ref;
+    mask_scores(vmask, kg, S);
+    follow_max(tile_max(S), scale_log2, st, O);
     uint32_t pk[8];
-    float lsum = 0.f;
+    softmax_weights(S, scale_log2, st, pk);
+    uint4 vv[8];
 #pragma unroll
-    for (int x = 0; x < 16; x += 2) {
-        const float p0 = __builtin_amdgcn_exp2f(fmaf(S[x], scale_log2, -m_use));
-        const float p1 = __builtin_amdgcn_exp2f(fmaf(S[x + 1], scale_log2, -m_use));
-        pk[x >> 1] = pack_bf16x2(p0, p1);
-        lsum = add_bf16x2(pk[x >> 1], lsum);   // the sum runs over the rounded weights the MFMA sees
-    }
-    l_run += lsum;
-    const uint4 pf0 = make_uint4(pk[0], pk[1], pk[2], pk[3]), pf1 = make_uint4(pk[4], pk[5], pk[6], pk[7]);
-#pragma unroll
-    for (int ks2 = 0; ks2 < 2; ++ks2)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint2 lo = v[(ks2 * 4 + j) * 2], hi = v[(ks2 * 4 + j) * 2 + 1];
-            O[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)),
-                                                           as_bf16x8(ks2 ? pf1 : pf0), O[j], 0, 0, 0);
-        }
+    for (int x = 0; x < 8; ++x) vv[x] = make_uint4(v[2 * x].x, v[2 * x].y, v[2 * x + 1].x, v[2 * x + 1].y);
+    add_values(vv, pk, O);
 }
 
 // Instrumented builds (-DSPECPV_TIMELINE): core clock against real time over a workgroup's life.  Cycles, 10 ns ticks and

@@ -423,7 +423,7 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
     };
 
     f32x16 O[4];
-    float m_ref = -INFINITY, l_run = 0.f;
+    RowState st;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -466,17 +466,17 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
         if (i + 2 < nch) issue(i + 2);
         if (!active) continue;
 
-        attend_chunk(kf, v, qf, vmask, kg, a.scale_log2, O, m_ref, l_run);
+        attend_chunk(kf, v, qf, vmask, kg, a.scale_log2, O, st);
     }
     __syncthreads();   // every wavefront is done with the rings: the epilogue reuses that LDS
     SPECPV_STAMP(7);   // main loop done
 
     // ---- merge the four token groups ---------------------------------------------------
     {
-        l_run = sum_xor32(l_run);
+        const float l_run = sum_xor32(st.l);
         const int row = rb * 32 + n;
         if (kg == 0) {
-            ms[tg * 64 + row] = m_ref;
+            ms[tg * 64 + row] = st.ref(l_run);
             ls[tg * 64 + row] = l_run;
         }
         // accumulator element 4q + x of tile j is channel 32j + 8q + 4kg + x of this lane's row
@@ -714,6 +714,8 @@ void attn_ctx_mfma_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
 // context, 32 splits, eight row blocks), 2590 with a run-time stage and a barrier per chunk, 2295 unrolled, 2085
 // with a period of four chunks, 2033 with two; 1400 for the requests and barriers alone (timing probe), 1024 for
 // the matrix instructions.
+// Where every wavefront has a row block to itself and 256 registers (128 channels, four or eight row blocks), the two
+// chunks of a ring half are worked on together (score_pair, attend_pair): 1780 cycles per chunk.
 constexpr int kGroupPeriod = 2;                  // chunks between two workgroup barriers
 constexpr int kGroupStages = 2 * kGroupPeriod;   // two halves
 // One 32-token chunk in LDS.  128 channels: as above (kStageBytes).  64 channels: 4 KiB of K (128-byte rows, 16-byte
@@ -763,6 +765,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     typedef Tile<D> TL;
     constexpr int W = group_waves(RB), F = RB & ~3;   // wavefronts; those with a row block to themselves
     constexpr bool PAIRED = W != RB;                // the others share one between two
+    constexpr bool PAIRS = D == 128 && !PAIRED;     // chunks are taken two at a time
     constexpr int KS = D / 16, NT = D / 32;         // k-steps of S^T, channel tiles of O^T
     constexpr int LPR = D / 8, RPO = 64 / LPR;      // lanes per row, rows per 1 KiB operation
     constexpr int KOPS = D / 16, OPS = 2 * KOPS;    // DMA operations of a chunk: K, then V
@@ -972,7 +975,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     asm volatile("" ::: "memory");
 
     f32x16 O[NT];
-    float m_ref = -INFINITY, l_run = 0.f;
+    RowState st;
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -1060,50 +1063,22 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
                 S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[ks]), qf[ks], S, 0, 0, 0);
         }
 
-        if (vmask != 0xffffffffu) {
-            // (rare: the lane's share of the bits is worked out here, from a value the compiler cannot see through,
-            // so that nothing of it is kept in registers across the loop)
-            int kg_o = kg;
-            asm volatile("" : "+v"(kg_o));
-            const uint32_t mine = vmask >> (kg_o * 4);
-#pragma unroll
-            for (int x = 0; x < 16; ++x)
-                if (!((mine >> ((x >> 2) * 8 + (x & 3))) & 1u)) S[x] = -INFINITY;
-        }
-        float mx = fmaxf(S[0], S[1]);
-#pragma unroll
-        for (int x = 2; x < 16; x += 2) mx = fmaxf(fmaxf(mx, S[x]), S[x + 1]);
-        mx = max_xor32(mx) * a.scale_log2;
-        // the reference max only moves when the true max gets more than 2^slack ahead
-        if (__any(mx > m_ref + kRescaleSlack)) {
-            const float m_new = mx > m_ref + kRescaleSlack ? mx : m_ref;
-            const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_ref - m_new);
-            m_ref = m_new;
-            l_run *= alpha;
-            if (__any(alpha != 1.f && l_run != 0.f)) {   // nothing to rescale while O is still zero
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-#pragma unroll
-                    for (int x = 0; x < 16; ++x) O[j][x] *= alpha;
-            }
-        }
-        const float m_use = m_ref == -INFINITY ? 0.f : m_ref;
+        mask_scores(vmask, kg, S);
+        follow_max(tile_max(S), a.scale_log2, st, O);
         uint32_t pk[8];
-        float lsum = 0.f;
+        if constexpr (D == 128) {
+            softmax_weights(S, a.scale_log2, st, pk);
+        } else {
+            float lsum = 0.f;
 #pragma unroll
-        for (int x = 0; x < 16; x += 2) {
-            const float p0 = __builtin_amdgcn_exp2f(fmaf(S[x], a.scale_log2, -m_use));
-            const float p1 = __builtin_amdgcn_exp2f(fmaf(S[x + 1], a.scale_log2, -m_use));
-            pk[x >> 1] = pack_bf16x2(p0, p1);
-            if (D == 64) {
-                S[x] = p0;
-                S[x + 1] = p1;
-                lsum += p0 + p1;
-            } else {
-                lsum = add_bf16x2(pk[x >> 1], lsum);   // the sum runs over the rounded weights the MFMA sees
+            for (int x = 0; x < 16; x += 2) {
+                S[x] = __builtin_amdgcn_exp2f(fmaf(S[x], a.scale_log2, st.neg_ref));
+                S[x + 1] = __builtin_amdgcn_exp2f(fmaf(S[x + 1], a.scale_log2, st.neg_ref));
+                pk[x >> 1] = pack_bf16x2(S[x], S[x + 1]);
+                lsum += S[x] + S[x + 1];
             }
+            st.l += lsum;
         }
-        l_run += lsum;
         pf0 = make_uint4(pk[0], pk[1], pk[2], pk[3]);
         pf1 = make_uint4(pk[4], pk[5], pk[6], pk[7]);
         if constexpr (RB > 8) pv_halves(vread + HOFF, std::integral_constant<int, SOFF>{});
@@ -1138,6 +1113,57 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
         chunk(std::integral_constant<int, S0>{}, vm_stage[S0]);
         if (i0 + 1 < nch) chunk(std::integral_constant<int, S0 + 1>{}, vm_stage[S0 + 1]);
     };
+    if constexpr (PAIRS) {
+        // A ring half at once, 64 tokens: scores and V operands into registers (score_pair), then softmax and values.
+        uint32_t next0 = vm_stage[0], next1 = vm_stage[1];   // validity of the chunks requested last
+        // chunks i, i + 1 (even i) into their ring half: what a wavefront executes here is in front of its arithmetic, so the
+        // common case, both there and whole, is one test
+        auto request = [&](int i) __attribute__((always_inline)) {
+            if (ALIGNED && i + 1 < nch && i + 1 - row_base < 64) {
+                const int ra = __builtin_amdgcn_readlane(row0vec, i - row_base), rb2 = __builtin_amdgcn_readlane(row0vec, i + 1 - row_base);
+                if ((ra | rb2) >= 0) {
+                    char *dst = ring + (i & 2) * TL::kStage;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const uint32_t row_off = (uint32_t)(h ? rb2 : ra) * st2;
+#pragma unroll
+                        for (int t = 0; t < NOPS; ++t)
+                            if (OPS % W == 0 || t < NOPS - 1 || n_ops == NOPS)
+                                __builtin_amdgcn_global_load_lds((glb_void_ptr)((src_base[t] + row_off) + src_off[t]), (lds_void_ptr)(dst + h * TL::kStage + dst_off[t]), 16, 0, kKvAux);
+                    }
+                    next0 = next1 = 0xffffffffu;
+                    return;
+                }
+            }
+#pragma unroll 1
+            for (int c = i; c < min(i + 2, nch); ++c) {
+                const uint32_t vm = issue(c, c & 3);
+                next0 = c & 1 ? next0 : vm;
+                next1 = c & 1 ? vm : next1;
+            }
+        };
+        int i0 = 0;
+        for (; i0 + 1 < nch; i0 += 2) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();   // chunks i0, i0 + 1 have landed; the other half is free
+            const uint32_t vm0 = next0, vm1 = next1;
+            request(i0 + 2);
+            const uint32_t off = (uint32_t)(i0 & 2) * TL::kStage;
+            const uint32_t k0 = kread0 + off, ka[8] = {k0, k0 ^ 32u, k0 ^ 64u, k0 ^ 96u, k0 ^ 128u, k0 ^ 160u, k0 ^ 192u, k0 ^ 224u};
+            f32x16 Sa, Sb;
+            uint4 va[8], vb[8];
+            if (live) score_pair<0, TL::kStage, 0, TL::kStage>(ka, vread + off, qf, Sa, Sb, va, vb);
+            if (live) attend_pair(Sa, Sb, va, vb, vm0, vm1, kg, a.scale_log2, O, st);
+        }
+        if (i0 < nch) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+        }
+        if (i0 < nch) {   // an odd chunk at the end
+            if (i0 & 2) chunk(std::integral_constant<int, 2>{}, next0);
+            else chunk(std::integral_constant<int, 0>{}, next0);
+        }
+    } else
     for (int i0 = 0; i0 < nch; i0 += kGroupStages) {
         period(i0, std::integral_constant<int, 0>{});
         if (i0 + kGroupPeriod < nch) period(i0 + kGroupPeriod, std::integral_constant<int, 1>{});
@@ -1154,15 +1180,15 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     *(float4 *)(raw + ((j * 4 + q) * 64 + lane) * 4) = make_float4(O[j][4 * q], O[j][4 * q + 1], O[j][4 * q + 2], O[j][4 * q + 3]);
-            *(float2 *)(raw + NT * 1024 + 2 * lane) = make_float2(m_ref, l_run);
+            *(float2 *)(raw + NT * 1024 + 2 * lane) = make_float2(-st.neg_ref, st.l);
         }
         __syncthreads();
         if (wave >= F && !odd) {
             const float2 ml = *(const float2 *)(raw + NT * 1024 + 2 * lane);
-            const float m_new = fmaxf(m_ref, ml.x), m_use = m_new == -INFINITY ? 0.f : m_new;
-            const float a0 = __builtin_amdgcn_exp2f(m_ref - m_use), a1 = __builtin_amdgcn_exp2f(ml.x - m_use);
-            m_ref = m_new;
-            l_run = l_run * a0 + ml.y * a1;
+            const float ref = -st.neg_ref, ref_new = fmaxf(ref, ml.x);
+            const float a0 = __builtin_amdgcn_exp2f(ref - ref_new), a1 = __builtin_amdgcn_exp2f(ml.x - ref_new);
+            st.neg_ref = -ref_new;
+            st.l = st.l * a0 + ml.y * a1;
 #pragma unroll
             for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -1176,7 +1202,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
         }
     }
     if (live && !odd) {
-    l_run = sum_xor32(l_run);
+    const float l_run = sum_xor32(st.l);
     const int64_t prow0 = (SK ? (int64_t)(u + bg) : (int64_t)bg * part.nsplit + sp) * R + r0w;
     const int n_rows = min(32, R - r0w);
     // accumulator element 4q + x of tile j is channel 32j + 8q + 4kg + x of this lane's row.  A wavefront reads back
@@ -1206,7 +1232,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
         const u32x4 x = *(const u32x4 *)(rows + row * TL::kRowPitch + 16 * (lane & 15));
         if (row < n_rows) __builtin_nontemporal_store(x, (u32x4 *)(part.o + (prow0 + row) * 64) + (lane & 15));
     }
-    if (kg == 0 && n < n_rows) *(float2 *)(part.ml + (prow0 + n) * 2) = make_float2(m_ref, l_run);
+    if (kg == 0 && n < n_rows) *(float2 *)(part.ml + (prow0 + n) * 2) = make_float2(st.ref(l_run), l_run);
     if (!SK || share_at >= share_end) SPECPV_CLOCKS_END(part.timeline, (size_t)blockIdx.y * gridDim.x + blockIdx.x, nch);
     }
     if (SK) __syncthreads();   // the next pair's chunks go where the rows were staged

@@ -9,11 +9,12 @@
 // from there into MFMA operand registers.
 //   TG = 8: tiles of 32 rows, one stage per wavefront.  One chunk per wavefront and the call is over in one round trip.
 //   TG = 4: tiles of 64 rows, two stages.
-//   TG = 2: tiles of 128 rows, four stages, three chunks requested up front.  Each K / V byte is pulled by half as many
+//   TG = 2: tiles of 128 rows, four stages, four chunks requested up front.  Each K / V byte is pulled by half as many
 //           workgroups as with TG = 4.
-// What bounds it at one sequence is latency, not a rate: arguments and list 1.5 us, the first chunk 2 us later, then a
-// chain of chunks that a wavefront takes 0.86 us each for when they are there; a ring of two stages refilled at 3 us
-// of loaded latency made that 1.8 us.  The planner (plan_attention) chooses TG and the splits.  Calls of one sequence, 8 KV
+// TG = 4 and 2 take two chunks at a time (score_pair, attend_pair).
+// What bounds it at one sequence is latency, not a rate: arguments and list 1.6 us, the requests (a CU takes 1 KiB per 27
+// cycles, so 128 KiB are 1.6 us) and the first two chunks at 4.3 us, then 1.9 us for every two (0.86 us a chunk and 0.3 us
+// between them when taken one by one).  The planner (plan_attention) chooses TG and the splits.  Calls of one sequence, 8 KV
 // heads at G = 4, in graphs of 16 layers, against tiles of one head's 64 nodes (TG = 4, 8 splits, whatever the node count),
 // side by side on one card: 4096 kept tokens, 60 nodes 17.7 -> 17.2 us (TG = 2, 16 splits; on other cards 17.8 -> 17.6 and
 // 17.8 -> 18.1), 1 node 14.9 -> 11.6 us (TG = 8, 16 splits); 8192 tokens, 60 nodes 31.8 -> 22.5 us; 2048 tokens, 60 nodes
@@ -62,7 +63,6 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
                           Shape s, Partials part, MfmaArgs a, unsigned long long *timeline)
 {
     constexpr int RB = 8 / TG, STG = RB;               // row blocks per workgroup; ring stages per token group
-    constexpr int AHEAD = TG == 2 ? 3 : STG;           // chunks requested in front of the one in use
     constexpr int KOPS = RB == 4 ? 4 : 8;              // K (or V) operations of a chunk that one wavefront issues
     constexpr int OPS = RB == 1 ? 16 : KOPS;           // all operations of a chunk that one wavefront issues
     // the leading scalar arguments repeat what the first round of reads needs: they arrive in registers
@@ -163,9 +163,6 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     const uint32_t vread = ring_addr + 8192u + (uint32_t)(4 * kg + ((lane & 15) >> 2)) * kVPiecePitch +
                            32u * (uint32_t)((lane >> 4) & 1) + 8u * (uint32_t)(lane & 3);   // + stage * kStageBytes
 
-    const int r4 = lane >> 4, pos = lane & 15;
-    const uint32_t sw0 = 16u * (uint32_t)(pos ^ r4), vsw = 16u * (uint32_t)pos;   // K row 4 i + r4: piece pos ^ ((4 i + r4) & 15) = sw0 ^ 64 (i & 3)
-    const uint32_t lane_row_off = (uint32_t)r4 * st2;
     const bool do_k = RB == 1 || rb < RB / 2, do_v = RB == 1 || rb >= RB / 2;   // which half of a chunk this wavefront brings
     const int op0 = RB == 4 ? 4 * (rb & 1) : 0;                                // ... from which operation on
 
@@ -213,7 +210,8 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     // Request this wavefront's share of chunk ci, 1 KiB per operation (one 256-byte row per 16 lanes): K operation i
     // brings rows 4i .. 4i+3, pieces swizzled by row & 15; V operation i brings rows i, i+8, i+16, i+24 into piece i.
     // rows given per lane (t = lane & 31: token tk of the chunk)
-    auto issue_rows = [&](const char *kbase, const char *vbase, const uint32_t stride, const uint32_t tk, char *dst) {
+    auto issue_rows = [&](const char *kbase, const char *vbase, const uint32_t stride, const uint32_t tk, char *dst, const int r4,
+                          const uint32_t sw0, const uint32_t vsw) __attribute__((always_inline)) {
         if (do_k) {
 #pragma unroll
             for (int x = 0; x < KOPS; ++x) {
@@ -231,24 +229,31 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
             }
         }
     };
-    auto issue = [&](int ci) {
+    auto issue = [&](int ci) __attribute__((always_inline)) {
         const int stg = ci & (STG - 1);
         char *dst = my_ring + stg * kStageBytes;
+        // (the lane's offsets are worked out here, from a lane number that the compiler cannot see through: kept over the
+        // loop, with the sums of base and offset that it makes of them, they take registers that the pairs of chunks need)
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const int r4 = ln >> 4, pos = ln & 15, n = ln & 31;
+        const uint32_t sw0 = 16u * (uint32_t)(pos ^ r4), vsw = 16u * (uint32_t)pos;   // K row 4 i + r4: piece pos ^ ((4 i + r4) & 15) = sw0 ^ 64 (i & 3)
+        const uint32_t lane_row_off = (uint32_t)r4 * st2;
         int tok;
         if (PEND && kctx > 0 && (uint32_t)(c0 + ci) >= C_ctx) {
             // a chunk of partially verified tokens: rows of the draft K / V arrays
             const int pr = (int)((uint32_t)(c0 + ci) - C_ctx) * 32 + n;
             const int ptok = pr < kctx ? pr : -1;
             const uint32_t vm = (uint32_t)__ballot(ptok >= 0);
-            vmv = lane == stg ? vm : vmv;
-            issue_rows(kdb, vdb, stp, (uint32_t)max(ptok, 0), dst);
+            vmv = ln == stg ? vm : vmv;
+            issue_rows(kdb, vdb, stp, (uint32_t)max(ptok, 0), dst, r4, sw0, vsw);
             return;
         }
         if (ALIGNED) {
             if (ci - row_base >= 64) fill_rows(ci);
             const int r0 = __builtin_amdgcn_readlane(row0vec, ci - row_base);
             if (r0 >= 0) {
-                vmv = lane == stg ? 0xffffffffu : vmv;
+                vmv = ln == stg ? 0xffffffffu : vmv;
                 const size_t first = (size_t)((uint32_t)r0 * st2);   // fits 32 bits (host-checked)
                 if (st2 == 256u) {
                     // rows are 256 bytes apart (the usual head-major cache): the instruction's
@@ -287,8 +292,8 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
             tok = rows_of.row((uint32_t)(c0 + ci), n);
         }
         const uint32_t vm = (uint32_t)__ballot(tok >= 0);
-        vmv = lane == stg ? vm : vmv;
-        issue_rows(kb, vb, st2, tok >= 0 ? (uint32_t)tok : 0u, dst);   // row 0 exists (L > 0); masked later
+        vmv = ln == stg ? vm : vmv;
+        issue_rows(kb, vb, st2, tok >= 0 ? (uint32_t)tok : 0u, dst, r4, sw0, vsw);   // row 0 exists (L > 0); masked later
     };
 
     if (ALIGNED && nch > 0) fill_rows_first();
@@ -302,7 +307,7 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     SPECPV_STAMP(1);   // arguments, lengths, list, query rows are in
 
     f32x16 O[4];
-    float m_ref = -INFINITY, l_run = 0.f;
+    RowState st;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -320,50 +325,83 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) qf[ks] = as_bf16x8(qraw[ks]);
     };
+    if (0 < nch) issue(0);
+    __builtin_amdgcn_s_barrier();   // the other wavefronts' shares of the query rows have landed, too
+    read_q();
+    if (TG == 2) __builtin_amdgcn_s_barrier();   // the last stages no longer hold query rows
 #pragma unroll
-    for (int c = 0; c < AHEAD; ++c)
+    for (int c = 1; c < STG; ++c)
         if (c < nch) issue(c);
     SPECPV_STAMP(2);   // first chunks requested
-    for (int i = 0; i < nch_max; ++i) {
-        const bool active = i < nch;
+    auto operand_addresses = [&](int stg, uint32_t (&ka)[8]) {
+        const uint32_t k0 = kread + (uint32_t)stg * kStageBytes;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) ka[ks] = k0 ^ (32u * (uint32_t)ks);
+    };
+    auto one_chunk = [&](int i) {   // it has landed
         const int stg = i & (STG - 1);
-        if (i < 4) SPECPV_STAMP(12 + i);   // done with chunk i - 1, about to wait for chunk i
-        // own share of chunk i has landed: the younger groups (at most AHEAD - 1) may stay in flight
-        if (AHEAD >= 3 && i + 2 < nch) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * OPS) : "memory");
-        else if (AHEAD >= 2 && i + 1 < nch) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(OPS) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (RB > 1 || i == 0) __builtin_amdgcn_s_barrier();   // ... and so have the other wavefronts' shares
-        if (i < 4) SPECPV_STAMP(3 + i);   // chunk i has landed
-        if (i == 0) {
-            read_q();
-            if (TG == 2) __builtin_amdgcn_s_barrier();   // the last stages no longer hold query rows
-        }
-        // four stages: the one that chunk i - 1 was read from is free (every wavefront has passed this iteration's barrier)
-        if (TG == 2 && i + AHEAD < nch) issue(i + AHEAD);
+        const uint32_t vmask = (uint32_t)__builtin_amdgcn_readlane((int)vmv, stg);
+        uint32_t ka[8];
         uint4 kf[8];
         uint2 v[16];
-        const uint32_t vmask = (uint32_t)__builtin_amdgcn_readlane((int)vmv, stg);
-        if (active) {
-            const uint32_t k0 = kread + (uint32_t)stg * kStageBytes;
-            const uint32_t ka[8] = {k0, k0 ^ 32u, k0 ^ 64u, k0 ^ 96u, k0 ^ 128u, k0 ^ 160u, k0 ^ 192u, k0 ^ 224u};
-            lds_read_k<0>(ka, kf);
-            lds_read_v<0>(vread + (uint32_t)stg * kStageBytes, v);
+        operand_addresses(stg, ka);
+        lds_read_k<0>(ka, kf);
+        lds_read_v<0>(vread + (uint32_t)stg * kStageBytes, v);
+        if (RB == 1 && i + 1 < nch) issue(i + 1);   // one stage: free as soon as the chunk is in registers
+        attend_chunk(kf, v, qf, vmask, kg, a.scale_log2, O, st);
+    };
+    if constexpr (RB == 1) {
+        for (int i = 0; i < nch; ++i) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (i < 4) SPECPV_STAMP(3 + i);
+            one_chunk(i);
         }
-        if (TG == 4) __builtin_amdgcn_s_barrier();       // both wavefronts of the pair hold chunk i in registers
-        if (TG != 2 && i + AHEAD < nch) issue(i + AHEAD);
-        if (!active) continue;
-
-        attend_chunk(kf, v, qf, vmask, kg, a.scale_log2, O, m_ref, l_run);
+    } else {
+        // Two chunks at a time: one wait, one barrier (two with two stages), one trip to LDS and one test of the maximum.
+        // The token groups' numbers of chunks differ by one at most; nch_max is the workgroup's.
+        auto landed = [&](int i) __attribute__((always_inline)) {   // chunks i, i + 1 (an odd last one: chunk i) are in LDS
+            if (i < 8) SPECPV_STAMP(12 + i / 2);   // about to wait for them
+            // own share; in front of the first two, the two requested behind them may stay in flight
+            if (TG == 2 && i == 0 && nch > 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * OPS) : "memory");
+            else if (TG == 2 && i == 0 && nch > 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(OPS) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();          // ... and the other wavefronts' shares
+            if (i < 8) SPECPV_STAMP(3 + i / 2);
+        };
+        auto request = [&](int i) __attribute__((always_inline)) {
+#pragma unroll 1
+            for (int c = i; c < min(i + 2, nch); ++c) issue(c);
+        };
+        for (int i = 0; i + 1 < nch_max; i += 2) {
+            const int stg = i & (STG - 1);
+            landed(i);
+            const uint32_t vm0 = (uint32_t)__builtin_amdgcn_readlane((int)vmv, stg), vm1 = (uint32_t)__builtin_amdgcn_readlane((int)vmv, stg + 1);
+            const bool both = i + 1 < nch;
+            // four stages: those of the two chunks before are free (the first two pairs were requested up front)
+            if (TG == 2 && i > 0) request(i + 2);
+            uint32_t ka[8];
+            f32x16 S0, S1;
+            uint4 v0[8], v1[8];
+            operand_addresses(stg, ka);
+            if (both) score_pair<0, kStageBytes, 0, kStageBytes>(ka, vread + (uint32_t)stg * kStageBytes, qf, S0, S1, v0, v1);
+            if (TG == 4 && i + 2 < nch_max) {
+                __builtin_amdgcn_s_barrier();      // two stages: both wavefronts of the group hold the chunks in registers
+                request(i + 2);
+            }
+            if (both) attend_pair(S0, S1, v0, v1, vm0, vm1, kg, a.scale_log2, O, st);
+        }
+        if (nch_max & 1) landed(nch_max - 1);
+        if (nch & 1) one_chunk(nch - 1);   // (landed at one of these barriers)
     }
     __syncthreads();   // every wavefront is done with the rings: the epilogue reuses that LDS
     SPECPV_STAMP(7);   // main loop done
 
     // ---- merge the token groups --------------------------------------------------------
     {
-        l_run = sum_xor32(l_run);
+        const float l_run = sum_xor32(st.l);
         const int row = rb * 32 + n;
         if (kg == 0) {
-            ms[tg * (32 * RB) + row] = m_ref;
+            ms[tg * (32 * RB) + row] = st.ref(l_run);
             ls[tg * (32 * RB) + row] = l_run;
         }
         // accumulator element 4q + x of tile j is channel 32j + 8q + 4kg + x of this lane's row
