@@ -14,7 +14,6 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((address_space(3))) void *lds_void_ptr;
 typedef const __attribute__((address_space(1))) void *glb_void_ptr;
 
-constexpr int kOPitch = 132;         // floats per staged output row (128 + 4: conflict-free 16-byte writes)
 // One 32-token chunk in LDS: 8 KiB of K (row-major, 16-byte pieces XOR-swizzled by row & 15: the LDS has 64
 // banks, so the 16 lanes that a 16-byte read serves per cycle must cover all 16 pieces of a 256-byte bank row;
 // with row & 7 the operand reads ran at half the rate) and
@@ -366,10 +365,6 @@ __device__ __forceinline__ uint32_t half_pair(float a, float b)
 {
     const f16x2 hv = {(_Float16)__builtin_amdgcn_fmed3f(a, -65504.f, 65504.f), (_Float16)__builtin_amdgcn_fmed3f(b, -65504.f, 65504.f)};
     return __builtin_bit_cast(uint32_t, hv);
-}
-__device__ __forceinline__ void store_partial_half(float *row, int lane, float a, float b)
-{
-    __builtin_nontemporal_store(half_pair(a, b), (uint32_t *)row + lane);
 }
 
 // max / sum over the two half-wavefronts (lane and lane ^ 32)

@@ -36,6 +36,7 @@
 
 namespace specpv {
 
+constexpr int kOPitch = 132;         // floats per staged output row (128 + 4: conflict-free 16-byte writes)
 constexpr int kStages = 2;           // ring depth per wavefront pair (eight-wavefront kernel)
 constexpr int kRingBytes = 4 * kStages * kStageBytes;
 constexpr int kQStageBytes = 2 * 8 * 1024;   // the query rows of a workgroup's two row blocks as MFMA operands (eight-wavefront kernel)

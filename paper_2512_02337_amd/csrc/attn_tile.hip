@@ -53,7 +53,7 @@ namespace specpv {
 #endif
 
 constexpr int kTileRing = 8 * kStageBytes;
-static_assert(kTileRing == 8 * 32 * kOPitch * (int)sizeof(float), "the merge of the token groups reuses the ring exactly");
+static_assert(kTileRing >= 8 * 16384, "the merge of the token groups reuses the ring");
 
 // PEND: partially verified tokens may stand in front of the tree (s.kctx > 0).
 template <bool ALIGNED, int TG, bool PEND>
@@ -73,7 +73,7 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     float *ms = (float *)lds_raw;            // [TG][32 RB]
     float *ls = ms + 256;                    // [TG][32 RB]
     char *ring = lds_raw + 2048;             // [TG][STG][K 8 KiB | V]
-    float *obuf = (float *)(lds_raw + 2048); // [TG][32 RB][kOPitch], reuses the ring after the main loop
+    char *merge = lds_raw + 2048;            // merge of the token groups: reuses the ring after the main loop
     SPECPV_CLOCKS_BEGIN;
     SPECPV_STAMP(0);   // entry
 
@@ -397,61 +397,81 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     SPECPV_STAMP(7);   // main loop done
 
     // ---- merge the token groups --------------------------------------------------------
+    // A wavefront finishes 64 / TG of the 64 accumulators of its row block's lanes, i.e. 128 / TG channels of 32 rows: it
+    // hands the others over as they lie in its registers, to the token groups that finish them, and takes in the other
+    // groups' share of its own.  (Every group's accumulators as rows through LDS, for eight wavefronts to pick up by row:
+    // twice the bytes each way; 2.2 us from the end of the loop to the stores at the headline shape, 1.5 so.)
+    constexpr int E = 64 / TG, E4 = E / 4;   // accumulators a wavefront finishes; as 16-byte pieces
+    auto piece = [&](int e4) -> float4 { return make_float4(O[e4 >> 2][4 * (e4 & 3)], O[e4 >> 2][4 * (e4 & 3) + 1], O[e4 >> 2][4 * (e4 & 3) + 2], O[e4 >> 2][4 * (e4 & 3) + 3]); };
+    // [row block][finishing group][group][piece][lane]
+    auto slot = [&](int to, int from) -> float4 * { return (float4 *)merge + ((((rb * TG + to) * TG + from) * E4) << 6); };
     {
         const float l_run = sum_xor32(st.l);
-        const int row = rb * 32 + n;
         if (kg == 0) {
-            ms[tg * (32 * RB) + row] = st.ref(l_run);
-            ls[tg * (32 * RB) + row] = l_run;
+            ms[tg * (32 * RB) + rb * 32 + n] = st.ref(l_run);
+            ls[tg * (32 * RB) + rb * 32 + n] = l_run;
         }
-        // accumulator element 4q + x of tile j is channel 32j + 8q + 4kg + x of this lane's row
-        float *dst = obuf + ((size_t)tg * (32 * RB) + row) * kOPitch;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int to = 0; to < TG; ++to)
+            if (to != tg) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *(float4 *)(dst + 32 * j + 8 * q + 4 * kg) = make_float4(O[j][4 * q], O[j][4 * q + 1], O[j][4 * q + 2], O[j][4 * q + 3]);
+                for (int x = 0; x < E4; ++x) slot(to, tg)[64 * x + lane] = piece(to * E4 + x);
+            }
     }
     __syncthreads();
-    constexpr int RPW = 4 * RB;   // rows each wavefront finishes
-    const int64_t prow0 = ((int64_t)bg * part.nsplit + sp) * R + row0 + wave * RPW;
-    const int n_rows = min(RPW, R - row0 - wave * RPW);   // may be negative
-    // weights of the token groups for the rows this wavefront finishes (lane -> row)
-    float wgt[TG], m_row = -INFINITY, l_row = 0.f;
+    float acc[E], m_row = -INFINITY, l_row = 0.f;
     {
-        const int row = wave * RPW + (lane & (RPW - 1));
+        const int row = rb * 32 + n;
         float mw[TG];
 #pragma unroll
         for (int w = 0; w < TG; ++w) { mw[w] = ms[w * (32 * RB) + row]; m_row = fmaxf(m_row, mw[w]); }
         const float m_use = m_row == -INFINITY ? 0.f : m_row;
+        float wgt[TG];
 #pragma unroll
         for (int w = 0; w < TG; ++w) {
             wgt[w] = __builtin_amdgcn_exp2f(mw[w] - m_use);   // 0 for a token group without valid tokens
             l_row = fmaf(ls[w * (32 * RB) + row], wgt[w], l_row);
         }
-    }
-    {
-        // channels 2 lane, 2 lane + 1 of each row, normalised by the row's l
         const float il = l_row > 0.f ? 1.f / l_row : 0.f;
-        float2 acc[RPW];
 #pragma unroll
-        for (int uu = 0; uu < RPW; ++uu) {
-            acc[uu] = make_float2(0.f, 0.f);
+        for (int x = 0; x < E; ++x) acc[x] = 0.f;
 #pragma unroll
-            for (int w = 0; w < TG; ++w) {
-                const float ww = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wgt[w]), uu));   // uniform: no LDS shuffle
-                const float2 x = *(const float2 *)(obuf + ((size_t)w * (32 * RB) + wave * RPW + uu) * kOPitch + 2 * lane);
-                acc[uu].x = fmaf(ww, x.x, acc[uu].x);
-                acc[uu].y = fmaf(ww, x.y, acc[uu].y);
+        for (int w = 0; w < TG; ++w) {
+            const float ww = wgt[w] * il;
+            if (w == tg) {
+#pragma unroll
+                for (int to = 0; to < TG; ++to)
+                    if (to == tg) {
+#pragma unroll
+                        for (int x = 0; x < E; ++x) acc[x] = fmaf(ww, O[(to * E + x) >> 4][(to * E + x) & 15], acc[x]);
+                    }
+            } else {
+#pragma unroll
+                for (int x = 0; x < E4; ++x) {
+                    const float4 y = slot(tg, w)[64 * x + lane];
+                    acc[4 * x] = fmaf(ww, y.x, acc[4 * x]);
+                    acc[4 * x + 1] = fmaf(ww, y.y, acc[4 * x + 1]);
+                    acc[4 * x + 2] = fmaf(ww, y.z, acc[4 * x + 2]);
+                    acc[4 * x + 3] = fmaf(ww, y.w, acc[4 * x + 3]);
+                }
             }
         }
-#pragma unroll
-        for (int uu = 0; uu < RPW; ++uu) {
-            const float ilu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(il), uu));
-            if (uu < n_rows) store_partial_half(part.o + (prow0 + uu) * 64, lane, acc[uu].x * ilu, acc[uu].y * ilu);   // 128 halves per row
-        }
     }
-    if (lane < n_rows && lane < RPW) *(float2 *)(part.ml + (prow0 + lane) * 2) = make_float2(m_row, l_row);
+    // as fp16 through this wavefront's own corner (nobody else reads it: no barrier), so that stores are whole pieces of rows
+    constexpr int RB256 = 256 / TG, PITCH = RB256 + 16, LPR = 16 / TG, RPP = 64 / LPR;   // bytes of a row here; lanes per row, rows per store
+    char *rows = (char *)slot(tg, 0);
+#pragma unroll
+    for (int x = 0; x < E4; ++x)
+        *(uint2 *)(rows + n * PITCH + 16 * x + 8 * kg) = make_uint2(half_pair(acc[4 * x], acc[4 * x + 1]), half_pair(acc[4 * x + 2], acc[4 * x + 3]));
+    const int64_t prow0 = ((int64_t)bg * part.nsplit + sp) * R + row0 + rb * 32;
+    const int n_rows = min(32, R - row0 - rb * 32);   // may be negative
+#pragma unroll
+    for (int x = 0; x < 32 / RPP; ++x) {
+        const int row = RPP * x + lane / LPR;
+        const u32x4 y = *(const u32x4 *)(rows + row * PITCH + 16 * (lane & (LPR - 1)));
+        if (row < n_rows) __builtin_nontemporal_store(y, (u32x4 *)((char *)(part.o + (prow0 + row) * 64) + tg * RB256) + (lane & (LPR - 1)));   // 128 halves per row
+    }
+    if (tg == 0 && kg == 0 && n < n_rows) *(float2 *)(part.ml + (prow0 + n) * 2) = make_float2(m_row, l_row);
     SPECPV_STAMP(8);   // partial stores issued
     SPECPV_CLOCKS_END(timeline, 3072 + ((size_t)blockIdx.y * gridDim.x + blockIdx.x), first_chunk(C, sp * TG + TG) - first_chunk(C, sp * TG));
     // The combine kernel that follows reads the tree's parents and, one trip later, its K / V rows: nobody
