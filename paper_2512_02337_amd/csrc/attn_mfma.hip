@@ -237,7 +237,7 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
     auto fill_rows = [&](int cb) {
         row_base = cb;
         int r = -1;
-        if (cb + lane < nch && (uint32_t)(c0 + cb + lane) < C_ctx) r = rows_of.first_row((uint32_t)(c0 + cb + lane));
+        if (cb + lane < nch && (uint32_t)(c0 + cb + lane) < C_ctx) r = rows_of.first_row<32>((uint32_t)(c0 + cb + lane));
         row0vec = r;
         // wait for the list entries here, inside the rare branch, so that the common path that
         // joins behind it carries no pending load (and no wait on the DMA prefetch)
@@ -253,7 +253,7 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
         const int e0 = __shfl(idv[0], src), e1 = __shfl(idv[1], src), e2 = __shfl(idv[2], src), e3 = __shfl(idv[3], src);
         const int q4 = (int)(slot >> 6);
         const int blk = q4 == 0 ? e0 : (q4 == 1 ? e1 : (q4 == 2 ? e2 : e3));
-        row0vec = (lane < nch && (uint32_t)(c0 + lane) < C_ctx) ? rows_of.encode(blk, p0, slot) : -1;   // p0 < T there: the slot is < cnt
+        row0vec = (lane < nch && (uint32_t)(c0 + lane) < C_ctx) ? rows_of.encode<32>(blk, p0, slot) : -1;   // p0 < T there: the slot is < cnt
     };
 
     uint32_t vmask_st[kStages];   // validity bits of the chunk this wavefront last requested rows for, per stage
@@ -759,7 +759,7 @@ static_assert(group_lds<128>(10) <= 160 * 1024 && group_lds<128>(4) <= 80 * 1024
 // ALU, 62.4 us here (55.1 us with two terms; 67.4 us with three whose differences take a widening and a subtraction each).
 // SK: shares of the chunks of all (sequence, KV head) pairs instead of splits (Partials::stream): a workgroup goes through
 // the one to three pairs that its share touches, one after the other.
-template <int D, bool ALIGNED, int RB, bool SK>
+template <int D, int SPAN, int RB, bool SK>
 __global__ __launch_bounds__(64 * group_waves(RB)) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : (RB > 8 ? 3 : 2), D == 64 ? 4 : (RB > 8 ? 3 : 2))))
 void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
 {
@@ -864,16 +864,18 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     const uint32_t vread1 = D == 128 ? 0u : (vp & 1u) ? vread - 64u : vread + 64u;   // 64 channels: tile 1 (see lds_read_v64)
 
     // ---- chunk -> token rows (see ChunkRows) ---------------------------------------------
-    // ALIGNED (B % 32 == 0): the first rows of the next 64 chunks sit in a register (lane t: chunk row_base + t) and are
+    // SPAN: the first rows of the next 64 runs sit in a register (lane t: run t from chunk row_base on) and are
     // picked with readlane; kPendingChunk: a chunk of partially verified tokens.
     constexpr int kPendingChunk = (int)0x80000000;
-    const ChunkRows rows_of{sel, a.div_B, s.B, nb, L, T};
+    constexpr int RUN = SPAN ? SPAN : 32, RPC = 32 / RUN, CPF = 64 / RPC;   // tokens of a run, runs of a chunk, chunks of 64 runs
+    const ChunkRows rows_of{sel, a.div_B, s.B, nb, min(L, nb * s.B), T};
     int row_base = 0, row0vec = -1;
     auto fill_rows = [&](int cb) {
         row_base = cb;
+        const int c = cb + lane / RPC;
         int r = -1;
-        if (cb + lane < nch && (uint32_t)(c0 + cb + lane) >= C_ctx) r = kPendingChunk;
-        if (cb + lane < nch && (uint32_t)(c0 + cb + lane) < C_ctx) r = rows_of.first_row((uint32_t)(c0 + cb + lane));
+        if (c < nch && (uint32_t)(c0 + c) >= C_ctx) r = kPendingChunk;
+        if (c < nch && (uint32_t)(c0 + c) < C_ctx) r = rows_of.first_row<RUN>((uint32_t)((c0 + cb) * RPC + lane));
         row0vec = r;
         // wait for the list entries here, inside the rare branch, so that the common path that
         // joins behind it carries no pending load (and no wait on the DMA prefetch)
@@ -923,14 +925,31 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
             dma16((o < KOPS ? kbase : vbase) + (tv + op_piece(o, lane_o)), dst + dst_off[t]);
         }
     };
+    // both runs of 16 rows whole: this lane's row of an operation lies in the first or in the second
+    auto request_runs = [&](int r0, int r1, char *dst) __attribute__((always_inline)) {
+        int lane_o = lane;
+        asm volatile("" : "+v"(lane_o));
+#pragma unroll
+        for (int t = 0; t < NOPS; ++t) {
+            if (OPS % W != 0 && t == NOPS - 1 && n_ops != NOPS) continue;
+            const int o = op0 + W * t;
+            const uint32_t run = (uint32_t)(op_row(o, lane_o) < 16 ? r0 : r1 - 16) * st2;   // (modulo 2^32)
+            __builtin_amdgcn_global_load_lds((glb_void_ptr)(src_base[t] + (run + src_off[t])), (lds_void_ptr)(dst + dst_off[t]), 16, 0, kKvAux);
+        }
+    };
     // Stage stg of the ring is a compile-time constant in the loop below (unrolled over the stages).
     auto issue = [&](int ci, int stg) __attribute__((always_inline)) -> uint32_t {
         char *dst = ring + stg * TL::kStage;
         int tok;
-        if (ALIGNED) {
-            if (ci - row_base >= 64) fill_rows(ci);
-            const int r0 = __builtin_amdgcn_readlane(row0vec, ci - row_base);
-            if (r0 >= 0) {
+        if (SPAN) {
+            if (ci - row_base >= CPF) fill_rows(ci);
+            const int r0 = __builtin_amdgcn_readlane(row0vec, RPC * (ci - row_base));
+            const int r1 = SPAN == 16 ? __builtin_amdgcn_readlane(row0vec, RPC * (ci - row_base) + 1) : 0;
+            if (SPAN == 16 && (r0 | r1) >= 0) {
+                request_runs(r0, r1, dst);
+                return 0xffffffffu;
+            }
+            if (SPAN == 32 && r0 >= 0) {
                 const uint32_t row_off = (uint32_t)r0 * st2;   // fits 32 bits (host-checked)
 #pragma unroll
                 for (int t = 0; t < NOPS; ++t)
@@ -949,8 +968,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
                 issue_rows(kdb, vdb, stp, (uint32_t)max(ptok, 0), dst);
                 return (uint32_t)__ballot(ptok >= 0);
             }
-            const int rr = -2 - r0;   // r0 == -1 gives -1
-            tok = (rr >= 0 && rr + n < L) ? rr + n : -1;
+            tok = SPAN == 32 ? rows_of.decode(r0, n) : rows_of.decode(n < 16 ? r0 : r1, n & 15);
         } else {
             if (s.kctx > 0 && (uint32_t)(c0 + ci) >= C_ctx) {
                 const int pr = (int)((uint32_t)(c0 + ci) - C_ctx) * 32 + n;
@@ -969,7 +987,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     bf16x8 qf[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) qf[ks] = as_bf16x8(qraw[ks]);
-    if (ALIGNED && nch > 0) fill_rows(0);
+    if (SPAN && nch > 0) fill_rows(0);
     // from here on only this wavefront's DMA groups (n_ops operations each) are in flight (an
     // instruction the compiler knows, see attn_ctx_mfma_kernel)
     __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -1120,7 +1138,7 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
         // chunks i, i + 1 (even i) into their ring half: what a wavefront executes here is in front of its arithmetic, so the
         // common case, both there and whole, is one test
         auto request = [&](int i) __attribute__((always_inline)) {
-            if (ALIGNED && i + 1 < nch && i + 1 - row_base < 64) {
+            if (SPAN == 32 && i + 1 < nch && i + 1 - row_base < CPF) {
                 const int ra = __builtin_amdgcn_readlane(row0vec, i - row_base), rb2 = __builtin_amdgcn_readlane(row0vec, i + 1 - row_base);
                 if ((ra | rb2) >= 0) {
                     char *dst = ring + (i & 2) * TL::kStage;
@@ -1304,6 +1322,7 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
     const dim3 grid(8 * GR, kind == kAttnGroup ? (a.n_units + 7) / 8 : ((a.n_bg + 7) / 8) * nctx);
     if (grid.y > 65535u) return hipErrorInvalidConfiguration;
     const bool aligned = s.B % 32 == 0;
+    const int span = aligned || !sel_idx ? 32 : (s.B % 16 == 0 ? 16 : 0);   // see ChunkRows
     const size_t lds_split = 2048 + (size_t)max(kRingBytes, 4 * 64 * kOPitch * (int)sizeof(float)) + kQStageBytes;
 #define SPECPV_SET_LDS(KERN, LDS)                                                                      \
         static PerDeviceOnce once;   /* one per kernel instantiation */                               \
@@ -1312,15 +1331,17 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
             return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(LDS)); \
         });                                                                                            \
         if (e0 != hipSuccess) return e0
-#define SPECPV_LAUNCH_GROUP_K(DD, AL, RR, SS)                                                          \
+#define SPECPV_LAUNCH_GROUP_K(DD, SP, RR, SS)                                                          \
     do {                                                                                               \
-        SPECPV_SET_LDS((attn_ctx_mfma_group_kernel<DD, AL, RR, SS>), group_lds<DD>(RR));                \
+        SPECPV_SET_LDS((attn_ctx_mfma_group_kernel<DD, SP, RR, SS>), group_lds<DD>(RR));                \
         hipLaunchKernelGGL(kern, grid, dim3(64 * group_waves(RR)), group_lds<DD>(RR), st, s, p, a);     \
     } while (0)
 #define SPECPV_LAUNCH_GROUP(DD, WW)                                                                    \
     do {                                                                                               \
-        if (aligned) { if (p.stream) SPECPV_LAUNCH_GROUP_K(DD, true, WW, true); else SPECPV_LAUNCH_GROUP_K(DD, true, WW, false); } \
-        else { if (p.stream) SPECPV_LAUNCH_GROUP_K(DD, false, WW, true); else SPECPV_LAUNCH_GROUP_K(DD, false, WW, false); }       \
+        if (p.stream) SPECPV_LAUNCH_GROUP_K(DD, 32, WW, true);   /* (no list) */                       \
+        else if (span == 32) SPECPV_LAUNCH_GROUP_K(DD, 32, WW, false);                                 \
+        else if (span == 16) SPECPV_LAUNCH_GROUP_K(DD, 16, WW, false);                                 \
+        else SPECPV_LAUNCH_GROUP_K(DD, 0, WW, false);                                                  \
     } while (0)
 #define SPECPV_LAUNCH_SPLIT(AL)                                                                        \
     do {                                                                                               \

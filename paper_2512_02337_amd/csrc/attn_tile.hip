@@ -55,8 +55,9 @@ namespace specpv {
 constexpr int kTileRing = 8 * kStageBytes;
 static_assert(kTileRing >= 8 * 16384, "the merge of the token groups reuses the ring");
 
+// SPAN: the rows of a chunk are one run of 32 consecutive ones, two of 16, or, 0, any (see ChunkRows).
 // PEND: partially verified tokens may stand in front of the tree (s.kctx > 0).
-template <bool ALIGNED, int TG, bool PEND>
+template <int SPAN, int TG, bool PEND>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, const int32_t *a_ctx_len,
                           const void *a_q, int a_n_sel, int a_M, int a_Hq, int a_nctx,
@@ -65,6 +66,8 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     constexpr int RB = 8 / TG, STG = RB;               // row blocks per workgroup; ring stages per token group
     constexpr int KOPS = RB == 4 ? 4 : 8;              // K (or V) operations of a chunk that one wavefront issues
     constexpr int OPS = RB == 1 ? 16 : KOPS;           // all operations of a chunk that one wavefront issues
+    constexpr int RUN = SPAN ? SPAN : 32, RPC = 32 / RUN;   // tokens of a run, runs of a chunk
+    constexpr int NID = SPAN == 16 ? 8 : 4;            // registers for the kept list, 64 entries each (smaller blocks, longer lists)
     // the leading scalar arguments repeat what the first round of reads needs: they arrive in registers
     s.ctx_len = a_ctx_len; s.q = a_q; s.M = a_M; s.Hq = a_Hq;
     a.sel_idx = a_sel_idx; a.sel_count = a_sel_count; a.n_sel = a_n_sel;
@@ -101,17 +104,19 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
 
     // Everything whose address only depends on the kernel arguments is requested up
     // front, so that the cold-miss latencies of these small reads overlap: context
-    // length, list length, the kept-block list (up to 256 entries, lane t: entries t, t + 64, ..)
+    // length, list length, the kept-block list (up to 256 or 512 entries, lane t: entries t, t + 64, ..)
     // and the query rows.
     const int32_t *sel = a.sel_idx ? a.sel_idx + (int64_t)bg * a.n_sel : nullptr;
     const uint32_t Bu = (uint32_t)s.B;
     const int L = s.ctx_len[b];
     const int cnt_raw = sel ? a.sel_count[bg] : 0;
-    const bool list_in_regs = ALIGNED && sel && a.n_sel <= 256;
-    int idv[4] = {-1, -1, -1, -1};
+    const bool list_in_regs = SPAN && sel && a.n_sel <= 64 * NID;
+    int idv[NID];
+#pragma unroll
+    for (int x = 0; x < NID; ++x) idv[x] = -1;
     if (list_in_regs) {
 #pragma unroll
-        for (int x = 0; x < 4; ++x)
+        for (int x = 0; x < NID; ++x)
             if (lane + 64 * x < a.n_sel) idv[x] = sel[lane + 64 * x];
     }
     // The query rows of a row block are the same for its TG wavefronts: each brings its share of the eight k-steps
@@ -178,31 +183,35 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     SPECPV_STAMP(9);   // the scalar reads (lengths, list length) are in: the chunk counts are known
 
     // ---- chunk -> token rows (see ChunkRows) ---------------------------------------------
-    // ALIGNED (B % 32 == 0): the first rows of the next 64 chunks of this wavefront sit in a register (lane t: chunk
-    // row_base + t) and are picked with readlane.
-    const ChunkRows rows_of{sel, a.div_B, s.B, nb, L, T};
+    // SPAN: the first rows of the next 64 runs of this wavefront's chunks sit in a register (lane t: run t from chunk
+    // row_base on) and are picked with readlane.
+    const ChunkRows rows_of{sel, a.div_B, s.B, nb, min(L, nb * s.B), T};
     int row_base = 0, row0vec = -1;
     auto fill_rows = [&](int cb) {
         row_base = cb;
+        const int c = cb + lane / RPC;
         int r = -1;
-        if (cb + lane < nch && (uint32_t)(c0 + cb + lane) < C_ctx) r = rows_of.first_row((uint32_t)(c0 + cb + lane));
+        if (c < nch && (uint32_t)(c0 + c) < C_ctx) r = rows_of.first_row<RUN>((uint32_t)((c0 + cb) * RPC + lane));
         row0vec = r;
         // wait for the list entries here, inside the rare branch, so that the common path that
         // joins behind it carries no pending load (and no wait on the DMA prefetch)
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
     };
-    // the first 64 chunks: the list sits in registers (lane t: entries t, t + 64, ...), so this is a
+    // the first 64 runs: the list sits in registers (lane t: entries t, t + 64, ...), so this is a
     // cross-lane read and no second trip to memory
     auto fill_rows_first = [&]() {
         if (!list_in_regs) { fill_rows(0); return; }
-        const uint32_t p0 = (uint32_t)(c0 + lane) * 32u;
+        const uint32_t p0 = (uint32_t)(c0 * RPC + lane) * (uint32_t)RUN;
         const uint32_t slot = a.div_B.div(p0);
-        const int src = (int)(slot & 63u);
-        const int e0 = __shfl(idv[0], src), e1 = __shfl(idv[1], src), e2 = __shfl(idv[2], src), e3 = __shfl(idv[3], src);
-        const int q4 = (int)(slot >> 6);
-        const int blk = q4 == 0 ? e0 : (q4 == 1 ? e1 : (q4 == 2 ? e2 : e3));
-        const int r = rows_of.encode(blk, p0, slot);   // (without a branch around it)
-        row0vec = (lane < nch && (uint32_t)(c0 + lane) < C_ctx) ? r : -1;   // p0 < T there: the slot is < cnt
+        const int src = (int)(slot & 63u), part_of = (int)(slot >> 6);
+        int blk = __shfl(idv[0], src);
+#pragma unroll
+        for (int x = 1; x < NID; ++x) {
+            const int e = __shfl(idv[x], src);
+            blk = part_of == x ? e : blk;
+        }
+        const int r = rows_of.encode<RUN>(blk, p0, slot);   // (without a branch around it)
+        row0vec = (lane / RPC < nch && (uint32_t)(c0 + lane / RPC) < C_ctx && p0 < T) ? r : -1;   // p0 < T: the slot is < cnt
     };
 
     uint32_t vmv = 0u;   // validity words of the chunks in the ring: lane t holds those of stage t
@@ -249,7 +258,29 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
             issue_rows(kdb, vdb, stp, (uint32_t)max(ptok, 0), dst, r4, sw0, vsw);
             return;
         }
-        if (ALIGNED) {
+        if (SPAN == 16) {
+            if (ci - row_base >= 32) fill_rows(ci);
+            const int ra = __builtin_amdgcn_readlane(row0vec, 2 * (ci - row_base)), rb16 = __builtin_amdgcn_readlane(row0vec, 2 * (ci - row_base) + 1);
+            if ((ra | rb16) >= 0) {
+                // both runs whole: K operations 0 .. 3 lie in the first, 4 .. 7 in the second, a V operation has two rows of each
+                vmv = ln == stg ? 0xffffffffu : vmv;
+                if (do_k) {
+#pragma unroll
+                    for (int x = 0; x < KOPS; ++x) {
+                        const int i = op0 + x;
+                        const size_t first = (size_t)((uint32_t)((i < 4 ? ra : rb16) + 4 * (i & 3)) * st2);   // fits 32 bits (host-checked)
+                        dma16(kb + first + (lane_row_off + (sw0 ^ (64u * (uint32_t)(x & 3)))), dst + i * 1024);
+                    }
+                }
+                if (do_v) {
+                    const uint32_t voff = (uint32_t)((r4 < 2 ? ra : rb16) + 8 * (r4 & 1)) * st2 + vsw;
+#pragma unroll
+                    for (int x = 0; x < KOPS; ++x) dma16(vb + (size_t)(uint32_t)(op0 + x) * st2 + voff, dst + 8192 + (op0 + x) * kVPiecePitch);
+                }
+                return;
+            }
+            tok = rows_of.decode(n < 16 ? ra : rb16, n & 15);
+        } else if (SPAN == 32) {
             if (ci - row_base >= 64) fill_rows(ci);
             const int r0 = __builtin_amdgcn_readlane(row0vec, ci - row_base);
             if (r0 >= 0) {
@@ -286,8 +317,7 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
                 }
                 return;
             }
-            const int rr = -2 - r0;   // r0 == -1 gives -1
-            tok = (rr >= 0 && rr + n < L) ? rr + n : -1;
+            tok = rows_of.decode(r0, n);
         } else {
             tok = rows_of.row((uint32_t)(c0 + ci), n);
         }
@@ -296,7 +326,7 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
         issue_rows(kb, vb, st2, tok >= 0 ? (uint32_t)tok : 0u, dst, r4, sw0, vsw);   // row 0 exists (L > 0); masked later
     };
 
-    if (ALIGNED && nch > 0) fill_rows_first();
+    if (SPAN && nch > 0) fill_rows_first();
     // every load above has been consumed here: from now on the only vector-memory
     // operations of this wavefront in flight are its own DMA groups (OPS operations each)
     // (as an instruction the compiler knows, not inline assembly: otherwise it assumes that the
@@ -508,12 +538,13 @@ hipError_t launch_attn_ctx_tile(const Shape &s, const int32_t *sel_idx, const in
     a.div_W = make_fastdiv((uint32_t)(nctx * tg));   // token ranges: one per token group of every split
     const dim3 grid(8 * tiles, (a.n_bg * nctx + 7) / 8);
     if (grid.y > 65535u) return hipErrorInvalidConfiguration;
-    const bool aligned = s.B % 32 == 0, pend = s.kctx > 0;
+    const int span = s.B % 32 == 0 || !sel_idx ? 32 : (s.B % 16 == 0 ? 16 : 0);   // see ChunkRows
+    const bool pend = s.kctx > 0;
     const size_t lds = 2048 + kTileRing + (tg == 2 ? 0 : (8 / tg) * 8192);
-#define SPECPV_LAUNCH(AL, TGV, PE)                                                                                   \
+#define SPECPV_LAUNCH(SP, TGV, PE)                                                                                   \
     do {                                                                                                             \
         static PerDeviceOnce once;   /* one per kernel instantiation */                                             \
-        auto kern = attn_ctx_tile_kernel<AL, TGV, PE>;                                                               \
+        auto kern = attn_ctx_tile_kernel<SP, TGV, PE>;                                                               \
         const hipError_t e0 = once.run([&] {                                                                         \
             return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);    \
         });                                                                                                          \
@@ -523,8 +554,9 @@ hipError_t launch_attn_ctx_tile(const Shape &s, const int32_t *sel_idx, const in
     } while (0)
 #define SPECPV_LAUNCH_TG(TGV)                                                                                        \
     do {                                                                                                             \
-        if (aligned) { if (pend) SPECPV_LAUNCH(true, TGV, true); else SPECPV_LAUNCH(true, TGV, false); }              \
-        else { if (pend) SPECPV_LAUNCH(false, TGV, true); else SPECPV_LAUNCH(false, TGV, false); }                    \
+        if (span == 32) { if (pend) SPECPV_LAUNCH(32, TGV, true); else SPECPV_LAUNCH(32, TGV, false); }               \
+        else if (span == 16) { if (pend) SPECPV_LAUNCH(16, TGV, true); else SPECPV_LAUNCH(16, TGV, false); }          \
+        else { if (pend) SPECPV_LAUNCH(0, TGV, true); else SPECPV_LAUNCH(0, TGV, false); }                            \
     } while (0)
     if (tg == 2) SPECPV_LAUNCH_TG(2);
     else if (tg == 4) SPECPV_LAUNCH_TG(4);
