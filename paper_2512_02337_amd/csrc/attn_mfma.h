@@ -27,24 +27,6 @@ constexpr int kStageBytes = 8192 + 8 * kVPiecePitch;
 constexpr int kKvAux = 2;
 constexpr float kRescaleSlack = 8.f; // the reference max may lag the true max by 2^8
 
-// Exact n / d for 0 <= n < 2^31 with a host-prepared multiplier (no integer divide
-// on the GPU: one takes about forty vector instructions).
-struct FastDiv {
-    uint32_t mul, shift, d;
-    __device__ __forceinline__ uint32_t div(uint32_t n) const { return d == 1 ? n : (__umulhi(n, mul) >> shift); }
-};
-static FastDiv make_fastdiv(uint32_t d)
-{
-    FastDiv f;
-    f.d = d;
-    uint32_t l = 0;
-    while ((1ull << l) < d) ++l;                       // l = ceil(log2 d)
-    if (d <= 1) { f.mul = 0; f.shift = 0; return f; }
-    f.mul = (uint32_t)(((1ull << (31 + l)) + d - 1) / d);   // ceil(2^(31+l) / d) <= 2^32 - 1 for d >= 2
-    f.shift = l - 1;
-    return f;
-}
-
 struct MfmaArgs {
     const int32_t *sel_idx, *sel_count;
     int n_sel;

@@ -12,6 +12,24 @@ namespace specpv {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
+// Exact n / d for 0 <= n < 2^31 with a host-prepared multiplier (no integer divide
+// on the GPU: one takes about forty vector instructions).
+struct FastDiv {
+    uint32_t mul, shift, d;
+    __device__ __forceinline__ uint32_t div(uint32_t n) const { return d == 1 ? n : (__umulhi(n, mul) >> shift); }
+};
+static FastDiv make_fastdiv(uint32_t d)
+{
+    FastDiv f;
+    f.d = d;
+    uint32_t l = 0;
+    while ((1ull << l) < d) ++l;                       // l = ceil(log2 d)
+    if (d <= 1) { f.mul = 0; f.shift = 0; return f; }
+    f.mul = (uint32_t)(((1ull << (31 + l)) + d - 1) / d);   // ceil(2^(31+l) / d) <= 2^32 - 1 for d >= 2
+    f.shift = l - 1;
+    return f;
+}
+
 // Flat view of one call's tensors, passed by value to the kernels.
 struct Shape {
     const void *k, *v;            // context KV, read in place
