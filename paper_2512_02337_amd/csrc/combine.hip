@@ -389,11 +389,14 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
 }
 
 // Two wavefronts per four rows shorten the chain; where the rows fill the chip several times over, one wavefront that does
-// both has fewer instructions in all and less to start.  Partial step, 60 nodes at G = 4, 8 KV heads: one sequence 17.9
-// against 18.4 us, two 23.5 against 23.3, eight 59.1 against 57.6, sixteen 99.4 against 97.5.
+// both has fewer instructions in all and less to start.  The line lies at a wavefront per SIMD (rows / 4 on 4 SIMDs a CU),
+// one wavefront against two below it: full pass over 64K, 78 nodes at G = 4, 8 KV heads (624 fours of rows) 109.1 / 107.2 us,
+// 45K tokens of two sequences at 64 channels, 37 nodes (592) 62.6 / 61.3, partial step, 64 nodes at G = 5 (1024), four
+// layers 81.9 / 79.9, two sequences of 60 nodes (960), four layers 89.6 / 90.0; beyond it: eight sequences 57.6 / 59.1,
+// sixteen 97.5 / 99.4.
 static bool combine_two_waves(const Shape &s)
 {
-    return (int64_t)s.batch * s.Hkv * s.M * ((s.G + 3) / 4) <= 2 * (int64_t)device_cu_count();
+    return (int64_t)s.batch * s.Hkv * s.M * ((s.G + 3) / 4) <= 4 * (int64_t)device_cu_count();
 }
 
 template <typename T, int D>
