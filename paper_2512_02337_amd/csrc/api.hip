@@ -350,13 +350,37 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
     return plan;
 }
 
+// Where a full pass on the group kernel recomputes many summaries, some of its workgroups do that beside the others, and
+// the plan's splits or shares are cut to the CUs that are left: the attention loop runs at the clock that the chip's power
+// allows and leaves a third of the memory's rate unused, the summaries are nothing but reads.  A CU takes in 45 bytes per
+// nanosecond with blocks of 64 (16 KiB in flight per wavefront; smaller blocks have less, and lose: refresh at 64K in blocks
+// of 16 134 us with two launches, 250 or more so), so the two sides end together with a fraction f / (1 + f) of the CUs on the
+// summaries; 0.235 was fitted to the fastest counts: stale refresh of 128K, eight row blocks, 0 / 40 / 48 / 56 / 64
+// workgroups: 202 / 211 / 195 / 193 / 196 us; of 64K, ten: 130 / 120 / 122 / 123 / 124; of 16K + 32K + 48K + 64K, eight:
+// 247 / 264 / 240 / 238 / 239.  Fewer than eight row blocks leave less of the memory's rate.
+static SumArgs side_summaries(const Shape &s, int64_t begin, void *kmax, void *kmin, AttnPlan &plan)
+{
+    const SumArgs none{0, 0, nullptr, nullptr};
+    if (plan.kind != kAttnGroup || s.D != 128 || s.B < 64 || attn_group_blocks(s) < 8 || begin >= s.max_blocks) return none;
+    const int64_t cus = device_cu_count(), parts = attn_group_parts(s), pairs = (int64_t)s.batch * s.Hkv;
+    const int64_t chunks = ((int64_t)s.max_blocks * s.B + 31) / 32, stale = chunks - begin * s.B / 32;
+    if (parts * (plan.stream ? plan.stream : pairs * plan.nsplit) > cus) return none;   // more than one round of workgroups
+    const double f = 0.235 * (double)stale / (attn_group_chunk_us(attn_group_blocks(s)) * (double)(chunks * parts));
+    const int64_t row = 8 * parts, rows = (int64_t)((double)cus * f / (1.0 + f) / (double)row + 0.5);   // of the grid
+    const int64_t left = (cus - rows * row) / parts;
+    if (rows < 1 || left < (plan.stream ? 1 : pairs)) return none;
+    if (plan.stream) plan.stream = (int)(plan.stream < left ? plan.stream : left);
+    else plan.nsplit = (int)(plan.nsplit < left / pairs ? plan.nsplit : left / pairs);
+    return SumArgs{(int)(rows * row), (int)begin, kmax, kmin};
+}
+
 // Process-wide choice of how specpv_partial_verify_attn runs shapes that the eight-wavefront kernel
 // takes (a testing aid, see specpv_debug_set_route).
 static int g_route = 0;
 static unsigned long long *g_timeline = nullptr;   // where instrumented builds (-DSPECPV_TIMELINE) put their time stamps
 
 static int run_attention(const Shape &s_in, const AttnPlan &plan, int dtype, const int32_t *sel_idx, const int32_t *sel_count,
-                         int n_sel, void *out, float *lse, void *workspace, size_t workspace_bytes, hipStream_t st)
+                         int n_sel, void *out, float *lse, void *workspace, size_t workspace_bytes, const SumArgs &sum, hipStream_t st)
 {
     Shape s = s_in;
     // the matrix-core kernels take the partially verified tokens in front of the tree along with the cache
@@ -374,13 +398,13 @@ static int run_attention(const Shape &s_in, const AttnPlan &plan, int dtype, con
     if (fused) {
         Partials p{w.part_o, w.fused_ml, nsplit + 1, 0, 0, nullptr};
         const FusedArgs f{out, lse, w.arrive, route == 3 ? 1 : 0, g_timeline};
-        e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, f, st);
+        e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, f, SumArgs{}, st);
         return e == hipSuccess ? SPECPV_OK : fail_hip(e);
     }
     Partials p{w.part_o, w.part_ml, nsplit, half_partials(s, plan.kind) ? 1 : 0, plan.stream, g_timeline};
     const FusedArgs none{nullptr, nullptr, nullptr, 0, g_timeline};
     if (plan.kind == kAttnSplit) e = launch_attn_ctx_tile(s, sel_idx, sel_count, n_sel, p, plan.tg, g_timeline, st);
-    else if (plan.kind != kAttnGeneric) e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, none, st);
+    else if (plan.kind != kAttnGeneric) e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, none, sum, st);
     else e = launch_attn_ctx_generic(s, dtype, sel_idx, sel_count, n_sel, p, st);
     if (e != hipSuccess) return fail_hip(e);
     e = launch_combine(s, dtype, p, out, lse, st);
@@ -503,7 +527,7 @@ int specpv_partial_verify_attn(const specpv_kv *kv, const specpv_tree *tree, con
     if (sel_idx && n_sel > (1 << 24)) return SPECPV_ELIMIT;
     const Shape s = make_shape(kv, tree);
     const AttnPlan plan = plan_attention(s, kv->dtype, sel_idx ? n_sel : s.max_blocks, !sel_idx, workspace_bytes);
-    return run_attention(s, plan, kv->dtype, sel_idx, sel_count, n_sel, out, lse, workspace, workspace_bytes, (hipStream_t)stream);
+    return run_attention(s, plan, kv->dtype, sel_idx, sel_count, n_sel, out, lse, workspace, workspace_bytes, SumArgs{}, (hipStream_t)stream);
 }
 
 int specpv_partial_verify_attn_static(const specpv_kv *kv, const specpv_tree *tree, const int32_t *sel_idx,
@@ -527,7 +551,7 @@ int specpv_partial_verify_attn_static(const specpv_kv *kv, const specpv_tree *tr
     void *ws = nullptr;
     const hipError_t e = static_scratch(&ws);
     if (e != hipSuccess) return fail_hip(e);
-    return run_attention(s, plan, kv->dtype, sel_idx, sel_count, n_sel, out, lse, ws, (size_t)SPECPV_STATIC_SCRATCH_BYTES, (hipStream_t)stream);
+    return run_attention(s, plan, kv->dtype, sel_idx, sel_count, n_sel, out, lse, ws, (size_t)SPECPV_STATIC_SCRATCH_BYTES, SumArgs{}, (hipStream_t)stream);
 }
 
 int specpv_full_verify_refresh(const specpv_kv *kv, const specpv_tree *tree, void *kmax, void *kmin,
@@ -542,15 +566,17 @@ int specpv_full_verify_refresh(const specpv_kv *kv, const specpv_tree *tree, voi
     if (!kmax || !kmin || !out || !sel_idx || !sel_count) return SPECPV_EINVAL;
     if (((uintptr_t)kmax | (uintptr_t)kmin | (uintptr_t)out) & 15) return SPECPV_EINVAL;
     const Shape s = make_shape(kv, tree);
-    const AttnPlan plan = plan_attention(s, kv->dtype, s.max_blocks, true, workspace_bytes);
+    AttnPlan plan = plan_attention(s, kv->dtype, s.max_blocks, true, workspace_bytes);
     const Workspace w = layout_workspace(s, plan, workspace);
     if (!workspace || workspace_bytes < w.need || (!scores && workspace_bytes < w.scores_need)) return SPECPV_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    if (stale_blk_begin >= 0) {
+    SumArgs sum{};
+    if (stale_blk_begin >= 0) sum = side_summaries(s, stale_blk_begin, kmax, kmin, plan);
+    if (stale_blk_begin >= 0 && sum.wgs == 0) {
         const hipError_t e = launch_summarize(s, kv->dtype, stale_blk_begin, -1, kmax, kmin, st);
         if (e != hipSuccess) return fail_hip(e);
     }
-    rc = run_attention(s, plan, kv->dtype, nullptr, nullptr, 0, out, lse, workspace, workspace_bytes, st);
+    rc = run_attention(s, plan, kv->dtype, nullptr, nullptr, 0, out, lse, workspace, workspace_bytes, sum, st);
     if (rc != SPECPV_OK) return rc;
     return run_select(s, kv->dtype, tree, kmax, kmin, cfg, sel_idx, sel_count, scores ? scores : w.scores, w.arrive, st);
 }

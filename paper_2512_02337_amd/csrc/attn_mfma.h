@@ -34,6 +34,9 @@ struct MfmaArgs {
     int n_units, row_tiles, n_bg;
     int n_row_blocks;   // group kernel: 32-row blocks of a KV head's M * G query rows
     FastDiv div_nsplit, div_hkv, div_B, div_W, div_M;
+    // group kernel: the first sum_rows rows of the grid recompute the summaries of the blocks from sum_begin on
+    int sum_rows, sum_begin;
+    void *kmax, *kmin;
 };
 
 // Which cache rows the 32-token chunks of one (sequence, KV head) cover: chunk c holds tokens 32 c .. 32 c + 31 of the kept

@@ -33,6 +33,7 @@
 // through (full verification of a long context, batches): there a workgroup serves all query heads of a KV head.  Short
 // ranges (the partial verification over a 4K-token cache) run attn_tile.hip.
 #include "attn_mfma.h"
+#include "summarize.h"
 
 namespace specpv {
 
@@ -774,11 +775,27 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     extern __shared__ char lds_raw[];
     char *ring = lds_raw;                  // [kGroupStages][K 8 KiB | V 8 pieces of 1088 B]
 
-    const int xcd = blockIdx.x & 7, wg_part = blockIdx.x >> 3;
-    const int u = blockIdx.y * 8 + xcd;
-    if (u >= a.n_units) return;
     int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if constexpr (D == 128 && SPAN == 32) {
+        if ((int)blockIdx.y < a.sum_rows) {
+            // a workgroup for the summaries: its wavefronts take every n-th of the stale blocks of all pairs
+            const int wgs = a.sum_rows * (int)gridDim.x, n = wgs * W;
+            int at = wave * wgs + (int)blockIdx.y * (int)gridDim.x + (int)blockIdx.x;
+            for (int b = 0; b < s.batch; ++b) {
+                const int L = s.ctx_len[b];
+                const int nb = min(L > 0 ? (int)a.div_B.div((uint32_t)L + (uint32_t)s.B - 1u) : 0, s.max_blocks), stale = max(nb - a.sum_begin, 0);
+                for (int g = 0; g < s.Hkv; ++g) {
+                    for (; at < stale; at += n) summarize_block<bf16_t, D>(s, b, g, a.sum_begin + at, L, a.kmax, a.kmin, lane);
+                    at -= stale;
+                }
+            }
+            return;
+        }
+    }
+    const int xcd = blockIdx.x & 7, wg_part = blockIdx.x >> 3;
+    const int u = ((int)blockIdx.y - (D == 128 && SPAN == 32 ? a.sum_rows : 0)) * 8 + xcd;
+    if (u >= a.n_units) return;
     // this wavefront's row block: rows r0w .. r0w + 31 of the KV head's M * G query rows.  A
     // workgroup may have a wavefront too many (row block counts that do not divide): it brings
     // its share of the chunks and keeps the barriers, but computes and stores nothing.
@@ -1293,7 +1310,7 @@ int attn_group_parts(const Shape &s) { return group_layout(s).parts; }
 int attn_group_blocks(const Shape &s) { return group_layout(s).blocks; }
 
 hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const int32_t *sel_count,
-                                int n_sel, Partials p, int nctx, int kind, const FusedArgs &f, hipStream_t st)
+                                int n_sel, Partials p, int nctx, int kind, const FusedArgs &f, const SumArgs &sum, hipStream_t st)
 {
     if (kind != kAttnSplit && kind != kAttnGroup) return hipErrorInvalidValue;
     if (kind == kAttnSplit && s.D != 128) return hipErrorInvalidValue;
@@ -1301,7 +1318,7 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
     if (fused != (kind == kAttnSplit) || (fused && nctx > 64) || p.nsplit != nctx + (fused ? 1 : 0)) return hipErrorInvalidValue;
     if (p.stream && (kind != kAttnGroup || s.batch > 64 || sel_idx)) return hipErrorInvalidValue;
     const GroupLayout gl = group_layout(s);
-    MfmaArgs a;
+    MfmaArgs a = {};
     a.sel_idx = sel_idx;
     a.sel_count = sel_count;
     a.n_sel = n_sel;
@@ -1319,7 +1336,14 @@ hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const in
     const int GR = kind == kAttnGroup ? gl.parts : s.G * a.row_tiles;
     // group kernel: a unit (sequence, KV head, split) per 8 consecutive x; split kernel: (sequence, KV
     // head) bg on XCD bg % 8 with all its splits and query heads (y = (bg / 8) * nctx + split)
-    const dim3 grid(8 * GR, kind == kAttnGroup ? (a.n_units + 7) / 8 : ((a.n_bg + 7) / 8) * nctx);
+    if (sum.wgs > 0) {
+        if (kind != kAttnGroup || sel_idx || s.D != 128) return hipErrorInvalidValue;
+        a.sum_rows = (sum.wgs + 8 * GR - 1) / (8 * GR);
+        a.sum_begin = sum.begin;
+        a.kmax = sum.kmax;
+        a.kmin = sum.kmin;
+    }
+    const dim3 grid(8 * GR, a.sum_rows + (kind == kAttnGroup ? (a.n_units + 7) / 8 : ((a.n_bg + 7) / 8) * nctx));
     if (grid.y > 65535u) return hipErrorInvalidConfiguration;
     const bool aligned = s.B % 32 == 0;
     const int span = aligned || !sel_idx ? 32 : (s.B % 16 == 0 ? 16 : 0);   // see ChunkRows

@@ -274,9 +274,14 @@ struct FusedArgs {
     unsigned long long *timeline;  // builds with -DSPECPV_TIMELINE: 16 time stamps per workgroup (else unused)
 };
 constexpr size_t kArriveBytes = 64 << 10;   // head of every workspace: 8192 arrival words
+// The summaries that a full pass recomputes on the side (kAttnGroup): workgroups for it, or 0; the blocks from `begin` on.
+struct SumArgs {
+    int wgs, begin;
+    void *kmax, *kmin;
+};
 // p.nsplit: slots per (sequence, head) in the partial arrays = nctx, or nctx + 1 when fused
 hipError_t launch_attn_ctx_mfma(const Shape &s, const int32_t *sel_idx, const int32_t *sel_count,
-                                int n_sel, Partials p, int nctx, int kind, const FusedArgs &f, hipStream_t st);
+                                int n_sel, Partials p, int nctx, int kind, const FusedArgs &f, const SumArgs &sum, hipStream_t st);
 // the kAttnSplit kernel (two-kernel route): tg = 2, 4 or 8 token groups and 256 / tg query rows per workgroup
 hipError_t launch_attn_ctx_tile(const Shape &s, const int32_t *sel_idx, const int32_t *sel_count, int n_sel, Partials p,
                                 int tg, unsigned long long *timeline, hipStream_t st);

@@ -1,0 +1,44 @@
+"""A full pass that recomputes summaries with some of its own workgroups: the summaries are those of the summary kernel to the
+bit, nothing in front of the stale range is touched, and the pass gives what it gives with summaries that are up to date."""
+import pytest
+import torch
+
+import workloads
+from helpers import GpuRun, say
+from test_gpu_parity import SMALL
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("ctx,B,M,Hq,Hkv", [([65536], 64, 60, 32, 8),              # eight row blocks
+                                            ([50001], 64, 60, 16, 4),              # a ragged last block
+                                            ([40000], 128, 75, 16, 4),             # ten row blocks, blocks of 128
+                                            ([32768, 777, 20000, 1], 64, 60, 32, 8),   # shares over a batch
+                                            ([60000], 64, 64, 64, 4)])             # thirty-two row blocks: four workgroups
+@pytest.mark.parametrize("part", [0.0, 0.4, 0.97])
+def test_against_the_summary_kernel(gpu_lib, ctx, B, M, Hq, Hkv, part):
+    say("case", ctx, B, M, Hq, Hkv, part)
+    cfg = dict(SMALL)
+    cfg.update(ctx=ctx, B=B, M=M, Hq=Hq, Hkv=Hkv, k=20, rho=[0.1] * len(ctx))
+    case = workloads.make_case(cfg, seed=59, device=torch.device("cuda"))
+    run = GpuRun(gpu_lib, case)
+    run.summarize()
+    run.refresh(-1)
+    torch.cuda.synchronize()
+    want = [x.clone() for x in (run.kmax, run.kmin, run.out, run.lse, run.sel_idx, run.sel_count)]
+    begin = int(part * case["max_blocks"])
+    for x in (run.kmax, run.kmin):
+        x[:, :, begin:] = -7.0
+    run.out.zero_()
+    run.refresh(begin)
+    torch.cuda.synchronize()
+    for b, L in enumerate(ctx):
+        nb = (L + B - 1) // B
+        assert torch.equal(run.kmax[b, :, :nb], want[0][b, :, :nb]) and torch.equal(run.kmin[b, :, :nb], want[1][b, :, :nb]), "summaries differ"
+        assert (run.kmax[b, :, max(nb, begin):] == -7.0).all(), "written behind the last block"
+    # another number of splits: other sums in fp32 and roundings of the partials to fp16 (2^-11), far below the output's bf16,
+    # so results differ by a unit in their last place at most, which is up to 2^-7 of a value
+    assert (run.out.float() - want[2].float()).abs().max() <= 2.0 ** -7 * want[2].float().abs().max()
+    # (a row's sum runs over weights rounded to bf16, 2^-9, against a reference that follows the splits)
+    assert (run.lse - want[3]).abs().max() <= 2.0 ** -8
+    assert torch.equal(run.sel_idx, want[4]) and torch.equal(run.sel_count, want[5])
