@@ -32,7 +32,8 @@
 // Epilogue: the TG token groups merge their (O, m, l) through LDS and write one split-KV partial per (split, row);
 // combine.hip finishes.
 //
-// grid: x = tile * 8 + xcd, y = (bg / 8) * nsplit + split   with bg = b * Hkv + g and xcd = bg % 8.  Workgroups are
+// grid: x = tile * 8 + xcd, y = (bg / 8) * nsplit + split   with bg = b * Hkv + g and xcd = bg % 8; with 8, 16, 32, ... KV heads
+// y = split, z = bg / 8: the same order without a division, which would wait for the argument block.  Workgroups are
 // handed to the 8 XCDs round-robin in linear order and gridDim.x is a multiple of 8, so a (sequence, KV head) stays on
 // XCD bg % 8 with all its splits and tiles: the K/V bytes of a split come from HBM once and from that XCD's L2 for the
 // other tiles, and the partials of a head are merged on the XCD that wrote them.  Where
@@ -45,8 +46,8 @@ namespace specpv {
 #ifdef SPECPV_TIMELINE
 #define SPECPV_STAMP(i)                                                                                                      \
     do {                                                                                                                     \
-        if (timeline && threadIdx.x == 0 && blockIdx.y * gridDim.x + blockIdx.x < 2048u)                                     \
-            timeline[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 16 + (i)] = __builtin_amdgcn_s_memrealtime();           \
+        const unsigned nth = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;                                 \
+        if (timeline && threadIdx.x == 0 && nth < 2048u) timeline[(size_t)nth * 16 + (i)] = __builtin_amdgcn_s_memrealtime();\
     } while (0)
 #else
 #define SPECPV_STAMP(i) do {} while (0)
@@ -60,7 +61,7 @@ static_assert(kTileRing >= 8 * 16384, "the merge of the token groups reuses the 
 template <int SPAN, int TG, bool PEND>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, const int32_t *a_ctx_len,
-                          const void *a_q, int a_n_sel, int a_M, int a_Hq, int a_nctx,
+                          const void *a_q, int a_n_sel, int a_M, int a_Hq, int a_nctx_groups,
                           Shape s, Partials part, MfmaArgs a, unsigned long long *timeline)
 {
     constexpr int RB = 8 / TG, STG = RB;               // row blocks per workgroup; ring stages per token group
@@ -71,7 +72,7 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     // the leading scalar arguments repeat what the first round of reads needs: they arrive in registers
     s.ctx_len = a_ctx_len; s.q = a_q; s.M = a_M; s.Hq = a_Hq;
     a.sel_idx = a_sel_idx; a.sel_count = a_sel_count; a.n_sel = a_n_sel;
-    const int nctx = a_nctx;
+    const int nctx = a_nctx_groups & 0xffff, groups = a_nctx_groups >> 16;   // splits; head_groups_code
     extern __shared__ char lds_raw[];
     float *ms = (float *)lds_raw;            // [TG][32 RB]
     float *ls = ms + 256;                    // [TG][32 RB]
@@ -82,19 +83,25 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
 
     // ---- which piece of work is this workgroup -------------------------------------
     const int xcd = blockIdx.x & 7, tile = blockIdx.x >> 3;
-    int bg, sp;
-    if ((a.n_bg & 7) == 0) {
-        const int bgh = (int)a.div_nsplit.div(blockIdx.y);
-        sp = (int)blockIdx.y - bgh * nctx;
-        bg = bgh * 8 + xcd;
+    int bg, sp, b, g;
+    if (groups) {
+        // (nothing here waits for a read: the argument block itself takes a trip to memory)
+        b = (int)blockIdx.z >> (groups - 1);
+        g = (((int)blockIdx.z - (b << (groups - 1))) << 3) + xcd;
+        s.Hkv = 4 << groups;
+        s.G = s.Hq >> (groups + 2);
+        bg = b * s.Hkv + g;
+        sp = (int)blockIdx.y;
     } else {
-        const int u = (int)blockIdx.y * 8 + xcd;
-        bg = (int)a.div_nsplit.div((uint32_t)u);
-        sp = u - bg * nctx;
+        // (one division for both orders, without branches: its numbers are then read in here and not at the kernel's entry)
+        const bool whole = (a.n_bg & 7) == 0;
+        const int u = whole ? (int)blockIdx.y : (int)blockIdx.y * 8 + xcd, q = (int)a.div_nsplit.div_straight((uint32_t)u);
+        sp = u - q * nctx;
+        bg = whole ? q * 8 + xcd : q;
+        b = (int)a.div_hkv.div_straight((uint32_t)bg);
+        g = bg - b * s.Hkv;
         if (bg >= a.n_bg) return;
     }
-    const int b = (int)a.div_hkv.div((uint32_t)bg);
-    const int g = bg - b * s.Hkv;
     const int R = s.M * s.G, row0 = tile * (32 * RB);
 
     const int lane = threadIdx.x & 63;
@@ -106,18 +113,22 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     // front, so that the cold-miss latencies of these small reads overlap: context
     // length, list length, the kept-block list (up to 256 or 512 entries, lane t: entries t, t + 64, ..)
     // and the query rows.
-    const int32_t *sel = a.sel_idx ? a.sel_idx + (int64_t)bg * a.n_sel : nullptr;
+    const int32_t *sel = a.sel_idx + (int64_t)bg * a.n_sel;   // (an offset from null where there are no lists: n_sel is 0)
     const uint32_t Bu = (uint32_t)s.B;
-    const int L = s.ctx_len[b];
-    const int cnt_raw = sel ? a.sel_count[bg] : 0;
-    const bool list_in_regs = SPAN && sel && a.n_sel <= 64 * NID;
+    // These go out before the argument block has arrived (one trip to memory by itself): they take only what came in
+    // registers.  The counts are vector loads because scalar ones return in any order, so that using one waits for the
+    // argument block as well.  With the combine kernel's reads done the same way: one layer of 128 k tokens of which 4 k are
+    // attended 16.7 -> 16.4 us, a call over 2 k listed tokens 13.2 -> 12.5 us.
+    const bool list_in_regs = SPAN && a.sel_idx && a.n_sel <= 64 * NID;
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    const int L_v = s.ctx_len[b + zero], cnt_v = (sel ? a.sel_count + bg : s.ctx_len + b)[zero];
     int idv[NID];
+    {
+        const int32_t *list = list_in_regs ? sel : s.ctx_len + b;
+        const int last = list_in_regs ? a.n_sel - 1 : 0;
 #pragma unroll
-    for (int x = 0; x < NID; ++x) idv[x] = -1;
-    if (list_in_regs) {
-#pragma unroll
-        for (int x = 0; x < NID; ++x)
-            if (lane + 64 * x < a.n_sel) idv[x] = sel[lane + 64 * x];
+        for (int x = 0; x < NID; ++x) idv[x] = list[min(lane + 64 * x, last)];   // (past the end: never asked for, slot < cnt <= n_sel)
     }
     // The query rows of a row block are the same for its TG wavefronts: each brings its share of the eight k-steps
     // straight into LDS, laid out as the operands are read (k-step ks: 1 KiB, lane l's 16 bytes at 16 l), and all read
@@ -139,10 +150,15 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
         }
     }
 
+    // the arguments that the chunks need arrive while the reads above are on their way (left to itself the compiler asks for
+    // each where it is first used, one trip to memory after the other)
+    asm volatile("" :: "s"(s.k), "s"(s.v), "s"(s.sb), "s"(s.sh), "s"(s.st), "s"(s.max_blocks), "s"(s.B), "s"(a.div_W.mul), "s"(a.div_W.shift),
+                 "s"(a.div_W.d), "s"(a.div_B.mul), "s"(a.div_B.shift), "s"(a.div_B.d), "s"(s.kd), "s"(s.vd));
+    const int L = __builtin_amdgcn_readfirstlane(L_v);
     int nb = L > 0 ? (int)a.div_B.div((uint32_t)(L + s.B - 1)) : 0;
     if (nb > s.max_blocks) nb = s.max_blocks;
     int cnt = nb;
-    if (sel) cnt = max(0, min(cnt_raw, a.n_sel));
+    if (sel) cnt = max(0, min(__builtin_amdgcn_readfirstlane(cnt_v), a.n_sel));
     const uint32_t T = nb > 0 ? (uint32_t)cnt * Bu : 0u;   // host guarantees max_blocks * B <= 2^30
     // chunks of cache tokens, then the chunks of the partially verified tokens (the first kctx draft nodes: a
     // chain that every query node descends from, so all rows attend all of them, like cache tokens)
@@ -503,7 +519,7 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     }
     if (tg == 0 && kg == 0 && n < n_rows) *(float2 *)(part.ml + (prow0 + n) * 2) = make_float2(m_row, l_row);
     SPECPV_STAMP(8);   // partial stores issued
-    SPECPV_CLOCKS_END(timeline, 3072 + ((size_t)blockIdx.y * gridDim.x + blockIdx.x), first_chunk(C, sp * TG + TG) - first_chunk(C, sp * TG));
+    SPECPV_CLOCKS_END(timeline, 3072 + ((size_t)(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x), first_chunk(C, sp * TG + TG) - first_chunk(C, sp * TG));
     // The combine kernel that follows reads the tree's parents and, one trip later, its K / V rows: nobody
     // has touched those in this call yet.  Ask for them here, on the way out: they are then in this XCD's L2, where that
     // kernel's workgroups of the same KV head run.  Eight lanes per node (four 64-byte pieces of its K row, four of its V
@@ -536,7 +552,9 @@ hipError_t launch_attn_ctx_tile(const Shape &s, const int32_t *sel_idx, const in
     a.div_B = make_fastdiv((uint32_t)s.B);
     a.div_M = make_fastdiv((uint32_t)s.M);
     a.div_W = make_fastdiv((uint32_t)(nctx * tg));   // token ranges: one per token group of every split
-    const dim3 grid(8 * tiles, (a.n_bg * nctx + 7) / 8);
+    int groups = head_groups_code(s.Hkv);
+    if (a.n_bg / 8 > 65535) groups = 0;
+    const dim3 grid(8 * tiles, groups ? nctx : (a.n_bg * nctx + 7) / 8, groups ? a.n_bg / 8 : 1);
     if (grid.y > 65535u) return hipErrorInvalidConfiguration;
     const int span = s.B % 32 == 0 || !sel_idx ? 32 : (s.B % 16 == 0 ? 16 : 0);   // see ChunkRows
     const bool pend = s.kctx > 0;
@@ -549,8 +567,8 @@ hipError_t launch_attn_ctx_tile(const Shape &s, const int32_t *sel_idx, const in
             return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);    \
         });                                                                                                          \
         if (e0 != hipSuccess) return e0;                                                                             \
-        hipLaunchKernelGGL(kern, grid, dim3(512), lds, st, sel_idx, sel_count, s.ctx_len, s.q, n_sel, s.M, s.Hq,     \
-                           nctx, s, p, a, timeline);                                                                 \
+        hipLaunchKernelGGL(kern, grid, dim3(512), lds, st, sel_idx, sel_count, s.ctx_len, s.q, sel_idx ? n_sel : 0, s.M, s.Hq, \
+                           nctx | groups << 16, s, p, a, timeline);                                                         \
     } while (0)
 #define SPECPV_LAUNCH_TG(TGV)                                                                                        \
     do {                                                                                                             \

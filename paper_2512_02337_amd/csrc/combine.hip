@@ -159,12 +159,13 @@ __device__ __forceinline__ float row16_max(float x)
 // partials' wavefront reads first.
 template <typename T, int D, int NP, bool MULTI, int NB, bool HALF, bool TWO>
 __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, const void *a_q, const float *a_po,
-                                                    const float *a_pml, int a_M, int a_Hq, int a_G, int a_nsplit,
+                                                    const float *a_pml, int a_M_Mk, int a_Hq, int a_G, int a_nsplit_groups,
                                                     Shape s, Partials part, void *out, float *lse, float scale_log2)
 {
     // the leading scalar arguments repeat what the first round of reads needs; they can be preloaded into registers
-    s.parent = a_parent; s.q = a_q; s.M = a_M; s.Hq = a_Hq; s.G = a_G;
-    part.o = const_cast<float *>(a_po); part.ml = const_cast<float *>(a_pml); part.nsplit = a_nsplit;
+    s.parent = a_parent; s.q = a_q; s.M = a_M_Mk & 0xff; s.Mk = a_M_Mk >> 8; s.Hq = a_Hq; s.G = a_G;
+    part.o = const_cast<float *>(a_po); part.ml = const_cast<float *>(a_pml); part.nsplit = a_nsplit_groups & 0xffff;
+    const int groups = a_nsplit_groups >> 16;   // head_groups_code
     constexpr int CPL = D / 16;   // channels per lane: d = (lane & 15) * CPL + x
     typedef typename Chan<T, CPL>::Raw Raw;
     __shared__ float tree_od[TWO ? 4 : 1][CPL / 4][64][4];   // [four heads][channels, four at a time][lane]
@@ -174,12 +175,18 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
     // x = XCD (workgroups go to the XCDs round-robin in linear order), y = node, z = bg / 8: the rows
     // of (sequence, KV head) bg are merged on XCD bg % 8, where the split kernel produced them
     const int bg = (int)blockIdx.z * 8 + (int)blockIdx.x;
-    if (bg >= s.batch * s.Hkv) return;
+    int b;
+    if (groups) {   // (nothing here waits for the argument block)
+        b = (int)blockIdx.z >> (groups - 1);
+        s.Hkv = 4 << groups;
+    } else {
+        if (bg >= s.batch * s.Hkv) return;
+        b = bg / s.Hkv;
+    }
     const int j = (int)blockIdx.y;
-    const int b = bg / s.Hkv;
     // wavefronts 0 .. n - 1: the tree segments of four query heads each; n .. 2n - 1: their partials.  A group size that is
     // no multiple of four leaves lanes that repeat the last head and store nothing
-    const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nq = TWO ? (int)(blockDim.x >> 7) : 0;
+    const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nq = TWO ? (s.G + 3) >> 2 : 0;   // (blockDim.x is read from memory)
     const bool tree_role = wave < nq;
     const int quad = TWO && !tree_role ? wave - nq : wave;
     const int g = bg - b * s.Hkv, hh = quad * 4 + (lane >> 4);
@@ -204,6 +211,7 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
     int a8[NB];
     Raw kd8[NB], vd8[NB];
     auto tree_rows = [&]() __attribute__((always_inline)) {
+        asm volatile("" :: "s"(s.kd), "s"(s.vd));   // read now, while the parents are on their way, not where they are first used
         root_path(j + s.koff, s.Mk, s.kctx, par0, par1, anc_lo, anc_hi);
         if (wave == 0) SPECPV_CSTAMP(1, 0);   // parents in, root path walked
 #pragma unroll
@@ -403,6 +411,7 @@ template <typename T, int D>
 static void launch_combine_t(const Shape &s, Partials p, void *out, float *lse, hipStream_t st)
 {
     const bool two = combine_two_waves(s);
+    const int groups = head_groups_code(s.Hkv);
     dim3 grid(8, s.M, (s.batch * s.Hkv + 7) / 8), block((two ? 128 : 64) * ((s.G + 3) / 4));
     const float scale_log2 = kLog2e / sqrtf((float)s.D);
     // fp16 partials: bf16 at 128 channels; the other element types and head dims have fp32 ones
@@ -410,9 +419,9 @@ static void launch_combine_t(const Shape &s, Partials p, void *out, float *lse, 
 #define SPECPV_LAUNCH_K(NP, MULTI, NB, HALF)                                                                              \
     do {                                                                                                                \
         if (two) hipLaunchKernelGGL((combine_kernel<T, D, NP, MULTI, NB, HALF, true>), grid, block, 0, st, s.parent, s.q, (const float *)p.o, \
-                                    (const float *)p.ml, s.M, s.Hq, s.G, p.nsplit, s, p, out, lse, scale_log2);           \
+                                    (const float *)p.ml, s.M | s.Mk << 8, s.Hq, s.G, p.nsplit | groups << 16, s, p, out, lse, scale_log2);           \
         else hipLaunchKernelGGL((combine_kernel<T, D, NP, MULTI, NB, HALF, false>), grid, block, 0, st, s.parent, s.q, (const float *)p.o, \
-                                (const float *)p.ml, s.M, s.Hq, s.G, p.nsplit, s, p, out, lse, scale_log2);               \
+                                (const float *)p.ml, s.M | s.Mk << 8, s.Hq, s.G, p.nsplit | groups << 16, s, p, out, lse, scale_log2);               \
     } while (0)
 #define SPECPV_LAUNCH_H(NP, MULTI, NB)                                                                                   \
     do {                                                                                                                \

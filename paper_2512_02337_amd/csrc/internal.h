@@ -17,6 +17,12 @@ constexpr float kLn2 = 0.6931471805599453f;
 struct FastDiv {
     uint32_t mul, shift, d;
     __device__ __forceinline__ uint32_t div(uint32_t n) const { return d == 1 ? n : (__umulhi(n, mul) >> shift); }
+    // the same without a branch: its three numbers are then read where it stands, not at the kernel's entry
+    __device__ __forceinline__ uint32_t div_straight(uint32_t n) const
+    {
+        const uint32_t q = __umulhi(n, mul) >> shift;
+        return d == 1 ? n : q;
+    }
 };
 static FastDiv make_fastdiv(uint32_t d)
 {
@@ -48,6 +54,16 @@ struct Shape {
     // and the draft-tree segment (combine kernel, single-kernel route) stops its root paths there.
     int kctx;
 };
+
+// How the kernels of one short call find their piece of work without waiting for their argument block: where a sequence has
+// 8, 16, 32, ... KV heads, grid z counts groups of eight of them (KV head g on XCD g % 8, which is blockIdx.x % 8), and a shift
+// that arrives in a register with the leading arguments does the rest.  0: no such number; else 1 + log2(Hkv / 8).
+static inline int head_groups_code(int Hkv)
+{
+    for (int sh = 0; sh < 16; ++sh)
+        if (Hkv == 8 << sh) return 1 + sh;
+    return 0;
+}
 
 // Split-KV partial results of the context part, one per (b, g, split, row), row hh * M + j of KV head g being node j of
 // its query head hh (the single-kernel route keeps its own order, [batch, Hq, nsplit, M]: it reads them back itself):
