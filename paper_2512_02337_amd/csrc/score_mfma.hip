@@ -135,6 +135,7 @@ struct ScoreArgs {
     float *scores;
     int reduce, last_node;
     int row0, rows;       // the query rows that count lie in row0 .. rows - 1 (row0: a multiple of 32)
+    int waves;            // of a workgroup
     int tiles, groups;    // tiles of a workgroup; workgroups of a (sequence, KV head)
     int sums;             // partial sums per tile and lane: one per block of 32 rows, blocks 16 apart share one
     int by_xcd;           // Hkv % 8 == 0: grid (groups * 8, Hkv / 8, batch), KV head g on XCD g % 8; else (groups, Hkv, batch)
@@ -163,12 +164,15 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const ScoreArgs &a, 
     extern __shared__ __attribute__((aligned(1024))) char score_smem[];
     char *tile = score_smem;
     float *red = (float *)(score_smem + a.tiles * TILE);   // [a.sums][tile][lane]
-    const int lane = threadIdx.x & 63, W = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, W = a.waves;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, kg = lane >> 5;
     const int i0 = group * 32 * a.tiles;
     const int R = s.M * s.G;
-    const int L = s.ctx_len[b];   // one sequence: only needed at the very end, its latency overlaps with everything else
+    // a vector load: a scalar one would hold up whoever waits for an argument.  One sequence: only needed at the very end
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    const int L_v = s.ctx_len[b + zero];
     // query rows r0 .. r0 + 31 as A operand: lane = row (every wavefront has at least one such block)
     int r0 = a.row0 + wave * 32;
     bf16x8 q[KS];
@@ -180,6 +184,7 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const ScoreArgs &a, 
         for (int ks = 0; ks < KS; ++ks) q[ks] = __builtin_bit_cast(bf16x8, *(const uint4 *)(qrow + ks * 16));
     };
     auto blocks = [&]() -> int {
+        const int L = __builtin_amdgcn_readfirstlane(L_v);
         const int nb = L > 0 ? (int)a.div_B.div((uint32_t)L + (uint32_t)s.B - 1u) : 0;
         return min(nb, s.max_blocks);
     };
@@ -195,11 +200,12 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const ScoreArgs &a, 
     {
         const int rl = lane / LPR, pos = lane % LPR;
         const int64_t arr_row0 = ((int64_t)b * s.Hkv + g) * s.max_blocks;
+        const uintptr_t to_min = (uintptr_t)a.kmin - (uintptr_t)a.kmax;   // (chosen as pointers, they are read from memory on every turn)
         for (int d = wave; d < 2 * OPS * n_t; d += W) {
             const int i = d & (OPS - 1), row = RPO * i + rl, t = d / (2 * OPS);
             const int blk = min(i0 + 32 * t + row, s.max_blocks - 1);
             const int piece = pos ^ (D == 128 ? row & 15 : (row >> 1) & 7);
-            const char *src = (const char *)((d & OPS) ? a.kmin : a.kmax) + ((arr_row0 + blk) * D) * 2 + 16 * piece;
+            const char *src = (const char *)((uintptr_t)a.kmax + ((d & OPS) ? to_min : 0)) + ((arr_row0 + blk) * D) * 2 + 16 * piece;
             __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(tile + (d / OPS) * HALF + i * 1024), 16, 0, 2);   // streaming hint: read once
         }
     }
@@ -299,6 +305,13 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const ScoreArgs &a, 
 template <int D, bool BOUND, int P>
 __global__ __launch_bounds__(64 * kScoreMaxWaves) void score_mfma_kernel(Shape s, ScoreArgs a, TopkArgs ta, unsigned long long *arrive, int wstride)
 {
+    // every argument in one trip to memory; left to itself the compiler asks for each where it is first used
+    asm volatile("" :: "s"(s.M), "s"(s.G), "s"(s.Hq), "s"(s.Hkv), "s"(s.B), "s"(s.batch), "s"(s.max_blocks), "s"(s.q), "s"(s.ctx_len),
+                 "s"(a.kmax), "s"(a.kmin), "s"(a.scores), "s"(a.reduce), "s"(a.last_node), "s"(a.row0), "s"(a.rows), "s"(a.sums), "s"(a.tiles));
+    asm volatile("" :: "s"(a.waves), "s"(a.groups), "s"(a.by_xcd), "s"(a.div_G.mul), "s"(a.div_G.shift), "s"(a.div_G.d),
+                 "s"(a.div_B.mul), "s"(a.div_B.shift), "s"(a.div_B.d));
+    if constexpr (P != 0)
+        asm volatile("" :: "s"(arrive), "s"(wstride), "s"(ta.ns), "s"(ta.nr), "s"(ta.k), "s"(ta.n_row), "s"(ta.sel_idx), "s"(ta.sel_count));
     const int group = a.by_xcd ? (int)blockIdx.x >> 3 : (int)blockIdx.x;
     const int g = a.by_xcd ? (int)blockIdx.y * 8 + ((int)blockIdx.x & 7) : (int)blockIdx.y, b = blockIdx.z;
     score_tiles<D, BOUND, P != 0>(s, a, group, g, b);
@@ -375,6 +388,7 @@ hipError_t launch_scores_mfma(const Shape &s, const void *kmax, const void *kmin
     const int per_cu = 16 / waves < 8 ? 16 / waves : 8, most = waves > 4 ? kScoreMostTiles : (waves > 2 ? 2 : 1);
     int64_t T = (total + per_cu * cus - 1) / (per_cu * cus);
     T = T < 1 ? 1 : (T > most ? most : T);
+    a.waves = waves;
     a.tiles = (int)T;
     a.sums = blocks32 < kScoreSums ? blocks32 : kScoreSums;
     a.groups = (int)((tiles1 + T - 1) / T);
