@@ -250,6 +250,10 @@ __global__ __launch_bounds__(256) void gather_blocks_kernel(Shape s, const int32
     constexpr int LPR = D / E;
     constexpr int RPP = 256 / LPR;
     const int g = blockIdx.y, b = blockIdx.z;
+    // every argument in one trip to memory; left to itself the compiler asks for each where it is first used (four layers of
+    // 128 k tokens, 4 k of them copied: 34.7 us, now 33.9)
+    asm volatile("" :: "s"(s.k), "s"(s.v), "s"(s.sb), "s"(s.sh), "s"(s.st), "s"(s.ctx_len), "s"(s.Hkv), "s"(s.B), "s"(s.max_blocks), "s"(sel_idx),
+                 "s"(sel_count), "s"(n_sel), "s"(parts), "s"(out_k), "s"(out_v));
     const int L = s.ctx_len[b];
     int nb = L > 0 ? (L + s.B - 1) / s.B : 0;
     if (nb > s.max_blocks) nb = s.max_blocks;
