@@ -207,7 +207,7 @@ __device__ __forceinline__ void lds_read_v(uint32_t addr, uint2 (&v)[16])
 // four bits); a register is read into again only behind the matrix instruction that was its last reader; "s_nop 11": the
 // twelve wait states between a 32x32x16 product and the vector ALU's read of it, which the compiler does not count in here.
 // With the single test of the maximum for both (attend_pair), core cycles per chunk of the full pass over 128K tokens, eight
-// row blocks: 2033 -> 1780.  The chip runs that loop at the clock its power allows (1.4 to 1.9 GHz), so a workgroup's 128
+// row blocks: 2033 -> 1800.  The chip runs that loop at the clock its power allows (1.4 to 1.9 GHz), so a workgroup's 128
 // chunks went from 138 - 150 us to 126 - 139, not in proportion.  Tried as well: the two wavefronts of a SIMD passing the
 // barrier at different points of this (2110), one of them requesting behind its scores (1890), wave priorities (no change).
 template <int K0, int K1, int V0, int V1>

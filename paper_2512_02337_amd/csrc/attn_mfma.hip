@@ -717,7 +717,7 @@ void attn_ctx_mfma_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
 // with a period of four chunks, 2033 with two; 1400 for the requests and barriers alone (timing probe), 1024 for
 // the matrix instructions.
 // Where every wavefront has a row block to itself and 256 registers (128 channels, four or eight row blocks), the two
-// chunks of a ring half are worked on together (score_pair, attend_pair): 1780 cycles per chunk.
+// chunks of a ring half are worked on together (score_pair, attend_pair): 1800 cycles per chunk.
 constexpr int kGroupPeriod = 2;                  // chunks between two workgroup barriers
 constexpr int kGroupStages = 2 * kGroupPeriod;   // two halves
 // One 32-token chunk in LDS.  128 channels: as above (kStageBytes).  64 channels: 4 KiB of K (128-byte rows, 16-byte

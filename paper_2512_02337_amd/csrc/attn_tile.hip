@@ -196,7 +196,7 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     const int c0 = first_chunk(C, wsid), c1 = first_chunk(C, wsid + 1);
     const int nch = c1 - c0;
     const int nch_max = first_chunk(C, sp * TG + 1) - first_chunk(C, sp * TG);   // token group 0 has the most
-    SPECPV_STAMP(9);   // the scalar reads (lengths, list length) are in: the chunk counts are known
+    SPECPV_STAMP(9);   // lengths and list length are in: the chunk counts are known
 
     // ---- chunk -> token rows (see ChunkRows) ---------------------------------------------
     // SPAN: the first rows of the next 64 runs of this wavefront's chunks sit in a register (lane t: run t from chunk

@@ -31,7 +31,7 @@ import workloads   # noqa: E402
 
 POINTS = ["entry", "arguments, lengths, list ids, query rows in", "first chunks requested (one kernel: draft rows done)",
           "chunk 0 landed (two kernels: chunks 0 and 1)", "chunk 1 landed (chunks 2 and 3)", "chunk 2 landed (4 and 5)", "chunk 3 landed (6 and 7)", "chunk loop done",
-          "partials stored (issued)", "two kernels: lengths and list length in (scalar reads) | one kernel: stores acknowledged", "one kernel: arrival known",
+          "partials stored (issued)", "two kernels: lengths and list length in | one kernel: stores acknowledged", "one kernel: arrival known",
           "one kernel: merged and stored (last workgroup of a tile)",
           "wavefront 0 starts to wait for chunk 0 (two kernels: 0 and 1)", "... for chunk 1 (2 and 3), done with those before", "... for chunk 2 (4 and 5)", "... for chunk 3 (6 and 7)"]
 
