@@ -119,7 +119,7 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     // registers.  The counts are vector loads because scalar ones return in any order, so that using one waits for the
     // argument block as well.  With the combine kernel's reads done the same way: one layer of 128 k tokens of which 4 k are
     // attended 16.7 -> 16.4 us, a call over 2 k listed tokens 13.2 -> 12.5 us.
-    const bool list_in_regs = SPAN && a.sel_idx && a.n_sel <= 64 * NID;
+    const bool list_in_regs = SPAN && a.sel_idx && (uint32_t)(a.n_sel - 1) < 64u * NID;   // (a list may have no room at all)
     int zero = 0;
     asm volatile("" : "+v"(zero));
     const int L_v = s.ctx_len[b + zero], cnt_v = (sel ? a.sel_count + bg : s.ctx_len + b)[zero];
