@@ -42,3 +42,26 @@ def test_against_the_summary_kernel(gpu_lib, ctx, B, M, Hq, Hkv, part):
     # (a row's sum runs over weights rounded to bf16, 2^-9, against a reference that follows the splits)
     assert (run.lse - want[3]).abs().max() <= 2.0 ** -8
     assert torch.equal(run.sel_idx, want[4]) and torch.equal(run.sel_count, want[5])
+
+
+@pytest.mark.parametrize("over", [dict(ctx=[65536]), dict(ctx=[30000, 777, 20000, 1]), dict(ctx=[9001], B=32, M=37, D=64),
+                                  dict(ctx=[2048], B=16, M=16, Hq=4, Hkv=1, D=64, dtype="f32")], ids=["long", "batch", "64 channels", "fp32"])
+def test_a_refresh_and_the_calls_it_stands_for(gpu_lib, over):
+    """Without stale summaries every result has the bits of the separate calls; with them, everything but out and lse."""
+    say("case", over)
+    cfg = dict(SMALL, B=64, M=60, Hq=32, Hkv=8, k=20)
+    cfg.update(over, rho=[0.1] * len(over["ctx"]))
+    case = workloads.make_case(cfg, seed=61, device=torch.device("cuda"))
+    run = GpuRun(gpu_lib, case)
+    run.summarize(); run.attend(None, None); run.select()
+    torch.cuda.synchronize()
+    results = lambda: [x.clone() for x in (run.kmax, run.kmin, run.scores, run.sel_idx, run.sel_count, run.out, run.lse)]
+    want = results()
+    for stale in (-1, 0, case["max_blocks"] // 2):
+        for x in (run.out, run.lse, run.scores, run.sel_idx, run.sel_count):
+            x.zero_()
+        run.refresh(stale)
+        torch.cuda.synchronize()
+        got = results()
+        for a, b in zip(got if stale < 0 else got[:5], want):
+            assert torch.equal(a, b), (stale, a.shape)
