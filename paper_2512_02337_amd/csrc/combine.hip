@@ -396,21 +396,33 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
     if (wave == nq) SPECPV_CSTAMP(4, nq);   // stored (issued)
 }
 
-// Two wavefronts per four rows shorten the chain; where the rows fill the chip several times over, one wavefront that does
-// both has fewer instructions in all and less to start.  The line lies at a wavefront per SIMD (rows / 4 on 4 SIMDs a CU),
-// one wavefront against two below it: full pass over 64K, 78 nodes at G = 4, 8 KV heads (624 fours of rows) 109.1 / 107.2 us,
-// 45K tokens of two sequences at 64 channels, 37 nodes (592) 62.6 / 61.3, partial step, 64 nodes at G = 5 (1024), four
-// layers 81.9 / 79.9, two sequences of 60 nodes (960), four layers 89.6 / 90.0; beyond it: eight sequences 57.6 / 59.1,
-// sixteen 97.5 / 99.4.
-static bool combine_two_waves(const Shape &s)
+// Two wavefronts per four rows shorten the chain; one that does both has less to start.  What decides is the partials: with
+// more than eight they are the longer half, and two wavefronts are faster however many rows there are; with eight or fewer
+// the tree segment is, and two pay only while the chip has room for every workgroup's extra wavefronts at once.  Whole calls
+// in graphs, one wavefront / two, us (8 KV heads at G = 4 unless stated; workgroups = sequences * KV heads * nodes):
+//   more than eight splits: 16, 480 workgroups 16.45 / 16.18, 1920 51.7 / 51.0; 32, 480 17.9 / 16.2, 1440 77.2 / 76.1; full pass
+//   in shares, 1920 workgroups 87.4 / 86.0, 7680 at G = 5 216 / 206; fp32, 32 splits, 1920 workgroups at 128 channels 222 / 204;
+//   eight or fewer, up to four heads a KV head: 192 workgroups 12.22 / 11.73 (eight) and 11.62 / 11.33 (four), 320 12.42 / 12.35
+//   and 11.83 / 12.07, 480 12.70 / 12.83 and 11.92 / 12.23, 960 20.78 / 20.79 and 12.79 / 12.90, 1920 37.7 / 37.3 and 22.0 / 22.2,
+//   3840 (planned) 34.7 / 36.3: the line at a workgroup per CU;
+//   ... more heads, where one workgroup has several fours of rows that share what they read: G = 5, 480 workgroups 19.68 / 19.15
+//   (eight) and 12.79 / 12.59 (four), 640 13.14 / 13.32 (four), 960 17.07 / 17.14; G = 16, 480 19.1 / 18.5 and 16.8 / 16.6: two
+//   workgroups per CU.
+// Partially verified tokens in front of the tree that the context kernel has left to the tree segment (fp32) make that long
+// enough to be worth a wavefront of its own up to one per SIMD: 16 of them, 64 channels, eight splits, 296 fours of rows 18.4 /
+// 17.3, 960 29.6 / 27.8, 1920 45.4 / 46.4; two splits 17.9 / 18.3 (960), 21.3 / 27.8 (1920), at 128 channels 47.2 / 44.4, 56 / 70.
+static bool combine_two_waves(const Shape &s, const Partials &p)
 {
-    return (int64_t)s.batch * s.Hkv * s.M * ((s.G + 3) / 4) <= 4 * (int64_t)device_cu_count();
+    if (p.stream || p.nsplit > 8) return true;
+    const int64_t wgs = (int64_t)s.batch * s.Hkv * s.M, fours = (s.G + 3) / 4, cus = device_cu_count();
+    if (s.koff > s.kctx) return wgs * fours <= 4 * cus;
+    return wgs <= (fours > 1 ? 2 : 1) * cus;
 }
 
 template <typename T, int D>
 static void launch_combine_t(const Shape &s, Partials p, void *out, float *lse, hipStream_t st)
 {
-    const bool two = combine_two_waves(s);
+    const bool two = combine_two_waves(s, p);
     const int groups = head_groups_code(s.Hkv);
     dim3 grid(8, s.M, (s.batch * s.Hkv + 7) / 8), block((two ? 128 : 64) * ((s.G + 3) / 4));
     const float scale_log2 = kLog2e / sqrtf((float)s.D);
