@@ -99,11 +99,13 @@ static Shape make_shape(const specpv_kv *kv, const specpv_tree *tree)
 }
 
 // What a call with bf16 at 128 channels would take, in microseconds, with one of the matrix-core kernels and `ns` splits,
-// less what does not depend on that choice.  The constants were fitted to whole calls in graph replays; against 1578 other
-// timings (130 shapes: 1 to 78 nodes, G = 2, 4, 5 and 8, 2 to 128 (sequence, KV head) pairs, 512 to 131072 attended tokens;
-// profiles/plan_timings) the model is 8 % off, root mean square, and the plan it chooses 1.2 % slower than the fastest
-// measured one in the mean, 14 % at most.  Taking the fewest partials among plans that the model holds within 1, 2, 4 or
-// 6 % of the best: 1.1, 1.3, 1.4, 1.9 %, so the best it is.  A workgroup per CU at a time takes its token range, p
+// less what does not depend on that choice.  The constants were fitted to whole calls in graph replays, of kernels that took
+// a chunk at a time; against 1578 other timings of today's (130 shapes: 1 to 78 nodes, G = 2, 4, 5 and 8, 2 to 128 (sequence,
+// KV head) pairs, 512 to 131072 attended tokens; profiles/plan_timings) the model is 8 % off, root mean square, and the plan
+// it chooses 0.9 % (one card) and 1.4 % (another) slower than the fastest measured one in the mean, 13 and 19 % at most.
+// Pairs of chunks took up to 12 % of the cycles of some of the loops; the constants per chunk cut by 5 or 10 %, together and
+// one by one, choose plans that lose 1.3 to 2.6 % where these lose 1.4.  Taking the fewest partials among plans that the
+// model holds within 1, 2, 4 or 6 % of the best: 1.4, 1.5, 1.6, 2.2 %, so the best it is.  A workgroup per CU at a time takes its token range, p
 // chunks one after the other, in `rounds`; besides that the K / V bytes have to come out of the L2s (once per tile) and
 // of HBM; partials are written and read back.
 struct AttnCost {
@@ -282,8 +284,8 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             const int blocks = attn_group_blocks(s);
             // AttnCost takes every sequence to be as long as the longest.  The group kernel, below, evens out the lengths of
             // a full pass; the tile kernel, which a few nodes may be faster with, does not.  24 nodes at G = 4, 16 sequences
-            // of 16K (512 chunks), 8 KV heads, tile kernel against shares: equal lengths 190 / 210 us, 1/16 to 16/16 of it
-            // 152 / 127, one long and fifteen short ones 141 / 50; four sequences of 8K (256 chunks): 35 / 39, 32 / 35, 30 / 28.
+            // of 16K (512 chunks), 8 KV heads, tile kernel against shares: equal lengths 203 / 209 us, 1/16 to 16/16 of it
+            // 159 / 124, one long and fifteen short ones 144 / 47; four sequences of 258 chunks: 37 / 43, 34 / 34, 30 / 25.
             const bool uneven = full && s.batch > 1 && chunks > 256;
             double best = -1.0, best_tile = -1.0;
             int64_t ns_tile = 1;
@@ -310,10 +312,10 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
         }
         plan.nsplit = (int)ns;
         // The sequences of a batch may differ in length, and the lengths live on the device: for a full pass the group
-        // kernel's workgroups take equal shares of all chunks.  (Before, four times as many splits as fill the chip evened
-        // that out, at the price of as many partials: full pass over 32K + 64K + 96K + 128K tokens at G = 5, 64 nodes:
-        // attention 510 us and combine 51 us with the splits, 525 and 15 us with the shares.)  Up to 1024 tokens there is
-        // nothing to even out.
+        // kernel's workgroups take equal shares of all chunks.  (Four times as many splits as fill the chip even that out
+        // too, at the price of as many partials: full pass over 32K + 64K + 96K + 128K tokens at G = 5, 64 nodes, attention
+        // and combine: 563 us with the splits that fill the chip, 462 with four times as many, 453 with the shares.)  Up to
+        // 1024 tokens there is nothing to even out.
         if (full && s.batch > 1 && s.batch <= 64 && plan.kind == kAttnGroup && chunks > 32 && (int64_t)s.batch * s.Hkv * chunks < ((int64_t)1 << 30)) {
             const int64_t pairs = (int64_t)s.batch * s.Hkv, R = (int64_t)s.M * s.G;
             int64_t wgs = cus * (s.D == 64 ? 2 : 1) / parts;
@@ -333,8 +335,10 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
         }
         // ... and for more sequences than the shares are worked out for, about eight workgroups per CU, 64 chunks or more
         // each, for the hardware to deal out.  100 sequences of 16K, 4 KV heads, 60 nodes at G = 4, with the model's three
-        // splits / with six: equal lengths 1090 / 1050 us, 1/100 to 100/100 of it 580 / 580, one long to fifteen short ones
-        // 310 / 255; 128 of 16K, 2 KV heads, 24 nodes, one split / eight: 459 / 380, 354 / 233, 345 / 115.
+        // splits / with six: equal lengths 968 / 1004 us, 1/100 to 100/100 of it 539 / 550, one long and the others a
+        // sixteenth of it 186 / 169; 72 of 32K, one KV head at G = 8, seven / fifteen: 613 / 670, 360 / 369, 147 / 121; 128 of
+        // 16K, 2 KV heads, 24 nodes, one split / two (eight would not fit the static array): 408 / 336, 313 / 232, 292 / 166.
+        // What equal lengths lose is less than what one long sequence among short ones gains.
         if (full && s.batch > 64 && plan.kind == kAttnGroup) {
             int64_t c = (8 * cus + base - 1) / base;
             if (c > 64) c = 64;

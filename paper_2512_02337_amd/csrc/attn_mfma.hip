@@ -1291,7 +1291,8 @@ static GroupLayout group_layout(const Shape &s)
 {
     GroupLayout g{(s.G * s.M + 31) / 32, 0, 0};
     // the fewest microseconds per chunk for all row blocks (attn_group_chunk_us; a part also pulls the chunk
-    // through its L2; full pass over 128K tokens at eight row blocks: 212 us with one workgroup of eight, 224 with two of four)
+    // through its L2; full pass over 128K tokens, 8 KV heads, the best of 16 and 32 splits: eight row blocks in one workgroup
+    // 148 us, in two of four 159; ten in one 177, in two of six 219, in two of eight 245; four in one 105, in two of two 112)
     double best = -1.0;
     for (int blocks = 2; blocks <= (s.D == 128 ? 10 : 8); blocks += 2) {
         const int parts = (g.n_row_blocks + blocks - 1) / blocks;

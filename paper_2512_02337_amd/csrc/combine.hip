@@ -8,8 +8,8 @@
 // two and a few hundred dependent instructions (a wavefront by itself issues one per eight cycles), and the two chains
 // have nothing in common until the last step.  Up to 16 partials are requested at once, 16 bytes per lane each, and a
 // lane works out the weights of its own partials only.  One sequence, 60 nodes, 8 KV heads at G = 4 (kernel trace,
-// medians): 4.9 us with 8 splits, 4.8 with 16, 7 with 32 (full pass); one wavefront that fetched eight partials a round
-// in 8-byte pieces and kept every (m, l) pair in every lane took 4.8 us with 8 splits and 14.4 with 32.
+// medians): 4.8 us with 16 splits, 6.6 - 7.4 with 32 (full pass), and 4.1 with 8 in one wavefront; one wavefront that fetched
+// eight partials a round in 8-byte pieces and kept every (m, l) pair in every lane took 4.8 us with 8 splits and 14.4 with 32.
 // (A tree segment on the matrix cores, dense over 32 nodes with a bit mask, was slower: a call 18.6 us with 8 splits.)
 #include "internal.h"
 #include <type_traits>
