@@ -4,12 +4,17 @@
 // partials of the context part by their log-sum-exp weights, normalise and store.
 // Sixteen lanes per output row (a lane owns D / 16 adjacent channels), four query heads of
 // one KV group per wavefront: they share the node, its root path and the draft K / V rows.
-// TWO: two wavefronts per four rows, one for the tree segment and one for the partials: each is a chain of a round trip or
-// two and a few hundred dependent instructions (a wavefront by itself issues one per eight cycles), and the two chains
-// have nothing in common until the last step.  Up to 16 partials are requested at once, 16 bytes per lane each, and a
-// lane works out the weights of its own partials only.  One sequence, 60 nodes, 8 KV heads at G = 4 (kernel trace,
-// medians): 4.8 us with 16 splits, 6.6 - 7.4 with 32 (full pass), and 4.1 with 8 in one wavefront; one wavefront that fetched
-// eight partials a round in 8-byte pieces and kept every (m, l) pair in every lane took 4.8 us with 8 splits and 14.4 with 32.
+// What bounds it is a chain: a trip for the parents, one for the draft rows that they name, and the sums, which a wavefront by
+// itself issues at one instruction per eight cycles.  The root path is therefore walked with two instructions a node (a lane
+// holds where the path goes on from its node, and that is the node itself where it ends: no test, no branch, no bit set), and
+// TWO: two wavefronts per four rows.  One takes the first four nodes of the path, the other the partials and the next four:
+// each has its rows under way while it works on what is there, and they meet in one exchange through LDS.  With more than
+// sixteen partials those are the longer half, and the first one takes all eight.  Up to 16 partials are requested at once, 16
+// bytes per lane each, and a lane works out the weights of its own partials only.  In-kernel stamps at one sequence, 60 nodes,
+// 8 KV heads at G = 4, 16 splits, us from entry: path walked 0.7, first half of the tree done 1.6, stored 2.4; with a bit set
+// of the path, taken apart again node by node, and the whole tree in one wavefront 1.0, 2.4 and 3.2.  Whole calls in a graph
+// of 16 layers 15.37 -> 14.71 us (one card) and 16.69 -> 16.02 (another); fp32, 16 nodes, four launches 18.8 -> 16.3.  A third
+// wavefront for the second half took another 0.8 %, and has no place at eight heads a KV head and more.
 // (A tree segment on the matrix cores, dense over 32 nodes with a bit mask, was slower: a call 18.6 us with 8 splits.)
 #include "internal.h"
 #include <type_traits>
@@ -195,78 +200,106 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
     const int64_t qrow = (((int64_t)b * s.M + j) * s.Hq + h) * D;
     if (wave == 0) SPECPV_CSTAMP(0, 0);   // entry
 
-    // ---- draft-tree segment: first the reads that only need the arguments, then the root path and its rows, then the sums ----
-    int par0 = -1, par1 = -1;
+    // ---- draft-tree segment: the node itself and its ancestors, path slot 0, 1, ... ------------------------------------
+    // With two wavefronts, the tree's takes the first NA slots and whatever comes behind the NB, the partials' the others.
+    // (More than 16 partials: the second half in the partials' wavefront costs it registers, 126 -> 160, and a full pass over
+    // 32K + 64K + 96K + 128K tokens at G = 5 459 -> 456 us without it.)
+    constexpr int NA = TWO && NB == 8 && !MULTI ? 4 : NB;
+    int par0 = 0, par1 = 0;   // where the path goes on from nodes lane and lane + 64: to the node itself where it ends
     Raw qraw;
     auto tree_first = [&]() __attribute__((always_inline)) {
         // the tree has s.Mk nodes; query row j is node j + s.koff (the nodes in front are keys only)
         const int32_t *par = s.parent + (int64_t)b * s.Mk;
-        if (lane < s.Mk) par0 = par[lane];
-        if (lane + 64 < s.Mk) par1 = par[lane + 64];
+        par0 = par[min(lane, s.Mk - 1)];
+        if (s.Mk > 64) par1 = par[min(lane + 64, s.Mk - 1)];
         Chan<T, CPL>::load(s.q, qrow + d0, qraw);
     };
-    unsigned long long anc_lo = 0ull, anc_hi = 0ull;
     const int64_t drow0 = (((int64_t)b * s.Mk) * s.Hkv + g) * D + d0;
     const int drow_step = s.Hkv * D;   // (Mk <= 128 rows: 32-bit offsets)
-    int a8[NB];
-    Raw kd8[NB], vd8[NB];
-    auto tree_rows = [&]() __attribute__((always_inline)) {
-        asm volatile("" :: "s"(s.kd), "s"(s.vd));   // read now, while the parents are on their way, not where they are first used
-        root_path(j + s.koff, s.Mk, s.kctx, par0, par1, anc_lo, anc_hi);
-        if (wave == 0) SPECPV_CSTAMP(1, 0);   // parents in, root path walked
+    int at = j + s.koff, last = -1;    // next slot's node; the slot's before it (the same: the path has ended)
+    // N slots: a[u] is a node, bias[u] 0, or -inf behind the path's end (a[u] then repeats its last node)
+    auto walk = [&](auto count, int *a, float *bias) __attribute__((always_inline)) {
+        constexpr int N = decltype(count)::value;
+        auto steps = [&](auto next) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            a8[u] = pop_node(anc_lo, anc_hi);
-            const int64_t drow = drow0 + max(a8[u], 0) * drow_step;
+            for (int u = 0; u < N; ++u) {
+                a[u] = at;
+                bias[u] = at == last ? -INFINITY : 0.f;
+                last = at;
+                at = next(at);
+            }
+        };
+        if (s.Mk <= 64) steps([&](int x) { return __builtin_amdgcn_readlane(par0, x); });
+        else steps([&](int x) { const int lo = __builtin_amdgcn_readlane(par0, x & 63), hi = __builtin_amdgcn_readlane(par1, x & 63); return x < 64 ? lo : hi; });
+    };
+    int a8[NB];
+    float bias[NB];
+    Raw kd8[NB], vd8[NB];
+    auto rows = [&](auto from, auto count) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = decltype(from)::value; u < decltype(from)::value + decltype(count)::value; ++u) {
+            const int64_t drow = drow0 + a8[u] * drow_step;
             Chan<T, CPL>::load(s.kd, drow, kd8[u]);
             Chan<T, CPL>::load(s.vd, drow, vd8[u]);
         }
     };
-    float m = -INFINITY, l = 0.f, od[CPL];   // the node itself and its ancestors
+    auto tree_path = [&]() __attribute__((always_inline)) {
+        asm volatile("" :: "s"(s.kd), "s"(s.vd));   // read now, while the parents are on their way, not where they are first used
+        // nodes below kctx (partially verified tokens that the context kernels have attended already) end a path, and so does
+        // a malformed parent[] (not strictly decreasing)
+        par0 = par0 >= s.kctx && par0 < lane ? par0 : lane;
+        if (s.Mk > 64) par1 = par1 >= s.kctx && par1 < lane + 64 ? par1 : lane + 64;
+        walk(std::integral_constant<int, NB>{}, a8, bias);
+    };
+    float m = -INFINITY, l = 0.f, od[CPL];
 #pragma unroll
     for (int x = 0; x < CPL; ++x) od[x] = 0.f;
-    auto tree_sums = [&]() __attribute__((always_inline)) {
-        // online softmax over four nodes (slots without a node have a[u] < 0 and weigh nothing)
-        auto four = [&](const int *a, const Raw *kdv, const Raw *vdv) __attribute__((always_inline)) {
-            float z[4];
+    // online softmax over four slots, the first of which holds a node
+    auto four = [&](const float *bi, const Raw *kdv, const Raw *vdv, auto first) __attribute__((always_inline)) {
+        float z[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) z[u] = a[u] >= 0 ? row16_sum(Chan<T, CPL>::dot(qraw, kdv[u])) * scale_log2 : -INFINITY;
-            const float m_new = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), m);
-            const float m_use = m_new == -INFINITY ? 0.f : m_new;
+        for (int u = 0; u < 4; ++u) z[u] = fmaf(row16_sum(Chan<T, CPL>::dot(qraw, kdv[u])), scale_log2, bi[u]);
+        float m_new = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
+        if (!decltype(first)::value) m_new = fmaxf(m_new, m);
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;
+        if (!decltype(first)::value) {
             const float alpha = __builtin_amdgcn_exp2f(m - m_use);
             l *= alpha;
 #pragma unroll
             for (int x = 0; x < CPL; ++x) od[x] *= alpha;
+        }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float pe = __builtin_amdgcn_exp2f(z[u] - m_use);   // 0 for the unused slots
-                l += pe;
-                float vf[CPL];
-                Chan<T, CPL>::unpack(vdv[u], vf);
+        for (int u = 0; u < 4; ++u) {
+            const float pe = __builtin_amdgcn_exp2f(z[u] - m_use);   // 0 for the unused slots
+            l += pe;
+            float vf[CPL];
+            Chan<T, CPL>::unpack(vdv[u], vf);
 #pragma unroll
-                for (int x = 0; x < CPL; ++x) od[x] = fmaf(pe, vf[x], od[x]);
-            }
-            m = m_new;
-        };
-        four(a8, kd8, vd8);
+            for (int x = 0; x < CPL; ++x) od[x] = fmaf(pe, vf[x], od[x]);
+        }
+        m = m_new;
+    };
+    typedef std::integral_constant<int, 0> I0;
+    typedef std::integral_constant<int, 4> I4;
+    typedef std::integral_constant<int, 8> I8;
+    // slots 0 .. NA - 1, and those behind the NB
+    auto tree_sums = [&]() __attribute__((always_inline)) {
+        four(bias, kd8, vd8, std::true_type{});
 #pragma unroll
-        for (int u = 4; u < NB; u += 4)
-            if (a8[u] >= 0) four(a8 + u, kd8 + u, vd8 + u);
-        while (anc_lo | anc_hi) {   // longer paths (partially verified tokens in front of the tree): 8 per trip
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                a8[u] = pop_node(anc_lo, anc_hi);
-                const int64_t drow = drow0 + max(a8[u], 0) * drow_step;
-                Chan<T, CPL>::load(s.kd, drow, kd8[u]);
-                Chan<T, CPL>::load(s.vd, drow, vd8[u]);
-            }
-            four(a8, kd8, vd8);
-            if (a8[4] >= 0) four(a8 + 4, kd8 + 4, vd8 + 4);
+        for (int u = 4; u < NA; u += 4)
+            if (bias[u] == 0.f) four(bias + u, kd8 + u, vd8 + u, std::false_type{});
+        while (at != last) {   // longer paths: 8 per trip
+            walk(I8{}, a8, bias);
+            rows(I0{}, I8{});
+            four(bias, kd8, vd8, std::false_type{});
+            if (bias[4] == 0.f) four(bias + 4, kd8 + 4, vd8 + 4, std::false_type{});
         }
     };
     if (TWO && tree_role) {
         tree_first();
-        tree_rows();
+        tree_path();
+        if (wave == 0) SPECPV_CSTAMP(1, 0);   // parents in, root path walked
+        rows(I0{}, std::integral_constant<int, NA>{});
         tree_sums();
 #pragma unroll
         for (int x = 0; x < CPL / 4; ++x) *(float4 *)tree_od[quad][x][lane] = make_float4(od[4 * x], od[4 * x + 1], od[4 * x + 2], od[4 * x + 3]);
@@ -313,8 +346,8 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
         if constexpr (N >= 4) { add(r[2], row_bcast<O + 2>(wk)); add(r[3], row_bcast<O + 3>(wk)); }
         if constexpr (N >= 8) { add(r[4], row_bcast<O + 4>(wk)); add(r[5], row_bcast<O + 5>(wk)); add(r[6], row_bcast<O + 6>(wk)); add(r[7], row_bcast<O + 7>(wk)); }
     };
-    typedef std::integral_constant<int, 0> I0;
-    typedef std::integral_constant<int, 8> I8;
+    bool more = false;   // two wavefronts: the path goes beyond the other one's slots
+    if (!TWO || NA < NB) tree_first();   // (in front of the partials: reads are waited for in their order)
     for (int s0 = 0;; s0 += 16 * KM) {   // 16 KM partials at a time (one trip, but for a pair with more than 64)
         float2 ml[KM];
 #pragma unroll
@@ -324,9 +357,16 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
         }
         P ra[NP];
         fetch(s0, ra);
-        if (!TWO && s0 == 0) {
-            tree_first();
-            tree_rows();
+        if (s0 == 0 && (!TWO || NA < NB)) {
+            tree_path();
+            if constexpr (!TWO) {
+                rows(I0{}, I4{});
+                if (NB > 8) rows(I4{}, std::integral_constant<int, NB - 4>{});
+                else if (bias[4] == 0.f) rows(I4{}, I4{});
+            } else {
+                more = bias[NA] == 0.f;
+                if (more) rows(std::integral_constant<int, NA>{}, std::integral_constant<int, NB - NA>{});
+            }
         }
         float m_new = -INFINITY;
 #pragma unroll
@@ -369,14 +409,17 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
     }
     if (wave == nq) SPECPV_CSTAMP(2, nq);   // context partials in and merged
     if (TWO) {
+        if (NA < NB && more) four(bias + NA, kd8 + NA, vd8 + NA, std::true_type{});
         __syncthreads();
-        const float2 tml = tree_ml[quad][lane];
-        m = tml.x;
-        l = tml.y;
+        const float2 tml = tree_ml[quad][lane];   // (its maximum is finite: the node itself is on its path)
+        const float m_tree = fmaxf(m, tml.x), w0 = __builtin_amdgcn_exp2f(m - m_tree), w1 = __builtin_amdgcn_exp2f(tml.x - m_tree);
+        m = m_tree;
+        l = fmaf(l, w0, tml.y * w1);
 #pragma unroll
         for (int x = 0; x < CPL / 4; ++x) {
             const float4 v = *(const float4 *)tree_od[quad][x][lane];
-            od[4 * x] = v.x; od[4 * x + 1] = v.y; od[4 * x + 2] = v.z; od[4 * x + 3] = v.w;
+            od[4 * x] = fmaf(od[4 * x], w0, v.x * w1); od[4 * x + 1] = fmaf(od[4 * x + 1], w0, v.y * w1);
+            od[4 * x + 2] = fmaf(od[4 * x + 2], w0, v.z * w1); od[4 * x + 3] = fmaf(od[4 * x + 3], w0, v.w * w1);
         }
     } else {
         tree_sums();
@@ -399,18 +442,19 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
 // Two wavefronts per four rows shorten the chain; one that does both has less to start.  What decides is the partials: with
 // more than eight they are the longer half, and two wavefronts are faster however many rows there are; with eight or fewer
 // the tree segment is, and two pay only while the chip has room for every workgroup's extra wavefronts at once.  Whole calls
-// in graphs, one wavefront / two, us (8 KV heads at G = 4 unless stated; workgroups = sequences * KV heads * nodes):
-//   more than eight splits: 16, 480 workgroups 16.45 / 16.18, 1920 51.7 / 51.0; 32, 480 17.9 / 16.2, 1440 77.2 / 76.1; full pass
-//   in shares, 1920 workgroups 87.4 / 86.0, 7680 at G = 5 216 / 206; fp32, 32 splits, 1920 workgroups at 128 channels 222 / 204;
-//   eight or fewer, up to four heads a KV head: 192 workgroups 12.22 / 11.73 (eight) and 11.62 / 11.33 (four), 320 12.42 / 12.35
-//   and 11.83 / 12.07, 480 12.70 / 12.83 and 11.92 / 12.23, 960 20.78 / 20.79 and 12.79 / 12.90, 1920 37.7 / 37.3 and 22.0 / 22.2,
-//   3840 (planned) 34.7 / 36.3: the line at a workgroup per CU;
-//   ... more heads, where one workgroup has several fours of rows that share what they read: G = 5, 480 workgroups 19.68 / 19.15
-//   (eight) and 12.79 / 12.59 (four), 640 13.14 / 13.32 (four), 960 17.07 / 17.14; G = 16, 480 19.1 / 18.5 and 16.8 / 16.6: two
-//   workgroups per CU.
+// in graphs as they are planned, one wavefront / two, us (8 KV heads at G = 4 unless stated; workgroups = sequences * KV heads *
+// nodes):
+//   eight or fewer splits, up to four heads a KV head: 192 workgroups 11.2 / 10.8, 256 12.0 / 11.8, 384 12.8 / 12.8, 480 12.9 /
+//   12.9, 960 16.2 / 16.1, 1920 21.9 / 21.8, 3840 33.0 / 33.8; fp32, 192 40.5 / 34.2: the line at a workgroup per CU;
+//   ... more heads, where one workgroup has several fours of rows that share what they read: G = 5, 480 workgroups 19.5 / 19.0,
+//   960 27.5 / 27.6, 1920 40.6 / 40.3; two KV heads at G = 8, 240 18.8 / 17.9, 960 29.7 / 29.7: two workgroups per CU;
+//   more than eight (kernels of before, which took the whole tree in one wavefront): 16, 480 workgroups 16.45 / 16.18, 1920
+//   51.7 / 51.0; 32, 480 17.9 / 16.2, 1440 77.2 / 76.1; full pass in shares, 1920 workgroups 87.4 / 86.0, 7680 at G = 5 216 / 206;
+//   fp32, 32 splits, 1920 workgroups at 128 channels 222 / 204.
 // Partially verified tokens in front of the tree that the context kernel has left to the tree segment (fp32) make that long
-// enough to be worth a wavefront of its own up to one per SIMD: 16 of them, 64 channels, eight splits, 296 fours of rows 18.4 /
-// 17.3, 960 29.6 / 27.8, 1920 45.4 / 46.4; two splits 17.9 / 18.3 (960), 21.3 / 27.8 (1920), at 128 channels 47.2 / 44.4, 56 / 70.
+// enough to be worth a wavefront of its own up to one per SIMD (kernels of before): 16 of them, 64 channels, eight splits, 296
+// fours of rows 18.4 / 17.3, 960 29.6 / 27.8, 1920 45.4 / 46.4; two splits 17.9 / 18.3 (960), 21.3 / 27.8 (1920), at 128
+// channels 47.2 / 44.4, 56 / 70.
 static bool combine_two_waves(const Shape &s, const Partials &p)
 {
     if (p.stream || p.nsplit > 8) return true;
