@@ -2,8 +2,8 @@
 // head) attend over the draft-tree segment (the node itself and its ancestors,
 // tree decode of Algorithm 1) on the vector ALU, merge that with the split-KV
 // partials of the context part by their log-sum-exp weights, normalise and store.
-// Sixteen lanes per output row (a lane owns D / 16 adjacent channels), four query heads of
-// one KV group per wavefront: they share the node, its root path and the draft K / V rows.
+// Sixteen lanes per output row (a lane owns D / 16 adjacent channels), four query heads of one KV group per wavefront, which
+// share the node, its root path and the draft K / V rows; or, PACK, any four rows of the KV head.
 // What bounds it is a chain: a trip for the parents, one for the draft rows that they name, and the sums, which a wavefront by
 // itself issues at one instruction per eight cycles.  The root path is therefore walked with two instructions a node (a lane
 // holds where the path goes on from its node, and that is the node itself where it ends: no test, no branch, no bit set), and
@@ -162,7 +162,7 @@ __device__ __forceinline__ float row16_max(float x)
 // HALF: the partials' O rows are fp16 and normalised (see Partials); else fp32 sums.
 // part.stream > 0 (MULTI only): the number and the place of a pair's partials follow from the sequence lengths, which the
 // partials' wavefront reads first.
-template <typename T, int D, int NP, bool MULTI, int NB, bool HALF, bool TWO>
+template <typename T, int D, int NP, bool MULTI, int NB, bool HALF, bool TWO, bool PACK>
 __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, const void *a_q, const float *a_po,
                                                     const float *a_pml, int a_M_Mk, int a_Hq, int a_G, int a_nsplit_groups,
                                                     Shape s, Partials part, void *out, float *lse, float scale_log2)
@@ -188,15 +188,25 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
         if (bg >= s.batch * s.Hkv) return;
         b = bg / s.Hkv;
     }
-    const int j = (int)blockIdx.y;
-    // wavefronts 0 .. n - 1: the tree segments of four query heads each; n .. 2n - 1: their partials.  A group size that is
-    // no multiple of four leaves lanes that repeat the last head and store nothing
-    const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nq = TWO ? (s.G + 3) >> 2 : 0;   // (blockDim.x is read from memory)
+    // wavefronts 0 .. n - 1: the tree segments of four rows each; n .. 2n - 1: their partials.  Lanes without a row (PACK: past
+    // the last one; else a group size that is no multiple of four) repeat the last one and store nothing
+    const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nq = TWO ? (PACK ? 1 : (s.G + 3) >> 2) : 0;   // (blockDim.x is read from memory)
     const bool tree_role = wave < nq;
     const int quad = TWO && !tree_role ? wave - nq : wave;
-    const int g = bg - b * s.Hkv, hh = quad * 4 + (lane >> 4);
-    const bool live = hh < s.G;
-    const int hc = live ? hh : s.G - 1, h = g * s.G + hc;
+    const int g = bg - b * s.Hkv;
+    int j = (int)blockIdx.y, hc;   // query row and head of the lane's sixteen
+    bool live;
+    if constexpr (PACK) {
+        const int row = j * 4 + (lane >> 4), most = s.M * s.G - 1, r = min(row, most);
+        j = (int)(((float)r + 0.5f) * __builtin_amdgcn_rcpf((float)s.G));   // (half a row away from the next whole number: r < 2^16)
+        hc = r - j * s.G;
+        live = row <= most;
+    } else {
+        const int hh = quad * 4 + (lane >> 4);
+        live = hh < s.G;
+        hc = live ? hh : s.G - 1;
+    }
+    const int h = g * s.G + hc;
     const int64_t qrow = (((int64_t)b * s.M + j) * s.Hq + h) * D;
     if (wave == 0) SPECPV_CSTAMP(0, 0);   // entry
 
@@ -229,9 +239,12 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
                 at = next(at);
             }
         };
-        if (s.Mk <= 64) steps([&](int x) { return __builtin_amdgcn_readlane(par0, x); });
+        if (PACK && s.Mk <= 64) steps([&](int x) { return __shfl(par0, x); });
+        else if (PACK) steps([&](int x) { const int lo = __shfl(par0, x & 63), hi = __shfl(par1, x & 63); return x < 64 ? lo : hi; });
+        else if (s.Mk <= 64) steps([&](int x) { return __builtin_amdgcn_readlane(par0, x); });
         else steps([&](int x) { const int lo = __builtin_amdgcn_readlane(par0, x & 63), hi = __builtin_amdgcn_readlane(par1, x & 63); return x < 64 ? lo : hi; });
     };
+    auto any = [](bool x) { return PACK ? __any(x) != 0 : x; };   // (of the sixteens' paths; one path is the wavefront's)
     int a8[NB];
     float bias[NB];
     Raw kd8[NB], vd8[NB];
@@ -287,12 +300,12 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
         four(bias, kd8, vd8, std::true_type{});
 #pragma unroll
         for (int u = 4; u < NA; u += 4)
-            if (bias[u] == 0.f) four(bias + u, kd8 + u, vd8 + u, std::false_type{});
-        while (at != last) {   // longer paths: 8 per trip
+            if (any(bias[u] == 0.f)) four(bias + u, kd8 + u, vd8 + u, std::false_type{});
+        while (any(at != last)) {   // longer paths: 8 per trip
             walk(I8{}, a8, bias);
             rows(I0{}, I8{});
             four(bias, kd8, vd8, std::false_type{});
-            if (bias[4] == 0.f) four(bias + 4, kd8 + 4, vd8 + 4, std::false_type{});
+            if (any(bias[4] == 0.f)) four(bias + 4, kd8 + 4, vd8 + 4, std::false_type{});
         }
     };
     if (TWO && tree_role) {
@@ -362,9 +375,9 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
             if constexpr (!TWO) {
                 rows(I0{}, I4{});
                 if (NB > 8) rows(I4{}, std::integral_constant<int, NB - 4>{});
-                else if (bias[4] == 0.f) rows(I4{}, I4{});
+                else if (any(bias[4] == 0.f)) rows(I4{}, I4{});
             } else {
-                more = bias[NA] == 0.f;
+                more = any(bias[NA] == 0.f);
                 if (more) rows(std::integral_constant<int, NA>{}, std::integral_constant<int, NB - NA>{});
             }
         }
@@ -448,6 +461,8 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
 //   12.9, 960 16.2 / 16.1, 1920 21.9 / 21.8, 3840 33.0 / 33.8; fp32, 192 40.5 / 34.2: the line at a workgroup per CU;
 //   ... more heads, where one workgroup has several fours of rows that share what they read: G = 5, 480 workgroups 19.5 / 19.0,
 //   960 27.5 / 27.6, 1920 40.6 / 40.3; two KV heads at G = 8, 240 18.8 / 17.9, 960 29.7 / 29.7: two workgroups per CU;
+//   packed rows (below), fours of rows: 150 10.80 / 10.80, 300 12.80 / 12.55, 600 14.45 / 14.15, 1200 27.1 / 27.0, 2400 38.95 /
+//   39.25, 9600 62.9 / 65.1: eight of them per CU;
 //   more than eight (kernels of before, which took the whole tree in one wavefront): 16, 480 workgroups 16.45 / 16.18, 1920
 //   51.7 / 51.0; 32, 480 17.9 / 16.2, 1440 77.2 / 76.1; full pass in shares, 1920 workgroups 87.4 / 86.0, 7680 at G = 5 216 / 206;
 //   fp32, 32 splits, 1920 workgroups at 128 channels 222 / 204.
@@ -455,29 +470,41 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
 // enough to be worth a wavefront of its own up to one per SIMD (kernels of before): 16 of them, 64 channels, eight splits, 296
 // fours of rows 18.4 / 17.3, 960 29.6 / 27.8, 1920 45.4 / 46.4; two splits 17.9 / 18.3 (960), 21.3 / 27.8 (1920), at 128
 // channels 47.2 / 44.4, 56 / 70.
-static bool combine_two_waves(const Shape &s, const Partials &p)
+static bool combine_two_waves(const Shape &s, const Partials &p, bool pack)
 {
     if (p.stream || p.nsplit > 8) return true;
-    const int64_t wgs = (int64_t)s.batch * s.Hkv * s.M, fours = (s.G + 3) / 4, cus = device_cu_count();
-    if (s.koff > s.kctx) return wgs * fours <= 4 * cus;
-    return wgs <= (fours > 1 ? 2 : 1) * cus;
+    const int64_t rows = (int64_t)s.batch * s.Hkv * s.M, cus = device_cu_count();
+    if (pack) return (rows * s.G + 3) / 4 <= 8 * cus;
+    const int64_t fours = (s.G + 3) / 4;
+    if (s.koff > s.kctx) return rows * fours <= 4 * cus;
+    return rows <= (fours > 1 ? 2 : 1) * cus;
 }
+// PACK: sixteen lanes take whatever row of the KV head is next, node by node, so that a group size that is no multiple of four
+// leaves no lanes idle (five heads take 75 workgroups per 60 nodes, not 120 wavefronts of which every second has one row of
+// four).  The rows of a wavefront then have paths of their own: the walk goes through the cross-lane unit.  Four layers in a
+// graph, fours by node / packed, us: G = 5, 60 nodes, one sequence 61.3 / 56.6 (2K kept) and 78.5 / 73.3 (4K), 16 nodes 45.4 /
+// 43.2, four sequences 166.6 / 155.9, sixteen (2K) 281.8 / 252.0; G = 1 with 16 KV heads 56.9 / 50.9; G = 2, four sequences 82.2
+// / 76.8; G = 3 55.4 / 51.2.  bf16 only: with fp32 inputs the rows themselves bind.
+static bool combine_packed(const Shape &s, int dtype) { return dtype == SPECPV_BF16 && s.G % 4 && s.koff <= s.kctx; }
 
 template <typename T, int D>
-static void launch_combine_t(const Shape &s, Partials p, void *out, float *lse, hipStream_t st)
+static void launch_combine_t(const Shape &s, int dtype, Partials p, void *out, float *lse, hipStream_t st)
 {
-    const bool two = combine_two_waves(s, p);
+    const bool pack = combine_packed(s, dtype), two = combine_two_waves(s, p, pack);
     const int groups = head_groups_code(s.Hkv);
-    dim3 grid(8, s.M, (s.batch * s.Hkv + 7) / 8), block((two ? 128 : 64) * ((s.G + 3) / 4));
+    dim3 grid(8, pack ? (s.M * s.G + 3) / 4 : s.M, (s.batch * s.Hkv + 7) / 8), block((two ? 128 : 64) * (pack ? 1 : (s.G + 3) / 4));
     const float scale_log2 = kLog2e / sqrtf((float)s.D);
     // fp16 partials: bf16 at 128 channels; the other element types and head dims have fp32 ones
     constexpr bool kHalf = std::is_same<T, bf16_t>::value && D == 128;
+#define SPECPV_LAUNCH(NP, MULTI, NB, HALF, TWO, PACK)                                                                            \
+        hipLaunchKernelGGL((combine_kernel<T, D, NP, MULTI, NB, HALF, TWO, PACK>), grid, block, 0, st, s.parent, s.q, (const float *)p.o, \
+                           (const float *)p.ml, s.M | s.Mk << 8, s.Hq, s.G, p.nsplit | groups << 16, s, p, out, lse, scale_log2)
 #define SPECPV_LAUNCH_K(NP, MULTI, NB, HALF)                                                                              \
     do {                                                                                                                \
-        if (two) hipLaunchKernelGGL((combine_kernel<T, D, NP, MULTI, NB, HALF, true>), grid, block, 0, st, s.parent, s.q, (const float *)p.o, \
-                                    (const float *)p.ml, s.M | s.Mk << 8, s.Hq, s.G, p.nsplit | groups << 16, s, p, out, lse, scale_log2);           \
-        else hipLaunchKernelGGL((combine_kernel<T, D, NP, MULTI, NB, HALF, false>), grid, block, 0, st, s.parent, s.q, (const float *)p.o, \
-                                (const float *)p.ml, s.M | s.Mk << 8, s.Hq, s.G, p.nsplit | groups << 16, s, p, out, lse, scale_log2);               \
+        constexpr bool kPack = std::is_same<T, bf16_t>::value && NB == 8;                                                    \
+        constexpr bool kOne = NP <= 8 && !MULTI;   /* (combine_two_waves) */                                               \
+        if (kPack && pack) { if (two || !kOne) SPECPV_LAUNCH(NP, MULTI, NB, HALF, true, kPack); else SPECPV_LAUNCH(NP, MULTI, NB, HALF, !kOne, kPack); }  \
+        else { if (two || !kOne) SPECPV_LAUNCH(NP, MULTI, NB, HALF, true, false); else SPECPV_LAUNCH(NP, MULTI, NB, HALF, !kOne, false); }  \
     } while (0)
 #define SPECPV_LAUNCH_H(NP, MULTI, NB)                                                                                   \
     do {                                                                                                                \
@@ -497,14 +524,15 @@ static void launch_combine_t(const Shape &s, Partials p, void *out, float *lse, 
 #undef SPECPV_LAUNCH_NP
 #undef SPECPV_LAUNCH_H
 #undef SPECPV_LAUNCH_K
+#undef SPECPV_LAUNCH
 }
 
 hipError_t launch_combine(const Shape &s, int dtype, Partials p, void *out, float *lse, hipStream_t st)
 {
     if (dtype == SPECPV_BF16) {
-        if (s.D == 128) launch_combine_t<bf16_t, 128>(s, p, out, lse, st); else launch_combine_t<bf16_t, 64>(s, p, out, lse, st);
+        if (s.D == 128) launch_combine_t<bf16_t, 128>(s, dtype, p, out, lse, st); else launch_combine_t<bf16_t, 64>(s, dtype, p, out, lse, st);
     } else {
-        if (s.D == 128) launch_combine_t<float, 128>(s, p, out, lse, st); else launch_combine_t<float, 64>(s, p, out, lse, st);
+        if (s.D == 128) launch_combine_t<float, 128>(s, dtype, p, out, lse, st); else launch_combine_t<float, 64>(s, dtype, p, out, lse, st);
     }
     return hipGetLastError();
 }
