@@ -322,7 +322,8 @@ int specpv_debug_set_route(int route);
 
 /* Testing and measuring aid, process-wide: how specpv_select_blocks and the refresh of
  * specpv_full_verify_refresh run scoring + selection (Section 3.2, eq. 2-3 and the top-k).
- *   0  the library's choice (currently two launches)
+ *   0  the library's choice (currently two launches; a refresh scores in the launch that merges its partials where it
+ *      can: bf16, eq. 2, and a place for the scores besides that of the partials)
  *   1  one launch where that is possible, two elsewhere: every scoring workgroup counts itself in on
  *      arrival words of its (sequence, KV head) at the head of the workspace, and the last one to
  *      arrive selects (no workgroup waits for another; the words are zero again afterwards).

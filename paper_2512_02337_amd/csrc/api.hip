@@ -166,7 +166,7 @@ static size_t part_row_bytes(const Shape &s, int kind)
 // plan.  `total` is what specpv_workspace_bytes promises: room for nsplit + 1 slots of fp32 (the context splits and the
 // draft-tree segment, as the single-kernel route lays them out: O, pairs at fused_ml) and, behind them, the scores.
 // Scores that a call keeps in the workspace stand behind the arrival words: they are written when the partials have been
-// read.
+// read.  A refresh that scores beside the merge puts them behind the rows of its plan, where there is room.
 struct Workspace {
     unsigned long long *arrive;
     float *part_o, *part_ml, *fused_ml, *scores;
@@ -383,8 +383,17 @@ static SumArgs side_summaries(const Shape &s, int64_t begin, void *kmax, void *k
 static int g_route = 0;
 static unsigned long long *g_timeline = nullptr;   // where instrumented builds (-DSPECPV_TIMELINE) put their time stamps
 
+// The scores that a full pass wants beside the merge of its partials.  done: they are there (else they are still to be taken).
+struct TailScores {
+    const void *kmax, *kmin;
+    int kind, reduce, last_node;
+    float *scores;
+    bool done;
+};
+
 static int run_attention(const Shape &s_in, const AttnPlan &plan, int dtype, const int32_t *sel_idx, const int32_t *sel_count,
-                         int n_sel, void *out, float *lse, void *workspace, size_t workspace_bytes, const SumArgs &sum, hipStream_t st)
+                         int n_sel, void *out, float *lse, void *workspace, size_t workspace_bytes, const SumArgs &sum, hipStream_t st,
+                         TailScores *tail = nullptr)
 {
     Shape s = s_in;
     // the matrix-core kernels take the partially verified tokens in front of the tree along with the cache
@@ -411,7 +420,12 @@ static int run_attention(const Shape &s_in, const AttnPlan &plan, int dtype, con
     else if (plan.kind != kAttnGeneric) e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, none, sum, st);
     else e = launch_attn_ctx_generic(s, dtype, sel_idx, sel_count, n_sel, p, st);
     if (e != hipSuccess) return fail_hip(e);
-    e = launch_combine(s, dtype, p, out, lse, st);
+    if (tail && tail->scores && refresh_tail_supported(s, dtype, p, tail->kind)) {
+        e = launch_refresh_tail(s, p, out, lse, tail->kmax, tail->kmin, tail->reduce, tail->last_node, tail->scores, st);
+        tail->done = true;
+    } else {
+        e = launch_combine(s, dtype, p, out, lse, st);
+    }
     if (e != hipSuccess) return fail_hip(e);
     return SPECPV_OK;
 }
@@ -445,7 +459,7 @@ static int g_select_route = 0;
 
 // arrive: the zeroed arrival words at the head of a workspace, or nullptr where the caller gave none
 static int run_select(const Shape &s, int dtype, const specpv_tree *tree, const void *kmax, const void *kmin,
-                      const specpv_select_cfg *cfg, int32_t *sel_idx, int32_t *sel_count, float *scores,
+                      const specpv_select_cfg *cfg, int32_t *sel_idx, int32_t *sel_count, float *scores, bool scored,
                       unsigned long long *arrive, hipStream_t st)
 {
     const int n_row = cfg->n_sink_blocks + cfg->k_blocks + cfg->n_recent_blocks + cfg->n_extra_slots;
@@ -456,10 +470,10 @@ static int run_select(const Shape &s, int dtype, const specpv_tree *tree, const 
     // costs, and the last workgroup then starts its selection with cold reads like a fresh kernel would.
     const bool one = arrive && __atomic_load_n(&g_select_route, __ATOMIC_RELAXED) == 1 && score_select_supported(s, dtype);
     // the scoring kernels count query rows: node last_node is row last_node - n_key_only
-    hipError_t e = launch_scores(s, dtype, kmax, kmin, (int)cfg->reduce, tree->last_node - tree->n_key_only,
-                                 (int)cfg->score, scores, one ? &sel : nullptr, one ? arrive : nullptr, st);
+    hipError_t e = scored ? hipSuccess : launch_scores(s, dtype, kmax, kmin, (int)cfg->reduce, tree->last_node - tree->n_key_only,
+                                                       (int)cfg->score, scores, one ? &sel : nullptr, one ? arrive : nullptr, st);
     if (e != hipSuccess) return fail_hip(e);
-    if (one) return SPECPV_OK;
+    if (one && !scored) return SPECPV_OK;
     e = launch_topk(s, scores, sel.ns, sel.nr, sel.k, n_row, sel_idx, sel_count, st);
     if (e != hipSuccess) return fail_hip(e);
     return SPECPV_OK;
@@ -516,7 +530,7 @@ int specpv_select_blocks(const specpv_kv *kv, const specpv_tree *tree, const voi
         scores = (float *)((char *)workspace + kArriveBytes);
     }
     unsigned long long *arrive = workspace && workspace_bytes >= kArriveBytes ? (unsigned long long *)workspace : nullptr;
-    return run_select(s, kv->dtype, tree, kmax, kmin, cfg, sel_idx, sel_count, scores, arrive, (hipStream_t)stream);
+    return run_select(s, kv->dtype, tree, kmax, kmin, cfg, sel_idx, sel_count, scores, false, arrive, (hipStream_t)stream);
 }
 
 int specpv_partial_verify_attn(const specpv_kv *kv, const specpv_tree *tree, const int32_t *sel_idx,
@@ -580,9 +594,15 @@ int specpv_full_verify_refresh(const specpv_kv *kv, const specpv_tree *tree, voi
         const hipError_t e = launch_summarize(s, kv->dtype, stale_blk_begin, -1, kmax, kmin, st);
         if (e != hipSuccess) return fail_hip(e);
     }
-    rc = run_attention(s, plan, kv->dtype, nullptr, nullptr, 0, out, lse, workspace, workspace_bytes, sum, st);
+    // Scores and the merge of the partials in one launch, where the scores have a place of their own: the caller's array, or
+    // behind the partials.  (In the place of the partials they can only follow the merge.)
+    const size_t behind = align_up(w.need);
+    float *apart = scores ? scores : (workspace_bytes >= behind + (w.scores_need - kArriveBytes) ? (float *)((char *)workspace + behind) : nullptr);
+    if (__atomic_load_n(&g_select_route, __ATOMIC_RELAXED) != 0) apart = nullptr;   // scoring as a launch of its own, or with the selection
+    TailScores tail{kmax, kmin, (int)cfg->score, (int)cfg->reduce, tree->last_node - tree->n_key_only, apart, false};
+    rc = run_attention(s, plan, kv->dtype, nullptr, nullptr, 0, out, lse, workspace, workspace_bytes, sum, st, &tail);
     if (rc != SPECPV_OK) return rc;
-    return run_select(s, kv->dtype, tree, kmax, kmin, cfg, sel_idx, sel_count, scores ? scores : w.scores, w.arrive, st);
+    return run_select(s, kv->dtype, tree, kmax, kmin, cfg, sel_idx, sel_count, tail.done ? apart : (scores ? scores : w.scores), tail.done, w.arrive, st);
 }
 
 int specpv_gather_blocks(const specpv_kv *kv, const int32_t *sel_idx, const int32_t *sel_count, int32_t n_sel,

@@ -16,154 +16,12 @@
 // of 16 layers 15.37 -> 14.71 us (one card) and 16.69 -> 16.02 (another); fp32, 16 nodes, four launches 18.8 -> 16.3.  A third
 // wavefront for the second half took another 0.8 %, and has no place at eight heads a KV head and more.
 // (A tree segment on the matrix cores, dense over 32 nodes with a bit mask, was slower: a call 18.6 us with 8 splits.)
-#include "internal.h"
-#include <type_traits>
+#include "combine.h"
 
 namespace specpv {
 
-// CPL adjacent channels of one row, 16 bytes per memory instruction (rows are 16-byte aligned).
-template <typename T, int CPL> struct Chan;
-template <int CPL> struct Chan<float, CPL> {
-    typedef float4 Raw[CPL / 4];
-    static __device__ __forceinline__ void load(const void *p, int64_t i, Raw &r) {
-#pragma unroll
-        for (int x = 0; x < CPL / 4; ++x) r[x] = *(const float4 *)((const float *)p + i + 4 * x);
-    }
-    static __device__ __forceinline__ void unpack(const Raw &r, float *f) {
-#pragma unroll
-        for (int x = 0; x < CPL / 4; ++x) { f[4 * x] = r[x].x; f[4 * x + 1] = r[x].y; f[4 * x + 2] = r[x].z; f[4 * x + 3] = r[x].w; }
-    }
-    static __device__ __forceinline__ float dot(const Raw &a, const Raw &b) {
-        float d = 0.f;
-#pragma unroll
-        for (int x = 0; x < CPL / 4; ++x) d = fmaf(a[x].w, b[x].w, fmaf(a[x].z, b[x].z, fmaf(a[x].y, b[x].y, fmaf(a[x].x, b[x].x, d))));
-        return d;
-    }
-    static __device__ __forceinline__ void store_stream(void *p, int64_t i, const float *f) {
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
-#pragma unroll
-        for (int x = 0; x < CPL / 4; ++x) {
-            f32x4 v = {f[4 * x], f[4 * x + 1], f[4 * x + 2], f[4 * x + 3]};
-            __builtin_nontemporal_store(v, (f32x4 *)((float *)p + i + 4 * x));
-        }
-    }
-};
-// acc + a.lo * b.lo + a.hi * b.hi for packed bf16 pairs: half the instructions of widening both and two fp32 FMAs, and the
-// same error (products of bf16 are exact in fp32).  Log-sum-exp of the draft segment alone against 64 bits, 37 and 60
-// nodes, queries of 1 and 4 times unit variance: rms 2.2e-7 and 2.3e-7, at most 2.0e-6, at 64 channels, 2.3e-7 and
-// 2.4e-7, at most 2.6e-6, at 128, with either.
-__device__ __forceinline__ float dot_bf16x2(uint32_t a, uint32_t b, float acc)
-{
-    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, b), acc, false);
-}
-template <> struct Chan<bf16_t, 8> {
-    typedef uint4 Raw;
-    static __device__ __forceinline__ float dot(const Raw &a, const Raw &b) {
-        return dot_bf16x2(a.w, b.w, dot_bf16x2(a.z, b.z, dot_bf16x2(a.y, b.y, dot_bf16x2(a.x, b.x, 0.f))));
-    }
-    static __device__ __forceinline__ void load(const void *p, int64_t i, Raw &r) { r = *(const uint4 *)((const uint16_t *)p + i); }
-    static __device__ __forceinline__ void unpack(const Raw &r, float *f) { Elem<bf16_t>::unpack(r, f); }
-    static __device__ __forceinline__ void store_stream(void *p, int64_t i, const float *f) {
-        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        u32x4 v;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) v[x] = float_to_bf16_bits(f[2 * x]) | ((uint32_t)float_to_bf16_bits(f[2 * x + 1]) << 16);
-        __builtin_nontemporal_store(v, (u32x4 *)((uint16_t *)p + i));
-    }
-};
-template <> struct Chan<bf16_t, 4> {
-    typedef uint2 Raw;
-    static __device__ __forceinline__ float dot(const Raw &a, const Raw &b) { return dot_bf16x2(a.y, b.y, dot_bf16x2(a.x, b.x, 0.f)); }
-    static __device__ __forceinline__ void load(const void *p, int64_t i, Raw &r) { r = *(const uint2 *)((const uint16_t *)p + i); }
-    static __device__ __forceinline__ void unpack(const Raw &r, float *f) {
-        f[0] = __uint_as_float(r.x << 16); f[1] = __uint_as_float(r.x & 0xffff0000u);
-        f[2] = __uint_as_float(r.y << 16); f[3] = __uint_as_float(r.y & 0xffff0000u);
-    }
-    static __device__ __forceinline__ void store_stream(void *p, int64_t i, const float *f) {
-        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-        u32x2 v;
-#pragma unroll
-        for (int x = 0; x < 2; ++x) v[x] = float_to_bf16_bits(f[2 * x]) | ((uint32_t)float_to_bf16_bits(f[2 * x + 1]) << 16);
-        __builtin_nontemporal_store(v, (u32x2 *)((uint16_t *)p + i));
-    }
-};
-// The lane's CPL fp32 values of a partial row (i: the row's first element + 4 * (lane & 15)), read
-// once: streaming hint.  Rows of 128 are stored so that piece x of all 16 lanes is one dense run
-// (partial_pos); the values come out in channel order.
-template <int CPL> __device__ __forceinline__ void load_partial(const float *p, int64_t i, float *f)
-{
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-#pragma unroll
-    for (int x = 0; x < CPL / 4; ++x) {
-#ifndef SPECPV_PARTIAL_PLAIN
-        const f32x4 v = __builtin_nontemporal_load((const f32x4 *)(p + i + 64 * x));
-#else
-        const f32x4 v = *(const f32x4 *)(p + i + 64 * x);
-#endif
-        f[4 * x] = v[0]; f[4 * x + 1] = v[1]; f[4 * x + 2] = v[2]; f[4 * x + 3] = v[3];
-    }
-}
-
-// The lane's channels of one partial as they come from memory, and as fp32 once they are used.
-template <int CPL, bool HALF> struct Part {   // fp32 form
-    float f[CPL];
-    __device__ __forceinline__ void load(const float *p, int64_t row, int D, int lane16) { load_partial<CPL>(p, row * D + 4 * lane16, f); }
-    __device__ __forceinline__ void value(float *v) const
-    {
-#pragma unroll
-        for (int x = 0; x < CPL; ++x) v[x] = f[x];
-    }
-};
-template <> struct Part<8, true> {   // fp16 form: the lane's eight adjacent channels are one 16-byte piece
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    u32x4 raw;
-    __device__ __forceinline__ void load(const float *p, int64_t row, int D, int lane16)
-    {
-        raw = __builtin_nontemporal_load((const u32x4 *)((const _Float16 *)p + row * D + lane16 * 8));
-    }
-    __device__ __forceinline__ void value(float *v) const
-    {
-        typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-        const f16x8 h = __builtin_bit_cast(f16x8, raw);
-#pragma unroll
-        for (int x = 0; x < 8; ++x) v[x] = (float)h[x];
-    }
-};
-
-// The value of lane U of a row of 16 lanes, in all of them.
-template <int U> __device__ __forceinline__ float row_bcast(float v) { return dpp_row<0x150 + U>(v); }   // row_newbcast
-__device__ __forceinline__ float row16_max(float x)
-{
-    x = fmaxf(x, dpp_row<0xB1>(x));
-    x = fmaxf(x, dpp_row<0x4E>(x));
-    x = fmaxf(x, dpp_row<0x141>(x));
-    return fmaxf(x, dpp_row<0x140>(x));
-}
-
-#ifdef SPECPV_TIMELINE
-#define SPECPV_CSTAMP(i, W)                                                                                  \
-    do {                                                                                                     \
-        if (part.timeline && threadIdx.x == 64 * (W) && (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x < 1024u) \
-            part.timeline[(2048 + ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 16 + (i)] = \
-                __builtin_amdgcn_s_memrealtime();                                                            \
-    } while (0)
-#else
-#define SPECPV_CSTAMP(i, W) do {} while (0)
-#endif
-
-// NP: context partials fetched at once (the smallest of 2, 4, 8, 16 that covers the split count keeps
-// the registers, and with them the resident wavefronts of a batch, in proportion).
-// MULTI: more splits than 16 (a full verification): rounds of NP = 8, each round's
-// reads requested before the previous round is merged.
-// NB: path nodes whose draft K / V rows are requested in the first go: 8 (a tree of candidates alone), or 24
-// when partially verified tokens stand in front of the tree as keys (every candidate's path then starts with
-// that whole chain; more registers, so only then).
-// HALF: the partials' O rows are fp16 and normalised (see Partials); else fp32 sums.
-// part.stream > 0 (MULTI only): the number and the place of a pair's partials follow from the sequence lengths, which the
-// partials' wavefront reads first.
 template <typename T, int D, int NP, bool MULTI, int NB, bool HALF, bool TWO, bool PACK>
-__global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, const void *a_q, const float *a_po,
+__global__ __launch_bounds__(512, MULTI && HALF ? 4 : 1) void combine_kernel(const int32_t *a_parent, const void *a_q, const float *a_po,
                                                     const float *a_pml, int a_M_Mk, int a_Hq, int a_G, int a_nsplit_groups,
                                                     Shape s, Partials part, void *out, float *lse, float scale_log2)
 {
@@ -171,12 +29,8 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
     s.parent = a_parent; s.q = a_q; s.M = a_M_Mk & 0xff; s.Mk = a_M_Mk >> 8; s.Hq = a_Hq; s.G = a_G;
     part.o = const_cast<float *>(a_po); part.ml = const_cast<float *>(a_pml); part.nsplit = a_nsplit_groups & 0xffff;
     const int groups = a_nsplit_groups >> 16;   // head_groups_code
-    constexpr int CPL = D / 16;   // channels per lane: d = (lane & 15) * CPL + x
-    typedef typename Chan<T, CPL>::Raw Raw;
-    __shared__ float tree_od[TWO ? 4 : 1][CPL / 4][64][4];   // [four heads][channels, four at a time][lane]
-    __shared__ float2 tree_ml[TWO ? 4 : 1][64];
-    const int lane = threadIdx.x & 63;
-    const int d0 = (lane & 15) * CPL;
+    __shared__ float4 tree_od[TWO ? 4 * (D / 64) * 64 : 1];
+    __shared__ float2 tree_ml[TWO ? 4 * 64 : 1];
     // x = XCD (workgroups go to the XCDs round-robin in linear order), y = node, z = bg / 8: the rows
     // of (sequence, KV head) bg are merged on XCD bg % 8, where the split kernel produced them
     const int bg = (int)blockIdx.z * 8 + (int)blockIdx.x;
@@ -188,268 +42,8 @@ __global__ __launch_bounds__(512) void combine_kernel(const int32_t *a_parent, c
         if (bg >= s.batch * s.Hkv) return;
         b = bg / s.Hkv;
     }
-    // wavefronts 0 .. n - 1: the tree segments of four rows each; n .. 2n - 1: their partials.  Lanes without a row (PACK: past
-    // the last one; else a group size that is no multiple of four) repeat the last one and store nothing
-    const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nq = TWO ? (PACK ? 1 : (s.G + 3) >> 2) : 0;   // (blockDim.x is read from memory)
-    const bool tree_role = wave < nq;
-    const int quad = TWO && !tree_role ? wave - nq : wave;
-    const int g = bg - b * s.Hkv;
-    int j = (int)blockIdx.y, hc;   // query row and head of the lane's sixteen
-    bool live;
-    if constexpr (PACK) {
-        const int row = j * 4 + (lane >> 4), most = s.M * s.G - 1, r = min(row, most);
-        j = (int)(((float)r + 0.5f) * __builtin_amdgcn_rcpf((float)s.G));   // (half a row away from the next whole number: r < 2^16)
-        hc = r - j * s.G;
-        live = row <= most;
-    } else {
-        const int hh = quad * 4 + (lane >> 4);
-        live = hh < s.G;
-        hc = live ? hh : s.G - 1;
-    }
-    const int h = g * s.G + hc;
-    const int64_t qrow = (((int64_t)b * s.M + j) * s.Hq + h) * D;
-    if (wave == 0) SPECPV_CSTAMP(0, 0);   // entry
-
-    // ---- draft-tree segment: the node itself and its ancestors, path slot 0, 1, ... ------------------------------------
-    // With two wavefronts, the tree's takes the first NA slots and whatever comes behind the NB, the partials' the others.
-    // (More than 16 partials: the second half in the partials' wavefront costs it registers, 126 -> 160, and a full pass over
-    // 32K + 64K + 96K + 128K tokens at G = 5 459 -> 456 us without it.)
-    constexpr int NA = TWO && NB == 8 && !MULTI ? 4 : NB;
-    int par0 = 0, par1 = 0;   // where the path goes on from nodes lane and lane + 64: to the node itself where it ends
-    Raw qraw;
-    auto tree_first = [&]() __attribute__((always_inline)) {
-        // the tree has s.Mk nodes; query row j is node j + s.koff (the nodes in front are keys only)
-        const int32_t *par = s.parent + (int64_t)b * s.Mk;
-        par0 = par[min(lane, s.Mk - 1)];
-        if (s.Mk > 64) par1 = par[min(lane + 64, s.Mk - 1)];
-        Chan<T, CPL>::load(s.q, qrow + d0, qraw);
-    };
-    const int64_t drow0 = (((int64_t)b * s.Mk) * s.Hkv + g) * D + d0;
-    const int drow_step = s.Hkv * D;   // (Mk <= 128 rows: 32-bit offsets)
-    int at = j + s.koff, last = -1;    // next slot's node; the slot's before it (the same: the path has ended)
-    // N slots: a[u] is a node, bias[u] 0, or -inf behind the path's end (a[u] then repeats its last node)
-    auto walk = [&](auto count, int *a, float *bias) __attribute__((always_inline)) {
-        constexpr int N = decltype(count)::value;
-        auto steps = [&](auto next) __attribute__((always_inline)) {
-#pragma unroll
-            for (int u = 0; u < N; ++u) {
-                a[u] = at;
-                bias[u] = at == last ? -INFINITY : 0.f;
-                last = at;
-                at = next(at);
-            }
-        };
-        if (PACK && s.Mk <= 64) steps([&](int x) { return __shfl(par0, x); });
-        else if (PACK) steps([&](int x) { const int lo = __shfl(par0, x & 63), hi = __shfl(par1, x & 63); return x < 64 ? lo : hi; });
-        else if (s.Mk <= 64) steps([&](int x) { return __builtin_amdgcn_readlane(par0, x); });
-        else steps([&](int x) { const int lo = __builtin_amdgcn_readlane(par0, x & 63), hi = __builtin_amdgcn_readlane(par1, x & 63); return x < 64 ? lo : hi; });
-    };
-    auto any = [](bool x) { return PACK ? __any(x) != 0 : x; };   // (of the sixteens' paths; one path is the wavefront's)
-    int a8[NB];
-    float bias[NB];
-    Raw kd8[NB], vd8[NB];
-    auto rows = [&](auto from, auto count) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = decltype(from)::value; u < decltype(from)::value + decltype(count)::value; ++u) {
-            const int64_t drow = drow0 + a8[u] * drow_step;
-            Chan<T, CPL>::load(s.kd, drow, kd8[u]);
-            Chan<T, CPL>::load(s.vd, drow, vd8[u]);
-        }
-    };
-    auto tree_path = [&]() __attribute__((always_inline)) {
-        asm volatile("" :: "s"(s.kd), "s"(s.vd));   // read now, while the parents are on their way, not where they are first used
-        // nodes below kctx (partially verified tokens that the context kernels have attended already) end a path, and so does
-        // a malformed parent[] (not strictly decreasing)
-        par0 = par0 >= s.kctx && par0 < lane ? par0 : lane;
-        if (s.Mk > 64) par1 = par1 >= s.kctx && par1 < lane + 64 ? par1 : lane + 64;
-        walk(std::integral_constant<int, NB>{}, a8, bias);
-    };
-    float m = -INFINITY, l = 0.f, od[CPL];
-#pragma unroll
-    for (int x = 0; x < CPL; ++x) od[x] = 0.f;
-    // online softmax over four slots, the first of which holds a node
-    auto four = [&](const float *bi, const Raw *kdv, const Raw *vdv, auto first) __attribute__((always_inline)) {
-        float z[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) z[u] = fmaf(row16_sum(Chan<T, CPL>::dot(qraw, kdv[u])), scale_log2, bi[u]);
-        float m_new = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
-        if (!decltype(first)::value) m_new = fmaxf(m_new, m);
-        const float m_use = m_new == -INFINITY ? 0.f : m_new;
-        if (!decltype(first)::value) {
-            const float alpha = __builtin_amdgcn_exp2f(m - m_use);
-            l *= alpha;
-#pragma unroll
-            for (int x = 0; x < CPL; ++x) od[x] *= alpha;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float pe = __builtin_amdgcn_exp2f(z[u] - m_use);   // 0 for the unused slots
-            l += pe;
-            float vf[CPL];
-            Chan<T, CPL>::unpack(vdv[u], vf);
-#pragma unroll
-            for (int x = 0; x < CPL; ++x) od[x] = fmaf(pe, vf[x], od[x]);
-        }
-        m = m_new;
-    };
-    typedef std::integral_constant<int, 0> I0;
-    typedef std::integral_constant<int, 4> I4;
-    typedef std::integral_constant<int, 8> I8;
-    // slots 0 .. NA - 1, and those behind the NB
-    auto tree_sums = [&]() __attribute__((always_inline)) {
-        four(bias, kd8, vd8, std::true_type{});
-#pragma unroll
-        for (int u = 4; u < NA; u += 4)
-            if (any(bias[u] == 0.f)) four(bias + u, kd8 + u, vd8 + u, std::false_type{});
-        while (any(at != last)) {   // longer paths: 8 per trip
-            walk(I8{}, a8, bias);
-            rows(I0{}, I8{});
-            four(bias, kd8, vd8, std::false_type{});
-            if (any(bias[4] == 0.f)) four(bias + 4, kd8 + 4, vd8 + 4, std::false_type{});
-        }
-    };
-    if (TWO && tree_role) {
-        tree_first();
-        tree_path();
-        if (wave == 0) SPECPV_CSTAMP(1, 0);   // parents in, root path walked
-        rows(I0{}, std::integral_constant<int, NA>{});
-        tree_sums();
-#pragma unroll
-        for (int x = 0; x < CPL / 4; ++x) *(float4 *)tree_od[quad][x][lane] = make_float4(od[4 * x], od[4 * x + 1], od[4 * x + 2], od[4 * x + 3]);
-        tree_ml[quad][lane] = make_float2(m, l);
-        if (wave == 0) SPECPV_CSTAMP(3, 0);   // draft K / V rows in, tree segment done
-        __syncthreads();
-        return;
-    }
-
-    // ---- context partials -----------------------------------------------------------------
-    const int R = s.M * s.G;   // rows of the KV head, head by head
-    int ns = part.nsplit;
-    int64_t slot0 = (int64_t)bg * ns;
-    if (MULTI && part.stream) {
-        const StreamShare sh(s, lane, part.stream);
-        const int C_b = __builtin_amdgcn_readlane(sh.chunks, b);
-        const int at = (__builtin_amdgcn_readlane(sh.upto, b) - C_b) * s.Hkv + g * C_b;
-        const int w0 = C_b > 0 ? sh.owner(at) : 0;
-        ns = C_b > 0 ? sh.owner(at + C_b - 1) - w0 + 1 : 0;
-        slot0 = w0 + bg;
-    }
-    const int64_t prow0 = slot0 * R + hc * s.M + j;
-    // (m, l) of partials u, u + 16, ... in lane u of the row's sixteen: each lane works out the weights of its own
-    constexpr int KM = MULTI ? 4 : 1;   // (64 partials at a time; a pair that holds most of a batch may have more)
-    const int u16 = lane & 15;
-    typedef Part<CPL, HALF> P;
-    float m_ctx = -INFINITY, l_ctx = 0.f, o[CPL];
-#pragma unroll
-    for (int x = 0; x < CPL; ++x) o[x] = 0.f;
-    auto fetch = [&](int sp0, P (&r)[NP]) {
-#pragma unroll
-        for (int u = 0; u < NP; ++u) r[u].load(part.o, prow0 + (int64_t)max(min(sp0 + u, ns - 1), 0) * R, D, u16);
-    };
-    auto add = [&](const P &r, float wt) {
-        float v[CPL];
-        r.value(v);
-#pragma unroll
-        for (int x = 0; x < CPL; ++x) o[x] = fmaf(wt, v[x], o[x]);
-    };
-    // partials OFF .. of the sixteen whose weights wk holds (weights past the split count are 0)
-    auto add_n = [&](const P *r, float wk, auto off, auto count) __attribute__((always_inline)) {
-        constexpr int O = decltype(off)::value, N = decltype(count)::value;
-        add(r[0], row_bcast<O>(wk)); add(r[1], row_bcast<O + 1>(wk));
-        if constexpr (N >= 4) { add(r[2], row_bcast<O + 2>(wk)); add(r[3], row_bcast<O + 3>(wk)); }
-        if constexpr (N >= 8) { add(r[4], row_bcast<O + 4>(wk)); add(r[5], row_bcast<O + 5>(wk)); add(r[6], row_bcast<O + 6>(wk)); add(r[7], row_bcast<O + 7>(wk)); }
-    };
-    bool more = false;   // two wavefronts: the path goes beyond the other one's slots
-    if (!TWO || NA < NB) tree_first();   // (in front of the partials: reads are waited for in their order)
-    for (int s0 = 0;; s0 += 16 * KM) {   // 16 KM partials at a time (one trip, but for a pair with more than 64)
-        float2 ml[KM];
-#pragma unroll
-        for (int k = 0; k < KM; ++k) {
-            const int sp = s0 + u16 + 16 * k;
-            ml[k] = sp < ns ? *(const float2 *)(part.ml + (prow0 + (int64_t)sp * R) * 2) : make_float2(-INFINITY, 0.f);
-        }
-        P ra[NP];
-        fetch(s0, ra);
-        if (s0 == 0 && (!TWO || NA < NB)) {
-            tree_path();
-            if constexpr (!TWO) {
-                rows(I0{}, I4{});
-                if (NB > 8) rows(I4{}, std::integral_constant<int, NB - 4>{});
-                else if (any(bias[4] == 0.f)) rows(I4{}, I4{});
-            } else {
-                more = any(bias[NA] == 0.f);
-                if (more) rows(std::integral_constant<int, NA>{}, std::integral_constant<int, NB - NA>{});
-            }
-        }
-        float m_new = -INFINITY;
-#pragma unroll
-        for (int k = 0; k < KM; ++k) m_new = fmaxf(m_new, ml[k].y > 0.f ? ml[k].x : -INFINITY);
-        m_new = fmaxf(row16_max(m_new), m_ctx);
-        if (MULTI && s0 > 0) {
-            const float alpha = m_ctx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ctx - m_new);
-            l_ctx *= alpha;
-#pragma unroll
-            for (int x = 0; x < CPL; ++x) o[x] *= alpha;
-        }
-        m_ctx = m_new;
-        float w[KM], l_new = 0.f;
-#pragma unroll
-        for (int k = 0; k < KM; ++k) {
-            const float e = ml[k].y > 0.f ? __builtin_amdgcn_exp2f(ml[k].x - m_ctx) : 0.f;
-            l_new = fmaf(ml[k].y, e, l_new);
-            w[k] = HALF ? e * ml[k].y : e;   // a normalised partial weighs in with its l
-        }
-        l_ctx += row16_sum(l_new);
-        if constexpr (!MULTI) {
-            add_n(ra, w[0], I0{}, std::integral_constant<int, NP < 8 ? NP : 8>{});
-            if constexpr (NP == 16) add_n(ra + 8, w[0], I8{}, I8{});
-            break;
-        } else {
-            static_assert(!MULTI || NP == 8, "eight partials per round");
-            P rb[NP];
-#pragma unroll
-            for (int k = 0; k < KM; ++k) {   // two register sets in turn
-                const int at = s0 + 16 * k;
-                if (at >= ns) break;
-                if (at + 8 < ns) fetch(at + 8, rb);
-                add_n(ra, w[k], I0{}, I8{});
-                if (at + 8 >= ns) break;
-                if (at + 16 < ns && k + 1 < KM) fetch(at + 16, ra);
-                add_n(rb, w[k], I8{}, I8{});
-            }
-            if (s0 + 16 * KM >= ns) break;
-        }
-    }
-    if (wave == nq) SPECPV_CSTAMP(2, nq);   // context partials in and merged
-    if (TWO) {
-        if (NA < NB && more) four(bias + NA, kd8 + NA, vd8 + NA, std::true_type{});
-        __syncthreads();
-        const float2 tml = tree_ml[quad][lane];   // (its maximum is finite: the node itself is on its path)
-        const float m_tree = fmaxf(m, tml.x), w0 = __builtin_amdgcn_exp2f(m - m_tree), w1 = __builtin_amdgcn_exp2f(tml.x - m_tree);
-        m = m_tree;
-        l = fmaf(l, w0, tml.y * w1);
-#pragma unroll
-        for (int x = 0; x < CPL / 4; ++x) {
-            const float4 v = *(const float4 *)tree_od[quad][x][lane];
-            od[4 * x] = fmaf(od[4 * x], w0, v.x * w1); od[4 * x + 1] = fmaf(od[4 * x + 1], w0, v.y * w1);
-            od[4 * x + 2] = fmaf(od[4 * x + 2], w0, v.z * w1); od[4 * x + 3] = fmaf(od[4 * x + 3], w0, v.w * w1);
-        }
-    } else {
-        tree_sums();
-    }
-    // ---- merge the two and store ---------------------------------------------------------
-    const float m_all = fmaxf(m, m_ctx);   // finite: the node itself is on its path
-    const float wd = __builtin_amdgcn_exp2f(m - m_all);
-    const float wc = m_ctx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ctx - m_all);
-    const float den = l * wd + l_ctx * wc;
-    const float inv = 1.f / den;
-    if (!live) return;
-    float res[CPL];
-#pragma unroll
-    for (int x = 0; x < CPL; ++x) res[x] = (od[x] * wd + o[x] * wc) * inv;
-    Chan<T, CPL>::store_stream(out, qrow + d0, res);
-    if (lse && u16 == 0) lse[((int64_t)b * s.M + j) * s.Hq + h] = (m_all + log2f(den)) * kLn2;
-    if (wave == nq) SPECPV_CSTAMP(4, nq);   // stored (issued)
+    const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (blockDim.x is read from memory)
+    combine_rows<T, D, NP, MULTI, NB, HALF, TWO, PACK, TWO && NB == 8 && !MULTI>(s, part, out, lse, scale_log2, bg, b, (int)blockIdx.y, wave, true, tree_od, tree_ml);
 }
 
 // Two wavefronts per four rows shorten the chain; one that does both has less to start.  What decides is the partials: with
@@ -485,7 +79,7 @@ static bool combine_two_waves(const Shape &s, const Partials &p, bool pack)
 // graph, fours by node / packed, us: G = 5, 60 nodes, one sequence 61.3 / 56.6 (2K kept) and 78.5 / 73.3 (4K), 16 nodes 45.4 /
 // 43.2, four sequences 166.6 / 155.9, sixteen (2K) 281.8 / 252.0; G = 1 with 16 KV heads 56.9 / 50.9; G = 2, four sequences 82.2
 // / 76.8; G = 3 55.4 / 51.2.  bf16 only: with fp32 inputs the rows themselves bind.
-static bool combine_packed(const Shape &s, int dtype) { return dtype == SPECPV_BF16 && s.G % 4 && s.koff <= s.kctx; }
+bool combine_packed(const Shape &s, int dtype) { return dtype == SPECPV_BF16 && s.G % 4 && s.koff <= s.kctx; }
 
 template <typename T, int D>
 static void launch_combine_t(const Shape &s, int dtype, Partials p, void *out, float *lse, hipStream_t st)

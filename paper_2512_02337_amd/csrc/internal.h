@@ -306,6 +306,11 @@ int attn_group_parts(const Shape &s);
 int attn_group_blocks(const Shape &s);   // row blocks of each
 double attn_group_chunk_us(int blocks);
 hipError_t launch_combine(const Shape &s, int dtype, Partials p, void *out, float *lse, hipStream_t st);
+bool combine_packed(const Shape &s, int dtype);
+// the merge and the scores (eq. 2) in one launch; kind: as for launch_scores
+bool refresh_tail_supported(const Shape &s, int dtype, const Partials &p, int kind);
+hipError_t launch_refresh_tail(const Shape &s, Partials p, void *out, float *lse, const void *kmax, const void *kmin, int reduce, int last_node,
+                               float *scores, hipStream_t st);
 // to_cache != 0: pending + accepted rows go to the cache tail (lengths, summaries updated);
 // otherwise the accepted rows join the pending rows of the buffer.  missed_words: the zeroed words at the
 // head of a workspace (kArriveBytes; zero again when the launches have finished).

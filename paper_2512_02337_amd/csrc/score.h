@@ -1,0 +1,282 @@
+// What the kernels that score blocks on the matrix cores share (score_mfma.hip, refresh_tail.hip): see score_mfma.hip.
+#pragma once
+#include "internal.h"
+
+namespace specpv {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+
+constexpr int kScoreMaxWaves = 16, kScoreMostTiles = 4, kScoreSums = 16;
+static inline int score_most_tiles(int waves) { return waves > 4 ? kScoreMostTiles : (waves > 2 ? 2 : 1); }   // of a workgroup, by what LDS holds
+
+typedef __attribute__((address_space(3))) void *lds_void_ptr;
+typedef const __attribute__((address_space(1))) void *glb_void_ptr;
+
+// sx, sn: the two score tiles of 32 query rows (q: A operands) against 32 blocks; a: this lane's LDS addresses of the Kmax
+// operands, the Kmin operands stand 64 D bytes behind them.  An operand register is read into again behind the matrix
+// instruction that was its last reader; "s_nop 11": the twelve wait states between such an instruction and the vector
+// ALU's read of its result, which the compiler does not count in here.
+__device__ __forceinline__ void score_products(const uint32_t (&a)[8], const bf16x8 (&q)[8], f32x16 &sx, f32x16 &sn)
+{
+    uint4 b[8];
+    asm volatile(
+        "ds_read_b128 %[b0], %[a0]\n\t"
+        "ds_read_b128 %[b1], %[a1]\n\t"
+        "ds_read_b128 %[b2], %[a2]\n\t"
+        "ds_read_b128 %[b3], %[a3]\n\t"
+        "ds_read_b128 %[b4], %[a4]\n\t"
+        "ds_read_b128 %[b5], %[a5]\n\t"
+        "ds_read_b128 %[b6], %[a6]\n\t"
+        "ds_read_b128 %[b7], %[a7]\n\t"
+        "s_waitcnt lgkmcnt(7)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sx], %[q0], %[b0], 0\n\t"
+        "ds_read_b128 %[b0], %[a0] offset:%[kn]\n\t"
+        "s_waitcnt lgkmcnt(7)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sx], %[q1], %[b1], %[sx]\n\t"
+        "ds_read_b128 %[b1], %[a1] offset:%[kn]\n\t"
+        "s_waitcnt lgkmcnt(7)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sx], %[q2], %[b2], %[sx]\n\t"
+        "ds_read_b128 %[b2], %[a2] offset:%[kn]\n\t"
+        "s_waitcnt lgkmcnt(7)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sx], %[q3], %[b3], %[sx]\n\t"
+        "ds_read_b128 %[b3], %[a3] offset:%[kn]\n\t"
+        "s_waitcnt lgkmcnt(7)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sx], %[q4], %[b4], %[sx]\n\t"
+        "ds_read_b128 %[b4], %[a4] offset:%[kn]\n\t"
+        "s_waitcnt lgkmcnt(7)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sx], %[q5], %[b5], %[sx]\n\t"
+        "ds_read_b128 %[b5], %[a5] offset:%[kn]\n\t"
+        "s_waitcnt lgkmcnt(7)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sx], %[q6], %[b6], %[sx]\n\t"
+        "ds_read_b128 %[b6], %[a6] offset:%[kn]\n\t"
+        "s_waitcnt lgkmcnt(7)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sx], %[q7], %[b7], %[sx]\n\t"
+        "ds_read_b128 %[b7], %[a7] offset:%[kn]\n\t"
+        "s_waitcnt lgkmcnt(7)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sn], %[q0], %[b0], 0\n\t"
+        "s_waitcnt lgkmcnt(6)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sn], %[q1], %[b1], %[sn]\n\t"
+        "s_waitcnt lgkmcnt(5)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sn], %[q2], %[b2], %[sn]\n\t"
+        "s_waitcnt lgkmcnt(4)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sn], %[q3], %[b3], %[sn]\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sn], %[q4], %[b4], %[sn]\n\t"
+        "s_waitcnt lgkmcnt(2)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sn], %[q5], %[b5], %[sn]\n\t"
+        "s_waitcnt lgkmcnt(1)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sn], %[q6], %[b6], %[sn]\n\t"
+        "s_waitcnt lgkmcnt(0)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sn], %[q7], %[b7], %[sn]\n\t"
+        "s_nop 11\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : [sx] "=&v"(sx), [sn] "=&v"(sn), [b0] "=&v"(b[0]), [b1] "=&v"(b[1]), [b2] "=&v"(b[2]), [b3] "=&v"(b[3]), [b4] "=&v"(b[4]), [b5] "=&v"(b[5]), [b6] "=&v"(b[6]), [b7] "=&v"(b[7])
+        : [a0] "v"(a[0]), [a1] "v"(a[1]), [a2] "v"(a[2]), [a3] "v"(a[3]), [a4] "v"(a[4]), [a5] "v"(a[5]), [a6] "v"(a[6]), [a7] "v"(a[7]),
+          [q0] "v"(q[0]), [q1] "v"(q[1]), [q2] "v"(q[2]), [q3] "v"(q[3]), [q4] "v"(q[4]), [q5] "v"(q[5]), [q6] "v"(q[6]), [q7] "v"(q[7]), [kn] "n"(8192)
+        : "memory");
+}
+__device__ __forceinline__ void score_products(const uint32_t (&a)[4], const bf16x8 (&q)[4], f32x16 &sx, f32x16 &sn)
+{
+    uint4 b[4];
+    asm volatile(
+        "ds_read_b128 %[b0], %[a0]\n\t"
+        "ds_read_b128 %[b1], %[a1]\n\t"
+        "ds_read_b128 %[b2], %[a2]\n\t"
+        "ds_read_b128 %[b3], %[a3]\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sx], %[q0], %[b0], 0\n\t"
+        "ds_read_b128 %[b0], %[a0] offset:%[kn]\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sx], %[q1], %[b1], %[sx]\n\t"
+        "ds_read_b128 %[b1], %[a1] offset:%[kn]\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sx], %[q2], %[b2], %[sx]\n\t"
+        "ds_read_b128 %[b2], %[a2] offset:%[kn]\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sx], %[q3], %[b3], %[sx]\n\t"
+        "ds_read_b128 %[b3], %[a3] offset:%[kn]\n\t"
+        "s_waitcnt lgkmcnt(3)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sn], %[q0], %[b0], 0\n\t"
+        "s_waitcnt lgkmcnt(2)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sn], %[q1], %[b1], %[sn]\n\t"
+        "s_waitcnt lgkmcnt(1)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sn], %[q2], %[b2], %[sn]\n\t"
+        "s_waitcnt lgkmcnt(0)\n\t"
+        "v_mfma_f32_32x32x16_bf16 %[sn], %[q3], %[b3], %[sn]\n\t"
+        "s_nop 11\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : [sx] "=&v"(sx), [sn] "=&v"(sn), [b0] "=&v"(b[0]), [b1] "=&v"(b[1]), [b2] "=&v"(b[2]), [b3] "=&v"(b[3])
+        : [a0] "v"(a[0]), [a1] "v"(a[1]), [a2] "v"(a[2]), [a3] "v"(a[3]),
+          [q0] "v"(q[0]), [q1] "v"(q[1]), [q2] "v"(q[2]), [q3] "v"(q[3]), [kn] "n"(4096)
+        : "memory");
+}
+
+struct ScoreArgs {
+    const uint16_t *kmax, *kmin;
+    float *scores;
+    int reduce, last_node;
+    int row0, rows;       // the query rows that count lie in row0 .. rows - 1 (row0: a multiple of 32)
+    int waves;            // of a workgroup
+    int tiles, groups;    // tiles of a workgroup; workgroups of a (sequence, KV head)
+    int sums;             // partial sums per tile and lane: one per block of 32 rows, blocks 16 apart share one
+    int by_xcd;           // Hkv % 8 == 0: grid (groups * 8, Hkv / 8, batch), KV head g on XCD g % 8; else (groups, Hkv, batch)
+    FastDiv div_G, div_B;
+};
+// bytes of a tile in LDS (Kmax | Kmin), and of a workgroup: tiles and partial sums
+constexpr int score_tile_bytes(int D) { return 128 * D; }
+static size_t score_lds(int D, int tiles, int sums) { return (size_t)tiles * (score_tile_bytes(D) + sums * 256); }
+
+// BOUND: the channel-wise bound instead of eq. 2.  Per channel the larger product is q * Kmax
+// where q >= 0 and q * Kmin where q < 0 (Kmax >= Kmin), so the bound is the sum of two inner
+// products as well: max(q, 0) . Kmax + min(q, 0) . Kmin, accumulated into one tile.
+// ACROSS: the scores are read by another workgroup of this launch: agent-scope stores, which go
+// past the caches that are private to a part of the chip.
+// group, g, b: which piece of work (the kernel's mapping of blockIdx)
+template <int D, bool BOUND, bool ACROSS>
+__device__ __forceinline__ void score_tiles(const Shape &s, const ScoreArgs &a, const int group, const int g, const int b)
+{
+    constexpr int KS = D / 16;                  // k-steps
+    constexpr int LPR = D / 8, RPO = 64 / LPR;  // lanes per row, rows per 1 KiB DMA operation
+    constexpr int OPS = D / 16;                 // DMA operations of one half (Kmax or Kmin) of a tile
+    constexpr int HALF = 64 * D, TILE = 2 * HALF;
+    // the summary tiles of this workgroup's blocks: row-major, 2 D bytes per block, the
+    // 16-byte pieces of row t stored at piece index p ^ (t & 15) (64 channels: p ^ ((t >> 1) & 7)) so that
+    // the operand reads (16 lanes per cycle, same piece, different rows) spread over all 64 banks
+    extern __shared__ __attribute__((aligned(1024))) char score_smem[];
+    char *tile = score_smem;
+    float *red = (float *)(score_smem + a.tiles * TILE);   // [a.sums][tile][lane]
+    const int lane = threadIdx.x & 63, W = a.waves;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 31, kg = lane >> 5;
+    const int i0 = group * 32 * a.tiles;
+    const int R = s.M * s.G;
+    // a vector load: a scalar one would hold up whoever waits for an argument.  One sequence: only needed at the very end
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    const int L_v = s.ctx_len[b + zero];
+    // query rows r0 .. r0 + 31 as A operand: lane = row (a wavefront without a block of rows of its own reads the last row and drops it)
+    int r0 = a.row0 + wave * 32;
+    bf16x8 q[KS];
+    auto read_q = [&]() {
+        const int r = min(r0 + n, R - 1);
+        const int j = (int)a.div_G.div((uint32_t)r), hh = r - j * s.G;
+        const uint16_t *qrow = (const uint16_t *)s.q + (((int64_t)b * s.M + j) * s.Hq + g * s.G + hh) * D + kg * 8;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) q[ks] = __builtin_bit_cast(bf16x8, *(const uint4 *)(qrow + ks * 16));
+    };
+    auto blocks = [&]() -> int {
+        const int L = __builtin_amdgcn_readfirstlane(L_v);
+        const int nb = L > 0 ? (int)a.div_B.div((uint32_t)L + (uint32_t)s.B - 1u) : 0;
+        return min(nb, s.max_blocks);
+    };
+    // in a batch the grid covers the longest sequence: workgroups past the end of a shorter one leave
+    // at once (there the wait for the length is cheaper than their reads)
+    const int lim = s.batch > 1 ? blocks() : s.max_blocks;
+    if (i0 >= lim) return;   // (only out of this function: the workgroup still counts itself in)
+    const int n_t = min(a.tiles, (lim - i0 + 31) >> 5);
+
+    // Summary rows go from memory straight into LDS (DMA operations of 1 KiB shared by the
+    // wavefronts; operation d of a tile brings RPO rows of Kmax (d < OPS) or Kmin, LPR lanes per row).  Rows past the end of
+    // the arrays repeat the last row; their scores are never stored.
+    {
+        const int rl = lane / LPR, pos = lane % LPR;
+        const int64_t arr_row0 = ((int64_t)b * s.Hkv + g) * s.max_blocks;
+        const uintptr_t to_min = (uintptr_t)a.kmin - (uintptr_t)a.kmax;   // (chosen as pointers, they are read from memory on every turn)
+        for (int d = wave; d < 2 * OPS * n_t; d += W) {
+            const int i = d & (OPS - 1), row = RPO * i + rl, t = d / (2 * OPS);
+            const int blk = min(i0 + 32 * t + row, s.max_blocks - 1);
+            const int piece = pos ^ (D == 128 ? row & 15 : (row >> 1) & 7);
+            const char *src = (const char *)((uintptr_t)a.kmax + ((d & OPS) ? to_min : 0)) + ((arr_row0 + blk) * D) * 2 + 16 * piece;
+            __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(tile + (d / OPS) * HALF + i * 1024), 16, 0, 2);   // streaming hint: read once
+        }
+    }
+    read_q();
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wavefront's DMA operations and query rows are in
+    __syncthreads();                      // ... and so are everybody else's
+    for (int rb = wave; r0 < a.rows; rb += W) {   // block of 32 rows, from row0 on
+        // summary tiles as B operands: lane = block, channels 16*ks + 8*kg .. +8
+        const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)tile + (uint32_t)n * (2u * D) +
+                              ((16u * (uint32_t)kg) ^ (D == 128 ? 16u * ((uint32_t)n & 15u) : 16u * (((uint32_t)n >> 1) & 7u)));
+        for (int t = 0; t < n_t; ++t) {
+            uint32_t at[KS];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) at[ks] = (base + (uint32_t)(t * TILE)) ^ (32u * (uint32_t)ks);
+            f32x16 sx, sn;
+            if constexpr (BOUND) {
+#pragma unroll
+                for (int x = 0; x < 16; ++x) sx[x] = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    // the packed bf16 pairs split by sign: 0xffff in the halves whose sign bit is set
+                    const uint4 w4 = __builtin_bit_cast(uint4, q[ks]);
+                    const uint32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+                    uint32_t pw[4], nw[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t m = ((w[e] >> 15) & 0x00010001u) * 0xffffu;
+                        nw[e] = w[e] & m;
+                        pw[e] = w[e] & ~m;
+                    }
+                    const char *p = tile + (at[ks] - (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)tile);
+                    const bf16x8 bx = __builtin_bit_cast(bf16x8, *(const uint4 *)p), bn = __builtin_bit_cast(bf16x8, *(const uint4 *)(p + HALF));
+                    sx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, make_uint4(pw[0], pw[1], pw[2], pw[3])), bx, sx, 0, 0, 0);
+                    sx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, make_uint4(nw[0], nw[1], nw[2], nw[3])), bn, sx, 0, 0, 0);
+                }
+            } else {
+                score_products(at, q, sx, sn);
+            }
+            float *mine = red + ((rb & (kScoreSums - 1)) * a.tiles + t) * 64 + lane;
+            float acc = rb < kScoreSums ? (a.reduce == SPECPV_REDUCE_MAX ? -INFINITY : 0.f) : *mine;
+            // accumulator slot x holds row r0 + (x>>2)*8 + kg*4 + (x&3) of this lane's block
+            if (a.reduce != SPECPV_REDUCE_LAST && r0 + 32 <= R) {
+                // all 32 rows count (every wavefront but the one with the ragged end): no per-row tests; the
+                // same order of operations as below
+                if (a.reduce == SPECPV_REDUCE_MAX) {
+#pragma unroll
+                    for (int x = 0; x < 16; ++x) acc = fmaxf(acc, BOUND ? sx[x] : fmaxf(sx[x], sn[x]));
+                } else {
+#pragma unroll
+                    for (int x = 0; x < 16; ++x) acc += BOUND ? sx[x] : fmaxf(sx[x], sn[x]);
+                }
+            } else {
+                const int lo = a.reduce == SPECPV_REDUCE_LAST ? a.last_node * s.G : 0, hi = a.reduce == SPECPV_REDUCE_LAST ? lo + s.G : R;
+#pragma unroll
+                for (int x = 0; x < 16; ++x) {
+                    const int row = r0 + (x >> 2) * 8 + kg * 4 + (x & 3);
+                    const float sv = BOUND ? sx[x] : fmaxf(sx[x], sn[x]);
+                    if (row >= lo && row < hi) acc = a.reduce == SPECPV_REDUCE_MAX ? fmaxf(acc, sv) : acc + sv;
+                }
+            }
+            *mine = acc;
+        }
+        r0 += W * 32;
+        if (r0 < a.rows) read_q();
+    }
+    __syncthreads();
+    const int nb = blocks();
+    for (int t = wave; t < n_t; t += W) {   // a wavefront per tile
+        float sum = red[t * 64 + lane];
+        for (int w = 1; w < a.sums; ++w) {
+            const float o = red[(w * a.tiles + t) * 64 + lane];
+            sum = a.reduce == SPECPV_REDUCE_MAX ? fmaxf(sum, o) : sum + o;
+        }
+        const float other = __shfl_xor(sum, 32);
+        float out;
+        if (a.reduce == SPECPV_REDUCE_MAX) out = fmaxf(sum, other);
+        else if (a.reduce == SPECPV_REDUCE_MEAN) out = (sum + other) / (float)R;
+        else out = (sum + other) / (float)s.G;
+        const int blk = i0 + 32 * t + n;
+        if (kg == 0 && blk < nb) {
+            float *dst = a.scores + ((int64_t)b * s.Hkv + g) * s.max_blocks + blk;
+            if (ACROSS) __hip_atomic_store((uint32_t *)dst, __float_as_uint(out), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else *dst = out;
+        }
+    }
+}
+
+// Tiles, wavefronts and workgroups for a shape (score_mfma.hip).  keep_all: one wavefront per block of 32 query rows, as the
+// selection in the same launch needs them.
+ScoreArgs score_plan(const Shape &s, const void *kmax, const void *kmin, int reduce, int last_node, float *scores, bool keep_all);
+
+}  // namespace specpv
