@@ -121,8 +121,8 @@ typedef struct specpv_select_cfg {
  * A workspace must be ZERO-FILLED ONCE before its first use (hipMemset, torch.zeros): its first
  * 64 KiB hold the arrival words through which the workgroups of the single-kernel route of
  * specpv_partial_verify_attn (specpv_debug_set_route) find out which of them finishes a row tile, and
- * those of the one-launch route of the selection (specpv_debug_set_select_route) which of them selects; a commit
- * with lists keeps its count of missing list entries there between its two launches.
+ * those of the one-launch route of the selection (specpv_debug_set_select_route) which of them selects; a commit's
+ * find out there which of them moves the counters, and count list entries without room.
  * Every call leaves them zero again, so one fill at
  * allocation is enough, whatever shapes use the workspace afterwards.
  * The size is what these descriptors' calls make best use of.  A smaller tree, fewer sequences or a shorter
@@ -284,8 +284,8 @@ typedef struct specpv_lists {
  * no free entry in a list row of sequence b.  Both are 0 unless the caller under-sized the
  * cache, the buffer or the list rows; a caller that cannot rule that out has to check them.
  * Writes through kv->k, kv->v (rows from L_b on; the allocation must cover max_blocks * B
- * tokens) and kv->ctx_len, n_pending [batch] (device), in stream order.  Workspace: 4 bytes
- * per sequence (specpv_workspace_bytes covers it). */
+ * tokens) and kv->ctx_len, n_pending [batch] (device), in stream order.  Workspace: its zeroed head,
+ * and 4 bytes per sequence (specpv_workspace_bytes covers it). */
 int specpv_commit_accepted(const specpv_kv *kv, void *buf_k, void *buf_v, int32_t pending_cap, int32_t M_tree,
                            int32_t *n_pending, const int32_t *accepted, const int32_t *n_accepted,
                            int32_t max_accept, specpv_mode mode, void *kmax, void *kmin,

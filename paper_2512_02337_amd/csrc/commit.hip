@@ -17,15 +17,52 @@ struct CommitLayers {
     void *kmax[kCommitLayers], *kmin[kCommitLayers];
     int32_t *idx[kCommitLayers], *cnt[kCommitLayers];
 };
-// Sequences per launch: one word each, at the head of the workspace, tells the update which of them had a list without
-// room for a block (0 otherwise; zero before and after the call).
-constexpr int kCommitSeqs = (int)(kArriveBytes / sizeof(uint32_t));
+// Words of a sequence at the head of the workspace, zero before and after the call: list entries that found no room, the
+// workgroups that have arrived (see arrive_and_update), and those of each of sixteen groups of them.  Each on a 128-byte line
+// of its own where a launch has few enough sequences.
+constexpr int kCommitWords = 18;
+constexpr int kCommitSeqs = (int)(kArriveBytes / (kCommitWords * sizeof(uint32_t)));   // sequences per launch
+struct CommitArrive {
+    uint32_t *words;
+    int stride;      // of a sequence's words, in words
+    int workgroups;  // of a sequence; 0: a launch follows that moves the counters
+    int32_t *ctx_len, *n_pending, *dropped;
+};
+
+// The counters (lengths, pending tokens) are read by every workgroup and moved once: by the workgroup of a sequence that finds
+// itself last to have read them.  Nobody waits, and no launch of a thread a sequence stands behind this one (32 layers: kernels
+// 7.6 + 1.4 us and the gap between them, 8.4 so; a pass, which is the host's time, 14.6 -> 11.5 us side by side).  Counting goes
+// over sixteen groups: atomics on one address go one after the other, 70 ns each.  One lane calls this, behind the barrier that
+// its workgroup's reads of the counters stand in front of; a count of missed entries has to be there before its arrival is.
+__device__ __forceinline__ void arrive_and_update(const CommitArrive &ar, int bl, int b, int id, uint32_t missed, bool lists, bool to_cache, int L, int n_plus_a, int total)
+{
+    uint32_t *const w = ar.words + (int64_t)bl * kCommitWords * ar.stride;
+    if (missed) {
+        const uint32_t before = __hip_atomic_fetch_max(w, missed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::"v"(before) : "memory");
+    }
+    if (!ar.workgroups) return;
+    auto last_of = [](uint32_t *word, uint32_t n) {
+        if (__hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u != n) return false;
+        __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return true;
+    };
+    const int N = ar.workgroups, j = id & 15;
+    if (N > 16 && !last_of(w + (2 + j) * ar.stride, (uint32_t)((N - j + 15) >> 4))) return;
+    if (!last_of(w + ar.stride, (uint32_t)min(N, 16))) return;
+    const uint32_t all_missed = lists ? __hip_atomic_exchange(w, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    if (to_cache) ar.ctx_len[b] = L + total;
+    ar.n_pending[b] = to_cache ? 0 : total;
+    if (ar.dropped) {
+        ar.dropped[2 * b] = n_plus_a - total;        // tokens that found no room
+        ar.dropped[2 * b + 1] = (int32_t)all_missed;   // list entries that found no room
+    }
+}
 
 // Everything that a commit does for one (KV head, sequence, layer), by one workgroup; a row of D elements is
 // D * sizeof(T) / 16 lanes.  What bounds it is the chain of cold reads -- counters, then rows, then the touched
 // blocks' older rows -- of a few KiB each, so the whole of it is one launch (copy, lists and summaries as launches of
-// their own took 4.9 + 3.3 + 8.4 us for 32 layers, of which this takes 7.5: the whole call 24 -> 15 us) and only the counters, which every
-// workgroup reads, are moved by a launch behind it.
+// their own took 4.9 + 3.3 + 8.4 us for 32 layers, of which this takes 7.5).
 //  * Every source row is read into registers before anything is written (the compaction of the buffer moves rows
 //    within one array).
 //  * Lists (Section 3.3: the committed tokens stay part of the partial cache): every block that received a token joins
@@ -35,7 +72,7 @@ constexpr int kCommitSeqs = (int)(kArriveBytes / sizeof(uint32_t));
 template <typename T, int D>
 __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, int b0, int P, int Mt, const int32_t *n_pending,
                                                      const int32_t *accepted, const int32_t *n_accepted, int max_accept, int to_cache,
-                                                     int with_sums, int n_sel, uint32_t *missed_words)
+                                                     int with_sums, int n_sel, CommitArrive ar)
 {
     T *const buf_k = (T *)lay.buf_k[blockIdx.z], *const buf_v = (T *)lay.buf_v[blockIdx.z];
     T *const cache_k = (T *)lay.k[blockIdx.z], *const cache_v = (T *)lay.v[blockIdx.z];
@@ -90,26 +127,26 @@ __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, 
             }
         }
     }
-    if (!to_cache || total == 0 || !(with_sums || n_sel)) return;   // uniform
     const int first = L / s.B, last = (L + total - 1) / s.B;        // blocks that received tokens (all below max_blocks)
-    if (n_sel && wave == 3) {
-        int32_t *row = lay.idx[blockIdx.z] + ((int64_t)b * s.Hkv + g) * n_sel;
-        int32_t *cntp = lay.cnt[blockIdx.z] + (int64_t)b * s.Hkv + g;
-        const int cnt0 = min(max(*cntp, 0), n_sel);
-        int cnt = cnt0, missed = 0;
-        for (int blk = first; blk <= last; ++blk) {
-            bool here = false;
-            for (int i = lane; i < cnt0; i += 64) here |= row[i] == blk;
-            if (__any(here)) continue;
-            if (cnt < n_sel) { if (lane == 0) row[cnt] = blk; ++cnt; }
-            else ++missed;
+    if (wave == 3) {
+        int missed = 0;
+        if (n_sel && to_cache && total > 0) {
+            int32_t *row = lay.idx[blockIdx.z] + ((int64_t)b * s.Hkv + g) * n_sel;
+            int32_t *cntp = lay.cnt[blockIdx.z] + (int64_t)b * s.Hkv + g;
+            const int cnt0 = min(max(*cntp, 0), n_sel);
+            int cnt = cnt0;
+            for (int blk = first; blk <= last; ++blk) {
+                bool here = false;
+                for (int i = lane; i < cnt0; i += 64) here |= row[i] == blk;
+                if (__any(here)) continue;
+                if (cnt < n_sel) { if (lane == 0) row[cnt] = blk; ++cnt; }
+                else ++missed;
+            }
+            if (lane == 0) *cntp = cnt;
         }
-        if (lane == 0) {
-            *cntp = cnt;
-            if (missed) atomicMax(&missed_words[bl], (uint32_t)missed);
-        }
+        if (lane == 0) arrive_and_update(ar, bl, b, (int)blockIdx.z * s.Hkv + g, (uint32_t)missed, n_sel > 0, to_cache != 0, L, n + a, total);
     }
-    if (!with_sums) return;
+    if (!to_cache || total == 0 || !with_sums) return;   // uniform
     __syncthreads();   // the new rows are in the cache (stores of this workgroup, read back by it)
     constexpr int WRP = 64 / LPR;   // rows per wavefront pass
     const int wr = lane / LPR;
@@ -149,32 +186,6 @@ __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, 
     }
 }
 
-// One thread per sequence, behind everything that reads the counters: the new lengths, and what found no room.
-__global__ void commit_update_kernel(Shape s, int b0, int n_seq, int P, int32_t *ctx_len, int32_t *n_pending,
-                                     const int32_t *n_accepted, int max_accept, int to_cache, uint32_t *missed_words, int32_t *dropped)
-{
-    const int bl = blockIdx.x * blockDim.x + threadIdx.x, b = b0 + bl;
-    if (bl >= n_seq) return;
-    const int L = ctx_len[b];
-    const int n = min(max(n_pending[b], 0), P);
-    const int a = min(max(n_accepted[b], 0), max_accept);
-    const uint32_t missed = missed_words ? missed_words[bl] : 0u;   // nullptr: a commit without lists
-    int stored;
-    if (to_cache) {
-        stored = min(n + a, max(0, s.max_blocks * s.B - L));
-        ctx_len[b] = L + stored;
-        n_pending[b] = 0;
-    } else {
-        stored = min(n + a, P);
-        n_pending[b] = stored;
-    }
-    if (missed) missed_words[bl] = 0u;
-    if (dropped) {
-        dropped[2 * b] = n + a - stored;        // tokens that found no room
-        dropped[2 * b + 1] = (int32_t)missed;   // list entries that found no room
-    }
-}
-
 // layers: n_layers entries each of k, v (the caches), buf_k, buf_v (the buffers) and, for a commit to
 // the cache, kmax, kmin (or all NULL).  s carries the shape, the strides and ctx_len (shared).
 hipError_t launch_commit(const Shape &s, int dtype, int n_layers, void *const *k, void *const *v,
@@ -188,7 +199,8 @@ hipError_t launch_commit(const Shape &s, int dtype, int n_layers, void *const *k
     const bool with_lists = to_cache && lists;
     for (int b0 = 0; b0 < s.batch; b0 += kCommitSeqs) {
         const int n_seq = s.batch - b0 < kCommitSeqs ? s.batch - b0 : kCommitSeqs;
-        // the workgroups of every layer read the counters, so all of them go before the update
+        // the workgroups of every layer read the counters: those of the last launch move them
+        CommitArrive ar{missed_words, (size_t)n_seq * kCommitWords * 128 <= kArriveBytes ? 32 : 1, 0, (int32_t *)s.ctx_len, n_pending, dropped};
         for (int l0 = 0; l0 < n_layers; l0 += kCommitLayers) {
             const int nl = n_layers - l0 < kCommitLayers ? n_layers - l0 : kCommitLayers;
             CommitLayers lay = {};
@@ -199,9 +211,10 @@ hipError_t launch_commit(const Shape &s, int dtype, int n_layers, void *const *k
                 if (with_lists) { lay.idx[l] = lists[l0 + l].sel_idx; lay.cnt[l] = lists[l0 + l].sel_count; }
             }
             const dim3 grid(s.Hkv, n_seq, nl);
+            ar.workgroups = l0 + nl == n_layers ? s.Hkv * nl : 0;
 #define SPECPV_COMMIT(T, DD)                                                                                                      \
     hipLaunchKernelGGL((commit_kernel<T, DD>), grid, dim3(256), 0, st, s, lay, b0, P, Mt, n_pending, accepted, n_accepted, max_accept, \
-                       to_cache, summaries ? 1 : 0, with_lists ? lists[0].n_sel : 0, missed_words)
+                       to_cache, summaries ? 1 : 0, with_lists ? lists[0].n_sel : 0, ar)
             if (dtype == SPECPV_BF16) {
                 if (s.D == 128) SPECPV_COMMIT(bf16_t, 128); else SPECPV_COMMIT(bf16_t, 64);
             } else {
@@ -211,10 +224,6 @@ hipError_t launch_commit(const Shape &s, int dtype, int n_layers, void *const *k
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(commit_update_kernel, dim3((n_seq + 63) / 64), dim3(64), 0, st, s, b0, n_seq, P,
-                           (int32_t *)s.ctx_len, n_pending, n_accepted, max_accept, to_cache, with_lists ? missed_words : nullptr, dropped);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
