@@ -119,13 +119,16 @@ struct ScoreArgs {
     int row0, rows;       // the query rows that count lie in row0 .. rows - 1 (row0: a multiple of 32)
     int waves;            // of a workgroup
     int tiles, groups;    // tiles of a workgroup; workgroups of a (sequence, KV head)
+    int staged;           // the query rows go through LDS (read_q)
     int sums;             // partial sums per tile and lane: one per block of 32 rows, blocks 16 apart share one
     int by_xcd;           // Hkv % 8 == 0: grid (groups * 8, Hkv / 8, batch), KV head g on XCD g % 8; else (groups, Hkv, batch)
     FastDiv div_G, div_B;
 };
-// bytes of a tile in LDS (Kmax | Kmin), and of a workgroup: tiles and partial sums
+// bytes of a tile in LDS (Kmax | Kmin), and of a workgroup: tiles, partial sums and, staged, 32 half rows (64 channels: rows)
+// of queries per wavefront
 constexpr int score_tile_bytes(int D) { return 128 * D; }
-static size_t score_lds(int D, int tiles, int sums) { return (size_t)tiles * (score_tile_bytes(D) + sums * 256); }
+constexpr int kScoreStage = 4096;
+static inline size_t score_lds(int D, int tiles, int sums, int staged_waves) { return (size_t)tiles * (score_tile_bytes(D) + sums * 256) + (size_t)staged_waves * kScoreStage; }
 
 // BOUND: the channel-wise bound instead of eq. 2.  Per channel the larger product is q * Kmax
 // where q >= 0 and q * Kmin where q < 0 (Kmax >= Kmin), so the bound is the sum of two inner
@@ -133,7 +136,8 @@ static size_t score_lds(int D, int tiles, int sums) { return (size_t)tiles * (sc
 // ACROSS: the scores are read by another workgroup of this launch: agent-scope stores, which go
 // past the caches that are private to a part of the chip.
 // group, g, b: which piece of work (the kernel's mapping of blockIdx)
-template <int D, bool BOUND, bool ACROSS>
+// STAGED: see read_staged.
+template <int D, bool BOUND, bool ACROSS, bool STAGED>
 __device__ __forceinline__ void score_tiles(const Shape &s, const ScoreArgs &a, const int group, const int g, const int b)
 {
     constexpr int KS = D / 16;                  // k-steps
@@ -158,12 +162,42 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const ScoreArgs &a, 
     // query rows r0 .. r0 + 31 as A operand: lane = row (a wavefront without a block of rows of its own reads the last row and drops it)
     int r0 = a.row0 + wave * 32;
     bf16x8 q[KS];
-    auto read_q = [&]() {
+    auto read_q = [&]() __attribute__((always_inline)) {
         const int r = min(r0 + n, R - 1);
         const int j = (int)a.div_G.div((uint32_t)r), hh = r - j * s.G;
         const uint16_t *qrow = (const uint16_t *)s.q + (((int64_t)b * s.M + j) * s.Hq + g * s.G + hh) * D + kg * 8;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) q[ks] = __builtin_bit_cast(bf16x8, *(const uint4 *)(qrow + ks * 16));
+    };
+    // Operand by operand a read touches 32 rows, 32 bytes of each, and a CU takes such a read in at a third of the rate of whole
+    // lines: 2.6 of 11.2 us at 60K in blocks of 16, 1.5 of 6.2 at 16K.  Staged, a read brings 128 bytes of eight rows, and they
+    // find their lanes through a corner of LDS that is this wavefront's own (no barrier): 16-byte piece p of row t at
+    // p ^ ((t >> 1) & 7).  The later turns of a wavefront read operand by operand: they have no registers for more.
+    constexpr int H = D / 64;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 raw[H][4];
+    auto load_staged = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = min(r0 + 8 * i + (lane >> 3), R - 1);
+            const int j = (int)a.div_G.div_straight((uint32_t)r), hh = r - j * s.G;
+            const uint16_t *qrow = (const uint16_t *)s.q + (((int64_t)b * s.M + j) * s.Hq + g * s.G + hh) * D + (lane & 7) * 8;
+#pragma unroll
+            for (int h = 0; h < H; ++h) raw[h][i] = *(const u32x4 *)(qrow + 64 * h);
+        }
+    };
+    auto read_staged = [&]() __attribute__((always_inline)) {
+        char *mine = (char *)(red + a.sums * a.tiles * 64) + wave * kScoreStage;
+        const int to = (lane >> 3) * 128, from = n * 128;
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) *(u32x4 *)(mine + 1024 * i + to + 16 * ((lane & 7) ^ ((4 * i + (lane >> 4)) & 7))) = raw[h][i];
+            asm volatile("" ::: "memory");   // (other lanes' values: the compiler keeps the order of LDS operations only if told)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) q[4 * h + x] = __builtin_bit_cast(bf16x8, *(const u32x4 *)(mine + from + 16 * ((2 * x + kg) ^ ((n >> 1) & 7))));
+            asm volatile("" ::: "memory");
+        }
     };
     auto blocks = [&]() -> int {
         const int L = __builtin_amdgcn_readfirstlane(L_v);
@@ -176,6 +210,7 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const ScoreArgs &a, 
     if (i0 >= lim) return;   // (only out of this function: the workgroup still counts itself in)
     const int n_t = min(a.tiles, (lim - i0 + 31) >> 5);
 
+    if constexpr (STAGED) load_staged();   // (in front of the tiles: reads come back in their order)
     // Summary rows go from memory straight into LDS (DMA operations of 1 KiB shared by the
     // wavefronts; operation d of a tile brings RPO rows of Kmax (d < OPS) or Kmin, LPR lanes per row).  Rows past the end of
     // the arrays repeat the last row; their scores are never stored.
@@ -191,7 +226,8 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const ScoreArgs &a, 
             __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(tile + (d / OPS) * HALF + i * 1024), 16, 0, 2);   // streaming hint: read once
         }
     }
-    read_q();
+    if constexpr (STAGED) read_staged();
+    else read_q();
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wavefront's DMA operations and query rows are in
     __syncthreads();                      // ... and so are everybody else's
     for (int rb = wave; r0 < a.rows; rb += W) {   // block of 32 rows, from row0 on

@@ -30,7 +30,7 @@ namespace specpv {
 // the group in on the pair's own word.  Pair p = b * Hkv + g owns the words arrive[(9 p + i) * wstride],
 // i = 0 for the pair, 1 + j for group j; all are zero before the launch, and whoever finds a count
 // complete sets it back to zero.
-template <int D, bool BOUND, int P>
+template <int D, bool BOUND, int P, bool STAGED>
 __global__ __launch_bounds__(64 * kScoreMaxWaves) void score_mfma_kernel(Shape s, ScoreArgs a, TopkArgs ta, unsigned long long *arrive, int wstride)
 {
     // every argument in one trip to memory; left to itself the compiler asks for each where it is first used
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(64 * kScoreMaxWaves) void score_mfma_kernel(Shape s
         asm volatile("" :: "s"(arrive), "s"(wstride), "s"(ta.ns), "s"(ta.nr), "s"(ta.k), "s"(ta.n_row), "s"(ta.sel_idx), "s"(ta.sel_count));
     const int group = a.by_xcd ? (int)blockIdx.x >> 3 : (int)blockIdx.x;
     const int g = a.by_xcd ? (int)blockIdx.y * 8 + ((int)blockIdx.x & 7) : (int)blockIdx.y, b = blockIdx.z;
-    score_tiles<D, BOUND, P != 0>(s, a, group, g, b);
+    score_tiles<D, BOUND, P != 0, STAGED>(s, a, group, g, b);
     if constexpr (P != 0) {
         __shared__ TopkLds lds;
         __shared__ int is_last;
@@ -113,9 +113,15 @@ ScoreArgs score_plan(const Shape &s, const void *kmax, const void *kmin, int red
     int64_t T = (total + per_cu * cus - 1) / (per_cu * cus);
     T = T < 1 ? 1 : (T > most ? most : T);
     a.waves = waves;
-    a.tiles = (int)T;
     a.sums = blocks32 < kScoreSums ? blocks32 : kScoreSums;
+    // Query rows through LDS where that costs no workgroup its place on a CU, and for more than four wavefronts (three sequences of
+    // 128K, 30 nodes, four wavefronts of two tiles 9.5 / 9.9 us): 60K in blocks of 16 10.9 / 10.1 us, 128K 8.0 / 7.0, 16K 6.1 / 5.4,
+    // 45 nodes, six wavefronts, 128K 7.3 / 6.4, 64K at G = 5, ten, 6.9 / 6.0 (scoring alone, kernel trace).
+    auto fit = [&](int staged_waves) { const int n = (int)(160 * 1024 / score_lds(s.D, (int)T, a.sums, staged_waves)); return n < per_cu ? n : per_cu; };
+    if (T == 3 && waves > 4 && waves <= 8 && !keep_all) T = 2;   // (three leave no room to stage; 1536 tiles 16.3 us, 13.5 so)
+    a.tiles = (int)T;
     a.groups = (int)((tiles1 + T - 1) / T);
+    a.staged = !keep_all && waves > 4 && fit(waves) == fit(0);
     a.by_xcd = s.Hkv % 8 == 0;
     a.div_G = make_fastdiv((uint32_t)s.G);
     a.div_B = make_fastdiv((uint32_t)s.B);
@@ -131,22 +137,22 @@ hipError_t launch_scores_mfma(const Shape &s, const void *kmax, const void *kmin
     const ScoreArgs a = score_plan(s, kmax, kmin, reduce, last_node, scores, sel != nullptr);
     const int waves = a.waves;
     const dim3 grid(a.by_xcd ? a.groups * 8 : a.groups, a.by_xcd ? s.Hkv / 8 : s.Hkv, s.batch), block(64 * waves);
-    const size_t lds = score_lds(s.D, a.tiles, a.sums);
+    const size_t lds = score_lds(s.D, a.tiles, a.sums, a.staged ? waves : 0);
     const int P = !sel ? 0 : (s.max_blocks <= 256 * 4 ? 4 : (s.max_blocks <= 256 * 8 ? 8 : 16));
     const TopkArgs ta = sel ? *sel : TopkArgs{0, 0, 0, 0, nullptr, nullptr};
     // every arrival word on a 128-byte line of its own where the region is large enough for that
     const int wstride = (size_t)s.batch * s.Hkv * 9 * 128 <= kArriveBytes ? 16 : 1;
-#define SPECPV_LAUNCH(DD, BOUND, PP)                                                                                        \
+#define SPECPV_LAUNCH(DD, BOUND, PP, ST)                                                                                        \
     do {                                                                                                                    \
         static PerDeviceOnce once;   /* one per kernel instantiation */                                                    \
-        auto kern = score_mfma_kernel<DD, BOUND, PP>;                                                                       \
-        const hipError_t e0 = once.run([&] { return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)score_lds(DD, kScoreMostTiles, kScoreSums)); }); \
+        auto kern = score_mfma_kernel<DD, BOUND, PP, ST>;                                                                       \
+        const hipError_t e0 = once.run([&] { return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)score_lds(DD, kScoreMostTiles, kScoreSums, kScoreMaxWaves)); }); \
         if (e0 != hipSuccess) return e0;                                                                                    \
         hipLaunchKernelGGL(kern, grid, block, lds, st, s, a, ta, arrive, wstride);                                          \
     } while (0)
 #define SPECPV_LAUNCH_P(DD, BOUND)                                                                                          \
-    do { if (P == 0) SPECPV_LAUNCH(DD, BOUND, 0); else if (P == 4) SPECPV_LAUNCH(DD, BOUND, 4);                              \
-         else if (P == 8) SPECPV_LAUNCH(DD, BOUND, 8); else SPECPV_LAUNCH(DD, BOUND, 16); } while (0)
+    do { if (P == 0 && a.staged) SPECPV_LAUNCH(DD, BOUND, 0, true); else if (P == 0) SPECPV_LAUNCH(DD, BOUND, 0, false); else if (P == 4) SPECPV_LAUNCH(DD, BOUND, 4, false);                              \
+         else if (P == 8) SPECPV_LAUNCH(DD, BOUND, 8, false); else SPECPV_LAUNCH(DD, BOUND, 16, false); } while (0)
     if (s.D == 128) { if (kind == SPECPV_SCORE_CHANNEL_BOUND) SPECPV_LAUNCH_P(128, true); else SPECPV_LAUNCH_P(128, false); }
     else { if (kind == SPECPV_SCORE_CHANNEL_BOUND) SPECPV_LAUNCH_P(64, true); else SPECPV_LAUNCH_P(64, false); }
 #undef SPECPV_LAUNCH_P
