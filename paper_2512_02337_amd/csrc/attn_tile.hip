@@ -131,23 +131,26 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
 #pragma unroll
         for (int x = 0; x < NID; ++x) idv[x] = list[min(lane + 64 * x, last)];   // (past the end: never asked for, slot < cnt <= n_sel)
     }
-    // The query rows of a row block are the same for its TG wavefronts: each brings its share of the eight k-steps
-    // straight into LDS, laid out as the operands are read (k-step ks: 1 KiB, lane l's 16 bytes at 16 l), and all read
-    // the whole from there once the requests have landed -- fewer bytes through the CU's memory path in the phase where
-    // the first K / V chunks are requested.  TG = 2: four row blocks are more than the ring leaves free, so they stand
+    // The query rows of a row block are the same for its TG wavefronts: each brings its share of them straight into LDS, four
+    // whole rows per operation, laid out like a K tile, and all read the whole from there once the requests have landed --
+    // fewer bytes through the CU's memory path in the phase where the first K / V chunks are requested.  (A k-step per
+    // operation, 32 bytes of 32 rows each, takes the memory path three times as long: headline 16.5 -> 15.9 us a layer.  The row's
+    // head by a reciprocal: it waits for no argument, and is half a row away from the next whole number, r < 2^12.)
+    // TG = 2: four row blocks are more than the ring leaves free, so they stand
     // in the groups' last stages, whose first chunk is requested behind them.
     auto q_stage = [&](int rbq) -> char * {
         return TG == 2 ? ring + ((rbq >> 1) * STG + (STG - 1)) * kStageBytes + (rbq & 1) * 8192 : ring + kTileRing + rbq * 8192;
     };
     {
-        const int r = min(row0 + rb * 32 + n, R - 1);   // rows past the end repeat the last one; never stored
-        const int hh = (int)a.div_M.div((uint32_t)r), j = r - hh * s.M;
-        const char *qrow = (const char *)((const uint16_t *)s.q + (((int64_t)b * s.M + j) * s.Hq + g * s.G + hh) * 128 + kg * 8);
         char *dst = q_stage(rb);
+        const float inv = __builtin_amdgcn_rcpf((float)s.M);
 #pragma unroll
         for (int x = 0; x < 8 / TG; ++x) {
-            const int ks = tg * (8 / TG) + x;   // a k-step is 16 channels: 32 bytes
-            __builtin_amdgcn_global_load_lds((glb_void_ptr)(qrow + 32 * ks), (lds_void_ptr)(dst + 1024 * ks), 16, 0, 0);
+            const int i = tg * (8 / TG) + x, row = 4 * i + (lane >> 4);
+            const int r = min(row0 + rb * 32 + row, R - 1);
+            const int hh = (int)(((float)r + 0.5f) * inv), j = r - hh * s.M;
+            const char *qrow = (const char *)((const uint16_t *)s.q + (((int64_t)b * s.M + j) * s.Hq + g * s.G + hh) * 128) + 16 * ((lane & 15) ^ (row & 15));
+            __builtin_amdgcn_global_load_lds((glb_void_ptr)qrow, (lds_void_ptr)(dst + 1024 * i), 16, 0, 0);
         }
     }
 
@@ -365,8 +368,8 @@ void attn_ctx_tile_kernel(const int32_t *a_sel_idx, const int32_t *a_sel_count, 
     // This wavefront's share of the query rows has landed (the wait above); the barrier in front of the first chunk
     // covers the others' shares.
     auto read_q = [&]() {
-        const uint32_t q0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)q_stage(rb) + (uint32_t)(lane * 16);
-        const uint32_t qa[8] = {q0, q0 + 1024u, q0 + 2048u, q0 + 3072u, q0 + 4096u, q0 + 5120u, q0 + 6144u, q0 + 7168u};
+        const uint32_t q0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)q_stage(rb) + (uint32_t)n * 256u + ((16u * (uint32_t)kg) ^ (16u * ((uint32_t)n & 15u)));
+        const uint32_t qa[8] = {q0, q0 ^ 32u, q0 ^ 64u, q0 ^ 96u, q0 ^ 128u, q0 ^ 160u, q0 ^ 192u, q0 ^ 224u};
         uint4 qraw[8];
         lds_read_k<0>(qa, qraw);
 #pragma unroll
