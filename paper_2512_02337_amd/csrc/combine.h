@@ -72,18 +72,18 @@ template <> struct Chan<bf16_t, 4> {
         __builtin_nontemporal_store(v, (u32x2 *)((uint16_t *)p + i));
     }
 };
-// The lane's CPL fp32 values of a partial row (i: the row's first element + 4 * (lane & 15)), read
+// The lane's CPL fp32 values of a partial row (p: the row's first element + 4 * (lane & 15)), read
 // once: streaming hint.  Rows of 128 are stored so that piece x of all 16 lanes is one dense run
 // (partial_pos); the values come out in channel order.
-template <int CPL> __device__ __forceinline__ void load_partial(const float *p, int64_t i, float *f)
+template <int CPL> __device__ __forceinline__ void load_partial(const float *p, float *f)
 {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int x = 0; x < CPL / 4; ++x) {
 #ifndef SPECPV_PARTIAL_PLAIN
-        const f32x4 v = __builtin_nontemporal_load((const f32x4 *)(p + i + 64 * x));
+        const f32x4 v = __builtin_nontemporal_load((const f32x4 *)(p + 64 * x));
 #else
-        const f32x4 v = *(const f32x4 *)(p + i + 64 * x);
+        const f32x4 v = *(const f32x4 *)(p + 64 * x);
 #endif
         f[4 * x] = v[0]; f[4 * x + 1] = v[1]; f[4 * x + 2] = v[2]; f[4 * x + 3] = v[3];
     }
@@ -92,7 +92,7 @@ template <int CPL> __device__ __forceinline__ void load_partial(const float *p, 
 // The lane's channels of one partial as they come from memory, and as fp32 once they are used.
 template <int CPL, bool HALF> struct Part {   // fp32 form
     float f[CPL];
-    __device__ __forceinline__ void load(const float *p, int64_t row, int D, int lane16) { load_partial<CPL>(p, row * D + 4 * lane16, f); }
+    __device__ __forceinline__ void load(const char *p) { load_partial<CPL>((const float *)p, f); }
     __device__ __forceinline__ void value(float *v) const
     {
 #pragma unroll
@@ -102,10 +102,7 @@ template <int CPL, bool HALF> struct Part {   // fp32 form
 template <> struct Part<8, true> {   // fp16 form: the lane's eight adjacent channels are one 16-byte piece
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     u32x4 raw;
-    __device__ __forceinline__ void load(const float *p, int64_t row, int D, int lane16)
-    {
-        raw = __builtin_nontemporal_load((const u32x4 *)((const _Float16 *)p + row * D + lane16 * 8));
-    }
+    __device__ __forceinline__ void load(const char *p) { raw = __builtin_nontemporal_load((const u32x4 *)p); }
     __device__ __forceinline__ void value(float *v) const
     {
         typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -177,6 +174,10 @@ __device__ __forceinline__ void combine_rows(const Shape &s, const Partials &par
     }
     const int h = g * s.G + hc;
     const int64_t qrow = (((int64_t)b * s.M + j) * s.Hq + h) * D;
+    // Draft rows and partials are read from a base that the wavefront shares and 32 bits a lane (128 draft rows; 65 partials, or
+    // as many as there are workgroups, of at most 2048 rows).  In 64 bits a lane the addresses were 130 of the kernel's 1900
+    // instructions, in front of the reads: partial verification at 128K, 16 layers, 233.1 us so, 231.9 now.
+    constexpr uint32_t SZ = sizeof(T);
     if (wave == 0) SPECPV_CSTAMP(0, 0);   // entry
 
     // ---- draft-tree segment: the node itself and its ancestors, path slot 0, 1, ... ------------------------------------
@@ -194,8 +195,9 @@ __device__ __forceinline__ void combine_rows(const Shape &s, const Partials &par
         if (s.Mk > 64) par1 = par[min(lane + 64, s.Mk - 1)];
         Chan<T, CPL>::load(s.q, qrow + d0, qraw);
     };
-    const int64_t drow0 = (((int64_t)b * s.Mk) * s.Hkv + g) * D + d0;
-    const int drow_step = s.Hkv * D;   // (Mk <= 128 rows: 32-bit offsets)
+    const int64_t drow0 = ((int64_t)b * s.Mk * s.Hkv + g) * (int64_t)(D * SZ);
+    const char *const kd_base = (const char *)s.kd + drow0, *const vd_base = (const char *)s.vd + drow0;
+    const uint32_t draft_step = (uint32_t)s.Hkv * (D * SZ);
     int at = j + s.koff, last = -1;    // next slot's node; the slot's before it (the same: the path has ended)
     // N slots: a[u] is a node, bias[u] 0, or -inf behind the path's end (a[u] then repeats its last node)
     auto walk = [&](auto count, int *a, float *bias) __attribute__((always_inline)) {
@@ -221,9 +223,9 @@ __device__ __forceinline__ void combine_rows(const Shape &s, const Partials &par
     auto rows = [&](auto from, auto count) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = decltype(from)::value; u < decltype(from)::value + decltype(count)::value; ++u) {
-            const int64_t drow = drow0 + a8[u] * drow_step;
-            Chan<T, CPL>::load(s.kd, drow, kd8[u]);
-            Chan<T, CPL>::load(s.vd, drow, vd8[u]);
+            const uint32_t off = (uint32_t)a8[u] * draft_step + (uint32_t)d0 * SZ;
+            Chan<T, CPL>::load(kd_base + off, 0, kd8[u]);
+            Chan<T, CPL>::load(vd_base + off, 0, vd8[u]);
         }
     };
     auto tree_path = [&]() __attribute__((always_inline)) {
@@ -320,7 +322,9 @@ __device__ __forceinline__ void combine_rows(const Shape &s, const Partials &par
         ns = C_b > 0 ? sh.owner(at + C_b - 1) - w0 + 1 : 0;
         slot0 = w0 + bg;
     }
-    const int64_t prow0 = slot0 * R + hc * s.M + j;
+    constexpr uint32_t ROW = D * (HALF ? 2 : 4);   // bytes of a partial row
+    const char *const po_base = (const char *)part.o + slot0 * (int64_t)R * ROW, *const ml_base = (const char *)part.ml + slot0 * (int64_t)R * 8;
+    const uint32_t prow = (uint32_t)(hc * s.M + j), po_off = prow * ROW + 16u * (uint32_t)(lane & 15), po_step = (uint32_t)R * ROW;
     // (m, l) of partials u, u + 16, ... in lane u of the row's sixteen: each lane works out the weights of its own
     constexpr int KM = MULTI ? 4 : 1;   // (64 partials at a time; a pair that holds most of a batch may have more)
     const int u16 = lane & 15;
@@ -330,7 +334,7 @@ __device__ __forceinline__ void combine_rows(const Shape &s, const Partials &par
     for (int x = 0; x < CPL; ++x) o[x] = 0.f;
     auto fetch = [&](int sp0, P (&r)[NP]) {
 #pragma unroll
-        for (int u = 0; u < NP; ++u) r[u].load(part.o, prow0 + (int64_t)max(min(sp0 + u, ns - 1), 0) * R, D, u16);
+        for (int u = 0; u < NP; ++u) r[u].load(po_base + (po_off + (uint32_t)max(min(sp0 + u, ns - 1), 0) * po_step));
     };
     auto add = [&](const P &r, float wt) {
         float v[CPL];
@@ -352,7 +356,7 @@ __device__ __forceinline__ void combine_rows(const Shape &s, const Partials &par
 #pragma unroll
         for (int k = 0; k < KM; ++k) {
             const int sp = s0 + u16 + 16 * k;
-            ml[k] = sp < ns ? *(const float2 *)(part.ml + (prow0 + (int64_t)sp * R) * 2) : make_float2(-INFINITY, 0.f);
+            ml[k] = sp < ns ? *(const float2 *)(ml_base + (prow + (uint32_t)sp * (uint32_t)R) * 8u) : make_float2(-INFINITY, 0.f);
         }
         P ra[NP];
         fetch(s0, ra);
