@@ -7,7 +7,6 @@
 namespace specpv {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
@@ -87,11 +86,6 @@ struct ChunkRows {
 
 __device__ __forceinline__ bf16x8 as_bf16x8(const uint4 &u) { return __builtin_bit_cast(bf16x8, u); }
 
-__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
-{
-    bf16x2 v = {(__bf16)a, (__bf16)b};
-    return __builtin_bit_cast(uint32_t, v);
-}
 // acc + lo(p) + hi(p) for a packed bf16 pair
 __device__ __forceinline__ float add_bf16x2(uint32_t p, float acc)
 {

@@ -662,7 +662,7 @@ __device__ __forceinline__ bool attn_ctx_pass(Shape s, Partials part, MfmaArgs a
             for (int uu = 0; uu < 4; ++uu) {
                 const int j = m0 + wave * RPW + u0 + uu;
                 const float iv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv), (u0 + uu) * 8));
-                const uint32_t packed = (uint32_t)float_to_bf16_bits(acc[uu].x * iv) | ((uint32_t)float_to_bf16_bits(acc[uu].y * iv) << 16);
+                const uint32_t packed = pack_bf16x2(acc[uu].x * iv, acc[uu].y * iv);
                 if (j < s.M)
                     __builtin_nontemporal_store(packed, (uint32_t *)((uint16_t *)f.out + (((int64_t)b * s.M + j) * s.Hq + h) * 128 + chan));
             }

@@ -52,7 +52,7 @@ template <> struct Chan<bf16_t, 8> {
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
         u32x4 v;
 #pragma unroll
-        for (int x = 0; x < 4; ++x) v[x] = float_to_bf16_bits(f[2 * x]) | ((uint32_t)float_to_bf16_bits(f[2 * x + 1]) << 16);
+        for (int x = 0; x < 4; ++x) v[x] = pack_bf16x2(f[2 * x], f[2 * x + 1]);
         __builtin_nontemporal_store(v, (u32x4 *)((uint16_t *)p + i));
     }
 };
@@ -68,7 +68,7 @@ template <> struct Chan<bf16_t, 4> {
         typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
         u32x2 v;
 #pragma unroll
-        for (int x = 0; x < 2; ++x) v[x] = float_to_bf16_bits(f[2 * x]) | ((uint32_t)float_to_bf16_bits(f[2 * x + 1]) << 16);
+        for (int x = 0; x < 2; ++x) v[x] = pack_bf16x2(f[2 * x], f[2 * x + 1]);
         __builtin_nontemporal_store(v, (u32x2 *)((uint16_t *)p + i));
     }
 };
