@@ -265,23 +265,24 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const ScoreArgs &a, 
             float *mine = red + ((rb & (kScoreSums - 1)) * a.tiles + t) * 64 + lane;
             float acc = rb < kScoreSums ? (a.reduce == SPECPV_REDUCE_MAX ? -INFINITY : 0.f) : *mine;
             // accumulator slot x holds row r0 + (x>>2)*8 + kg*4 + (x&3) of this lane's block
-            if (a.reduce != SPECPV_REDUCE_LAST && r0 + 32 <= R) {
+            if (a.reduce == SPECPV_REDUCE_MAX) {
+                // (rows past the end are the last row once more)
+#pragma unroll
+                for (int x = 0; x < 16; ++x) acc = fmaxf(acc, BOUND ? sx[x] : fmaxf(sx[x], sn[x]));
+            } else if (a.reduce != SPECPV_REDUCE_LAST && r0 + 32 <= R) {
                 // all 32 rows count (every wavefront but the one with the ragged end): no per-row tests; the
                 // same order of operations as below
-                if (a.reduce == SPECPV_REDUCE_MAX) {
 #pragma unroll
-                    for (int x = 0; x < 16; ++x) acc = fmaxf(acc, BOUND ? sx[x] : fmaxf(sx[x], sn[x]));
-                } else {
-#pragma unroll
-                    for (int x = 0; x < 16; ++x) acc += BOUND ? sx[x] : fmaxf(sx[x], sn[x]);
-                }
+                for (int x = 0; x < 16; ++x) acc += BOUND ? sx[x] : fmaxf(sx[x], sn[x]);
             } else {
+                // (a row that does not count weighs in as nothing: with a branch for each, this wavefront was the last one home.
+                // Four at a time: all sixteen conditions at once are more scalar registers than there are.)
                 const int lo = a.reduce == SPECPV_REDUCE_LAST ? a.last_node * s.G : 0, hi = a.reduce == SPECPV_REDUCE_LAST ? lo + s.G : R;
+                const int from = r0 + kg * 4 - lo;
 #pragma unroll
                 for (int x = 0; x < 16; ++x) {
-                    const int row = r0 + (x >> 2) * 8 + kg * 4 + (x & 3);
-                    const float sv = BOUND ? sx[x] : fmaxf(sx[x], sn[x]);
-                    if (row >= lo && row < hi) acc = a.reduce == SPECPV_REDUCE_MAX ? fmaxf(acc, sv) : acc + sv;
+                    acc += (uint32_t)(from + (x >> 2) * 8 + (x & 3)) < (uint32_t)(hi - lo) ? (BOUND ? sx[x] : fmaxf(sx[x], sn[x])) : 0.f;
+                    if ((x & 3) == 3) __builtin_amdgcn_sched_barrier(0);
                 }
             }
             *mine = acc;
@@ -292,10 +293,18 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const ScoreArgs &a, 
     __syncthreads();
     const int nb = blocks();
     for (int t = wave; t < n_t; t += W) {   // a wavefront per tile
-        float sum = red[t * 64 + lane];
-        for (int w = 1; w < a.sums; ++w) {
-            const float o = red[(w * a.tiles + t) * 64 + lane];
-            sum = a.reduce == SPECPV_REDUCE_MAX ? fmaxf(sum, o) : sum + o;
+        // (all reads of eight sums in one round trip to LDS; a sum past the last weighs in as nothing)
+        const bool by_max = a.reduce == SPECPV_REDUCE_MAX;
+        float sum = by_max ? -INFINITY : 0.f;
+        for (int w0 = 0; w0 < a.sums; w0 += 8) {
+            float o[8];
+#pragma unroll
+            for (int w = 0; w < 8; ++w) o[w] = red[(min(w0 + w, a.sums - 1) * a.tiles + t) * 64 + lane];
+#pragma unroll
+            for (int w = 0; w < 8; ++w) {
+                if (w0 + w >= a.sums) o[w] = by_max ? -INFINITY : 0.f;
+                sum = by_max ? fmaxf(sum, o[w]) : sum + o[w];
+            }
         }
         const float other = __shfl_xor(sum, 32);
         float out;
