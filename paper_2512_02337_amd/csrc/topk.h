@@ -73,7 +73,7 @@ struct TopkLds {
     __attribute__((aligned(16))) uint32_t wave_min[16];
     __attribute__((aligned(16))) uint32_t wave_max[16];
     __attribute__((aligned(16))) uint32_t wave_tot[16];
-    uint32_t list[64];
+    __attribute__((aligned(16))) uint32_t list[64];
     uint32_t n_list;
 };
 
@@ -142,6 +142,7 @@ __device__ __forceinline__ void topk_fast_body(TopkLds &lds, const float *scores
             raw[j] = *p;
     }
     if (tid < 256) { lds.hist[0][tid] = 0; lds.hist[1][tid] = 0; }   // ahead of the first barrier below
+    if (tid < 64) lds.list[tid] = 0;
     if (tid == 0) lds.n_list = 0;
     const int L = ctx_len[b];
     int nb = L > 0 ? (L + B - 1) / B : 0;
@@ -208,17 +209,19 @@ __device__ __forceinline__ void topk_fast_body(TopkLds &lds, const float *scores
                         if ((live >> j) & 1u) lds.list[atomicAdd(&lds.n_list, 1u)] = key[j];
                 }
                 __syncthreads();
-                // every wavefront for itself: how many of the listed keys are greater, how many equal
-                const uint32_t own = lane < d.count ? lds.list[lane] : 0u;
-                int greater = 0, equal = 0;
-                for (int i = 0; i < d.count; ++i) {
-                    const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)own, i);
-                    greater += o > own ? 1 : 0;
-                    equal += o == own ? 1 : 0;
+                // Every wavefront for itself: how many of the listed keys are greater than the lane's (entries past the last are 0,
+                // greater than none); the threshold is the smallest key with fewer than krem in front of it.  Four keys a read, the
+                // same for all lanes: two instructions a key, where up to four wavefronts of a SIMD do this at a time.
+                // (A readlane, two comparisons and two counts a key: 3840 blocks 6.2 us, 5.9 so; 8192 blocks 11.6, 10.6.)
+                const uint32_t own = lds.list[lane];
+                int greater = 0;
+                for (int i = 0; i < d.count; i += 4) {
+                    const uint4 o = *(const uint4 *)(lds.list + i);
+                    greater += (o.x > own ? 1 : 0) + (o.y > own ? 1 : 0) + (o.z > own ? 1 : 0) + (o.w > own ? 1 : 0);
                 }
-                const int owner = __builtin_ctzll(__ballot(lane < d.count && greater < krem && greater + equal >= krem));
-                prefix = (uint32_t)__builtin_amdgcn_readlane((int)own, owner);
-                krem -= __builtin_amdgcn_readlane(greater, owner);
+                const bool in_front = lane < d.count && greater < krem;
+                prefix = wave_min_u32(in_front ? own : 0xffffffffu);
+                krem -= __builtin_amdgcn_readlane(greater, __builtin_ctzll(__ballot(in_front && own == prefix)));
 #pragma unroll
                 for (int j = 0; j < P; ++j)
                     if (key[j] != prefix) live &= ~(1u << j);
