@@ -61,15 +61,17 @@ __device__ __forceinline__ void arrive_and_update(const CommitArrive &ar, int bl
 
 // Everything that a commit does for one (KV head, sequence, layer), by one workgroup; a row of D elements is
 // D * sizeof(T) / 16 lanes.  What bounds it is the chain of cold reads -- counters, then rows, then the touched
-// blocks' older rows -- of a few KiB each, so the whole of it is one launch (copy, lists and summaries as launches of
-// their own took 4.9 + 3.3 + 8.4 us for 32 layers, of which this takes 7.5).
+// blocks' older rows, with them -- of a few KiB each, so the whole of it is one launch (copy, lists and summaries as launches of
+// their own took 4.9 + 3.3 + 8.4 us for 32 layers, of which this takes 7.0).
 //  * Every source row is read into registers before anything is written (the compaction of the buffer moves rows
 //    within one array).
 //  * Lists (Section 3.3: the committed tokens stay part of the partial cache): every block that received a token joins
 //    the kept-block list behind the entries it has, unless it is listed already (the ragged last block of the local
 //    window).
 //  * Summaries (eq. 1) of the blocks that received tokens: a wavefront per block, lanes over 16-byte pieces of a row.
-template <typename T, int D>
+// ROWS: the rows that a workgroup keeps in registers.  Rows that move within the buffer are all of them; those that go to the cache
+// go there so many at a time.
+template <typename T, int D, int ROWS>
 __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, int b0, int P, int Mt, const int32_t *n_pending,
                                                      const int32_t *accepted, const int32_t *n_accepted, int max_accept, int to_cache,
                                                      int with_sums, int n_sel, CommitArrive ar)
@@ -79,7 +81,7 @@ __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, 
     constexpr int E = Elem<T>::kPerVec;
     constexpr int LPR = D / E;                     // lanes per row
     constexpr int RPP = 256 / LPR;                 // rows per pass
-    constexpr int PASSES = (kCommitMaxRows + RPP - 1) / RPP;
+    constexpr int PASSES = (ROWS + RPP - 1) / RPP;
     const int g = blockIdx.x, bl = blockIdx.y, b = b0 + bl;
     const int c = threadIdx.x % LPR, r0 = threadIdx.x / LPR, lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -97,63 +99,112 @@ __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, 
     auto buf_row = [&](T *base, int row) -> uint4 * {
         return (uint4 *)(base + (((int64_t)b * buf_rows + row) * s.Hkv + g) * D) + c;
     };
-    uint4 kr[PASSES], vr[PASSES];
-#pragma unroll
-    for (int p = 0; p < PASSES; ++p) {
-        const int i = p * RPP + r0;
+    const bool sums = to_cache && total > 0 && with_sums;    // uniform
+    const int first = L / s.B, last = (L + total - 1) / s.B;        // blocks that received tokens (all below max_blocks)
+    // The wavefronts of a call to the cache meet once, here, where each has read the counters (the fourth may move them from
+    // here on), and then go their own ways: whatever one needs of the rows it reads itself, all of it in one trip.  (Summaries of
+    // rows read back from the cache behind the stores, two more trips in the chain: 32 layers of one sequence in blocks of 64 / of
+    // 16 tokens, 16 layers of 16 sequences 7.9 / 7.8 / 15.5 us; 7.0 / 6.1 / 13.1 so.)
+    if (to_cache) {
+        asm volatile("" :: "v"(L), "v"(n_raw), "v"(a_raw) : "memory");
+        __builtin_amdgcn_s_barrier();
+    }
+    // the list that the fourth wavefront looks after: requested with the rows, entries lane and lane + 64
+    const bool with_list = wave == 3 && n_sel && to_cache;   // uniform
+    int32_t *const list = with_list ? lay.idx[blockIdx.z] + ((int64_t)b * s.Hkv + g) * n_sel : nullptr;
+    int32_t *const cntp = with_list ? lay.cnt[blockIdx.z] + (int64_t)b * s.Hkv + g : nullptr;
+    int cnt_raw = 0, list0 = -1, list1 = -1;
+    if (with_list) {
+        cnt_raw = *cntp;
+        if (lane < n_sel) list0 = list[lane];
+        if (lane + 64 < n_sel) list1 = list[lane + 64];
+    }
+    // where row i of those that move comes from
+    auto source = [&](int i) -> int {
         const int x = i - n;
         const int e0 = __shfl(acc0, x & 63), e1 = __shfl(acc1, x & 63);
-        kr[p] = vr[p] = make_uint4(0u, 0u, 0u, 0u);
-        if (i < total) {
-            int src;
-            if (i < n) src = P - n + i;                                   // pending token i (oldest first)
-            else src = P + min(max(x < 64 ? e0 : e1, 0), Mt - 1);         // accepted candidate
-            kr[p] = *buf_row(buf_k, src);
-            vr[p] = *buf_row(buf_v, src);
-        }
-    }
-    __syncthreads();
+        return i < n ? P - n + i                                    // pending token i (oldest first)
+                     : P + min(max(x < 64 ? e0 : e1, 0), Mt - 1);   // accepted candidate
+    };
+    uint4 kr[PASSES], vr[PASSES];
+    auto read_rows = [&](int from) {
 #pragma unroll
-    for (int p = 0; p < PASSES; ++p) {
-        const int i = p * RPP + r0;
-        if (i < total) {
-            if (to_cache) {
-                const int64_t off = (int64_t)b * s.sb + (int64_t)g * s.sh + (int64_t)(L + i) * s.st;
-                *((uint4 *)(cache_k + off) + c) = kr[p];
-                *((uint4 *)(cache_v + off) + c) = vr[p];
-            } else {
+        for (int p = 0; p < PASSES; ++p) {
+            const int i = from + p * RPP + r0, src = source(i);
+            kr[p] = vr[p] = make_uint4(0u, 0u, 0u, 0u);
+            if (i < total) {
+                kr[p] = *buf_row(buf_k, src);
+                vr[p] = *buf_row(buf_v, src);
+            }
+        }
+    };
+    read_rows(0);
+    if (ROWS == kCommitMaxRows || !to_cache) {
+        __syncthreads();   // every source row is read
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const int i = p * RPP + r0;
+            if (i < total) {
                 *buf_row(buf_k, P - total + i) = kr[p];
                 *buf_row(buf_v, P - total + i) = vr[p];
             }
         }
+        if (wave == 3 && lane == 0) arrive_and_update(ar, bl, b, (int)blockIdx.z * s.Hkv + g, 0u, n_sel > 0, false, L, n + a, total);
+        return;
     }
-    const int first = L / s.B, last = (L + total - 1) / s.B;        // blocks that received tokens (all below max_blocks)
+    // a wavefront per block: eight passes of rows at a time, the first of the older and of the new ones together
+    constexpr int WRP = 64 / LPR, U = 8;   // rows per pass
+    const int wr = lane / LPR;
+    const T *const base = cache_k + (int64_t)b * s.sb + (int64_t)g * s.sh + c * E;   // (64 is a multiple of LPR: c is lane % LPR)
+    uint4 u_old[U], u_new[U];
+    auto read_old = [&](int t, int t1) {   // rows t .. t1 - 1, as many of them as there are in U passes
+#pragma unroll
+        for (int x = 0; x < U; ++x)
+            if (t + x * WRP < t1) u_old[x] = *(const uint4 *)(base + (int64_t)min(t + x * WRP + wr, t1 - 1) * s.st);   // (the last row again: no effect)
+    };
+    auto read_new = [&](int r, int r1) {
+#pragma unroll
+        for (int x = 0; x < U; ++x)
+            if (r + x * WRP < r1) u_new[x] = *buf_row(buf_k, source(min(r + x * WRP + wr, r1 - 1)));
+    };
+    int blk = first + wave, t0 = 0, t1 = 0, n0 = 0, n1 = 0;   // the block's older rows, and its new ones among those that move
+    auto request = [&]() {
+        t0 = blk * s.B; t1 = min(t0 + s.B, L);
+        n0 = max(t0 - L, 0); n1 = min(t0 + s.B - L, total);
+        read_old(t0, t1);
+        read_new(n0, n1);
+    };
+    if (sums && blk <= last) request();
     if (wave == 3) {
         int missed = 0;
-        if (n_sel && to_cache && total > 0) {
-            int32_t *row = lay.idx[blockIdx.z] + ((int64_t)b * s.Hkv + g) * n_sel;
-            int32_t *cntp = lay.cnt[blockIdx.z] + (int64_t)b * s.Hkv + g;
-            const int cnt0 = min(max(*cntp, 0), n_sel);
+        if (with_list && total > 0) {
+            const int cnt0 = min(max(cnt_raw, 0), n_sel);
             int cnt = cnt0;
-            for (int blk = first; blk <= last; ++blk) {
-                bool here = false;
-                for (int i = lane; i < cnt0; i += 64) here |= row[i] == blk;
+            for (int i = first; i <= last; ++i) {
+                bool here = (lane < cnt0 && list0 == i) || (lane + 64 < cnt0 && list1 == i);
+                for (int x = lane + 128; x < cnt0; x += 64) here |= list[x] == i;
                 if (__any(here)) continue;
-                if (cnt < n_sel) { if (lane == 0) row[cnt] = blk; ++cnt; }
+                if (cnt < n_sel) { if (lane == 0) list[cnt] = i; ++cnt; }
                 else ++missed;
             }
             if (lane == 0) *cntp = cnt;
         }
-        if (lane == 0) arrive_and_update(ar, bl, b, (int)blockIdx.z * s.Hkv + g, (uint32_t)missed, n_sel > 0, to_cache != 0, L, n + a, total);
+        if (lane == 0) arrive_and_update(ar, bl, b, (int)blockIdx.z * s.Hkv + g, (uint32_t)missed, n_sel > 0, true, L, n + a, total);
     }
-    if (!to_cache || total == 0 || !with_sums) return;   // uniform
-    __syncthreads();   // the new rows are in the cache (stores of this workgroup, read back by it)
-    constexpr int WRP = 64 / LPR;   // rows per wavefront pass
-    const int wr = lane / LPR;
-    const T *base = cache_k + (int64_t)b * s.sb + (int64_t)g * s.sh + c * E;   // (64 is a multiple of LPR: c is lane % LPR)
+    for (int from = 0; from < total; from += ROWS) {
+        if (from > 0) read_rows(from);
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const int i = from + p * RPP + r0;
+            if (i >= total) continue;
+            const int64_t off = (int64_t)b * s.sb + (int64_t)g * s.sh + (int64_t)(L + i) * s.st;
+            *((uint4 *)(cache_k + off) + c) = kr[p];
+            *((uint4 *)(cache_v + off) + c) = vr[p];
+        }
+    }
+    if (!sums) return;
     T *const kmax = (T *)lay.kmax[blockIdx.z], *const kmin = (T *)lay.kmin[blockIdx.z];
-    for (int i = first + wave; i <= last; i += 4) {
-        const int t0 = i * s.B, t1 = min(t0 + s.B, L + total);
+    for (; blk <= last;) {
         float mx[E], mn[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) { mx[e] = -INFINITY; mn[e] = INFINITY; }
@@ -163,12 +214,17 @@ __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, 
 #pragma unroll
             for (int e = 0; e < E; ++e) { mx[e] = fmaxf(mx[e], f[e]); mn[e] = fminf(mn[e], f[e]); }
         };
-        for (int t = t0 + wr; t < t1; t += 8 * WRP) {
-            uint4 u[8];
+        for (int t = t0; t < t1;) {
 #pragma unroll
-            for (int x = 0; x < 8; ++x) u[x] = *(const uint4 *)(base + (int64_t)min(t + x * WRP, t1 - 1) * s.st);   // (the last row again: no effect)
+            for (int x = 0; x < U; ++x) if (t + x * WRP < t1) fold(u_old[x]);
+            t += U * WRP;
+            if (t < t1) read_old(t, t1);
+        }
+        for (int r = n0; r < n1;) {
 #pragma unroll
-            for (int x = 0; x < 8; ++x) fold(u[x]);
+            for (int x = 0; x < U; ++x) if (r + x * WRP < n1) fold(u_new[x]);
+            r += U * WRP;
+            if (r < n1) read_new(r, n1);
         }
 #pragma unroll
         for (int off = LPR; off < 64; off <<= 1) {
@@ -179,10 +235,12 @@ __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, 
             }
         }
         if (wr == 0) {
-            const int64_t o = (((int64_t)b * s.Hkv + g) * s.max_blocks + i) * D + c * E;
+            const int64_t o = (((int64_t)b * s.Hkv + g) * s.max_blocks + blk) * D + c * E;
             *(uint4 *)(kmax + o) = Elem<T>::pack(mx);
             *(uint4 *)(kmin + o) = Elem<T>::pack(mn);
         }
+        blk += 4;
+        if (blk <= last) request();
     }
 }
 
@@ -212,14 +270,20 @@ hipError_t launch_commit(const Shape &s, int dtype, int n_layers, void *const *k
             }
             const dim3 grid(s.Hkv, n_seq, nl);
             ar.workgroups = l0 + nl == n_layers ? s.Hkv * nl : 0;
-#define SPECPV_COMMIT(T, DD)                                                                                                      \
-    hipLaunchKernelGGL((commit_kernel<T, DD>), grid, dim3(256), 0, st, s, lay, b0, P, Mt, n_pending, accepted, n_accepted, max_accept, \
+            // 32 rows are a quarter of the registers: all that a commit to the cache needs, whatever the buffer's size, and what moves
+            // within a buffer of up to 32, accepted rows included.  With registers for 128 everywhere: one sequence, 32 layers 7.2 us,
+            // 6.9 so; four, 28 layers 11.2 / 7.8; eight in fp32, 28 layers 21.9 / 15.6; within the buffer, four, 28 layers 5.5 / 4.6.
+#define SPECPV_COMMIT(T, DD, ROWS)                                                                                                \
+    hipLaunchKernelGGL((commit_kernel<T, DD, ROWS>), grid, dim3(256), 0, st, s, lay, b0, P, Mt, n_pending, accepted, n_accepted, max_accept, \
                        to_cache, summaries ? 1 : 0, with_lists ? lists[0].n_sel : 0, ar)
+#define SPECPV_COMMIT_D(T, ROWS) if (s.D == 128) SPECPV_COMMIT(T, 128, ROWS); else SPECPV_COMMIT(T, 64, ROWS)
+            const bool few = to_cache || P + max_accept <= 32;
             if (dtype == SPECPV_BF16) {
-                if (s.D == 128) SPECPV_COMMIT(bf16_t, 128); else SPECPV_COMMIT(bf16_t, 64);
+                if (few) { SPECPV_COMMIT_D(bf16_t, 32); } else { SPECPV_COMMIT_D(bf16_t, kCommitMaxRows); }
             } else {
-                if (s.D == 128) SPECPV_COMMIT(float, 128); else SPECPV_COMMIT(float, 64);
+                if (few) { SPECPV_COMMIT_D(float, 32); } else { SPECPV_COMMIT_D(float, kCommitMaxRows); }
             }
+#undef SPECPV_COMMIT_D
 #undef SPECPV_COMMIT
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
