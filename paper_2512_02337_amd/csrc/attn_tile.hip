@@ -12,10 +12,10 @@
 //   TG = 2: tiles of 128 rows, four stages, four chunks requested up front.  Each K / V byte is pulled by half as many
 //           workgroups as with TG = 4.
 // TG = 4 and 2 take two chunks at a time (score_pair, attend_pair).
-// What bounds it at one sequence is latency, not a rate.  Headline step, us from entry (timeline.py): arguments and list 1.6,
-// the requests accepted 3.5 (a CU takes 1 KiB per 27 cycles, so 128 KiB are 1.6 us), the first two chunks landed 4.5 and worked
-// on 5.8, the other two landed 6.4 and worked on 8.4, partials stored 10.0 (a chunk at a time: the first landed 3.7, the last
-// worked on 8.8, stored 11.0).  The planner (plan_attention) chooses TG and the splits.  Calls of one sequence, 8 KV
+// What bounds it at one sequence is latency, not a rate.  Headline step, us from entry (timeline.py): arguments, list and query rows 1.3,
+// the requests accepted 3.1 (a CU takes 1 KiB per 27 cycles, so 128 KiB are 1.6 us), the first two chunks landed 4.1 and worked
+// on 5.5, the other two landed 6.0 and worked on 7.9, partials stored 9.4 (query rows operand by operand: 1.6 and 10.0; with
+// them a chunk at a time: the last worked on 8.8, stored 11.0).  The planner (plan_attention) chooses TG and the splits.  Calls of one sequence, 8 KV
 // heads at G = 4, in graphs of 16 layers, against tiles of one head's 64 nodes (TG = 4, 8 splits, whatever the node count),
 // side by side on one card: 4096 kept tokens, 60 nodes 17.7 -> 17.2 us (TG = 2, 16 splits; on other cards 17.8 -> 17.6 and
 // 17.8 -> 18.1), 1 node 14.9 -> 11.6 us (TG = 8, 16 splits); 8192 tokens, 60 nodes 31.8 -> 22.5 us; 2048 tokens, 60 nodes

@@ -11,7 +11,7 @@
 // each has its rows under way while it works on what is there, and they meet in one exchange through LDS.  With more than
 // sixteen partials those are the longer half, and the first one takes all eight.  Up to 16 partials are requested at once, 16
 // bytes per lane each, and a lane works out the weights of its own partials only.  In-kernel stamps at one sequence, 60 nodes,
-// 8 KV heads at G = 4, 16 splits, us from entry: path walked 0.7, first half of the tree done 1.6, stored 2.4; with a bit set
+// 8 KV heads at G = 4, 16 splits, us from entry: path walked 0.5, first half of the tree done 1.6, stored 2.2; with a bit set
 // of the path, taken apart again node by node, and the whole tree in one wavefront 1.0, 2.4 and 3.2.  Whole calls in a graph
 // of 16 layers 15.37 -> 14.71 us (one card) and 16.69 -> 16.02 (another); fp32, 16 nodes, four launches 18.8 -> 16.3.  A third
 // wavefront for the second half took another 0.8 %, and has no place at eight heads a KV head and more.
