@@ -284,7 +284,9 @@ typedef struct specpv_lists {
  * no free entry in a list row of sequence b.  Both are 0 unless the caller under-sized the
  * cache, the buffer or the list rows; a caller that cannot rule that out has to check them.
  * Writes through kv->k, kv->v (rows from L_b on; the allocation must cover max_blocks * B
- * tokens) and kv->ctx_len, n_pending [batch] (device), in stream order.  Workspace: its zeroed head,
+ * tokens) and kv->ctx_len, n_pending [batch] (device), in stream order.  The buffer may lie in the cache it
+ * goes to (one sequence, token-major rows, written behind the committed tokens); other overlaps are the
+ * caller's mistake.  Workspace: its zeroed head,
  * and 4 bytes per sequence (specpv_workspace_bytes covers it). */
 int specpv_commit_accepted(const specpv_kv *kv, void *buf_k, void *buf_v, int32_t pending_cap, int32_t M_tree,
                            int32_t *n_pending, const int32_t *accepted, const int32_t *n_accepted,

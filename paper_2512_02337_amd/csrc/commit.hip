@@ -63,15 +63,15 @@ __device__ __forceinline__ void arrive_and_update(const CommitArrive &ar, int bl
 // D * sizeof(T) / 16 lanes.  What bounds it is the chain of cold reads -- counters, then rows, then the touched
 // blocks' older rows, with them -- of a few KiB each, so the whole of it is one launch (copy, lists and summaries as launches of
 // their own took 4.9 + 3.3 + 8.4 us for 32 layers, of which this takes 7.0).
-//  * Every source row is read into registers before anything is written (the compaction of the buffer moves rows
-//    within one array).
+//  * Rows that move within the buffer are read into registers, all of them, before anything is written; and so are those of a
+//    buffer that lies in the cache (one sequence, token-major: candidates written where the cache goes on, and moved up here).
 //  * Lists (Section 3.3: the committed tokens stay part of the partial cache): every block that received a token joins
 //    the kept-block list behind the entries it has, unless it is listed already (the ragged last block of the local
 //    window).
 //  * Summaries (eq. 1) of the blocks that received tokens: a wavefront per block, lanes over 16-byte pieces of a row.
-// ROWS: the rows that a workgroup keeps in registers.  Rows that move within the buffer are all of them; those that go to the cache
-// go there so many at a time.
-template <typename T, int D, int ROWS>
+// ROWS: the rows that a workgroup keeps in registers.  Rows that move within one array are all of them; others that go to the cache
+// go there so many at a time.  IN_PLACE: a commit to the cache out of a buffer that lies in it; the summaries then read the new rows back.
+template <typename T, int D, int ROWS, bool IN_PLACE>
 __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, int b0, int P, int Mt, const int32_t *n_pending,
                                                      const int32_t *accepted, const int32_t *n_accepted, int max_accept, int to_cache,
                                                      int with_sums, int n_sel, CommitArrive ar)
@@ -139,18 +139,23 @@ __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, 
         }
     };
     read_rows(0);
+    auto cache_row = [&](int i) -> int64_t { return (int64_t)b * s.sb + (int64_t)g * s.sh + (int64_t)(L + i) * s.st; };
     if (ROWS == kCommitMaxRows || !to_cache) {
         __syncthreads();   // every source row is read
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
             const int i = p * RPP + r0;
-            if (i < total) {
-                *buf_row(buf_k, P - total + i) = kr[p];
-                *buf_row(buf_v, P - total + i) = vr[p];
-            }
+            if (i >= total) continue;
+            uint4 *const to_k = IN_PLACE ? (uint4 *)(cache_k + cache_row(i)) + c : buf_row(buf_k, P - total + i);
+            uint4 *const to_v = IN_PLACE ? (uint4 *)(cache_v + cache_row(i)) + c : buf_row(buf_v, P - total + i);
+            *to_k = kr[p];
+            *to_v = vr[p];
         }
-        if (wave == 3 && lane == 0) arrive_and_update(ar, bl, b, (int)blockIdx.z * s.Hkv + g, 0u, n_sel > 0, false, L, n + a, total);
-        return;
+        if (!IN_PLACE) {
+            if (wave == 3 && lane == 0) arrive_and_update(ar, bl, b, (int)blockIdx.z * s.Hkv + g, 0u, n_sel > 0, false, L, n + a, total);
+            return;
+        }
+        __syncthreads();   // the new rows are in the cache (stores of this workgroup, read back by it)
     }
     // a wavefront per block: eight passes of rows at a time, the first of the older and of the new ones together
     constexpr int WRP = 64 / LPR, U = 8;   // rows per pass
@@ -169,8 +174,8 @@ __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, 
     };
     int blk = first + wave, t0 = 0, t1 = 0, n0 = 0, n1 = 0;   // the block's older rows, and its new ones among those that move
     auto request = [&]() {
-        t0 = blk * s.B; t1 = min(t0 + s.B, L);
-        n0 = max(t0 - L, 0); n1 = min(t0 + s.B - L, total);
+        t0 = blk * s.B; t1 = min(t0 + s.B, IN_PLACE ? L + total : L);
+        if (!IN_PLACE) { n0 = max(t0 - L, 0); n1 = min(t0 + s.B - L, total); }
         read_old(t0, t1);
         read_new(n0, n1);
     };
@@ -191,15 +196,14 @@ __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, 
         }
         if (lane == 0) arrive_and_update(ar, bl, b, (int)blockIdx.z * s.Hkv + g, (uint32_t)missed, n_sel > 0, true, L, n + a, total);
     }
-    for (int from = 0; from < total; from += ROWS) {
+    for (int from = 0; !IN_PLACE && from < total; from += ROWS) {
         if (from > 0) read_rows(from);
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
             const int i = from + p * RPP + r0;
             if (i >= total) continue;
-            const int64_t off = (int64_t)b * s.sb + (int64_t)g * s.sh + (int64_t)(L + i) * s.st;
-            *((uint4 *)(cache_k + off) + c) = kr[p];
-            *((uint4 *)(cache_v + off) + c) = vr[p];
+            *((uint4 *)(cache_k + cache_row(i)) + c) = kr[p];
+            *((uint4 *)(cache_v + cache_row(i)) + c) = vr[p];
         }
     }
     if (!sums) return;
@@ -244,6 +248,15 @@ __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, 
     }
 }
 
+// Whether a layer's buffers lie in its caches (as far as strides and extents tell).
+static bool buffer_in_cache(const Shape &s, size_t elem, const void *k, const void *v, const void *buf_k, const void *buf_v, int rows)
+{
+    const uintptr_t cache = (uintptr_t)(((s.batch - 1) * s.sb + (s.Hkv - 1) * s.sh + ((int64_t)s.max_blocks * s.B - 1) * s.st + s.D) * (int64_t)elem);
+    const uintptr_t buf = (uintptr_t)s.batch * rows * s.Hkv * s.D * elem;
+    auto meet = [&](const void *c, const void *p) { return (uintptr_t)p < (uintptr_t)c + cache && (uintptr_t)c < (uintptr_t)p + buf; };
+    return meet(k, buf_k) || meet(k, buf_v) || meet(v, buf_k) || meet(v, buf_v);
+}
+
 // layers: n_layers entries each of k, v (the caches), buf_k, buf_v (the buffers) and, for a commit to
 // the cache, kmax, kmin (or all NULL).  s carries the shape, the strides and ctx_len (shared).
 hipError_t launch_commit(const Shape &s, int dtype, int n_layers, void *const *k, void *const *v,
@@ -262,7 +275,9 @@ hipError_t launch_commit(const Shape &s, int dtype, int n_layers, void *const *k
         for (int l0 = 0; l0 < n_layers; l0 += kCommitLayers) {
             const int nl = n_layers - l0 < kCommitLayers ? n_layers - l0 : kCommitLayers;
             CommitLayers lay = {};
+            bool in_place = false;
             for (int l = 0; l < nl; ++l) {
+                if (to_cache) in_place |= buffer_in_cache(s, dtype == SPECPV_BF16 ? 2 : 4, k[l0 + l], v[l0 + l], buf_k[l0 + l], buf_v[l0 + l], P + Mt);
                 lay.k[l] = k[l0 + l]; lay.v[l] = v[l0 + l];
                 lay.buf_k[l] = buf_k[l0 + l]; lay.buf_v[l] = buf_v[l0 + l];
                 if (summaries) { lay.kmax[l] = kmax[l0 + l]; lay.kmin[l] = kmin[l0 + l]; }
@@ -273,16 +288,19 @@ hipError_t launch_commit(const Shape &s, int dtype, int n_layers, void *const *k
             // 32 rows are a quarter of the registers: all that a commit to the cache needs, whatever the buffer's size, and what moves
             // within a buffer of up to 32, accepted rows included.  With registers for 128 everywhere: one sequence, 32 layers 7.2 us,
             // 6.9 so; four, 28 layers 11.2 / 7.8; eight in fp32, 28 layers 21.9 / 15.6; within the buffer, four, 28 layers 5.5 / 4.6.
-#define SPECPV_COMMIT(T, DD, ROWS)                                                                                                \
-    hipLaunchKernelGGL((commit_kernel<T, DD, ROWS>), grid, dim3(256), 0, st, s, lay, b0, P, Mt, n_pending, accepted, n_accepted, max_accept, \
+#define SPECPV_COMMIT(T, DD, ROWS, IN)                                                                                            \
+    hipLaunchKernelGGL((commit_kernel<T, DD, ROWS, IN>), grid, dim3(256), 0, st, s, lay, b0, P, Mt, n_pending, accepted, n_accepted, max_accept, \
                        to_cache, summaries ? 1 : 0, with_lists ? lists[0].n_sel : 0, ar)
-#define SPECPV_COMMIT_D(T, ROWS) if (s.D == 128) SPECPV_COMMIT(T, 128, ROWS); else SPECPV_COMMIT(T, 64, ROWS)
+#define SPECPV_COMMIT_D(T, ROWS, IN) do { if (s.D == 128) SPECPV_COMMIT(T, 128, ROWS, IN); else SPECPV_COMMIT(T, 64, ROWS, IN); } while (0)
+#define SPECPV_COMMIT_R(T)                                                                                                        \
+    do {                                                                                                                          \
+        if (in_place) SPECPV_COMMIT_D(T, kCommitMaxRows, true);                                                                   \
+        else if (few) SPECPV_COMMIT_D(T, 32, false);                                                                              \
+        else SPECPV_COMMIT_D(T, kCommitMaxRows, false);                                                                           \
+    } while (0)
             const bool few = to_cache || P + max_accept <= 32;
-            if (dtype == SPECPV_BF16) {
-                if (few) { SPECPV_COMMIT_D(bf16_t, 32); } else { SPECPV_COMMIT_D(bf16_t, kCommitMaxRows); }
-            } else {
-                if (few) { SPECPV_COMMIT_D(float, 32); } else { SPECPV_COMMIT_D(float, kCommitMaxRows); }
-            }
+            if (dtype == SPECPV_BF16) SPECPV_COMMIT_R(bf16_t); else SPECPV_COMMIT_R(float);
+#undef SPECPV_COMMIT_R
 #undef SPECPV_COMMIT_D
 #undef SPECPV_COMMIT
             const hipError_t e = hipGetLastError();
