@@ -8,6 +8,8 @@ namespace specpv {
 // The draft's K or V rows as a buffer of the hardware's: a read at kNowhere is outside of it and gives zeros.
 typedef __amdgpu_buffer_rsrc_t RowsOf;
 constexpr uint32_t kNowhere = 0xffff0000u;
+// A sequence's draft rows reach beyond such a buffer (fp32, 128 channels, 128 nodes: from 65536 KV heads).
+static inline bool draft_rows_wide(const Shape &s, size_t elem) { return (uint64_t)s.Mk * s.Hkv * s.D * elem > kNowhere; }
 __device__ __forceinline__ RowsOf rows_of(const char *p, uint32_t bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(p), 0, (int)bytes, 0x00027000); }
 
 // CPL adjacent channels of one row, 16 bytes per memory instruction (rows are 16-byte aligned).
@@ -157,7 +159,8 @@ __device__ __forceinline__ float row16_max(float x)
 // bg = b * Hkv + g; at_row: the query row, or, PACK, the four of rows; wave: of the wavefronts that share it; stores: whether
 // there is such a row.  tree_od [fours][D / 64][64], tree_ml [fours][64] (TWO): where those wavefronts meet; all of a workgroup
 // come to the one barrier.
-template <typename T, int D, int NP, bool MULTI, int NB, bool HALF, bool TWO, bool PACK, bool SHARED>
+// WIDE (draft_rows_wide): a buffer for each row.
+template <typename T, int D, int NP, bool MULTI, int NB, bool HALF, bool TWO, bool PACK, bool SHARED, bool WIDE = false>
 __device__ __forceinline__ void combine_rows(const Shape &s, const Partials &part, void *out, float *lse, const float scale_log2, const int bg, const int b,
                                              const int at_row, const int wave, const bool stores, float4 *tree_od, float2 *tree_ml)
 {
@@ -208,8 +211,7 @@ __device__ __forceinline__ void combine_rows(const Shape &s, const Partials &par
     };
     const int64_t drow0 = ((int64_t)b * s.Mk * s.Hkv + g) * (int64_t)(D * SZ);
     const uint32_t draft_step = (uint32_t)s.Hkv * (D * SZ);
-    const uint64_t draft_all = (uint64_t)s.Mk * draft_step - (uint32_t)g * (D * SZ);
-    const uint32_t draft_bytes = draft_all >> 32 ? kNowhere : min((uint32_t)draft_all, kNowhere);
+    const uint32_t draft_bytes = (uint32_t)s.Mk * draft_step - (uint32_t)g * (D * SZ);
     const char *kd = nullptr, *vd = nullptr;
     int at = j + s.koff, last = -1;    // next slot's node; the slot's before it (the same: the path has ended)
     // N slots: off[u] is a node's row, bias[u] 0; behind the path's end kNowhere and -inf (rows of zeros: a weight of zero times an
@@ -220,7 +222,7 @@ __device__ __forceinline__ void combine_rows(const Shape &s, const Partials &par
         auto steps = [&](auto next) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < N; ++u) {
-                off[u] = at == last ? kNowhere : (uint32_t)at * draft_step;
+                off[u] = at == last ? kNowhere : (WIDE ? (uint32_t)at : (uint32_t)at * draft_step);
                 bias[u] = at == last ? -INFINITY : 0.f;
                 last = at;
                 at = next(at);
@@ -235,7 +237,18 @@ __device__ __forceinline__ void combine_rows(const Shape &s, const Partials &par
     uint32_t off8[NB];
     float bias[NB];
     Raw kd8[NB], vd8[NB];
+    static_assert(!WIDE || !PACK, "a row's buffer is the wavefront's");
     auto rows = [&](auto from, auto count) __attribute__((always_inline)) {
+        if constexpr (WIDE) {
+#pragma unroll
+            for (int u = decltype(from)::value; u < decltype(from)::value + decltype(count)::value; ++u) {
+                const uint32_t bytes = off8[u] == kNowhere ? 0u : (uint32_t)(D * SZ);
+                const int64_t row = drow0 + (bytes ? (int64_t)off8[u] * draft_step : 0);
+                Chan<T, CPL>::load(rows_of(kd + row, bytes), (uint32_t)d0 * SZ, kd8[u]);
+                Chan<T, CPL>::load(rows_of(vd + row, bytes), (uint32_t)d0 * SZ, vd8[u]);
+            }
+            return;
+        }
         const RowsOf kd_rows = rows_of(kd + drow0, draft_bytes), vd_rows = rows_of(vd + drow0, draft_bytes);
 #pragma unroll
         for (int u = decltype(from)::value; u < decltype(from)::value + decltype(count)::value; ++u) {

@@ -20,7 +20,7 @@
 
 namespace specpv {
 
-template <typename T, int D, int NP, bool MULTI, int NB, bool HALF, bool TWO, bool PACK>
+template <typename T, int D, int NP, bool MULTI, int NB, bool HALF, bool TWO, bool PACK, bool WIDE = false>
 __global__ __launch_bounds__(512, MULTI && HALF ? 4 : 1) void combine_kernel(const int32_t *a_parent, const void *a_q, const float *a_po,
                                                     const float *a_pml, int a_M_Mk, int a_Hq, int a_G, int a_nsplit_groups,
                                                     Shape s, Partials part, void *out, float *lse, float scale_log2)
@@ -43,7 +43,7 @@ __global__ __launch_bounds__(512, MULTI && HALF ? 4 : 1) void combine_kernel(con
         b = bg / s.Hkv;
     }
     const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (blockDim.x is read from memory)
-    combine_rows<T, D, NP, MULTI, NB, HALF, TWO, PACK, TWO && NB == 8 && !MULTI>(s, part, out, lse, scale_log2, bg, b, (int)blockIdx.y, wave, true, tree_od, tree_ml);
+    combine_rows<T, D, NP, MULTI, NB, HALF, TWO, PACK, TWO && NB == 8 && !MULTI, WIDE>(s, part, out, lse, scale_log2, bg, b, (int)blockIdx.y, wave, true, tree_od, tree_ml);
 }
 
 // Two wavefronts per four rows shorten the chain; one that does both has less to start.  What decides is the partials: with
@@ -79,19 +79,19 @@ static bool combine_two_waves(const Shape &s, const Partials &p, bool pack)
 // graph, fours by node / packed, us: G = 5, 60 nodes, one sequence 61.3 / 56.6 (2K kept) and 78.5 / 73.3 (4K), 16 nodes 45.4 /
 // 43.2, four sequences 166.6 / 155.9, sixteen (2K) 281.8 / 252.0; G = 1 with 16 KV heads 56.9 / 50.9; G = 2, four sequences 82.2
 // / 76.8; G = 3 55.4 / 51.2.  bf16 only: with fp32 inputs the rows themselves bind.
-bool combine_packed(const Shape &s, int dtype) { return dtype == SPECPV_BF16 && s.G % 4 && s.koff <= s.kctx; }
+bool combine_packed(const Shape &s, int dtype) { return dtype == SPECPV_BF16 && s.G % 4 && s.koff <= s.kctx && !draft_rows_wide(s, sizeof(uint16_t)); }
 
 template <typename T, int D>
 static void launch_combine_t(const Shape &s, int dtype, Partials p, void *out, float *lse, hipStream_t st)
 {
-    const bool pack = combine_packed(s, dtype), two = combine_two_waves(s, p, pack);
+    const bool wide = draft_rows_wide(s, sizeof(T)), pack = combine_packed(s, dtype), two = wide || combine_two_waves(s, p, pack);
     const int groups = head_groups_code(s.Hkv);
     dim3 grid(8, pack ? (s.M * s.G + 3) / 4 : s.M, (s.batch * s.Hkv + 7) / 8), block((two ? 128 : 64) * (pack ? 1 : (s.G + 3) / 4));
     const float scale_log2 = kLog2e / sqrtf((float)s.D);
     // fp16 partials: bf16 at 128 channels; the other element types and head dims have fp32 ones
     constexpr bool kHalf = std::is_same<T, bf16_t>::value && D == 128;
-#define SPECPV_LAUNCH(NP, MULTI, NB, HALF, TWO, PACK)                                                                            \
-        hipLaunchKernelGGL((combine_kernel<T, D, NP, MULTI, NB, HALF, TWO, PACK>), grid, block, 0, st, s.parent, s.q, (const float *)p.o, \
+#define SPECPV_LAUNCH(NP, MULTI, NB, HALF, ...)                                                                                  \
+        hipLaunchKernelGGL((combine_kernel<T, D, NP, MULTI, NB, HALF, __VA_ARGS__>), grid, block, 0, st, s.parent, s.q, (const float *)p.o, \
                            (const float *)p.ml, s.M | s.Mk << 8, s.Hq, s.G, p.nsplit | groups << 16, s, p, out, lse, scale_log2)
 #define SPECPV_LAUNCH_K(NP, MULTI, NB, HALF)                                                                              \
     do {                                                                                                                \
@@ -109,7 +109,8 @@ static void launch_combine_t(const Shape &s, int dtype, Partials p, void *out, f
     do {                                                                                                                \
         if (s.koff > s.kctx) SPECPV_LAUNCH_K(NP, MULTI, 24, false); else SPECPV_LAUNCH_H(NP, MULTI, 8);                  \
     } while (0)
-    if (p.stream) SPECPV_LAUNCH_NP(8, true);
+    if (wide) { if (kHalf && p.o_half) SPECPV_LAUNCH(8, true, 8, kHalf, true, false, true); else SPECPV_LAUNCH(8, true, 8, false, true, false, true); }   // (any count of partials)
+    else if (p.stream) SPECPV_LAUNCH_NP(8, true);
     else if (p.nsplit <= 2) SPECPV_LAUNCH_NP(2, false);
     else if (p.nsplit <= 4) SPECPV_LAUNCH_NP(4, false);
     else if (p.nsplit <= 8) SPECPV_LAUNCH_NP(8, false);

@@ -73,7 +73,7 @@ bool refresh_tail_supported(const Shape &s, int dtype, const Partials &p, int ki
 {
     // (the grid's y counts a KV head's scoring workgroups and its rows, z eights of KV heads)
     return dtype == SPECPV_BF16 && kind == SPECPV_SCORE_EQ2 && s.koff <= s.kctx && (p.o_half != 0) == (s.D == 128) &&
-           s.max_blocks <= 32 * 60000 && (int64_t)s.batch * s.Hkv <= 8 * 65535;
+           s.max_blocks <= 32 * 60000 && (int64_t)s.batch * s.Hkv <= 8 * 65535 && !draft_rows_wide(s, sizeof(uint16_t));
 }
 
 hipError_t launch_refresh_tail(const Shape &s, Partials p, void *out, float *lse, const void *kmax, const void *kmin, int reduce, int last_node,
