@@ -118,7 +118,10 @@ ScoreArgs score_plan(const Shape &s, const void *kmax, const void *kmin, int red
     // 128K, 30 nodes, four wavefronts of two tiles 9.5 / 9.9 us): 60K in blocks of 16 10.9 / 10.1 us, 128K 8.0 / 7.0, 16K 6.1 / 5.4,
     // 45 nodes, six wavefronts, 128K 7.3 / 6.4, 64K at G = 5, ten, 6.9 / 6.0 (scoring alone, kernel trace).
     auto fit = [&](int staged_waves) { const int n = (int)(160 * 1024 / score_lds(s.D, (int)T, a.sums, staged_waves)); return n < per_cu ? n : per_cu; };
-    if (T == 3 && waves > 4 && waves <= 8 && !keep_all) T = 2;   // (three leave no room to stage; 1536 tiles 16.3 us, 13.5 so)
+    // (Two tiles staged rather than three that leave no room to stage, as at 128 channels and seven or eight wavefronts: 1536 tiles 16.3 us,
+    // 13.5 so.  Where three staged ones fit they stay: scoring + selection of 1100 / 1300 / 1536 tiles, cut to two / three, six
+    // wavefronts 15.9 / 14.8, 16.2 / 14.9, 17.1 / 15.7; 64 channels, eight 12.6 / 12.3, 13.0 / 12.6, 13.5 / 13.0; five, 2304 tiles 16.2 / 14.6.)
+    if (T == 3 && waves > 4 && waves <= 8 && !keep_all && fit(waves) < fit(0)) T = 2;
     a.tiles = (int)T;
     a.groups = (int)((tiles1 + T - 1) / T);
     a.staged = !keep_all && waves > 4 && fit(waves) == fit(0);
