@@ -70,12 +70,15 @@ __device__ __forceinline__ void arrive_and_update(const CommitArrive &ar, int bl
 //    window).
 //  * Summaries (eq. 1) of the blocks that received tokens: a wavefront per block, lanes over 16-byte pieces of a row.
 // ROWS: the rows that a workgroup keeps in registers.  Rows that move within one array are all of them; others that go to the cache
-// go there so many at a time.  IN_PLACE: a commit to the cache out of a buffer that lies in it; the summaries then read the new rows back.
-template <typename T, int D, int ROWS, bool IN_PLACE>
+// go there so many at a time.
+// kInPlace: out of a buffer that lies in the cache; the summaries then read the new rows back.
+enum CommitTo { kWithinBuffer, kToCache, kInPlace };
+template <typename T, int D, int ROWS, CommitTo TO>
 __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, int b0, int P, int Mt, const int32_t *n_pending,
-                                                     const int32_t *accepted, const int32_t *n_accepted, int max_accept, int to_cache,
+                                                     const int32_t *accepted, const int32_t *n_accepted, int max_accept,
                                                      int with_sums, int n_sel, CommitArrive ar)
 {
+    constexpr bool to_cache = TO != kWithinBuffer, IN_PLACE = TO == kInPlace;
     T *const buf_k = (T *)lay.buf_k[blockIdx.z], *const buf_v = (T *)lay.buf_v[blockIdx.z];
     T *const cache_k = (T *)lay.k[blockIdx.z], *const cache_v = (T *)lay.v[blockIdx.z];
     constexpr int E = Elem<T>::kPerVec;
@@ -140,7 +143,7 @@ __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, 
     };
     read_rows(0);
     auto cache_row = [&](int i) -> int64_t { return (int64_t)b * s.sb + (int64_t)g * s.sh + (int64_t)(L + i) * s.st; };
-    if (ROWS == kCommitMaxRows || !to_cache) {
+    if (TO != kToCache) {
         __syncthreads();   // every source row is read
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
@@ -151,7 +154,7 @@ __global__ __launch_bounds__(256) void commit_kernel(Shape s, CommitLayers lay, 
             *to_k = kr[p];
             *to_v = vr[p];
         }
-        if (!IN_PLACE) {
+        if (!to_cache) {
             if (wave == 3 && lane == 0) arrive_and_update(ar, bl, b, (int)blockIdx.z * s.Hkv + g, 0u, n_sel > 0, false, L, n + a, total);
             return;
         }
@@ -285,20 +288,22 @@ hipError_t launch_commit(const Shape &s, int dtype, int n_layers, void *const *k
             }
             const dim3 grid(s.Hkv, n_seq, nl);
             ar.workgroups = l0 + nl == n_layers ? s.Hkv * nl : 0;
-            // 32 rows are a quarter of the registers: all that a commit to the cache needs, whatever the buffer's size, and what moves
-            // within a buffer of up to 32, accepted rows included.  With registers for 128 everywhere: one sequence, 32 layers 7.2 us,
-            // 6.9 so; four, 28 layers 11.2 / 7.8; eight in fp32, 28 layers 21.9 / 15.6; within the buffer, four, 28 layers 5.5 / 4.6.
-#define SPECPV_COMMIT(T, DD, ROWS, IN)                                                                                            \
-    hipLaunchKernelGGL((commit_kernel<T, DD, ROWS, IN>), grid, dim3(256), 0, st, s, lay, b0, P, Mt, n_pending, accepted, n_accepted, max_accept, \
-                       to_cache, summaries ? 1 : 0, with_lists ? lists[0].n_sel : 0, ar)
-#define SPECPV_COMMIT_D(T, ROWS, IN) do { if (s.D == 128) SPECPV_COMMIT(T, 128, ROWS, IN); else SPECPV_COMMIT(T, 64, ROWS, IN); } while (0)
+            // 32 rows are a quarter of the registers: all that a commit to the cache needs, whatever the buffer's size, and all that moves
+            // within a buffer of up to 32 pending rows (what finds no room there is dropped).  With registers for 128 everywhere: one
+            // sequence, 32 layers 7.2 us, 6.9 so; four, 28 layers 11.2 / 7.8; eight in fp32, 28 layers 21.9 / 15.6; within the
+            // buffer, 28 rows with five to eight accepted, one sequence, 32 layers 5.0 / 4.7; sixteen, 16 layers 10.0-12.0 / 9.1-11.2; eight in
+            // fp32, 28 layers 17.5-19.7 / 15.3-17.1 (kernel trace).
+#define SPECPV_COMMIT(T, DD, ROWS, TO)                                                                                            \
+    hipLaunchKernelGGL((commit_kernel<T, DD, ROWS, TO>), grid, dim3(256), 0, st, s, lay, b0, P, Mt, n_pending, accepted, n_accepted, max_accept, \
+                       summaries ? 1 : 0, with_lists ? lists[0].n_sel : 0, ar)
+#define SPECPV_COMMIT_D(T, ROWS, TO) do { if (s.D == 128) SPECPV_COMMIT(T, 128, ROWS, TO); else SPECPV_COMMIT(T, 64, ROWS, TO); } while (0)
 #define SPECPV_COMMIT_R(T)                                                                                                        \
     do {                                                                                                                          \
-        if (in_place) SPECPV_COMMIT_D(T, kCommitMaxRows, true);                                                                   \
-        else if (few) SPECPV_COMMIT_D(T, 32, false);                                                                              \
-        else SPECPV_COMMIT_D(T, kCommitMaxRows, false);                                                                           \
+        if (in_place) SPECPV_COMMIT_D(T, kCommitMaxRows, kInPlace);                                                               \
+        else if (to_cache) SPECPV_COMMIT_D(T, 32, kToCache);                                                                      \
+        else if (P <= 32) SPECPV_COMMIT_D(T, 32, kWithinBuffer);                                                                  \
+        else SPECPV_COMMIT_D(T, kCommitMaxRows, kWithinBuffer);                                                                   \
     } while (0)
-            const bool few = to_cache || P + max_accept <= 32;
             if (dtype == SPECPV_BF16) SPECPV_COMMIT_R(bf16_t); else SPECPV_COMMIT_R(float);
 #undef SPECPV_COMMIT_R
 #undef SPECPV_COMMIT_D

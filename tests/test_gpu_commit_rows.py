@@ -50,3 +50,37 @@ def test_rows_and_summaries(gpu_lib, dtype, D, P, most, B):
     for l in range(layers):
         for got, ref in zip((ks[l], vs[l], kx[l], kn[l]), (w[l] for w in want)):
             assert torch.equal(got, ref), l
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("P,most", [(28, 5), (31, 1), (32, 1), (32, 9), (33, 4), (64, 40)])
+def test_rows_within_the_buffer(gpu_lib, dtype, D, P, most):
+    sp, dev = gpu_lib, torch.device("cuda")
+    say("case", dtype, D, P, most)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Hkv, Mt, layers = 3, most + 5, 2
+    pend = np.array([0, P, P - 1, P // 2, max(0, P - most), 3])
+    acc = np.array([most, most, most, 0, most, 1])
+    batch = len(pend)
+    rng = np.random.default_rng(P + D + most)
+    path = np.sort(np.stack([rng.permutation(Mt)[:most] for _ in range(batch)]), 1)
+    t = lambda x: torch.tensor(x, dtype=torch.int32, device=dev)
+    cache = torch.zeros((batch, Hkv, 16, D), device=dev, dtype=dt)
+    bk, bv = ([torch.randn((batch, P + Mt, Hkv, D), device=dev).to(dt) for _ in range(layers)] for _ in range(2))
+    want = [[x.clone() for x in y] for y in (bk, bv)]
+    stored = []
+    for b in range(batch):
+        rows = ([P - pend[b] + i for i in range(pend[b])] + [P + path[b, i] for i in range(acc[b])])[:P]
+        stored.append(len(rows))
+        for w, src in zip(want, (bk, bv)):
+            for l in range(layers):
+                w[l][b, P - len(rows):P] = src[l][b, rows]
+    pend_d, ctx_d = t(pend), t([0] * batch)
+    kvs = [sp.KV(cache, cache.clone(), ctx_d, 16, 1) for _ in range(layers)]
+    ws = torch.zeros((sp.specpv_workspace_bytes(kvs[0]),), dtype=torch.uint8, device=dev)
+    sp.specpv_commit_accepted_layers(kvs, bk, bv, P, Mt, pend_d, t(path), t(acc), sp.MODE_PARTIAL, workspace=ws)
+    torch.cuda.synchronize()
+    assert pend_d.tolist() == stored
+    for l in range(layers):
+        assert torch.equal(bk[l], want[0][l]) and torch.equal(bv[l], want[1][l]), l
