@@ -49,21 +49,23 @@ __global__ __launch_bounds__(512, MULTI && HALF ? 4 : 1) void combine_kernel(con
 // Two wavefronts per four rows shorten the chain; one that does both has less to start.  What decides is the partials: with
 // more than eight they are the longer half, and two wavefronts are faster however many rows there are; with eight or fewer
 // the tree segment is, and two pay only while the chip has room for every workgroup's extra wavefronts at once.  Whole calls
-// in graphs as they are planned, one wavefront / two, us (8 KV heads at G = 4 unless stated; workgroups = sequences * KV heads *
-// nodes):
-//   eight or fewer splits, up to four heads a KV head: 192 workgroups 11.2 / 10.8, 256 12.0 / 11.8, 384 12.8 / 12.8, 480 12.9 /
-//   12.9, 960 16.2 / 16.1, 1920 21.9 / 21.8, 3840 33.0 / 33.8; fp32, 192 40.5 / 34.2: the line at a workgroup per CU;
-//   ... more heads, where one workgroup has several fours of rows that share what they read: G = 5, 480 workgroups 19.5 / 19.0,
-//   960 27.5 / 27.6, 1920 40.6 / 40.3; two KV heads at G = 8, 240 18.8 / 17.9, 960 29.7 / 29.7: two workgroups per CU;
-//   packed rows (below), fours of rows: 150 10.80 / 10.80, 300 12.80 / 12.55, 600 14.45 / 14.15, 1200 27.1 / 27.0, 2400 38.95 /
-//   39.25, 9600 62.9 / 65.1: eight of them per CU;
-//   more than eight (kernels of before, which took the whole tree in one wavefront): 16, 480 workgroups 16.45 / 16.18, 1920
-//   51.7 / 51.0; 32, 480 17.9 / 16.2, 1440 77.2 / 76.1; full pass in shares, 1920 workgroups 87.4 / 86.0, 7680 at G = 5 216 / 206;
-//   fp32, 32 splits, 1920 workgroups at 128 channels 222 / 204.
+// in graphs as they are planned, one wavefront / two, us, runs of one side within 1 to 3 % (8 KV heads at G = 4 unless stated;
+// workgroups = sequences * KV heads * nodes):
+//   eight or fewer splits, up to four heads a KV head: 48 workgroups 9.11 / 8.92, 192 10.71 / 10.68 and 12.77 / 12.61, 384 12.36 / 12.42,
+//   480 11.13 / 11.23, 960 12.61 / 12.69 and 15.04 / 14.99, 1920 15.75 / 15.73, 3072 22.8 / 23.0, 3840 21.3 / 21.3, 7680 32.9 / 33.3
+//   and 48.8 / 49.5: the line at a workgroup per CU;
+//   ... more heads, where one workgroup has several fours of rows that share what they read: two KV heads at G = 8, 120 12.4 / 12.1,
+//   240 14.5 / 14.0, 480 15.55 / 14.89 and 12.9 / 12.6, 960 15.64 / 15.64, 1920 20.7 / 21.2: two workgroups per CU;
+//   packed rows (below), fours of rows: 240 10.30 / 10.23, 600 11.88 / 11.95 and 13.8 / 13.5, 1200 14.53 / 14.50, 1920 22.65 / 22.19, 2400
+//   34.5 / 34.8, 3840 23.7 / 24.4, 9600 38.7 / 40.5: eight of them per CU;
+//   nine to sixteen: 192 workgroups 12.42 / 12.10 and 16.1 / 15.4, 384 21.5 / 21.3, 480 14.94 / 14.49; G = 5, 192 16.4 / 15.6, 960 33.8 /
+//   33.5 (384 15.8 / 16.1); G = 8, 120 14.8 / 14.5, 240 21.8 / 21.4; fp32, 480 and 512 90.8 / 81.6 and 96.1 / 87.1;
+//   more, and shares: 32 splits, 96 35.3 / 31.0; full pass in shares, 1920 74 / 61, 7680 205 / 176, at G = 5 184 / 138; fp32, 64
+//   splits, 96 69.6 / 62.3; 64 channels, 480 29.9 / 29.5, shares equal.
 // Partially verified tokens in front of the tree that the context kernel has left to the tree segment (fp32) make that long
-// enough to be worth a wavefront of its own up to one per SIMD (kernels of before): 16 of them, 64 channels, eight splits, 296
-// fours of rows 18.4 / 17.3, 960 29.6 / 27.8, 1920 45.4 / 46.4; two splits 17.9 / 18.3 (960), 21.3 / 27.8 (1920), at 128
-// channels 47.2 / 44.4, 56 / 70.
+// enough to be worth a wavefront of its own up to one per SIMD: 16 of them, 64 channels, three splits, 480 35.2 / 34.9, two, 512
+// 47.9 / 47.9, one, 1024 91.7 / 92.8, 1920 94.6 / 96.7, 3840 100.2 / 104.7; twelve, 128 channels, eight splits, 128 42.9 / 33.7, 480 82.3 /
+// 76.6, 1024 197 / 193, 1920 204 / 206.
 static bool combine_two_waves(const Shape &s, const Partials &p, bool pack)
 {
     if (p.stream || p.nsplit > 8) return true;
