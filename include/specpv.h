@@ -286,8 +286,8 @@ typedef struct specpv_lists {
  * Writes through kv->k, kv->v (rows from L_b on; the allocation must cover max_blocks * B
  * tokens) and kv->ctx_len, n_pending [batch] (device), in stream order.  The buffer may lie in the cache it
  * goes to (one sequence, token-major rows, written behind the committed tokens); other overlaps are the
- * caller's mistake.  Workspace: its zeroed head,
- * and 4 bytes per sequence (specpv_workspace_bytes covers it). */
+ * caller's mistake.  Workspace: its zeroed head;
+ * 4 bytes per sequence behind it are asked for and reserved (specpv_workspace_bytes covers them). */
 int specpv_commit_accepted(const specpv_kv *kv, void *buf_k, void *buf_v, int32_t pending_cap, int32_t M_tree,
                            int32_t *n_pending, const int32_t *accepted, const int32_t *n_accepted,
                            int32_t max_accept, specpv_mode mode, void *kmax, void *kmin,
@@ -301,7 +301,7 @@ int specpv_commit_accepted(const specpv_kv *kv, void *buf_k, void *buf_v, int32_
  * layers must share one shape, one set of strides, one dtype and ONE ctx_len array; the counters
  * (ctx_len, n_pending) are read by every layer's copies and updated once afterwards, so the
  * result is what specpv_commit_accepted would give per layer on private copies of the counters.
- * 1 <= n_layers <= SPECPV_MAX_LAYERS.  A few launches for up to 32 layers instead of a few per layer. */
+ * 1 <= n_layers <= SPECPV_MAX_LAYERS.  One launch for up to 32 layers and 910 sequences. */
 #define SPECPV_MAX_LAYERS 256
 int specpv_commit_accepted_layers(const specpv_kv *const *kv, void *const *buf_k, void *const *buf_v,
                                   int32_t n_layers, int32_t pending_cap, int32_t M_tree,

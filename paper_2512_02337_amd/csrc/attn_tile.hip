@@ -554,7 +554,6 @@ hipError_t launch_attn_ctx_tile(const Shape &s, const int32_t *sel_idx, const in
     a.div_nsplit = make_fastdiv((uint32_t)nctx);
     a.div_hkv = make_fastdiv((uint32_t)s.Hkv);
     a.div_B = make_fastdiv((uint32_t)s.B);
-    a.div_M = make_fastdiv((uint32_t)s.M);
     a.div_W = make_fastdiv((uint32_t)(nctx * tg));   // token ranges: one per token group of every split
     int groups = head_groups_code(s.Hkv);
     if (a.n_bg / 8 > 65535) groups = 0;

@@ -1,10 +1,10 @@
 // What a full verification does behind its context attention, in one launch: the merge of the partials (combine.hip) and the
 // scores of the blocks (score_mfma.hip).  Neither needs the other.  The merge is a chain of round trips with few wavefronts a
 // CU and no matrix work; the scores are a round trip and then matrix work: side by side the shorter one costs nothing, and
-// one launch less is waited for.  The first workgroups of the grid score (the selection that follows waits for all of them), the others
-// merge, as many rows each as a scoring workgroup has wavefronts for.  Results are those of the two launches to the bit:
-// the same functions on the same pieces.  (Times: launch_refresh_tail.  What is left is bound by the longer of the two, three
-// round trips and the partials' 8 to 20 MB, and by the start of the launch.)
+// one launch less is waited for.  The grid goes by eights of (sequence, KV head) pairs: of each the first workgroups score (the
+// selection that follows waits for all of them), the others merge, as many rows each as a scoring workgroup has wavefronts for.
+// Results are those of the two launches to the bit: the same functions on the same pieces.  (Times: launch_refresh_tail.  What is
+// left is bound by the longer of the two, three round trips and the partials' 8 to 20 MB, and by the start of the launch.)
 #include "combine.h"
 #include "score.h"
 
