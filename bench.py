@@ -25,14 +25,14 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 # RECORDED, not live: HBM bytes per specpv_partial_verify_attn call from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE
 # (KiB per dispatch, FETCH scaled by 2.0 as a plain device copy calibrates it), and the per-kernel durations of a
-# rocprofv3 --kernel-trace --stats run, as committed under profiles/.  They describe the launch plan named here
+# rocprofv3 --kernel-trace run of 16 layers in a graph, as committed under profiles/.  They describe the launch plan named here
 # (kernels and split count); the line carries them only while the library still plans the call that way.
 RECORDED = {"llama8b_128k": {
     "plan": {"kernels": ["attn_ctx_tile_kernel", "combine_kernel"], "splits": 16},
-    "traffic_bytes": (8694 + 4385) * 2 * 1024 + (7920 + 480) * 1024,
+    "traffic_bytes": (8694 + 4387) * 2 * 1024 + (7920 + 480) * 1024,
     "traffic_source": "profiles/pmc_traffic_llama8b_128k.md",
-    "kernels": [{"name": "attn_ctx_tile_kernel", "us": 11.7}, {"name": "combine_kernel", "us": 4.1}],
-    "kernels_source": "profiles/kernel_durations_llama8b_128k.md"}}
+    "kernels": [{"name": "attn_ctx_tile_kernel", "us": 10.5}, {"name": "combine_kernel", "us": 4.7}],
+    "kernels_source": "profiles/kernel_durations_cases.md"}}
 
 
 def parse():
