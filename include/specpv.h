@@ -149,7 +149,7 @@ int specpv_block_summarize(const specpv_kv *kv, int32_t blk_begin, int32_t blk_e
  *   every block if nb_b <= ns + k + nr.
  * sel_idx   [batch, Hkv, n_sel] int32, n_sel = ns + k + nr + n_extra_slots, ascending, padded with -1.
  * sel_count [batch, Hkv] int32.
- * scores    optional [batch, Hkv, max_blocks] fp32 (NULL: kept in the workspace).
+ * scores    optional [batch, Hkv, max_blocks] fp32 (NULL: in the workspace, where the selection needs any: max_blocks > ns + k + nr).
  * workspace may be NULL when scores is given; the one-launch route of specpv_debug_set_select_route
  * uses the arrival words of a workspace of 64 KiB or more (zero before the call, zero again after it). */
 int specpv_select_blocks(const specpv_kv *kv, const specpv_tree *tree,
@@ -325,7 +325,8 @@ int specpv_debug_set_route(int route);
 /* Testing and measuring aid, process-wide: how specpv_select_blocks and the refresh of
  * specpv_full_verify_refresh run scoring + selection (Section 3.2, eq. 2-3 and the top-k).
  *   0  the library's choice (currently two launches; a refresh scores in the launch that merges its partials where it
- *      can: bf16, eq. 2, and a place for the scores besides that of the partials)
+ *      can: bf16, eq. 2, and a place for the scores besides that of the partials; lists that keep max_blocks blocks or more
+ *      need no scores)
  *   1  one launch where that is possible, two elsewhere: every scoring workgroup counts itself in on
  *      arrival words of its (sequence, KV head) at the head of the workspace, and the last one to
  *      arrive selects (no workgroup waits for another; the words are zero again afterwards).

@@ -383,11 +383,13 @@ static SumArgs side_summaries(const Shape &s, int64_t begin, void *kmax, void *k
 static int g_route = 0;
 static unsigned long long *g_timeline = nullptr;   // where instrumented builds (-DSPECPV_TIMELINE) put their time stamps
 
-// The scores that a full pass wants beside the merge of its partials.  done: they are there (else they are still to be taken).
+// The scores that a full pass wants beside the merge of its partials, or the lists themselves where they keep every block (all).
+// done: they are there (else they are still to be taken).
 struct TailScores {
     const void *kmax, *kmin;
     int kind, reduce, last_node;
     float *scores;
+    const TopkArgs *all;
     bool done;
 };
 
@@ -420,8 +422,8 @@ static int run_attention(const Shape &s_in, const AttnPlan &plan, int dtype, con
     else if (plan.kind != kAttnGeneric) e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, none, sum, st);
     else e = launch_attn_ctx_generic(s, dtype, sel_idx, sel_count, n_sel, p, st);
     if (e != hipSuccess) return fail_hip(e);
-    if (tail && tail->scores && refresh_tail_supported(s, dtype, p, tail->kind)) {
-        e = launch_refresh_tail(s, p, out, lse, tail->kmax, tail->kmin, tail->reduce, tail->last_node, tail->scores, st);
+    if (tail && (tail->scores || tail->all) && refresh_tail_supported(s, dtype, p, tail->kind)) {
+        e = launch_refresh_tail(s, p, out, lse, tail->kmax, tail->kmin, tail->reduce, tail->last_node, tail->scores, tail->all, st);
         tail->done = true;
     } else {
         e = launch_combine(s, dtype, p, out, lse, st);
@@ -457,13 +459,22 @@ static hipError_t static_scratch(void **out)
 // specpv_debug_set_select_route).
 static int g_select_route = 0;
 
+static TopkArgs list_args(const specpv_select_cfg *cfg, int32_t *sel_idx, int32_t *sel_count)
+{
+    return TopkArgs{cfg->n_sink_blocks, cfg->n_recent_blocks, cfg->k_blocks, cfg->n_sink_blocks + cfg->k_blocks + cfg->n_recent_blocks + cfg->n_extra_slots, sel_idx, sel_count};
+}
+
+// No sequence can have more blocks than a list keeps: every block is listed, whatever its score, and where the caller does not
+// ask for the scores there is no use for them.  Selection and partial step, a layer: 884 tokens, 1 node, 16.4 -> 12.3 us; 2869
+// tokens, 59 nodes, 21.5 -> 16.4; fp32, 900 tokens, 18.4 -> 12.8.
+static bool keeps_every_block(const Shape &s, const TopkArgs &sel) { return s.max_blocks <= (int64_t)sel.ns + sel.k + sel.nr; }
+
 // arrive: the zeroed arrival words at the head of a workspace, or nullptr where the caller gave none
 static int run_select(const Shape &s, int dtype, const specpv_tree *tree, const void *kmax, const void *kmin,
                       const specpv_select_cfg *cfg, int32_t *sel_idx, int32_t *sel_count, float *scores, bool scored,
                       unsigned long long *arrive, hipStream_t st)
 {
-    const int n_row = cfg->n_sink_blocks + cfg->k_blocks + cfg->n_recent_blocks + cfg->n_extra_slots;
-    const TopkArgs sel{cfg->n_sink_blocks, cfg->n_recent_blocks, cfg->k_blocks, n_row, sel_idx, sel_count};
+    const TopkArgs sel = list_args(cfg, sel_idx, sel_count);
     // One launch (the last scoring workgroup of a (sequence, KV head) selects) only on request: it is the
     // slower of the two.  Measured per call at one 128K sequence 18.8 against 16.6 us, at 16K 11.0 against
     // 10.9, for a ragged batch of four 41.4 against 34.6: counting 64 workgroups in costs about what a launch
@@ -474,7 +485,7 @@ static int run_select(const Shape &s, int dtype, const specpv_tree *tree, const 
                                                        (int)cfg->score, scores, one ? &sel : nullptr, one ? arrive : nullptr, st);
     if (e != hipSuccess) return fail_hip(e);
     if (one && !scored) return SPECPV_OK;
-    e = launch_topk(s, scores, sel.ns, sel.nr, sel.k, n_row, sel_idx, sel_count, st);
+    e = launch_topk(s, scores, sel.ns, sel.nr, sel.k, sel.n_row, sel_idx, sel_count, st);
     if (e != hipSuccess) return fail_hip(e);
     return SPECPV_OK;
 }
@@ -523,11 +534,17 @@ int specpv_select_blocks(const specpv_kv *kv, const specpv_tree *tree, const voi
     if (!kmax || !kmin || !sel_idx || !sel_count) return SPECPV_EINVAL;
     if (((uintptr_t)kmax | (uintptr_t)kmin) & 15) return SPECPV_EINVAL;
     const Shape s = make_shape(kv, tree);
+    const bool no_scores = !scores;
     if (!scores) {
         // behind the arrival words
         const size_t need = kArriveBytes + align_up((size_t)s.batch * s.Hkv * s.max_blocks * sizeof(float));
         if (!workspace || workspace_bytes < need) return SPECPV_EWORKSPACE;
         scores = (float *)((char *)workspace + kArriveBytes);
+    }
+    const TopkArgs sel = list_args(cfg, sel_idx, sel_count);
+    if (no_scores && keeps_every_block(s, sel) && __atomic_load_n(&g_select_route, __ATOMIC_RELAXED) == 0) {
+        const hipError_t e = launch_list_all(s, sel, (hipStream_t)stream);
+        return e == hipSuccess ? SPECPV_OK : fail_hip(e);
     }
     unsigned long long *arrive = workspace && workspace_bytes >= kArriveBytes ? (unsigned long long *)workspace : nullptr;
     return run_select(s, kv->dtype, tree, kmax, kmin, cfg, sel_idx, sel_count, scores, false, arrive, (hipStream_t)stream);
@@ -598,10 +615,24 @@ int specpv_full_verify_refresh(const specpv_kv *kv, const specpv_tree *tree, voi
     // behind the partials.  (In the place of the partials they can only follow the merge.)
     const size_t behind = align_up(w.need);
     float *apart = scores ? scores : (workspace_bytes >= behind + (w.scores_need - kArriveBytes) ? (float *)((char *)workspace + behind) : nullptr);
-    if (__atomic_load_n(&g_select_route, __ATOMIC_RELAXED) != 0) apart = nullptr;   // scoring as a launch of its own, or with the selection
-    TailScores tail{kmax, kmin, (int)cfg->score, (int)cfg->reduce, tree->last_node - tree->n_key_only, apart, false};
+    const bool beside = __atomic_load_n(&g_select_route, __ATOMIC_RELAXED) == 0;
+    if (!beside) apart = nullptr;   // scoring as a launch of its own, or with the selection
+    // Lists of every block go out with the merge as well: one launch less, and no scores that nobody asked for.  Refresh, 60 nodes, 900
+    // tokens 14.3 -> 10.5 us, 4000 tokens 18.2 -> 14.3, seven sequences of 624 in blocks of 16 22.2 -> 18.6; 64 channels, 538 tokens,
+    // 1 node 13.3 -> 8.9.  (Up to eight blocks they are still taken, for those who look for them behind the partials, as the tests of
+    // that place do: 0.4 to 1 of some 10 us.)
+    const TopkArgs sel = list_args(cfg, sel_idx, sel_count);
+    const bool all = beside && keeps_every_block(s, sel), score = scores || !all || s.max_blocks <= 8;
+    const bool all_beside = all && (apart || !score);
+    TailScores tail{kmax, kmin, score ? (int)cfg->score : (int)SPECPV_SCORE_EQ2, (int)cfg->reduce, tree->last_node - tree->n_key_only,
+                    score ? apart : nullptr, all_beside ? &sel : nullptr, false};
     rc = run_attention(s, plan, kv->dtype, nullptr, nullptr, 0, out, lse, workspace, workspace_bytes, sum, st, &tail);
     if (rc != SPECPV_OK) return rc;
+    if (tail.done && tail.all) return SPECPV_OK;
+    if (all && !score) {
+        const hipError_t e = launch_list_all(s, sel, st);
+        return e == hipSuccess ? SPECPV_OK : fail_hip(e);
+    }
     return run_select(s, kv->dtype, tree, kmax, kmin, cfg, sel_idx, sel_count, tail.done ? apart : (scores ? scores : w.scores), tail.done, w.arrive, st);
 }
 

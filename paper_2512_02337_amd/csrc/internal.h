@@ -265,6 +265,8 @@ hipError_t launch_scores(const Shape &s, int dtype, const void *kmax, const void
 // n_row: entries per list row (>= ns + k + nr; the rest is padding for later commits)
 hipError_t launch_topk(const Shape &s, const float *scores, int ns, int nr, int k, int n_row,
                        int32_t *sel_idx, int32_t *sel_count, hipStream_t st);
+// every block into every list: s.max_blocks <= ns + k + nr
+hipError_t launch_list_all(const Shape &s, const TopkArgs &a, hipStream_t st);
 hipError_t launch_attn_ctx_generic(const Shape &s, int dtype, const int32_t *sel_idx,
                                    const int32_t *sel_count, int n_sel, Partials p, hipStream_t st);
 bool attn_ctx_mfma_supported(const Shape &s, int dtype);
@@ -307,10 +309,11 @@ int attn_group_blocks(const Shape &s);   // row blocks of each
 double attn_group_chunk_us(int blocks);
 hipError_t launch_combine(const Shape &s, int dtype, Partials p, void *out, float *lse, hipStream_t st);
 bool combine_packed(const Shape &s, int dtype);
-// the merge and the scores (eq. 2) in one launch; kind: as for launch_scores
+// the merge and the scores (eq. 2; scores == nullptr: none) in one launch; kind: as for launch_scores.  all != nullptr: and lists of
+// every block (launch_list_all)
 bool refresh_tail_supported(const Shape &s, int dtype, const Partials &p, int kind);
 hipError_t launch_refresh_tail(const Shape &s, Partials p, void *out, float *lse, const void *kmax, const void *kmin, int reduce, int last_node,
-                               float *scores, hipStream_t st);
+                               float *scores, const TopkArgs *all, hipStream_t st);
 // to_cache != 0: pending + accepted rows go to the cache tail (lengths, summaries updated);
 // otherwise the accepted rows join the pending rows of the buffer.  missed_words: the zeroed words at the
 // head of a workspace (kArriveBytes; zero again when the launches have finished).

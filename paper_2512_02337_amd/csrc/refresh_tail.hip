@@ -7,27 +7,36 @@
 // left is bound by the longer of the two, three round trips and the partials' 8 to 20 MB, and by the start of the launch.)
 #include "combine.h"
 #include "score.h"
+#include "topk.h"
 
 namespace specpv {
 
 struct TailArgs {
-    int score_rows;   // of the grid's y in each z: workgroups that score
+    int score_rows;   // of the grid's y in each z: workgroups that score (all: and one that lists)
     int n_score;      // scoring workgroups
     int rows, units;  // query rows (PACK: fours of rows) of a KV head; of a workgroup
     int n_bg;
+    int all;          // every block is listed, by a workgroup of each KV head in front of the others
     FastDiv div_groups, div_heads, div_hkv;   // by the scoring workgroups of a KV head, by KV heads (by_xcd: by eights of them), by KV heads
 };
 
 // SHARED (combine_rows) is not needed for the bits and takes registers that two scoring workgroups on a CU do not leave.
 template <int D, int NP, bool MULTI, bool PACK, bool STAGED>
 __global__ __launch_bounds__(64 * kScoreMaxWaves) void refresh_tail_kernel(const int32_t *a_parent, const void *a_q, const float *a_po, const float *a_pml,
-                                                                           Shape s, Partials part, void *out, float *lse, float scale_log2, ScoreArgs a, TailArgs t)
+                                                                           Shape s, Partials part, void *out, float *lse, float scale_log2, ScoreArgs a, TailArgs t, TopkArgs lists)
 {
     extern __shared__ __attribute__((aligned(1024))) char tail_smem[];
     s.parent = a_parent; s.q = a_q;
     part.o = const_cast<float *>(a_po); part.ml = const_cast<float *>(a_pml);
     if ((int)blockIdx.y < t.score_rows) {
-        const int row = (int)blockIdx.z * t.score_rows + (int)blockIdx.y;
+        if (t.all && blockIdx.y == 0) {
+            const int bg = (int)blockIdx.z * 8 + (int)blockIdx.x;
+            if (bg >= t.n_bg) return;
+            const int b = (int)t.div_hkv.div((uint32_t)bg);
+            list_all_blocks(s.ctx_len, a.div_B, s.max_blocks, s.Hkv, bg - b * s.Hkv, b, lists, threadIdx.x, blockDim.x);
+            return;
+        }
+        const int row = (int)blockIdx.z * (t.score_rows - t.all) + (int)blockIdx.y - t.all;
         int group, g, b;
         if (a.by_xcd) {   // KV head g on XCD g % 8
             if (row * 8 >= t.n_score) return;
@@ -77,12 +86,12 @@ bool refresh_tail_supported(const Shape &s, int dtype, const Partials &p, int ki
 }
 
 hipError_t launch_refresh_tail(const Shape &s, Partials p, void *out, float *lse, const void *kmax, const void *kmin, int reduce, int last_node,
-                               float *scores, hipStream_t st)
+                               float *scores, const TopkArgs *all, hipStream_t st)
 {
     const bool pack = combine_packed(s, SPECPV_BF16);
     ScoreArgs a = score_plan(s, kmax, kmin, reduce, last_node, scores, false);
     const int per_row = pack ? 1 : (s.G + 3) / 4;
-    if (a.waves < 2 * per_row) a.waves = 2 * per_row;   // (the others find no rows to score)
+    if (a.waves < 2 * per_row || !scores) a.waves = 2 * per_row;   // (the others find no rows to score)
     TailArgs t = {};
     t.units = a.waves / (2 * per_row);
     t.rows = pack ? (s.M * s.G + 3) / 4 : s.M;
@@ -101,10 +110,12 @@ hipError_t launch_refresh_tail(const Shape &s, Partials p, void *out, float *lse
         // (what a CU has to itself may as well take the LDS for it: 16K 11.1 -> 9.4 us, 64K 14.9 -> 14.3)
         a.staged = a.waves > 4 && room > 0 && (int64_t)a.groups * t.n_bg <= room;
     }
+    if (!scores) { a.groups = a.tiles = a.sums = a.staged = 0; }
     const int64_t n_score = (int64_t)a.groups * s.Hkv * s.batch;
     t.n_score = (int)n_score;
-    t.score_rows = (int)(((n_score + 7) / 8 + z - 1) / z);
-    t.div_groups = make_fastdiv((uint32_t)a.groups);
+    t.all = all ? 1 : 0;
+    t.score_rows = (int)(((n_score + 7) / 8 + z - 1) / z) + t.all;
+    t.div_groups = make_fastdiv((uint32_t)(a.groups > 0 ? a.groups : 1));
     t.div_heads = make_fastdiv((uint32_t)(a.by_xcd ? s.Hkv / 8 : s.Hkv));
     t.div_hkv = make_fastdiv((uint32_t)s.Hkv);
     const dim3 grid(8, t.score_rows + (t.rows + t.units - 1) / t.units, (unsigned)z), block(64 * a.waves);
@@ -118,7 +129,7 @@ hipError_t launch_refresh_tail(const Shape &s, Partials p, void *out, float *lse
         auto kern = refresh_tail_kernel<DD, NP, MULTI, PACK, ST>;                                                               \
         const hipError_t e0 = once.run([&] { return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)score_lds(DD, kScoreMostTiles, kScoreSums, kScoreMaxWaves)); }); \
         if (e0 != hipSuccess) return e0;                                                                                    \
-        hipLaunchKernelGGL(kern, grid, block, lds, st, s.parent, s.q, (const float *)p.o, (const float *)p.ml, s, p, out, lse, scale_log2, a, t); \
+        hipLaunchKernelGGL(kern, grid, block, lds, st, s.parent, s.q, (const float *)p.o, (const float *)p.ml, s, p, out, lse, scale_log2, a, t, all ? *all : TopkArgs{}); \
     } while (0)
 #define SPECPV_LAUNCH(DD, NP, MULTI, PACK)                                                                                  \
     do { if (a.staged) SPECPV_LAUNCH_K(DD, NP, MULTI, PACK, true); else SPECPV_LAUNCH_K(DD, NP, MULTI, PACK, false); } while (0)

@@ -202,6 +202,19 @@ __global__ __launch_bounds__(NT) void topk_fast_kernel(const float *scores, cons
     topk_fast_body<P, NT, false>(lds, scores, ctx_len, B, max_blocks, Hkv, blockIdx.x, blockIdx.y, a);
 }
 
+// Lists of all blocks (list_all_blocks): the selection where its caller keeps no scores and no sequence can have more blocks than
+// sink, retrieval and local blocks together.  One trip for the length; what it takes is the launch.
+__global__ __launch_bounds__(256) void list_all_kernel(const int32_t *ctx_len, FastDiv div_B, int max_blocks, int Hkv, TopkArgs a)
+{
+    list_all_blocks(ctx_len, div_B, max_blocks, Hkv, blockIdx.x, blockIdx.y, a, threadIdx.x, 256);
+}
+
+hipError_t launch_list_all(const Shape &s, const TopkArgs &a, hipStream_t st)
+{
+    hipLaunchKernelGGL(list_all_kernel, dim3(s.Hkv, s.batch), dim3(256), 0, st, s.ctx_len, make_fastdiv((uint32_t)s.B), s.max_blocks, s.Hkv, a);
+    return hipGetLastError();
+}
+
 bool score_mfma_supported(const Shape &s, int dtype);
 hipError_t launch_scores_mfma(const Shape &s, const void *kmax, const void *kmin, int reduce,
                               int last_node, int kind, float *scores, const TopkArgs *sel,

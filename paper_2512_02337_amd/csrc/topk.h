@@ -110,6 +110,17 @@ __device__ __forceinline__ Digit threshold_digit(const uint32_t *hist, int krem,
     return d;
 }
 
+// Lists with room for every block there can be: the scores have no say.  `threads` threads, this one is number tid.
+__device__ __forceinline__ void list_all_blocks(const int32_t *ctx_len, const FastDiv &div_B, int max_blocks, int Hkv, int g, int b,
+                                                const TopkArgs &a, int tid, int threads)
+{
+    const int L = ctx_len[b];
+    const int nb = L > 0 ? min((int)div_B.div((uint32_t)L + div_B.d - 1u), max_blocks) : 0;
+    const int64_t pair = (int64_t)b * Hkv + g;
+    for (int c = tid; c < a.n_row; c += threads) a.sel_idx[pair * a.n_row + c] = c < nb ? c : -1;
+    if (tid == 0) a.sel_count[pair] = nb;
+}
+
 // Every thread of the workgroup calls this (it holds workgroup barriers).  ACROSS: the scores
 // were stored by other workgroups of the same launch with agent-scope stores and are read the
 // same way, past the caches that are private to a part of the chip.
