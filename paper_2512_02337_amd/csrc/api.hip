@@ -357,15 +357,15 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
 // Where a full pass on the group kernel recomputes many summaries, some of its workgroups do that beside the others, and
 // the plan's splits or shares are cut to the CUs that are left: the attention loop runs at the clock that the chip's power
 // allows and leaves a third of the memory's rate unused, the summaries are nothing but reads.  A CU takes in 45 bytes per
-// nanosecond with blocks of 64 (16 KiB in flight per wavefront; smaller blocks have less, and lose: refresh at 64K in blocks
-// of 16 134 us with two launches, 250 or more so), so the two sides end together with a fraction f / (1 + f) of the CUs on the
+// nanosecond (16 KiB in flight per wavefront: blocks of 64, twos of 32 or fours of 16; other small blocks have less, and lose), so the two sides end together with a fraction f / (1 + f) of the CUs on the
 // summaries; 0.235 was fitted to the fastest counts: stale refresh of 128K, eight row blocks, 0 / 40 / 48 / 56 / 64
 // workgroups: 202 / 211 / 195 / 193 / 196 us; of 64K, ten: 130 / 120 / 122 / 123 / 124; of 16K + 32K + 48K + 64K, eight:
-// 247 / 264 / 240 / 238 / 239.  Fewer than eight row blocks leave less of the memory's rate.
+// 247 / 264 / 240 / 238 / 239.  Fewer than eight row blocks leave less of the memory's rate.  Small blocks, two launches /
+// so: 64K in blocks of 32 113.8 / 102.9, of 16 118.1 / 108.9; 2 x 30000 at G = 5 in blocks of 16 135.0 / 123.6; 8 x 28046 354 / 350.
 static SumArgs side_summaries(const Shape &s, int64_t begin, void *kmax, void *kmin, AttnPlan &plan)
 {
     const SumArgs none{0, 0, nullptr, nullptr};
-    if (plan.kind != kAttnGroup || s.D != 128 || s.B < 64 || attn_group_blocks(s) < 8 || begin >= s.max_blocks) return none;
+    if (plan.kind != kAttnGroup || s.D != 128 || (s.B < 64 && s.B != 32 && s.B != 16) || attn_group_blocks(s) < 8 || begin >= s.max_blocks) return none;
     const int64_t cus = device_cu_count(), parts = attn_group_parts(s), pairs = (int64_t)s.batch * s.Hkv;
     const int64_t chunks = ((int64_t)s.max_blocks * s.B + 31) / 32, stale = chunks - begin * s.B / 32;
     if (parts * (plan.stream ? plan.stream : pairs * plan.nsplit) > cus) return none;   // more than one round of workgroups

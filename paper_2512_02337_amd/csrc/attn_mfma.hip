@@ -779,14 +779,20 @@ void attn_ctx_mfma_group_kernel(Shape s, Partials part, MfmaArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (D == 128 && SPAN == 32) {
         if ((int)blockIdx.y < a.sum_rows) {
-            // a workgroup for the summaries: its wavefronts take every n-th of the stale blocks of all pairs
+            // a workgroup for the summaries: its wavefronts take every n-th of the stale blocks (or twos, fours of small ones) of all pairs
+            const int per = s.B == 16 ? 4 : (s.B == 32 ? 2 : 1);
             const int wgs = a.sum_rows * (int)gridDim.x, n = wgs * W;
             int at = wave * wgs + (int)blockIdx.y * (int)gridDim.x + (int)blockIdx.x;
             for (int b = 0; b < s.batch; ++b) {
                 const int L = s.ctx_len[b];
-                const int nb = min(L > 0 ? (int)a.div_B.div((uint32_t)L + (uint32_t)s.B - 1u) : 0, s.max_blocks), stale = max(nb - a.sum_begin, 0);
+                const int nb = min(L > 0 ? (int)a.div_B.div((uint32_t)L + (uint32_t)s.B - 1u) : 0, s.max_blocks), stale = (max(nb - a.sum_begin, 0) + per - 1) / per;
                 for (int g = 0; g < s.Hkv; ++g) {
-                    for (; at < stale; at += n) summarize_block<bf16_t, D>(s, b, g, a.sum_begin + at, L, a.kmax, a.kmin, lane);
+                    for (; at < stale; at += n) {
+                        const int i = a.sum_begin + at * per;
+                        if (per == 1) summarize_block<bf16_t, D>(s, b, g, i, L, a.kmax, a.kmin, lane);
+                        else if (per == 2) summarize_small<bf16_t, D, 8>(s, b, g, i, nb, L, a.kmax, a.kmin, lane);
+                        else summarize_small<bf16_t, D, 4>(s, b, g, i, nb, L, a.kmax, a.kmin, lane);
+                    }
                     at -= stale;
                 }
             }
