@@ -11,7 +11,7 @@ LIB = os.path.join(HERE, "libspecpv.so")
 NATIVE = os.path.join(HERE, "_native.so")
 # the same library with time stamps inside the partial-verify attention kernel (timeline.py uses it)
 LIB_TIMELINE = os.path.join(HERE, "libspecpv_timeline.so")
-SOURCES = ["api.hip", "summarize.hip", "select.hip", "score_mfma.hip", "attn_generic.hip",
+SOURCES = ["api.hip", "summarize.hip", "select.hip", "score_mfma.hip", "attn_generic.hip", "attn_f32.hip",
            "attn_mfma.hip", "attn_tile.hip", "combine.hip", "refresh_tail.hip", "commit.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

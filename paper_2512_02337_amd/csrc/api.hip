@@ -212,6 +212,7 @@ static size_t static_need(const Shape &s, const AttnPlan &plan)
 static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool full, size_t bytes)
 {
     AttnPlan plan{1, !attn_ctx_mfma_supported(s, dtype) ? kAttnGeneric : (s.D == 64 ? kAttnGroup : kAttnSplit), 4, 0};
+    if (plan.kind == kAttnGeneric) plan.tg = 0;
     // partial rows that have room (Workspace), and splits
     const size_t row_bytes = part_row_bytes(s, plan.kind), pair_rows = (size_t)s.M * s.G, fixed_bytes = kArriveBytes + 512;
     const int64_t room_rows = bytes > fixed_bytes ? (int64_t)((bytes - fixed_bytes) / row_bytes) : 0;   // (< 2^63: a row has more than one byte)
@@ -248,7 +249,28 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
         // tokens each for the shortest ranges, whose time is one wavefront's chain)
         const int64_t few = few_splits(tokens);
         int64_t ns = few;
-        if (tokens > 1024) {
+        const int64_t pairs = (int64_t)s.batch * s.Hkv, R = (int64_t)s.M * s.G, parts = (R + kF32Rows - 1) / kF32Rows, chunks = (tokens + 31) / 32;
+        // K and V rows by way of LDS (attn_f32.hip) for more than one tile of 16 query rows, where there is enough to do.  Best splits of
+        // either, by way of LDS / straight from memory, us: 128 channels, 8 KV heads, 60 nodes at G = 4, 16K 172 / 199, 37 nodes 136 /
+        // 199, 8 nodes 60 / 69, one KV head, 16 nodes 43 / 54, 2K 15.4 / 16.2, 8 nodes 14.4 / 14.0; 64 channels, 8 KV heads, 37 nodes, 16K
+        // 72 / 93, 2K 20.1 / 21.4, 30 nodes 17.5 / 16.7, 4K 24.5 / 25.9; one KV head, 30 nodes, 16K 24.6 / 28.0, 4K 14.2 / 14.3, 1100 11.2 / 10.7.
+        const bool staged = dtype == SPECPV_F32 && R > 16 && tokens > 1024 && n_blocks * s.B < ((int64_t)1 << 31) - 64 &&
+                            (s.D == 128 ? R > 48 || tokens > 2048 : tokens > 4096 || pairs * parts * chunks >= 2048);
+        if (staged) {
+            // Workgroups of a CU share its matrix cores, four at a time its registers; a chunk (32 tokens here) takes one by itself its
+            // latency.  Partials are written and read back.  Fitted to 3000 timings of 190 shapes: the splits that this chooses are 1.7 %
+            // slower than the fastest in the mean.
+            const double share = s.D == 128 ? 1.48 : 0.73, alone = s.D == 128 ? 4.0 : 2.4, partials = 1.0 * (double)pairs * (double)R * s.D * 4e-6;
+            double best = -1.0;
+            const int64_t most = at_hand(static_room([&] { return few; }, chunks < 64 ? chunks : 64));
+            for (int64_t c = 1; c <= most; ++c) {
+                const int64_t here = (pairs * parts * c + cus - 1) / cus, p = (chunks + c - 1) / c;
+                const double work = share * (double)here > alone ? share * (double)here : alone;
+                const double us = (double)p * work + 0.56 * (double)((here + 3) / 4) + partials * (double)c + (c > 16 ? 0.1 : 0.0);
+                if (best < 0.0 || us < best) { best = us; ns = c; }
+            }
+            plan.tg = 1;
+        } else if (tokens > 1024) {
             const int64_t waves = (int64_t)((s.G * s.M + 31) / 32) * s.batch * s.Hkv;
             ns = (8 * cus + waves - 1) / waves;
             if (ns > tokens / 64) ns = tokens / 64;
@@ -420,6 +442,7 @@ static int run_attention(const Shape &s_in, const AttnPlan &plan, int dtype, con
     const FusedArgs none{nullptr, nullptr, nullptr, 0, g_timeline};
     if (plan.kind == kAttnSplit) e = launch_attn_ctx_tile(s, sel_idx, sel_count, n_sel, p, plan.tg, g_timeline, st);
     else if (plan.kind != kAttnGeneric) e = launch_attn_ctx_mfma(s, sel_idx, sel_count, n_sel, p, nsplit, plan.kind, none, sum, st);
+    else if (plan.tg) e = launch_attn_ctx_f32(s, sel_idx, sel_count, n_sel, p, st);
     else e = launch_attn_ctx_generic(s, dtype, sel_idx, sel_count, n_sel, p, st);
     if (e != hipSuccess) return fail_hip(e);
     if (tail && (tail->scores || tail->all) && refresh_tail_supported(s, dtype, p, tail->kind)) {

@@ -1,5 +1,5 @@
 // Context part of the verification attention for any supported dtype and head dim on the fp32 matrix
-// instructions (fp32 inputs, and bf16 caches too large for the 32-bit offsets of the bf16 kernels).  Products and
+// instructions (small fp32 calls -- larger ones: attn_f32.hip --, and bf16 caches too large for the 32-bit offsets of the bf16 kernels).  Products and
 // sums are fp32, as on the vector ALU, at twice its rate.
 //
 // A wavefront owns NR tiles of 16 query rows of a KV head (row r = head r / M of the group, node r % M) and one KV

@@ -267,6 +267,9 @@ hipError_t launch_topk(const Shape &s, const float *scores, int ns, int nr, int 
                        int32_t *sel_idx, int32_t *sel_count, hipStream_t st);
 // every block into every list: s.max_blocks <= ns + k + nr
 hipError_t launch_list_all(const Shape &s, const TopkArgs &a, hipStream_t st);
+// fp32 with several tiles of query rows to a KV head (attn_f32.hip), kF32Rows rows to a workgroup
+constexpr int kF32Rows = 64;
+hipError_t launch_attn_ctx_f32(const Shape &s, const int32_t *sel_idx, const int32_t *sel_count, int n_sel, Partials p, hipStream_t st);
 hipError_t launch_attn_ctx_generic(const Shape &s, int dtype, const int32_t *sel_idx,
                                    const int32_t *sel_count, int n_sel, Partials p, hipStream_t st);
 bool attn_ctx_mfma_supported(const Shape &s, int dtype);
@@ -278,7 +281,7 @@ enum AttnKind { kAttnGeneric = 0, kAttnSplit = 1, kAttnGroup = 3 };
 struct AttnPlan {
     int nsplit;
     int kind;
-    int tg;       // kAttnSplit: token groups per workgroup
+    int tg;       // kAttnSplit: token groups per workgroup; kAttnGeneric: 1 where attn_f32.hip does it
     int stream;   // kAttnGroup: workgroups that share the chunks of all pairs (see Partials), or 0
 };
 // The whole call in the eight-wavefront kernel (kAttnSplit only): the draft-tree segment as one more
