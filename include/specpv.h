@@ -180,10 +180,10 @@ int specpv_partial_verify_attn(const specpv_kv *kv, const specpv_tree *tree,
  * fixed arguments, tight serving loops, harnesses that forbid hipMalloc.  The same computation
  * as specpv_partial_verify_attn (same kernels, results bit-identical to those with a workspace of the
  * size that specpv_workspace_bytes states) with the split-KV partial
- * results kept in a file-scope device array of SPECPV_STATIC_SCRATCH_BYTES inside the library
+ * results kept in a file-scope device array of 64 MiB inside the library
  * (one copy per GPU, held until the process ends).  The call allocates nothing and calls no
- * allocating routine.  A call whose partial results would not fit (specpv_workspace_bytes with
- * cfg == NULL says how much a shape needs) returns SPECPV_ELIMIT, and specpv_last_hip_error()
+ * allocating routine.  A call whose partial results, with few enough splits, would not fit
+ * SPECPV_STATIC_SCRATCH_BYTES returns SPECPV_ELIMIT, and specpv_last_hip_error()
  * then holds the two sizes; nothing has been enqueued.  Every call on a GPU shares that GPU's
  * array, which keeps the last call's contents; nothing in it needs to start at zero.  Calls that
  * overlap on one GPU (two streams without an ordering between them) race on it: order them. */

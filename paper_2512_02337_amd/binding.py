@@ -312,7 +312,7 @@ def specpv_partial_verify_attn(kv, tree, sel_idx, sel_count, out, lse=None, work
 
 def specpv_partial_verify_attn_static(kv, tree, sel_idx, sel_count, out, lse=None):
     """specpv_partial_verify_attn without a workspace: the partial results live in the library's own
-    static device array (at most STATIC_SCRATCH_BYTES; larger shapes raise SpecPVError -3)."""
+    static device array (shapes that few splits take beyond STATIC_SCRATCH_BYTES raise SpecPVError -3)."""
     rc = (_native or _loaded()).partial_static(kv, tree, sel_idx, sel_count, out, lse)
     if rc is not None and rc != -3:   # (-3: the text below)
         return _check(rc)

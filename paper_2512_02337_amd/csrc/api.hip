@@ -135,6 +135,13 @@ struct AttnCost {
         const int64_t rounds = ((int64_t)s.batch * s.Hkv * parts * ns + cus - 1) / cus, p = (chunks + ns - 1) / ns;
         return us(rounds, p, 3.11, attn_group_chunk_us(blocks), parts, ns);
     }
+    // ... in equal shares of all chunks, whose partials are found by the lengths and merged in rounds
+    double shares(int parts, int blocks, int64_t wgs) const
+    {
+        const double pairs = (double)s.batch * s.Hkv, p = pairs * (double)chunks / (double)wgs;
+        const double chain = 3.11 + p * attn_group_chunk_us(blocks) * (double)parts * (double)wgs / (double)device_cu_count(), memory = kv * (0.02 * (double)parts + 0.115);
+        return sqrt(chain * chain + memory * memory) + 0.199 * ((double)wgs + pairs) * s.M * s.G * 512e-6 + 6.0;
+    }
 };
 
 // The fewest splits that specpv_partial_verify_attn_static has to have room for: the count by which a shape was first
@@ -154,6 +161,11 @@ static int64_t first_splits(const Shape &s, int64_t chunks, int64_t cus)
     const int64_t row_blocks = (s.G * s.M + 31) / 32, parts = row_blocks == 9 || row_blocks == 10 ? 1 : (row_blocks + 7) / 8;
     return chunks >= 32 * ns ? best_of((int64_t)s.batch * s.Hkv * parts, 1, at_most(chunks / 8)) : ns;
 }
+
+// The array of specpv_partial_verify_attn_static.  Larger than the SPECPV_STATIC_SCRATCH_BYTES by which it takes calls, so that no
+// plan has to be cut to those: every call runs the plan that the static one would.  Cut to 16 MiB / as it is now: refresh, fp32, 37
+// nodes at G = 4, 16K, 8 KV heads, 26 / 32 splits 179 / 151 us; full pass, 64 channels, 15005 and 30011 tokens, 25 / 32 splits 55.7 / 48.9.
+constexpr int64_t kStaticArray = 64 << 20;
 
 // Bytes of a partial row: O as fp16 (bf16 at 128 channels) or fp32, and the (m, l) pair.
 static bool half_partials(const Shape &s, int kind) { return kind != kAttnGeneric && s.D == 128; }
@@ -202,6 +214,9 @@ static size_t static_need(const Shape &s, const AttnPlan &plan)
     return plan.stream || half_partials(s, plan.kind) ? w.need : w.total;
 }
 
+// A split of a full pass with no more chunks than these is short enough for sequences of any lengths (plan_attention).
+constexpr int64_t kShortSplit = 48;
+
 // Which kernel the context part of the attention runs on and how many KV splits it uses when
 // it covers n_blocks blocks per (sequence, KV head).  Host-only and deterministic in its
 // arguments, so specpv_workspace_bytes and the calls agree.  full: every block of sequences whose
@@ -209,8 +224,11 @@ static size_t static_need(const Shape &s, const AttnPlan &plan)
 // bytes: what the caller's workspace has.  A smaller tree may be worth more splits than a larger one, so a workspace that
 // was sized for the largest tree of a decode loop need not hold the plan of every smaller one: then the call takes the
 // splits that fit (one always does where the larger tree's plan did).
-static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool full, size_t bytes)
+// taking: the plan, cut to SPECPV_STATIC_SCRATCH_BYTES, by which specpv_partial_verify_attn_static decides whether it takes a call.  It
+// runs the plan of every other call then, whose partials fit kStaticArray.
+static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool full, size_t bytes, bool taking = false)
 {
+    const int64_t array = taking ? (int64_t)SPECPV_STATIC_SCRATCH_BYTES : kStaticArray;
     AttnPlan plan{1, !attn_ctx_mfma_supported(s, dtype) ? kAttnGeneric : (s.D == 64 ? kAttnGroup : kAttnSplit), 4, 0};
     if (plan.kind == kAttnGeneric) plan.tg = 0;
     // partial rows that have room (Workspace), and splits
@@ -230,12 +248,12 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
     // (a list may have room for more blocks than there are)
     const int64_t tokens = (n_blocks < s.max_blocks ? n_blocks : (int64_t)s.max_blocks) * s.B;
     if (tokens <= 0) return plan;
-    // what specpv_partial_verify_attn_static took with the splits of fp32 partials that a call had at first must fit its
-    // array with more of them: no more splits than have room, where those few have
+    // what specpv_partial_verify_attn_static took with the splits of fp32 partials that a call had at first must fit the
+    // array with more of them: no more splits than have room, where those few have in SPECPV_STATIC_SCRATCH_BYTES
     const int64_t static_slot = rows * (s.D + 2) * (int64_t)sizeof(float), static_fixed = (int64_t)kArriveBytes + 1024;
     auto static_splits = [&]() {
         const bool half = half_partials(s, plan.kind);
-        return ((int64_t)SPECPV_STATIC_SCRATCH_BYTES - static_fixed) / (half ? rows * (2 * s.D + 8) : static_slot) - (half ? 0 : 1);
+        return (array - static_fixed) / (half ? rows * (2 * s.D + 8) : static_slot) - (half ? 0 : 1);
     };
     auto static_room = [&](auto few_of, int64_t ns) {
         const int64_t room = static_splits();
@@ -254,7 +272,7 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
         // either, by way of LDS / straight from memory, us: 128 channels, 8 KV heads, 60 nodes at G = 4, 16K 172 / 199, 37 nodes 136 /
         // 199, 8 nodes 60 / 69, one KV head, 16 nodes 43 / 54, 2K 15.4 / 16.2, 8 nodes 14.4 / 14.0; 64 channels, 8 KV heads, 37 nodes, 16K
         // 72 / 93, 2K 20.1 / 21.4, 30 nodes 17.5 / 16.7, 4K 24.5 / 25.9; one KV head, 30 nodes, 16K 24.6 / 28.0, 4K 14.2 / 14.3, 1100 11.2 / 10.7.
-        const bool staged = dtype == SPECPV_F32 && R > 16 && tokens > 1024 && n_blocks * s.B < ((int64_t)1 << 31) - 64 &&
+        const bool staged = !taking && dtype == SPECPV_F32 && R > 16 && tokens > 1024 && n_blocks * s.B < ((int64_t)1 << 31) - 64 &&
                             (s.D == 128 ? R > 48 || tokens > 2048 : tokens > 4096 || pairs * parts * chunks >= 2048);
         if (staged) {
             // Workgroups of a CU share its matrix cores, four at a time its registers; a chunk (32 tokens here) takes one by itself its
@@ -290,16 +308,33 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
         int64_t ns = 1;
         bool keep_static = false;
         if (s.D == 64) {
-            // the group kernel; two workgroups share a CU, four chunks or more per split
-            const int64_t slots = 2 * cus;
-            int64_t most = chunks / 4 > 1 ? (chunks / 4 < 64 ? chunks / 4 : 64) : 1, best = -1;
+            // the group kernel; two workgroups or more have room on a CU, but share what it gives
             const int64_t few = few_splits(tokens);
+            int64_t most = chunks / (taking ? 4 : 2) > 1 ? (chunks / (taking ? 4 : 2) < 64 ? chunks / (taking ? 4 : 2) : 64) : 1;
             most = at_hand(static_room([&] { return few; }, most));
             // up to 1024 tokens: the few splits of the vector-ALU kernel are enough
             if (chunks <= 32 && most > few) most = few;
-            for (int64_t c = 1; c <= most; ++c) {
-                const int64_t cost = (base * c + slots - 1) / slots * ((chunks + c - 1) / c * 8 + 10) + c;
-                if (best < 0 || cost < best) { best = cost; ns = c; }
+            if (taking) {
+                const int64_t slots = 2 * cus;
+                int64_t best = -1;
+                for (int64_t c = 1; c <= most; ++c) {
+                    const int64_t cost = (base * c + slots - 1) / slots * ((chunks + c - 1) / c * 8 + 10) + c;
+                    if (best < 0 || cost < best) { best = cost; ns = c; }
+                }
+            } else {
+                // us, fitted to 3700 timings of 249 shapes (1 to 60 nodes, G = 4, 5 and 8, 2 to 80 pairs, 1100 to 30000 tokens): the
+                // splits that this chooses are 0.7 % slower than the fastest in the mean, 2.2 % for batches of lengths 1 / n to n / n.
+                // (Splits that filled two places a CU: 8.6 % slower than these.  64 channels, 8 KV heads at G = 4, 37 nodes, 8K 21.2 ->
+                // 17.8 us, four sequences of 4K 28.7 -> 24.0; one node, 16 of up to 3000 21.6 -> 16.9.)
+                const double chunk = 0.243 + 0.092 * attn_group_blocks(s), partials = 0.371 * (double)s.batch * s.Hkv * (double)(s.M * s.G) * 256e-6;
+                double best = -1.0;
+                for (int64_t c = 1; c <= most; ++c) {
+                    const int64_t here = (base * c + cus - 1) / cus, p = (chunks + c - 1) / c;
+                    const double share = 0.808 * (double)here > 1.0 ? 0.808 * (double)here : 1.0;
+                    const double us = (double)p * chunk * share + (here > 2 ? 0.973 * (double)(here - 2) : 0.0) + 0.285 * (double)here + partials * (double)c +
+                                      0.247 * (double)((c + 7) / 8) + (c > 16 ? 0.486 : 0.0);
+                    if (best < 0.0 || us < best) { best = us; ns = c; }
+                }
             }
         } else {
             const AttnCost cost(s, chunks);
@@ -308,11 +343,14 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             // a full pass; the tile kernel, which a few nodes may be faster with, does not.  24 nodes at G = 4, 16 sequences
             // of 16K (512 chunks), 8 KV heads, tile kernel against shares: equal lengths 203 / 209 us, 1/16 to 16/16 of it
             // 159 / 124, one long and fifteen short ones 144 / 47; four sequences of 258 chunks: 37 / 43, 34 / 34, 30 / 25.
-            const bool uneven = full && s.batch > 1 && chunks > 256;
+            // Few pairs take the tile kernel where its ranges are short: 30000 + 15000 tokens, 2 KV heads, 37 nodes at G = 8 37.5 us,
+            // the group kernel 43.7, shares 44.8; with 32 pairs, 6K to 25K tokens, 18 nodes at G = 5 71.8 / 58.1 / 60.4; 16 pairs and
+            // one node 37.8 / 37.3 / 45.2.
+            const bool uneven = full && s.batch > 1 && chunks > 256, small = (int64_t)s.batch * s.Hkv <= 8 || (int64_t)s.M * s.G <= 32;
             double best = -1.0, best_tile = -1.0;
             int64_t ns_tile = 1;
             auto take = [&](double us, int kind, int tg, int64_t c) {
-                if (uneven && kind == kAttnSplit) {
+                if (uneven && kind == kAttnSplit && (taking || !small || chunks > kShortSplit * c * tg)) {
                     if (best_tile < 0.0 || us < best_tile) { best_tile = us; ns_tile = c; }
                 } else if (best < 0.0 || us < best) {
                     best = us; plan.kind = kind; plan.tg = tg; ns = c;
@@ -333,22 +371,32 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             if (keep_static && ns > static_splits()) ns = static_splits();
         }
         plan.nsplit = (int)ns;
+        const int64_t shares = cus * ((s.D == 64 || !taking) && (taking || attn_group_blocks(s) <= 2) ? 2 : 1) / parts;   // workgroups of them
         // The sequences of a batch may differ in length, and the lengths live on the device: for a full pass the group
         // kernel's workgroups take equal shares of all chunks.  (Four times as many splits as fill the chip even that out
         // too, at the price of as many partials: full pass over 32K + 64K + 96K + 128K tokens at G = 5, 64 nodes, attention
         // and combine: 563 us with the splits that fill the chip, 462 with four times as many, 453 with the shares.)  Up to
-        // 1024 tokens there is nothing to even out.
-        if (full && s.batch > 1 && s.batch <= 64 && plan.kind == kAttnGroup && chunks > 32 && (int64_t)s.batch * s.Hkv * chunks < ((int64_t)1 << 30)) {
+        // 1024 tokens there is nothing to even out, and little where a split has few chunks: its partials have one place each, where a
+        // share's are found by the lengths and merged in rounds.  Shares / splits, us, of equal lengths, 1 / n to n / n, one long and the
+        // others a sixteenth of it, 60 nodes, 8 KV heads: 16 sequences of 3000, G = 5, four splits of 24 chunks 99.5 / 94.3, 91.9 / 69.9,
+        // 49.7 / 48.9, two of 47 99.5 / 83.2, 91.9 / 71.3, 49.7 / 65.7; 16 of 2048, two of 32 77.0 / 64.3, 79.7 / 55.4, 45.5 / 51.4;
+        // 10 of 4096, G = 4, three of 43 69.2 / 58.4, 53.6 / 51.2, 34.2 / 48.2; 2 of 16384, 16 of 32 50.8 / 46.8, 44.9 / 44.2, 39.9 / 38.3.
+        // 64 channels, where a chunk has less to do, 37 nodes: two sequences of 15005 and 30011, 32 splits 52.4 / 48.9; four of 8192 by
+        // quarters 32.8 / 32.1; 16 by sixteenths of 3000 45.4 / 42.2.
+        // (and, 128 channels, where the splits don't cost another round: 11 sequences of 5855, 37 nodes, shares 72.5, five splits 76.5)
+        const bool short_splits = !taking && (s.D == 64 ? chunks <= 32 * ns : chunks <= kShortSplit * ns && AttnCost(s, chunks).group(parts, attn_group_blocks(s), ns, cus) <
+                                                                                  AttnCost(s, chunks).shares(parts, attn_group_blocks(s), shares < 1 ? 1 : shares));
+        if (full && s.batch > 1 && s.batch <= 64 && plan.kind == kAttnGroup && chunks > 32 && !short_splits && (int64_t)s.batch * s.Hkv * chunks < ((int64_t)1 << 30)) {
             const int64_t pairs = (int64_t)s.batch * s.Hkv, R = (int64_t)s.M * s.G;
-            int64_t wgs = cus * (s.D == 64 ? 2 : 1) / parts;
+            int64_t wgs = shares;
             if (wgs > pairs * chunks / 8) wgs = pairs * chunks / 8;   // eight chunks or more each
             if (wgs < 1) wgs = 1;
-            const int64_t static_slots = ((int64_t)SPECPV_STATIC_SCRATCH_BYTES - static_fixed) / (R * (int64_t)row_bytes) - pairs;
+            const int64_t static_slots = (array - static_fixed) / (R * (int64_t)row_bytes) - pairs;
             if (keep_static && wgs > static_slots && static_slots >= wgs / 2) wgs = static_slots;
             // the workspace of as many splits as hold that many slots
             const int64_t bytes = (wgs + pairs) * R * (int64_t)row_bytes + 512, slot = pairs * R * (4 * s.D + 8);
             const int64_t splits = (bytes + slot - 1) / slot > 1 ? (bytes + slot - 1) / slot - 1 : 1;
-            const bool fits = (int64_t)kArriveBytes + bytes <= (int64_t)SPECPV_STATIC_SCRATCH_BYTES;
+            const bool fits = (int64_t)kArriveBytes + bytes <= array;
             const int64_t at_most = room_rows / R - pairs;   // ... that the caller's has room for
             if (at_most >= 1 && splits <= 64 && (fits || (!keep_static && static_room([&] { return s.D == 64 ? few_splits(tokens) : first_splits(s, chunks, cus); }, 64) == 64))) {
                 plan.stream = (int)(wgs < at_most ? wgs : at_most);
@@ -366,7 +414,10 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             if (c > 64) c = 64;
             while (c > ns && (chunks + c - 1) / c < 64) --c;
             // (what fits the static array still does)
-            auto in_static = [&](int64_t n) { return static_need(s, AttnPlan{(int)n, plan.kind, plan.tg, 0}) <= (size_t)SPECPV_STATIC_SCRATCH_BYTES; };
+            auto in_static = [&](int64_t n) {
+                const AttnPlan x{(int)n, plan.kind, plan.tg, 0};
+                return (taking ? static_need(s, x) : layout_workspace(s, x, nullptr).need) <= (size_t)array;
+            };
             if (in_static(ns))
                 while (c > ns && !in_static(c)) --c;
             c = at_hand(c);
@@ -458,7 +509,7 @@ static int run_attention(const Shape &s_in, const AttnPlan &plan, int dtype, con
 // Library-owned scratch for callers that cannot pass a workspace (specpv_partial_verify_attn_static).
 // One copy per GPU, alive until the process ends.  In host code the array's name is only a handle:
 // the device address comes from hipGetSymbolAddress, once per device, and is what the kernels get.
-static __device__ __align__(256) unsigned char scratch[SPECPV_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[kStaticArray];
 
 static hipError_t static_scratch(void **out)
 {
@@ -598,18 +649,24 @@ int specpv_partial_verify_attn_static(const specpv_kv *kv, const specpv_tree *tr
     if (sel_idx && (!sel_count || n_sel < 0)) return SPECPV_EINVAL;
     if (sel_idx && n_sel > (1 << 24)) return SPECPV_ELIMIT;
     const Shape s = make_shape(kv, tree);
-    // the same plan as specpv_partial_verify_attn; its partial results must fit the static array
-    const AttnPlan plan = plan_attention(s, kv->dtype, sel_idx ? n_sel : s.max_blocks, !sel_idx, SIZE_MAX);
-    const size_t need = static_need(s, plan);
+    // what a plan cut to SPECPV_STATIC_SCRATCH_BYTES has room for there is taken ...
+    const int64_t blocks = sel_idx ? n_sel : s.max_blocks;
+    const size_t need = static_need(s, plan_attention(s, kv->dtype, blocks, !sel_idx, SIZE_MAX, true));
     if (need > (size_t)SPECPV_STATIC_SCRATCH_BYTES) {
         snprintf(g_hip_err, sizeof(g_hip_err), "static scratch: the call needs %zu bytes, the array holds %zu",
                  need, (size_t)SPECPV_STATIC_SCRATCH_BYTES);
         return SPECPV_ELIMIT;
     }
+    // ... and run with the plan of specpv_partial_verify_attn, whose partial results fit the array
+    const AttnPlan plan = plan_attention(s, kv->dtype, blocks, !sel_idx, SIZE_MAX);
+    if (layout_workspace(s, plan, nullptr).need > (size_t)kStaticArray) {
+        snprintf(g_hip_err, sizeof(g_hip_err), "static scratch: the plan needs %zu bytes", layout_workspace(s, plan, nullptr).need);
+        return SPECPV_ELIMIT;
+    }
     void *ws = nullptr;
     const hipError_t e = static_scratch(&ws);
     if (e != hipSuccess) return fail_hip(e);
-    return run_attention(s, plan, kv->dtype, sel_idx, sel_count, n_sel, out, lse, ws, (size_t)SPECPV_STATIC_SCRATCH_BYTES, SumArgs{}, (hipStream_t)stream);
+    return run_attention(s, plan, kv->dtype, sel_idx, sel_count, n_sel, out, lse, ws, (size_t)kStaticArray, SumArgs{}, (hipStream_t)stream);
 }
 
 int specpv_full_verify_refresh(const specpv_kv *kv, const specpv_tree *tree, void *kmax, void *kmin,
