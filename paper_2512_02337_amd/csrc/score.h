@@ -130,6 +130,59 @@ constexpr int score_tile_bytes(int D) { return 128 * D; }
 constexpr int kScoreStage = 4096;
 static inline size_t score_lds(int D, int tiles, int sums, int staged_waves) { return (size_t)tiles * (score_tile_bytes(D) + sums * 256) + (size_t)staged_waves * kScoreStage; }
 
+// What 32 query rows from r0 on (q: A operands) add to `acc`, for the tile of blocks whose operands stand at `at` (tile: where LDS begins).
+template <int D, bool BOUND>
+__device__ __forceinline__ float score_rows(const uint32_t (&at)[D / 16], const bf16x8 (&q)[D / 16], char *tile, int r0, int R, int reduce, int last_node, int G, int kg, float acc)
+{
+    constexpr int KS = D / 16, HALF = 64 * D;
+    f32x16 sx, sn;
+    if constexpr (BOUND) {
+#pragma unroll
+        for (int x = 0; x < 16; ++x) sx[x] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            // the packed bf16 pairs split by sign: 0xffff in the halves whose sign bit is set
+            const uint4 w4 = __builtin_bit_cast(uint4, q[ks]);
+            const uint32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+            uint32_t pw[4], nw[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t m = ((w[e] >> 15) & 0x00010001u) * 0xffffu;
+                nw[e] = w[e] & m;
+                pw[e] = w[e] & ~m;
+            }
+            const char *p = tile + (at[ks] - (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)tile);
+            const bf16x8 bx = __builtin_bit_cast(bf16x8, *(const uint4 *)p), bn = __builtin_bit_cast(bf16x8, *(const uint4 *)(p + HALF));
+            sx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, make_uint4(pw[0], pw[1], pw[2], pw[3])), bx, sx, 0, 0, 0);
+            sx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, make_uint4(nw[0], nw[1], nw[2], nw[3])), bn, sx, 0, 0, 0);
+        }
+    } else {
+        score_products(at, q, sx, sn);
+    }
+    // accumulator slot x holds row r0 + (x>>2)*8 + kg*4 + (x&3) of this lane's block
+    if (reduce == SPECPV_REDUCE_MAX) {
+        // (rows past the end are the last row once more)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) acc = fmaxf(acc, BOUND ? sx[x] : fmaxf(sx[x], sn[x]));
+    } else if (reduce != SPECPV_REDUCE_LAST && r0 + 32 <= R) {
+        // all 32 rows count (every wavefront but the one with the ragged end): no per-row tests; the
+        // same order of operations as below
+#pragma unroll
+        for (int x = 0; x < 16; ++x) acc += BOUND ? sx[x] : fmaxf(sx[x], sn[x]);
+    } else {
+        // (a row that does not count weighs in as nothing: with a branch for each, this wavefront was the last one home.
+        // Four at a time: all sixteen conditions at once are more scalar registers than there are.)
+        const int lo = reduce == SPECPV_REDUCE_LAST ? last_node * G : 0, hi = reduce == SPECPV_REDUCE_LAST ? lo + G : R;
+        const int from = r0 + kg * 4 - lo;
+#pragma unroll
+        for (int x = 0; x < 16; ++x) {
+            acc += (uint32_t)(from + (x >> 2) * 8 + (x & 3)) < (uint32_t)(hi - lo) ? (BOUND ? sx[x] : fmaxf(sx[x], sn[x])) : 0.f;
+            if ((x & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    return acc;
+}
+
 // BOUND: the channel-wise bound instead of eq. 2.  Per channel the larger product is q * Kmax
 // where q >= 0 and q * Kmin where q < 0 (Kmax >= Kmin), so the bound is the sum of two inner
 // products as well: max(q, 0) . Kmax + min(q, 0) . Kmin, accumulated into one tile.
@@ -238,53 +291,9 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const ScoreArgs &a, 
             uint32_t at[KS];
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) at[ks] = (base + (uint32_t)(t * TILE)) ^ (32u * (uint32_t)ks);
-            f32x16 sx, sn;
-            if constexpr (BOUND) {
-#pragma unroll
-                for (int x = 0; x < 16; ++x) sx[x] = 0.f;
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    // the packed bf16 pairs split by sign: 0xffff in the halves whose sign bit is set
-                    const uint4 w4 = __builtin_bit_cast(uint4, q[ks]);
-                    const uint32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
-                    uint32_t pw[4], nw[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const uint32_t m = ((w[e] >> 15) & 0x00010001u) * 0xffffu;
-                        nw[e] = w[e] & m;
-                        pw[e] = w[e] & ~m;
-                    }
-                    const char *p = tile + (at[ks] - (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)tile);
-                    const bf16x8 bx = __builtin_bit_cast(bf16x8, *(const uint4 *)p), bn = __builtin_bit_cast(bf16x8, *(const uint4 *)(p + HALF));
-                    sx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, make_uint4(pw[0], pw[1], pw[2], pw[3])), bx, sx, 0, 0, 0);
-                    sx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, make_uint4(nw[0], nw[1], nw[2], nw[3])), bn, sx, 0, 0, 0);
-                }
-            } else {
-                score_products(at, q, sx, sn);
-            }
             float *mine = red + ((rb & (kScoreSums - 1)) * a.tiles + t) * 64 + lane;
             float acc = rb < kScoreSums ? (a.reduce == SPECPV_REDUCE_MAX ? -INFINITY : 0.f) : *mine;
-            // accumulator slot x holds row r0 + (x>>2)*8 + kg*4 + (x&3) of this lane's block
-            if (a.reduce == SPECPV_REDUCE_MAX) {
-                // (rows past the end are the last row once more)
-#pragma unroll
-                for (int x = 0; x < 16; ++x) acc = fmaxf(acc, BOUND ? sx[x] : fmaxf(sx[x], sn[x]));
-            } else if (a.reduce != SPECPV_REDUCE_LAST && r0 + 32 <= R) {
-                // all 32 rows count (every wavefront but the one with the ragged end): no per-row tests; the
-                // same order of operations as below
-#pragma unroll
-                for (int x = 0; x < 16; ++x) acc += BOUND ? sx[x] : fmaxf(sx[x], sn[x]);
-            } else {
-                // (a row that does not count weighs in as nothing: with a branch for each, this wavefront was the last one home.
-                // Four at a time: all sixteen conditions at once are more scalar registers than there are.)
-                const int lo = a.reduce == SPECPV_REDUCE_LAST ? a.last_node * s.G : 0, hi = a.reduce == SPECPV_REDUCE_LAST ? lo + s.G : R;
-                const int from = r0 + kg * 4 - lo;
-#pragma unroll
-                for (int x = 0; x < 16; ++x) {
-                    acc += (uint32_t)(from + (x >> 2) * 8 + (x & 3)) < (uint32_t)(hi - lo) ? (BOUND ? sx[x] : fmaxf(sx[x], sn[x])) : 0.f;
-                    if ((x & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-                }
-            }
+            acc = score_rows<D, BOUND>(at, q, tile, r0, R, a.reduce, a.last_node, s.G, kg, acc);
             *mine = acc;
         }
         r0 += W * 32;
@@ -317,6 +326,138 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const ScoreArgs &a, 
             if (ACROSS) __hip_atomic_store((uint32_t *)dst, __float_as_uint(out), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             else *dst = out;
         }
+    }
+}
+
+// LDS of score_stream: two halves of tiles and of partial sums.
+static inline size_t score_stream_lds(int D, int tiles, int sums) { return 2 * (size_t)tiles * (score_tile_bytes(D) + sums * 256); }
+
+// Scores of every a.groups-th group of a.tiles tiles, from `group` on (eq. 2): where a (sequence, KV head) has many tiles, a workgroup
+// keeps the query rows in registers, a block of 32 to a wavefront, and goes through its groups while the next one's rows are on their
+// way.  One barrier a group: behind it the group's tiles have landed, everybody is done with the half that the next group goes to, and
+// the sums of the group before are there, to be added up and stored.  Reads and writes of LDS are assembly: the compiler would have each
+// wait for the tiles that are on their way.
+template <int D>
+__device__ __forceinline__ void score_stream(const Shape &s, const ScoreArgs &a, const int group, const int g, const int b)
+{
+    constexpr int KS = D / 16, LPR = D / 8, RPO = 64 / LPR, OPS = D / 16, HALF = 64 * D, TILE = 2 * HALF, H = D / 64;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __attribute__((aligned(1024))) char score_smem[];
+    const int lane = threadIdx.x & 63, W = a.waves, T = a.tiles, R = s.M * s.G;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 31, kg = lane >> 5;
+    const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)score_smem;
+    const uint32_t red = ring + 2u * (uint32_t)(T * TILE), red_half = (uint32_t)(a.sums * T * 256);   // [half][sums][tile][lane]
+    const int L = s.ctx_len[b];
+    const int nb = min(L > 0 ? (int)a.div_B.div((uint32_t)L + (uint32_t)s.B - 1u) : 0, s.max_blocks);
+    const int step = a.groups * 32 * T;
+    int i0 = group * 32 * T;
+    if (i0 >= nb) return;
+    const int r0 = a.row0 + wave * 32;
+    // the query rows as whole lines, through what will be the second half of the tiles (score_tiles: read_staged)
+    u32x4 raw[H][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = min(r0 + 8 * i + (lane >> 3), R - 1);
+        const int j = (int)a.div_G.div_straight((uint32_t)r), hh = r - j * s.G;
+        const uint16_t *qrow = (const uint16_t *)s.q + (((int64_t)b * s.M + j) * s.Hq + g * s.G + hh) * D + (lane & 7) * 8;
+#pragma unroll
+        for (int h = 0; h < H; ++h) raw[h][i] = *(const u32x4 *)(qrow + 64 * h);
+    }
+    const int rl = lane / LPR, pos = lane % LPR;
+    const int64_t arr_row0 = ((int64_t)b * s.Hkv + g) * s.max_blocks;
+    const uintptr_t to_min = (uintptr_t)a.kmin - (uintptr_t)a.kmax;
+    auto request = [&](int first, int half) __attribute__((always_inline)) {   // (score_tiles has the layout)
+        const int n_t = min(T, (nb - first + 31) >> 5);
+        for (int d = wave; d < 2 * OPS * n_t; d += W) {
+            const int i = d & (OPS - 1), row = RPO * i + rl, t = d / (2 * OPS);
+            const int blk = min(first + 32 * t + row, s.max_blocks - 1);
+            const int piece = pos ^ (D == 128 ? row & 15 : (row >> 1) & 7);
+            const char *src = (const char *)((uintptr_t)a.kmax + ((d & OPS) ? to_min : 0)) + ((arr_row0 + blk) * D) * 2 + 16 * piece;
+            __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(score_smem + half * T * TILE + (d / OPS) * HALF + i * 1024), 16, 0, 2);
+        }
+    };
+    request(i0, 0);
+    bf16x8 q[KS];
+    {
+        char *mine = score_smem + T * TILE + wave * kScoreStage;
+        const int to = (lane >> 3) * 128, from = n * 128;
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) *(u32x4 *)(mine + 1024 * i + to + 16 * ((lane & 7) ^ ((4 * i + (lane >> 4)) & 7))) = raw[h][i];
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int x = 0; x < 4; ++x) q[4 * h + x] = __builtin_bit_cast(bf16x8, *(const u32x4 *)(mine + from + 16 * ((2 * x + kg) ^ ((n >> 1) & 7))));
+            asm volatile("" ::: "memory");
+        }
+    }
+    const uint32_t lane_at = (uint32_t)n * (2u * D) + ((16u * (uint32_t)kg) ^ (D == 128 ? 16u * ((uint32_t)n & 15u) : 16u * (((uint32_t)n >> 1) & 7u)));
+    const bool by_max = a.reduce == SPECPV_REDUCE_MAX;
+    auto add_up = [&](int first, int half) __attribute__((always_inline)) {
+        const int n_t = min(T, (nb - first + 31) >> 5);
+        for (int t = wave; t < n_t; t += W) {   // a wavefront per tile
+            float sum = by_max ? -INFINITY : 0.f;
+            for (int w0 = 0; w0 < a.sums; w0 += 8) {
+                float o[8];
+                uint32_t at[8];
+#pragma unroll
+                for (int w = 0; w < 8; ++w) at[w] = red + (uint32_t)half * red_half + (uint32_t)(((min(w0 + w, a.sums - 1) * T + t) * 64 + lane) * 4);
+                asm volatile(
+                    "ds_read_b32 %0, %8\n\t"
+                    "ds_read_b32 %1, %9\n\t"
+                    "ds_read_b32 %2, %10\n\t"
+                    "ds_read_b32 %3, %11\n\t"
+                    "ds_read_b32 %4, %12\n\t"
+                    "ds_read_b32 %5, %13\n\t"
+                    "ds_read_b32 %6, %14\n\t"
+                    "ds_read_b32 %7, %15\n\t"
+                    "s_waitcnt lgkmcnt(0)"
+                    : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4]), "=&v"(o[5]), "=&v"(o[6]), "=&v"(o[7])
+                    : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(at[4]), "v"(at[5]), "v"(at[6]), "v"(at[7])
+                    : "memory");
+#pragma unroll
+                for (int w = 0; w < 8; ++w) {
+                    if (w0 + w >= a.sums) o[w] = by_max ? -INFINITY : 0.f;
+                    sum = by_max ? fmaxf(sum, o[w]) : sum + o[w];
+                }
+            }
+            const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);
+            const float lo = __uint_as_float(both[0]), hi = __uint_as_float(both[1]);   // sums of lanes n and n + 32
+            float out;
+            if (by_max) out = fmaxf(lo, hi);
+            else if (a.reduce == SPECPV_REDUCE_MEAN) out = (lo + hi) / (float)R;
+            else out = (lo + hi) / (float)s.G;
+            const int blk = first + 32 * t + n;
+            if (kg == 0 && blk < nb) a.scores[arr_row0 + blk] = out;
+        }
+    };
+    int before = -1;
+    for (int half = 0;; half ^= 1) {
+        __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const int next = i0 + step;
+        if (next < nb) request(next, half ^ 1);
+        if (before >= 0) add_up(before, half ^ 1);
+        const int n_t = min(T, (nb - i0 + 31) >> 5);
+        for (int t = 0; t < n_t; ++t) {
+            uint32_t at[KS];
+            const uint32_t base = ring + (uint32_t)((half * T + t) * TILE) + lane_at;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) at[ks] = base ^ (32u * (uint32_t)ks);
+            const float acc = score_rows<D, false>(at, q, score_smem, r0, R, a.reduce, a.last_node, s.G, kg, by_max ? -INFINITY : 0.f);
+            asm volatile("ds_write_b32 %0, %1" ::"v"(red + (uint32_t)half * red_half + (uint32_t)(((wave * T + t) * 64 + lane) * 4)), "v"(acc) : "memory");
+        }
+        before = i0;
+        if (next >= nb) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            add_up(before, half);
+            return;
+        }
+        i0 = next;
     }
 }
 

@@ -73,6 +73,14 @@ __global__ __launch_bounds__(64 * kScoreMaxWaves) void score_mfma_kernel(Shape s
     }
 }
 
+template <int D>
+__global__ __launch_bounds__(64 * kScoreMaxWaves) void score_stream_kernel(Shape s, ScoreArgs a)
+{
+    const int group = a.by_xcd ? (int)blockIdx.x >> 3 : (int)blockIdx.x;
+    const int g = a.by_xcd ? (int)blockIdx.y * 8 + ((int)blockIdx.x & 7) : (int)blockIdx.y, b = blockIdx.z;
+    score_stream<D>(s, a, group, g, b);
+}
+
 bool score_mfma_supported(const Shape &s, int dtype) { return dtype == SPECPV_BF16; }
 
 bool score_select_supported(const Shape &s, int dtype)
@@ -131,13 +139,51 @@ ScoreArgs score_plan(const Shape &s, const void *kmax, const void *kmin, int red
     return a;
 }
 
+// Whether the scores go by streams (score_stream), and their tiles and workgroups: where a workgroup for every place on the chip has a
+// group of tiles or more.  One block of query rows is a read of the summaries and little else, and is faster with all of them under way
+// at once.  Scores and selection, tiles at once / by streams, us: 8 KV heads at G = 5, 78 nodes, 4 x 1024 blocks 21.6 / 16.2, 60 nodes,
+// 8 x 512 18.3 / 16.5, 512 to 2048 blocks in four 21.8 / 20.4; G = 4, 64 nodes, 8 x 1753 29.2 / 26.0, 24 nodes, 2 x 2048 12.3 / 11.4,
+// one node (one block), 4 x 2048 12.9 / 14.0.
+static bool score_stream_plan(const Shape &s, ScoreArgs &a)
+{
+    const int blocks32 = (a.rows - a.row0 + 31) / 32;
+    if (blocks32 < 2 || blocks32 > kScoreMaxWaves) return false;
+    const int64_t tiles1 = (s.max_blocks + 31) / 32, pairs = (int64_t)s.Hkv * s.batch, cus = device_cu_count();
+    const int T = (blocks32 * kScoreStage + score_tile_bytes(s.D) - 1) / score_tile_bytes(s.D);   // room for the query rows' way
+    const int64_t fit = (int64_t)(160 * 1024 / score_stream_lds(s.D, T, blocks32)), per_cu = 16 / blocks32 < fit ? 16 / blocks32 : fit;
+    if (per_cu < 1) return false;
+    const int64_t phases = (tiles1 + T - 1) / T;
+    int64_t groups = per_cu * cus / pairs;
+    if (groups < 1) groups = 1;
+    if (phases < groups) return false;
+    a.waves = a.sums = blocks32;
+    a.tiles = T;
+    a.groups = (int)groups;
+    a.staged = 0;
+    return true;
+}
+
 // sel != nullptr: the selection runs in the same launch (score_select_supported(s, dtype) holds and
 // arrive points to zeroed words)
 hipError_t launch_scores_mfma(const Shape &s, const void *kmax, const void *kmin, int reduce,
                               int last_node, int kind, float *scores, const TopkArgs *sel,
                               unsigned long long *arrive, hipStream_t st)
 {
-    const ScoreArgs a = score_plan(s, kmax, kmin, reduce, last_node, scores, sel != nullptr);
+    ScoreArgs a = score_plan(s, kmax, kmin, reduce, last_node, scores, sel != nullptr);
+    if (!sel && kind == SPECPV_SCORE_EQ2 && score_stream_plan(s, a)) {
+        const dim3 grid(a.by_xcd ? a.groups * 8 : a.groups, a.by_xcd ? s.Hkv / 8 : s.Hkv, s.batch), block(64 * a.waves);
+#define SPECPV_LAUNCH(DD)                                                                                                       \
+        do {                                                                                                                    \
+            static PerDeviceOnce once;                                                                                          \
+            auto kern = score_stream_kernel<DD>;                                                                                \
+            const hipError_t e0 = once.run([&] { return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); }); \
+            if (e0 != hipSuccess) return e0;                                                                                    \
+            hipLaunchKernelGGL(kern, grid, block, score_stream_lds(DD, a.tiles, a.sums), st, s, a);                             \
+        } while (0)
+        if (s.D == 128) SPECPV_LAUNCH(128); else SPECPV_LAUNCH(64);
+#undef SPECPV_LAUNCH
+        return hipGetLastError();
+    }
     const int waves = a.waves;
     const dim3 grid(a.by_xcd ? a.groups * 8 : a.groups, a.by_xcd ? s.Hkv / 8 : s.Hkv, s.batch), block(64 * waves);
     const size_t lds = score_lds(s.D, a.tiles, a.sums, a.staged ? waves : 0);
