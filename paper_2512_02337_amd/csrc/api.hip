@@ -496,7 +496,7 @@ static int run_attention(const Shape &s_in, const AttnPlan &plan, int dtype, con
     else if (plan.tg) e = launch_attn_ctx_f32(s, sel_idx, sel_count, n_sel, p, st);
     else e = launch_attn_ctx_generic(s, dtype, sel_idx, sel_count, n_sel, p, st);
     if (e != hipSuccess) return fail_hip(e);
-    if (tail && (tail->scores || tail->all) && refresh_tail_supported(s, dtype, p, tail->kind)) {
+    if (tail && (tail->scores || tail->all) && refresh_tail_supported(s, dtype, p, tail->kind) && (!tail->scores || refresh_tail_pays(s, tail->reduce, tail->last_node))) {
         e = launch_refresh_tail(s, p, out, lse, tail->kmax, tail->kmin, tail->reduce, tail->last_node, tail->scores, tail->all, st);
         tail->done = true;
     } else {
@@ -713,7 +713,7 @@ int specpv_full_verify_refresh(const specpv_kv *kv, const specpv_tree *tree, voi
         const hipError_t e = launch_list_all(s, sel, st);
         return e == hipSuccess ? SPECPV_OK : fail_hip(e);
     }
-    return run_select(s, kv->dtype, tree, kmax, kmin, cfg, sel_idx, sel_count, tail.done ? apart : (scores ? scores : w.scores), tail.done, w.arrive, st);
+    return run_select(s, kv->dtype, tree, kmax, kmin, cfg, sel_idx, sel_count, scores ? scores : (apart ? apart : w.scores), tail.done, w.arrive, st);
 }
 
 int specpv_gather_blocks(const specpv_kv *kv, const int32_t *sel_idx, const int32_t *sel_count, int32_t n_sel,

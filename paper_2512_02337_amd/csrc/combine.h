@@ -364,9 +364,17 @@ __device__ __forceinline__ void combine_rows(const Shape &s, const Partials &par
     float m_ctx = -INFINITY, l_ctx = 0.f, o[CPL];
 #pragma unroll
     for (int x = 0; x < CPL; ++x) o[x] = 0.f;
+    // (rounds of eight: the last four only where there are more than four)
     auto fetch = [&](int sp0, P (&r)[NP]) {
+        constexpr int N = MULTI ? 4 : NP;
 #pragma unroll
-        for (int u = 0; u < NP; ++u) r[u].load(po_base + (po_off + (uint32_t)max(min(sp0 + u, ns - 1), 0) * po_step));
+        for (int u = 0; u < N; ++u) r[u].load(po_base + (po_off + (uint32_t)max(min(sp0 + u, ns - 1), 0) * po_step));
+        if constexpr (MULTI) {
+            if (sp0 + 4 < ns) {
+#pragma unroll
+                for (int u = 4; u < NP; ++u) r[u].load(po_base + (po_off + (uint32_t)max(min(sp0 + u, ns - 1), 0) * po_step));
+            }
+        }
     };
     auto add = [&](const P &r, float wt) {
         float v[CPL];
@@ -434,10 +442,12 @@ __device__ __forceinline__ void combine_rows(const Shape &s, const Partials &par
                 const int at = s0 + 16 * k;
                 if (at >= ns) break;
                 if (at + 8 < ns) fetch(at + 8, rb);
-                add_n(ra, w[k], I0{}, I8{});
+                add_n(ra, w[k], I0{}, I4{});
+                if (at + 4 < ns) add_n(ra + 4, w[k], I4{}, I4{});
                 if (at + 8 >= ns) break;
                 if (at + 16 < ns && k + 1 < KM) fetch(at + 16, ra);
-                add_n(rb, w[k], I8{}, I8{});
+                add_n(rb, w[k], I8{}, I4{});
+                if (at + 12 < ns) add_n(rb + 4, w[k], std::integral_constant<int, 12>{}, I4{});
             }
             if (s0 + 16 * KM >= ns) break;
         }

@@ -85,6 +85,19 @@ bool refresh_tail_supported(const Shape &s, int dtype, const Partials &p, int ki
            s.max_blocks <= 32 * 60000 && (int64_t)s.batch * s.Hkv <= 8 * 65535 && !draft_rows_wide(s, sizeof(uint16_t));
 }
 
+// Where the merge alone has eight fours of rows for every CU and there is little to score, the merge's workgroups pay more for the LDS and the
+// wavefronts of the scoring ones than a launch costs.  Tail / merge and scores apart (kernel trace, us; blocks of 32 query rows times tiles of
+// 32 blocks): 16 sequences of 2K at G = 4, 60 nodes (1024) 19.3 / 9.9 + 5.1, of 4K (2048) 23.6 / 17.5 + 5.8; 10 of 4K at G = 5 (1600) 24.4 /
+// 9.3 + 5.7; 11 of 5855 in blocks of 32, 37 nodes (2640) 19.1 / 8.4 + 8.4; 8 of 28046 in blocks of 16, 64 nodes (28160) 38.9 / 11.6 + 28.9;
+// 32K + 64K + 96K + 128K at G = 5 (20480) 28.2 / 10.9 + 24.5.
+bool refresh_tail_pays(const Shape &s, int reduce, int last_node)
+{
+    const bool pack = combine_packed(s, SPECPV_BF16);
+    const ScoreArgs a = score_plan(s, nullptr, nullptr, reduce, last_node, nullptr, false);
+    const int64_t pairs = (int64_t)s.batch * s.Hkv, fours = pairs * (pack ? (s.M * s.G + 3) / 4 : s.M * ((s.G + 3) / 4));
+    return fours < 8 * (int64_t)device_cu_count() || (int64_t)((a.rows - a.row0 + 31) / 32) * ((s.max_blocks + 31) / 32) * pairs > 4096;
+}
+
 hipError_t launch_refresh_tail(const Shape &s, Partials p, void *out, float *lse, const void *kmax, const void *kmin, int reduce, int last_node,
                                float *scores, const TopkArgs *all, hipStream_t st)
 {
