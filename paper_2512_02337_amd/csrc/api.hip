@@ -344,9 +344,8 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             // of 16K (512 chunks), 8 KV heads, tile kernel against shares: equal lengths 203 / 209 us, 1/16 to 16/16 of it
             // 159 / 124, one long and fifteen short ones 144 / 47; four sequences of 258 chunks: 37 / 43, 34 / 34, 30 / 25.
             // Few pairs take the tile kernel where its ranges are short: 30000 + 15000 tokens, 2 KV heads, 37 nodes at G = 8 37.5 us,
-            // the group kernel 43.7, shares 44.8; with 32 pairs, 6K to 25K tokens, 18 nodes at G = 5 71.8 / 58.1 / 60.4; 16 pairs and
-            // one node 37.8 / 37.3 / 45.2.
-            const bool uneven = full && s.batch > 1 && chunks > 256, small = (int64_t)s.batch * s.Hkv <= 8 || (int64_t)s.M * s.G <= 32;
+            // the group kernel 43.7, shares 44.8; with 32 pairs, 6K to 25K tokens, 18 nodes at G = 5 71.8 / 58.1 / 60.4.
+            const bool uneven = full && s.batch > 1 && chunks > 256, small = (int64_t)s.batch * s.Hkv <= 8;
             double best = -1.0, best_tile = -1.0;
             int64_t ns_tile = 1;
             auto take = [&](double us, int kind, int tg, int64_t c) {

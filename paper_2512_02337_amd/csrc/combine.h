@@ -148,7 +148,7 @@ __device__ __forceinline__ float row16_max(float x)
 
 // NP: context partials fetched at once (the smallest of 2, 4, 8, 16 that covers the split count keeps
 // the registers, and with them the resident wavefronts of a batch, in proportion).
-// MULTI: more splits than 16 (a full verification): rounds of NP = 8, each round's
+// MULTI: more splits than 16 (a full verification), or shares: rounds of NP = 8 or 4, each round's
 // reads requested before the previous round is merged.
 // NB: path nodes whose draft K / V rows are requested in the first go: 8 (a tree of candidates alone), or 24
 // when partially verified tokens stand in front of the tree as keys (every candidate's path then starts with
@@ -364,17 +364,9 @@ __device__ __forceinline__ void combine_rows(const Shape &s, const Partials &par
     float m_ctx = -INFINITY, l_ctx = 0.f, o[CPL];
 #pragma unroll
     for (int x = 0; x < CPL; ++x) o[x] = 0.f;
-    // (rounds of eight: the last four only where there are more than four)
     auto fetch = [&](int sp0, P (&r)[NP]) {
-        constexpr int N = MULTI ? 4 : NP;
 #pragma unroll
-        for (int u = 0; u < N; ++u) r[u].load(po_base + (po_off + (uint32_t)max(min(sp0 + u, ns - 1), 0) * po_step));
-        if constexpr (MULTI) {
-            if (sp0 + 4 < ns) {
-#pragma unroll
-                for (int u = 4; u < NP; ++u) r[u].load(po_base + (po_off + (uint32_t)max(min(sp0 + u, ns - 1), 0) * po_step));
-            }
-        }
+        for (int u = 0; u < NP; ++u) r[u].load(po_base + (po_off + (uint32_t)max(min(sp0 + u, ns - 1), 0) * po_step));
     };
     auto add = [&](const P &r, float wt) {
         float v[CPL];
@@ -435,19 +427,32 @@ __device__ __forceinline__ void combine_rows(const Shape &s, const Partials &par
             if constexpr (NP == 16) add_n(ra + 8, w[0], I8{}, I8{});
             break;
         } else {
-            static_assert(!MULTI || NP == 8, "eight partials per round");
+            static_assert(!MULTI || NP == 8 || NP == 4, "partials per round");
             P rb[NP];
+            typedef std::integral_constant<int, 12> I12;
 #pragma unroll
             for (int k = 0; k < KM; ++k) {   // two register sets in turn
                 const int at = s0 + 16 * k;
                 if (at >= ns) break;
-                if (at + 8 < ns) fetch(at + 8, rb);
-                add_n(ra, w[k], I0{}, I4{});
-                if (at + 4 < ns) add_n(ra + 4, w[k], I4{}, I4{});
-                if (at + 8 >= ns) break;
-                if (at + 16 < ns && k + 1 < KM) fetch(at + 16, ra);
-                add_n(rb, w[k], I8{}, I4{});
-                if (at + 12 < ns) add_n(rb + 4, w[k], std::integral_constant<int, 12>{}, I4{});
+                if constexpr (NP == 8) {
+                    if (at + 8 < ns) fetch(at + 8, rb);
+                    add_n(ra, w[k], I0{}, I8{});
+                    if (at + 8 >= ns) break;
+                    if (at + 16 < ns && k + 1 < KM) fetch(at + 16, ra);
+                    add_n(rb, w[k], I8{}, I8{});
+                } else {
+                    if (at + 4 < ns) fetch(at + 4, rb);
+                    add_n(ra, w[k], I0{}, I4{});
+                    if (at + 4 >= ns) break;
+                    if (at + 8 < ns) fetch(at + 8, ra);
+                    add_n(rb, w[k], I4{}, I4{});
+                    if (at + 8 >= ns) break;
+                    if (at + 12 < ns) fetch(at + 12, rb);
+                    add_n(ra, w[k], I8{}, I4{});
+                    if (at + 12 >= ns) break;
+                    if (at + 16 < ns && k + 1 < KM) fetch(at + 16, ra);
+                    add_n(rb, w[k], I12{}, I4{});
+                }
             }
             if (s0 + 16 * KM >= ns) break;
         }

@@ -112,6 +112,7 @@ static void launch_combine_t(const Shape &s, int dtype, Partials p, void *out, f
         if (s.koff > s.kctx) SPECPV_LAUNCH_K(NP, MULTI, 24, false); else SPECPV_LAUNCH_H(NP, MULTI, 8);                  \
     } while (0)
     if (wide) { if (kHalf && p.o_half) SPECPV_LAUNCH(8, true, 8, kHalf, true, false, true); else SPECPV_LAUNCH(8, true, 8, false, true, false, true); }   // (any count of partials)
+    else if (p.stream && p.stream <= 4 * (int64_t)s.batch * s.Hkv) SPECPV_LAUNCH_NP(4, true);   // a pair's shares are few: 16 sequences of 4K 17.5 / 15.2 us
     else if (p.stream) SPECPV_LAUNCH_NP(8, true);
     else if (p.nsplit <= 2) SPECPV_LAUNCH_NP(2, false);
     else if (p.nsplit <= 4) SPECPV_LAUNCH_NP(4, false);
