@@ -18,32 +18,55 @@ namespace specpv {
 // ---------------------------------------------------------------------------
 constexpr int kScoreF32MaxWaves = 16;
 
-template <int D>
+// STAGED: the summary rows go through LDS, once per workgroup and as whole lines; operand by operand every wavefront reads 64 bytes of
+// sixteen rows at a time, which a CU takes in at a third of the rate.  Selection and partial step, 60 nodes at G = 4, 44 blocks, 64
+// channels 27.2 -> 25.1 us; refresh, 37 nodes, 128 channels, 6 x 72 blocks 42.4 -> 39.5.  One tile of query rows has nobody to share
+// with (1 node, 512 blocks, 43.3; through LDS 44.3).
+template <int D, bool STAGED>
 __global__ __launch_bounds__(64 * kScoreF32MaxWaves) void score_f32_kernel(Shape s, const float *__restrict__ kmax, const float *__restrict__ kmin,
                                                                            int reduce, int last_node, int kind, float *__restrict__ scores)
 {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     constexpr int Q = D / 16;   // 16-byte pieces per lane and row
+    constexpr int P = D / 4;    // 16-byte pieces of a row
     __shared__ float red[kScoreF32MaxWaves][16];
+    __shared__ __attribute__((aligned(1024))) f32x4 rows[STAGED ? 2 : 1][STAGED ? 16 : 1][P];   // Kmax, Kmin of the blocks: piece p of row r at p ^ r
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
     const int n = lane & 15, kg = lane >> 4;
     const int g = blockIdx.y, b = blockIdx.z;
     const int i = blockIdx.x * 16 + n;
     const int R = s.M * s.G;
     const int L = s.ctx_len[b];
-    // (columns past the end of the arrays repeat the last block; their scores are never stored)
-    const int64_t so = (((int64_t)b * s.Hkv + g) * s.max_blocks + min(i, s.max_blocks - 1)) * D + 4 * kg;
-    f32x4 kx[Q], kn[Q];
-#pragma unroll
-    for (int x = 0; x < Q; ++x) { kx[x] = *(const f32x4 *)(kmax + so + 16 * x); kn[x] = *(const f32x4 *)(kmin + so + 16 * x); }
-    float acc = reduce == SPECPV_REDUCE_MAX ? -INFINITY : 0.f;
-    for (int r0 = wave * 16; r0 < R; r0 += W * 16) {
+    f32x4 q[Q];
+    auto read_q = [&](int r0) __attribute__((always_inline)) {
         const int r = min(r0 + n, R - 1);
         const int j = r / s.G, hh = r - j * s.G;
         const float *qrow = (const float *)s.q + (((int64_t)b * s.M + j) * s.Hq + g * s.G + hh) * D + 4 * kg;
-        f32x4 q[Q];
 #pragma unroll
         for (int x = 0; x < Q; ++x) q[x] = *(const f32x4 *)(qrow + 16 * x);
+    };
+    // (rows past the end of the arrays repeat the last block; their scores are never stored)
+    const int64_t arr_row0 = ((int64_t)b * s.Hkv + g) * s.max_blocks;
+    f32x4 kx[Q], kn[Q];
+    if constexpr (STAGED) {
+        for (int t = threadIdx.x; t < 2 * 16 * P; t += blockDim.x) {
+            const int row = (t / P) & 15, piece = t % P;
+            const float *src = (t < 16 * P ? kmax : kmin) + (arr_row0 + min((int)blockIdx.x * 16 + row, s.max_blocks - 1)) * D + 4 * piece;
+            rows[t / (16 * P)][row][piece ^ row] = *(const f32x4 *)src;
+        }
+        if (wave * 16 < R) read_q(wave * 16);   // (fewer than four tiles of rows leave wavefronts that only bring summaries)
+        __syncthreads();
+#pragma unroll
+        for (int x = 0; x < Q; ++x) { kx[x] = rows[0][n][(4 * x + kg) ^ n]; kn[x] = rows[1][n][(4 * x + kg) ^ n]; }
+    } else {
+        const int64_t so = (arr_row0 + min(i, s.max_blocks - 1)) * D + 4 * kg;
+#pragma unroll
+        for (int x = 0; x < Q; ++x) { kx[x] = *(const f32x4 *)(kmax + so + 16 * x); kn[x] = *(const f32x4 *)(kmin + so + 16 * x); }
+        read_q(wave * 16);
+    }
+    float acc = reduce == SPECPV_REDUCE_MAX ? -INFINITY : 0.f;
+    for (int r0 = wave * 16; r0 < R; r0 += W * 16) {
+        if (r0 > wave * 16) read_q(r0);
         f32x4 sx = {0.f, 0.f, 0.f, 0.f}, sn = sx;
 #pragma unroll
         for (int x = 0; x < Q; ++x)
@@ -74,7 +97,7 @@ __global__ __launch_bounds__(64 * kScoreF32MaxWaves) void score_f32_kernel(Shape
     __syncthreads();
     if (threadIdx.x >= 16) return;
     float out = red[0][n];
-    for (int w = 1; w < W; ++w) out = reduce == SPECPV_REDUCE_MAX ? fmaxf(out, red[w][n]) : out + red[w][n];
+    for (int w = 1; w < W && w * 16 < R; ++w) out = reduce == SPECPV_REDUCE_MAX ? fmaxf(out, red[w][n]) : out + red[w][n];
     if (reduce == SPECPV_REDUCE_MEAN) out /= (float)R;
     else if (reduce == SPECPV_REDUCE_LAST) out /= (float)s.G;
     int nb = L > 0 ? (L + s.B - 1) / s.B : 0;
@@ -86,10 +109,12 @@ static hipError_t launch_scores_f32(const Shape &s, const void *kmax, const void
                                     float *scores, hipStream_t st)
 {
     const int row_tiles = (s.M * s.G + 15) / 16;
-    dim3 grid((s.max_blocks + 15) / 16, s.Hkv, s.batch), block(64 * (row_tiles < kScoreF32MaxWaves ? row_tiles : kScoreF32MaxWaves));
-#define SPECPV_LAUNCH(DD) \
-    hipLaunchKernelGGL((score_f32_kernel<DD>), grid, block, 0, st, s, (const float *)kmax, (const float *)kmin, reduce, last_node, kind, scores)
-    if (s.D == 128) SPECPV_LAUNCH(128); else SPECPV_LAUNCH(64);
+    const int waves = row_tiles == 1 ? 1 : row_tiles < 4 ? 4 : (row_tiles < kScoreF32MaxWaves ? row_tiles : kScoreF32MaxWaves);
+    dim3 grid((s.max_blocks + 15) / 16, s.Hkv, s.batch), block(64 * waves);
+#define SPECPV_LAUNCH(DD, ST) \
+    hipLaunchKernelGGL((score_f32_kernel<DD, ST>), grid, block, 0, st, s, (const float *)kmax, (const float *)kmin, reduce, last_node, kind, scores)
+    if (row_tiles == 1) { if (s.D == 128) SPECPV_LAUNCH(128, false); else SPECPV_LAUNCH(64, false); }
+    else { if (s.D == 128) SPECPV_LAUNCH(128, true); else SPECPV_LAUNCH(64, true); }
 #undef SPECPV_LAUNCH
     return hipGetLastError();
 }
