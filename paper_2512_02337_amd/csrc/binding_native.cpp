@@ -27,7 +27,9 @@ template <typename F> F fn(Fn i) { return (F)g_fn[i]; }
 // The C descriptor behind the attribute `c` of a KV, Tree or SelectCfg object (a ctypes structure).
 template <typename S> class Desc {
 public:
-    explicit Desc(PyObject *o)
+    Desc() = default;
+    explicit Desc(PyObject *o) { open(o); }
+    void open(PyObject *o)   // once
     {
         PyObject *c = PyObject_GetAttr(o, s_c);
         if (!c || PyObject_GetBuffer(c, &view_, PyBUF_SIMPLE) != 0) PyErr_Clear();
@@ -289,14 +291,14 @@ PyObject *commit_layers(PyObject *, PyObject *const *a, Py_ssize_t n)
     const Items kxs(a[9]), kns(a[10]), sis(a[12]), scs(a[13]);
     if (sums && (kxs.size() != nl || kns.size() != nl)) Py_RETURN_NONE;
     if (with_lists && (sis.size() != nl || scs.size() != nl)) Py_RETURN_NONE;
-    std::vector<std::unique_ptr<Desc<specpv_kv>>> d(nl);
-    std::vector<const specpv_kv *> kv(nl);
-    std::vector<void *> bk(nl), bv(nl), kx(nl), kn(nl);
-    std::vector<specpv_lists> ls(nl);
+    const std::unique_ptr<Desc<specpv_kv>[]> d(new Desc<specpv_kv>[nl]);
+    const specpv_kv *kv[SPECPV_MAX_LAYERS];
+    void *bk[SPECPV_MAX_LAYERS], *bv[SPECPV_MAX_LAYERS], *kx[SPECPV_MAX_LAYERS], *kn[SPECPV_MAX_LAYERS];
+    specpv_lists ls[SPECPV_MAX_LAYERS];
     for (Py_ssize_t l = 0; l < nl; ++l) {
-        d[l] = std::make_unique<Desc<specpv_kv>>(kvs[l]);
-        if (!*d[l]) Py_RETURN_NONE;
-        kv[l] = d[l]->get();
+        d[l].open(kvs[l]);
+        if (!d[l]) Py_RETURN_NONE;
+        kv[l] = d[l].get();
         const specpv_kv *k0 = kv[0];
         if (!tensor(bks[l], scalar(k0), {k0->batch, (int64_t)cap + mt, k0->n_kv_heads, k0->head_dim}, &bk[l]) ||
             !tensor(bvs[l], scalar(k0), {k0->batch, (int64_t)cap + mt, k0->n_kv_heads, k0->head_dim}, &bv[l]))
@@ -322,8 +324,8 @@ PyObject *commit_layers(PyObject *, PyObject *const *a, Py_ssize_t n)
     void *st = stream();
     return enter([&] {
         return fn<decltype(&specpv_commit_accepted_layers)>(kCommitLayers)(
-            kv.data(), bk.data(), bv.data(), (int32_t)nl, cap, mt, (int32_t *)np_, (int32_t *)ac, (int32_t *)na, (int32_t)max_accept, (specpv_mode)mode,
-            sums ? kx.data() : nullptr, sums ? kn.data() : nullptr, with_lists ? ls.data() : nullptr, (int32_t *)dr, ws, wb, st);
+            kv, bk, bv, (int32_t)nl, cap, mt, (int32_t *)np_, (int32_t *)ac, (int32_t *)na, (int32_t)max_accept, (specpv_mode)mode,
+            sums ? kx : nullptr, sums ? kn : nullptr, with_lists ? ls : nullptr, (int32_t *)dr, ws, wb, st);
     });
 }
 
