@@ -412,11 +412,10 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             int64_t c = (8 * cus + base - 1) / base;
             if (c > 64) c = 64;
             while (c > ns && (chunks + c - 1) / c < 64) --c;
-            // (what fits the static array still does)
-            auto in_static = [&](int64_t n) {
-                const AttnPlan x{(int)n, plan.kind, plan.tg, 0};
-                return (taking ? static_need(s, x) : layout_workspace(s, x, nullptr).need) <= (size_t)array;
-            };
+            // Each round of workgroups starts and ends for itself: where the splits in hand have partials of 16 MiB or less, no more than
+            // stay so.  128 of 16K, 2 KV heads, 24 nodes, refreshed, two splits / four / eight: equal lengths 351-360 / 370 / 376 us, 1/128 to
+            // 128/128 of it 241 / 235 / 235.  (It is also what the static entry point was taken by.)
+            auto in_static = [&](int64_t n) { return static_need(s, AttnPlan{(int)n, plan.kind, plan.tg, 0}) <= (size_t)SPECPV_STATIC_SCRATCH_BYTES; };
             if (in_static(ns))
                 while (c > ns && !in_static(c)) --c;
             c = at_hand(c);
