@@ -414,10 +414,16 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             while (c > ns && (chunks + c - 1) / c < 64) --c;
             // Each round of workgroups starts and ends for itself: where the splits in hand have partials of 16 MiB or less, no more than
             // stay so.  128 of 16K, 2 KV heads, 24 nodes, refreshed, two splits / four / eight: equal lengths 351-360 / 370 / 376 us, 1/128 to
-            // 128/128 of it 241 / 235 / 235.  (It is also what the static entry point was taken by.)
-            auto in_static = [&](int64_t n) { return static_need(s, AttnPlan{(int)n, plan.kind, plan.tg, 0}) <= (size_t)SPECPV_STATIC_SCRATCH_BYTES; };
-            if (in_static(ns))
-                while (c > ns && !in_static(c)) --c;
+            // 128/128 of it 241 / 235 / 235.
+            // What has room in the static array of the entry point that has one still does.
+            for (const size_t room : {(size_t)SPECPV_STATIC_SCRATCH_BYTES, (size_t)array}) {
+                auto in = [&](int64_t n) {
+                    const AttnPlan x{(int)n, plan.kind, plan.tg, 0};
+                    return (taking || room < (size_t)array ? static_need(s, x) : layout_workspace(s, x, nullptr).need) <= room;
+                };
+                if (!in(ns)) continue;
+                while (c > ns && !in(c)) --c;
+            }
             c = at_hand(c);
             if (c > ns) plan.nsplit = (int)c;
         }
