@@ -376,22 +376,33 @@ __device__ __forceinline__ void stream_store16(void *p, uint4 v)
 // A workgroup brings U passes of 4 KiB of K and as many of V: small pieces, because what costs time is the chain of
 // length, count, index, rows and stores, which many workgroups overlap.  The first workgroup of a sequence works out the
 // sequence's gathered length instead (a launch to clear it and atomics before).  Per call at 64 blocks of 64 tokens and
-// eight KV heads 12.8 -> 9.8 us, 33.6 MB read and written; one and four passes of 4 KiB: 9.8, 9.4 (eight sequences of
-// 32K: 49.7, 50.9 against 48.5 with two).
+// eight KV heads 12.8 -> 9.8 us, 33.6 MB read and written (passes of a workgroup: launch_gather).
+// List entry, count and length are requested together, out of the leading arguments, which arrive in registers: no trip for the
+// arguments in front of it and none for the length, and no division.  A layer in a graph, 8 KV heads of 128 channels, 32 blocks of 64
+// 6.10 -> 5.48 us, 100 of 32 7.50 -> 7.08, 64 of 16 5.20 -> 4.70; 2 heads, 64 of 64 3.82 -> 3.50.  in_turn: the length first (launch_gather).
 template <typename T, int D, int U>
-__global__ __launch_bounds__(256) void gather_blocks_kernel(Shape s, const int32_t *sel_idx, const int32_t *sel_count,
-                                                            int n_sel, int parts, T *out_k, T *out_v, int32_t *out_len)
+__global__ __launch_bounds__(256) void gather_blocks_kernel(const int32_t *sel_idx, const int32_t *sel_count, const int32_t *a_ctx_len, int n_sel, int a_Hkv,
+                                                            uint32_t parts_mul, uint32_t parts_shift, uint32_t parts, int in_turn, Shape s, FastDiv div_B, T *out_k, T *out_v,
+                                                            int32_t *out_len)
 {
+    s.ctx_len = a_ctx_len; s.Hkv = a_Hkv;
     constexpr int E = Elem<T>::kPerVec;
     constexpr int LPR = D / E;
     constexpr int RPP = 256 / LPR;
     const int g = blockIdx.y, b = blockIdx.z;
-    // every argument in one trip to memory; left to itself the compiler asks for each where it is first used (four layers of
-    // 128 k tokens, 4 k of them copied: 34.7 us, now 33.9)
-    asm volatile("" :: "s"(s.k), "s"(s.v), "s"(s.sb), "s"(s.sh), "s"(s.st), "s"(s.ctx_len), "s"(s.Hkv), "s"(s.B), "s"(s.max_blocks), "s"(sel_idx),
-                 "s"(sel_count), "s"(n_sel), "s"(parts), "s"(out_k), "s"(out_v));
-    const int L = s.ctx_len[b];
-    int nb = L > 0 ? (L + s.B - 1) / s.B : 0;
+    const int at = max((int)blockIdx.x - 1, 0), slot = (int)FastDiv{parts_mul, parts_shift, parts}.div_straight((uint32_t)at), r0 = (at - slot * (int)parts) * U * RPP;
+    // (vector loads: a scalar one would be waited for together with the arguments)
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    const int64_t bg = (int64_t)b * s.Hkv + g;
+    const int L_v = s.ctx_len[b + zero];
+    if (in_turn) asm volatile("" :: "s"(__builtin_amdgcn_readfirstlane(L_v)));
+    const int cnt_v = sel_count[bg + zero], entry_v = sel_idx[bg * n_sel + slot + zero];
+    // every other argument in one trip to memory; left to itself the compiler asks for each where it is first used
+    asm volatile("" :: "s"(s.k), "s"(s.v), "s"(s.sb), "s"(s.sh), "s"(s.st), "s"(s.B), "s"(s.max_blocks), "s"(div_B.mul), "s"(div_B.shift), "s"(div_B.d), "s"(out_k),
+                 "s"(out_v));
+    const int L = __builtin_amdgcn_readfirstlane(L_v);
+    int nb = L > 0 ? (int)div_B.div_straight((uint32_t)L + (uint32_t)s.B - 1u) : 0;
     if (nb > s.max_blocks) nb = s.max_blocks;
     if (blockIdx.x == 0) {
         if (g || !out_len) return;
@@ -410,9 +421,7 @@ __global__ __launch_bounds__(256) void gather_blocks_kernel(Shape s, const int32
         if (threadIdx.x == 0) out_len[b] = max(max(most[0], most[1]), max(most[2], most[3]));
         return;
     }
-    const int slot = (blockIdx.x - 1) / parts, r0 = ((blockIdx.x - 1) % parts) * U * RPP;
-    const int blk_in_row = sel_idx[((int64_t)b * s.Hkv + g) * n_sel + slot];   // requested along with the count
-    const int blk = slot < sel_count[(int64_t)b * s.Hkv + g] ? blk_in_row : -1;
+    const int blk = slot < __builtin_amdgcn_readfirstlane(cnt_v) ? __builtin_amdgcn_readfirstlane(entry_v) : -1;
     const bool valid = blk >= 0 && blk < nb;
     const int c = threadIdx.x % LPR, rsub = threadIdx.x / LPR;
     const int64_t src0 = (int64_t)b * s.sb + (int64_t)g * s.sh + c * E;
@@ -441,19 +450,33 @@ __global__ __launch_bounds__(256) void gather_blocks_kernel(Shape s, const int32
 hipError_t launch_gather(const Shape &s, int dtype, const int32_t *sel_idx, const int32_t *sel_count, int n_sel,
                          void *out_k, void *out_v, int32_t *out_len, hipStream_t st)
 {
-    constexpr int U = 2;
-    const int rows = U * 256 * 16 / (s.D * (dtype == SPECPV_BF16 ? 2 : 4));   // of a block, per workgroup
+    const int pass = 256 * 16 / (s.D * (dtype == SPECPV_BF16 ? 2 : 4));   // rows of a pass
+    const int64_t cus = device_cu_count();
+    auto workgroups = [&](int u) { return (int64_t)((s.B + u * pass - 1) / (u * pass)) * n_sel * s.Hkv * s.batch; };
+    // Four passes where those make one to two workgroups a CU: nothing is left to follow them, and each has twice the reads under way.  8 KV
+    // heads, 64 blocks of 64, two / four: 8.36 / 7.65 us (4.3 TB/s); fewer workgroups leave CUs idle (2 heads 3.50 / 4.17), more of them
+    // cover each other's trips (two sequences 13.3 / 13.8, eight 47 / 49; fp32 13.3 / 13.9).
+    const bool four = workgroups(4) > cus && workgroups(4) <= 2 * cus;
+    const int rows = (four ? 4 : 2) * pass;   // of a block, per workgroup
     const int parts = (s.B + rows - 1) / rows;
     if (s.batch > 65535 || s.Hkv > 65535 || (int64_t)n_sel * parts >= (1 << 30)) return hipErrorInvalidConfiguration;   // before anything is enqueued
+    // More workgroups than have a place at once hide the length's trip, and with their requests spread out the chip's reads and writes
+    // interfere less.  Together / the length first: four sequences of 8 heads, 64 blocks of 64, 24.9 / 24.5 us, sixteen 92.6 / 91.5 (5.9
+    // TB/s), in blocks of 16 23.7 / 23.0; two (as many as have a place) 13.3 / 13.5.
+    const int in_turn = workgroups(2) > 8 * cus;
+    const FastDiv div_parts = make_fastdiv((uint32_t)parts);
     const dim3 grid(1 + n_sel * parts, s.Hkv, s.batch);
-#define SPECPV_GATHER(T, DD) \
-    hipLaunchKernelGGL((gather_blocks_kernel<T, DD, U>), grid, dim3(256), 0, st, s, sel_idx, sel_count, n_sel, parts, (T *)out_k, (T *)out_v, out_len)
+#define SPECPV_GATHER_U(T, DD, U) \
+    hipLaunchKernelGGL((gather_blocks_kernel<T, DD, U>), grid, dim3(256), 0, st, sel_idx, sel_count, s.ctx_len, n_sel, s.Hkv, div_parts.mul, div_parts.shift, div_parts.d, in_turn, s, \
+                       make_fastdiv((uint32_t)s.B), (T *)out_k, (T *)out_v, out_len)
+#define SPECPV_GATHER(T, DD) do { if (four) SPECPV_GATHER_U(T, DD, 4); else SPECPV_GATHER_U(T, DD, 2); } while (0)
     if (dtype == SPECPV_BF16) {
         if (s.D == 128) SPECPV_GATHER(bf16_t, 128); else SPECPV_GATHER(bf16_t, 64);
     } else {
         if (s.D == 128) SPECPV_GATHER(float, 128); else SPECPV_GATHER(float, 64);
     }
 #undef SPECPV_GATHER
+#undef SPECPV_GATHER_U
     return hipGetLastError();
 }
 
