@@ -379,12 +379,24 @@ __device__ __forceinline__ void stream_store16(void *p, uint4 v)
 // eight KV heads 12.8 -> 9.8 us, 33.6 MB read and written (passes of a workgroup: launch_gather).
 // List entry, count and length are requested together, out of the leading arguments, which arrive in registers: no trip for the
 // arguments in front of it and none for the length, and no division.  A layer in a graph, 8 KV heads of 128 channels, 32 blocks of 64
-// 6.10 -> 5.48 us, 100 of 32 7.50 -> 7.08, 64 of 16 5.20 -> 4.70; 2 heads, 64 of 64 3.82 -> 3.50.  in_turn: the length first (launch_gather).
+// 6.10 -> 5.48 us, 100 of 32 7.50 -> 7.08, 64 of 16 5.20 -> 4.70; 2 heads, 64 of 64 3.82 -> 3.50.  shift_in_turn: + 32, the length first
+// (launch_gather).  What need not arrive in registers is one argument: fifteen of them cost the host 0.3 us a launch.
+struct GatherArgs {
+    Shape s;
+    FastDiv div_B;
+    void *k, *v;
+    int32_t *len;
+};
 template <typename T, int D, int U>
 __global__ __launch_bounds__(256) void gather_blocks_kernel(const int32_t *sel_idx, const int32_t *sel_count, const int32_t *a_ctx_len, int n_sel, int a_Hkv,
-                                                            uint32_t parts_mul, uint32_t parts_shift, uint32_t parts, int in_turn, Shape s, FastDiv div_B, T *out_k, T *out_v,
-                                                            int32_t *out_len)
+                                                            uint32_t parts_mul, uint32_t parts, int shift_in_turn, GatherArgs a)
 {
+    Shape s = a.s;
+    const FastDiv div_B = a.div_B;
+    T *const out_k = (T *)a.k, *const out_v = (T *)a.v;
+    int32_t *const out_len = a.len;
+    const uint32_t parts_shift = (uint32_t)shift_in_turn & 31u;
+    const bool in_turn = shift_in_turn & 32;
     s.ctx_len = a_ctx_len; s.Hkv = a_Hkv;
     constexpr int E = Elem<T>::kPerVec;
     constexpr int LPR = D / E;
@@ -463,12 +475,12 @@ hipError_t launch_gather(const Shape &s, int dtype, const int32_t *sel_idx, cons
     // More workgroups than have a place at once hide the length's trip, and with their requests spread out the chip's reads and writes
     // interfere less.  Together / the length first: four sequences of 8 heads, 64 blocks of 64, 24.9 / 24.5 us, sixteen 92.6 / 91.5 (5.9
     // TB/s), in blocks of 16 23.7 / 23.0; two (as many as have a place) 13.3 / 13.5.
-    const int in_turn = workgroups(2) > 8 * cus;
     const FastDiv div_parts = make_fastdiv((uint32_t)parts);
+    const int shift_in_turn = (int)div_parts.shift | (workgroups(2) > 8 * cus ? 32 : 0);
+    const GatherArgs a{s, make_fastdiv((uint32_t)s.B), out_k, out_v, out_len};
     const dim3 grid(1 + n_sel * parts, s.Hkv, s.batch);
 #define SPECPV_GATHER_U(T, DD, U) \
-    hipLaunchKernelGGL((gather_blocks_kernel<T, DD, U>), grid, dim3(256), 0, st, sel_idx, sel_count, s.ctx_len, n_sel, s.Hkv, div_parts.mul, div_parts.shift, div_parts.d, in_turn, s, \
-                       make_fastdiv((uint32_t)s.B), (T *)out_k, (T *)out_v, out_len)
+    hipLaunchKernelGGL((gather_blocks_kernel<T, DD, U>), grid, dim3(256), 0, st, sel_idx, sel_count, s.ctx_len, n_sel, s.Hkv, div_parts.mul, div_parts.d, shift_in_turn, a)
 #define SPECPV_GATHER(T, DD) do { if (four) SPECPV_GATHER_U(T, DD, 4); else SPECPV_GATHER_U(T, DD, 2); } while (0)
     if (dtype == SPECPV_BF16) {
         if (s.D == 128) SPECPV_GATHER(bf16_t, 128); else SPECPV_GATHER(bf16_t, 64);
