@@ -379,8 +379,8 @@ __device__ __forceinline__ void stream_store16(void *p, uint4 v)
 // eight KV heads 12.8 -> 9.8 us, 33.6 MB read and written (passes of a workgroup: launch_gather).
 // List entry, count and length are requested together, out of the leading arguments, which arrive in registers: no trip for the
 // arguments in front of it and none for the length, and no division.  A layer in a graph, 8 KV heads of 128 channels, 32 blocks of 64
-// 6.10 -> 5.48 us, 100 of 32 7.50 -> 7.08, 64 of 16 5.20 -> 4.70; 2 heads, 64 of 64 3.82 -> 3.50.  shift_in_turn: + 32, the length first
-// (launch_gather).  What need not arrive in registers is one argument: fifteen of them cost the host 0.3 us a launch.
+// 6.10 -> 5.48 us, 100 of 32 7.50 -> 7.08, 64 of 16 5.20 -> 4.70 (those with the length's workgroup as it was); 2 heads, 64 of 64 3.82 -> 3.50.  shift_in_turn: + 32, the length first
+// (launch_gather).  What need not arrive in registers is one argument (as one each, fifteen in all, two layers of ten blocks of 64, which the host bounds, 9.2 us, so 8.55).
 struct GatherArgs {
     Shape s;
     FastDiv div_B;
@@ -418,12 +418,24 @@ __global__ __launch_bounds__(256) void gather_blocks_kernel(const int32_t *sel_i
     if (nb > s.max_blocks) nb = s.max_blocks;
     if (blockIdx.x == 0) {
         if (g || !out_len) return;
+        // a wavefront takes every fourth head, four of them and 64 entries of each at a time, counts and entries together: head by head and
+        // count by count this workgroup was what a small gather waited for: a layer in a graph, 8 KV heads of 128 channels, 13 blocks of 64 3.90 -> 3.28 us,
+        // 32 5.48 -> 4.97, 64 of 16 4.71 -> 3.81
         int rows = 0;
-        for (int h = 0; h < s.Hkv; ++h) {
-            const int cnt = min(sel_count[(int64_t)b * s.Hkv + h], n_sel);
-            for (int slot = threadIdx.x; slot < cnt; slot += 256) {
-                const int blk = sel_idx[((int64_t)b * s.Hkv + h) * n_sel + slot];
-                if (blk >= 0 && blk < nb) rows = max(rows, slot * s.B + min(s.B, L - blk * s.B));   // token rows up to and including this block
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        for (int h0 = wave; h0 < s.Hkv; h0 += 16) {
+            for (int slot0 = 0; slot0 < n_sel; slot0 += 64) {
+                const int slot_e = slot0 + lane;
+                int cnt[4], entry[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int64_t row = (int64_t)b * s.Hkv + min(h0 + 4 * u, s.Hkv - 1);   // (past the last head: that one again)
+                    cnt[u] = sel_count[row + zero];
+                    entry[u] = sel_idx[row * n_sel + min(slot_e, n_sel - 1)];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)   // token rows up to and including this block
+                    if (slot_e < min(cnt[u], n_sel) && entry[u] >= 0 && entry[u] < nb) rows = max(rows, slot_e * s.B + min(s.B, L - entry[u] * s.B));
             }
         }
         __shared__ int most[4];
