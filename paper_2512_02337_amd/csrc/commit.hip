@@ -373,6 +373,13 @@ __device__ __forceinline__ void stream_store16(void *p, uint4 v)
     __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, v), (u32x4_t *)p);
 }
 
+struct GatherArgs {
+    Shape s;
+    FastDiv div_B;
+    void *k, *v;
+    int32_t *len;
+};
+
 // A workgroup brings U passes of 4 KiB of K and as many of V: small pieces, because what costs time is the chain of
 // length, count, index, rows and stores, which many workgroups overlap.  The first workgroup of a sequence works out the
 // sequence's gathered length instead (a launch to clear it and atomics before).  Per call at 64 blocks of 64 tokens and
@@ -381,12 +388,6 @@ __device__ __forceinline__ void stream_store16(void *p, uint4 v)
 // arguments in front of it and none for the length, and no division.  A layer in a graph, 8 KV heads of 128 channels, 32 blocks of 64
 // 6.10 -> 5.48 us, 100 of 32 7.50 -> 7.08, 64 of 16 5.20 -> 4.70 (those with the length's workgroup as it was); 2 heads, 64 of 64 3.82 -> 3.50.  shift_in_turn: + 32, the length first
 // (launch_gather).  What need not arrive in registers is one argument (as one each, fifteen in all, two layers of ten blocks of 64, which the host bounds, 9.2 us, so 8.55).
-struct GatherArgs {
-    Shape s;
-    FastDiv div_B;
-    void *k, *v;
-    int32_t *len;
-};
 template <typename T, int D, int U>
 __global__ __launch_bounds__(256) void gather_blocks_kernel(const int32_t *sel_idx, const int32_t *sel_count, const int32_t *a_ctx_len, int n_sel, int a_Hkv,
                                                             uint32_t parts_mul, uint32_t parts, int shift_in_turn, GatherArgs a)
