@@ -3,6 +3,7 @@
 // The summary kernel calls it, and so do workgroups of a full pass that recomputes them (attn_mfma.hip).
 #pragma once
 #include "internal.h"
+#include "rows.h"
 #include <type_traits>
 #ifndef SPECPV_SUM_UNR
 #define SPECPV_SUM_UNR 16
@@ -103,7 +104,7 @@ __device__ __forceinline__ void summarize_block(const Shape &s, int b, int g, in
 }
 
 // Blocks of N passes of RPP rows, fewer than UNR: as many blocks as have UNR passes together, i0 and those behind it up to `end`,
-// their rows all under way at once.
+// their rows all under way at once.  Rows of blocks that are not there, or behind the last token, are the last row once more.
 template <typename T, int D, int N>
 __device__ __forceinline__ void summarize_small(const Shape &s, int b, int g, int i0, int end, int L, void *kmax, void *kmin, int lane)
 {
@@ -112,7 +113,7 @@ __device__ __forceinline__ void summarize_small(const Shape &s, int b, int g, in
     const T *base = (const T *)s.k + (int64_t)b * s.sb + (int64_t)g * s.sh + c * E;
     uint4 u[UNR];
 #pragma unroll
-    for (int x = 0; x < UNR; ++x) u[x] = load_stream((const uint4 *)(base + (int64_t)min(t0 + x * RPP + rsub, L - 1) * s.st));
+    for (int x = 0; x < UNR; ++x) u[x] = load_stream((const uint4 *)(base + (int64_t)row_below(t0 + x * RPP + rsub, L, end, N * RPP) * s.st));
     const int64_t o = (((int64_t)b * s.Hkv + g) * s.max_blocks + i0) * D;
 #pragma unroll
     for (int j = 0; j < UNR / N; ++j) {

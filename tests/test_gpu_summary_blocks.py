@@ -73,3 +73,39 @@ def test_small_blocks_on_the_side(gpu_lib, ctx, B, M, Hq, Hkv, part):
     assert torch.equal(run.sel_idx, want[2]) and torch.equal(run.sel_count, want[3])
     # another number of splits: a unit in the last place of a bf16 value at most (test_gpu_side_summaries.py)
     assert ((run.out.float() - want[4].float()).abs() <= 2.0 ** -7 * want[4].float().abs() + 1e-3).all()
+
+
+@pytest.mark.parametrize("dt,D,B", [(torch.bfloat16, 128, 16), (torch.bfloat16, 128, 32), (torch.bfloat16, 64, 16), (torch.float32, 64, 16)])
+@pytest.mark.parametrize("short", [1, 2, 3])
+def test_sequences_longer_than_the_cache_has_blocks(gpu_lib, dt, D, B, short):
+    """The summaries of the blocks that are there, and nothing behind them."""
+    say("case", dt, D, B, short)
+    Hkv, all_blocks = 8, 1032
+    nb = all_blocks - short
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    k = torch.randn((1, Hkv, all_blocks * B, D), generator=gen, device="cuda", dtype=dt)
+    k[:, :, nb * B:] = float("nan")
+    kv = gpu_lib.KV(k, k, torch.tensor([all_blocks * B], dtype=torch.int32, device="cuda"), B, nb)
+    mx = torch.full((1, Hkv, all_blocks, D), -7.0, dtype=dt, device="cuda")   # (the kernel's arrays are its first nb * Hkv rows)
+    mn = torch.full_like(mx, -7.0)
+    gpu_lib.specpv_block_summarize(kv, 0, -1, mx.view(-1)[:Hkv * nb * D].view(1, Hkv, nb, D), mn.view(-1)[:Hkv * nb * D].view(1, Hkv, nb, D))
+    torch.cuda.synchronize()
+    rows = k[:, :, :nb * B].view(1, Hkv, nb, B, D)
+    assert torch.equal(mx.view(-1)[:Hkv * nb * D].view(1, Hkv, nb, D), rows.amax(3)) and torch.equal(mn.view(-1)[:Hkv * nb * D].view(1, Hkv, nb, D), rows.amin(3))
+    assert (mx.view(-1)[Hkv * nb * D:] == -7.0).all() and (mn.view(-1)[Hkv * nb * D:] == -7.0).all()
+
+
+@pytest.mark.parametrize("B,short", [(16, 1), (16, 2), (16, 3), (32, 1)])
+def test_side_summaries_of_sequences_longer_than_the_cache(gpu_lib, B, short):
+    say("case", B, short)
+    cfg = dict(SMALL)
+    cfg.update(ctx=[30000], B=B, M=60, Hq=32, Hkv=8, k=20, rho=[0.1])
+    case = workloads.make_case(cfg, seed=59, device=torch.device("cuda"))
+    nb = case["max_blocks"] // 4 * 4 - short
+    case = dict(case, max_blocks=nb)
+    run = GpuRun(gpu_lib, case)
+    run.kv = gpu_lib.KV(run.k, run.v, case["ctx_len"], B, nb)
+    run.refresh(0)
+    torch.cuda.synchronize()
+    rows = case["k"][:, :, :nb * B].view(1, 8, nb, B, -1)
+    assert torch.equal(run.kmax, rows.amax(3)) and torch.equal(run.kmin, rows.amin(3))
