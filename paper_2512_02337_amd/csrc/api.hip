@@ -127,8 +127,9 @@ struct AttnCost {
         // (pairs that are a multiple of 8 stay on their XCD)
         const int64_t rounds = bg % 8 ? (bg * tiles * ns + cus - 1) / cus : (bg / 8 * tiles * ns + cus / 8 - 1) / (cus / 8);
         const int64_t p = (chunks + ns * tg - 1) / (ns * tg);
-        return us(rounds, p, tg == 2 ? 2.03 : (tg == 4 ? 1.59 : 1.67), tg == 2 ? 0.97 : (tg == 4 ? 1.50 : 2.13), tiles, ns);
+        return us(rounds, p, tg == 2 ? 2.03 : (tg == 4 ? 1.59 : 1.67), tile_chunk_us(tg), tiles, ns);
     }
+    static double tile_chunk_us(int tg) { return tg == 2 ? 0.97 : (tg == 4 ? 1.50 : 2.13); }
     // the group kernel (attn_mfma.hip)
     double group(int parts, int blocks, int64_t ns, int64_t cus) const
     {
@@ -141,6 +142,18 @@ struct AttnCost {
         const double pairs = (double)s.batch * s.Hkv, p = pairs * (double)chunks / (double)wgs;
         const double chain = 3.11 + p * attn_group_chunk_us(blocks) * (double)parts * (double)wgs / (double)device_cu_count(), memory = kv * (0.02 * (double)parts + 0.115);
         return sqrt(chain * chain + memory * memory) + 0.199 * ((double)wgs + pairs) * s.M * s.G * 512e-6 + 6.0;
+    }
+    // Whether splits of `p` chunks, `chunk_us` each, hold up against `wgs` shares when the lengths differ as much as they may: one
+    // sequence with all the chunks, the others with a sixteenth.  A split's chain stays what it was; the shares' chain is cut to the
+    // chunks that there are, but then the long sequence has most of the shares, and its combine takes them in rounds, a tenth of a
+    // microsecond each.  For 94 shapes (2 to 32 sequences, 1 to 8 KV heads, 1 to 60 nodes, 1 K to 64 K tokens) with the splits that the
+    // costs above choose, the chain that splits have more over the shares of the long pair, against the slowest of equal lengths, 1 / n
+    // to n / n, one long first and one long last, splits / shares: up to 0.09 us a share (41 shapes) 1.02 at most, 0.82 in the mean;
+    // 0.1 to 0.2: 0.9 to 1.38; 0.2 to 0.5: up to 1.44; beyond: up to 1.55.
+    bool splits_hold(double p, double chunk_us, int blocks, int64_t wgs) const
+    {
+        const double of_share = (double)s.Hkv * (double)chunks * (1.0 + (double)(s.batch - 1) / 16.0) / (double)wgs, share = of_share < 1.0 ? 1.0 : of_share;
+        return p * chunk_us - share * attn_group_chunk_us(blocks) <= 0.09 * (double)chunks / share;
     }
 };
 
@@ -213,9 +226,6 @@ static size_t static_need(const Shape &s, const AttnPlan &plan)
     const Workspace w = layout_workspace(s, plan, nullptr);
     return plan.stream || half_partials(s, plan.kind) ? w.need : w.total;
 }
-
-// A split of a full pass with no more chunks than these is short enough for sequences of any lengths (plan_attention).
-constexpr int64_t kShortSplit = 48;
 
 // Which kernel the context part of the attention runs on and how many KV splits it uses when
 // it covers n_blocks blocks per (sequence, KV head).  Host-only and deterministic in its
@@ -305,6 +315,13 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
         const int64_t chunks = (tokens + 31) / 32;   // 32-token chunks per (sequence, KV head)
         const int parts = attn_group_parts(s);
         const int64_t base = (int64_t)s.batch * s.Hkv * parts;   // group kernel: workgroups per split
+        // ... and workgroups of equal shares (below): one a CU; for few rows, which leave room for it, two, eight chunks or more each
+        const bool two = taking ? s.D == 64 : attn_group_blocks(s) <= 2;
+        int64_t shares = cus * (two ? 2 : 1) / parts;
+        if (shares > (int64_t)s.batch * s.Hkv * chunks / 8) shares = (int64_t)s.batch * s.Hkv * chunks / 8;
+        if (shares < 1) shares = 1;
+        const AttnCost cost(s, chunks);
+        const int blocks = attn_group_blocks(s);
         int64_t ns = 1;
         bool keep_static = false;
         if (s.D == 64) {
@@ -337,19 +354,17 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
                 }
             }
         } else {
-            const AttnCost cost(s, chunks);
-            const int blocks = attn_group_blocks(s);
             // AttnCost takes every sequence to be as long as the longest.  The group kernel, below, evens out the lengths of
             // a full pass; the tile kernel, which a few nodes may be faster with, does not.  24 nodes at G = 4, 16 sequences
             // of 16K (512 chunks), 8 KV heads, tile kernel against shares: equal lengths 203 / 209 us, 1/16 to 16/16 of it
             // 159 / 124, one long and fifteen short ones 144 / 47; four sequences of 258 chunks: 37 / 43, 34 / 34, 30 / 25.
-            // Few pairs take the tile kernel where its ranges are short: 30000 + 15000 tokens, 2 KV heads, 37 nodes at G = 8 37.5 us,
-            // the group kernel 43.7, shares 44.8; with 32 pairs, 6K to 25K tokens, 18 nodes at G = 5 71.8 / 58.1 / 60.4.
-            const bool uneven = full && s.batch > 1 && chunks > 256, small = (int64_t)s.batch * s.Hkv <= 8;
+            // Few pairs take it where its ranges are so short that shares gain nothing (splits_hold): 30000 + 15000 tokens, 2 KV heads, 37
+            // nodes at G = 8 37.5 us, the group kernel 43.7, shares 44.8; with 32 pairs, 6K to 25K tokens, 18 nodes at G = 5 71.8 / 58.1 / 60.4.
+            const bool uneven = full && s.batch > 1 && chunks > 256, small = !taking && (int64_t)s.batch * s.Hkv <= 8;
             double best = -1.0, best_tile = -1.0;
             int64_t ns_tile = 1;
             auto take = [&](double us, int kind, int tg, int64_t c) {
-                if (uneven && kind == kAttnSplit && (taking || !small || chunks > kShortSplit * c * tg)) {
+                if (uneven && kind == kAttnSplit && !(small && cost.splits_hold((double)((chunks + c * tg - 1) / (c * tg)), AttnCost::tile_chunk_us(tg), blocks, shares))) {
                     if (best_tile < 0.0 || us < best_tile) { best_tile = us; ns_tile = c; }
                 } else if (best < 0.0 || us < best) {
                     best = us; plan.kind = kind; plan.tg = tg; ns = c;
@@ -370,26 +385,22 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             if (keep_static && ns > static_splits()) ns = static_splits();
         }
         plan.nsplit = (int)ns;
-        const int64_t shares = cus * ((s.D == 64 || !taking) && (taking || attn_group_blocks(s) <= 2) ? 2 : 1) / parts;   // workgroups of them
         // The sequences of a batch may differ in length, and the lengths live on the device: for a full pass the group
         // kernel's workgroups take equal shares of all chunks.  (Four times as many splits as fill the chip even that out
         // too, at the price of as many partials: full pass over 32K + 64K + 96K + 128K tokens at G = 5, 64 nodes, attention
         // and combine: 563 us with the splits that fill the chip, 462 with four times as many, 453 with the shares.)  Up to
         // 1024 tokens there is nothing to even out, and little where a split has few chunks: its partials have one place each, where a
         // share's are found by the lengths and merged in rounds.  Shares / splits, us, of equal lengths, 1 / n to n / n, one long and the
-        // others a sixteenth of it, 60 nodes, 8 KV heads: 16 sequences of 3000, G = 5, four splits of 24 chunks 99.5 / 94.3, 91.9 / 69.9,
-        // 49.7 / 48.9, two of 47 99.5 / 83.2, 91.9 / 71.3, 49.7 / 65.7; 16 of 2048, two of 32 77.0 / 64.3, 79.7 / 55.4, 45.5 / 51.4;
-        // 10 of 4096, G = 4, three of 43 69.2 / 58.4, 53.6 / 51.2, 34.2 / 48.2; 2 of 16384, 16 of 32 50.8 / 46.8, 44.9 / 44.2, 39.9 / 38.3.
+        // others a sixteenth of it.  Splits: 3 sequences of 7055, 37 nodes, 4 KV heads, 21 of 11 chunks 34 / 28, 31 / 26, 28 / 27; 2 of 57746,
+        // 24 nodes at G = 8, 2 heads, 64 of 29 chunks 52 / 43, 46 / 41, 44 / 39.  Shares: 60 nodes, 8 heads, 16 of 3000 at G = 5, two of 47
+        // 99 / 83, 92 / 71, 50 / 66; 10 of 4096, three of 43 69 / 58, 54 / 51, 34 / 48; 4 of 8192, eight of 32 60 / 58, 50 / 52, 39 / 46.
         // 64 channels, where a chunk has less to do, 37 nodes: two sequences of 15005 and 30011, 32 splits 52.4 / 48.9; four of 8192 by
         // quarters 32.8 / 32.1; 16 by sixteenths of 3000 45.4 / 42.2.
-        // (and, 128 channels, where the splits don't cost another round: 11 sequences of 5855, 37 nodes, shares 72.5, five splits 76.5)
-        const bool short_splits = !taking && (s.D == 64 ? chunks <= 32 * ns : chunks <= kShortSplit * ns && AttnCost(s, chunks).group(parts, attn_group_blocks(s), ns, cus) <
-                                                                                  AttnCost(s, chunks).shares(parts, attn_group_blocks(s), shares < 1 ? 1 : shares));
+        const bool short_splits = !taking && (s.D == 64 ? chunks <= 32 * ns : cost.group(parts, blocks, ns, cus) < cost.shares(parts, blocks, shares) &&
+                                                                               cost.splits_hold((double)((chunks + ns - 1) / ns), attn_group_chunk_us(blocks), blocks, shares));
         if (full && s.batch > 1 && s.batch <= 64 && plan.kind == kAttnGroup && chunks > 32 && !short_splits && (int64_t)s.batch * s.Hkv * chunks < ((int64_t)1 << 30)) {
             const int64_t pairs = (int64_t)s.batch * s.Hkv, R = (int64_t)s.M * s.G;
             int64_t wgs = shares;
-            if (wgs > pairs * chunks / 8) wgs = pairs * chunks / 8;   // eight chunks or more each
-            if (wgs < 1) wgs = 1;
             const int64_t static_slots = (array - static_fixed) / (R * (int64_t)row_bytes) - pairs;
             if (keep_static && wgs > static_slots && static_slots >= wgs / 2) wgs = static_slots;
             // the workspace of as many splits as hold that many slots
