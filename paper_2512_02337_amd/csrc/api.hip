@@ -315,8 +315,10 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
         const int64_t chunks = (tokens + 31) / 32;   // 32-token chunks per (sequence, KV head)
         const int parts = attn_group_parts(s);
         const int64_t base = (int64_t)s.batch * s.Hkv * parts;   // group kernel: workgroups per split
-        // ... and workgroups of equal shares (below): one a CU; for few rows, which leave room for it, two, eight chunks or more each
-        const bool two = taking ? s.D == 64 : attn_group_blocks(s) <= 2;
+        // ... and workgroups of equal shares (below): one a CU, for few rows, which leave room for it, two, eight chunks or more each.  Two
+        // only where a pair can get no more than 64 of them: one long sequence of a few heads has most of them merged for itself.  One /
+        // two, equal lengths and one long: 8 heads, one node, 4 of 32K 115 / 97, 44 / 41 us; one head, 24 of 22K 62 / 56, 27.5 / 30.4.
+        const bool two = taking ? s.D == 64 : attn_group_blocks(s) <= 2 && (s.D == 64 || 2 * cus <= 64 * (int64_t)s.Hkv);
         int64_t shares = cus * (two ? 2 : 1) / parts;
         if (shares > (int64_t)s.batch * s.Hkv * chunks / 8) shares = (int64_t)s.batch * s.Hkv * chunks / 8;
         if (shares < 1) shares = 1;

@@ -49,3 +49,9 @@ def test_shares_where_one_long_sequence_would_wait_for_itself(batch, Hkv, G, M, 
 @pytest.mark.parametrize("batch,Hkv,G,M,ctx", [(3, 4, 4, 37, 7055), (2, 2, 8, 24, 57746), (16, 1, 8, 37, 4710), (2, 2, 8, 37, 30000)])
 def test_splits_where_their_chains_are_short(batch, Hkv, G, M, ctx):
     assert splits_asked_for(batch, Hkv, G, M, ctx) > room_of_shares(batch, Hkv, G, M, 256)
+
+
+@cpu_only
+@pytest.mark.parametrize("batch,Hkv,G,M,ctx,shares", [(16, 1, 4, 8, 36448, 256), (24, 1, 4, 1, 22336, 256), (4, 4, 4, 16, 26752, 256), (4, 8, 4, 1, 32416, 512), (16, 8, 8, 1, 13376, 512)])
+def test_shares_of_few_rows(batch, Hkv, G, M, ctx, shares):
+    assert splits_asked_for(batch, Hkv, G, M, ctx) == room_of_shares(batch, Hkv, G, M, shares)
