@@ -261,16 +261,17 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
     // what specpv_partial_verify_attn_static took with the splits of fp32 partials that a call had at first must fit the
     // array with more of them: no more splits than have room, where those few have in SPECPV_STATIC_SCRATCH_BYTES
     const int64_t static_slot = rows * (s.D + 2) * (int64_t)sizeof(float), static_fixed = (int64_t)kArriveBytes + 1024;
-    auto static_splits = [&]() {
+    auto static_splits = [&](int64_t bytes) {
         const bool half = half_partials(s, plan.kind);
-        return (array - static_fixed) / (half ? rows * (2 * s.D + 8) : static_slot) - (half ? 0 : 1);
+        return (bytes - static_fixed) / (half ? rows * (2 * s.D + 8) : static_slot) - (half ? 0 : 1);
     };
-    auto static_room = [&](auto few_of, int64_t ns) {
-        const int64_t room = static_splits();
+    auto static_room_of = [&](int64_t bytes, auto few_of, int64_t ns) {
+        const int64_t room = static_splits(bytes);
         if (ns <= room || room < 1) return ns;
         const bool few_fit = static_fixed + static_slot * (few_of() + 1) + (int64_t)s.batch * s.Hkv * s.max_blocks * (int64_t)sizeof(float) <= (int64_t)SPECPV_STATIC_SCRATCH_BYTES;
         return few_fit ? room : ns;
     };
+    auto static_room = [&](auto few_of, int64_t ns) { return static_room_of(array, few_of, ns); };
     const int64_t cus = device_cu_count();
     if (plan.kind == kAttnGeneric) {
         // two wavefronts of 32 rows per SIMD, 64 tokens or more each (the few splits up to 1024 tokens, and half that many
@@ -315,16 +316,22 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
         const int64_t chunks = (tokens + 31) / 32;   // 32-token chunks per (sequence, KV head)
         const int parts = attn_group_parts(s);
         const int64_t base = (int64_t)s.batch * s.Hkv * parts;   // group kernel: workgroups per split
-        // ... and workgroups of equal shares (below): one a CU, for few rows, which leave room for it, two, eight chunks or more each.  Two
-        // only where a pair can get no more than 64 of them: one long sequence of a few heads has most of them merged for itself.  One /
+        // ... and workgroups of equal shares (below), eight chunks or more each: one a CU, with 64 channels and for few rows, which leave room
+        // for it, two (64 channels, 60 nodes, 8 heads at G = 5, 24 of 3000, equal and 1 / n to n / n, one / two 176 / 172, 146 / 108 us).  For
+        // few rows of 128 channels only where a pair can get no more than 64 of them: one long sequence of a few heads has most of them merged for itself.  One /
         // two, equal lengths and one long: 8 heads, one node, 4 of 32K 115 / 97, 44 / 41 us; one head, 24 of 22K 62 / 56, 27.5 / 30.4.
-        const bool two = taking ? s.D == 64 : attn_group_blocks(s) <= 2 && (s.D == 64 || 2 * cus <= 64 * (int64_t)s.Hkv);
+        const bool two = s.D == 64 || (!taking && attn_group_blocks(s) <= 2 && 2 * cus <= 64 * (int64_t)s.Hkv);
+        const bool can_share = full && s.batch > 1 && s.batch <= 64;
         int64_t shares = cus * (two ? 2 : 1) / parts;
-        if (shares > (int64_t)s.batch * s.Hkv * chunks / 8) shares = (int64_t)s.batch * s.Hkv * chunks / 8;
+        if (can_share && shares > (int64_t)s.batch * s.Hkv * chunks / 8) shares = (int64_t)s.batch * s.Hkv * chunks / 8;
         if (shares < 1) shares = 1;
         const AttnCost cost(s, chunks);
         const int blocks = attn_group_blocks(s);
-        int64_t ns = 1;
+        // the slots of the shares, the workspace of as many splits as hold those, and whether their partials take more than 16 MiB
+        const int64_t share_bytes = can_share ? (shares + (int64_t)s.batch * s.Hkv) * (int64_t)(pair_rows * row_bytes) + 512 : 0;
+        const int64_t split_bytes = can_share ? rows * (4 * s.D + 8) : 1, share_splits = (share_bytes + split_bytes - 1) / split_bytes > 1 ? (share_bytes + split_bytes - 1) / split_bytes - 1 : 1;
+        const bool many_partials = (int64_t)kArriveBytes + share_bytes > (int64_t)SPECPV_STATIC_SCRATCH_BYTES;
+        int64_t ns = 1, least = 1;
         bool keep_static = false;
         if (s.D == 64) {
             // the group kernel; two workgroups or more have room on a CU, but share what it gives
@@ -333,13 +340,18 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             most = at_hand(static_room([&] { return few; }, most));
             // up to 1024 tokens: the few splits of the vector-ALU kernel are enough
             if (chunks <= 32 && most > few) most = few;
-            if (taking) {
+            // the splits that fill two places a CU
+            auto filling = [&](int64_t at_most) {
                 const int64_t slots = 2 * cus;
-                int64_t best = -1;
-                for (int64_t c = 1; c <= most; ++c) {
+                int64_t best = -1, n = 1;
+                for (int64_t c = 1; c <= at_most; ++c) {
                     const int64_t cost = (base * c + slots - 1) / slots * ((chunks + c - 1) / c * 8 + 10) + c;
-                    if (best < 0 || cost < best) { best = cost; ns = c; }
+                    if (best < 0 || cost < best) { best = cost; n = c; }
                 }
+                return n;
+            };
+            if (taking) {
+                ns = filling(most);
             } else {
                 // us, fitted to 3700 timings of 249 shapes (1 to 60 nodes, G = 4, 5 and 8, 2 to 80 pairs, 1100 to 30000 tokens): the
                 // splits that this chooses are 0.7 % slower than the fastest in the mean, 2.2 % for batches of lengths 1 / n to n / n.
@@ -353,6 +365,14 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
                     const double us = (double)p * chunk * share + (here > 2 ? 0.973 * (double)(here - 2) : 0.0) + 0.285 * (double)here + partials * (double)c +
                                       0.247 * (double)((c + 7) / 8) + (c > 16 ? 0.486 : 0.0);
                     if (best < 0.0 || us < best) { best = us; ns = c; }
+                }
+                // The fit is of equal lengths.  Where shares have no room and splits stand in for them, not fewer than fill the chip (with
+                // partials of 16 MiB or less, if a few have): 3 sequences of 7800, 24 nodes at G = 5, ten splits (the fit's) / nineteen, equal lengths, 1 / n to n / n, one long
+                // 1.07 / 1.00, 1.15 / 1.02, 1.27 / 1.01 of what they were; one head, 6 of 24K, 16 nodes, 42 / 63 one long 21.3 / 20.4 us.
+                if ((can_share && (many_partials || share_splits > 64)) || (full && s.batch > 64)) {
+                    const int64_t quarter = chunks / 4 > 64 ? 64 : chunks / 4;
+                    const int64_t n = filling(at_hand(static_room_of(SPECPV_STATIC_SCRATCH_BYTES, [&] { return few; }, quarter > 1 ? quarter : 1)));
+                    if (least < n) least = n;
                 }
             }
         } else {
@@ -383,8 +403,8 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             }
             ns = static_room([&] { return first_splits(s, chunks, cus); }, ns);
             // (where the tile kernel would have been taken and its partials fit the static array, the group kernel's do too)
-            keep_static = best_tile >= 0.0 && best_tile < best && static_room([&] { return first_splits(s, chunks, cus); }, ns_tile) <= static_splits();
-            if (keep_static && ns > static_splits()) ns = static_splits();
+            keep_static = best_tile >= 0.0 && best_tile < best && static_room([&] { return first_splits(s, chunks, cus); }, ns_tile) <= static_splits(array);
+            if (keep_static && ns > static_splits(array)) ns = static_splits(array);
         }
         plan.nsplit = (int)ns;
         // The sequences of a batch may differ in length, and the lengths live on the device: for a full pass the group
@@ -396,18 +416,20 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
         // others a sixteenth of it.  Splits: 3 sequences of 7055, 37 nodes, 4 KV heads, 21 of 11 chunks 34 / 28, 31 / 26, 28 / 27; 2 of 57746,
         // 24 nodes at G = 8, 2 heads, 64 of 29 chunks 52 / 43, 46 / 41, 44 / 39.  Shares: 60 nodes, 8 heads, 16 of 3000 at G = 5, two of 47
         // 99 / 83, 92 / 71, 50 / 66; 10 of 4096, three of 43 69 / 58, 54 / 51, 34 / 48; 4 of 8192, eight of 32 60 / 58, 50 / 52, 39 / 46.
-        // 64 channels, where a chunk has less to do, 37 nodes: two sequences of 15005 and 30011, 32 splits 52.4 / 48.9; four of 8192 by
-        // quarters 32.8 / 32.1; 16 by sixteenths of 3000 45.4 / 42.2.
-        const bool short_splits = !taking && (s.D == 64 ? chunks <= 32 * ns : cost.group(parts, blocks, ns, cus) < cost.shares(parts, blocks, shares) &&
+        // 64 channels, up to 32 chunks of a split, which have less to do there: where the pairs are few, so that one long sequence has
+        // splits enough, or the shares' partials many.  Shares / splits: 8 heads, 2 sequences of 21.7K, one node 31 / 26, 27 / 25, 25 / 22;
+        // 5 of 11K, 60 nodes at G = 5 1.00 / 0.88, 1.00 / 0.95, 1.00 / 0.95; 32 of 1300, 60 nodes 85 / 72, 90 / 59, 45 / 49.  Many pairs of
+        // few rows keep the shares: 16 of 2650, one node 28 / 26, 24 / 24, 17 / 21; 32 of 4100, 16 nodes at G = 8 one long 1.00 / 1.65.
+        const bool short_splits = !taking && (s.D == 64 ? chunks <= 32 * ns && ((int64_t)s.batch * s.Hkv <= 40 || many_partials) : cost.group(parts, blocks, ns, cus) < cost.shares(parts, blocks, shares) &&
                                                                                cost.splits_hold((double)((chunks + ns - 1) / ns), attn_group_chunk_us(blocks), blocks, shares));
-        if (full && s.batch > 1 && s.batch <= 64 && plan.kind == kAttnGroup && chunks > 32 && !short_splits && (int64_t)s.batch * s.Hkv * chunks < ((int64_t)1 << 30)) {
+        if (can_share && plan.kind == kAttnGroup && chunks > 32 && !short_splits && (int64_t)s.batch * s.Hkv * chunks < ((int64_t)1 << 30)) {
             const int64_t pairs = (int64_t)s.batch * s.Hkv, R = (int64_t)s.M * s.G;
             int64_t wgs = shares;
             const int64_t static_slots = (array - static_fixed) / (R * (int64_t)row_bytes) - pairs;
             if (keep_static && wgs > static_slots && static_slots >= wgs / 2) wgs = static_slots;
             // the workspace of as many splits as hold that many slots
-            const int64_t bytes = (wgs + pairs) * R * (int64_t)row_bytes + 512, slot = pairs * R * (4 * s.D + 8);
-            const int64_t splits = (bytes + slot - 1) / slot > 1 ? (bytes + slot - 1) / slot - 1 : 1;
+            const int64_t bytes = (wgs + pairs) * R * (int64_t)row_bytes + 512;
+            const int64_t splits = (bytes + split_bytes - 1) / split_bytes > 1 ? (bytes + split_bytes - 1) / split_bytes - 1 : 1;
             const bool fits = (int64_t)kArriveBytes + bytes <= array;
             const int64_t at_most = room_rows / R - pairs;   // ... that the caller's has room for
             if (at_most >= 1 && splits <= 64 && (fits || (!keep_static && static_room([&] { return s.D == 64 ? few_splits(tokens) : first_splits(s, chunks, cus); }, 64) == 64))) {
@@ -415,6 +437,7 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
                 plan.nsplit = (int)splits;
             }
         }
+        if (!plan.stream && least > ns) plan.nsplit = (int)(ns = least);
         // ... and for more sequences than the shares are worked out for, about eight workgroups per CU, 64 chunks or more
         // each, for the hardware to deal out.  100 sequences of 16K, 4 KV heads, 60 nodes at G = 4, with the model's three
         // splits / with six: equal lengths 968 / 1004 us, 1/100 to 100/100 of it 539 / 550, one long and the others a

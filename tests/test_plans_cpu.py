@@ -32,7 +32,7 @@ def splits_asked_for(batch, Hkv, G, M, ctx, D=128, B=64, dtype=1):
 def room_of_shares(batch, Hkv, G, M, shares, D=128):
     """The splits that hold the slots of so many shares."""
     R, pairs = M * G, batch * Hkv
-    bytes_ = (shares + pairs) * R * (2 * D + 8 if D == 128 else 4 * D + 8) + 512
+    bytes_ = (shares + pairs) * R * (2 * D + 8 if D == 128 else 4 * D + 8) + 512   # (fp16 partials at 128 channels)
     slot = pairs * R * (4 * D + 8)
     return max(1, (bytes_ + slot - 1) // slot - 1)
 
@@ -55,3 +55,15 @@ def test_splits_where_their_chains_are_short(batch, Hkv, G, M, ctx):
 @pytest.mark.parametrize("batch,Hkv,G,M,ctx,shares", [(16, 1, 4, 8, 36448, 256), (24, 1, 4, 1, 22336, 256), (4, 4, 4, 16, 26752, 256), (4, 8, 4, 1, 32416, 512), (16, 8, 8, 1, 13376, 512)])
 def test_shares_of_few_rows(batch, Hkv, G, M, ctx, shares):
     assert splits_asked_for(batch, Hkv, G, M, ctx) == room_of_shares(batch, Hkv, G, M, shares)
+
+
+@cpu_only
+@pytest.mark.parametrize("batch,Hkv,G,M,ctx,shares", [(16, 8, 4, 1, 2654, 512), (32, 8, 8, 16, 4448, 512), (8, 8, 5, 16, 2300, 512), (24, 8, 5, 60, 2976, 256), (11, 8, 8, 60, 10528, 256)])
+def test_64_channels_shares(batch, Hkv, G, M, ctx, shares):
+    assert splits_asked_for(batch, Hkv, G, M, ctx, 64) == room_of_shares(batch, Hkv, G, M, shares, 64)
+
+
+@cpu_only
+@pytest.mark.parametrize("batch,Hkv,G,M,ctx,splits", [(8, 1, 4, 16, 30902, 61), (3, 8, 5, 24, 7802, 19), (8, 2, 4, 30, 10000, 29), (100, 4, 4, 60, 8192, 5), (2, 8, 4, 37, 30011, 32)])
+def test_64_channels_splits(batch, Hkv, G, M, ctx, splits):
+    assert splits_asked_for(batch, Hkv, G, M, ctx, 64) >= splits
