@@ -272,6 +272,8 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
         return few_fit ? room : ns;
     };
     auto static_room = [&](auto few_of, int64_t ns) { return static_room_of(array, few_of, ns); };
+    // whether specpv_partial_verify_attn_static takes the call
+    auto taken = [&]() { return taking || static_need(s, plan_attention(s, dtype, n_blocks, full, SIZE_MAX, true)) <= (size_t)SPECPV_STATIC_SCRATCH_BYTES; };
     const int64_t cus = device_cu_count();
     if (plan.kind == kAttnGeneric) {
         // two wavefronts of 32 rows per SIMD, 64 tokens or more each (the few splits up to 1024 tokens, and half that many
@@ -403,7 +405,7 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             }
             ns = static_room([&] { return first_splits(s, chunks, cus); }, ns);
             // (where the tile kernel would have been taken and its partials fit the static array, the group kernel's do too)
-            keep_static = best_tile >= 0.0 && best_tile < best && static_room([&] { return first_splits(s, chunks, cus); }, ns_tile) <= static_splits(array);
+            keep_static = best_tile >= 0.0 && best_tile < best && static_room([&] { return first_splits(s, chunks, cus); }, ns_tile) <= static_splits(array) && taken();
             if (keep_static && ns > static_splits(array)) ns = static_splits(array);
         }
         plan.nsplit = (int)ns;
@@ -451,15 +453,16 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             // Each round of workgroups starts and ends for itself: where the splits in hand have partials of 16 MiB or less, no more than
             // stay so.  128 of 16K, 2 KV heads, 24 nodes, refreshed, two splits / four / eight: equal lengths 351-360 / 370 / 376 us, 1/128 to
             // 128/128 of it 241 / 235 / 235.
-            // What has room in the static array of the entry point that has one still does.
-            for (const size_t room : {(size_t)SPECPV_STATIC_SCRATCH_BYTES, (size_t)array}) {
-                auto in = [&](int64_t n) {
-                    const AttnPlan x{(int)n, plan.kind, plan.tg, 0};
-                    return (taking || room < (size_t)array ? static_need(s, x) : layout_workspace(s, x, nullptr).need) <= room;
-                };
-                if (!in(ns)) continue;
-                while (c > ns && !in(c)) --c;
-            }
+            auto in = [&](int64_t n, size_t room) {
+                const AttnPlan x{(int)n, plan.kind, plan.tg, 0};
+                return (room == (size_t)SPECPV_STATIC_SCRATCH_BYTES ? static_need(s, x) : layout_workspace(s, x, nullptr).need) <= room;
+            };
+            if (in(ns, SPECPV_STATIC_SCRATCH_BYTES))
+                while (c > ns && !in(c, SPECPV_STATIC_SCRATCH_BYTES)) --c;
+            // A call that specpv_partial_verify_attn_static takes has room in its array.  (72 of 16K, one head at G = 8, 60 nodes, which it does
+            // not take: one long 94 us with eight splits, 100 with the seven that would have.)
+            if (!taking && c > ns && in(ns, (size_t)array) && !in(c, (size_t)array) && taken())
+                while (c > ns && !in(c, (size_t)array)) --c;
             c = at_hand(c);
             if (c > ns) plan.nsplit = (int)c;
         }

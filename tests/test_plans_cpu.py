@@ -67,3 +67,9 @@ def test_64_channels_shares(batch, Hkv, G, M, ctx, shares):
 @pytest.mark.parametrize("batch,Hkv,G,M,ctx,splits", [(8, 1, 4, 16, 30902, 61), (3, 8, 5, 24, 7802, 19), (8, 2, 4, 30, 10000, 29), (100, 4, 4, 60, 8192, 5), (2, 8, 4, 37, 30011, 32)])
 def test_64_channels_splits(batch, Hkv, G, M, ctx, splits):
     assert splits_asked_for(batch, Hkv, G, M, ctx, 64) >= splits
+
+
+@cpu_only
+@pytest.mark.parametrize("batch,Hkv,G,M,ctx,D,splits", [(72, 1, 8, 60, 16384, 128, 8), (72, 1, 8, 60, 16384, 64, 8), (128, 2, 4, 24, 16384, 128, 2), (128, 2, 4, 24, 16384, 64, 8)])
+def test_more_than_64_sequences(batch, Hkv, G, M, ctx, D, splits):
+    assert splits_asked_for(batch, Hkv, G, M, ctx, D) == splits
