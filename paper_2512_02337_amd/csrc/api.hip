@@ -291,10 +291,19 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             // Workgroups of a CU share its matrix cores, four at a time its registers; a chunk (32 tokens here) takes one by itself its
             // latency.  Partials are written and read back.  Fitted to 3000 timings of 190 shapes: the splits that this chooses are 1.7 %
             // slower than the fastest in the mean.
-            const double share = s.D == 128 ? 1.48 : 0.73, alone = s.D == 128 ? 4.0 : 2.4, partials = 1.0 * (double)pairs * (double)R * s.D * 4e-6;
+            // Up to 32 rows leave two of a workgroup's four wavefronts idle: half of the share, and no more workgroups than have a place (16
+            // sequences of 2400, 20 rows, 8 heads, six splits / eight, equal lengths and one long 0.40 / 0.38, 1.18 / 0.9 of straight from
+            // memory; 4 of 5900, 32 rows, 23 / 30, 0.68 / 0.63, 1.03 / 0.92).  Batches have two splits or more: with one, sequences of
+            // different lengths keep the chip for as long as the longest (24 of 1350, 60 nodes, one / two, equal lengths and one long 384 /
+            // 377, 227 / 153 us).
+            const bool half = R <= 32;
+            const double share = (s.D == 128 ? 1.48 : 0.73) * (half ? 0.5 : 1.0), alone = s.D == 128 ? 4.0 : 2.4, partials = 1.0 * (double)pairs * (double)R * s.D * 4e-6;
             double best = -1.0;
-            const int64_t most = at_hand(static_room([&] { return few; }, chunks < 64 ? chunks : 64));
-            for (int64_t c = 1; c <= most; ++c) {
+            int64_t most = static_room([&] { return few; }, chunks < 64 ? chunks : 64);
+            if (half && most > 4 * cus / pairs) most = 4 * cus / pairs;
+            const int64_t least = full && s.batch > 1 && chunks > 1 ? 2 : 1;
+            most = at_hand(most > least ? most : least);
+            for (int64_t c = least < most ? least : most; c <= most; ++c) {
                 const int64_t here = (pairs * parts * c + cus - 1) / cus, p = (chunks + c - 1) / c;
                 const double work = share * (double)here > alone ? share * (double)here : alone;
                 const double us = (double)p * work + 0.56 * (double)((here + 3) / 4) + partials * (double)c + (c > 16 ? 0.1 : 0.0);
@@ -313,7 +322,9 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             ns = want < most ? want : most;
             if (ns < few) ns = few;
         }
-        plan.nsplit = (int)at_hand(static_room([&] { return few; }, ns));
+        // (straight from memory: partials of no more than 16 MiB, where a few splits have no more.  16 sequences of 1500, 5 nodes at G = 4, 8 heads, 11
+        // splits / 16: equal lengths 170 / 162 us, one long 48 / 65)
+        plan.nsplit = (int)at_hand(static_room_of(staged ? array : (int64_t)SPECPV_STATIC_SCRATCH_BYTES, [&] { return few; }, ns));
     } else {
         const int64_t chunks = (tokens + 31) / 32;   // 32-token chunks per (sequence, KV head)
         const int parts = attn_group_parts(s);

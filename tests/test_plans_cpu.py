@@ -73,3 +73,11 @@ def test_64_channels_splits(batch, Hkv, G, M, ctx, splits):
 @pytest.mark.parametrize("batch,Hkv,G,M,ctx,D,splits", [(72, 1, 8, 60, 16384, 128, 8), (72, 1, 8, 60, 16384, 64, 8), (128, 2, 4, 24, 16384, 128, 2), (128, 2, 4, 24, 16384, 64, 8)])
 def test_more_than_64_sequences(batch, Hkv, G, M, ctx, D, splits):
     assert splits_asked_for(batch, Hkv, G, M, ctx, D) == splits
+
+
+@cpu_only
+@pytest.mark.parametrize("batch,Hkv,G,M,ctx,D,least,most", [
+    (11, 8, 8, 60, 3296, 128, 2, 2), (24, 8, 4, 60, 1344, 128, 2, 2), (32, 8, 4, 37, 1184, 64, 2, 2), (16, 8, 4, 5, 2432, 128, 7, 12), (4, 8, 4, 8, 5888, 128, 27, 32),
+    (16, 8, 4, 8, 1312, 64, 7, 8), (16, 8, 4, 5, 1500, 128, 7, 11), (16, 8, 4, 4, 1500, 128, 1, 14)])
+def test_fp32_splits(batch, Hkv, G, M, ctx, D, least, most):
+    assert least <= splits_asked_for(batch, Hkv, G, M, ctx, D, dtype=0) <= most
