@@ -85,17 +85,18 @@ bool refresh_tail_supported(const Shape &s, int dtype, const Partials &p, int ki
            s.max_blocks <= 32 * 60000 && (int64_t)s.batch * s.Hkv <= 8 * 65535 && !draft_rows_wide(s, sizeof(uint16_t));
 }
 
-// Where the merge alone has eight fours of rows for every CU and there is little to score, the merge's workgroups pay more for the LDS and the
-// wavefronts of the scoring ones than a launch costs.  Tail / merge and scores apart (kernel trace, us; blocks of 32 query rows times tiles of
-// 32 blocks): 16 sequences of 2K at G = 4, 60 nodes (1024) 19.3 / 9.9 + 5.1, of 4K (2048) 23.6 / 17.5 + 5.8; 10 of 4K at G = 5 (1600) 24.4 /
-// 9.3 + 5.7; 11 of 5855 in blocks of 32, 37 nodes (2640) 19.1 / 8.4 + 8.4; 8 of 28046 in blocks of 16, 64 nodes (28160) 38.9 / 11.6 + 28.9;
-// 32K + 64K + 96K + 128K at G = 5 (20480) 28.2 / 10.9 + 24.5.
+// Where the merge alone has eighteen fours of rows for every CU and there is little to score, the merge's workgroups pay more for the LDS and
+// the wavefronts of the scoring ones than a launch costs.  Whole refreshes of 81 shapes (1 to 32 sequences) with up to 4096 blocks of 32 query
+// rows times tiles of 32 blocks to score, apart / together, equal lengths and one long, means: 18 to 31 fours a CU 0.93 / 1.00, 0.94 / 1.00 (16
+// sequences of 12K, 24 nodes at G = 8 131 us 0.91 / 0.98, 0.86 / 0.99); 11 to 18 0.98 / 0.99, 1.02 / 1.00; eight to 11 1.00 / 1.00, 1.04 / 0.99 (11 of
+// 6300, 60 nodes, 4 heads 1.01 / 0.99, 1.10 / 1.00).  With more to score, 4480 / 4800 / 5120 / 7680: 0.92 / 0.99, 0.99 / 0.99, 0.96 / 0.99, 1.01 / 1.01;
+// 20480: tail 28.2 / 10.9 + 24.5 us.
 bool refresh_tail_pays(const Shape &s, int reduce, int last_node)
 {
     const bool pack = combine_packed(s, SPECPV_BF16);
     const ScoreArgs a = score_plan(s, nullptr, nullptr, reduce, last_node, nullptr, false);
     const int64_t pairs = (int64_t)s.batch * s.Hkv, fours = pairs * (pack ? (s.M * s.G + 3) / 4 : s.M * ((s.G + 3) / 4));
-    return fours < 8 * (int64_t)device_cu_count() || (int64_t)((a.rows - a.row0 + 31) / 32) * ((s.max_blocks + 31) / 32) * pairs > 4096;
+    return fours < 18 * (int64_t)device_cu_count() || (int64_t)((a.rows - a.row0 + 31) / 32) * ((s.max_blocks + 31) / 32) * pairs > 4096;
 }
 
 hipError_t launch_refresh_tail(const Shape &s, Partials p, void *out, float *lse, const void *kmax, const void *kmin, int reduce, int last_node,
