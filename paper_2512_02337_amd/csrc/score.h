@@ -1,6 +1,7 @@
 // What the kernels that score blocks on the matrix cores share (score_mfma.hip, refresh_tail.hip): see score_mfma.hip.
 #pragma once
 #include "internal.h"
+#include "topk.h"
 
 namespace specpv {
 
@@ -118,11 +119,12 @@ struct ScoreArgs {
     int reduce, last_node;
     int row0, rows;       // the query rows that count lie in row0 .. rows - 1 (row0: a multiple of 32)
     int waves;            // of a workgroup
-    int tiles, groups;    // tiles of a workgroup; workgroups of a (sequence, KV head)
+    int tiles, groups;    // tiles of a workgroup; workgroups of a (sequence, KV head) (streams: of a KV head)
+    int rounds;           // streams: groups of tiles that a workgroup needs to go through at most
     int staged;           // the query rows go through LDS (read_q)
     int sums;             // partial sums per tile and lane: one per block of 32 rows, blocks 16 apart share one
     int by_xcd;           // Hkv % 8 == 0: grid (groups * 8, Hkv / 8, batch), KV head g on XCD g % 8; else (groups, Hkv, batch)
-    FastDiv div_G, div_B;
+    FastDiv div_G, div_B, div_tiles;
 };
 // bytes of a tile in LDS (Kmax | Kmin), and of a workgroup: tiles, partial sums and, staged, 32 half rows (64 channels: rows)
 // of queries per wavefront
@@ -332,14 +334,50 @@ __device__ __forceinline__ void score_tiles(const Shape &s, const ScoreArgs &a, 
 // LDS of score_stream: two halves of tiles and of partial sums.
 static inline size_t score_stream_lds(int D, int tiles, int sums) { return 2 * (size_t)tiles * (score_tile_bytes(D) + sums * 256); }
 
-// Scores of every a.groups-th group of a.tiles tiles, from `group` on (eq. 2): where a (sequence, KV head) has many tiles, a workgroup
+// Which stream a workgroup is: the a.groups workgroups of a KV head are dealt to the sequences by their lengths, so that the longest
+// way is as short as they allow: the fewest groups of tiles r that a workgroup has to go through, and to each sequence as many
+// workgroups as it has r-groups.  (As many for each sequence, sixteen sequences of 2048 blocks, 8 heads, 60 nodes at G = 5: two workgroups
+// went through 22 groups of a long one among short ones, 46.8 us of scores and selection; tiles at once 21.5.)  A lane a sequence.
+struct ScoreStream {
+    int b, L;             // the sequence and its length
+    int group, groups;    // groups of tiles from `group` on, every `groups`-th; groups == 0: none
+    __device__ __forceinline__ ScoreStream(const Shape &s, const ScoreArgs &a, int w)
+    {
+        if (s.batch == 1) {
+            b = 0; L = s.ctx_len[0]; group = w; groups = a.groups;
+            return;
+        }
+        const int lane = threadIdx.x & 63;
+        const int length = lane < s.batch ? s.ctx_len[lane] : 0;
+        const int blocks = min(length > 0 ? (int)a.div_B.div((uint32_t)length + (uint32_t)s.B - 1u) : 0, s.max_blocks);
+        const uint32_t n = a.div_tiles.div(((uint32_t)blocks + 31u) / 32u + (uint32_t)a.tiles - 1u);   // groups of tiles
+        auto workgroups = [&](uint32_t r) { return (int)((n + r - 1u) / r); };
+        int lo = 1, hi = a.rounds;   // (a.rounds are enough for sequences that are all as long as may be)
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (__builtin_amdgcn_readlane(wave_inclusive_scan(workgroups((uint32_t)mid)), 63) <= a.groups) hi = mid;
+            else lo = mid + 1;
+        }
+        const int mine = workgroups((uint32_t)lo), upto = wave_inclusive_scan(mine);
+        const unsigned long long behind = __ballot(w < upto);
+        b = L = group = groups = 0;
+        if (!behind) return;
+        b = __builtin_ctzll(behind);
+        groups = __builtin_amdgcn_readlane(mine, b);
+        group = w - (__builtin_amdgcn_readlane(upto, b) - groups);
+        L = __builtin_amdgcn_readlane(length, b);
+    }
+};
+
+// Scores of one stream's groups of a.tiles tiles (eq. 2): where a (sequence, KV head) has many tiles, a workgroup
 // keeps the query rows in registers, a block of 32 to a wavefront, and goes through its groups while the next one's rows are on their
 // way.  One barrier a group: behind it the group's tiles have landed, everybody is done with the half that the next group goes to, and
 // the sums of the group before are there, to be added up and stored.  Reads and writes of LDS are assembly: the compiler would have each
 // wait for the tiles that are on their way.
 template <int D>
-__device__ __forceinline__ void score_stream(const Shape &s, const ScoreArgs &a, const int group, const int g, const int b)
+__device__ __forceinline__ void score_stream(const Shape &s, const ScoreArgs &a, const ScoreStream &mine, const int g)
 {
+    const int b = mine.b, L = mine.L;
     constexpr int KS = D / 16, LPR = D / 8, RPO = 64 / LPR, OPS = D / 16, HALF = 64 * D, TILE = 2 * HALF, H = D / 64;
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     extern __shared__ __attribute__((aligned(1024))) char score_smem[];
@@ -348,11 +386,10 @@ __device__ __forceinline__ void score_stream(const Shape &s, const ScoreArgs &a,
     const int n = lane & 31, kg = lane >> 5;
     const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)score_smem;
     const uint32_t red = ring + 2u * (uint32_t)(T * TILE), red_half = (uint32_t)(a.sums * T * 256);   // [half][sums][tile][lane]
-    const int L = s.ctx_len[b];
     const int nb = min(L > 0 ? (int)a.div_B.div((uint32_t)L + (uint32_t)s.B - 1u) : 0, s.max_blocks);
-    const int step = a.groups * 32 * T;
-    int i0 = group * 32 * T;
-    if (i0 >= nb) return;
+    const int step = mine.groups * 32 * T;
+    int i0 = mine.group * 32 * T;
+    if (step == 0 || i0 >= nb) return;
     const int r0 = a.row0 + wave * 32;
     // the query rows as whole lines, through what will be the second half of the tiles (score_tiles: read_staged)
     u32x4 raw[H][4];
@@ -380,15 +417,15 @@ __device__ __forceinline__ void score_stream(const Shape &s, const ScoreArgs &a,
     request(i0, 0);
     bf16x8 q[KS];
     {
-        char *mine = score_smem + T * TILE + wave * kScoreStage;
+        char *corner = score_smem + T * TILE + wave * kScoreStage;
         const int to = (lane >> 3) * 128, from = n * 128;
 #pragma unroll
         for (int h = 0; h < H; ++h) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) *(u32x4 *)(mine + 1024 * i + to + 16 * ((lane & 7) ^ ((4 * i + (lane >> 4)) & 7))) = raw[h][i];
+            for (int i = 0; i < 4; ++i) *(u32x4 *)(corner + 1024 * i + to + 16 * ((lane & 7) ^ ((4 * i + (lane >> 4)) & 7))) = raw[h][i];
             asm volatile("" ::: "memory");
 #pragma unroll
-            for (int x = 0; x < 4; ++x) q[4 * h + x] = __builtin_bit_cast(bf16x8, *(const u32x4 *)(mine + from + 16 * ((2 * x + kg) ^ ((n >> 1) & 7))));
+            for (int x = 0; x < 4; ++x) q[4 * h + x] = __builtin_bit_cast(bf16x8, *(const u32x4 *)(corner + from + 16 * ((2 * x + kg) ^ ((n >> 1) & 7))));
             asm volatile("" ::: "memory");
         }
     }

@@ -76,9 +76,9 @@ __global__ __launch_bounds__(64 * kScoreMaxWaves) void score_mfma_kernel(Shape s
 template <int D>
 __global__ __launch_bounds__(64 * kScoreMaxWaves) void score_stream_kernel(Shape s, ScoreArgs a)
 {
-    const int group = a.by_xcd ? (int)blockIdx.x >> 3 : (int)blockIdx.x;
-    const int g = a.by_xcd ? (int)blockIdx.y * 8 + ((int)blockIdx.x & 7) : (int)blockIdx.y, b = blockIdx.z;
-    score_stream<D>(s, a, group, g, b);
+    const int w = a.by_xcd ? (int)blockIdx.x >> 3 : (int)blockIdx.x;   // of the KV head's
+    const int g = a.by_xcd ? (int)blockIdx.y * 8 + ((int)blockIdx.x & 7) : (int)blockIdx.y;
+    score_stream<D>(s, a, ScoreStream(s, a, w), g);
 }
 
 bool score_mfma_supported(const Shape &s, int dtype) { return dtype == SPECPV_BF16; }
@@ -141,9 +141,14 @@ ScoreArgs score_plan(const Shape &s, const void *kmax, const void *kmin, int red
 
 // Whether the scores go by streams (score_stream), and their tiles and workgroups: where a workgroup for every place on the chip has a
 // group of tiles or more.  One block of query rows is a read of the summaries and little else, and is faster with all of them under way
-// at once.  Scores and selection, tiles at once / by streams, us: 8 KV heads at G = 5, 78 nodes, 4 x 1024 blocks 21.6 / 16.2, 60 nodes,
-// 8 x 512 18.3 / 16.5, 512 to 2048 blocks in four 21.8 / 20.4; G = 4, 64 nodes, 8 x 1753 29.2 / 26.0, 24 nodes, 2 x 2048 12.3 / 11.4,
-// one node (one block), 4 x 2048 12.9 / 14.0.
+// at once.  Batches that have several groups to a workgroup go by streams where these are dealt without much loss (equal lengths fill 72 %
+// of the rounds; 64 channels, whose tiles cost less than what is lost, 85 %) and where workgroups are left to deal: two to a sequence,
+// with 64 channels four.  Scores and selection, tiles at once / by streams, us, equal lengths, 1 / n to n / n, one long and the others a
+// sixteenth: 8 KV heads, 60 nodes, G = 5, 16 x 2048 blocks 71 / 62, 45 / 43, 23 / 17, 8 x 1024 24 / 23, 20 / 16, 19 / 12, G = 4, 16 x 2048 57
+// / 47, 37 / 30, 23 / 15, 4 x 1024, 78 nodes at G = 5 22 / 16, 20 / 14, 19 / 13.  Beyond the lines: 32 x 824, 37 nodes at G = 8 (as many
+// workgroups as sequences) 59 / 51, 38 / 44, 19 / 40; 17 x 512, 60 nodes at G = 5 27 / 29, 21 / 22 (equal lengths fill 40 %); 64 channels,
+// 37 nodes, 32 x 597 18.9 / 19.5, 14.6 / 16.2, 24 x 114 9.2 / 10.6, 12 x 554 at G = 8 14.0 / 15.1; one node (one block), 4 x 2048 12.9 / 14.0.
+// Of 160 random shapes the slowest of those and of one long last is 0.91 of tiles at once in the mean.
 static bool score_stream_plan(const Shape &s, ScoreArgs &a)
 {
     const int blocks32 = (a.rows - a.row0 + 31) / 32;
@@ -152,10 +157,15 @@ static bool score_stream_plan(const Shape &s, ScoreArgs &a)
     const int T = (blocks32 * kScoreStage + score_tile_bytes(s.D) - 1) / score_tile_bytes(s.D);   // room for the query rows' way
     const int64_t fit = (int64_t)(160 * 1024 / score_stream_lds(s.D, T, blocks32)), per_cu = 16 / blocks32 < fit ? 16 / blocks32 : fit;
     if (per_cu < 1) return false;
-    const int64_t phases = (tiles1 + T - 1) / T;
-    int64_t groups = per_cu * cus / pairs;
-    if (groups < 1) groups = 1;
-    if (phases < groups) return false;
+    const int64_t phases = (tiles1 + T - 1) / T, groups = per_cu * cus / s.Hkv;   // of the longest sequence; workgroups of a KV head
+    if (s.batch > 64 || groups < s.batch || phases < groups / s.batch) return false;   // (a lane a sequence: ScoreStream)
+    const int64_t rounds = (phases + groups / s.batch - 1) / (groups / s.batch);
+    if (s.batch > 1) {
+        if (s.D == 64 && groups < 4 * (int64_t)s.batch) return false;
+        if (rounds > 1 && (groups < 2 * (int64_t)s.batch || (double)(phases * pairs) < (s.D == 128 ? 0.72 : 0.85) * (double)(rounds * per_cu * cus))) return false;
+    }
+    a.rounds = (int)rounds;
+    a.div_tiles = make_fastdiv((uint32_t)T);
     a.waves = a.sums = blocks32;
     a.tiles = T;
     a.groups = (int)groups;
@@ -171,7 +181,7 @@ hipError_t launch_scores_mfma(const Shape &s, const void *kmax, const void *kmin
 {
     ScoreArgs a = score_plan(s, kmax, kmin, reduce, last_node, scores, sel != nullptr);
     if (!sel && kind == SPECPV_SCORE_EQ2 && score_stream_plan(s, a)) {
-        const dim3 grid(a.by_xcd ? a.groups * 8 : a.groups, a.by_xcd ? s.Hkv / 8 : s.Hkv, s.batch), block(64 * a.waves);
+        const dim3 grid(a.by_xcd ? a.groups * 8 : a.groups, a.by_xcd ? s.Hkv / 8 : s.Hkv), block(64 * a.waves);
 #define SPECPV_LAUNCH(DD)                                                                                                       \
         do {                                                                                                                    \
             static PerDeviceOnce once;                                                                                          \
