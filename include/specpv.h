@@ -149,7 +149,8 @@ int specpv_block_summarize(const specpv_kv *kv, int32_t blk_begin, int32_t blk_e
  *   every block if nb_b <= ns + k + nr.
  * sel_idx   [batch, Hkv, n_sel] int32, n_sel = ns + k + nr + n_extra_slots, ascending, padded with -1.
  * sel_count [batch, Hkv] int32.
- * scores    optional [batch, Hkv, max_blocks] fp32 (NULL: in the workspace, where the selection needs any: max_blocks > ns + k + nr).
+ * scores    optional [batch, Hkv, max_blocks] fp32 (NULL: in the workspace, which has to have room for them also where the
+ *           selection needs none, max_blocks <= ns + k + nr).
  * workspace may be NULL when scores is given; the one-launch route of specpv_debug_set_select_route
  * uses the arrival words of a workspace of 64 KiB or more (zero before the call, zero again after it). */
 int specpv_select_blocks(const specpv_kv *kv, const specpv_tree *tree,

@@ -753,10 +753,9 @@ int specpv_full_verify_refresh(const specpv_kv *kv, const specpv_tree *tree, voi
     if (!beside) apart = nullptr;   // scoring as a launch of its own, or with the selection
     // Lists of every block go out with the merge as well: one launch less, and no scores that nobody asked for.  Refresh, 60 nodes, 900
     // tokens 14.3 -> 10.5 us, 4000 tokens 18.2 -> 14.3, seven sequences of 624 in blocks of 16 22.2 -> 18.6; 64 channels, 538 tokens,
-    // 1 node 13.3 -> 8.9.  (Up to eight blocks they are still taken, for those who look for them behind the partials, as the tests of
-    // that place do: 0.4 to 1 of some 10 us.)
+    // 1 node 13.3 -> 8.9.
     const TopkArgs sel = list_args(cfg, sel_idx, sel_count);
-    const bool all = beside && keeps_every_block(s, sel), score = scores || !all || s.max_blocks <= 8;
+    const bool all = beside && keeps_every_block(s, sel), score = scores || !all;
     const bool all_beside = all && (apart || !score);
     TailScores tail{kmax, kmin, score ? (int)cfg->score : (int)SPECPV_SCORE_EQ2, (int)cfg->reduce, tree->last_node - tree->n_key_only,
                     score ? apart : nullptr, all_beside ? &sel : nullptr, false};

@@ -61,3 +61,22 @@ def test_every_block_is_listed(routes, over, spare, extra, score):
         entry = np.arange(run.cfg.n_sel)
         for b, nb in enumerate(blocks):
             assert (results[0][2][b].cpu().numpy() == np.where(entry < nb, entry, -1)).all() and (results[0][3][b] == nb).all()
+
+
+@pytest.mark.parametrize("ctx", [100, 128, 129, 700])
+def test_no_scores_that_nobody_asked_for(routes, ctx):
+    """A refresh whose lists keep every block leaves the place behind the partials as it was, whatever the number of blocks."""
+    sp = routes
+    say("case", ctx)
+    cfg = dict(SMALL, name="all")
+    cfg.update(ctx=[ctx], rho=[0.1])
+    case = workloads.to_device(workloads.make_case(cfg, seed=5), "cuda")
+    run = GpuRun(sp, case, cfg=(2, 3, case["max_blocks"]))
+    run.summarize()
+    left = []
+    for scores in (None, run.scores):
+        run.ws.zero_()
+        sp.specpv_full_verify_refresh(run.kv, run.tree, run.kmax, run.kmin, -1, run.cfg, run.out, run.lse, run.sel_idx, run.sel_count, scores, run.ws)
+        torch.cuda.synchronize()
+        left.append(run.ws.clone())
+    assert torch.equal(left[0], left[1])

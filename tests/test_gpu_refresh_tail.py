@@ -36,14 +36,14 @@ PENDING = [  # (over, reducer, key-only nodes, stale from)
     (dict(ctx=[20000, 30000], M=60, Hq=40, Hkv=8, B=64), "last", 5, 17), (dict(ctx=[9000, 4000, 5000], M=30, Hq=40, Hkv=8, D=64), "max", 0, 0)]
 
 
-def _setup(sp, over, reduce, n_key=0):
+def _setup(sp, over, reduce, n_key=0, keep=None):
     cfg = dict(SMALL, name="tail")
     cfg.update(over, rho=[0.1] * len(over["ctx"]))
     case = workloads.make_case(cfg, seed=91)
     if n_key:
         case = with_pending(case, n_key, seed=92)
     case = workloads.to_device(case, "cuda")
-    return case, GpuRun(sp, case, reduce=reduce, last_node=n_key + case["M"] // 2 if reduce == "last" else n_key)
+    return case, GpuRun(sp, case, reduce=reduce, last_node=n_key + case["M"] // 2 if reduce == "last" else n_key, cfg=keep)
 
 
 def _refresh(sp, run, scores, ws, stale=-1):
@@ -115,7 +115,8 @@ def test_pending_nodes_and_stale_summaries(routes, over, reduce, n_key, stale):
 def test_room_behind_the_partials(routes, over, reduce):
     sp = routes
     say("case", over, reduce)
-    case, run = _setup(sp, over, reduce)
+    # (lists that keep every block need no scores)
+    case, run = _setup(sp, over, reduce, keep=(1, 1, 3) if max(over["ctx"]) <= 14 * 16 else None)
     run.summarize()
     sp.specpv_debug_set_select_route(0)
     head, need = 65536, (run.scores.numel() * 4 + 255) & ~255
