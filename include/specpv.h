@@ -201,8 +201,8 @@ int specpv_partial_verify_attn_static(const specpv_kv *kv, const specpv_tree *tr
  *      -> sel_idx, sel_count (and scores if not NULL).
  * Summaries, scores and lists are those of the three calls above issued one after another, bit for bit.  So are out and
  * lse (of specpv_partial_verify_attn with sel_idx == NULL and a workspace of the same size) where no summaries are
- * recomputed.  With stale_blk_begin >= 0 a long pass with many query rows (bf16, head dim 128, blocks of 64 tokens or
- * more) may give a part of its workgroups to the summaries and cut the context into fewer pieces: out and lse are then the
+ * recomputed.  With stale_blk_begin >= 0 a long pass with many query rows (bf16, head dim 128, blocks of 16, 32, or 64
+ * tokens and more) may give a part of its workgroups to the summaries and cut the context into fewer pieces: out and lse are then the
  * same sums over other pieces, equal up to the roundings that the pieces bring with them (weights to bf16 against a
  * piece's own reference, a piece's result to fp16), and follow stale_blk_begin in their last bits. */
 int specpv_full_verify_refresh(const specpv_kv *kv, const specpv_tree *tree,

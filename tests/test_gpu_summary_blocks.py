@@ -60,7 +60,7 @@ def test_small_blocks_on_the_side(gpu_lib, ctx, B, M, Hq, Hkv, part):
     run.summarize()
     run.refresh(-1)
     torch.cuda.synchronize()
-    want = [x.clone() for x in (run.kmax, run.kmin, run.sel_idx, run.sel_count, run.out)]
+    want = [x.clone() for x in (run.kmax, run.kmin, run.sel_idx, run.sel_count, run.out, run.lse)]
     begin = int(part * run.case["max_blocks"])
     for x in (run.kmax, run.kmin):
         x[:, :, begin:] = -7.0
@@ -73,6 +73,7 @@ def test_small_blocks_on_the_side(gpu_lib, ctx, B, M, Hq, Hkv, part):
     assert torch.equal(run.sel_idx, want[2]) and torch.equal(run.sel_count, want[3])
     # another number of splits: a unit in the last place of a bf16 value at most (test_gpu_side_summaries.py)
     assert ((run.out.float() - want[4].float()).abs() <= 2.0 ** -7 * want[4].float().abs() + 1e-3).all()
+    assert (run.lse - want[5]).abs().max() <= 2.0 ** -8
 
 
 @pytest.mark.parametrize("dt,D,B", [(torch.bfloat16, 128, 16), (torch.bfloat16, 128, 32), (torch.bfloat16, 64, 16), (torch.float32, 64, 16)])
