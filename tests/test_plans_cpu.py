@@ -70,6 +70,12 @@ def test_64_channels_splits(batch, Hkv, G, M, ctx, splits):
 
 
 @cpu_only
+@pytest.mark.parametrize("batch,Hkv,M,ctx,shares", [(3, 8, 9, 8193, 512), (3, 8, 60, 8193, 256), (3, 8, 1, 8300, 512), (64, 1, 3, 8500, 256)])
+def test_the_cases_of_uneven_batches(batch, Hkv, M, ctx, shares):
+    assert splits_asked_for(batch, Hkv, 4, M, ctx, B=32) == room_of_shares(batch, Hkv, 4, M, shares)
+
+
+@cpu_only
 @pytest.mark.parametrize("batch,Hkv,G,M,ctx,D,splits", [(72, 1, 8, 60, 16384, 128, 8), (72, 1, 8, 60, 16384, 64, 8), (128, 2, 4, 24, 16384, 128, 2), (128, 2, 4, 24, 16384, 64, 8)])
 def test_more_than_64_sequences(batch, Hkv, G, M, ctx, D, splits):
     assert splits_asked_for(batch, Hkv, G, M, ctx, D) == splits
