@@ -143,17 +143,22 @@ struct AttnCost {
         const double chain = 3.11 + p * attn_group_chunk_us(blocks) * (double)parts * (double)wgs / (double)device_cu_count(), memory = kv * (0.02 * (double)parts + 0.115);
         return sqrt(chain * chain + memory * memory) + 0.199 * ((double)wgs + pairs) * s.M * s.G * 512e-6 + 6.0;
     }
-    // Whether splits of `p` chunks, `chunk_us` each, hold up against `wgs` shares when the lengths differ as much as they may: one
+    // Whether ranges of `p` chunks, `chunk_us` each, hold up against `wgs` shares when the lengths differ as much as they may: one
     // sequence with all the chunks, the others with a sixteenth.  A split's chain stays what it was; the shares' chain is cut to the
     // chunks that there are, but then the long sequence has most of the shares, and its combine takes them in rounds, a tenth of a
     // microsecond each.  For 94 shapes (2 to 32 sequences, 1 to 8 KV heads, 1 to 60 nodes, 1 K to 64 K tokens) with the splits that the
     // costs above choose, the chain that splits have more over the shares of the long pair, against the slowest of equal lengths, 1 / n
     // to n / n, one long first and one long last, splits / shares: up to 0.09 us a share (41 shapes) 1.02 at most, 0.82 in the mean;
     // 0.1 to 0.2: 0.9 to 1.38; 0.2 to 0.5: up to 1.44; beyond: up to 1.55.
-    bool splits_hold(double p, double chunk_us, int blocks, int64_t wgs) const
+    // The group kernel's splits gain elsewhere too: up to four sequences have nine chunks in hand (8 heads, 60 nodes at G = 5, two of 5000 0.79, three
+    // of 4100 0.89, two of 18K, seventeen chunks more, 1.05), and where there are more pairs than shares, most of which then run through
+    // several, two partials of a pair beyond them (64 sequences of 1300, 64 nodes 0.81, 0.49, 0.82, 0.90).
+    bool splits_hold(double p, double chunk_us, int blocks, int64_t wgs, bool group) const
     {
         const double of_share = (double)s.Hkv * (double)chunks * (1.0 + (double)(s.batch - 1) / 16.0) / (double)wgs, share = of_share < 1.0 ? 1.0 : of_share;
-        return p * chunk_us - share * attn_group_chunk_us(blocks) <= 0.09 * (double)chunks / share;
+        const double more = p * chunk_us - share * attn_group_chunk_us(blocks), merged = 0.09 * (double)chunks / share;
+        const double beyond = (double)s.batch * s.Hkv - (double)wgs, pairs = group && beyond > 0.0 ? beyond * s.M * s.G * 528e-6 : 0.0, hand = group && s.batch <= 4 ? 9.0 * chunk_us : 0.0;
+        return more <= (merged > hand ? merged : hand) + pairs;
     }
 };
 
@@ -382,7 +387,7 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
                 // The fit is of equal lengths.  Where shares have no room and splits stand in for them, not fewer than fill the chip (with
                 // partials of 16 MiB or less, if a few have): 3 sequences of 7800, 24 nodes at G = 5, ten splits (the fit's) / nineteen, equal lengths, 1 / n to n / n, one long
                 // 1.07 / 1.00, 1.15 / 1.02, 1.27 / 1.01 of what they were; one head, 6 of 24K, 16 nodes, 42 / 63 one long 21.3 / 20.4 us.
-                if ((can_share && (many_partials || share_splits > 64)) || (full && s.batch > 64)) {
+                if (chunks > 32 && ((can_share && (many_partials || share_splits > 64)) || (full && s.batch > 64))) {
                     const int64_t quarter = chunks / 4 > 64 ? 64 : chunks / 4;
                     const int64_t n = filling(at_hand(static_room_of(SPECPV_STATIC_SCRATCH_BYTES, [&] { return few; }, quarter > 1 ? quarter : 1)));
                     if (least < n) least = n;
@@ -399,7 +404,7 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
             double best = -1.0, best_tile = -1.0;
             int64_t ns_tile = 1;
             auto take = [&](double us, int kind, int tg, int64_t c) {
-                if (uneven && kind == kAttnSplit && !(small && cost.splits_hold((double)((chunks + c * tg - 1) / (c * tg)), AttnCost::tile_chunk_us(tg), blocks, shares))) {
+                if (uneven && kind == kAttnSplit && !(small && cost.splits_hold((double)((chunks + c * tg - 1) / (c * tg)), AttnCost::tile_chunk_us(tg), blocks, shares, false))) {
                     if (best_tile < 0.0 || us < best_tile) { best_tile = us; ns_tile = c; }
                 } else if (best < 0.0 || us < best) {
                     best = us; plan.kind = kind; plan.tg = tg; ns = c;
@@ -431,10 +436,11 @@ static AttnPlan plan_attention(const Shape &s, int dtype, int64_t n_blocks, bool
         // 99 / 83, 92 / 71, 50 / 66; 10 of 4096, three of 43 69 / 58, 54 / 51, 34 / 48; 4 of 8192, eight of 32 60 / 58, 50 / 52, 39 / 46.
         // 64 channels, up to 32 chunks of a split, which have less to do there: where the pairs are few, so that one long sequence has
         // splits enough, or the shares' partials many.  Shares / splits: 8 heads, 2 sequences of 21.7K, one node 31 / 26, 27 / 25, 25 / 22;
-        // 5 of 11K, 60 nodes at G = 5 1.00 / 0.88, 1.00 / 0.95, 1.00 / 0.95; 32 of 1300, 60 nodes 85 / 72, 90 / 59, 45 / 49.  Many pairs of
+        // 5 of 11K, 60 nodes at G = 5 1.00 / 0.88, 1.00 / 0.95, 1.00 / 0.95; 32 of 1300, 60 nodes 85 / 72, 90 / 59, 45 / 49;
+        // up to four sequences of many partials 48 chunks (two of 49K, 24 nodes at G = 8 0.78 / 0.73, 0.78 / 0.74, 0.84 / 0.75 of what they were).  Many pairs of
         // few rows keep the shares: 16 of 2650, one node 28 / 26, 24 / 24, 17 / 21; 32 of 4100, 16 nodes at G = 8 one long 1.00 / 1.65.
-        const bool short_splits = !taking && (s.D == 64 ? chunks <= 32 * ns && ((int64_t)s.batch * s.Hkv <= 40 || many_partials) : cost.group(parts, blocks, ns, cus) < cost.shares(parts, blocks, shares) &&
-                                                                               cost.splits_hold((double)((chunks + ns - 1) / ns), attn_group_chunk_us(blocks), blocks, shares));
+        const bool short_splits = !taking && (s.D == 64 ? chunks <= (many_partials && s.batch <= 4 ? 48 : 32) * ns && ((int64_t)s.batch * s.Hkv <= 40 || many_partials) : cost.group(parts, blocks, ns, cus) < cost.shares(parts, blocks, shares) &&
+                                                                               cost.splits_hold((double)((chunks + ns - 1) / ns), attn_group_chunk_us(blocks), blocks, shares, true));
         if (can_share && plan.kind == kAttnGroup && chunks > 32 && !short_splits && (int64_t)s.batch * s.Hkv * chunks < ((int64_t)1 << 30)) {
             const int64_t pairs = (int64_t)s.batch * s.Hkv, R = (int64_t)s.M * s.G;
             int64_t wgs = shares;

@@ -87,3 +87,9 @@ def test_more_than_64_sequences(batch, Hkv, G, M, ctx, D, splits):
     (16, 8, 4, 8, 1312, 64, 7, 8), (16, 8, 4, 5, 1500, 128, 7, 11), (16, 8, 4, 4, 1500, 128, 1, 14)])
 def test_fp32_splits(batch, Hkv, G, M, ctx, D, least, most):
     assert least <= splits_asked_for(batch, Hkv, G, M, ctx, D, dtype=0) <= most
+
+
+@cpu_only
+@pytest.mark.parametrize("batch,Hkv,G,M,ctx", [(48, 8, 5, 37, 619), (65, 8, 4, 24, 790), (32, 8, 8, 60, 1024)])
+def test_64_channels_few_splits_up_to_1024_tokens(batch, Hkv, G, M, ctx):
+    assert splits_asked_for(batch, Hkv, G, M, ctx, 64) == 1
