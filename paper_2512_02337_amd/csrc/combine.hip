@@ -112,7 +112,11 @@ static void launch_combine_t(const Shape &s, int dtype, Partials p, void *out, f
         if (s.koff > s.kctx) SPECPV_LAUNCH_K(NP, MULTI, 24, false); else SPECPV_LAUNCH_H(NP, MULTI, 8);                  \
     } while (0)
     if (wide) { if (kHalf && p.o_half) SPECPV_LAUNCH(8, true, 8, kHalf, true, false, true); else SPECPV_LAUNCH(8, true, 8, false, true, false, true); }   // (any count of partials)
-    else if (p.stream && p.stream <= 4 * (int64_t)s.batch * s.Hkv) SPECPV_LAUNCH_NP(4, true);   // a pair's shares are few: 16 sequences of 4K 17.5 / 15.2 us
+    // A pair's shares are few (more wavefronts have room), and where one sequence is long and has most of them there are rows enough to hide
+    // their rounds.  Rounds of eight / four, full passes, equal lengths, one long first and last: 16 sequences of 4K, 8 heads 17.5 / 15.2 us
+    // (the combine), 16 of 5500, 60 nodes 1 / 0.97, 0.95, 0.97, 64 of 2400, 64 channels 0.93, 0.84, 0.83; few rows, 16 of 2600, one node, 64
+    // channels 1.00, 1.07, 1.16, two heads, 64 of 13.6K, 16 nodes 0.99, 1.01, 1.11.
+    else if (p.stream && p.stream <= 4 * (int64_t)s.batch * s.Hkv && p.stream <= 64 * (int64_t)s.Hkv && s.M * s.G >= 64) SPECPV_LAUNCH_NP(4, true);
     else if (p.stream) SPECPV_LAUNCH_NP(8, true);
     else if (p.nsplit <= 2) SPECPV_LAUNCH_NP(2, false);
     else if (p.nsplit <= 4) SPECPV_LAUNCH_NP(4, false);

@@ -17,6 +17,9 @@ CASES = [
     (dict(ctx=[20000, 5000, 12000], G=4, D=64), "64 channels"),
     (dict(ctx=[700 * ((7 * i) % 11) for i in range(64)], G=2, M=64), "64 sequences"),
     (dict(ctx=[700 * ((7 * i) % 11) for i in range(65)], G=2, M=64), "65: back to splits"),
+    (dict(ctx=[400 * ((7 * i) % 11) for i in range(16)], G=4, Hkv=8), "eight heads: few shares to a pair"),
+    (dict(ctx=[4000] + [40] * 14 + [0], G=4, Hkv=8), "eight heads, one long"),
+    (dict(ctx=[400 * ((7 * i) % 11) for i in range(16)], G=4, Hkv=8, D=64, M=16), "eight heads, 64 channels"),
 ]
 
 
@@ -26,8 +29,9 @@ def test_against_the_oracle(gpu_lib, over, tag):
     cfg = dict(SMALL)
     over = dict(over)
     G = over.pop("G")
-    cfg.update(B=64, M=60, Hq=2 * G, Hkv=2)
+    cfg.update(B=64, M=60, Hkv=2)
     cfg.update(over)
+    cfg["Hq"] = G * cfg["Hkv"]
     cfg["rho"] = [0.1] * len(cfg["ctx"])
     case = workloads.to_device(workloads.make_case(cfg, seed=41), "cuda")
     for layout in ("bhtd", "bthd"):
