@@ -6,10 +6,11 @@
 
 namespace specpv {
 
-// N > 0: blocks of N passes (summarize_small).
+// N > 0: blocks of N passes (summarize_small).  fp32 takes registers for six wavefronts a SIMD and no more: it has fewer to keep, and small
+// blocks need the wavefronts (64 channels, 65536 blocks of 2 tokens 21.4 us with five, 19.2 with six; with seven 128 channels spill).
 template <typename T, int D, int N>
-__global__ __launch_bounds__(256) void summarize_kernel(Shape s, int blk_begin, int blk_end,
-                                                        void *kmax, void *kmin)
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 6 : 1)
+void summarize_kernel(Shape s, int blk_begin, int blk_end, void *kmax, void *kmin)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int g = blockIdx.y, b = blockIdx.z;
@@ -33,7 +34,8 @@ hipError_t launch_summarize(const Shape &s, int dtype, int blk_begin, int blk_en
     // Blocks of two or four passes go by as many to a wavefront as make sixteen loads a lane, where there are more of them than the
     // chip has places for wavefronts: by itself such a block has few bytes under way.  One block / several to a wavefront: blocks of 16,
     // 128 channels, 16384 blocks 15.9 / 15.1 us, 8192 8.4 / 7.8, 4096 4.9 / 5.3, 2048 3.6 / 4.2; 64 channels, 16384 11.8 / 9.6, 4096 4.1 /
-    // 5.7.  Blocks of eight passes have enough: 16384 blocks 12.4 / 13.9.
+    // 5.7.  Blocks of eight passes have enough: 16384 blocks 12.4 / 13.9.  fp32, 128 channels: blocks of 8, 8192 blocks 7.2 / 5.9, 26000
+    // 20.5 / 21.3; of 4, 16384 9.9 / 8.2.
     const int rows = 1024 / (s.D * (dtype == SPECPV_BF16 ? 2 : 4)), passes = s.B % rows ? 0 : s.B / rows;
     const bool many = (int64_t)(hi - blk_begin) * s.Hkv * s.batch >= (int64_t)32 * device_cu_count();
     const int N = many && (passes == 2 || passes == 4) ? passes : 0, per = N ? SPECPV_SUM_UNR / N : 1;

@@ -29,4 +29,4 @@ def test_rows_of_small_blocks(tmp_path):
     # and the kernel goes by it
     text = open(os.path.join(CSRC, "summarize.h")).read()
     body = text[text.index("void summarize_small("):]
-    assert body.count("load_stream(") == 1 and "row_below(t0 + x * RPP + rsub, L, end, N * RPP)" in body[body.index("load_stream("):]
+    assert body.count("load_keys<") == 1 and "row_below(t0 + x * RPP + rsub, L, end, N * RPP)" in body[body.index("load_keys<"):]
