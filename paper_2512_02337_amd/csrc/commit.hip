@@ -419,25 +419,28 @@ __global__ __launch_bounds__(256) void gather_blocks_kernel(const int32_t *sel_i
     if (nb > s.max_blocks) nb = s.max_blocks;
     if (blockIdx.x == 0) {
         if (g || !out_len) return;
-        // a wavefront takes every fourth head, four of them and 64 entries of each at a time, counts and entries together: head by head and
+        // 64 entries of a head at a time, a wavefront every fourth of those, four of them together, counts and entries: head by head and
         // count by count this workgroup was what a small gather waited for: a layer in a graph, 8 KV heads of 128 channels, 13 blocks of 64 3.90 -> 3.28 us,
-        // 32 5.48 -> 4.97, 64 of 16 4.71 -> 3.81
+        // 32 5.48 -> 4.97, 64 of 16 4.71 -> 3.81.  With whole heads dealt to the wavefronts, one head left three of them idle: 161 blocks of 24 3.36 -> 2.92,
+        // two sequences of 475 of 16, 64 channels, 4.95 -> 3.19.
         int rows = 0;
         const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        for (int h0 = wave; h0 < s.Hkv; h0 += 16) {
-            for (int slot0 = 0; slot0 < n_sel; slot0 += 64) {
-                const int slot_e = slot0 + lane;
-                int cnt[4], entry[4];
+        const int pieces = (n_sel + 63) >> 6;   // of a head's entries
+        int h = 0, piece = wave;                // (what the wavefront takes next; the counters go on without a division)
+        while (h < s.Hkv) {
+            int cnt[4], entry[4], at_slot[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int64_t row = (int64_t)b * s.Hkv + min(h0 + 4 * u, s.Hkv - 1);   // (past the last head: that one again)
-                    cnt[u] = sel_count[row + zero];
-                    entry[u] = sel_idx[row * n_sel + min(slot_e, n_sel - 1)];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u)   // token rows up to and including this block
-                    if (slot_e < min(cnt[u], n_sel) && entry[u] >= 0 && entry[u] < nb) rows = max(rows, slot_e * s.B + min(s.B, L - entry[u] * s.B));
+            for (int u = 0; u < 4; ++u) {
+                while (piece >= pieces && h < s.Hkv) { piece -= pieces; ++h; }
+                const int64_t row = (int64_t)b * s.Hkv + min(h, s.Hkv - 1);   // (past the last head: nothing)
+                at_slot[u] = h < s.Hkv ? 64 * piece + lane : n_sel;
+                cnt[u] = sel_count[row + zero];
+                entry[u] = sel_idx[row * n_sel + min(at_slot[u], n_sel - 1)];
+                piece += 4;
             }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)   // token rows up to and including this block
+                if (at_slot[u] < min(cnt[u], n_sel) && entry[u] >= 0 && entry[u] < nb) rows = max(rows, at_slot[u] * s.B + min(s.B, L - entry[u] * s.B));
         }
         __shared__ int most[4];
         for (int off = 32; off; off >>= 1) rows = max(rows, __shfl_xor(rows, off));

@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("D,Hkv,B,lengths,n_sel", [
     (128, 8, 64, [1000], 9), (128, 2, 16, [1, 513, 300], 5), (64, 1, 24, [200, 77], 1), (128, 3, 80, [0, 401], 6), (64, 8, 129, [1290], 12),
     (128, 8, 64, [1500], 64), (128, 8, 61, [900], 63),   # four passes to a workgroup
+    (64, 1, 16, [300, 900], 475), (128, 3, 8, [500], 1030), (128, 1, 16, [200], 64), (64, 5, 16, [333], 129), (128, 19, 4, [90], 300),   # pieces of 64 entries dealt to four wavefronts
     (64, 20, 16, [300], 70),                              # more heads and entries than are looked at in one go for the length
     (64, 8, 16, [700, 5], 160)])                          # more workgroups than have a place at once
 def test_gather_edges(gpu_lib, dtype, D, Hkv, B, lengths, n_sel):
