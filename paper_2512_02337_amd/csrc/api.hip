@@ -150,14 +150,15 @@ struct AttnCost {
     // costs above choose, the chain that splits have more over the shares of the long pair, against the slowest of equal lengths, 1 / n
     // to n / n, one long first and one long last, splits / shares: up to 0.09 us a share (41 shapes) 1.02 at most, 0.82 in the mean;
     // 0.1 to 0.2: 0.9 to 1.38; 0.2 to 0.5: up to 1.44; beyond: up to 1.55.
-    // The group kernel's splits gain elsewhere too: up to four sequences have nine chunks in hand (8 heads, 60 nodes at G = 5, two of 5000 0.79, three
-    // of 4100 0.89, two of 18K, seventeen chunks more, 1.05), and where there are more pairs than shares, most of which then run through
-    // several, two partials of a pair beyond them (64 sequences of 1300, 64 nodes 0.81, 0.49, 0.82, 0.90).
+    // The group kernel's splits gain elsewhere too: up to four sequences have eleven chunks and a half in hand (130 shapes, refreshes, splits / shares: up to
+    // there equal lengths 0.77 to 1.0, 0.84 in the mean, 1 / n to n / n 0.75 to 1.0, one long 0.70 to 1.05, long last 0.59 to 1.0; where the lengths happen to divide into whole
+    // shares, one long up to 1.2, a few tokens beside them 1.0: four of 3269 / 3200, 37 nodes at G = 5, 28.2 / 24.3, 29.3 / 29.3 us; four of 8192, 22 chunks, 1.23 at any
+    // length), and where there are more pairs than shares, most of which then run through several, two partials of a pair beyond them (64 sequences of 1300, 64 nodes 0.81, 0.49, 0.82, 0.90).
     bool splits_hold(double p, double chunk_us, int blocks, int64_t wgs, bool group) const
     {
         const double of_share = (double)s.Hkv * (double)chunks * (1.0 + (double)(s.batch - 1) / 16.0) / (double)wgs, share = of_share < 1.0 ? 1.0 : of_share;
         const double more = p * chunk_us - share * attn_group_chunk_us(blocks), merged = 0.09 * (double)chunks / share;
-        const double beyond = (double)s.batch * s.Hkv - (double)wgs, pairs = group && beyond > 0.0 ? beyond * s.M * s.G * 528e-6 : 0.0, hand = group && s.batch <= 4 ? 9.0 * chunk_us : 0.0;
+        const double beyond = (double)s.batch * s.Hkv - (double)wgs, pairs = group && beyond > 0.0 ? beyond * s.M * s.G * 528e-6 : 0.0, hand = group && s.batch <= 4 ? 11.5 * chunk_us : 0.0;
         return more <= (merged > hand ? merged : hand) + pairs;
     }
 };
@@ -182,7 +183,7 @@ static int64_t first_splits(const Shape &s, int64_t chunks, int64_t cus)
 
 // The array of specpv_partial_verify_attn_static.  Larger than the SPECPV_STATIC_SCRATCH_BYTES by which it takes calls, so that no
 // plan has to be cut to those: every call runs the plan that the static one would.  Cut to 16 MiB / as it is now: refresh, fp32, 37
-// nodes at G = 4, 16K, 8 KV heads, 26 / 32 splits 179 / 151 us; full pass, 64 channels, 15005 and 30011 tokens, 25 / 32 splits 55.7 / 48.9.
+// nodes at G = 4, 16K, 8 KV heads, 26 / 32 splits 175 / 146 us; full pass, 64 channels, 15005 and 30011 tokens, 25 / 32 splits 52.7 / 46.6.
 constexpr int64_t kStaticArray = 64 << 20;
 
 // Bytes of a partial row: O as fp16 (bf16 at 128 channels) or fp32, and the (m, l) pair.

@@ -13,8 +13,8 @@
 // What bounds it: the matrix instructions of the wavefronts that share a SIMD (64 % of the time busy at 37 nodes and 16K tokens), rows
 // that fill up a workgroup's 64, and for small calls a chunk's trip.  Read straight from memory, as in attn_generic.hip, a K operand
 // touches 64 bytes of sixteen rows, which a CU takes in at a third of the rate of whole lines, once per tile.  Refresh, fp32, 37 nodes at
-// G = 4, 16K tokens: 8 KV heads of 128 channels 258 -> 148 us, of 64 117 -> 82; six sequences of 1137, 2 heads 58 -> 39.5 (with their scores by way of LDS too); 30 nodes, one head of
-// 64, 4K 21.8 -> 15.0.  Two partial steps over 4K tokens of 8 heads, 128 channels, 60 nodes 161 -> 120, 12 nodes 80 -> 55.  Workgroups
+// G = 4, 16K tokens: 8 KV heads of 128 channels 239 -> 150 us, of 64 118 -> 82; six sequences of 1137, 2 heads 59 -> 41 (with their scores by way of
+// LDS too).  A partial step over 4K tokens of 8 heads, 128 channels, 60 nodes 81 -> 55, 12 nodes 40 -> 28.  Workgroups
 // of five to sixteen wavefronts, which read less, are slower (60 nodes, 16K: 173 with four, 174 with eight, 270 with five).
 #include "internal.h"
 

@@ -40,13 +40,13 @@ def room_of_shares(batch, Hkv, G, M, shares, D=128):
 @cpu_only
 @pytest.mark.parametrize("batch,Hkv,G,M,ctx,shares", [
     (16, 8, 5, 60, 3000, 256), (16, 8, 4, 60, 2048, 256), (10, 8, 4, 60, 4096, 256), (4, 8, 4, 60, 8192, 256), (8, 1, 4, 60, 32768, 256), (8, 1, 8, 37, 49152, 256),
-    (4, 2, 4, 60, 32768, 256), (5, 4, 8, 60, 8000, 128), (16, 1, 4, 60, 24321, 256), (32, 1, 8, 24, 5746, 256), (3, 8, 5, 37, 12000, 256), (8, 2, 4, 37, 23722, 256)])
+    (4, 2, 4, 60, 32768, 256), (5, 4, 8, 60, 8000, 128), (16, 1, 4, 60, 24321, 256), (32, 1, 8, 24, 5746, 256), (3, 8, 5, 37, 12000, 256), (8, 2, 4, 37, 23722, 256), (4, 8, 4, 46, 5400, 256)])
 def test_shares_where_one_long_sequence_would_wait_for_itself(batch, Hkv, G, M, ctx, shares):
     assert splits_asked_for(batch, Hkv, G, M, ctx) == room_of_shares(batch, Hkv, G, M, shares)
 
 
 @cpu_only
-@pytest.mark.parametrize("batch,Hkv,G,M,ctx", [(3, 4, 4, 37, 7055), (2, 2, 8, 24, 57746), (16, 1, 8, 37, 4710), (2, 2, 8, 37, 30000)])
+@pytest.mark.parametrize("batch,Hkv,G,M,ctx", [(3, 4, 4, 37, 7055), (2, 2, 8, 24, 57746), (16, 1, 8, 37, 4710), (2, 2, 8, 37, 30000), (4, 8, 4, 46, 3480), (3, 8, 4, 60, 4400)])
 def test_splits_where_their_chains_are_short(batch, Hkv, G, M, ctx):
     assert splits_asked_for(batch, Hkv, G, M, ctx) > room_of_shares(batch, Hkv, G, M, 256)
 
