@@ -557,7 +557,7 @@ static int run_attention(const Shape &s_in, const AttnPlan &plan, int dtype, con
     else if (plan.tg) e = launch_attn_ctx_f32(s, sel_idx, sel_count, n_sel, p, st);
     else e = launch_attn_ctx_generic(s, dtype, sel_idx, sel_count, n_sel, p, st);
     if (e != hipSuccess) return fail_hip(e);
-    if (tail && (tail->scores || tail->all) && refresh_tail_supported(s, dtype, p, tail->kind) && (!tail->scores || refresh_tail_pays(s, tail->reduce, tail->last_node))) {
+    if (tail && (tail->scores || tail->all) && refresh_tail_supported(s, dtype, p, tail->kind) && (!tail->scores || refresh_tail_pays(s, p, tail->reduce, tail->last_node))) {
         e = launch_refresh_tail(s, p, out, lse, tail->kmax, tail->kmin, tail->reduce, tail->last_node, tail->scores, tail->all, st);
         tail->done = true;
     } else {

@@ -315,7 +315,7 @@ bool combine_packed(const Shape &s, int dtype);
 // the merge and the scores (eq. 2; scores == nullptr: none) in one launch; kind: as for launch_scores.  all != nullptr: and lists of
 // every block (launch_list_all)
 bool refresh_tail_supported(const Shape &s, int dtype, const Partials &p, int kind);
-bool refresh_tail_pays(const Shape &s, int reduce, int last_node);   // (with scores)
+bool refresh_tail_pays(const Shape &s, const Partials &p, int reduce, int last_node);   // (with scores)
 hipError_t launch_refresh_tail(const Shape &s, Partials p, void *out, float *lse, const void *kmax, const void *kmin, int reduce, int last_node,
                                float *scores, const TopkArgs *all, hipStream_t st);
 // to_cache != 0: pending + accepted rows go to the cache tail (lengths, summaries updated);

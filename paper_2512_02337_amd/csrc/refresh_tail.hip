@@ -85,18 +85,20 @@ bool refresh_tail_supported(const Shape &s, int dtype, const Partials &p, int ki
            s.max_blocks <= 32 * 60000 && (int64_t)s.batch * s.Hkv <= 8 * 65535 && !draft_rows_wide(s, sizeof(uint16_t));
 }
 
-// Where the merge alone has eighteen fours of rows for every CU and there is little to score, the merge's workgroups pay more for the LDS and
-// the wavefronts of the scoring ones than a launch costs.  Whole refreshes of 81 shapes (1 to 32 sequences) with up to 4096 blocks of 32 query
-// rows times tiles of 32 blocks to score, apart / together, equal lengths and one long, means: 18 to 31 fours a CU 0.93 / 1.00, 0.94 / 1.00 (16
-// sequences of 12K, 24 nodes at G = 8 131 us 0.91 / 0.98, 0.86 / 0.99); 11 to 18 0.98 / 0.99, 1.02 / 1.00; eight to 11 1.00 / 1.00, 1.04 / 0.99 (11 of
-// 6300, 60 nodes, 4 heads 1.01 / 0.99, 1.10 / 1.00).  With more to score, 4480 / 4800 / 5120 / 7680: 0.92 / 0.99, 0.99 / 0.99, 0.96 / 0.99, 1.01 / 1.01;
-// 20480: tail 28.2 / 10.9 + 24.5 us.
-bool refresh_tail_pays(const Shape &s, int reduce, int last_node)
+// Where the merge alone has so many fours of rows for every CU and there is little to score, the merge's workgroups pay more for the LDS and
+// the wavefronts of the scoring ones than a launch costs; how many, follows from how long a four takes.  Whole refreshes of 150 shapes (1 to 32
+// sequences) with up to 4096 blocks of 32 query rows times tiles of 32 blocks to score, apart / together, equal lengths, 1 / n to n / n, one long, means
+// by fours a CU.  128 channels, splits: 6 to 8 1.01, 1.02, 1.03; 8 to 11 0.98, 0.98, 1.01 (4 of 3480 by quarters, 66 nodes at G = 4 43.8 / 46.6 us);
+// 14 to 18 0.93, 0.93, 0.96.  Shares, whose places are found by the lengths: 8 to 14 1.00, 1.00, 1.04; 14 to 18 0.95, 0.95, 0.97; beyond 24 0.91,
+// 0.92, 0.93.  64 channels, whose partials are twice the bytes: 14 to 18 1.01, 1.02, 1.02; 18 to 24 0.99, 1.00, 0.99; beyond 0.92, 0.92, 0.89.  With more to
+// score, 4480 / 4800 / 5120 / 7680: 0.92 / 0.99, 0.99 / 0.99, 0.96 / 0.99, 1.01 / 1.01; 20480: tail 28.2 / 10.9 + 24.5 us.
+bool refresh_tail_pays(const Shape &s, const Partials &p, int reduce, int last_node)
 {
     const bool pack = combine_packed(s, SPECPV_BF16);
     const ScoreArgs a = score_plan(s, nullptr, nullptr, reduce, last_node, nullptr, false);
     const int64_t pairs = (int64_t)s.batch * s.Hkv, fours = pairs * (pack ? (s.M * s.G + 3) / 4 : s.M * ((s.G + 3) / 4));
-    return fours < 18 * (int64_t)device_cu_count() || (int64_t)((a.rows - a.row0 + 31) / 32) * ((s.max_blocks + 31) / 32) * pairs > 4096;
+    const int64_t line = s.D == 64 ? 18 : (p.stream ? 14 : 8);
+    return fours < line * (int64_t)device_cu_count() || (int64_t)((a.rows - a.row0 + 31) / 32) * ((s.max_blocks + 31) / 32) * pairs > 4096;
 }
 
 hipError_t launch_refresh_tail(const Shape &s, Partials p, void *out, float *lse, const void *kmax, const void *kmin, int reduce, int last_node,

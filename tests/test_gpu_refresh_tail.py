@@ -19,7 +19,7 @@ CASES = [  # (over, reducer)
     (dict(ctx=[100], M=1, Hq=8, Hkv=8), "mean"), (dict(ctx=[700], M=24), "max"), (dict(ctx=[3000], M=60, Hq=32, Hkv=8), "last"),
     (dict(ctx=[9001], M=60, Hq=32, Hkv=8), "mean"), (dict(ctx=[20000], M=78, Hq=32, Hkv=8, B=64), "mean"), (dict(ctx=[33000], M=60, Hq=32, Hkv=8), "max"),
     (dict(ctx=[4000], M=60, Hq=40, Hkv=8), "mean"), (dict(ctx=[9000, 200, 5000], M=60, Hq=40, Hkv=8), "mean"), (dict(ctx=[9000, 0, 5000], M=60, Hq=32, Hkv=8), "last"),
-    (dict(ctx=[5000], M=128, Hq=32, Hkv=2), "mean"), (dict(ctx=[5000], M=3, Hq=48, Hkv=3), "mean"), (dict(ctx=[2000] * 5, M=17, Hq=6, Hkv=3), "max"),
+    (dict(ctx=[3480, 2610, 1740, 870], M=66, Hq=32, Hkv=8, B=64), "max"), (dict(ctx=[5000], M=128, Hq=32, Hkv=2), "mean"), (dict(ctx=[5000], M=3, Hq=48, Hkv=3), "mean"), (dict(ctx=[2000] * 5, M=17, Hq=6, Hkv=3), "max"),
     (dict(ctx=[6000, 3000], M=37, Hq=32, Hkv=8, D=64), "mean"), (dict(ctx=[900], M=5, Hq=10, Hkv=2, D=64), "last"), (dict(ctx=[12000], M=64, Hq=16, Hkv=4, D=64), "max")]
 
 
